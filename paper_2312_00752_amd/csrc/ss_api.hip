@@ -268,6 +268,8 @@ bool scan_fwd_fusable(const ss_fwd_params* p, int R)
     if (!p || p->seqlen < 1 || p->io_dtype != SS_BF16 || !stageable(p) || slots(p) > 16) return false;
     if (R < 8 || R % 8 != 0 || R > 256 || (p->flags & SS_EXACT_ZOH_B)) return false;
     if (p->seqlen % 8 != 0 || (size_t)p->seqlen * 64 * sizeof(float) >= ((size_t)1 << 31)) return false;
+    // eight states or fewer are dealt out to kernels of one or two slots per lane, which are built without the projection
+    if (slots(p) <= 8) return false;
     if (plan_segments(p->batch, p->dim, p->seqlen, p->flags).nseg != 1) return false;
     return p->workspace && aligned(p->workspace, 256) &&
            p->workspace_bytes >= ws_layout(p, (p->flags & SS_SAVE_FOR_BWD) != 0).total;

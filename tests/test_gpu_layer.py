@@ -92,6 +92,15 @@ def test_layer_full_size_bf16():
 # bf16 shapes with D % 32 == 0 and R % 8 == 0 take the hand-written matrix-core decode path (ragged
 # batch tiles of 8 and of 16, ragged 64-channel groups, N below 16, R off and at the limits of the 32-wide
 # contraction steps); the others take the library GEMMs
+@pytest.mark.parametrize("dstate", [1, 4, 8, 9])
+def test_layer_few_states_on_an_unsplit_sequence(dstate):
+    """Up to eight states run on kernels that read delta from memory: the layer must have written it."""
+    w = make_layer_inputs(5, 72, 320, dstate, "bf16", seed=dstate, rank=64)
+    out, _ = _gpu(w, backward=False)
+    ref = inn.inner_fwd(rnd=_rnd("bf16"), nthreads=0, **{k: w[k] for k in PARAMS})
+    assert_close(out, ref["out"], "bf16", "out", exact_inputs=False)
+
+
 @pytest.mark.parametrize("io,shape", [("bf16", (4, 96, 256, 16, 8)), ("f32", (2, 40, 72, 5, 3)), ("bf16", (1, 33, 128, 16, 6)),
                                       ("bf16", (21, 40, 96, 8, 40)), ("bf16", (1, 20, 64, 16, 256)),
                                       ("bf16", (17, 24, 160, 12, 24)), ("bf16", (3, 20, 32, 16, 16)),
