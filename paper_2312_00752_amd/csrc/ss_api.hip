@@ -186,9 +186,9 @@ int check_fwd(const ss_fwd_params* p, bool for_bwd, bool bc_dense = true)
 
 // Whether a pass over fewer than 16 states deals them out to the waves in turn (FwdArgs::il): the
 // common path only.  Forward and backward call derive it from the same arguments.
-inline bool deals_states(int vec_ok, uint32_t flags)
+inline bool deals_states(int dpp_ok, uint32_t flags)
 {
-    return vec_ok && !(flags & (SS_EXACT_ZOH_B | SS_B_FIXED | SS_C_FIXED | SS_COMPLEX_STATE));
+    return dpp_ok && !(flags & (SS_EXACT_ZOH_B | SS_B_FIXED | SS_C_FIXED | SS_COMPLEX_STATE));
 }
 
 ss::FwdArgs make_fwd_args(const ss_fwd_params* p, long bc_bstride)
@@ -198,8 +198,10 @@ ss::FwdArgs make_fwd_args(const ss_fwd_params* p, long bc_bstride)
     a.acc_y = 0;
     a.flags = p->flags;
     // 16-byte slices, addressed through per-workgroup buffer resources (64 rows, 31-bit offsets)
-    a.vec_ok = p->seqlen % 8 == 0 && (size_t)p->seqlen * 64 * sizeof(float) < ((size_t)1 << 31);
-    a.il = deals_states(a.vec_ok, p->flags) && a.N < 16;
+    a.ld_ud = p->seqlen; a.ld_bc = p->seqlen;
+    a.dpp_ok = p->seqlen >= 8 && (size_t)p->seqlen * 64 * sizeof(float) < ((size_t)1 << 31);
+    a.vec_ok = a.dpp_ok && p->seqlen % 8 == 0;
+    a.il = deals_states(a.dpp_ok, p->flags) && a.N < 16;
     a.u = p->u; a.delta = p->delta; a.z = (p->flags & SS_HAS_Z) ? p->z : nullptr;
     a.Bm = p->Bmat; a.Cm = p->Cmat; a.A = p->A;
     a.bc_bstride = bc_bstride;
@@ -227,7 +229,7 @@ void narrow_to_group(ss::FwdArgs& a, const ss_fwd_params* p, int g, size_t ckpt_
     const int n0 = g * 16;
     const size_t esz = p->io_dtype == SS_BF16 ? 2 : 4;
     a.N = slots(p) - n0 < 16 ? slots(p) - n0 : 16;
-    a.il = deals_states(a.vec_ok, p->flags) && a.N < 16;
+    a.il = deals_states(a.dpp_ok, p->flags) && a.N < 16;
     a.A = at(a.A, n0);
     a.h0 = at(a.h0, n0);
     a.h_last = at(a.h_last, n0);
@@ -261,13 +263,13 @@ int static_scratch(void** out)
 
 namespace ss {
 
-// The fused projection exists for the plain bf16 kernel on an unsplit sequence of whole 8-step
-// slices, with a workspace for the repacked operands.
+// The fused projection exists for the plain bf16 kernel on an unsplit sequence of at least 8 steps,
+// with a workspace.
 bool scan_fwd_fusable(const ss_fwd_params* p, int R)
 {
     if (!p || p->seqlen < 1 || p->io_dtype != SS_BF16 || !stageable(p) || slots(p) > 16) return false;
     if (R < 8 || R % 8 != 0 || R > 256 || (p->flags & SS_EXACT_ZOH_B)) return false;
-    if (p->seqlen % 8 != 0 || (size_t)p->seqlen * 64 * sizeof(float) >= ((size_t)1 << 31)) return false;
+    if (p->seqlen < 8 || (size_t)p->seqlen * 64 * sizeof(float) >= ((size_t)1 << 31)) return false;
     // eight states or fewer are dealt out to kernels of one or two slots per lane, which are built without the projection
     if (slots(p) <= 8) return false;
     if (plan_segments(p->batch, p->dim, p->seqlen, p->flags).nseg != 1) return false;
@@ -287,10 +289,10 @@ static int scan_fwd_impl(const ss_fwd_params* p, long bc_bstride, const void* W_
     char* ws = static_cast<char*>(p->workspace);
     const int groups = p->seqlen == 0 ? 1 : (slots(p) + 15) / 16;
     size_t ckpt_group = 0;
-    // the repacked copy serves the scalar path only: sequences of whole 16-byte pieces stage B and C through LDS instead
+    // the repacked copy serves the scalar path only: the other kernels stage B and C through LDS instead
     auto stage = [&](const WsLayout& w) {
         a.Lp = w.Lp;
-        if (a.vec_ok) return true;
+        if (a.dpp_ok) return true;
         if (ss::launch_stage_bc(a, ws + w.bcs_off, p->io_dtype, static_cast<hipStream_t>(stream)) != 0) return false;
         a.bcs = ws + w.bcs_off;
         return true;

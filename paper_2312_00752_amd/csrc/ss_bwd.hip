@@ -532,7 +532,9 @@ struct BwdSmemDpp {
 // where g dphi/dA = (abar g dt - g phi)/A needs neither a division nor dphi itself.  That difference cancels
 // like dt A / 2 and so magnifies phi's own rounding error by 2 / |dt A|: below |dt A| = 2^-4 (and for A = 0)
 // the term is g dt^2 (1/2 + x/3 + x^2/8) instead.
-template <typename T, int SPL, bool ZOH = false>
+// RAG: rows of any length >= 8 and any pitch (see scan_fwd_kernel).  Slices are read at element alignment from
+// inside the row and shifted into place, and rows past D cleared, in the blocks that need it only.
+template <typename T, int SPL, bool ZOH = false, bool RAG = false>
 __global__ void __launch_bounds__(THREADS, ZOH ? 1 : 2) scan_bwd_dpp_kernel(const BwdArgs a)
 {
     extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
@@ -577,6 +579,18 @@ __global__ void __launch_bounds__(THREADS, ZOH ? 1 : 2) scan_bwd_dpp_kernel(cons
     const rsrc_t bbc_ = make_rsrc(static_cast<const T*>(s_which ? f.Cm : f.Bm) + (long)b * f.bc_bstride,
                                   (uint32_t)N * (uint32_t)L * (uint32_t)sizeof(T));
     const uint32_t bc_row_off = s_n < N ? (uint32_t)s_n * (uint32_t)L * (uint32_t)sizeof(T) : BUF_OFF;
+    // RAG: plain pointers to the workgroup's first row and offsets of this thread's row, clamped to a valid one
+    const uint32_t esz = (uint32_t)sizeof(T);
+    const int r_row = min(pr, rows_here - 1);
+    const uint32_t r_off = (uint32_t)r_row * (uint32_t)L * esz, r_off_ud = (uint32_t)r_row * (uint32_t)f.ld_ud * esz;
+    const uint32_t r_off_bc = (uint32_t)min(s_n, N - 1) * (uint32_t)f.ld_bc * esz;
+    const long wg_ud = ((long)b * f.D + d0) * f.ld_ud;
+    const T* const ru_p = static_cast<const T*>(f.u) + wg_ud;
+    const T* const rd_p = static_cast<const T*>(f.delta) + wg_ud;
+    const T* const ro_p = static_cast<const T*>(a.dout) + wg_first;
+    const T* const rz_p = has_z ? static_cast<const T*>(f.z) + wg_first : ro_p;
+    const T* const ry_p = has_z ? static_cast<const T*>(f.ysave) + wg_first : ro_p;
+    const T* const rbc_p = static_cast<const T*>(s_which ? f.Cm : f.Bm) + (long)b * f.bc_bstride;
 
     // ---- state view: lane -> row, wave -> states 4w..4w+3 --------------------------------
     const bool s_ok = d0 + lane < f.D;
@@ -614,6 +628,22 @@ __global__ void __launch_bounds__(THREADS, ZOH ? 1 : 2) scan_bwd_dpp_kernel(cons
         for (int s = 0; s < LG; ++s) {
             const int blk = grp * LG + s;
             const int t0 = blk * BT + pq * BSL;
+            if constexpr (RAG) {
+                const uint32_t t = (uint32_t)row_piece(t0, BSL, L) * esz;
+                ru[s] = io4<T>::load_elem(ru_p, r_off_ud + t);
+                rd[s] = io4<T>::load_elem(rd_p, r_off_ud + t);
+                ro[s] = io4<T>::load_elem(ro_p, r_off + t);
+                rz[s] = io4<T>::load_elem(rz_p, has_z ? r_off + t : 0u);
+                ry[s] = io4<T>::load_elem(ry_p, has_z ? r_off + t : 0u);
+                const uint32_t tb = r_off_bc + (uint32_t)row_piece(blk * BT + 2 * s_tp, 2, L) * esz;
+                if constexpr (sizeof(T) == 2) {
+                    rbc[s] = load_any<uint32_t>(rbc_p, tb);
+                } else {
+                    const u32x2 x = load_any<u32x2>(rbc_p, tb);
+                    rbc[s] = make_uint2(x[0], x[1]);
+                }
+                continue;
+            }
             // slices are whole or empty; rows past D lie beyond the resource
             const uint32_t off = t0 < L ? row_off + (uint32_t)t0 * (uint32_t)sizeof(T) : BUF_OFF;
             ru[s] = io4<T>::load_buf(bu_, off);
@@ -633,12 +663,23 @@ __global__ void __launch_bounds__(THREADS, ZOH ? 1 : 2) scan_bwd_dpp_kernel(cons
     // the 64-byte neighbourhood are written back to back.
     typename io4<T>::packed keep_du{}, keep_dl{}, keep_dz{};
     uint32_t keep_off = BUF_OFF;
+    bool keep_live = false;   // RAG: something waits
     auto store_paired = [&](rsrc_t rs, uint32_t off, typename io4<T>::packed now, typename io4<T>::packed& keep, bool odd) {
         if constexpr (LG == 2) {
             if (odd) { keep = now; return; }
             io4<T>::store_packed(rs, keep_off, keep);   // switched off when nothing waits
         }
         io4<T>::store_packed(rs, off, now);
+    };
+    // RAG: the same at element alignment; off of the present block's slice, nv of its steps inside the row (0 for rows past D)
+    auto store_paired_rag = [&](void* base, long first, uint32_t off, int t0, int nv, typename io4<T>::packed now,
+                                typename io4<T>::packed& keep, bool odd) {
+        T* const p = static_cast<T*>(base) + first;
+        if constexpr (LG == 2) {
+            if (odd) { keep = now; return; }
+            if (keep_live) io4<T>::store_elem(p, off + BT * esz, keep, p_ok ? min(max(L - (t0 + BT), 0), BSL) : 0);
+        }
+        io4<T>::store_elem(p, off, now, nv);
     };
 
     auto load_ckpt = [&](int blk) {
@@ -650,6 +691,7 @@ __global__ void __launch_bounds__(THREADS, ZOH ? 1 : 2) scan_bwd_dpp_kernel(cons
         const int t0 = tc + pq * BSL;
         const bool live = p_ok && t0 < L;
         const uint32_t off = t0 < L ? row_off + (uint32_t)t0 * (uint32_t)sizeof(T) : BUF_OFF;
+        const int nv = p_ok ? min(max(L - t0, 0), BSL) : 0;   // RAG: steps of the slice inside the row
         // the state entering this block was requested a block ago (see scan_bwd_kernel)
         const float4 hck4 = hck_next;
         if (blk > blk_begin) hck_next = load_ckpt(blk - 1);
@@ -661,6 +703,20 @@ __global__ void __launch_bounds__(THREADS, ZOH ? 1 : 2) scan_bwd_dpp_kernel(cons
             float z4[BSL], y4[BSL];
             bcpair_t bcw{};
             const int slot = blk & (LG - 1);  // uniform
+            if constexpr (RAG) {
+                if (tc + BT > L || rows_here < ROWS) {   // uniform
+                    const int sh = p_ok ? t0 - row_piece(t0, BSL, L) : BSL, ts = tc + 2 * s_tp;
+                    const int shb = ts - row_piece(ts, 2, L);
+#pragma unroll
+                    for (int s = 0; s < LG; ++s)
+                        if (slot == s) {
+                            io4<T>::drop(ru[s], sh); io4<T>::drop(rd[s], sh); io4<T>::drop(ro[s], sh);
+                            io4<T>::drop(rz[s], sh); io4<T>::drop(ry[s], sh);
+                            if constexpr (sizeof(T) == 2) rbc[s] = shb == 0 ? rbc[s] : (shb == 1 ? rbc[s] >> 16 : 0u);
+                            else rbc[s] = shb == 0 ? rbc[s] : (shb == 1 ? make_uint2(rbc[s].y, 0u) : make_uint2(0u, 0u));
+                        }
+                }
+            }
 #pragma unroll
             for (int s = 0; s < LG; ++s) {  // unrolled so the register arrays stay statically indexed
                 if (slot == s) {
@@ -679,6 +735,7 @@ __global__ void __launch_bounds__(THREADS, ZOH ? 1 : 2) scan_bwd_dpp_kernel(cons
                 const float x = v4[j] + bias_eff;
                 float sp, sg;
                 if (softplus) softplus_sigmoid(x, sp, sg); else { sp = x; sg = sg_lin; }
+                if constexpr (RAG) { sp = j < nv ? sp : 0.0f; sg = j < nv ? sg : 0.0f; }   // a slice may be partly inside
                 dt4[j] = sp;
                 sg4[j] = sg;
                 du4[j] = ZOH ? u4[j] : sp * u4[j];
@@ -693,7 +750,11 @@ __global__ void __launch_bounds__(THREADS, ZOH ? 1 : 2) scan_bwd_dpp_kernel(cons
                     dy4[j] = o4[j] * zs;
                     dz4[j] = (o4[j] * y4[j]) * fmaf(zs, 1.0f - s, s);   // dout y d[z sigmoid(z)]/dz
                 }
-                store_paired(bdz_, off, io4<T>::pack(dz4), keep_dz, blk & 1);   // switched off for all but the first state group
+                if constexpr (RAG) {
+                    if (a.dz) store_paired_rag(a.dz, wg_first, r_off + (uint32_t)t0 * esz, t0, nv, io4<T>::pack(dz4), keep_dz, blk & 1);
+                } else {
+                    store_paired(bdz_, off, io4<T>::pack(dz4), keep_dz, blk & 1);   // switched off for all but the first state group
+                }
             }
             *reinterpret_cast<float4*>(&sm.dt[pr][pq * BSL]) = make_float4(dt4[0], dt4[1], dt4[2], dt4[3]);
             *reinterpret_cast<float4*>(&sm.du[pr][pq * BSL]) = make_float4(du4[0], du4[1], du4[2], du4[3]);
@@ -701,6 +762,7 @@ __global__ void __launch_bounds__(THREADS, ZOH ? 1 : 2) scan_bwd_dpp_kernel(cons
             float2 bc2;
             if constexpr (sizeof(T) == 2) bc2 = make_float2(bf16_lo(bcw), bf16_hi(bcw));
             else bc2 = make_float2(__uint_as_float(bcw.x), __uint_as_float(bcw.y));
+            if constexpr (RAG) bc2 = s_n < N ? bc2 : make_float2(0.0f, 0.0f);   // slots without a state
             *reinterpret_cast<float2*>(&sm.bcp[s_which][s_tp >> 1][s_n][(s_tp & 1) * 2]) = bc2;
         }
         if ((blk & (LG - 1)) == 0 && blk > blk_begin) issue_group(blk / LG - 1);  // in flight during the sweeps below
@@ -847,14 +909,31 @@ __global__ void __launch_bounds__(THREADS, ZOH ? 1 : 2) scan_bwd_dpp_kernel(cons
             }
             if (a.acc) {  // states beyond the first 16: add to the earlier groups' du and ddelta
                 float pu[BSL], pl[BSL];
-                io4<T>::unpack(io4<T>::load_buf(bdu_, off), pu);
-                io4<T>::unpack(io4<T>::load_buf(bdd_, off), pl);
+                if constexpr (RAG) {
+                    const int tp = row_piece(t0, BSL, L);
+                    typename io4<T>::raw xu = io4<T>::load_elem(static_cast<const T*>(a.du) + wg_ud, r_off_ud + (uint32_t)tp * esz);
+                    typename io4<T>::raw xl = io4<T>::load_elem(static_cast<const T*>(a.ddelta) + wg_ud, r_off_ud + (uint32_t)tp * esz);
+                    io4<T>::drop(xu, t0 - tp);
+                    io4<T>::drop(xl, t0 - tp);
+                    io4<T>::unpack(xu, pu);
+                    io4<T>::unpack(xl, pl);
+                } else {
+                    io4<T>::unpack(io4<T>::load_buf(bdu_, off), pu);
+                    io4<T>::unpack(io4<T>::load_buf(bdd_, off), pl);
+                }
 #pragma unroll
                 for (int j = 0; j < BSL; ++j) { du4[j] += pu[j]; dl4[j] += pl[j]; }
             }
-            store_paired(bdu_, off, io4<T>::pack(du4), keep_du, blk & 1);
-            store_paired(bdd_, off, io4<T>::pack(dl4), keep_dl, blk & 1);
-            if constexpr (LG == 2) keep_off = (blk & 1) ? off : BUF_OFF;
+            if constexpr (RAG) {
+                const uint32_t off_ud = r_off_ud + (uint32_t)t0 * esz;
+                store_paired_rag(a.du, wg_ud, off_ud, t0, nv, io4<T>::pack(du4), keep_du, blk & 1);
+                store_paired_rag(a.ddelta, wg_ud, off_ud, t0, nv, io4<T>::pack(dl4), keep_dl, blk & 1);
+                if constexpr (LG == 2) keep_live = blk & 1;
+            } else {
+                store_paired(bdu_, off, io4<T>::pack(du4), keep_du, blk & 1);
+                store_paired(bdd_, off, io4<T>::pack(dl4), keep_dl, blk & 1);
+                if constexpr (LG == 2) keep_off = (blk & 1) ? off : BUF_OFF;
+            }
         }
     }
 
@@ -1003,8 +1082,8 @@ __global__ void __launch_bounds__(THREADS) adjoint_agg_kernel(const BwdArgs a)
 // The adjoint aggregate on the common path (real state, selective C, L % 8 == 0): as
 // adjoint_agg_kernel, with the chunk's C staged through an LDS tile and taken as a quad-broadcast
 // DPP operand (see scan_bwd_dpp_kernel), buffer-addressed inputs requested two chunks ahead into
-// compile-time slots, and no scalar loads.
-template <typename T, int SPL>
+// compile-time slots, and no scalar loads.  RAG: rows of any length >= 8 and any pitch (see scan_fwd_kernel).
+template <typename T, int SPL, bool RAG = false>
 __global__ void __launch_bounds__(THREADS) adjoint_agg_dpp_kernel(const BwdArgs a)
 {
     constexpr int NGC = CHUNK_T / GROUP_T;
@@ -1041,6 +1120,14 @@ __global__ void __launch_bounds__(THREADS) adjoint_agg_dpp_kernel(const BwdArgs 
     const rsrc_t bc_ = make_rsrc(static_cast<const T*>(f.Cm) + (long)b * f.bc_bstride,
                                  w < 2 ? (uint32_t)N * (uint32_t)L * (uint32_t)sizeof(T) : 0u);
     const uint32_t c_row_off = s_n < N ? (uint32_t)s_n * (uint32_t)L * (uint32_t)sizeof(T) : BUF_OFF;
+    const uint32_t esz = (uint32_t)sizeof(T);
+    const int r_row = min(pr, rows_here - 1);
+    const uint32_t r_off = (uint32_t)r_row * (uint32_t)L * esz, r_off_ud = (uint32_t)r_row * (uint32_t)f.ld_ud * esz;
+    const uint32_t r_off_c = (uint32_t)min(s_n, N - 1) * (uint32_t)f.ld_bc * esz;
+    const T* const rd_p = static_cast<const T*>(f.delta) + ((long)b * f.D + d0) * f.ld_ud;
+    const T* const ro_p = static_cast<const T*>(a.dout) + wg_first;
+    const T* const rz_p = has_z ? static_cast<const T*>(f.z) + wg_first : ro_p;
+    const T* const rc_p = static_cast<const T*>(f.Cm) + (long)b * f.bc_bstride;
 
     const bool s_ok = d0 + lane < f.D;
     const int sd = s_ok ? d0 + lane : f.D - 1;
@@ -1060,6 +1147,15 @@ __global__ void __launch_bounds__(THREADS) adjoint_agg_dpp_kernel(const BwdArgs 
     typename io4<T>::raw rc_[PF];
     auto issue_loads = [&](int c, auto slot_tag) {   // chunk c (walking down from c_end - 1) into a compile-time slot
         constexpr int s = decltype(slot_tag)::value;
+        if constexpr (RAG) {   // before the segment's start: its first chunk again (never used)
+            const int cc = max(c, c_begin) * CHUNK_T;
+            const uint32_t t = (uint32_t)row_piece(cc + pq * SLICE, SLICE, L) * esz;
+            rd_[s] = io8<T>::load_elem(rd_p, r_off_ud + t);
+            ro_[s] = io8<T>::load_elem(ro_p, r_off + t);
+            rz_[s] = io8<T>::load_elem(rz_p, has_z ? r_off + t : 0u);
+            rc_[s] = io4<T>::load_elem(rc_p, r_off_c + (uint32_t)row_piece(cc + s_tq * GROUP_T, GROUP_T, L) * esz);
+            return;
+        }
         const int t0 = c * CHUNK_T + pq * SLICE;
         const uint32_t off = (t0 < L && c >= c_begin) ? row_off + (uint32_t)t0 * (uint32_t)sizeof(T) : BUF_OFF;   // slices are whole or empty
         rd_[s] = io8<T>::load_buf(bd_, off);
@@ -1077,6 +1173,16 @@ __global__ void __launch_bounds__(THREADS) adjoint_agg_dpp_kernel(const BwdArgs 
         const bool live = p_ok && t0 < L;
         {
             float v8[SLICE], o8[SLICE], z8[SLICE], dt8[SLICE], c4[GROUP_T];
+            const int nv = min(max(L - t0, 0), SLICE);
+            if constexpr (RAG) {
+                if ((c + 1) * CHUNK_T > L) {   // uniform
+                    const int sh = t0 - row_piece(t0, SLICE, L), ts = c * CHUNK_T + s_tq * GROUP_T;
+                    io8<T>::drop(rd_[SLOT], sh);
+                    io8<T>::drop(ro_[SLOT], sh);
+                    io8<T>::drop(rz_[SLOT], sh);
+                    io4<T>::drop(rc_[SLOT], ts - row_piece(ts, GROUP_T, L));
+                }
+            }
             io8<T>::unpack(rd_[SLOT], v8);
             io8<T>::unpack(ro_[SLOT], o8);
             if (has_z) io8<T>::unpack(rz_[SLOT], z8);
@@ -1087,6 +1193,7 @@ __global__ void __launch_bounds__(THREADS) adjoint_agg_dpp_kernel(const BwdArgs 
                 const float x = v8[j] + bias_eff;
                 float sp, sg;
                 if (softplus) softplus_sigmoid(x, sp, sg); else sp = x;
+                if constexpr (RAG) sp = j < nv ? sp : 0.0f;
                 dt8[j] = sp;
                 if (has_z) o8[j] *= z8[j] * sigmoid_fast(z8[j]);
             }
@@ -1096,6 +1203,10 @@ __global__ void __launch_bounds__(THREADS) adjoint_agg_dpp_kernel(const BwdArgs 
             pd4[1] = make_float4(dt8[4], dt8[5], dt8[6], dt8[7]);
             py4[0] = make_float4(o8[0], o8[1], o8[2], o8[3]);
             py4[1] = make_float4(o8[4], o8[5], o8[6], o8[7]);
+            if constexpr (RAG) {   // slots without a state
+#pragma unroll
+                for (int j = 0; j < GROUP_T; ++j) c4[j] = s_n < N ? c4[j] : 0.0f;
+            }
             if (w < 2) *reinterpret_cast<float4*>(&s_c[s_tq][s_n][0]) = make_float4(c4[0], c4[1], c4[2], c4[3]);
         }
         issue_loads(c - PF, slot_tag);
@@ -1288,23 +1399,49 @@ static int launch_scan_bwd_complex(const BwdArgs& a, dim3 grid, hipStream_t stre
 }
 
 // the common case (scan_bwd_dpp_kernel), with the adjoint aggregates of a split sequence first
-template <typename T, bool FULLN, int SPL, bool ZOH = false>
-static int launch_scan_bwd_dpp(const BwdArgs& a, dim3 grid, hipStream_t stream)
+template <typename T, int SPL, bool ZOH, bool RAG>
+static int launch_bwd_dpp_t(const BwdArgs& a, dim3 grid, hipStream_t stream)
 {
     if (a.f.nseg > 1) {
-        adjoint_agg_dpp_kernel<T, SPL><<<dim3(grid.x, (unsigned)(a.f.nseg - 1)), dim3(THREADS), 0, stream>>>(a);
+        adjoint_agg_dpp_kernel<T, SPL, RAG><<<dim3(grid.x, (unsigned)(a.f.nseg - 1)), dim3(THREADS), 0, stream>>>(a);
         const long n = (long)a.f.B * a.f.D * NPAD;
         carry_bwd_kernel<<<dim3((unsigned)((n + 255) / 256)), dim3(256), 0, stream>>>(a);
     }
-    auto kern = scan_bwd_dpp_kernel<T, SPL, ZOH>;
+    auto kern = scan_bwd_dpp_kernel<T, SPL, ZOH, RAG>;
     static std::atomic<bool> lds_ok[MAX_DEVICES];   // this launcher is instantiated once per kernel
     if (!allow_backward_lds_once(reinterpret_cast<const void*>(kern), lds_ok, sizeof(BwdSmemDpp))) return -1;
     kern<<<dim3(grid.x, (unsigned)a.f.nseg), dim3(THREADS), sizeof(BwdSmemDpp), stream>>>(a);
     return hipGetLastError() == hipSuccess ? 0 : -1;
 }
+template <typename T, bool RAG>
+static int launch_bwd_dpp(const BwdArgs& a, dim3 grid, hipStream_t stream)
+{
+    if (a.f.flags & F_EXACT_ZOH_B) return launch_bwd_dpp_t<T, STATES_PER_LANE, true, RAG>(a, grid, stream);
+    const int spl = slots_for(a.f.N, a.f.il);   // fewer than 16 states dealt out to the waves: kernels built for 1 or 2 slots per lane
+    if (spl == 1) return launch_bwd_dpp_t<T, 1, false, RAG>(a, grid, stream);
+    if (spl == 2) return launch_bwd_dpp_t<T, 2, false, RAG>(a, grid, stream);
+    return launch_bwd_dpp_t<T, STATES_PER_LANE, false, RAG>(a, grid, stream);
+}
 
+// Real state, selective B and C, fewer than 8 steps or rows beyond the kernels above: the scalar path.
+template <typename T, bool ZOH>
+static int launch_bwd_scalar(const BwdArgs& a, dim3 grid, hipStream_t stream)
+{
+    if (a.f.nseg > 1) {
+        adjoint_agg_kernel<T, false, false><<<dim3(grid.x, (unsigned)(a.f.nseg - 1)), dim3(THREADS), 0, stream>>>(a);
+        const long n = (long)a.f.B * a.f.D * NPAD;
+        carry_bwd_kernel<<<dim3((unsigned)((n + 255) / 256)), dim3(256), 0, stream>>>(a);
+    }
+    auto kern = scan_bwd_kernel<T, false, false, ZOH>;
+    static std::atomic<bool> lds_ok[MAX_DEVICES];   // this launcher is instantiated once per kernel
+    if (!allow_backward_lds_once(reinterpret_cast<const void*>(kern), lds_ok, sizeof(BwdSmem))) return -1;
+    kern<<<dim3(grid.x, (unsigned)a.f.nseg), dim3(THREADS), sizeof(BwdSmem), stream>>>(a);
+    return hipGetLastError() == hipSuccess ? 0 : -1;
+}
+
+// complex state and time-invariant B and / or C
 template <typename T, bool VEC, bool FULLN, bool ZOH>
-static int launch_scan_bwd(const BwdArgs& a, dim3 grid, hipStream_t stream)
+static int launch_bwd_variant(const BwdArgs& a, dim3 grid, hipStream_t stream)
 {
     const int bcfix = ((a.f.flags & F_B_FIXED) ? 1 : 0) | ((a.f.flags & F_C_FIXED) ? 2 : 0);
     if constexpr (!ZOH) {
@@ -1317,28 +1454,25 @@ static int launch_scan_bwd(const BwdArgs& a, dim3 grid, hipStream_t stream)
     }
     if (bcfix == 1) return launch_scan_bwd_fixed<T, VEC, FULLN, ZOH, 1>(a, grid, stream);
     if (bcfix == 2) return launch_scan_bwd_fixed<T, VEC, FULLN, ZOH, 2>(a, grid, stream);
-    if (bcfix == 3) return launch_scan_bwd_fixed<T, VEC, FULLN, ZOH, 3>(a, grid, stream);
-    if constexpr (VEC && FULLN && ZOH) {   // exact ZOH: the same kernel, built for sixteen states
-        return launch_scan_bwd_dpp<T, FULLN, STATES_PER_LANE, true>(a, grid, stream);
-    } else if constexpr (VEC && !ZOH) {   // real state, first-order B-bar, selective B and C, whole 16-byte pieces
-        if constexpr (!FULLN) {    // fewer than 16 states dealt out to the waves: kernels built for 1 or 2 slots per lane
-            const int spl = slots_for(a.f.N, a.f.il);
-            if (spl == 1) return launch_scan_bwd_dpp<T, FULLN, 1>(a, grid, stream);
-            if (spl == 2) return launch_scan_bwd_dpp<T, FULLN, 2>(a, grid, stream);
-        }
-        return launch_scan_bwd_dpp<T, FULLN, STATES_PER_LANE>(a, grid, stream);
-    } else {
-        if (a.f.nseg > 1) {
-            adjoint_agg_kernel<T, VEC, FULLN><<<dim3(grid.x, (unsigned)(a.f.nseg - 1)), dim3(THREADS), 0, stream>>>(a);
-            const long n = (long)a.f.B * a.f.D * NPAD;
-            carry_bwd_kernel<<<dim3((unsigned)((n + 255) / 256)), dim3(256), 0, stream>>>(a);
-        }
-        auto kern = scan_bwd_kernel<T, VEC, FULLN, ZOH>;
-        static std::atomic<bool> lds_ok[MAX_DEVICES];   // this launcher is instantiated once per kernel
-        if (!allow_backward_lds_once(reinterpret_cast<const void*>(kern), lds_ok, sizeof(BwdSmem))) return -1;
-        kern<<<dim3(grid.x, (unsigned)a.f.nseg), dim3(THREADS), sizeof(BwdSmem), stream>>>(a);
-        return hipGetLastError() == hipSuccess ? 0 : -1;
+    return launch_scan_bwd_fixed<T, VEC, FULLN, ZOH, 3>(a, grid, stream);
+}
+
+template <typename T>
+static int launch_bwd_io(const BwdArgs& a, dim3 grid, hipStream_t stream)
+{
+    const FwdArgs& f = a.f;
+    const bool zoh = f.flags & F_EXACT_ZOH_B, fulln = f.N == NPAD;
+    if (!(f.flags & (F_B_FIXED | F_C_FIXED | F_COMPLEX))) {
+        if (f.vec_ok) return launch_bwd_dpp<T, false>(a, grid, stream);
+        if (f.dpp_ok) return launch_bwd_dpp<T, true>(a, grid, stream);
+        return zoh ? launch_bwd_scalar<T, true>(a, grid, stream) : launch_bwd_scalar<T, false>(a, grid, stream);
     }
+    if (zoh)   // built for the fastest and the most general shape only
+        return f.vec_ok && fulln ? launch_bwd_variant<T, true, true, true>(a, grid, stream)
+                                 : launch_bwd_variant<T, false, false, true>(a, grid, stream);
+    if (f.vec_ok && fulln) return launch_bwd_variant<T, true, true, false>(a, grid, stream);
+    if (f.vec_ok) return launch_bwd_variant<T, true, false, false>(a, grid, stream);
+    return launch_bwd_variant<T, false, false, false>(a, grid, stream);
 }
 
 int launch_bwd(const BwdArgs& a, int io_dtype, hipStream_t stream)
@@ -1360,25 +1494,7 @@ int launch_bwd(const BwdArgs& a, int io_dtype, hipStream_t stream)
     if (zB || zC) zero_kernel<<<dim3((unsigned)((nbc + 255) / 256)), dim3(256), 0, stream>>>(zB, zC, nbc);
     const int groups = (f.D + ROWS - 1) / ROWS;
     const dim3 grid((unsigned)(f.B * groups));
-    const bool fulln = f.N == NPAD;
-    int rc;
-    if (f.flags & F_EXACT_ZOH_B) {  // the variant is built for the fastest and the most general shape only
-        if (io_dtype == 0) {
-            if (f.vec_ok && fulln) rc = launch_scan_bwd<float, true, true, true>(a, grid, stream);
-            else rc = launch_scan_bwd<float, false, false, true>(a, grid, stream);
-        } else {
-            if (f.vec_ok && fulln) rc = launch_scan_bwd<bf16_t, true, true, true>(a, grid, stream);
-            else rc = launch_scan_bwd<bf16_t, false, false, true>(a, grid, stream);
-        }
-    } else if (io_dtype == 0) {
-        if (f.vec_ok && fulln) rc = launch_scan_bwd<float, true, true, false>(a, grid, stream);
-        else if (f.vec_ok) rc = launch_scan_bwd<float, true, false, false>(a, grid, stream);
-        else rc = launch_scan_bwd<float, false, false, false>(a, grid, stream);
-    } else {
-        if (f.vec_ok && fulln) rc = launch_scan_bwd<bf16_t, true, true, false>(a, grid, stream);
-        else if (f.vec_ok) rc = launch_scan_bwd<bf16_t, true, false, false>(a, grid, stream);
-        else rc = launch_scan_bwd<bf16_t, false, false, false>(a, grid, stream);
-    }
+    const int rc = io_dtype == 0 ? launch_bwd_io<float>(a, grid, stream) : launch_bwd_io<bf16_t>(a, grid, stream);
     if (rc != 0) return rc;
     finalize_kernel<<<dim3(fin_blocks), dim3(64 * FIN_LANES), 0, stream>>>(a, 1);
     return hipGetLastError() == hipSuccess ? 0 : -1;

@@ -210,6 +210,38 @@ __device__ __forceinline__ uint32_t buf_load_elem(rsrc_t r, uint32_t off)
     else return (uint32_t)__builtin_amdgcn_raw_buffer_load_b32(r, (int)off, 0, 0);
 }
 
+// ---- rows of any length: accesses aligned to an element only ---------------------------------
+// The widest loads and stores at an address that is a multiple of the element size.  The hardware takes
+// them in one instruction (the compiler's default access mode on this target), so a row that is not a
+// whole number of 16-byte pieces costs the same instructions as one that is; what it loses is the
+// out-of-range rule of the buffer resources, so offsets are clamped into the row instead (row_piece).
+template <typename V, int A> struct elem_aligned { typedef V type __attribute__((aligned(A))); };
+template <typename V, typename T>
+__device__ __forceinline__ V load_any(const T* base, uint32_t byte_off)
+{
+    return *reinterpret_cast<const typename elem_aligned<V, (int)sizeof(T)>::type*>(reinterpret_cast<const char*>(base) + byte_off);
+}
+template <typename V, typename T>
+__device__ __forceinline__ void store_any(T* base, uint32_t byte_off, V v)
+{
+    *reinterpret_cast<typename elem_aligned<V, (int)sizeof(T)>::type*>(reinterpret_cast<char*>(base) + byte_off) = v;
+}
+// A piece of `len` steps starting at t of a row of L >= len steps: where to read it so that the access stays
+// inside the row.  A piece that ends past the row is read from L - len; dropping its first t - row_piece(t)
+// elements (drop_front) leaves the piece's own, followed by zeros.
+__device__ __forceinline__ int row_piece(int t, int len, int L) { return min(t, L - len); }
+// v without its first n elements of ELEM_BITS bits, zeros moving in at the end (n >= 0; the whole vector or more: zeros)
+template <int ELEM_BITS>
+__device__ __forceinline__ u32x4 drop_front(u32x4 v, int n)
+{
+    const uint64_t lo = (uint64_t(v[1]) << 32) | v[0], hi = (uint64_t(v[3]) << 32) | v[2];
+    const int s = n * ELEM_BITS;
+    uint64_t a = 0, b = 0;
+    if (s < 64) { a = s == 0 ? lo : (lo >> s) | (hi << (64 - s)); b = hi >> s; }
+    else if (s < 128) a = hi >> (s - 64);
+    return u32x4{(uint32_t)a, (uint32_t)(a >> 32), (uint32_t)b, (uint32_t)(b >> 32)};
+}
+
 // ---- 8 consecutive io elements <-> 8 floats -------------------------------------------
 // VEC: every row starts 16-byte aligned and L is a multiple of 8, so a slice is either
 // whole (nvalid == 8, one or two 16-byte accesses) or empty.  Otherwise the `nvalid`
@@ -246,7 +278,42 @@ template <> struct io8<float> {
         r.b = make_float4(__uint_as_float(y.x), __uint_as_float(y.y), __uint_as_float(y.z), __uint_as_float(y.w));
         return r;
     }
+    static __device__ __forceinline__ raw load_elem(const float* p, uint32_t off)   // eight elements at element alignment
+    {
+        const u32x4 x = load_any<u32x4>(p, off), y = load_any<u32x4>(p, off + 16);
+        raw r;
+        r.a = make_float4(__uint_as_float(x[0]), __uint_as_float(x[1]), __uint_as_float(x[2]), __uint_as_float(x[3]));
+        r.b = make_float4(__uint_as_float(y[0]), __uint_as_float(y[1]), __uint_as_float(y[2]), __uint_as_float(y[3]));
+        return r;
+    }
+    static __device__ __forceinline__ void drop(raw& r, int n)   // the first n elements; zeros move in
+    {
+        float v[8], o[8];
+        unpack(r, v);
+#pragma unroll
+        for (int j = 0; j < 8; ++j) o[j] = 0.0f;
+#pragma unroll
+        for (int k = 0; k < 8; ++k)
+            if (n == k) {
+#pragma unroll
+                for (int j = 0; j + k < 8; ++j) o[j] = v[j + k];
+            }
+        r.a = make_float4(o[0], o[1], o[2], o[3]);
+        r.b = make_float4(o[4], o[5], o[6], o[7]);
+    }
     struct packed { uint4 a, b; };   // eight elements as stored
+    static __device__ __forceinline__ void store_elem(float* p, uint32_t off, const packed& x, int n)   // the first n elements
+    {
+        if (n >= 8) {
+            store_any(p, off, u32x4{x.a.x, x.a.y, x.a.z, x.a.w});
+            store_any(p, off + 16, u32x4{x.b.x, x.b.y, x.b.z, x.b.w});
+        } else {
+            const uint32_t w[8] = {x.a.x, x.a.y, x.a.z, x.a.w, x.b.x, x.b.y, x.b.z, x.b.w};
+#pragma unroll
+            for (int j = 0; j < 7; ++j)
+                if (j < n) store_any(p, off + 4u * j, w[j]);
+        }
+    }
     static __device__ __forceinline__ packed pack(const float (&v)[8])
     {
         return {make_uint4(__float_as_uint(v[0]), __float_as_uint(v[1]), __float_as_uint(v[2]), __float_as_uint(v[3])),
@@ -303,7 +370,30 @@ template <> struct io8<bf16_t> {
         r.w = buf_load16_once(rs, off);
         return r;
     }
+    static __device__ __forceinline__ raw load_elem(const bf16_t* p, uint32_t off)   // eight elements at element alignment
+    {
+        const u32x4 x = load_any<u32x4>(p, off);
+        raw r;
+        r.w = make_uint4(x[0], x[1], x[2], x[3]);
+        return r;
+    }
+    static __device__ __forceinline__ void drop(raw& r, int n)   // the first n elements; zeros move in
+    {
+        const u32x4 x = drop_front<16>(u32x4{r.w.x, r.w.y, r.w.z, r.w.w}, n);
+        r.w = make_uint4(x[0], x[1], x[2], x[3]);
+    }
     typedef uint4 packed;   // eight elements as stored
+    static __device__ __forceinline__ void store_elem(bf16_t* p, uint32_t off, packed x, int n)   // the first n elements
+    {
+        if (n >= 8) {
+            store_any(p, off, u32x4{x.x, x.y, x.z, x.w});
+        } else {
+            const uint32_t w[4] = {x.x, x.y, x.z, x.w};
+#pragma unroll
+            for (int j = 0; j < 7; ++j)
+                if (j < n) store_any(p, off + 2u * j, bf16_t(w[j >> 1] >> (16 * (j & 1))));
+        }
+    }
     static __device__ __forceinline__ packed pack(const float (&v)[8])
     {
         return make_uint4(pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3]), pack_bf16x2(v[4], v[5]), pack_bf16x2(v[6], v[7]));
@@ -360,7 +450,30 @@ template <> struct io4<float> {
         r.a = make_float4(__uint_as_float(x.x), __uint_as_float(x.y), __uint_as_float(x.z), __uint_as_float(x.w));
         return r;
     }
+    static __device__ __forceinline__ raw load_elem(const float* p, uint32_t off)   // four elements at element alignment
+    {
+        const u32x4 x = load_any<u32x4>(p, off);
+        raw r;
+        r.a = make_float4(__uint_as_float(x[0]), __uint_as_float(x[1]), __uint_as_float(x[2]), __uint_as_float(x[3]));
+        return r;
+    }
+    static __device__ __forceinline__ void drop(raw& r, int n)   // the first n elements; zeros move in
+    {
+        const u32x4 x = drop_front<32>(u32x4{__float_as_uint(r.a.x), __float_as_uint(r.a.y), __float_as_uint(r.a.z), __float_as_uint(r.a.w)}, n);
+        r.a = make_float4(__uint_as_float(x[0]), __uint_as_float(x[1]), __uint_as_float(x[2]), __uint_as_float(x[3]));
+    }
     typedef uint4 packed;   // four elements as stored
+    static __device__ __forceinline__ void store_elem(float* p, uint32_t off, packed x, int n)   // the first n elements
+    {
+        if (n >= 4) {
+            store_any(p, off, u32x4{x.x, x.y, x.z, x.w});
+        } else {
+            const uint32_t w[3] = {x.x, x.y, x.z};
+#pragma unroll
+            for (int j = 0; j < 3; ++j)
+                if (j < n) store_any(p, off + 4u * j, w[j]);
+        }
+    }
     static __device__ __forceinline__ packed pack(const float (&v)[4])
     {
         return make_uint4(__float_as_uint(v[0]), __float_as_uint(v[1]), __float_as_uint(v[2]), __float_as_uint(v[3]));
@@ -407,7 +520,30 @@ template <> struct io4<bf16_t> {
         r.w = buf_load8(rs, off);
         return r;
     }
+    static __device__ __forceinline__ raw load_elem(const bf16_t* p, uint32_t off)   // four elements at element alignment
+    {
+        const u32x2 x = load_any<u32x2>(p, off);
+        raw r;
+        r.w = make_uint2(x[0], x[1]);
+        return r;
+    }
+    static __device__ __forceinline__ void drop(raw& r, int n)   // the first n elements; zeros move in
+    {
+        const u32x4 x = drop_front<16>(u32x4{r.w.x, r.w.y, 0u, 0u}, n);
+        r.w = make_uint2(x[0], x[1]);
+    }
     typedef uint2 packed;   // four elements as stored
+    static __device__ __forceinline__ void store_elem(bf16_t* p, uint32_t off, packed x, int n)   // the first n elements
+    {
+        if (n >= 4) {
+            store_any(p, off, u32x2{x.x, x.y});
+        } else {
+            const uint32_t w[2] = {x.x, x.y};
+#pragma unroll
+            for (int j = 0; j < 3; ++j)
+                if (j < n) store_any(p, off + 2u * j, bf16_t(w[j >> 1] >> (16 * (j & 1))));
+        }
+    }
     static __device__ __forceinline__ packed pack(const float (&v)[4]) { return make_uint2(pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3])); }
     static __device__ __forceinline__ void store_packed(rsrc_t rs, uint32_t off, packed p)   // dropped if off is out of range
     {

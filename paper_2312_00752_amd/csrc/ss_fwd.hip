@@ -52,11 +52,18 @@ typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));   // MFMA operand a
 // (input_step_dpp, readout_step_dpp).  No scalar loads or their waits (which also drain LDS reads and
 // vice versa), no repacking pass, no touching of cache lines ahead, and no vector-memory wait that
 // has to cover the previous chunk's stores.
+// RAG (PAT): rows of any length >= 8 and any pitch.  Slices are read in one access at element alignment, the
+// one that reaches past the end from inside the row (row_piece), and shifted into place in the last chunk
+// only; a partial slice is stored element by element.  Everything else is the aligned kernel's.  Such rows
+// used to take the scalar path with one access per element: 8 x 1536 x 2047 in bf16, main + aggregate pass
+// 309 + 139 -> 158 + 90 us (2048 steps: 137 + 86), backward 1632 + 385 -> 445 + 93 us (320 + 84); float32,
+// 4 x 1536 x 2047, all passes: 865 -> 512 us.
 template <typename T, bool VEC, bool FULLN, bool AGG, bool ZOH, int BCFIX = 0, bool CPLX = false, bool STAGED = false,
-          int FUSED_KS = 0, int SPL = STATES_PER_LANE, bool PAT = false>
+          int FUSED_KS = 0, int SPL = STATES_PER_LANE, bool PAT = false, bool RAG = false>
 __global__ void __launch_bounds__(THREADS, (PAT && FUSED_KS <= 4 && !(ZOH && AGG)) ? 2 : 1) scan_fwd_kernel(const FwdArgs a)
 {
     static_assert(!PAT || (VEC && BCFIX == 0 && !CPLX && !STAGED), "PAT: vector path, real state, selective B and C");
+    static_assert(!RAG || PAT, "RAG: a form of the PAT kernel");
     constexpr int NGC = CHUNK_T / GROUP_T;
     __shared__ __attribute__((aligned(16))) float s_bc[PAT ? 2 : 1][PAT ? NGC : 1][PAT ? NPAD : 1][GROUP_T];   // PAT: B (0) and C (1) of the chunk
     __shared__ __attribute__((aligned(16))) float s_dt[ROWS][TPAD];
@@ -115,6 +122,16 @@ __global__ void __launch_bounds__(THREADS, (PAT && FUSED_KS <= 4 && !(ZOH && AGG
     const rsrc_t bbc = make_rsrc(static_cast<const T*>(s_which ? a.Cm : a.Bm) + (long)b * a.bc_bstride,
                                  s_on ? (uint32_t)N * (uint32_t)L * (uint32_t)sizeof(T) : 0u);
     const uint32_t bc_row_off = s_n < N ? (uint32_t)s_n * (uint32_t)L * (uint32_t)sizeof(T) : BUF_OFF;
+    // RAG: plain pointers to the workgroup's first row and offsets of this thread's row, clamped to a valid one
+    const uint32_t esz = (uint32_t)sizeof(T);
+    const int r_row = min(pr, rows_here - 1);
+    const uint32_t r_off = (uint32_t)r_row * (uint32_t)L * esz, r_off_ud = (uint32_t)r_row * (uint32_t)a.ld_ud * esz;
+    const uint32_t r_off_bc = (uint32_t)min(s_n, N - 1) * (uint32_t)a.ld_bc * esz;
+    const T* const ru_p = static_cast<const T*>(a.u) + ((long)b * a.D + d0) * a.ld_ud;
+    const T* const rd_p = static_cast<const T*>(a.delta) + ((long)b * a.D + d0) * a.ld_ud;
+    const T* const rz_p = has_z ? static_cast<const T*>(a.z) + wg_first : ru_p;
+    const T* const rp_p = acc_on ? static_cast<const T*>(has_z ? a.ysave : a.out) + wg_first : ru_p;
+    const T* const rbc_p = static_cast<const T*>(s_which ? a.Cm : a.Bm) + (long)b * a.bc_bstride;
 
     // ---- state view: lane -> row, wave -> states 4w..4w+3 -------------------------------
     const bool s_ok = d0 + lane < a.D;
@@ -195,7 +212,15 @@ __global__ void __launch_bounds__(THREADS, (PAT && FUSED_KS <= 4 && !(ZOH && AGG
         constexpr int s = decltype(slot_tag)::value;
         const int t0 = c * CHUNK_T + pq * SLICE;
         const int nv = min(max(L - t0, 0), SLICE);
-        if constexpr (VEC) {   // slices are whole or empty
+        if constexpr (RAG) {   // past the segment's end: its last chunk again (never used)
+            const int cc = min(c, c_end - 1) * CHUNK_T;
+            const uint32_t t = (uint32_t)row_piece(cc + pq * SLICE, SLICE, L) * esz;
+            ru_[s] = io8<T>::load_elem(ru_p, r_off_ud + t);
+            if constexpr (FUSED_KS == 0) rd_[s] = io8<T>::load_elem(rd_p, r_off_ud + t);
+            rz_[s] = io8<T>::load_elem(rz_p, has_z ? r_off + t : 0u);
+            rp_[s] = io8<T>::load_elem(rp_p, acc_on ? r_off + t : 0u);
+            rbc_[s] = io4<T>::load_elem(rbc_p, r_off_bc + (uint32_t)row_piece(cc + s_tq * GROUP_T, GROUP_T, L) * esz);
+        } else if constexpr (VEC) {   // slices are whole or empty
             const uint32_t off = (nv == SLICE && c < c_end) ? row_off + (uint32_t)t0 * (uint32_t)sizeof(T) : BUF_OFF;
             ru_[s] = io8<T>::load_buf(bu, off);
             if constexpr (FUSED_KS == 0) rd_[s] = io8<T>::load_buf(bd, off);
@@ -269,7 +294,20 @@ __global__ void __launch_bounds__(THREADS, (PAT && FUSED_KS <= 4 && !(ZOH && AGG
     // by tensor, and the even chunk's results wait in registers for the odd chunk's.
     constexpr bool PAIR = PAT && sizeof(T) == 2 && PF == 2;
     auto issue_pair = [&](int c0) {   // chunks c0 (slot 0) and c0 + 1 (slot 1)
-      if constexpr (PAIR) {
+      if constexpr (PAIR && RAG) {
+        uint32_t t[2], tb[2];
+#pragma unroll
+        for (int s = 0; s < 2; ++s) {
+            const int cc = min(c0 + s, c_end - 1) * CHUNK_T;
+            t[s] = (uint32_t)row_piece(cc + pq * SLICE, SLICE, L) * esz;
+            tb[s] = r_off_bc + (uint32_t)row_piece(cc + s_tq * GROUP_T, GROUP_T, L) * esz;
+        }
+        ru_[0] = io8<T>::load_elem(ru_p, r_off_ud + t[0]); ru_[1] = io8<T>::load_elem(ru_p, r_off_ud + t[1]);
+        if constexpr (FUSED_KS == 0) { rd_[0] = io8<T>::load_elem(rd_p, r_off_ud + t[0]); rd_[1] = io8<T>::load_elem(rd_p, r_off_ud + t[1]); }
+        rz_[0] = io8<T>::load_elem(rz_p, has_z ? r_off + t[0] : 0u); rz_[1] = io8<T>::load_elem(rz_p, has_z ? r_off + t[1] : 0u);
+        rp_[0] = io8<T>::load_elem(rp_p, acc_on ? r_off + t[0] : 0u); rp_[1] = io8<T>::load_elem(rp_p, acc_on ? r_off + t[1] : 0u);
+        rbc_[0] = io4<T>::load_elem(rbc_p, tb[0]); rbc_[1] = io4<T>::load_elem(rbc_p, tb[1]);
+      } else if constexpr (PAIR) {
         uint32_t off[2], boff[2];
 #pragma unroll
         for (int s = 0; s < 2; ++s) {
@@ -308,8 +346,18 @@ __global__ void __launch_bounds__(THREADS, (PAT && FUSED_KS <= 4 && !(ZOH && AGG
         const int t0 = tc + pq * SLICE;
         const int nv = min(max(L - t0, 0), SLICE);
         // ---- A: pointwise pre-processing --------------------------------------------
-        const typename io8<T>::raw ru = ru_[SLOT], rd = rd_[SLOT], rz = rz_[SLOT];
-        const typename io4<T>::raw rbc = rbc_[SLOT];
+        typename io8<T>::raw ru = ru_[SLOT], rd = rd_[SLOT], rz = rz_[SLOT];
+        typename io4<T>::raw rbc = rbc_[SLOT];
+        if constexpr (RAG) {
+            if (tc + CHUNK_T > L) {   // uniform: the last chunk of a row that does not fill it
+                const int sh = t0 - row_piece(t0, SLICE, L), ts = tc + s_tq * GROUP_T;
+                io8<T>::drop(ru, sh);
+                if constexpr (FUSED_KS == 0) io8<T>::drop(rd, sh);
+                io8<T>::drop(rz, sh);
+                if (acc_on) io8<T>::drop(rp_[SLOT], sh);
+                io4<T>::drop(rbc, ts - row_piece(ts, GROUP_T, L));
+            }
+        }
         float p8[SLICE];
         if constexpr (VEC) {
             if (acc_on) io8<T>::unpack(rp_[SLOT], p8);   // uniform: only with more than 16 states
@@ -317,6 +365,10 @@ __global__ void __launch_bounds__(THREADS, (PAT && FUSED_KS <= 4 && !(ZOH && AGG
         if constexpr (PAT) {
             float bc4[GROUP_T];
             io4<T>::unpack(rbc, bc4);
+            if constexpr (RAG) {   // slots without a state
+#pragma unroll
+                for (int j = 0; j < GROUP_T; ++j) bc4[j] = s_n < N ? bc4[j] : 0.0f;
+            }
             *reinterpret_cast<float4*>(&s_bc[s_which][s_tq][s_n][0]) = make_float4(bc4[0], bc4[1], bc4[2], bc4[3]);
         }
         io8<T>::unpack(ru, u8);
@@ -335,7 +387,7 @@ __global__ void __launch_bounds__(THREADS, (PAT && FUSED_KS <= 4 && !(ZOH && AGG
             // PAT without the in-kernel projection: a slice is whole or empty, and an empty one was read as
             // zeros; a bias of -1e30 (0 without softplus) then makes its step sizes exactly 0, the identity of
             // the recurrence, without a select per element
-            constexpr bool ZERO_BY_BIAS = PAT && FUSED_KS == 0;
+            constexpr bool ZERO_BY_BIAS = PAT && FUSED_KS == 0 && !RAG;
             const float bias_e = !ZERO_BY_BIAS || nv == SLICE ? bias : (softplus ? -1e30f : 0.0f);
 #pragma unroll
             for (int j = 0; j < SLICE; ++j) {
@@ -536,6 +588,20 @@ __global__ void __launch_bounds__(THREADS, (PAT && FUSED_KS <= 4 && !(ZOH && AGG
                 if (SLOT == 0 && c + 1 < c_end) {   // wait for the odd chunk
                     held_y = py;
                     held_o = po;
+                } else if constexpr (RAG) {
+                    const uint32_t off_t = (uint32_t)t0 * esz;
+                    if (p_ok) {
+                        T* const yp = static_cast<T*>(a.ysave) + wg_first;
+                        T* const op = static_cast<T*>(a.out) + wg_first;
+                        if (SLOT == 1) {   // the even chunk before an odd one is whole
+                            if (keep_y) io8<T>::store_elem(yp, r_off + off_t - CHUNK_T * esz, held_y, SLICE);
+                            if (keep_y) io8<T>::store_elem(yp, r_off + off_t, py, nv);
+                            io8<T>::store_elem(op, r_off + off_t - CHUNK_T * esz, held_o, SLICE);
+                        } else if (keep_y) {
+                            io8<T>::store_elem(yp, r_off + off_t, py, nv);
+                        }
+                        io8<T>::store_elem(op, r_off + off_t, po, nv);
+                    }
                 } else {
                     // the even chunk before an odd one is whole; a lone even chunk has nothing waiting
                     const uint32_t off_e = SLOT == 1 ? row_off + (uint32_t)(t0 - CHUNK_T) * (uint32_t)sizeof(T) : BUF_OFF;
@@ -544,6 +610,13 @@ __global__ void __launch_bounds__(THREADS, (PAT && FUSED_KS <= 4 && !(ZOH && AGG
                     io8<T>::store_packed(bo, off_e, held_o);
                     io8<T>::store_packed(bo, off, po);
                 }
+            } else if constexpr (RAG) {
+                if (keep_y && p_ok) io8<T>::store_elem(static_cast<T*>(a.ysave) + wg_first, r_off + (uint32_t)t0 * esz, io8<T>::pack(y8), nv);
+                if (has_z) {
+#pragma unroll
+                    for (int j = 0; j < SLICE; ++j) y8[j] *= z8[j] * sigmoid_fast(z8[j]);
+                }
+                if (p_ok) io8<T>::store_elem(static_cast<T*>(a.out) + wg_first, r_off + (uint32_t)t0 * esz, io8<T>::pack(y8), nv);
             } else if constexpr (VEC) {
                 io8<T>::store_buf(by, off, y8);   // y before the gate, for the backward pass's dz (if kept)
                 if (has_z) {
@@ -1063,10 +1136,10 @@ __global__ void copy_state_kernel(const float* __restrict__ src, float* __restri
 
 // Wave-packed copy of the selective B and C for the forward kernels (layout: FwdArgs::bcs).
 // A thread writes the four steps of one (batch entry, state, group of steps, B or C).
-// deal: a last group of fewer than 16 states is dealt out to the waves in turn (FwdArgs::il).
+// The scalar path does not deal its states out (FwdArgs::il is 0 there).
 template <typename T>
 __global__ void stage_bc_kernel(const T* __restrict__ Bm, const T* __restrict__ Cm, long bstride, T* __restrict__ dst,
-                                int B, int NS, int L, int Lp, int deal)
+                                int B, int NS, int L, int Lp)
 {
     const long i = (long)blockIdx.x * blockDim.x + threadIdx.x;
     const int tgroups = Lp / GROUP_T, sgroups = (NS + NPAD - 1) / NPAD * NWAVES;   // every wave of every pass has a piece
@@ -1077,7 +1150,7 @@ __global__ void stage_bc_kernel(const T* __restrict__ Bm, const T* __restrict__ 
     const int sg = (int)((piece / tgroups) % sgroups);
     const int b = (int)(piece / ((long)tgroups * sgroups));
     const int grp = sg / NWAVES;
-    const int n = grp * NPAD + slot_state(sg % NWAVES, r % STATES_PER_LANE, deal && NS - grp * NPAD < NPAD), t = tg * GROUP_T;
+    const int n = grp * NPAD + slot_state(sg % NWAVES, r % STATES_PER_LANE, 0), t = tg * GROUP_T;
     const T* src = (r >= STATES_PER_LANE ? Cm : Bm) + (long)b * bstride + (long)n * L + t;
     T v[GROUP_T];
 #pragma unroll
@@ -1092,16 +1165,14 @@ __global__ void stage_bc_kernel(const T* __restrict__ Bm, const T* __restrict__ 
 
 int launch_stage_bc(const FwdArgs& a, void* bcs, int io_dtype, hipStream_t stream)
 {
-    // a carries all NS states here; whether a partial last group is dealt out depends on the path alone
-    const int deal = a.vec_ok && !(a.flags & (F_EXACT_ZOH_B | F_B_FIXED | F_C_FIXED | F_COMPLEX));
     const long n = (long)a.B * ((a.NS + NPAD - 1) / NPAD * NWAVES) * (a.Lp / GROUP_T) * 2 * STATES_PER_LANE;
     const dim3 grid((unsigned)((n + 255) / 256));
     if (io_dtype == 0)
         stage_bc_kernel<float><<<grid, dim3(256), 0, stream>>>(static_cast<const float*>(a.Bm), static_cast<const float*>(a.Cm),
-                                                               a.bc_bstride, static_cast<float*>(bcs), a.B, a.NS, a.L, a.Lp, deal);
+                                                               a.bc_bstride, static_cast<float*>(bcs), a.B, a.NS, a.L, a.Lp);
     else
         stage_bc_kernel<bf16_t><<<grid, dim3(256), 0, stream>>>(static_cast<const bf16_t*>(a.Bm), static_cast<const bf16_t*>(a.Cm),
-                                                                a.bc_bstride, static_cast<bf16_t*>(bcs), a.B, a.NS, a.L, a.Lp, deal);
+                                                                a.bc_bstride, static_cast<bf16_t*>(bcs), a.B, a.NS, a.L, a.Lp);
     return hipGetLastError() == hipSuccess ? 0 : -1;
 }
 
@@ -1126,42 +1197,62 @@ static void launch_fwd_complex(const FwdArgs& a, hipStream_t stream)
     scan_fwd_kernel<T, VEC, FULLN, false, false, BCFIX, true><<<dim3((unsigned)(a.B * groups), (unsigned)a.nseg), block, 0, stream>>>(a);
 }
 
-// real state, selective B and C
-template <typename T, bool VEC, bool FULLN, bool ZOH, int SPL>
-static void launch_fwd_selective(const FwdArgs& a, hipStream_t stream)
+// Real state, selective B and C, rows of at least 8 steps: B and C as quad-broadcast operands.
+template <typename T, bool ZOH, int SPL, bool RAG>
+static void launch_fwd_dpp_t(const FwdArgs& a, hipStream_t stream)
 {
     const int groups = (a.D + ROWS - 1) / ROWS;
     const dim3 block(THREADS);
-    constexpr bool PAT = VEC;          // B and C through the LDS tile; otherwise the scalar path (repacked copy if there is one)
     if (a.nseg > 1) {
-        if (PAT || a.bcs)
-            scan_fwd_kernel<T, VEC, FULLN, true, ZOH, 0, false, !PAT, 0, SPL, PAT><<<dim3((unsigned)(a.B * groups), (unsigned)(a.nseg - 1)), block, 0, stream>>>(a);
-        else
-            scan_fwd_kernel<T, VEC, FULLN, true, ZOH, 0, false, false, 0, SPL, false><<<dim3((unsigned)(a.B * groups), (unsigned)(a.nseg - 1)), block, 0, stream>>>(a);
+        scan_fwd_kernel<T, true, false, true, ZOH, 0, false, false, 0, SPL, true, RAG><<<dim3((unsigned)(a.B * groups), (unsigned)(a.nseg - 1)), block, 0, stream>>>(a);
         const long n = (long)a.B * a.D * NPAD;
         carry_fwd_kernel<<<dim3((unsigned)((n + 255) / 256)), dim3(256), 0, stream>>>(a);
     }
-    if constexpr (sizeof(T) == 2 && VEC && !ZOH && SPL == STATES_PER_LANE) {
+    if constexpr (sizeof(T) == 2 && !ZOH && SPL == STATES_PER_LANE) {
         if (a.W_dt) {   // the caller has checked: unsplit, R <= 256
             if (a.Rp <= 128)
-                scan_fwd_kernel<T, VEC, FULLN, false, ZOH, 0, false, false, 4, SPL, true><<<dim3((unsigned)(a.B * groups), 1u), block, 0, stream>>>(a);
+                scan_fwd_kernel<T, true, false, false, ZOH, 0, false, false, 4, SPL, true, RAG><<<dim3((unsigned)(a.B * groups), 1u), block, 0, stream>>>(a);
             else
-                scan_fwd_kernel<T, VEC, FULLN, false, ZOH, 0, false, false, 8, SPL, true><<<dim3((unsigned)(a.B * groups), 1u), block, 0, stream>>>(a);
+                scan_fwd_kernel<T, true, false, false, ZOH, 0, false, false, 8, SPL, true, RAG><<<dim3((unsigned)(a.B * groups), 1u), block, 0, stream>>>(a);
             return;
         }
     }
-    if (PAT || a.bcs)
-        scan_fwd_kernel<T, VEC, FULLN, false, ZOH, 0, false, !PAT, 0, SPL, PAT><<<dim3((unsigned)(a.B * groups), (unsigned)a.nseg), block, 0, stream>>>(a);
-    else
-        scan_fwd_kernel<T, VEC, FULLN, false, ZOH, 0, false, false, 0, SPL, false><<<dim3((unsigned)(a.B * groups), (unsigned)a.nseg), block, 0, stream>>>(a);
+    scan_fwd_kernel<T, true, false, false, ZOH, 0, false, false, 0, SPL, true, RAG><<<dim3((unsigned)(a.B * groups), (unsigned)a.nseg), block, 0, stream>>>(a);
+}
+// Rows of whole 16-byte pieces take the kernel with buffer-addressed accesses, all others the one for any row length.
+// Fewer than 16 states dealt out to the waves: kernels built for 1 or 2 slots per lane.
+template <typename T, bool RAG>
+static void launch_fwd_dpp(const FwdArgs& a, hipStream_t stream)
+{
+    if (a.flags & F_EXACT_ZOH_B) return launch_fwd_dpp_t<T, true, STATES_PER_LANE, RAG>(a, stream);
+    const int spl = slots_for(a.N, a.il);
+    if (spl == 1) return launch_fwd_dpp_t<T, false, 1, RAG>(a, stream);
+    if (spl == 2) return launch_fwd_dpp_t<T, false, 2, RAG>(a, stream);
+    launch_fwd_dpp_t<T, false, STATES_PER_LANE, RAG>(a, stream);
 }
 
-template <typename T, bool VEC, bool FULLN, bool ZOH>
-static void launch_fwd_t(const FwdArgs& a, hipStream_t stream)
+// Real state, selective B and C, fewer than 8 steps or rows beyond the kernels above: the scalar path (from the
+// repacked copy of B and C if there is one).
+template <typename T, bool ZOH>
+static void launch_fwd_scalar(const FwdArgs& a, hipStream_t stream)
 {
     const int groups = (a.D + ROWS - 1) / ROWS;
-    const dim3 block(THREADS);
-    // time-invariant B and/or C: never split (the planner keeps nseg == 1 for them)
+    const dim3 block(THREADS), main_grid((unsigned)(a.B * groups), (unsigned)a.nseg);
+    if (a.nseg > 1) {
+        const dim3 agg_grid((unsigned)(a.B * groups), (unsigned)(a.nseg - 1));
+        if (a.bcs) scan_fwd_kernel<T, false, false, true, ZOH, 0, false, true><<<agg_grid, block, 0, stream>>>(a);
+        else scan_fwd_kernel<T, false, false, true, ZOH><<<agg_grid, block, 0, stream>>>(a);
+        const long n = (long)a.B * a.D * NPAD;
+        carry_fwd_kernel<<<dim3((unsigned)((n + 255) / 256)), dim3(256), 0, stream>>>(a);
+    }
+    if (a.bcs) scan_fwd_kernel<T, false, false, false, ZOH, 0, false, true><<<main_grid, block, 0, stream>>>(a);
+    else scan_fwd_kernel<T, false, false, false, ZOH><<<main_grid, block, 0, stream>>>(a);
+}
+
+// complex state and time-invariant B and / or C (the latter never split: the planner keeps nseg == 1 for them)
+template <typename T, bool VEC, bool FULLN, bool ZOH>
+static void launch_fwd_variant(const FwdArgs& a, hipStream_t stream)
+{
     const int bcfix = ((a.flags & F_B_FIXED) ? 1 : 0) | ((a.flags & F_C_FIXED) ? 2 : 0);
     if constexpr (!ZOH) {
         if (a.flags & F_COMPLEX) {
@@ -1173,13 +1264,26 @@ static void launch_fwd_t(const FwdArgs& a, hipStream_t stream)
     }
     if (bcfix == 1) return launch_fwd_fixed<T, VEC, FULLN, ZOH, 1>(a, stream);
     if (bcfix == 2) return launch_fwd_fixed<T, VEC, FULLN, ZOH, 2>(a, stream);
-    if (bcfix == 3) return launch_fwd_fixed<T, VEC, FULLN, ZOH, 3>(a, stream);
-    if constexpr (VEC && !FULLN && !ZOH) {   // fewer than 16 states dealt out to the waves: kernels built for 1 or 2 slots per lane
-        const int spl = slots_for(a.N, a.il);
-        if (spl == 1) return launch_fwd_selective<T, VEC, FULLN, ZOH, 1>(a, stream);
-        if (spl == 2) return launch_fwd_selective<T, VEC, FULLN, ZOH, 2>(a, stream);
+    launch_fwd_fixed<T, VEC, FULLN, ZOH, 3>(a, stream);
+}
+
+template <typename T>
+static void launch_fwd_io(const FwdArgs& a, hipStream_t stream)
+{
+    const bool zoh = a.flags & F_EXACT_ZOH_B, fulln = a.N == NPAD;
+    if (!(a.flags & (F_B_FIXED | F_C_FIXED | F_COMPLEX))) {
+        if (a.vec_ok) return launch_fwd_dpp<T, false>(a, stream);
+        if (a.dpp_ok) return launch_fwd_dpp<T, true>(a, stream);
+        if (zoh) return launch_fwd_scalar<T, true>(a, stream);
+        return launch_fwd_scalar<T, false>(a, stream);
     }
-    launch_fwd_selective<T, VEC, FULLN, ZOH, STATES_PER_LANE>(a, stream);
+    if (zoh) {   // built for the fastest and the most general shape only
+        if (a.vec_ok && fulln) return launch_fwd_variant<T, true, true, true>(a, stream);
+        return launch_fwd_variant<T, false, false, true>(a, stream);
+    }
+    if (a.vec_ok && fulln) return launch_fwd_variant<T, true, true, false>(a, stream);
+    if (a.vec_ok) return launch_fwd_variant<T, true, false, false>(a, stream);
+    launch_fwd_variant<T, false, false, false>(a, stream);
 }
 
 int launch_fwd(const FwdArgs& a, int io_dtype, hipStream_t stream)
@@ -1192,24 +1296,8 @@ int launch_fwd(const FwdArgs& a, int io_dtype, hipStream_t stream)
         }
         return hipGetLastError() == hipSuccess ? 0 : -1;
     }
-    const bool fulln = a.N == NPAD;
-    if (a.flags & F_EXACT_ZOH_B) {  // the variant is built for the fastest and the most general shape only
-        if (io_dtype == 0) {
-            if (a.vec_ok && fulln) launch_fwd_t<float, true, true, true>(a, stream);
-            else launch_fwd_t<float, false, false, true>(a, stream);
-        } else {
-            if (a.vec_ok && fulln) launch_fwd_t<bf16_t, true, true, true>(a, stream);
-            else launch_fwd_t<bf16_t, false, false, true>(a, stream);
-        }
-    } else if (io_dtype == 0) {
-        if (a.vec_ok && fulln) launch_fwd_t<float, true, true, false>(a, stream);
-        else if (a.vec_ok) launch_fwd_t<float, true, false, false>(a, stream);
-        else launch_fwd_t<float, false, false, false>(a, stream);
-    } else {
-        if (a.vec_ok && fulln) launch_fwd_t<bf16_t, true, true, false>(a, stream);
-        else if (a.vec_ok) launch_fwd_t<bf16_t, true, false, false>(a, stream);
-        else launch_fwd_t<bf16_t, false, false, false>(a, stream);
-    }
+    if (io_dtype == 0) launch_fwd_io<float>(a, stream);
+    else launch_fwd_io<bf16_t>(a, stream);
     return hipGetLastError() == hipSuccess ? 0 : -1;
 }
 
