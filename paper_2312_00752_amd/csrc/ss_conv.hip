@@ -12,6 +12,7 @@
 
 #include "ss_conv.h"
 #include "ss_device.h"
+#include "ss_kernels.h"
 
 namespace ss {
 
@@ -21,12 +22,18 @@ constexpr int PIECE = WAVE * 8;          // steps one wave covers per pass
 
 struct ConvArgs {
     int B, D, L, W;
+    int ld_v;   // elements between rows of out (forward) / dout (backward); L, or a multiple of 8 beyond it: the rest of a row of out is written as zeros
     unsigned flags;
     const void *x, *state_in, *dout;
     const float *w, *bias;
     void *out, *state_out, *dx;
     float *dw, *dbias;
 };
+
+// How the rows of a call are read and written: one element at a time (fewer than 8 steps), in whole aligned
+// 16-byte pieces (L a multiple of 8), or in pieces at element alignment (any other length: the piece that
+// reaches past the end is read from inside the row and shifted into place, see row_piece).
+enum { ROWS_SHORT, ROWS_WHOLE, ROWS_ANY };
 
 template <typename T> __device__ __forceinline__ float io_to_f32(T v);
 template <> __device__ __forceinline__ float io_to_f32<float>(float v) { return v; }
@@ -52,34 +59,28 @@ __device__ __forceinline__ float before_start(const T* __restrict__ state_row, i
     return (state_row != nullptr && idx >= 0) ? io_to_f32<T>(state_row[idx]) : 0.0f;
 }
 
-// xs[0..2] = x[t0-3..t0-1], xs[3..10] = x[t0..t0+7] (zero past the end of the row).
-template <typename T, bool VEC>
+// xs[0..2] = x[t0-3..t0-1], xs[3..10] = x[t0..t0+7] (zero past the end of the row); one element at a time.
+template <typename T>
 __device__ __forceinline__ void load_window(const T* __restrict__ row, const T* __restrict__ state_row, int t0,
                                             int L, int W, float (&xs)[HALO + 8])
 {
     const int nvalid = min(max(L - t0, 0), 8);
     float cur[8];
-    io8<T>::unpack(io8<T>::template load<VEC>(row + t0, nvalid), cur);
+    io8<T>::unpack(io8<T>::template load<false>(row + t0, nvalid), cur);
 #pragma unroll
     for (int j = 0; j < 8; ++j) xs[HALO + j] = cur[j];
-    if (VEC && t0 > 0 && nvalid > 0) {
-        // t0 is a multiple of 8, so the four samples in front of the slice are aligned
-        float h[4];
-        io4<T>::unpack(io4<T>::template load<true>(row + t0 - 4, 4), h);
-        xs[0] = h[1]; xs[1] = h[2]; xs[2] = h[3];
-    } else {
 #pragma unroll
-        for (int j = 0; j < HALO; ++j) {
-            const int t = t0 - HALO + j;
-            xs[j] = (nvalid == 0) ? 0.0f : (t >= 0 ? io_to_f32<T>(row[t]) : before_start<T>(state_row, t, W));
-        }
+    for (int j = 0; j < HALO; ++j) {
+        const int t = t0 - HALO + j;
+        xs[j] = (nvalid == 0) ? 0.0f : (t >= 0 ? io_to_f32<T>(row[t]) : before_start<T>(state_row, t, W));
     }
 }
 
-// The same for rows of whole 8-step slices (L a multiple of 8), in two halves so that all the
-// loads of a unit are issued back to back and waited for once: branch-free buffer loads (an
-// offset out of range returns zeros), where the pointer form above waits for each conditional
-// load in turn.  `next` additionally fetches the 4 samples after the slice.
+// The same for rows of 8 steps and more, in two halves so that all the loads of a unit are issued back to
+// back and waited for once, where the form above waits for each conditional load in turn.  Rows of whole
+// slices (L a multiple of 8): branch-free buffer loads (an offset out of range returns zeros); others: loads
+// at element alignment from clamped places, shifted and masked when unpacked.  `next` additionally fetches
+// the 4 samples after the slice.
 template <typename T>
 struct window_raw {
     typename io8<T>::raw cur;
@@ -88,6 +89,34 @@ struct window_raw {
 };
 template <typename T>
 __device__ __forceinline__ uint32_t row_bytes(int L) { return (uint32_t)L * (uint32_t)sizeof(T); }   // rows below 2^31 bytes (checked by the host)
+template <typename T, bool NEXT>
+__device__ __forceinline__ window_raw<T> issue_window_any(const T* row, const T* state_row, int t0, int L, int W)
+{
+    window_raw<T> r;
+    const uint32_t esz = (uint32_t)sizeof(T);
+    r.cur = io8<T>::load_elem(row, (uint32_t)row_piece(t0, 8, L) * esz);
+    r.halo = io4<T>::load_elem(row, (uint32_t)row_piece(max(t0 - 4, 0), 4, L) * esz);
+    if (NEXT) r.next = io4<T>::load_elem(row, (uint32_t)row_piece(t0 + 8, 4, L) * esz);
+    const T* const st = state_row ? state_row : row;   // W - 1 samples, or a row of at least 8
+#pragma unroll
+    for (int j = 0; j < HALO; ++j) {
+        const T v = st[max(min(j - (TAPS - W), W - 2), 0)];
+        if constexpr (sizeof(T) == 2) r.st[j] = v; else r.st[j] = __float_as_uint(v);
+    }
+    return r;
+}
+// after issue_window_any: shifts the pieces into place and clears what lies outside the row
+template <typename T, bool NEXT>
+__device__ __forceinline__ void settle_window(window_raw<T>& r, bool has_state, int t0, int L, int W)
+{
+    if (t0 + 12 > L) {   // only the last lanes of a row
+        io8<T>::drop(r.cur, t0 - row_piece(t0, 8, L));
+        if (t0 > 0) io4<T>::drop(r.halo, t0 - 4 - row_piece(t0 - 4, 4, L));
+        if (NEXT) io4<T>::drop(r.next, t0 + 8 - row_piece(t0 + 8, 4, L));
+    }
+#pragma unroll
+    for (int j = 0; j < HALO; ++j) r.st[j] = has_state && j >= TAPS - W ? r.st[j] : 0u;
+}
 template <typename T, bool NEXT>
 __device__ __forceinline__ window_raw<T> issue_window(rsrc_t brow, rsrc_t bstate, int t0, int L, int W)
 {
@@ -130,7 +159,9 @@ __device__ __forceinline__ float conv_at(const float (&k4)[TAPS], float bias, co
 
 // ---- forward --------------------------------------------------------------------------------
 // One wave per (row, piece); grid = ceil(B*D*pieces / NWAVES) workgroups.
-template <typename T, bool VEC, bool SILU>
+// Bound by HBM.  ROWS_ANY at 8 x 1536 x 2047 bf16: 60 -> 24 us (2048 steps: 21); its backward kernel, which has
+// five misaligned accesses to the forward's three, 105 -> 55 us (2048 steps: 34).
+template <typename T, int KIND, bool SILU>
 __global__ __launch_bounds__(THREADS) void conv_fwd_kernel(const ConvArgs a)
 {
     const int lane = threadIdx.x & (WAVE - 1);
@@ -150,13 +181,18 @@ __global__ __launch_bounds__(THREADS) void conv_fwd_kernel(const ConvArgs a)
     const float bias = (a.flags & SS_CONV_HAS_BIAS) ? a.bias[d] : 0.0f;
 
     float xs[HALO + 8];
-    if constexpr (VEC) {
+    if constexpr (KIND == ROWS_ANY) {
+        float unused[4];
+        window_raw<T> wr = issue_window_any<T, false>(row, state_row, t0, a.L, a.W);
+        settle_window<T, false>(wr, state_row != nullptr, t0, a.L, a.W);
+        unpack_window<T, false>(wr, t0, xs, unused);
+    } else if constexpr (KIND == ROWS_WHOLE) {
         const rsrc_t brow = make_rsrc(row, row_bytes<T>(a.L));
         const rsrc_t bstate = make_rsrc(state_row ? state_row : row, state_row ? (uint32_t)(a.W - 1) * (uint32_t)sizeof(T) : 0u);
         float unused[4];
         unpack_window<T, false>(issue_window<T, false>(brow, bstate, t0, a.L, a.W), t0, xs, unused);
     } else {
-        load_window<T, VEC>(row, state_row, t0, a.L, a.W, xs);
+        load_window<T>(row, state_row, t0, a.L, a.W, xs);
     }
     float o[8];
 #pragma unroll
@@ -165,7 +201,18 @@ __global__ __launch_bounds__(THREADS) void conv_fwd_kernel(const ConvArgs a)
         o[j] = SILU ? v * sigmoid_fast(v) : v;
     }
     const int nvalid = min(a.L - t0, 8);
-    io8<T>::template store<VEC>(static_cast<T*>(a.out) + (size_t)r * a.L + t0, o, nvalid);
+    T* const orow = static_cast<T*>(a.out) + (size_t)r * a.ld_v;
+    if constexpr (KIND == ROWS_ANY) {
+        if (a.ld_v > a.L) {   // a padded pitch: the slice is whole, zeros past the end
+#pragma unroll
+            for (int j = 0; j < 8; ++j) o[j] = j < nvalid ? o[j] : 0.0f;
+            io8<T>::store_elem(orow, (uint32_t)t0 * (uint32_t)sizeof(T), io8<T>::pack(o), 8);
+        } else {
+            io8<T>::store_elem(orow, (uint32_t)t0 * (uint32_t)sizeof(T), io8<T>::pack(o), nvalid);
+        }
+    } else {
+        io8<T>::template store<KIND == ROWS_WHOLE>(orow + t0, o, nvalid);
+    }
 
     if ((a.flags & SS_CONV_WRITE_STATE) && t0 + 8 >= a.L) {  // the lane that holds the last sample
         T* so = static_cast<T*>(a.state_out) + (size_t)r * (a.W - 1);
@@ -191,7 +238,7 @@ __global__ void conv_state_copy_kernel(const T* __restrict__ in, T* __restrict__
 // dx[t] = sum_j k4[j] * dv[t+3-j], dv = dout * SiLU'(v);  dk4[j] = sum_{b,t} dv[t] x[t-3+j].
 // grid = (D, nsplit): the waves of column d share out its B*pieces (row, piece) units, keep
 // the tap and bias gradients in registers and add them to dw/dbias once at the end.
-template <typename T, bool VEC, bool SILU>
+template <typename T, int KIND, bool SILU>
 __global__ __launch_bounds__(THREADS) void conv_bwd_kernel(const ConvArgs a)
 {
     const int lane = threadIdx.x & (WAVE - 1);
@@ -211,13 +258,26 @@ __global__ __launch_bounds__(THREADS) void conv_bwd_kernel(const ConvArgs a)
         const size_t r = (size_t)b * a.D + d;
         const int t0 = piece * PIECE + lane * 8;
         const T* row = static_cast<const T*>(a.x) + r * a.L;
-        const T* grow = static_cast<const T*>(a.dout) + r * a.L;
+        const T* grow = static_cast<const T*>(a.dout) + r * a.ld_v;
         const T* state_row = (a.flags & SS_CONV_HAS_STATE) ? static_cast<const T*>(a.state_in) + r * (a.W - 1) : nullptr;
         const int nvalid = min(max(a.L - t0, 0), 8);
 
         float xs[HALO + 8], g[8], dv[8 + HALO];
-        float xn[4] = {0.f, 0.f, 0.f, 0.f}, gn[4] = {0.f, 0.f, 0.f, 0.f};   // VEC: x and dout of the 4 steps after the slice
-        if constexpr (VEC) {
+        float xn[4] = {0.f, 0.f, 0.f, 0.f}, gn[4] = {0.f, 0.f, 0.f, 0.f};   // x and dout of the 4 steps after the slice (8 steps and more)
+        if constexpr (KIND == ROWS_ANY) {
+            const uint32_t esz = (uint32_t)sizeof(T);
+            window_raw<T> wr = issue_window_any<T, true>(row, state_row, t0, a.L, a.W);
+            typename io8<T>::raw rg = io8<T>::load_elem(grow, (uint32_t)row_piece(t0, 8, a.L) * esz);
+            typename io4<T>::raw rgn = io4<T>::load_elem(grow, (uint32_t)row_piece(t0 + 8, 4, a.L) * esz);
+            settle_window<T, true>(wr, state_row != nullptr, t0, a.L, a.W);
+            if (t0 + 12 > a.L) {
+                io8<T>::drop(rg, t0 - row_piece(t0, 8, a.L));
+                io4<T>::drop(rgn, t0 + 8 - row_piece(t0 + 8, 4, a.L));
+            }
+            unpack_window<T, true>(wr, t0, xs, xn);
+            io8<T>::unpack(rg, g);
+            io4<T>::unpack(rgn, gn);
+        } else if constexpr (KIND == ROWS_WHOLE) {
             const rsrc_t brow = make_rsrc(row, row_bytes<T>(a.L));
             const rsrc_t bgrow = make_rsrc(grow, row_bytes<T>(a.L));
             const rsrc_t bstate = make_rsrc(state_row ? state_row : row, state_row ? (uint32_t)(a.W - 1) * (uint32_t)sizeof(T) : 0u);
@@ -229,8 +289,8 @@ __global__ __launch_bounds__(THREADS) void conv_bwd_kernel(const ConvArgs a)
             io8<T>::unpack(rg, g);
             io4<T>::unpack(rgn, gn);
         } else {
-            load_window<T, VEC>(row, state_row, t0, a.L, a.W, xs);
-            io8<T>::unpack(io8<T>::template load<VEC>(grow + t0, nvalid), g);
+            load_window<T>(row, state_row, t0, a.L, a.W, xs);
+            io8<T>::unpack(io8<T>::template load<false>(grow + t0, nvalid), g);
         }
 #pragma unroll
         for (int j = 0; j < 8; ++j) {
@@ -253,13 +313,13 @@ __global__ __launch_bounds__(THREADS) void conv_bwd_kernel(const ConvArgs a)
             float xe[2 * HALO];   // x[t0+5 .. t0+10]
 #pragma unroll
             for (int j = 0; j < 2 * HALO; ++j) {
-                if constexpr (VEC) xe[j] = j < HALO ? xs[HALO + 5 + j] : xn[j - HALO];
+                if constexpr (KIND != ROWS_SHORT) xe[j] = j < HALO ? xs[HALO + 5 + j] : xn[j - HALO];
                 else xe[j] = (t0 + 5 + j < a.L) ? io_to_f32<T>(row[t0 + 5 + j]) : 0.0f;
             }
 #pragma unroll
             for (int j = 0; j < HALO; ++j) {
                 float gj;
-                if constexpr (VEC) gj = gn[j];
+                if constexpr (KIND != ROWS_SHORT) gj = gn[j];
                 else gj = (t0 + 8 + j < a.L) ? io_to_f32<T>(grow[t0 + 8 + j]) : 0.0f;
                 if (SILU) {
                     const float v = conv_at(k4, bias, xe + j);
@@ -278,7 +338,8 @@ __global__ __launch_bounds__(THREADS) void conv_bwd_kernel(const ConvArgs a)
 #pragma unroll
             for (int i = 0; i < TAPS; ++i) gk[i] = fmaf(dv[j], xs[j + i], gk[i]);
         }
-        io8<T>::template store<VEC>(static_cast<T*>(a.dx) + r * a.L + t0, o, nvalid);
+        if constexpr (KIND == ROWS_ANY) io8<T>::store_elem(static_cast<T*>(a.dx) + r * a.L, (uint32_t)t0 * (uint32_t)sizeof(T), io8<T>::pack(o), nvalid);
+        else io8<T>::template store<KIND == ROWS_WHOLE>(static_cast<T*>(a.dx) + r * a.L + t0, o, nvalid);
     }
 
 #pragma unroll
@@ -345,18 +406,18 @@ __global__ void conv_step_kernel(T* __restrict__ state, const T* __restrict__ x_
 }
 
 // ---- host ---------------------------------------------------------------------------------------
-template <typename T, bool VEC>
+template <typename T, int KIND>
 hipError_t launch_conv_fwd_t(const ConvArgs& a, hipStream_t st)
 {
     const long pieces = (a.L + PIECE - 1) / PIECE;
     const long units = (long)a.B * a.D * pieces;
     const dim3 grid((unsigned)((units + NWAVES - 1) / NWAVES));
-    if (a.flags & SS_CONV_SILU) hipLaunchKernelGGL((conv_fwd_kernel<T, VEC, true>), grid, dim3(THREADS), 0, st, a);
-    else hipLaunchKernelGGL((conv_fwd_kernel<T, VEC, false>), grid, dim3(THREADS), 0, st, a);
+    if (a.flags & SS_CONV_SILU) hipLaunchKernelGGL((conv_fwd_kernel<T, KIND, true>), grid, dim3(THREADS), 0, st, a);
+    else hipLaunchKernelGGL((conv_fwd_kernel<T, KIND, false>), grid, dim3(THREADS), 0, st, a);
     return hipGetLastError();
 }
 
-template <typename T, bool VEC>
+template <typename T, int KIND>
 hipError_t launch_conv_bwd_t(const ConvArgs& a, hipStream_t st)
 {
     const long pieces = (a.L + PIECE - 1) / PIECE;
@@ -367,17 +428,18 @@ hipError_t launch_conv_bwd_t(const ConvArgs& a, hipStream_t st)
     nsplit = nsplit < most ? nsplit : most;
     nsplit = nsplit < 1 ? 1 : (nsplit > 65535 ? 65535 : nsplit);
     const dim3 grid((unsigned)a.D, (unsigned)nsplit);
-    if (a.flags & SS_CONV_SILU) hipLaunchKernelGGL((conv_bwd_kernel<T, VEC, true>), grid, dim3(THREADS), 0, st, a);
-    else hipLaunchKernelGGL((conv_bwd_kernel<T, VEC, false>), grid, dim3(THREADS), 0, st, a);
+    if (a.flags & SS_CONV_SILU) hipLaunchKernelGGL((conv_bwd_kernel<T, KIND, true>), grid, dim3(THREADS), 0, st, a);
+    else hipLaunchKernelGGL((conv_bwd_kernel<T, KIND, false>), grid, dim3(THREADS), 0, st, a);
     return hipGetLastError();
 }
 
 template <typename T>
 hipError_t launch_conv_t(const ConvArgs& a, bool bwd, hipStream_t st)
 {
-    const bool vec = a.L % 8 == 0;
-    if (bwd) return vec ? launch_conv_bwd_t<T, true>(a, st) : launch_conv_bwd_t<T, false>(a, st);
-    return vec ? launch_conv_fwd_t<T, true>(a, st) : launch_conv_fwd_t<T, false>(a, st);
+    const int kind = a.L % 8 == 0 ? ROWS_WHOLE : (a.L >= 8 ? ROWS_ANY : ROWS_SHORT);
+    if (kind == ROWS_WHOLE) return bwd ? launch_conv_bwd_t<T, ROWS_WHOLE>(a, st) : launch_conv_fwd_t<T, ROWS_WHOLE>(a, st);
+    if (kind == ROWS_ANY) return bwd ? launch_conv_bwd_t<T, ROWS_ANY>(a, st) : launch_conv_fwd_t<T, ROWS_ANY>(a, st);
+    return bwd ? launch_conv_bwd_t<T, ROWS_SHORT>(a, st) : launch_conv_fwd_t<T, ROWS_SHORT>(a, st);
 }
 
 }  // namespace ss
@@ -418,6 +480,7 @@ ss::ConvArgs make_conv_args(const ss_conv_params* p)
 {
     ss::ConvArgs a{};
     a.B = p->batch; a.D = p->dim; a.L = p->seqlen; a.W = p->width;
+    a.ld_v = p->seqlen;
     a.flags = p->flags;
     if (p->width == 1) a.flags &= ~(unsigned)(SS_CONV_HAS_STATE | SS_CONV_WRITE_STATE);
     a.x = p->x; a.state_in = p->state_in; a.w = p->w; a.bias = p->bias;

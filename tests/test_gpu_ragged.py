@@ -66,3 +66,28 @@ def test_ragged_rows(io, batch, seqlen, dim, dstate, zoh):
         util.assert_close(grads[k], rb[ORACLE_NAME.get(k, k)], io, k, exact_inputs=exact)
     for k, (pool, view) in outs.items():
         assert bool((pool[:PAD] == PATTERN).all()) and bool((pool[PAD + view.numel():] == PATTERN).all()), k
+
+
+@pytest.mark.parametrize("io", ["f32", "bf16"])
+@pytest.mark.parametrize("batch,dim,seqlen,width", [(2, 3, 9, 4), (1, 2, 11, 3), (3, 5, 15, 2), (1, 4, 509, 4), (2, 3, 517, 4),
+                                                    (1, 2, 1021, 1)])
+def test_ragged_convolution(io, batch, dim, seqlen, width):
+    import torch
+    from oracle import conv_oracle as cv
+    from paper_2312_00752_amd import binding as B
+    w = wl.make_conv_inputs(batch, dim, seqlen, width, io, seed=seqlen)
+    tio = torch.bfloat16 if io == "bf16" else torch.float32
+    g = {}
+    for k in ("x", "dout"):
+        pool, g[k] = _guarded(w[k].shape, tio, float("nan"))
+        g[k].copy_(torch.from_numpy(w[k]))
+    wt, bias = torch.from_numpy(w["w"]).cuda(), torch.from_numpy(w["bias"]).cuda()
+    pool, out = _guarded(w["x"].shape, tio, PATTERN)
+    B.ss_conv_fwd(g["x"], wt, bias, out=out)
+    grads = B.ss_conv_bwd(g["dout"], g["x"], wt, bias)
+    torch.cuda.synchronize()
+    ref, rg = cv.conv_fwd(w["x"], w["w"], w["bias"], None, True), cv.conv_bwd(w["x"], w["w"], w["dout"], w["bias"], None, True)
+    util.assert_close(out, ref["out"], io, "out")
+    for k in ("dx", "dw", "dbias"):
+        util.assert_close(grads[k], rg[k], io, k)
+    assert bool((pool[:PAD] == PATTERN).all()) and bool((pool[PAD + out.numel():] == PATTERN).all())
