@@ -83,33 +83,76 @@ __device__ __forceinline__ void reduce_take(float (*red)[RED_PITCH], float* acc,
     if (p == 0) acc[(vi & 3) * BT + (vi >> 2)] = s;
     wave_lds_fence();
 }
-// The same for a kernel built for SPL slots per lane: a group of steps then yields 4 * SPL values, and the
-// 16-value tile takes 4 / SPL groups before it is summed.  Value row = (group within the tile) * 4 SPL +
-// step j * SPL + slot k; the totals of slot k at step t of the block go to acc[k * BT + t].
-template <int SPL>
-__device__ __forceinline__ void reduce_put_n(const float (&v)[RED_VALUES], float (*red)[RED_PITCH], int lane, int g)
+// The same sums without LDS, for kernels whose values come out of DPP arithmetic anyway: a tree over the
+// lanes that halves the number of registers at each level.  Level i takes two registers to one: lanes whose
+// selecting bit is clear keep the first one's pair sums, the others the second one's, at two instructions per
+// result (a lane swap and an add, or two adds whose DPP masks write one half each): 2.0 vector instructions per
+// value against 1.3 through the LDS tile above, but no LDS traffic, which was half of this kernel's, no wait for
+// it and four spilled registers fewer: backward of 8 x 4096 x 2048 bf16 0.74 -> 0.66 ms, forward + backward of
+// 8 x 1536 x 2048 606 -> 571 us, with the exact zero-order hold 1250 -> 1177 us.
+//   level:          0               1               2             3                  4              5
+//   partner:        lane ^ 32       lane ^ 16       lane ^ 8      lane ^ 7           lane ^ 1       lane ^ 2
+//   selecting bit:  5               4               3             2                  0              1
+template <int LEVEL>
+__device__ __forceinline__ float merge_lanes(float a, float b, int lane)
 {
-    constexpr int GPT = STATES_PER_LANE / SPL;   // groups per tile
-    const int base = (g % GPT) * GROUP_T * SPL;
+    if constexpr (LEVEL == 0) {
+        const auto x = __builtin_amdgcn_permlane32_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+        return __uint_as_float(x[0]) + __uint_as_float(x[1]);
+    } else if constexpr (LEVEL == 1) {
+        const auto x = __builtin_amdgcn_permlane16_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+        return __uint_as_float(x[0]) + __uint_as_float(x[1]);
+    } else if constexpr (LEVEL == 2) {
+        float r;   // the leading wait states cover operands written just before (a DPP read needs two)
+        asm("s_nop 1\n\t"
+            "v_add_f32_dpp %0, %1, %1 row_ror:8 row_mask:0xf bank_mask:0x3\n\t"
+            "v_add_f32_dpp %0, %2, %2 row_ror:8 row_mask:0xf bank_mask:0xc"
+            : "=&v"(r) : "v"(a), "v"(b));
+        return r;
+    } else if constexpr (LEVEL == 3) {
+        float r;
+        asm("s_nop 1\n\t"
+            "v_add_f32_dpp %0, %1, %1 row_half_mirror row_mask:0xf bank_mask:0x5\n\t"
+            "v_add_f32_dpp %0, %2, %2 row_half_mirror row_mask:0xf bank_mask:0xa"
+            : "=&v"(r) : "v"(a), "v"(b));
+        return r;
+    } else {
+        const bool odd = (lane >> (LEVEL - 4)) & 1;
+        const float keep = odd ? b : a, give = odd ? a : b;
+        constexpr int ctrl = LEVEL == 4 ? 0xb1 : 0x4e;   // quad_perm [1,0,3,2], [2,3,0,1]
+        return keep + __uint_as_float(__builtin_amdgcn_update_dpp(0, __float_as_uint(give), ctrl, 0xf, 0xf, true));
+    }
+}
+// Sums over the 64 rows of a wave of the 16 * SPL values (index e = step * SPL + slot) that a block's steps
+// yield for one of dB, dC.  A group of four steps is merged to one register as soon as it is complete
+// (merge_group), the four groups at the end (merge_block); lane l then holds the total of value lane_value(l).
+// A kernel for fewer than four slots has levels left over: those lanes hold copies.
+template <int SPL>
+__device__ __forceinline__ float merge_group(const float (&v)[RED_VALUES], int lane)
+{
+    auto at = [&](int e) { return v[(e / SPL) * STATES_PER_LANE + e % SPL]; };   // slot k of step j sits at 4 j + k
+    float a[2 * SPL];
 #pragma unroll
-    for (int j = 0; j < GROUP_T; ++j)
+    for (int i = 0; i < 2 * SPL; ++i) a[i] = merge_lanes<0>(at(2 * i), at(2 * i + 1), lane);
+    float b[SPL];
 #pragma unroll
-        for (int k = 0; k < SPL; ++k) red[base + j * SPL + k][lane] = v[j * STATES_PER_LANE + k];
-    wave_lds_fence();
+    for (int i = 0; i < SPL; ++i) b[i] = merge_lanes<1>(a[2 * i], a[2 * i + 1], lane);
+    if constexpr (SPL == 1) return b[0];
+    else if constexpr (SPL == 2) return merge_lanes<2>(b[0], b[1], lane);
+    else return merge_lanes<3>(merge_lanes<2>(b[0], b[1], lane), merge_lanes<2>(b[2], b[3], lane), lane);
 }
 template <int SPL>
-__device__ __forceinline__ void reduce_take_n(float (*red)[RED_PITCH], float* acc, int lane, int g_first)   // g_first: lowest group in the tile
+__device__ __forceinline__ float merge_block(const float (&s)[BT / GROUP_T], int lane)
 {
-    constexpr int GPT = STATES_PER_LANE / SPL;
-    const int p = lane >> 4, vi = lane & 15;
-    const float4* src = reinterpret_cast<const float4*>(&red[vi][16 * p]);
-    const float4 a0 = src[0], a1 = src[1], a2 = src[2], a3 = src[3];
-    float s = ((a0.x + a0.y) + (a0.z + a0.w)) + ((a1.x + a1.y) + (a1.z + a1.w)) +
-              ((a2.x + a2.y) + (a2.z + a2.w)) + ((a3.x + a3.y) + (a3.z + a3.w));
-    s = sum_over_lane_quarters(s);
-    const int gi = vi / (GROUP_T * SPL), j = (vi % (GROUP_T * SPL)) / SPL, k = vi % SPL;
-    if (p == 0) acc[k * BT + (g_first + gi) * GROUP_T + j] = s;
-    wave_lds_fence();
+    constexpr int L0 = SPL == 4 ? 4 : (SPL == 2 ? 3 : 2);
+    float r = merge_lanes<L0 + 1>(merge_lanes<L0>(s[0], s[1], lane), merge_lanes<L0>(s[2], s[3], lane), lane);
+    if constexpr (SPL == 1) asm("s_nop 1\n\tv_add_f32_dpp %0, %0, %0 quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf" : "+v"(r));
+    if constexpr (SPL <= 2) asm("s_nop 1\n\tv_add_f32_dpp %0, %0, %0 quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf" : "+v"(r));
+    return r;
+}
+__device__ __forceinline__ int lane_value(int lane)
+{
+    return ((lane >> 5) & 1) | ((lane >> 3) & 2) | ((lane >> 1) & 4) | ((lane << 1) & 8) | ((lane << 4) & 48);
 }
 
 // Same decomposition as the forward kernel (64 rows x 4 waves; wave w owns states
@@ -517,8 +560,6 @@ struct BwdSmemDpp {
     float dy[ROWS][BPAD];
     float pdd[NWAVES][ROWS][BPAD];
     float psb[NWAVES][ROWS][BPAD];
-    float red[NWAVES][RED_VALUES][RED_PITCH];
-    float dbc[NWAVES][2][STATES_PER_LANE][BT];
     float bcp[2][BT / GROUP_T][NPAD][GROUP_T];   // B (0) and C (1) of the block
 };
 
@@ -612,8 +653,9 @@ __global__ void __launch_bounds__(THREADS, ZOH ? 1 : 2) scan_bwd_dpp_kernel(cons
         else ag4[k] = a.seg_g[(seg_rows + srow) * NPAD + w * STATES_PER_LANE + k];
         dA[k] = 0.0f;
     }
-    float* const dbc = &sm.dbc[w][0][0][0];
-    float (*const red)[RED_PITCH] = sm.red[w];
+    // the value of the cross-row sums this lane ends up with: slot vk at step vt of a block
+    const int ve = lane_value(lane) & (BT * SPL - 1), vt = ve / SPL, vn = slot_state(w, ve % SPL, f.il);
+    const bool v_ok = vn < N && (lane_value(lane) < BT * SPL);
     const int pat = slot_state(w, lane & 3, f.il) * GROUP_T;   // in a group's [state][step] tile: the state of slot lane % 4
 
     const int nblocks = blk_end;
@@ -771,7 +813,7 @@ __global__ void __launch_bounds__(THREADS, ZOH ? 1 : 2) scan_bwd_dpp_kernel(cons
         // ---- B1: recompute the states of the block -----------------------------------------
         __builtin_amdgcn_s_setprio(2);
         constexpr int NG = BT / GROUP_T;
-        constexpr int GPT = STATES_PER_LANE / SPL;   // groups of steps per tile of the cross-row reduction
+        float sC[NG], sB[NG];   // a group's share of the cross-row sums
         f32x4_t as4[BT], hs4[BT];   // abar_t (exact ZOH: phi_t) and h_t
         {
             f32x4_t h4 = {hck4.x, hck4.y, hck4.z, hck4.w};
@@ -808,12 +850,10 @@ __global__ void __launch_bounds__(THREADS, ZOH ? 1 : 2) scan_bwd_dpp_kernel(cons
 #pragma unroll
                     for (int k = 0; k < SPL; ++k) dCv[j * STATES_PER_LANE + k] = dy * h4[k];
                 }
-                // the tile of the previous GPT groups is summed a group later, before this group's values go in
-                if (g > 0 && g % GPT == 0) reduce_take_n<SPL>(red, dbc + STATES_PER_LANE * BT, lane, g - GPT);
-                reduce_put_n<SPL>(dCv, red, lane, g);
+                sC[g] = merge_group<SPL>(dCv, lane);
             }
-            reduce_take_n<SPL>(red, dbc + STATES_PER_LANE * BT, lane, NG - GPT);
         }
+        const float dC_total = merge_block<SPL>(sC, lane);
         // ---- B2: adjoint recurrence, last step of the block first --------------------------
         __builtin_amdgcn_s_setprio(3);
 #pragma unroll
@@ -866,21 +906,14 @@ __global__ void __launch_bounds__(THREADS, ZOH ? 1 : 2) scan_bwd_dpp_kernel(cons
             }
             *reinterpret_cast<float4*>(&sm.pdd[w][lane][tl]) = make_float4(dd[0], dd[1], dd[2], dd[3]);
             *reinterpret_cast<float4*>(&sm.psb[w][lane][tl]) = make_float4(sb[0], sb[1], sb[2], sb[3]);
-            if (g < NG - 1 && (g + 1) % GPT == 0) reduce_take_n<SPL>(red, dbc, lane, g + 1);  // the tile of the GPT groups above
-            reduce_put_n<SPL>(dBv, red, lane, g);
+            sB[g] = merge_group<SPL>(dBv, lane);
         }
-        reduce_take_n<SPL>(red, dbc, lane, 0);
         // ---- flush this wave's dB/dC of the block to global memory -------------------------
-        wave_lds_fence();
-#pragma unroll
-        for (int i = 0; i < 2 * STATES_PER_LANE * BT / WAVE; ++i) {
-            const int idx = i * WAVE + lane;
-            const int which = idx / (STATES_PER_LANE * BT), k = (idx / BT) % STATES_PER_LANE, t = idx % BT;
-            const int n = slot_state(w, k, f.il);
-            if (k < SPL && n < N && tc + t < L) {
-                float* dst = (which ? a.dC : a.dB) + (long)b * a.dbc_bstride + (long)n * L + tc + t;
-                atomicAdd(dst, dbc[idx]);
-            }
+        const float dB_total = merge_block<SPL>(sB, lane);
+        if (v_ok && tc + vt < L) {
+            const long at = (long)b * a.dbc_bstride + (long)vn * L + tc + vt;
+            atomicAdd(a.dB + at, dB_total);
+            atomicAdd(a.dC + at, dC_total);
         }
         __syncthreads();
 
