@@ -1,7 +1,7 @@
 // The layer's projections (Algorithm 2 with the selection functions of Section 3.2: s_B, s_C linear in
 // the input; s_Delta in the low-rank form Linear_D(Linear_R(x)) of Section 3.6) and their gradients, as
 // this library's own kernels.  All of them are "skinny" products: one side of each is the (D, L) matrix
-// of a batch entry (u, delta, d delta, du), the other has R or R + 2N (128..160) rows, so they are
+// of a batch entry (u, delta, d delta, du), the other has R or R + 2N (8..192) rows, so they are
 // bound by reading or writing a (B, D, L) tensor once, not by arithmetic, and are built around that:
 // the big operand is read (or the big result written) exactly once, in 128-byte row pieces, and the
 // small operand is shared through LDS or the L2.
@@ -13,8 +13,8 @@
 // accumulator element i is row 4 * (l / 16) + i, column l % 16):
 //   gemm_nt_kernel    C = A B^T with both operands contiguous along the contraction index (the
 //                     weight gradients: contraction over L).  A workgroup takes 64 rows of the big
-//                     operand (a 16-row fragment per wave straight from global memory) against all
-//                     <= 160 rows of the small one, staged in 64-wide slabs through LDS.
+//                     operand (a 16-row fragment per wave straight from global memory) against up to
+//                     192 rows of the small one, staged in 64-wide slabs through LDS.
 //   gemm_rows_kernel  few output rows, long contraction over the ROWS of the (K, N) operand
 //                     ([r;B;C] = W_x u, dr = W_dt^T ddelta): that operand is contiguous along N, not
 //                     along the contraction index, so two rows at a time are interleaved into 32-bit
@@ -24,8 +24,8 @@
 //                     in registers as fragments; the product is formed transposed so that a lane
 //                     holds four consecutive columns, and leaves through an LDS tile as whole
 //                     128-byte row pieces.
-// gemm_generic_kernel takes every other shape, stride and dtype (64 x 64 tiles through LDS, 4 x 4
-// outputs per thread on the vector ALU): the float32 layer, odd sizes and the tiny per-token products.
+// gemm_generic_kernel takes every other stride and dtype (64 x 64 tiles through LDS, 4 x 4 outputs per
+// thread on the vector ALU): the float32 layer, sizes below 8 and the tiny per-token products.
 #include <hip/hip_runtime.h>
 #include <type_traits>
 
@@ -111,12 +111,16 @@ int launch_generic(const GemmArgs& g, hipStream_t stream)
 
 
 // ---- matrix-core kernels (bf16) -------------------------------------------------------------------
+// Each exists twice.  The plain form takes operands made of whole 16-byte pieces (pitches and batch strides
+// multiples of 8 elements, 16-byte aligned, contraction and columns whole slabs and tiles).  The RAG form takes
+// any size from 8 up and any pitch: pieces are read in one access at element alignment from inside the row
+// (row_piece), and only the last slab or tile, a uniform case, shifts the piece that reaches past the end into
+// place with zeros behind it; rows past the end re-read the last one and what comes of them is not stored.
+// Such sizes (sequences that are not a multiple of 64, widths that are not a multiple of 512 and so ranks that
+// are not a multiple of 16) used to take the general kernel: [r;B;C] and delta of 4 x 4096 x 1531 338 us each.
 typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
-// 16 bytes as a native vector: copies of it are plain loads and stores (a copy of the uint4 STRUCT is a
-// memcpy, and registers that are only ever memcpy'd into and out of stay in scratch memory)
-typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 union Frag8 { uint4 u; bf16x8_t v; };
-constexpr int MAXST = 10;          // the small operand has at most 160 rows
+constexpr int MAXST = 12;          // 16-row tiles of the small operand in one launch (192 rows); kernels are built for 6, 10 or 12
 constexpr int KSLAB = 64;          // contraction indices per step
 constexpr int KP = KSLAB + 8;      // LDS pitch of a slab row (bf16): 144 bytes, 16-byte aligned, off the banks
 constexpr int XPITCH = 64 + 4;     // LDS pitch of a row of pairs (32-bit)
@@ -129,23 +133,54 @@ __device__ __forceinline__ f32x4_t mfma_bf16(uint4 a, uint4 b, f32x4_t c)
     return __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa.v, fb.v, c, 0, 0, 0);
 }
 
+// Eight consecutive elements from index k of a row of n; native vectors, not the uint4 struct: a copy of that
+// struct is a memcpy, and registers that are only ever memcpy'd into and out of stay in scratch memory.
+template <bool RAG>
+__device__ __forceinline__ u32x4 piece(const bf16_t* __restrict__ row, int k, int n)
+{
+    if constexpr (RAG) return load_any<u32x4>(row + row_piece(k, 8, n), 0u);
+    else return *reinterpret_cast<const u32x4*>(row + k);
+}
+// The same with the non-temporal hint.
+template <bool RAG>
+__device__ __forceinline__ uint4 piece_stream(const bf16_t* __restrict__ row, int k, int n)
+{
+    typedef u32x4 any_t __attribute__((aligned(2)));
+    u32x4 v;
+    if constexpr (RAG) v = __builtin_nontemporal_load(reinterpret_cast<const any_t*>(row + row_piece(k, 8, n)));
+    else v = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(row + k));
+    return make_uint4(v.x, v.y, v.z, v.w);
+}
+// A piece read so, from index k on, zeros past the row's end.
+__device__ __forceinline__ u32x4 cut(u32x4 v, int k, int n) { return drop_front<16>(v, k - row_piece(k, 8, n)); }
+__device__ __forceinline__ uint4 cut(uint4 v, int k, int n)
+{
+    const u32x4 x = cut(u32x4{v.x, v.y, v.z, v.w}, k, n);
+    return make_uint4(x[0], x[1], x[2], x[3]);
+}
+
 // 16-byte pieces of an (S rows) x (64 columns) slab of a row-major bf16 matrix: piece p -> row p / 8,
-// columns 8 * (p % 8) ..+7; thread t takes pieces t, t + 256, ... (five cover 160 rows).  Pieces past
-// row S - 1 re-read the last row and land in LDS rows that no fragment reads (the LDS slab always
-// has 160 rows): a load under a per-lane condition would have to be waited for on the spot, to be
-// merged with the register's old value.
-__device__ __forceinline__ void slab_load(u32x4 (&x)[5], const bf16_t* __restrict__ src, long ld, int S, int k0, int tid)
+// columns 8 * (p % 8) ..+7; thread t takes pieces t, t + 256, ... (NST / 2 of them cover 16 NST rows).  Pieces
+// past row S - 1 re-read the last row and land in LDS rows whose products are not stored: a load under a
+// per-lane condition would have to be waited for on the spot, to be merged with the register's old value.
+template <bool RAG, int NST>
+__device__ __forceinline__ void slab_load(u32x4 (&x)[NST / 2], const bf16_t* __restrict__ src, long ld, int S, int k0, int K, int tid)
 {
 #pragma unroll
-    for (int e = 0; e < 5; ++e) {
+    for (int e = 0; e < NST / 2; ++e) {
         const int p = tid + 256 * e, row = min(p >> 3, S - 1);
-        x[e] = *reinterpret_cast<const u32x4*>(src + (long)row * ld + k0 + (p & 7) * 8);
+        x[e] = piece<RAG>(src + (long)row * ld, k0 + (p & 7) * 8, K);
     }
 }
-__device__ __forceinline__ void slab_store(const u32x4 (&x)[5], bf16_t (*dst)[KP], int tid)
+template <bool RAG, int NST>
+__device__ __forceinline__ void slab_store(u32x4 (&x)[NST / 2], bf16_t (*dst)[KP], int k0, int K, int tid)
 {
+    if (RAG && k0 + KSLAB > K) {   // uniform: the last slab
 #pragma unroll
-    for (int e = 0; e < 5; ++e) {
+        for (int e = 0; e < NST / 2; ++e) x[e] = cut(x[e], k0 + ((tid + 256 * e) & 7) * 8, K);
+    }
+#pragma unroll
+    for (int e = 0; e < NST / 2; ++e) {
         const int p = tid + 256 * e;
         *reinterpret_cast<u32x4*>(&dst[p >> 3][(p & 7) * 8]) = x[e];
     }
@@ -172,58 +207,58 @@ __device__ __forceinline__ void pair_rows(uint4 lo, uint4 hi, uint4& out0, uint4
 // moves from its registers into the other LDS buffer before the step's one barrier.  The operand that
 // streams from HBM is loaded with the non-temporal hint so that it does not push the small one out
 // of the L2.  Requests past the last slab re-read the last slab (never used) instead of branching, so
-// that the compiler's wait counts stay those of the steady state.
+// that the compiler's wait counts stay those of the steady state; the up to PD - 1 slabs left over are written
+// out behind the loop.
 constexpr int PD = 4;
 constexpr long ROWS_MIN_WGS = 512;   // two workgroups of gemm_rows_kernel fit on each of the 256 CUs
 constexpr int ROWS_MIN_SPLIT_K = 4096;   // shorter contractions lose more to the second launch than they gain (K = 1536: 21 -> 25 us)
-__device__ __forceinline__ uint4 load16_stream(const bf16_t* p)
-{
-    const u32x4 v = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(p));
-    return make_uint4(v.x, v.y, v.z, v.w);
-}
 
 // C[big][small] (or, OUT_T, C[small][big]), float32, = sum_k Big[big][k] Small[small][k] per batch entry.
-// grid (big rows / 64, batch).  K % (64 * PD) == 0, big rows % 64 == 0, S % 16 == 0, S <= 160.
-template <bool OUT_T>
-__global__ void __launch_bounds__(256) gemm_nt_kernel(const bf16_t* __restrict__ Big, long big_ld, long big_batch,
+// grid (M big rows / 64 rounded up, batch).  S <= 16 NST.  Plain: K % 64 == 0, M % 64 == 0, ldc and c_batch % 4 == 0.
+template <bool OUT_T, bool RAG, int NST>
+__global__ void __launch_bounds__(256, 2) gemm_nt_kernel(const bf16_t* __restrict__ Big, long big_ld, long big_batch,
                                                        const bf16_t* __restrict__ Small, long small_ld, long small_batch,
-                                                       float* __restrict__ C, long ldc, long c_batch, int S, int K)
+                                                       float* __restrict__ C, long ldc, long c_batch, int M, int S, int K)
 {
-    __shared__ __attribute__((aligned(16))) bf16_t Ss[2][MAXST * 16][KP];
+    __shared__ __attribute__((aligned(16))) bf16_t Ss[2][NST * 16][KP];
     const int tid = threadIdx.x, w = tid >> 6, lane = tid & 63, g = lane >> 4, j = lane & 15;
     const int d0 = blockIdx.x * 64;
     const long b = blockIdx.y;
-    const bf16_t* __restrict__ arow = Big + b * big_batch + (long)(d0 + 16 * w + j) * big_ld + 8 * g;
+    const bf16_t* __restrict__ arow = Big + b * big_batch + (long)(RAG ? min(d0 + 16 * w + j, M - 1) : d0 + 16 * w + j) * big_ld;
     const bf16_t* __restrict__ sm = Small + b * small_batch;
-    const int ST = S >> 4;
-    const int nsteps = K / KSLAB;
-    f32x4_t acc[MAXST];
+    const int ST = (S + 15) >> 4;
+    const int nsteps = (K + KSLAB - 1) / KSLAB;
+    f32x4_t acc[NST];
 #pragma unroll
-    for (int ct = 0; ct < MAXST; ++ct) acc[ct] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+    for (int ct = 0; ct < NST; ++ct) acc[ct] = f32x4_t{0.f, 0.f, 0.f, 0.f};
     // one named set of registers per slot, and the step written out per slot (a macro), so that every
     // register set is addressed statically
-    u32x4 sr0[5], sr1[5], sr2[5], sr3[5];
+    u32x4 sr0[NST / 2], sr1[NST / 2], sr2[NST / 2], sr3[NST / 2];
     uint4 ar0[2], ar1[2], ar2[2], ar3[2];
 #define SS_NT_ISSUE(s_, SR, AR)                                          \
     {                                                                    \
         const int k0_ = min((s_), nsteps - 1) * KSLAB;                   \
-        AR[0] = load16_stream(arow + k0_);                               \
-        AR[1] = load16_stream(arow + k0_ + 32);                          \
-        slab_load(SR, sm, small_ld, S, k0_, tid);                        \
+        AR[0] = piece_stream<RAG>(arow, k0_ + 8 * g, K);                 \
+        AR[1] = piece_stream<RAG>(arow, k0_ + 32 + 8 * g, K);            \
+        slab_load<RAG, NST>(SR, sm, small_ld, S, k0_, K, tid);           \
     }
     // step s_ out of LDS buffer BUF; this slot's registers are free again (its slab went into LDS a
     // step ago, its fragments are copied out first), the next slot's slab moves into the other buffer
 #define SS_NT_STEP(s_, BUF, SR, AR, SRN)                                                                              \
     {                                                                                                                 \
-        const uint4 a_cur[2] = {AR[0], AR[1]};                                                                        \
+        uint4 a_cur[2] = {AR[0], AR[1]};                                                                              \
+        if (RAG && ((s_) + 1) * KSLAB > K) {                                                                          \
+            a_cur[0] = cut(a_cur[0], (s_) * KSLAB + 8 * g, K);                                                        \
+            a_cur[1] = cut(a_cur[1], (s_) * KSLAB + 32 + 8 * g, K);                                                   \
+        }                                                                                                             \
         SS_NT_ISSUE((s_) + PD, SR, AR)                                                                                \
         _Pragma("unroll") for (int ks = 0; ks < 2; ++ks)                                                              \
-            _Pragma("unroll") for (int ct = 0; ct < MAXST; ++ct) if (ct < ST)                                         \
+            _Pragma("unroll") for (int ct = 0; ct < NST; ++ct) if (ct < ST)                                           \
             {                                                                                                         \
                 const uint4 bf = *reinterpret_cast<const uint4*>(&Ss[BUF][16 * ct + j][32 * ks + 8 * g]);             \
                 acc[ct] = mfma_bf16(a_cur[ks], bf, acc[ct]);                                                          \
             }                                                                                                         \
-        if ((s_) + 1 < nsteps) slab_store(SRN, Ss[(BUF) ^ 1], tid);                                                   \
+        if ((s_) + 1 < nsteps) slab_store<RAG, NST>(SRN, Ss[(BUF) ^ 1], ((s_) + 1) * KSLAB, K, tid);                  \
         __syncthreads();                                                                                              \
     }
     SS_NT_ISSUE(0, sr0, ar0)
@@ -234,78 +269,92 @@ __global__ void __launch_bounds__(256) gemm_nt_kernel(const bf16_t* __restrict__
     __builtin_amdgcn_sched_barrier(0);
     SS_NT_ISSUE(3, sr3, ar3)
     __builtin_amdgcn_sched_barrier(0);
-    slab_store(sr0, Ss[0], tid);
+    slab_store<RAG, NST>(sr0, Ss[0], 0, K, tid);
     __syncthreads();
-    for (int s0 = 0; s0 < nsteps; s0 += PD) {
+    int s0 = 0;
+    for (; s0 + PD <= nsteps; s0 += PD) {
         SS_NT_STEP(s0, 0, sr0, ar0, sr1)
         SS_NT_STEP(s0 + 1, 1, sr1, ar1, sr2)
         SS_NT_STEP(s0 + 2, 0, sr2, ar2, sr3)
         SS_NT_STEP(s0 + 3, 1, sr3, ar3, sr0)
     }
+    if (s0 < nsteps) SS_NT_STEP(s0, 0, sr0, ar0, sr1)
+    if (s0 + 1 < nsteps) SS_NT_STEP(s0 + 1, 1, sr1, ar1, sr2)
+    if (s0 + 2 < nsteps) SS_NT_STEP(s0 + 2, 0, sr2, ar2, sr3)
 #undef SS_NT_STEP
 #undef SS_NT_ISSUE
     float* __restrict__ c = C + b * c_batch;
 #pragma unroll
-    for (int ct = 0; ct < MAXST; ++ct)
-        if (ct < ST) {
-            const int row = d0 + 16 * w + 4 * g, col = 16 * ct + j;
-            if (OUT_T) {
-                *reinterpret_cast<float4*>(c + (long)col * ldc + row) = make_float4(acc[ct][0], acc[ct][1], acc[ct][2], acc[ct][3]);
-            } else {
+    for (int ct = 0; ct < NST; ++ct) {
+        const int row = d0 + 16 * w + 4 * g, col = 16 * ct + j;
+        if (col >= S) continue;
+        if (OUT_T && !RAG) {
+            *reinterpret_cast<float4*>(c + (long)col * ldc + row) = make_float4(acc[ct][0], acc[ct][1], acc[ct][2], acc[ct][3]);
+        } else {
 #pragma unroll
-                for (int i = 0; i < 4; ++i) c[(long)(row + i) * ldc + col] = acc[ct][i];
-            }
+            for (int i = 0; i < 4; ++i)
+                if (!RAG || row + i < M) c[OUT_T ? (long)col * ldc + row + i : (long)(row + i) * ldc + col] = acc[ct][i];
         }
+    }
 }
 
 // Out (S x N per batch entry, bf16) = W (S x K, contiguous along K) X (K x N, contiguous along N).
-// grid (N / 64, batch, parts).  K % (64 * PD * parts) == 0, N % 64 == 0, S % 16 == 0, S <= 160.
-// With parts > 1 workgroup (., ., z) contracts over the z-th part of K and leaves its float32 share in
-// Part[z][batch entry][S][N] for rows_reduce_kernel: a product with few columns would otherwise put a single
+// grid (N / 64 rounded up, batch, parts).  S <= 16 NST.  Plain: K % 64 == 0, N % 64 == 0.
+// With parts > 1 workgroup (., ., z) contracts over the z-th part of K (none of them empty) and leaves its float32
+// share in Part[z][batch entry][S][N] for rows_reduce_kernel: a product with few columns would otherwise put a single
 // workgroup on a CU, with nothing to run while that one waits at its barrier.
-__global__ void __launch_bounds__(256) gemm_rows_kernel(const bf16_t* __restrict__ W, long w_ld, long w_batch,
+template <bool RAG, int NST>
+__global__ void __launch_bounds__(256, 2) gemm_rows_kernel(const bf16_t* __restrict__ W, long w_ld, long w_batch,
                                                          const bf16_t* __restrict__ X, long x_ld, long x_batch,
-                                                         bf16_t* __restrict__ Out, long o_ld, long o_batch, int S, int K,
+                                                         bf16_t* __restrict__ Out, long o_ld, long o_batch, int S, int N, int K,
                                                          float* __restrict__ Part)
 {
-    __shared__ __attribute__((aligned(16))) bf16_t Ws[2][MAXST * 16][KP];
+    __shared__ __attribute__((aligned(16))) bf16_t Ws[2][NST * 16][KP];
     __shared__ __attribute__((aligned(16))) uint32_t Xp[2][KSLAB / 2][XPITCH];
     const int tid = threadIdx.x, w = tid >> 6, lane = tid & 63, g = lane >> 4, j = lane & 15;
     const int n0 = blockIdx.x * 64;
     const long b = blockIdx.y;
-    const int kper = K / (int)gridDim.z;
-    const long kbase = (long)blockIdx.z * kper;
-    const bf16_t* __restrict__ wm = W + b * w_batch + kbase;
+    const int slabs = (K + KSLAB - 1) / KSLAB, per_part = (slabs + (int)gridDim.z - 1) / (int)gridDim.z;
+    const int first = blockIdx.z * per_part, nsteps = min(slabs - first, per_part);   // this part's slabs
+    const bf16_t* __restrict__ wm = W + b * w_batch;
     const int xp = tid >> 3, xo = tid & 7;   // pair of rows, group of eight columns
-    const bf16_t* __restrict__ xrow = X + b * x_batch + (kbase + 2 * xp) * x_ld + n0 + 8 * xo;
-    const int ST = S >> 4;
+    const bf16_t* __restrict__ xcol = X + b * x_batch;
+    const int ST = (S + 15) >> 4;
     // The four waves split the S x 64 tile two by two: wave (wv, wc) has half of the output's row tiles and
     // column tiles 2 wc, 2 wc + 1, so that every weight fragment read from LDS feeds two MFMAs (with a wave
     // per column tile each wave read the whole weight slab and LDS was the limit: 78 -> 68 us).  The same
     // split of gemm_nt_kernel doubles its global fragment loads and registers and measured slower (61 -> 88 us).
     const int wv = w >> 1, wc = w & 1;
     const int RH = (ST + 1) >> 1;
-    constexpr int MAXRH = MAXST / 2;
-    const int nsteps = kper / KSLAB;
+    constexpr int MAXRH = NST / 2;
     f32x4_t acc[MAXRH][2];
 #pragma unroll
     for (int ri = 0; ri < MAXRH; ++ri) acc[ri][0] = acc[ri][1] = f32x4_t{0.f, 0.f, 0.f, 0.f};
-    u32x4 wr0[5], wr1[5], wr2[5], wr3[5];   // one named set of registers per slot, steps written out (see gemm_nt_kernel)
+    u32x4 wr0[NST / 2], wr1[NST / 2], wr2[NST / 2], wr3[NST / 2];   // one named set of registers per slot, steps written out (see gemm_nt_kernel)
     uint4 xr0[2], xr1[2], xr2[2], xr3[2];
-#define SS_ROWS_ISSUE(s_, WR, XR)                                        \
-    {                                                                    \
-        const long k0_ = (long)min((s_), nsteps - 1) * KSLAB;            \
-        XR[0] = load16_stream(xrow + k0_ * x_ld);                        \
-        XR[1] = load16_stream(xrow + (k0_ + 1) * x_ld);                  \
-        slab_load(WR, wm, w_ld, S, (int)k0_, tid);                       \
+#define SS_ROWS_ISSUE(s_, WR, XR)                                                          \
+    {                                                                                      \
+        const int k0_ = (first + min((s_), nsteps - 1)) * KSLAB, x0_ = k0_ + 2 * xp;       \
+        XR[0] = piece_stream<RAG>(xcol + (long)(RAG ? min(x0_, K - 1) : x0_) * x_ld, n0 + 8 * xo, N);         \
+        XR[1] = piece_stream<RAG>(xcol + (long)(RAG ? min(x0_ + 1, K - 1) : x0_ + 1) * x_ld, n0 + 8 * xo, N); \
+        slab_load<RAG, NST>(WR, wm, w_ld, S, k0_, K, tid);                                 \
     }
-#define SS_ROWS_FILL(BUF, WR, XR)                                        \
-    {                                                                    \
-        slab_store(WR, Ws[BUF], tid);                                    \
-        uint4 o0_, o1_;                                                  \
-        pair_rows(XR[0], XR[1], o0_, o1_);                               \
-        *reinterpret_cast<uint4*>(&Xp[BUF][xp][8 * xo]) = o0_;           \
-        *reinterpret_cast<uint4*>(&Xp[BUF][xp][8 * xo + 4]) = o1_;       \
+#define SS_ROWS_FILL(s_, BUF, WR, XR)                                                      \
+    {                                                                                      \
+        const int k0_ = (first + (s_)) * KSLAB;                                            \
+        slab_store<RAG, NST>(WR, Ws[BUF], k0_, K, tid);                                    \
+        if (RAG && n0 + 64 > N) {                                                          \
+            XR[0] = cut(XR[0], n0 + 8 * xo, N);                                            \
+            XR[1] = cut(XR[1], n0 + 8 * xo, N);                                            \
+        }                                                                                  \
+        if (RAG && k0_ + KSLAB > K) {                                                      \
+            if (k0_ + 2 * xp >= K) XR[0] = make_uint4(0u, 0u, 0u, 0u);                     \
+            if (k0_ + 2 * xp + 1 >= K) XR[1] = make_uint4(0u, 0u, 0u, 0u);                 \
+        }                                                                                  \
+        uint4 o0_, o1_;                                                                    \
+        pair_rows(XR[0], XR[1], o0_, o1_);                                                 \
+        *reinterpret_cast<uint4*>(&Xp[BUF][xp][8 * xo]) = o0_;                             \
+        *reinterpret_cast<uint4*>(&Xp[BUF][xp][8 * xo + 4]) = o1_;                         \
     }
 #define SS_ROWS_STEP(s_, BUF, WR, XR, WRN, XRN)                                                                       \
     {                                                                                                                 \
@@ -322,7 +371,7 @@ __global__ void __launch_bounds__(256) gemm_rows_kernel(const bf16_t* __restrict
                 acc[ri][1] = mfma_bf16(af, bf1, acc[ri][1]);                                                          \
             }                                                                                                         \
         }                                                                                                             \
-        if ((s_) + 1 < nsteps) SS_ROWS_FILL((BUF) ^ 1, WRN, XRN)                                                      \
+        if ((s_) + 1 < nsteps) SS_ROWS_FILL((s_) + 1, (BUF) ^ 1, WRN, XRN)                                            \
         __syncthreads();                                                                                              \
     }
     SS_ROWS_ISSUE(0, wr0, xr0)
@@ -333,54 +382,59 @@ __global__ void __launch_bounds__(256) gemm_rows_kernel(const bf16_t* __restrict
     __builtin_amdgcn_sched_barrier(0);
     SS_ROWS_ISSUE(3, wr3, xr3)
     __builtin_amdgcn_sched_barrier(0);
-    SS_ROWS_FILL(0, wr0, xr0)
+    SS_ROWS_FILL(0, 0, wr0, xr0)
     __syncthreads();
-    for (int s0 = 0; s0 < nsteps; s0 += PD) {
+    int s0 = 0;
+    for (; s0 + PD <= nsteps; s0 += PD) {
         SS_ROWS_STEP(s0, 0, wr0, xr0, wr1, xr1)
         SS_ROWS_STEP(s0 + 1, 1, wr1, xr1, wr2, xr2)
         SS_ROWS_STEP(s0 + 2, 0, wr2, xr2, wr3, xr3)
         SS_ROWS_STEP(s0 + 3, 1, wr3, xr3, wr0, xr0)
     }
+    if (s0 < nsteps) SS_ROWS_STEP(s0, 0, wr0, xr0, wr1, xr1)
+    if (s0 + 1 < nsteps) SS_ROWS_STEP(s0 + 1, 1, wr1, xr1, wr2, xr2)
+    if (s0 + 2 < nsteps) SS_ROWS_STEP(s0 + 2, 0, wr2, xr2, wr3, xr3)
 #undef SS_ROWS_STEP
 #undef SS_ROWS_FILL
 #undef SS_ROWS_ISSUE
-    if (gridDim.z > 1) {
-        const long ncols = (long)gridDim.x * 64;
-        float* __restrict__ pp = Part + ((long)blockIdx.z * gridDim.y + b) * S * ncols + n0 + 32 * wc + j;
-#pragma unroll
-        for (int ri = 0; ri < MAXRH; ++ri)
-            if (ri < RH && wv * RH + ri < ST) {
-#pragma unroll
-                for (int c2 = 0; c2 < 2; ++c2)
-#pragma unroll
-                    for (int i = 0; i < 4; ++i) pp[(long)(16 * (wv * RH + ri) + 4 * g + i) * ncols + 16 * c2] = acc[ri][c2][i];
-            }
-        return;
-    }
-    bf16_t* __restrict__ o = Out + b * o_batch + n0 + 32 * wc + j;
+    const bool split = gridDim.z > 1;
+    float* __restrict__ pp = Part + ((long)blockIdx.z * gridDim.y + b) * S * N;
+    bf16_t* __restrict__ o = Out + b * o_batch;
 #pragma unroll
     for (int ri = 0; ri < MAXRH; ++ri)
-        if (ri < RH && wv * RH + ri < ST) {
 #pragma unroll
-            for (int c2 = 0; c2 < 2; ++c2)
+        for (int c2 = 0; c2 < 2; ++c2) {
+            const int row = 16 * (wv * RH + ri) + 4 * g, col = n0 + 32 * wc + j + 16 * c2;
+            if (ri >= RH || (RAG && col >= N)) continue;
 #pragma unroll
-                for (int i = 0; i < 4; ++i)
-                    o[(long)(16 * (wv * RH + ri) + 4 * g + i) * o_ld + 16 * c2] = bf16_t(f32_to_bf16_bits(acc[ri][c2][i]));
+            for (int i = 0; i < 4; ++i) {
+                if (row + i >= S) continue;
+                if (split) pp[(long)(row + i) * N + col] = acc[ri][c2][i];
+                else o[(long)(row + i) * o_ld + col] = bf16_t(f32_to_bf16_bits(acc[ri][c2][i]));
+            }
         }
 }
 
-// Out[b][row][8 c ..+7] (bf16) = sum over the parts of Part[part][b][row][8 c ..+7]; one thread per eight columns.
+// Out[b][row][8 c ..+7] (bf16) = sum over the parts of Part[part][b][row][8 c ..+7]; one thread per eight columns
+// (RAG: per column).
+template <bool RAG>
 __global__ void __launch_bounds__(256) rows_reduce_kernel(const float* __restrict__ Part, int parts, long part_stride,
                                                            bf16_t* __restrict__ Out, long o_ld, long o_batch, int S, int ncols,
                                                            long items)
 {
     const long idx = (long)blockIdx.x * 256 + threadIdx.x;
     if (idx >= items) return;
-    const int per_row = ncols >> 3;
+    const int per_row = RAG ? ncols : ncols >> 3;
     const int c8 = (int)(idx % per_row);
     const long br = idx / per_row;
     const int row = (int)(br % S);
     const long b = br / S;
+    if constexpr (RAG) {
+        float v = Part[br * ncols + c8];
+        for (int z = 1; z < parts; ++z) v += Part[z * part_stride + br * ncols + c8];
+        Out[b * o_batch + (long)row * o_ld + c8] = bf16_t(f32_to_bf16_bits(v));
+        return;
+    }
     const float* __restrict__ src = Part + br * ncols + 8 * c8;
     float4 lo = *reinterpret_cast<const float4*>(src), hi = *reinterpret_cast<const float4*>(src + 4);
     for (int z = 1; z < parts; ++z) {
@@ -398,71 +452,86 @@ __global__ void __launch_bounds__(256) rows_reduce_kernel(const float* __restric
 }
 
 // Out (M x N per batch entry, bf16) [+]= W (M x K, contiguous along K) Y (K x N, contiguous along N).
-// grid (N / 64, M / (64 * mtiles), batch), mtiles = 64-row tiles of the result per workgroup (the small operand is
-// prepared once for all of them).  K % 32 == 0, K <= 160, N % 64 == 0, M % (64 * mtiles) == 0.
+// grid (N / 64, M / (64 * mtiles), batch) rounded up, mtiles = 64-row tiles of the result per workgroup (the small
+// operand is prepared once for all of them).  K <= 32 NKS.  Plain: K % 32 == 0, N % 64 == 0, M % (64 * mtiles) == 0.
+template <bool RAG, int NKS>
 __global__ void __launch_bounds__(256) gemm_cols_kernel(const bf16_t* __restrict__ W, long w_ld, const bf16_t* __restrict__ Y,
                                                          long y_ld, long y_batch, bf16_t* __restrict__ Out, long o_ld, long o_batch,
-                                                         int K, int accumulate, int mtiles)
+                                                         int M, int N, int K, int accumulate, int mtiles)
 {
-    __shared__ __attribute__((aligned(16))) uint32_t Yp[MAXST * 8][XPITCH];        // pairs of contraction indices x 64 columns
+    __shared__ __attribute__((aligned(16))) uint32_t Yp[NKS * 16][XPITCH];         // pairs of contraction indices x 64 columns
     __shared__ __attribute__((aligned(16))) float Os[64][64 + 4];                 // a tile of the result on its way out (two of them, one barrier per tile: slower, 71 -> 76 us)
     const int tid = threadIdx.x, w = tid >> 6, lane = tid & 63, g = lane >> 4, j = lane & 15;
     const int n0 = blockIdx.x * 64;
     const int m_base = blockIdx.y * 64 * mtiles;
     const long b = blockIdx.z;
-    const bf16_t* __restrict__ y = Y + b * y_batch + n0;
-    const int KS = K >> 5;   // 32-wide contraction steps (<= 5)
+    const bf16_t* __restrict__ y = Y + b * y_batch;
+    const int KS = (K + 31) >> 5;   // 32-wide contraction steps (<= NKS)
     // the small operand, paired and into LDS: item p -> pair of rows p / 8, eight columns from 8 * (p % 8)
-    for (int p = tid; p < (K >> 1) * 8; p += 256) {
+    for (int p = tid; p < KS * 16 * 8; p += 256) {
         const int pr = p >> 3, po = p & 7;
-        const uint4 lo = *reinterpret_cast<const uint4*>(y + (long)(2 * pr) * y_ld + 8 * po);
-        const uint4 hi = *reinterpret_cast<const uint4*>(y + (long)(2 * pr + 1) * y_ld + 8 * po);
+        u32x4 lo = piece<RAG>(y + (long)(RAG ? min(2 * pr, K - 1) : 2 * pr) * y_ld, n0 + 8 * po, N);
+        u32x4 hi = piece<RAG>(y + (long)(RAG ? min(2 * pr + 1, K - 1) : 2 * pr + 1) * y_ld, n0 + 8 * po, N);
+        if constexpr (RAG) {
+            const u32x4 zero = {0u, 0u, 0u, 0u};
+            lo = 2 * pr < K ? cut(lo, n0 + 8 * po, N) : zero;
+            hi = 2 * pr + 1 < K ? cut(hi, n0 + 8 * po, N) : zero;
+        }
         uint4 o0, o1;
-        pair_rows(lo, hi, o0, o1);
+        pair_rows(make_uint4(lo[0], lo[1], lo[2], lo[3]), make_uint4(hi[0], hi[1], hi[2], hi[3]), o0, o1);
         *reinterpret_cast<uint4*>(&Yp[pr][8 * po]) = o0;
         *reinterpret_cast<uint4*>(&Yp[pr][8 * po + 4]) = o1;
     }
     __syncthreads();
     // ... and from there into registers as fragments: first operand of the transposed product,
     // row = column 16 ct + j of Y, contraction indices 32 ks + 8 g ..+7
-    uint4 yf[4][MAXST / 2];
+    uint4 yf[4][NKS];
 #pragma unroll
     for (int ct = 0; ct < 4; ++ct)
 #pragma unroll
-        for (int ks = 0; ks < MAXST / 2; ++ks)
+        for (int ks = 0; ks < NKS; ++ks)
             if (ks < KS) {
                 const uint32_t* q = &Yp[16 * ks + 4 * g][16 * ct + j];
                 yf[ct][ks] = make_uint4(q[0], q[XPITCH], q[2 * XPITCH], q[3 * XPITCH]);
             }
-    const bf16_t* __restrict__ wrow = W + (long)(m_base + 16 * w + j) * w_ld + 8 * g;
-    uint4 wf[MAXST / 2];
+    const bf16_t* __restrict__ wcol = W;
+    auto load_w = [&](uint4 (&f)[NKS], int m0) {
+        const bf16_t* __restrict__ wrow = wcol + (long)(RAG ? min(m0 + 16 * w + j, M - 1) : m0 + 16 * w + j) * w_ld;
 #pragma unroll
-    for (int ks = 0; ks < MAXST / 2; ++ks)
-        if (ks < KS) wf[ks] = *reinterpret_cast<const uint4*>(wrow + 32 * ks);
-    bf16_t* __restrict__ o = Out + b * o_batch + n0;
+        for (int ks = 0; ks < NKS; ++ks)
+            if (ks < KS) {
+                const u32x4 x = piece<RAG>(wrow, 32 * ks + 8 * g, K);
+                f[ks] = make_uint4(x[0], x[1], x[2], x[3]);
+            }
+    };
+    uint4 wf[NKS];
+    load_w(wf, m_base);
+    bf16_t* __restrict__ o = Out + b * o_batch;
     for (int mt = 0; mt < mtiles; ++mt) {
         const int m0 = m_base + 64 * mt;
-        uint4 wc[MAXST / 2];
+        if (RAG && m0 >= M) break;   // uniform
+        uint4 wc[NKS];
 #pragma unroll
-        for (int ks = 0; ks < MAXST / 2; ++ks) wc[ks] = wf[ks];
-        if (mt + 1 < mtiles) {
-#pragma unroll
-            for (int ks = 0; ks < MAXST / 2; ++ks)
-                if (ks < KS) wf[ks] = *reinterpret_cast<const uint4*>(wrow + (long)64 * (mt + 1) * w_ld + 32 * ks);
+        for (int ks = 0; ks < NKS; ++ks) {
+            wc[ks] = wf[ks];
+            if (RAG && ks < KS && 32 * (ks + 1) > K) wc[ks] = cut(wc[ks], 32 * ks + 8 * g, K);   // the last step
         }
+        if (mt + 1 < mtiles) load_w(wf, m0 + 64);
         // earlier values of this tile, for accumulation: requested before the arithmetic
         uint4 prev[2];
 #pragma unroll
         for (int e = 0; e < 2; ++e) {
             const int idx = tid + 256 * e, row = idx >> 3, pc = idx & 7;
-            prev[e] = accumulate ? *reinterpret_cast<const uint4*>(o + (long)(m0 + row) * o_ld + 8 * pc) : make_uint4(0u, 0u, 0u, 0u);
+            u32x4 x = {0u, 0u, 0u, 0u};
+            if (accumulate) x = piece<RAG>(o + (long)(RAG ? min(m0 + row, M - 1) : m0 + row) * o_ld, n0 + 8 * pc, N);
+            prev[e] = make_uint4(x[0], x[1], x[2], x[3]);
         }
         f32x4_t acc[4];
 #pragma unroll
         for (int ct = 0; ct < 4; ++ct) {
             acc[ct] = f32x4_t{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-            for (int ks = 0; ks < MAXST / 2; ++ks)
+            for (int ks = 0; ks < NKS; ++ks)
                 if (ks < KS) acc[ct] = mfma_bf16(yf[ct][ks], wc[ks], acc[ct]);   // (Y^T W^T): row 16 ct + 4 g + i of Y^T, column 16 w + j of W^T
         }
         if (mt > 0) __syncthreads();   // the previous tile has left Os
@@ -476,72 +545,122 @@ __global__ void __launch_bounds__(256) gemm_cols_kernel(const bf16_t* __restrict
             const float4 lo = *reinterpret_cast<const float4*>(&Os[row][8 * pc]);
             const float4 hi = *reinterpret_cast<const float4*>(&Os[row][8 * pc + 4]);
             float r[8] = {lo.x, lo.y, lo.z, lo.w, hi.x, hi.y, hi.z, hi.w};
+            if (RAG && n0 + 64 > N) prev[e] = cut(prev[e], n0 + 8 * pc, N);
             const uint32_t c[4] = {prev[e].x, prev[e].y, prev[e].z, prev[e].w};   // zeros unless accumulating
 #pragma unroll
             for (int m = 0; m < 4; ++m) {
                 r[2 * m] += bf16_lo(c[m]);
                 r[2 * m + 1] += bf16_hi(c[m]);
             }
-            const uint4 v = make_uint4(pack_bf16x2(r[0], r[1]), pack_bf16x2(r[2], r[3]), pack_bf16x2(r[4], r[5]), pack_bf16x2(r[6], r[7]));
-            *reinterpret_cast<uint4*>(o + (long)(m0 + row) * o_ld + 8 * pc) = v;
+            bf16_t* dst = o + (long)(m0 + row) * o_ld + n0 + 8 * pc;
+            if constexpr (RAG) {
+                if (m0 + row < M) io8<bf16_t>::store_elem(dst, 0u, io8<bf16_t>::pack(r), N - (n0 + 8 * pc));
+            } else {
+                *reinterpret_cast<uint4*>(dst) = io8<bf16_t>::pack(r);
+            }
         }
     }
 }
 
 inline bool al16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15) == 0; }
+inline bool mult8(long x) { return x % 8 == 0; }
+inline unsigned tiles64(int n) { return (unsigned)((n + 63) / 64); }
+
+// One launch each (the small operand has at most 16 * MAXST rows); ST = its 16-row tiles.
+template <bool OUT_T, bool RAG>
+void launch_nt(const bf16_t* big, long big_ld, long big_batch, const bf16_t* small, long small_ld, long small_batch, float* C,
+               long ldc, long c_batch, int M, int S, int K, int batch, hipStream_t stream)
+{
+    const dim3 grid(tiles64(M), (unsigned)batch);
+    const int ST = (S + 15) / 16;
+#define SS_LAUNCH_NT(NST) hipLaunchKernelGGL((gemm_nt_kernel<OUT_T, RAG, NST>), grid, dim3(256), 0, stream, big, big_ld, big_batch, \
+                                             small, small_ld, small_batch, C, ldc, c_batch, M, S, K)
+    if (ST <= 6) SS_LAUNCH_NT(6); else if (ST <= 10) SS_LAUNCH_NT(10); else SS_LAUNCH_NT(12);
+#undef SS_LAUNCH_NT
+}
+template <bool RAG>
+void launch_rows(const GemmArgs& g, const bf16_t* A, bf16_t* C, int S, int parts, hipStream_t stream)
+{
+    const dim3 grid(tiles64(g.N), (unsigned)g.batch, (unsigned)parts);
+    const int ST = (S + 15) / 16;
+    const bf16_t* B = static_cast<const bf16_t*>(g.B);
+    float* ws = static_cast<float*>(g.split_ws);
+#define SS_LAUNCH_ROWS(NST) hipLaunchKernelGGL((gemm_rows_kernel<RAG, NST>), grid, dim3(256), 0, stream, A, g.a_m, g.a_batch, B, \
+                                               g.b_k, g.b_batch, C, g.ldc, g.c_batch, S, g.N, g.K, ws)
+    if (ST <= 6) SS_LAUNCH_ROWS(6); else if (ST <= 10) SS_LAUNCH_ROWS(10); else SS_LAUNCH_ROWS(12);
+#undef SS_LAUNCH_ROWS
+    if (parts > 1) {
+        const bool whole = !RAG;
+        const long items = (long)g.batch * S * (whole ? g.N / 8 : g.N);
+        hipLaunchKernelGGL((rows_reduce_kernel<RAG>), dim3((unsigned)((items + 255) / 256)), dim3(256), 0, stream, ws, parts,
+                           (long)g.batch * S * g.N, C, g.ldc, g.c_batch, S, g.N, items);
+    }
+}
+template <bool RAG>
+void launch_cols(const GemmArgs& g, int mtiles, hipStream_t stream)
+{
+    const dim3 grid(tiles64(g.N), (unsigned)((tiles64(g.M) + mtiles - 1) / mtiles), (unsigned)g.batch);
+    const int KS = (g.K + 31) / 32;
+    const bf16_t *A = static_cast<const bf16_t*>(g.A), *B = static_cast<const bf16_t*>(g.B);
+#define SS_LAUNCH_COLS(NKS) hipLaunchKernelGGL((gemm_cols_kernel<RAG, NKS>), grid, dim3(256), 0, stream, A, g.a_m, B, g.b_k, g.b_batch, \
+                                               static_cast<bf16_t*>(g.C), g.ldc, g.c_batch, g.M, g.N, g.K, g.accumulate ? 1 : 0, mtiles)
+    if (KS <= 3) SS_LAUNCH_COLS(3); else if (KS <= 5) SS_LAUNCH_COLS(5); else SS_LAUNCH_COLS(6);
+#undef SS_LAUNCH_COLS
+}
 
 // The matrix-core kernel for this product, if there is one; SS_ERR_UNSUPPORTED otherwise (nothing enqueued).
 int launch_fast(const GemmArgs& g, hipStream_t stream)
 {
-    if (!g.bf16 || g.K <= 0 || !al16(g.A) || !al16(g.B) || !al16(g.C)) return SS_ERR_UNSUPPORTED;
+    if (!g.bf16 || g.K < 8 || g.M / 64 > 65535 || g.N / 64 > 65535) return SS_ERR_UNSUPPORTED;
     const bf16_t* A = static_cast<const bf16_t*>(g.A);
     const bf16_t* B = static_cast<const bf16_t*>(g.B);
-    auto mult8 = [](long x) { return x % 8 == 0; };
-    if (g.a_k == 1 && g.b_k == 1 && g.c_float && !g.accumulate && g.K % (KSLAB * PD) == 0 && mult8(g.a_m) && mult8(g.b_n) &&
-        mult8(g.a_batch) && mult8(g.b_batch) && g.ldc % 4 == 0 && g.c_batch % 4 == 0) {
-        // C = A B^T: the operand with many rows is split over workgroups and waves
+    const bool whole = al16(g.A) && al16(g.B) && al16(g.C) && mult8(g.a_batch) && mult8(g.b_batch);   // operands made of aligned 16-byte pieces
+    constexpr int SMAX = MAXST * 16;
+    if (g.a_k == 1 && g.b_k == 1 && g.c_float && !g.accumulate) {
+        // C = A B^T: the operand with more rows is split over workgroups and waves, the other one, up to SMAX rows at a time,
+        // goes through LDS
         float* C = static_cast<float*>(g.C);
-        if (g.N % 16 == 0 && g.N <= MAXST * 16 && g.M % 64 == 0 && g.M / 64 <= 65535) {
-            hipLaunchKernelGGL(gemm_nt_kernel<false>, dim3((unsigned)(g.M / 64), (unsigned)g.batch), dim3(256), 0, stream, A, g.a_m,
-                               g.a_batch, B, g.b_n, g.b_batch, C, g.ldc, g.c_batch, g.N, g.K);
-            return hipGetLastError() == hipSuccess ? SS_OK : SS_ERR_LAUNCH;
+        const bool out_t = g.M < g.N;
+        const int big = out_t ? g.N : g.M, small = out_t ? g.M : g.N;
+        const bool rag = !(whole && g.K % KSLAB == 0 && big % 64 == 0 && mult8(g.a_m) && mult8(g.b_n) && g.ldc % 4 == 0 && g.c_batch % 4 == 0);
+        for (int s0 = 0; s0 < small; s0 += SMAX) {
+            const int S = small - s0 < SMAX ? small - s0 : SMAX;
+            if (out_t) {
+                auto f = rag ? launch_nt<true, true> : launch_nt<true, false>;
+                f(B, g.b_n, g.b_batch, A + (long)s0 * g.a_m, g.a_m, g.a_batch, C + (long)s0 * g.ldc, g.ldc, g.c_batch, big, S, g.K, g.batch, stream);
+            } else {
+                auto f = rag ? launch_nt<false, true> : launch_nt<false, false>;
+                f(A, g.a_m, g.a_batch, B + (long)s0 * g.b_n, g.b_n, g.b_batch, C + s0, g.ldc, g.c_batch, big, S, g.K, g.batch, stream);
+            }
         }
-        if (g.M % 16 == 0 && g.M <= MAXST * 16 && g.N % 64 == 0 && g.N / 64 <= 65535) {
-            hipLaunchKernelGGL(gemm_nt_kernel<true>, dim3((unsigned)(g.N / 64), (unsigned)g.batch), dim3(256), 0, stream, B, g.b_n,
-                               g.b_batch, A, g.a_m, g.a_batch, C, g.ldc, g.c_batch, g.M, g.K);
-            return hipGetLastError() == hipSuccess ? SS_OK : SS_ERR_LAUNCH;
-        }
-        return SS_ERR_UNSUPPORTED;
+        return hipGetLastError() == hipSuccess ? SS_OK : SS_ERR_LAUNCH;
     }
-    if (g.a_k == 1 && g.b_n == 1 && !g.c_float && g.N % 64 == 0 && g.N / 64 <= 65535 && mult8(g.a_m) && mult8(g.b_k) &&
-        mult8(g.a_batch) && mult8(g.b_batch) && mult8(g.ldc) && mult8(g.c_batch)) {
-        bf16_t* C = static_cast<bf16_t*>(g.C);
-        if (!g.accumulate && g.M % 16 == 0 && g.M <= MAXST * 16 && g.K % (KSLAB * PD) == 0) {
-            // fewer than two workgroups per CU: two parts if the workspace holds two float32 shares (headline shape: 66 -> 57 us both launches together; four parts measured slower)
-            const long wgs = (long)(g.N / 64) * g.batch;
-            const size_t share = (size_t)g.batch * g.M * g.N * sizeof(float);
-            const int parts = (wgs < ROWS_MIN_WGS && g.K >= ROWS_MIN_SPLIT_K && g.K % (KSLAB * PD * 2) == 0 && g.split_ws && 2 * share <= g.split_ws_bytes) ? 2 : 1;
-            hipLaunchKernelGGL(gemm_rows_kernel, dim3((unsigned)(g.N / 64), (unsigned)g.batch, (unsigned)parts), dim3(256), 0, stream,
-                               A, g.a_m, g.a_batch, B, g.b_k, g.b_batch, C, g.ldc, g.c_batch, g.M, g.K, static_cast<float*>(g.split_ws));
-            if (parts > 1) {
-                const long items = (long)g.batch * g.M * (g.N / 8);
-                hipLaunchKernelGGL(rows_reduce_kernel, dim3((unsigned)((items + 255) / 256)), dim3(256), 0, stream,
-                                   static_cast<const float*>(g.split_ws), parts, (long)g.batch * g.M * g.N, C, g.ldc, g.c_batch, g.M,
-                                   g.N, items);
-            }
+    if (g.a_k == 1 && g.b_n == 1 && !g.c_float && g.N >= 8) {
+        const bool whole_c = whole && g.N % 64 == 0 && mult8(g.a_m) && mult8(g.b_k) && mult8(g.ldc) && mult8(g.c_batch);
+        if (g.K <= MAXST * 16 && g.a_batch == 0) {
+            // as many 64-row tiles per workgroup as fit, up to 16, while the launch keeps >= 1024 workgroups
+            int mtiles = 1;
+            const long cols = (long)tiles64(g.N) * g.batch, mt = tiles64(g.M);
+            for (int c = 16; c > 1; c >>= 1)
+                if (mt % c == 0 && cols * (mt / c) >= 1024) { mtiles = c; break; }
+            if (whole_c && g.K % 32 == 0 && g.M % 64 == 0) launch_cols<false>(g, mtiles, stream);
+            else launch_cols<true>(g, mtiles, stream);
             return hipGetLastError() == hipSuccess ? SS_OK : SS_ERR_LAUNCH;
         }
-        if (g.K % 32 == 0 && g.K <= MAXST * 16 && g.M % 64 == 0 && g.a_batch == 0) {
-            // as many 64-row tiles per workgroup as divide M, up to 16, while the launch keeps >= 1024 workgroups
-            int mtiles = 1;
-            const long cols = (long)(g.N / 64) * g.batch;
-            for (int c = 16; c > 1; c >>= 1)
-                if ((g.M / 64) % c == 0 && cols * (g.M / 64 / c) >= 1024) { mtiles = c; break; }
-            if (g.M / (64 * mtiles) <= 65535) {
-                hipLaunchKernelGGL(gemm_cols_kernel, dim3((unsigned)(g.N / 64), (unsigned)(g.M / (64 * mtiles)), (unsigned)g.batch),
-                                   dim3(256), 0, stream, A, g.a_m, B, g.b_k, g.b_batch, C, g.ldc, g.c_batch, g.K, g.accumulate ? 1 : 0, mtiles);
-                return hipGetLastError() == hipSuccess ? SS_OK : SS_ERR_LAUNCH;
+        if (!g.accumulate) {
+            bf16_t* C = static_cast<bf16_t*>(g.C);
+            const bool rag = !(whole_c && g.K % KSLAB == 0);
+            // fewer than two workgroups per CU: two parts if the workspace holds two float32 shares (headline shape: 66 -> 57 us both launches together; four parts measured slower)
+            const long wgs = (long)tiles64(g.N) * g.batch;
+            const size_t share = (size_t)g.batch * g.M * g.N * sizeof(float);
+            const int parts = (wgs < ROWS_MIN_WGS && g.K >= ROWS_MIN_SPLIT_K && g.split_ws && 2 * share <= g.split_ws_bytes) ? 2 : 1;
+            for (int s0 = 0; s0 < g.M; s0 += SMAX) {   // in stream order: the shares of one launch are added up before the next overwrites them
+                const int S = g.M - s0 < SMAX ? g.M - s0 : SMAX;
+                const bf16_t* a = A + (long)s0 * g.a_m;
+                bf16_t* c = C + (long)s0 * g.ldc;
+                if (rag) launch_rows<true>(g, a, c, S, parts, stream); else launch_rows<false>(g, a, c, S, parts, stream);
             }
+            return hipGetLastError() == hipSuccess ? SS_OK : SS_ERR_LAUNCH;
         }
     }
     return SS_ERR_UNSUPPORTED;

@@ -1,0 +1,97 @@
+"""The matrix-core projection products at sizes off every tile: sequences, widths and ranks that are no multiple of
+16, 64 or 8, pitches that are not the row length, operands that start at any element.
+
+Every operand lies in a larger buffer of NaNs, so that a value read from outside its rows and used shows in the
+result, and nothing around the result may change.
+"""
+import pytest
+import torch
+
+from paper_2312_00752_amd import binding as B
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+BF = torch.bfloat16
+
+
+def _inside(x, pad):
+    """x as a view into a NaN buffer: `pad` elements in front, rows `pad` further apart than their length."""
+    nb, rows, cols = x.shape
+    buf = torch.full((nb * rows * (cols + pad) + pad,), float("nan"), dtype=x.dtype, device=DEV)
+    view = buf[pad:].view(nb, rows, cols + pad)[:, :, :cols] if pad else buf.view(nb, rows, cols)
+    view.copy_(x)
+    return view
+
+
+def _rand(nb, rows, cols, seed):
+    g = torch.Generator().manual_seed(seed)
+    return (torch.randn((nb, rows, cols), generator=g) * 0.5).to(BF).to(DEV)
+
+
+def _check(A, X, out_dtype, trans_b=False, accumulate=False, workspace=None, pad=0):
+    a64, b64 = A.cpu().double(), X.cpu().double()
+    ref = torch.matmul(a64, b64.transpose(-1, -2) if trans_b else b64)
+    size = a64.abs() @ (b64.transpose(-1, -2) if trans_b else b64).abs()   # bounds every rounding of the sum
+    C = _inside(torch.full(ref.shape, float("nan"), dtype=out_dtype, device=DEV), pad)
+    if accumulate:
+        C.copy_(_rand(*ref.shape, 99))
+        ref = ref + C.cpu().double()
+    B.ss_proj_gemm(A, X, C, trans_b=trans_b, accumulate=accumulate, workspace=workspace)
+    torch.cuda.synchronize()
+    got = C.cpu().double()
+    # float32 sums: K roundings (or truncations) by 2^-23 of the sum of magnitudes at most; a bf16 result is rounded once more
+    K = A.shape[-1]
+    bound = K * 2.0 ** -23 * size + (2.0 ** -8 * ref.abs() if out_dtype == BF else 0.0) + 1e-30
+    assert torch.isfinite(got).all()
+    assert ((got - ref).abs() <= bound).all(), ((got - ref).abs() / bound).max()
+    if pad:
+        whole = C.as_strided((C.shape[0], C.shape[1], C.shape[2] + pad), C.stride())
+        assert torch.isnan(whole[:, :, C.shape[2]:]).all()
+
+
+# (batch, D, L, R, Mx): the smallest the kernels take; one short of and one past their tiles; more rows of the small
+# operand than one launch holds (192); a contraction in two parts
+SIZES = [(2, 9, 8, 8, 11), (2, 63, 65, 8, 13), (1, 200, 67, 25, 57), (3, 129, 127, 33, 97), (2, 264, 131, 96, 161),
+         (1, 328, 321, 160, 192), (1, 100, 200, 191, 223), (1, 4105, 71, 12, 44)]
+
+
+@pytest.mark.parametrize("pad", [0, 3])
+@pytest.mark.parametrize("nb,D,L,R,Mx", SIZES)
+def test_products_of_any_size(nb, D, L, R, Mx, pad):
+    u = _inside(_rand(nb, D, L, 1), pad)
+    P = _inside(_rand(nb, Mx, L, 2), pad)
+    r = P[:, :R]
+    W_x, W_dt = _inside(_rand(1, Mx, D, 3), pad)[0], _inside(_rand(1, D, R, 4), pad)[0]
+    W_xT, W_dtT = _inside(_rand(1, D, Mx, 5), pad)[0], _inside(_rand(1, R, D, 6), pad)[0]
+    ws = torch.full((2 * nb * Mx * L * 4,), 0xFF, dtype=torch.uint8, device=DEV)
+    _check(W_x, u, BF, pad=pad)
+    _check(W_x, u, BF, workspace=ws, pad=pad)
+    _check(W_dtT, u, BF, workspace=ws, pad=pad)
+    _check(W_dt, r, BF, pad=pad)
+    _check(W_xT, P, BF, accumulate=True, pad=pad)
+    _check(u, r, torch.float32, trans_b=True, pad=pad)
+    _check(P, u, torch.float32, trans_b=True, pad=pad)
+
+
+@pytest.mark.parametrize("slabs", [1, 2, 3, 5, 6, 7])
+def test_whole_slabs_not_a_multiple_of_the_pipeline(slabs):
+    """Aligned operands whose contraction is a whole number of 64-wide slabs but not of four of them."""
+    n = 64 * slabs
+    X = _rand(2, n, 128, 7)
+    _check(_rand(1, 80, n, 8)[0], X, BF)                                    # rows of X contracted
+    _check(_rand(2, 128, n, 9), _rand(2, 48, n, 10), torch.float32, trans_b=True)
+    _check(_rand(2, 40, n, 11), _rand(2, 192, n, 12), torch.float32, trans_b=True)
+
+
+def test_infinities_and_nan_stay_where_they_belong():
+    """A last row or column of infinities reaches the results that contain it and no others."""
+    nb, D, L, M = 1, 71, 77, 19
+    u, W = _rand(nb, D, L, 13), _rand(1, M, D, 14)[0]
+    u[0, D - 1, 5] = float("inf")
+    W[:, D - 1] = W[:, D - 1].abs() + 0.1
+    C = torch.empty((nb, M, L), dtype=BF, device=DEV)
+    B.ss_proj_gemm(W, u, C)
+    torch.cuda.synchronize()
+    assert (C[0, :, 5] == float("inf")).all()
+    C[0, :, 5] = 0
+    assert torch.isfinite(C).all()
