@@ -6,7 +6,10 @@ have been built (``python -m paper_2312_00752_amd.build``); loading fails loudly
 has not been.
 """
 import ctypes
+import math
 import os
+
+import torch
 
 _PKG = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_PKG, "libss_scan.so")
@@ -168,7 +171,6 @@ def ss_version():
 
 # ---------------------------------------------------------------- tensor marshalling
 def _io_code(t):
-    import torch
     if t.dtype == torch.float32:
         return SS_F32
     if t.dtype == torch.bfloat16:
@@ -180,6 +182,9 @@ def _ptr(t, dtype=None, shape=None, name="tensor"):
     """Device pointer of a dense CUDA tensor (or None)."""
     if t is None:
         return None
+    # the checks of a good call in one expression (a call marshals about ten tensors); the messages below
+    if t.is_cuda and t.is_contiguous() and (dtype is None or t.dtype is dtype) and (shape is None or t.shape == shape):
+        return t.data_ptr()
     if not t.is_cuda:
         raise ValueError("%s must live on the GPU" % name)
     if not t.is_contiguous():
@@ -206,18 +211,25 @@ def empty_channel_skewed(n, shape, dtype, device):
     tensors at mutually skewed addresses takes the tensor-to-tensor part of that away (2^20-step
     float32 workload: 9.5 -> 7.6 ms forward + backward); shapes with short rows are unaffected.  The
     library cannot do this for tensors it is handed; callers that allocate them can."""
-    import math
-    import torch
-    esz = torch.empty((), dtype=dtype).element_size()
-    nbytes = int(math.prod(shape)) * esz
-    pitch = (nbytes + 255) // 256 * 256 + CHANNEL_SKEW_BYTES
-    pool = torch.empty(max(1, n * pitch), dtype=torch.uint8, device=device)
-    return [pool[i * pitch: i * pitch + nbytes].view(dtype).view(tuple(shape)) for i in range(n)]
+    numel, strides = 1, []
+    for d in reversed(shape):
+        strides.insert(0, numel)
+        numel *= max(1, int(d))
+    esz = dtype.itemsize
+    pitch = ((math.prod(shape) * esz + 255) // 256 * 256 + CHANNEL_SKEW_BYTES) // esz   # elements
+    pool = torch.empty(max(1, n * pitch), dtype=dtype, device=device)
+    return [pool.as_strided(shape, strides, i * pitch) for i in range(n)]
+
+
+# the current stream's handle without building a torch.cuda.Stream around it (2 us of every call)
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+_device_index = getattr(torch._C, "_cuda_getDevice", None)
 
 
 def _stream(stream):
-    import torch
     if stream is None:
+        if _raw_stream is not None and _device_index is not None:
+            return _raw_stream(_device_index())
         return torch.cuda.current_stream().cuda_stream
     if isinstance(stream, int):
         return stream
@@ -226,7 +238,6 @@ def _stream(stream):
 
 def _fwd_params(u, delta, A, Bmat, Cmat, Dskip, z, delta_bias, h0, delta_softplus, exact_zoh=False,
                 complex_state=False):
-    import torch
     f32 = torch.float32
     nb, nd, nl = u.shape
     nn = A.shape[1]
@@ -292,7 +303,6 @@ def ss_scan_fwd(u, delta, A, Bmat, Cmat, Dskip=None, z=None, delta_bias=None, h0
     ``save_for_bwd`` (the default when a workspace is given) the call leaves what
     ``ss_scan_bwd`` needs in it; without, the workspace only serves as scratch that lets
     a long sequence with few rows be split across workgroups."""
-    import torch
     p = _fwd_params(u, delta, A, Bmat, Cmat, Dskip, z, delta_bias, h0, delta_softplus, exact_zoh, complex_state)
     state_shape = (p.batch, p.dim, p.dstate) + ((2,) if complex_state else ())
     if out is None:
@@ -318,7 +328,6 @@ def ss_scan_fwd_static(u, delta, A, Bmat, Cmat, Dskip=None, z=None, delta_bias=N
                        delta_softplus=False, *, out, h_last=None, exact_zoh=False, complex_state=False, stream=None):
     """Enqueue the plain forward scan with the library's own static device scratch: the call
     allocates nothing, so ``out`` (and ``h_last`` if wanted) must be given.  Returns (out, h_last)."""
-    import torch
     p = _fwd_params(u, delta, A, Bmat, Cmat, Dskip, z, delta_bias, h0, delta_softplus, exact_zoh, complex_state)
     state_shape = (p.batch, p.dim, p.dstate) + ((2,) if complex_state else ())
     p.out = _ptr(out, u.dtype, u.shape, "out")
@@ -340,7 +349,6 @@ def ss_scan_bwd(dout, u, delta, A, Bmat, Cmat, workspace, Dskip=None, z=None, de
     corresponding input was not given).  ``grads``: a dict an earlier call returned; its
     tensors are written again instead of allocating new ones.  Freshly allocated du, ddelta and dz
     are views into one allocation (``empty_channel_skewed``): it lives as long as any of them."""
-    import torch
     f32 = torch.float32
     q = BwdParams()
     q.fwd = _fwd_params(u, delta, A, Bmat, Cmat, Dskip, z, delta_bias, h0, delta_softplus, exact_zoh, complex_state)
@@ -386,7 +394,6 @@ def ss_step(h, u_t, delta_t, A, B_t, C_t, Dskip=None, z_t=None, delta_bias=None,
             stream=None):
     """Enqueue one recurrent step; ``h`` (B,D,N) float32 is updated in place.  Returns out_t.
     With ``b_fixed`` / ``c_fixed`` B_t / C_t is the time-invariant (D,N) float32 parameter."""
-    import torch
     f32 = torch.float32
     nb, nd, nn = h.shape[:3]
     c2 = (2,) if complex_state else ()
@@ -423,7 +430,6 @@ def ss_step(h, u_t, delta_t, A, B_t, C_t, Dskip=None, z_t=None, delta_bias=None,
 
 # ---------------------------------------------------------------- short causal convolution
 def _conv_params(x, w, bias, state_in, silu):
-    import torch
     f32 = torch.float32
     nb, nd, nl = x.shape
     width = w.shape[1]
@@ -445,7 +451,6 @@ def _conv_params(x, w, bias, state_in, silu):
 
 def ss_conv_fwd(x, w, bias=None, state_in=None, silu=True, out=None, return_state=False, stream=None):
     """Enqueue the causal convolution (+ SiLU).  Returns (out, state_out or None)."""
-    import torch
     p = _conv_params(x, w, bias, state_in, silu)
     if out is None:
         out = torch.empty_like(x)
@@ -463,7 +468,6 @@ def ss_conv_fwd(x, w, bias=None, state_in=None, silu=True, out=None, return_stat
 
 def ss_conv_bwd(dout, x, w, bias=None, state_in=None, silu=True, stream=None):
     """Enqueue the backward convolution.  Returns dict(dx, dw, dbias)."""
-    import torch
     q = ConvBwdParams()
     q.fwd = _conv_params(x, w, bias, state_in, silu)
     g = {"dx": torch.empty_like(x), "dw": torch.empty_like(w),
@@ -480,7 +484,6 @@ def ss_conv_bwd(dout, x, w, bias=None, state_in=None, silu=True, stream=None):
 
 def ss_conv_step(state, x_t, w, bias=None, silu=True, out_t=None, stream=None):
     """Enqueue one token of the convolution; ``state`` (B,D,W-1) is updated in place."""
-    import torch
     nb, nd = x_t.shape
     width = w.shape[1]
     p = ConvStepParams()
@@ -519,7 +522,6 @@ def ss_layer_scratch_bytes(batch, dim, seqlen, dstate, dt_rank, conv_width=4, io
 
 
 def _layer_params(x, z, conv_w, conv_b, W_x, W_dt, dt_bias, A, Dskip, saved, scratch):
-    import torch
     f32 = torch.float32
     nb, nd, nl = x.shape
     nn = A.shape[1]
@@ -549,7 +551,6 @@ def ss_layer_fwd(x, z, conv_w, conv_b, W_x, W_dt, dt_bias, A, Dskip, scratch, sa
     """Enqueue the layer's forward pass; ``saved`` (if given) is filled for ``ss_layer_bwd``.
     Returns out, or (out, h_last, conv_state) with ``return_states`` (written into the caller's
     ``h_last`` (B,D,N) float32 and ``conv_state`` (B,D,W-1) tensors if given)."""
-    import torch
     p = _layer_params(x, z, conv_w, conv_b, W_x, W_dt, dt_bias, A, Dskip, saved, scratch)
     if out is None:
         out = torch.empty_like(x)
@@ -576,7 +577,6 @@ def ss_layer_step_scratch_bytes(batch, dim, dstate, dt_rank, io_dtype=SS_BF16):
 def ss_layer_step(h, conv_state, x_t, z_t, conv_w, conv_b, W_x, W_dt, dt_bias, A, Dskip, scratch, out_t=None,
                   stream=None):
     """Enqueue one token of the layer; ``h`` (B,D,N) and ``conv_state`` (B,D,W-1) are updated in place."""
-    import torch
     f32 = torch.float32
     nb, nd, nn = h.shape
     rank = W_dt.shape[1]
@@ -609,7 +609,6 @@ def ss_layer_step(h, conv_state, x_t, z_t, conv_w, conv_b, W_x, W_dt, dt_bias, A
 
 def ss_layer_bwd(dout, x, z, conv_w, conv_b, W_x, W_dt, dt_bias, A, Dskip, scratch, saved, stream=None):
     """Enqueue the layer's backward pass.  Returns a dict of gradients (weights in float32)."""
-    import torch
     f32 = torch.float32
     q = LayerBwdParams()
     q.fwd = _layer_params(x, z, conv_w, conv_b, W_x, W_dt, dt_bias, A, Dskip, saved, scratch)
@@ -634,7 +633,6 @@ def ss_proj_gemm(A, B, C, trans_a=False, trans_b=False, accumulate=False, genera
     C is float32 or of the operands' dtype.  ``workspace``: optional uint8 device tensor of
     ``ss_proj_gemm_workspace_bytes(C)`` bytes that lets a product with few rows and columns split its
     contraction across workgroups."""
-    import torch
     def view(t):
         if t.stride(-1) != 1:
             raise ValueError("the last axis must be contiguous")
