@@ -650,8 +650,15 @@ __global__ void __launch_bounds__(THREADS, ZOH ? 1 : 2) scan_bwd_dpp_kernel(cons
         A2[k] = An[k] * LOG2E;
         invA[k] = An[k] == 0.0f ? 0.0f : 1.0f / An[k];
         if (seg == f.nseg - 1) ag4[k] = (n_ok[k] && a.dh_last) ? a.dh_last[srow * NS + nc] : 0.0f;  // abar_L g_L := dh_last
-        else ag4[k] = a.seg_g[(seg_rows + srow) * NPAD + w * STATES_PER_LANE + k];
+        else ag4[k] = f.nseg <= CARRY_INLINE ? 0.0f : a.seg_g[(seg_rows + srow) * NPAD + w * STATES_PER_LANE + k];
         dA[k] = 0.0f;
+    }
+    if (f.nseg <= CARRY_INLINE && seg < f.nseg - 1) {   // from the aggregates of the segments after this one
+        const long rows = (long)f.B * f.D, last = f.nseg - 1;
+        ag4 = chain_segments(
+            f.nseg - 1 - seg, A2,
+            [&](int i) { return *(reinterpret_cast<const f32x4_t*>(a.seg_g + ((last - i) * rows + srow) * NPAD) + w); },
+            [&](int i) { return f.seg_sumdt[(last - i) * rows + srow]; });
     }
     // the value of the cross-row sums this lane ends up with: slot vk at step vt of a block
     const int ve = lane_value(lane) & (BT * SPL - 1), vt = ve / SPL, vn = slot_state(w, ve % SPL, f.il);
@@ -1117,7 +1124,7 @@ __global__ void __launch_bounds__(THREADS) adjoint_agg_kernel(const BwdArgs a)
 // DPP operand (see scan_bwd_dpp_kernel), buffer-addressed inputs requested two chunks ahead into
 // compile-time slots, and no scalar loads.  RAG: rows of any length >= 8 and any pitch (see scan_fwd_kernel).
 template <typename T, int SPL, bool RAG = false>
-__global__ void __launch_bounds__(THREADS) adjoint_agg_dpp_kernel(const BwdArgs a)
+__global__ void __launch_bounds__(THREADS, 4) adjoint_agg_dpp_kernel(const BwdArgs a)
 {
     constexpr int NGC = CHUNK_T / GROUP_T;
     __shared__ __attribute__((aligned(16))) float s_dt[ROWS][TPAD];
@@ -1246,14 +1253,17 @@ __global__ void __launch_bounds__(THREADS) adjoint_agg_dpp_kernel(const BwdArgs 
         __syncthreads();
         __builtin_amdgcn_s_setprio(2);   // as in scan_bwd_kernel: the recurrence at a raised wave priority
         float4 dtc[NGC], dyc[NGC], Cpc[NGC];
-#pragma unroll
-        for (int g = 0; g < NGC; ++g) {
+        auto read_group = [&](int g) {
             dtc[g] = *reinterpret_cast<const float4*>(&s_dt[lane][g * GROUP_T]);
             dyc[g] = *reinterpret_cast<const float4*>(&s_dy[lane][g * GROUP_T]);
             Cpc[g] = *reinterpret_cast<const float4*>(&s_c[g][pat][0]);
-        }
+        };
+        read_group(NGC - 1);
 #pragma unroll
         for (int g = NGC - 1; g >= 0; --g) {
+            // four waves per SIMD instead of two: see the aggregate pass of scan_fwd_kernel
+            __builtin_amdgcn_sched_barrier(0);
+            if (g > 0) read_group(g - 1);
 #pragma unroll
             for (int j = GROUP_T - 1; j >= 0; --j) {
                 const float dt = f4_get(dtc[g], j), dy = f4_get(dyc[g], j);
@@ -1438,7 +1448,7 @@ static int launch_bwd_dpp_t(const BwdArgs& a, dim3 grid, hipStream_t stream)
     if (a.f.nseg > 1) {
         adjoint_agg_dpp_kernel<T, SPL, RAG><<<dim3(grid.x, (unsigned)(a.f.nseg - 1)), dim3(THREADS), 0, stream>>>(a);
         const long n = (long)a.f.B * a.f.D * NPAD;
-        carry_bwd_kernel<<<dim3((unsigned)((n + 255) / 256)), dim3(256), 0, stream>>>(a);
+        if (a.f.nseg > CARRY_INLINE) carry_bwd_kernel<<<dim3((unsigned)((n + 255) / 256)), dim3(256), 0, stream>>>(a);
     }
     auto kern = scan_bwd_dpp_kernel<T, SPL, ZOH, RAG>;
     static std::atomic<bool> lds_ok[MAX_DEVICES];   // this launcher is instantiated once per kernel

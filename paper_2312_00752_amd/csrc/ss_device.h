@@ -816,4 +816,37 @@ __device__ __forceinline__ void readout_step_dpp(float& y, float Cq, const float
 }
 #undef SS_QP
 
+// ---- segments of a split sequence --------------------------------------------------------------
+// What enters a segment from the n segments before it, for a lane's four slots: c = loc(0), then
+// c = exp(A sum_dt(i)) c + loc(i) for i = 1 .. n-1, where loc(i) / sum_dt(i) are segment i's own end state and sum
+// of step sizes (counted from the far end).  Up to CARRY_INLINE segments every workgroup works this out
+// for itself at its start: a few hundred bytes per row from the L2, loads of eight segments at a time in flight,
+// instead of a launch between the two passes that depend on each other (9 us forward and 5 us backward at
+// 8 x 1536 x 2048; the chain itself is below 2 us).  Longer chains, which every workgroup would repeat, keep the
+// kernel of their own.
+constexpr int CARRY_INLINE = 16;
+template <typename LOC, typename SUM>
+__device__ __forceinline__ f32x4_t chain_segments(int n, const float (&A2)[STATES_PER_LANE], LOC loc, SUM sum_dt)
+{
+    constexpr int BATCH = 8;
+    f32x4_t c = loc(0);
+    for (int i0 = 1; i0 < n; i0 += BATCH) {
+        f32x4_t l[BATCH];
+        float sd[BATCH];
+#pragma unroll
+        for (int j = 0; j < BATCH; ++j) {
+            const int i = min(i0 + j, n - 1);
+            l[j] = loc(i);
+            sd[j] = sum_dt(i);
+        }
+#pragma unroll
+        for (int j = 0; j < BATCH; ++j)
+            if (i0 + j < n) {   // uniform
+#pragma unroll
+                for (int k = 0; k < STATES_PER_LANE; ++k) c[k] = fmaf(exp2_fast(A2[k] * sd[j]), c[k], l[j][k]);
+            }
+    }
+    return c;
+}
+
 }  // namespace ss

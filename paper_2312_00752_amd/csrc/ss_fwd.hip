@@ -23,7 +23,8 @@ typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));   // MFMA operand a
 // When the sequence is split into segments (blockIdx.y), the kernel runs twice: first with
 // AGG = true on every segment but the last, from the zero state (segment 0: from h0),
 // producing only the segment's end state and the sum of its step sizes; then, after
-// carry_fwd_kernel has turned those into each segment's incoming state, with AGG = false.
+// carry_fwd_kernel has turned those into each segment's incoming state (with few segments every workgroup of the
+// second run does that for itself, chain_segments), with AGG = false.
 // ZOH selects the exact zero-order-hold B-bar of Eq. 4: the LDS tile that otherwise carries
 // dt*u then carries u, and each state multiplies it by phi(dt, A) = (abar - 1) / A.
 // BCFIX: bit 0 / bit 1 set when B / C is the time-invariant (D,N) float32 parameter of
@@ -60,7 +61,7 @@ typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));   // MFMA operand a
 // 4 x 1536 x 2047, all passes: 865 -> 512 us.
 template <typename T, bool VEC, bool FULLN, bool AGG, bool ZOH, int BCFIX = 0, bool CPLX = false, bool STAGED = false,
           int FUSED_KS = 0, int SPL = STATES_PER_LANE, bool PAT = false, bool RAG = false>
-__global__ void __launch_bounds__(THREADS, (PAT && FUSED_KS <= 4 && !(ZOH && AGG)) ? 2 : 1) scan_fwd_kernel(const FwdArgs a)
+__global__ void __launch_bounds__(THREADS, PAT && AGG ? 4 : ((PAT && FUSED_KS <= 4) ? 2 : 1)) scan_fwd_kernel(const FwdArgs a)
 {
     static_assert(!PAT || (VEC && BCFIX == 0 && !CPLX && !STAGED), "PAT: vector path, real state, selective B and C");
     static_assert(!RAG || PAT, "RAG: a form of the PAT kernel");
@@ -143,6 +144,8 @@ __global__ void __launch_bounds__(THREADS, (PAT && FUSED_KS <= 4 && !(ZOH && AGG
     const T* __restrict__ gB[STATES_PER_LANE];
     const T* __restrict__ gC[STATES_PER_LANE];
     bool n_ok[STATES_PER_LANE];
+    // the incoming state is worked out here from the aggregates of the segments before (see chain_segments)
+    const bool chained = PAT && !AGG && FUSED_KS == 0 && a.nseg <= CARRY_INLINE;
 #pragma unroll
     for (int k = 0; k < STATES_PER_LANE; ++k) {
         const int n = slot_state(w, k, a.il);
@@ -152,11 +155,21 @@ __global__ void __launch_bounds__(THREADS, (PAT && FUSED_KS <= 4 && !(ZOH && AGG
         A2[k] = An[k] * LOG2E;
         invA[k] = An[k] != 0.0f ? 1.0f / An[k] : 0.0f;
         if (seg == 0) h[k] = (n_ok[k] && (a.flags & F_HAS_H0)) ? a.h0[srow * NS + nc] : 0.0f;
-        else h[k] = AGG ? 0.0f : a.seg_h[((long)seg * a.B * a.D + srow) * NPAD + w * STATES_PER_LANE + k];
+        else h[k] = AGG || chained ? 0.0f : a.seg_h[((long)seg * a.B * a.D + srow) * NPAD + w * STATES_PER_LANE + k];
         gB[k] = BFIX ? nullptr : static_cast<const T*>(a.Bm) + (long)b * a.bc_bstride + (long)nc * L;
         gC[k] = CFIX ? nullptr : static_cast<const T*>(a.Cm) + (long)b * a.bc_bstride + (long)nc * L;
         Bf[k] = (BFIX && n_ok[k]) ? static_cast<const float*>(a.Bm)[(long)sd * NS + nc] : 0.0f;
         Cf[k] = (CFIX && n_ok[k]) ? static_cast<const float*>(a.Cm)[(long)sd * NS + nc] : 0.0f;
+    }
+    if constexpr (PAT && !AGG && FUSED_KS == 0) {
+        if (chained && seg > 0) {
+            const long rows = (long)a.B * a.D;
+            const f32x4_t c = chain_segments(
+                seg, A2, [&](int s) { return *(reinterpret_cast<const f32x4_t*>(a.seg_h + (s * rows + srow) * NPAD) + w); },
+                [&](int s) { return a.seg_sumdt[s * rows + srow]; });
+#pragma unroll
+            for (int k = 0; k < STATES_PER_LANE; ++k) h[k] = c[k];
+        }
     }
     // staged B and C: this wave's pieces, one per group of steps, consecutive in memory
     const T* __restrict__ const sbc =
@@ -217,15 +230,19 @@ __global__ void __launch_bounds__(THREADS, (PAT && FUSED_KS <= 4 && !(ZOH && AGG
             const uint32_t t = (uint32_t)row_piece(cc + pq * SLICE, SLICE, L) * esz;
             ru_[s] = io8<T>::load_elem(ru_p, r_off_ud + t);
             if constexpr (FUSED_KS == 0) rd_[s] = io8<T>::load_elem(rd_p, r_off_ud + t);
-            rz_[s] = io8<T>::load_elem(rz_p, has_z ? r_off + t : 0u);
-            rp_[s] = io8<T>::load_elem(rp_p, acc_on ? r_off + t : 0u);
+            if constexpr (!AGG) {
+                rz_[s] = io8<T>::load_elem(rz_p, has_z ? r_off + t : 0u);
+                rp_[s] = io8<T>::load_elem(rp_p, acc_on ? r_off + t : 0u);
+            }
             rbc_[s] = io4<T>::load_elem(rbc_p, r_off_bc + (uint32_t)row_piece(cc + s_tq * GROUP_T, GROUP_T, L) * esz);
         } else if constexpr (VEC) {   // slices are whole or empty
             const uint32_t off = (nv == SLICE && c < c_end) ? row_off + (uint32_t)t0 * (uint32_t)sizeof(T) : BUF_OFF;
             ru_[s] = io8<T>::load_buf(bu, off);
             if constexpr (FUSED_KS == 0) rd_[s] = io8<T>::load_buf(bd, off);
-            rz_[s] = io8<T>::load_buf(bz, off);
-            rp_[s] = io8<T>::load_buf(bp, off);
+            if constexpr (!AGG) {
+                rz_[s] = io8<T>::load_buf(bz, off);
+                rp_[s] = io8<T>::load_buf(bp, off);
+            }
             if constexpr (PAT) {   // L % 8 == 0: a group of four steps is whole or past the end
                 const int ts = c * CHUNK_T + s_tq * GROUP_T;
                 rbc_[s] = io4<T>::load_buf(bbc, (ts < L && c < c_end) ? bc_row_off + (uint32_t)ts * (uint32_t)sizeof(T) : BUF_OFF);
@@ -304,8 +321,10 @@ __global__ void __launch_bounds__(THREADS, (PAT && FUSED_KS <= 4 && !(ZOH && AGG
         }
         ru_[0] = io8<T>::load_elem(ru_p, r_off_ud + t[0]); ru_[1] = io8<T>::load_elem(ru_p, r_off_ud + t[1]);
         if constexpr (FUSED_KS == 0) { rd_[0] = io8<T>::load_elem(rd_p, r_off_ud + t[0]); rd_[1] = io8<T>::load_elem(rd_p, r_off_ud + t[1]); }
-        rz_[0] = io8<T>::load_elem(rz_p, has_z ? r_off + t[0] : 0u); rz_[1] = io8<T>::load_elem(rz_p, has_z ? r_off + t[1] : 0u);
-        rp_[0] = io8<T>::load_elem(rp_p, acc_on ? r_off + t[0] : 0u); rp_[1] = io8<T>::load_elem(rp_p, acc_on ? r_off + t[1] : 0u);
+        if constexpr (!AGG) {
+            rz_[0] = io8<T>::load_elem(rz_p, has_z ? r_off + t[0] : 0u); rz_[1] = io8<T>::load_elem(rz_p, has_z ? r_off + t[1] : 0u);
+            rp_[0] = io8<T>::load_elem(rp_p, acc_on ? r_off + t[0] : 0u); rp_[1] = io8<T>::load_elem(rp_p, acc_on ? r_off + t[1] : 0u);
+        }
         rbc_[0] = io4<T>::load_elem(rbc_p, tb[0]); rbc_[1] = io4<T>::load_elem(rbc_p, tb[1]);
       } else if constexpr (PAIR) {
         uint32_t off[2], boff[2];
@@ -319,8 +338,10 @@ __global__ void __launch_bounds__(THREADS, (PAT && FUSED_KS <= 4 && !(ZOH && AGG
         }
         ru_[0] = io8<T>::load_buf(bu, off[0]); ru_[1] = io8<T>::load_buf(bu, off[1]);
         if constexpr (FUSED_KS == 0) { rd_[0] = io8<T>::load_buf(bd, off[0]); rd_[1] = io8<T>::load_buf(bd, off[1]); }
-        rz_[0] = io8<T>::load_buf(bz, off[0]); rz_[1] = io8<T>::load_buf(bz, off[1]);
-        rp_[0] = io8<T>::load_buf(bp, off[0]); rp_[1] = io8<T>::load_buf(bp, off[1]);
+        if constexpr (!AGG) {
+            rz_[0] = io8<T>::load_buf(bz, off[0]); rz_[1] = io8<T>::load_buf(bz, off[1]);
+            rp_[0] = io8<T>::load_buf(bp, off[0]); rp_[1] = io8<T>::load_buf(bp, off[1]);
+        }
         rbc_[0] = io4<T>::load_buf(bbc, boff[0]); rbc_[1] = io4<T>::load_buf(bbc, boff[1]);
       }
     };
@@ -353,7 +374,7 @@ __global__ void __launch_bounds__(THREADS, (PAT && FUSED_KS <= 4 && !(ZOH && AGG
                 const int sh = t0 - row_piece(t0, SLICE, L), ts = tc + s_tq * GROUP_T;
                 io8<T>::drop(ru, sh);
                 if constexpr (FUSED_KS == 0) io8<T>::drop(rd, sh);
-                io8<T>::drop(rz, sh);
+                if constexpr (!AGG) io8<T>::drop(rz, sh);
                 if (acc_on) io8<T>::drop(rp_[SLOT], sh);
                 io4<T>::drop(rbc, ts - row_piece(ts, GROUP_T, L));
             }
@@ -468,14 +489,23 @@ __global__ void __launch_bounds__(THREADS, (PAT && FUSED_KS <= 4 && !(ZOH && AGG
         // the loop, and inside it only the scalar loads of the next group are outstanding.
         float4 dtc[NG], duc[NG], Bpc[PAT ? NG : 1], Cpc[PAT ? NG : 1];
         const int pat = slot_state(w, lane & 3, a.il);   // PAT: the state of slot lane % 4
-#pragma unroll
-        for (int g = 0; g < NG; ++g) {
+        auto read_group = [&](int g) {
             dtc[g] = *reinterpret_cast<const float4*>(&s_dt[lane][g * GROUP_T]);
             duc[g] = *reinterpret_cast<const float4*>(&s_du[lane][g * GROUP_T]);
             if constexpr (PAT) {
                 Bpc[g] = *reinterpret_cast<const float4*>(&s_bc[0][g][pat][0]);
                 if (!AGG) Cpc[g] = *reinterpret_cast<const float4*>(&s_bc[1][g][pat][0]);
             }
+        };
+        // The aggregate pass has little LDS and nothing but the recurrence, so it runs four waves per SIMD: a group
+        // is read one ahead, and the barrier below keeps the scheduler from starting every later group early
+        // (which took all 256 or 512 registers, spills included, and one or two waves per SIMD).
+        constexpr bool LEAN = PAT && AGG;
+        if constexpr (LEAN) {
+            read_group(0);
+        } else {
+#pragma unroll
+            for (int g = 0; g < NG; ++g) read_group(g);
         }
         if constexpr (STAGED) {
 #pragma unroll
@@ -490,6 +520,10 @@ __global__ void __launch_bounds__(THREADS, (PAT && FUSED_KS <= 4 && !(ZOH && AGG
                 if (g + 1 < NG) fetch_bc(g + 1, cur ^ 1);  // in flight while group g is consumed
             }
             const int tl = g * GROUP_T;  // step within the chunk
+            if constexpr (LEAN) {
+                __builtin_amdgcn_sched_barrier(0);
+                if (g + 1 < NG) read_group(g + 1);
+            }
             const float4 dt4 = dtc[g], du4 = duc[g];
             if (g > 0 && tl % CKPT_T == 0) save_ckpt((tc + tl) / CKPT_T);
             float yp[GROUP_T];
@@ -548,6 +582,8 @@ __global__ void __launch_bounds__(THREADS, (PAT && FUSED_KS <= 4 && !(ZOH && AGG
             }
             if (!AGG)
                 *reinterpret_cast<float4*>(&s_yp[w][lane][tl]) = make_float4(yp[0], yp[1], yp[2], yp[3]);
+            if constexpr (LEAN)   // the group ends here: left alone, half of the chunk's arithmetic sinks below the barriers
+                asm volatile("" : "+v"(h[0]), "+v"(h[1]), "+v"(h[2]), "+v"(h[3]));
         }
         // delta_raw of the next chunk, before the barrier: the next phase A rewrites s_rT after it
         if (c + 1 < c_end) project();
@@ -1206,7 +1242,7 @@ static void launch_fwd_dpp_t(const FwdArgs& a, hipStream_t stream)
     if (a.nseg > 1) {
         scan_fwd_kernel<T, true, false, true, ZOH, 0, false, false, 0, SPL, true, RAG><<<dim3((unsigned)(a.B * groups), (unsigned)(a.nseg - 1)), block, 0, stream>>>(a);
         const long n = (long)a.B * a.D * NPAD;
-        carry_fwd_kernel<<<dim3((unsigned)((n + 255) / 256)), dim3(256), 0, stream>>>(a);
+        if (a.nseg > CARRY_INLINE) carry_fwd_kernel<<<dim3((unsigned)((n + 255) / 256)), dim3(256), 0, stream>>>(a);
     }
     if constexpr (sizeof(T) == 2 && !ZOH && SPL == STATES_PER_LANE) {
         if (a.W_dt) {   // the caller has checked: unsplit, R <= 256
