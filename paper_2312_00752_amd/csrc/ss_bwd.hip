@@ -172,12 +172,10 @@ __device__ __forceinline__ int lane_value(int lane)
 // BCFIX (bit 0: B, bit 1: C): the operand is the time-invariant (D,N) parameter; it is held in
 // registers like A and its gradient, a sum over batch and time, is accumulated per lane like
 // dA instead of being reduced over the rows of the workgroup.
-// The exact-ZOH and time-invariant-B/C variants need more registers than two workgroups per
-// compute unit leave (they spilled hundreds); they are built for one workgroup per unit instead.
-// (Exact ZOH with sixteen states and whole 16-byte pieces runs on scan_bwd_dpp_kernel; this kernel
-// takes its other shapes.)
+// Exact ZOH with a time-invariant B or C needs more registers than two workgroups per compute unit leave; it is
+// built for one.  (Exact ZOH with selective B and C runs on scan_bwd_dpp_kernel but for the shortest rows.)
 template <typename T, bool VEC, bool FULLN, bool ZOH, int BCFIX = 0, bool CPLX = false>
-__global__ void __launch_bounds__(THREADS, (ZOH || BCFIX != 0) ? 1 : 2) scan_bwd_kernel(const BwdArgs a)
+__global__ void __launch_bounds__(THREADS, ZOH ? 1 : 2) scan_bwd_kernel(const BwdArgs a)
 {
     extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
     BwdSmem& sm = *reinterpret_cast<BwdSmem*>(smem_raw);
@@ -385,6 +383,7 @@ __global__ void __launch_bounds__(THREADS, (ZOH || BCFIX != 0) ? 1 : 2) scan_bwd
                     if (g > 0) reduce_take(red, dbc + STATES_PER_LANE * BT + tl - GROUP_T, lane);  // previous group
                     reduce_put(dCv, red, lane);
                 }
+                if (CFIX) asm volatile("" : "+v"(dCf[0]), "+v"(dCf[1]), "+v"(dCf[2]), "+v"(dCf[3]));
             }
             if (!CFIX) reduce_take(red, dbc + STATES_PER_LANE * BT + (NG - 1) * GROUP_T, lane);
         }
@@ -461,6 +460,9 @@ __global__ void __launch_bounds__(THREADS, (ZOH || BCFIX != 0) ? 1 : 2) scan_bwd
                 if (g < NG - 1) reduce_take(red, dbc + tl + GROUP_T, lane);  // previous (later) group
                 reduce_put(dBv, red, lane);
             }
+            // the sums that only the end of the loop reads are formed here, not below the sweep (see scan_bwd_dpp_kernel)
+            asm volatile("" : "+v"(dA[0]), "+v"(dA[1]), "+v"(dA[2]), "+v"(dA[3]));
+            if (BFIX) asm volatile("" : "+v"(dBf[0]), "+v"(dBf[1]), "+v"(dBf[2]), "+v"(dBf[3]));
         }
         if (!BFIX) reduce_take(red, dbc, lane);
         // ---- flush this wave's dB/dC of the block to global memory -------------------------
@@ -572,11 +574,12 @@ struct BwdSmemDpp {
 //     dB  = sum_d (g phi) u                          dA_n += g abar h_prev dt + g B u dphi/dA,
 // where g dphi/dA = (abar g dt - g phi)/A needs neither a division nor dphi itself.  That difference cancels
 // like dt A / 2 and so magnifies phi's own rounding error by 2 / |dt A|: below |dt A| = 2^-4 (and for A = 0)
-// the term is g dt^2 (1/2 + x/3 + x^2/8) instead.
+// the term is g dt^2 (1/2 + x/3 + x^2/8) instead.  (8 x 1536 x 2048 bf16: 731 us with one workgroup per compute unit
+// and 361 registers, 553 us with two and 256.)
 // RAG: rows of any length >= 8 and any pitch (see scan_fwd_kernel).  Slices are read at element alignment from
 // inside the row and shifted into place, and rows past D cleared, in the blocks that need it only.
 template <typename T, int SPL, bool ZOH = false, bool RAG = false>
-__global__ void __launch_bounds__(THREADS, ZOH ? 1 : 2) scan_bwd_dpp_kernel(const BwdArgs a)
+__global__ void __launch_bounds__(THREADS, 2) scan_bwd_dpp_kernel(const BwdArgs a)
 {
     extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
     BwdSmemDpp& sm = *reinterpret_cast<BwdSmemDpp*>(smem_raw);
@@ -914,6 +917,9 @@ __global__ void __launch_bounds__(THREADS, ZOH ? 1 : 2) scan_bwd_dpp_kernel(cons
             *reinterpret_cast<float4*>(&sm.pdd[w][lane][tl]) = make_float4(dd[0], dd[1], dd[2], dd[3]);
             *reinterpret_cast<float4*>(&sm.psb[w][lane][tl]) = make_float4(sb[0], sb[1], sb[2], sb[3]);
             sB[g] = merge_group<SPL>(dBv, lane);
+            // The group's arithmetic ends here.  (Left alone, the sums of dA, which only the end of the loop reads, sink
+            // below everything else, and 140 values wait in scratch memory for them.)
+            if constexpr (ZOH) asm volatile("" : "+v"(dA[0]), "+v"(dA[1]), "+v"(dA[2]), "+v"(dA[3]), "+v"(sB[g]));
         }
         // ---- flush this wave's dB/dC of the block to global memory -------------------------
         const float dB_total = merge_block<SPL>(sB, lane);
