@@ -433,7 +433,7 @@ static int step_impl(const ss_step_params* p, long bc_stride, const float* P, co
         if (q && !aligned(q, esz)) return SS_ERR_ALIGN;
     if (!P && (!aligned(p->B_t, (p->flags & SS_B_FIXED) ? 4 : esz) || !aligned(p->C_t, (p->flags & SS_C_FIXED) ? 4 : esz)))
         return SS_ERR_ALIGN;
-    if (P && (!aligned(P, 16) || !aligned(W_dt, 16) || !aligned(p->h, 16) || R % 8 != 0 || ldp % 4 != 0)) return SS_ERR_ALIGN;
+    if (P && (!aligned(P, 16) || !aligned(W_dt, 16) || !aligned(p->h, 16))) return SS_ERR_ALIGN;
     const void* f32[] = {p->A, p->Dskip, p->delta_bias};
     for (const void* q : f32)
         if (q && !aligned(q, 4)) return SS_ERR_ALIGN;
@@ -443,7 +443,7 @@ static int step_impl(const ss_step_params* p, long bc_stride, const float* P, co
     a.B_t = P ? nullptr : p->B_t; a.C_t = P ? nullptr : p->C_t; a.bc_stride = bc_stride;
     a.P = P; a.W_dt = W_dt; a.R = R; a.ldp = ldp; a.A = p->A; a.Dskip = p->Dskip; a.bias = p->delta_bias;
     a.out_t = p->out_t;
-    if (P) return ss::launch_step_projected(a, static_cast<hipStream_t>(stream)) == 0 ? SS_OK : SS_ERR_LAUNCH;
+    if (P) return ss::launch_step_projected(a, p->io_dtype, static_cast<hipStream_t>(stream)) == 0 ? SS_OK : SS_ERR_LAUNCH;
     return ss::launch_step(a, p->io_dtype, static_cast<hipStream_t>(stream)) == 0 ? SS_OK : SS_ERR_LAUNCH;
 }
 
@@ -455,7 +455,7 @@ int step_strided(const ss_step_params* p, long bc_stride, void* stream)
 int step_projected(const ss_step_params* p, const float* P, const void* W_dt, int R, int ldp, void* stream)
 {
     if (!p || !P || !W_dt) return SS_ERR_NULL;
-    if (p->io_dtype != SS_BF16 || R > 256 || p->dstate > 16 || ldp > 256 + 2 * 16) return SS_ERR_UNSUPPORTED;
+    if (R < 8 || R > 256 || p->dstate > 16 || ldp != R + 2 * p->dstate) return SS_ERR_UNSUPPORTED;
     return step_impl(p, 0, P, W_dt, R, ldp, stream);
 }
 

@@ -242,6 +242,30 @@ __device__ __forceinline__ u32x4 drop_front(u32x4 v, int n)
     return u32x4{(uint32_t)a, (uint32_t)(a >> 32), (uint32_t)b, (uint32_t)(b >> 32)};
 }
 
+// ---- 16 x 16 products on the matrix cores, either io type ----------------------------------------------
+// One 16-byte piece per lane and operand: lane l holds row (column) l % 16 at the E consecutive contraction
+// indices from E * (l / 16); accumulator element i of lane l is row 4 * (l / 16) + i, column l % 16.  bf16: one
+// 16x16x32 MFMA.  float: four 16x16x4 MFMAs, the i-th of which contracts over element i of the four lane groups.
+typedef float f32x4_t __attribute__((ext_vector_type(4)));
+template <typename T>
+struct tile_mma {
+    static constexpr int E = 16 / (int)sizeof(T), K = 4 * E;   // elements per piece, contraction indices per step
+    static __device__ __forceinline__ f32x4_t step(u32x4 a, u32x4 b, f32x4_t c)
+    {
+        if constexpr (sizeof(T) == 2) {
+            typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+            return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
+        } else {
+#pragma unroll
+            for (int i = 0; i < 4; ++i) c = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(a[i]), __uint_as_float(b[i]), c, 0, 0, 0);
+            return c;
+        }
+    }
+    // the piece from index k of a row of n >= E elements, at element alignment from inside the row, and shifted into place
+    static __device__ __forceinline__ u32x4 load(const T* row, int k, int n) { return load_any<u32x4>(row + row_piece(k, E, n), 0u); }
+    static __device__ __forceinline__ u32x4 cut(u32x4 v, int k, int n) { return drop_front<8 * (int)sizeof(T)>(v, k - row_piece(k, E, n)); }
+};
+
 // ---- 8 consecutive io elements <-> 8 floats -------------------------------------------
 // VEC: every row starts 16-byte aligned and L is a multiple of 8, so a slice is either
 // whole (nvalid == 8, one or two 16-byte accesses) or empty.  Otherwise the `nvalid`
@@ -710,7 +734,6 @@ __device__ __forceinline__ void consume_touch(uint32_t v) { asm volatile("" ::"v
 // quad_perm [k,k,k,k]: every lane then reads slot k's value.  The compiler folds such a broadcast
 // into a multiply only now and then and never into a multiply-add with an accumulator, so these
 // instruction groups are written out.
-typedef float f32x4_t __attribute__((ext_vector_type(4)));
 
 // The input term of Eq. 2a for a lane's SPL states: bu[k] = B_k * du, with Bq holding B of the
 // wave's states in every group of four lanes (slot k in lane k).  Written out for the same

@@ -964,9 +964,9 @@ __global__ void __launch_bounds__(256) step_multi_kernel(const StepArgs a)
     }
 }
 
-// Single-token step of the layer's decode (bf16 I/O): as step_kernel, but delta_t, B_t and C_t come
+// Single-token step of the layer's decode : as step_kernel, but delta_t, B_t and C_t come
 // from the float32 output P = [r; B; C] of the projection (the sum of STEP_NPARTS partial results,
-// rounded to bf16 as the layer stores it) and delta_t = W_dt r_t + bias is formed here.  A workgroup
+// rounded to the io type as the layer stores it) and delta_t = W_dt r_t + bias is formed here.  A workgroup
 // owns 64 channels and a tile of BT = 16 or 8 batch entries.  It stages the tile's rows of P in LDS;
 // four of its eight waves then form the 16 x 64 block of W_dt r_t on the matrix cores (one 16 x 16
 // tile per wave, rows past the tile shadowing its last one, W_dt rows straight from global memory)
@@ -975,19 +975,21 @@ __global__ void __launch_bounds__(256) step_multi_kernel(const StepArgs a)
 // batch entries.  The 8-entry tile needs fewer registers (two workgroups per CU instead of one) and
 // gives twice the workgroups; the launcher picks the tile from the number of workgroups each gives.  The state, u and z of those entries are
 // requested before anything else, so that their latency overlaps the projection.  Real, first-order,
-// selective B / C only; R <= 256 and a multiple of 8, N <= 16.
+// selective B / C only; 8 <= R <= 256, N <= 16.  Rows of W_dt are read at element alignment, their last piece cut.
 constexpr int SP_MFMA_ROWS = 16;                  // rows of the MFMA tile: the largest batch tile
 constexpr int SP_THREADS = 512;                   // 64 channels x 4 quarters x 2 halves of the batch tile
-constexpr int STEP_MAX_LDP = 256 + 2 * NPAD;      // R <= 256 and N <= 16 on this path
-constexpr int SP_MAX_KSTEPS = 256 / 32;             // contraction steps of the delta projection (R <= 256)
+constexpr int SP_MAX_R = 256;
+constexpr int STEP_MAX_LDP = SP_MAX_R + 2 * NPAD;   // R <= 256 and N <= 16 on this path
 constexpr int SP_LDP = STEP_MAX_LDP + 4;          // row stride of the staged P in floats: 16-byte rows, off the banks
 
-template <bool FULLN, int SP_BT>
-__global__ void __launch_bounds__(SP_THREADS) step_proj_kernel(const StepArgs a)
+template <typename T, bool FULLN, int SP_BT>
+__global__ void __launch_bounds__(SP_THREADS, SP_BT == 8 && sizeof(T) == 2 ? 4 : 2) step_proj_kernel(const StepArgs a)
 {
     static_assert(SP_BT == 8 || SP_BT == SP_MFMA_ROWS, "batch tile");
     constexpr int SP_PER = SP_BT / 2;                // batch entries per thread
-    __shared__ __attribute__((aligned(16))) float s_p[SP_BT][SP_LDP];
+    using mma = tile_mma<T>;
+    constexpr int SP_MAX_KSTEPS = SP_MAX_R / mma::K;  // contraction steps of the delta projection
+    __shared__ __attribute__((aligned(16))) float s_p[SP_BT][SP_LDP];   // r, and from SP_MAX_R on B and C
     __shared__ float s_dt[SP_MFMA_ROWS][64];
     const int tid = threadIdx.x;
     const int lane = tid & 63;
@@ -999,9 +1001,14 @@ __global__ void __launch_bounds__(SP_THREADS) step_proj_kernel(const StepArgs a)
     const int N = a.N, R = a.R;
     const int b0 = blockIdx.y * SP_BT;
     const int nbt = min(SP_BT, a.B - b0);            // batch entries of this tile
-    const bf16_t* u_t = static_cast<const bf16_t*>(a.u_t);
-    const bf16_t* z_t = static_cast<const bf16_t*>(a.z_t);
-    auto as_stored = [](float v) -> float { return bf16_to_f32(bf16_t(f32_to_bf16_bits(v))); };
+    const T* u_t = static_cast<const T*>(a.u_t);
+    const T* z_t = static_cast<const T*>(a.z_t);
+    auto cvt = [](T v) -> float {
+        if constexpr (sizeof(T) == 2) return bf16_to_f32(v); else return v;
+    };
+    auto as_stored = [](float v) -> float {
+        if constexpr (sizeof(T) == 2) return bf16_to_f32(bf16_t(f32_to_bf16_bits(v))); else return v;
+    };
 
     // Everything the thread needs from global memory is requested here, in straight-line code
     // with no branch between the loads (optional operands are read through a valid stand-in
@@ -1009,9 +1016,9 @@ __global__ void __launch_bounds__(SP_THREADS) step_proj_kernel(const StepArgs a)
     // wait for that load before issuing the next, one memory latency after another.
     const int sq = q * STATES_PER_LANE;               // this quarter's first state
     const bool has_z = a.flags & F_HAS_Z, has_D = a.flags & F_HAS_D, has_bias = a.flags & F_HAS_DELTA_BIAS;
-    const bf16_t* zp = has_z ? z_t : u_t;
+    const T* zp = has_z ? z_t : u_t;
     float hv[SP_PER][STATES_PER_LANE];
-    bf16_t ub_raw[SP_PER], zb_raw[SP_PER];
+    T ub_raw[SP_PER], zb_raw[SP_PER];
 #pragma unroll
     for (int i = 0; i < SP_PER; ++i) {
         const int b = min(b0 + half * SP_PER + i, a.B - 1);
@@ -1032,21 +1039,17 @@ __global__ void __launch_bounds__(SP_THREADS) step_proj_kernel(const StepArgs a)
     const float D_raw = (has_D ? a.Dskip : a.A)[has_D ? d : 0];
 
     // Waves 0-3 form the tile (batch entries) x (channels d0 + 16 * wave ..+15) of r W_dt^T after
-    // the staging below.  Operand layout of the 16x16x32 bf16 MFMA: lane l holds row (column)
-    // l % 16 of the first (second) operand at contraction indices 8 * (l / 16) ..+7; accumulator
-    // element i of lane l is row 4 * (l / 16) + i, column l % 16.  Their pieces of W_dt are
-    // requested now, with everything else (from a clamped, valid address; zeroed below where the
-    // piece lies past R).
+    // the staging below (fragments as tile_mma describes).  Their pieces of W_dt are requested now, with everything
+    // else (from a clamped, valid place; what lies past R meets zeros of r below).
     const int dcol = 16 * (wave & 3) + (lane & 15);
     const int wrow = min(d0 + dcol, a.D - 1);
-    const int ksub = 8 * (lane >> 4);
-    union WFrag { unsigned short s[8]; bf16x8_t v; } wfrag[SP_MAX_KSTEPS];
+    const int ksub = mma::E * (lane >> 4);
+    u32x4 wfrag[SP_MAX_KSTEPS];
     const float bias_raw = (has_bias ? a.bias : a.A)[has_bias ? wrow : 0];
     {
-        const bf16_t* wp = static_cast<const bf16_t*>(a.W_dt) + (long)wrow * R;
+        const T* wp = static_cast<const T*>(a.W_dt) + (long)wrow * R;
 #pragma unroll
-        for (int i = 0; i < SP_MAX_KSTEPS; ++i)
-            wfrag[i].v = *reinterpret_cast<const bf16x8_t*>(wp + min(32 * i + ksub, R - 8));   // R is a multiple of 8
+        for (int i = 0; i < SP_MAX_KSTEPS; ++i) wfrag[i] = mma::load(wp, mma::K * i + ksub, R);
     }
 
     {
@@ -1069,7 +1072,8 @@ __global__ void __launch_bounds__(SP_THREADS) step_proj_kernel(const StepArgs a)
             float s = v[j][0];
 #pragma unroll
             for (int k = 1; k < STEP_NPARTS; ++k) s += v[j][k];
-            if (i < count) s_p[i / a.ldp][i % a.ldp] = as_stored(s);
+            const int col = i % a.ldp;
+            if (i < count) s_p[i / a.ldp][col < R ? col : SP_MAX_R + col - R] = as_stored(s);
         }
     }
     __syncthreads();
@@ -1080,19 +1084,26 @@ __global__ void __launch_bounds__(SP_THREADS) step_proj_kernel(const StepArgs a)
         f32x4_t acc = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
         for (int i = 0; i < SP_MAX_KSTEPS; ++i) {
-            const int k = 32 * i;
+            const int k = mma::K * i;
             if (k < R) {                                      // uniform
-                union { unsigned short s[8]; bf16x8_t v; } av;
+                float pv[mma::E];
 #pragma unroll
-                for (int e = 0; e < 8; ++e) av.s[e] = 0;
-                if (k + ksub < R) {                           // R is a multiple of 8
-                    const float4 p0 = *reinterpret_cast<const float4*>(pp + k);
-                    const float4 p1 = *reinterpret_cast<const float4*>(pp + k + 4);
-                    const float pv[8] = {p0.x, p0.y, p0.z, p0.w, p1.x, p1.y, p1.z, p1.w};
-#pragma unroll
-                    for (int e = 0; e < 8; ++e) av.s[e] = (unsigned short)(__float_as_uint(pv[e]) >> 16);   // exact: rounded above
+                for (int e = 0; e < mma::E; e += 4) {
+                    const float4 p4 = *reinterpret_cast<const float4*>(pp + k + e);
+                    pv[e] = p4.x; pv[e + 1] = p4.y; pv[e + 2] = p4.z; pv[e + 3] = p4.w;
                 }
-                acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av.v, wfrag[i].v, acc, 0, 0, 0);
+                u32x4 av, wv = wfrag[i];
+                if (k + mma::K > R) {                         // uniform: the last step
+                    wv = mma::cut(wv, k + ksub, R);
+#pragma unroll
+                    for (int e = 0; e < mma::E; ++e) pv[e] = k + ksub + e < R ? pv[e] : 0.0f;
+                }
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    if constexpr (sizeof(T) == 2) av[e] = pack_bf16x2(pv[2 * e], pv[2 * e + 1]);   // exact: rounded above
+                    else av[e] = __float_as_uint(pv[e]);
+                }
+                acc = mma::step(av, wv, acc);
             }
         }
 #pragma unroll
@@ -1119,20 +1130,20 @@ __global__ void __launch_bounds__(SP_THREADS) step_proj_kernel(const StepArgs a)
         const long row = (long)(b0 + bl) * a.D + d;
         const float* pb = s_p[bl];
         const float dt = s_dt[bl][dl];
-        const float u = bf16_to_f32(ub_raw[i]);
+        const float u = cvt(ub_raw[i]);
         const float du = dt * u;
         float Bq[STATES_PER_LANE], Cq[STATES_PER_LANE];
         if constexpr (FULLN) {
-            const float4 b4 = *reinterpret_cast<const float4*>(pb + R + sq);
-            const float4 c4 = *reinterpret_cast<const float4*>(pb + R + NPAD + sq);
+            const float4 b4 = *reinterpret_cast<const float4*>(pb + SP_MAX_R + sq);
+            const float4 c4 = *reinterpret_cast<const float4*>(pb + SP_MAX_R + NPAD + sq);
             Bq[0] = b4.x; Bq[1] = b4.y; Bq[2] = b4.z; Bq[3] = b4.w;
             Cq[0] = c4.x; Cq[1] = c4.y; Cq[2] = c4.z; Cq[3] = c4.w;
         } else {
 #pragma unroll
             for (int k = 0; k < STATES_PER_LANE; ++k) {
                 const bool ok = sq + k < N;
-                Bq[k] = ok ? pb[R + sq + k] : 0.0f;
-                Cq[k] = ok ? pb[R + N + sq + k] : 0.0f;
+                Bq[k] = ok ? pb[SP_MAX_R + sq + k] : 0.0f;
+                Cq[k] = ok ? pb[SP_MAX_R + N + sq + k] : 0.0f;
             }
         }
         float y = 0.0f;
@@ -1156,10 +1167,13 @@ __global__ void __launch_bounds__(SP_THREADS) step_proj_kernel(const StepArgs a)
         y += __shfl_xor(y, 2);
         y = fmaf(Dsk, u, y);
         if (has_z) {
-            const float z = bf16_to_f32(zb_raw[i]);
+            const float z = cvt(zb_raw[i]);
             y *= z * sigmoid_fast(z);
         }
-        if (d_ok && q == 0) static_cast<bf16_t*>(a.out_t)[row] = bf16_t(f32_to_bf16_bits(y));
+        if (d_ok && q == 0) {
+            if constexpr (sizeof(T) == 2) static_cast<bf16_t*>(a.out_t)[row] = bf16_t(f32_to_bf16_bits(y));
+            else static_cast<float*>(a.out_t)[row] = y;
+        }
     }
 }
 
@@ -1377,7 +1391,8 @@ int launch_step(const StepArgs& a, int io_dtype, hipStream_t stream)
     return hipGetLastError() == hipSuccess ? 0 : -1;
 }
 
-int launch_step_projected(const StepArgs& a, hipStream_t stream)
+template <typename T>
+static void launch_step_projected_t(const StepArgs& a, hipStream_t stream)
 {
     // One workgroup per CU is the fastest arrangement (the state streams while the projection's
     // dependent steps run), so: 8-entry batch tiles while they fit the chip's 256 CUs once, 16-entry
@@ -1389,12 +1404,18 @@ int launch_step_projected(const StepArgs& a, hipStream_t stream)
     const dim3 grid((unsigned)groups, (unsigned)(wide ? (a.B + SP_MFMA_ROWS - 1) / SP_MFMA_ROWS : (a.B + 7) / 8));
     const dim3 block(SP_THREADS);
     if (a.N == NPAD) {
-        if (wide) step_proj_kernel<true, SP_MFMA_ROWS><<<grid, block, 0, stream>>>(a);
-        else step_proj_kernel<true, 8><<<grid, block, 0, stream>>>(a);
+        if (wide) step_proj_kernel<T, true, SP_MFMA_ROWS><<<grid, block, 0, stream>>>(a);
+        else step_proj_kernel<T, true, 8><<<grid, block, 0, stream>>>(a);
     } else {
-        if (wide) step_proj_kernel<false, SP_MFMA_ROWS><<<grid, block, 0, stream>>>(a);
-        else step_proj_kernel<false, 8><<<grid, block, 0, stream>>>(a);
+        if (wide) step_proj_kernel<T, false, SP_MFMA_ROWS><<<grid, block, 0, stream>>>(a);
+        else step_proj_kernel<T, false, 8><<<grid, block, 0, stream>>>(a);
     }
+}
+
+int launch_step_projected(const StepArgs& a, int io_dtype, hipStream_t stream)
+{
+    if (io_dtype == 0) launch_step_projected_t<float>(a, stream);
+    else launch_step_projected_t<bf16_t>(a, stream);
     return hipGetLastError() == hipSuccess ? 0 : -1;
 }
 

@@ -105,7 +105,7 @@ int launch_fwd(const FwdArgs& a, int io_dtype, hipStream_t stream);
 int launch_stage_bc(const FwdArgs& a, void* bcs, int io_dtype, hipStream_t stream);
 int launch_bwd(const BwdArgs& a, int io_dtype, hipStream_t stream);
 int launch_step(const StepArgs& a, int io_dtype, hipStream_t stream);
-int launch_step_projected(const StepArgs& a, hipStream_t stream);   // bf16 I/O only
+int launch_step_projected(const StepArgs& a, int io_dtype, hipStream_t stream);
 
 // The public scan entry points with one extra degree of freedom: B and C of batch entry b
 // start b * bc_bstride elements after Bmat / Cmat (the public calls pass dstate * seqlen).

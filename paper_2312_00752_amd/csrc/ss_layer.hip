@@ -68,52 +68,60 @@ __global__ void sum_partials_kernel(const T* __restrict__ part, int nb, long n, 
 }
 
 // ---- decode: [r;B;C]_t = u_t @ W_x^T on the matrix cores --------------------------------------------
-// P (nb, nm) float32 = u (nb, D) @ W (nm, D)^T, both operands bf16 with the contraction index
-// contiguous, which is exactly how v_mfma_f32_16x16x32_bf16 wants its fragments: lane l supplies row
-// l % 16 of either operand and the 8 consecutive k starting at 8 * (l / 16), one 16-byte load each, no
-// staging.  The product is tiny (64 x 160 x 4096 for the headline layer) and bound by the latency of
-// getting W and u on chip, so it is spread thin: workgroup (x, y, z) owns the 16 x 16 tile (x, y) of P
-// over the z-th part of the contraction index and spreads that part over its eight waves (k-steps of
-// 32, four per wave); the waves' accumulators are added through LDS in a fixed order and written to
-// the z-th partial result, P + z * nb * nm.  The consumer adds the few partial results, again in a
-// fixed order, so the outcome does not depend on timing (atomics across workgroups would make it
-// so).  Requires D % 32 == 0.
-typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
-typedef float f32x4_t __attribute__((ext_vector_type(4)));
+// P (nb, nm) float32 = u (nb, D) @ W (nm, D)^T, both operands with the contraction index contiguous, which is
+// exactly how the matrix cores want their fragments (tile_mma): one 16-byte load each, no staging, at element
+// alignment, so any D that holds a whole piece will do; the step that reaches past D cuts its pieces.  The
+// product is tiny (64 x 160 x 4096 for the headline layer) and bound by the latency of getting W and u on
+// chip, so it is spread thin: workgroup (x, y, z) owns the 16 x 16 tile (x, y) of P over the z-th part of the
+// contraction index and spreads that part over its eight waves (four steps' loads in flight per wave); the waves'
+// accumulators are added through LDS in a fixed order and written to the z-th partial result, P + z * nb * nm.
+// The consumer adds the few partial results, again in a fixed order, so the outcome does not depend on timing
+// (atomics across workgroups would make it so).  RAG: D is not a whole number of steps or W's rows are not aligned.
 constexpr int XP_WAVES = 8;
 constexpr int XP_NPARTS = ss::STEP_NPARTS;   // partial results (fixed, so that the consumer can unroll over them)
 
-__global__ void __launch_bounds__(64 * XP_WAVES) xproj_decode_kernel(const ss::bf16_t* __restrict__ u,
-                                                                     const ss::bf16_t* __restrict__ W,
+template <typename T, bool RAG>
+__global__ void __launch_bounds__(64 * XP_WAVES) xproj_decode_kernel(const T* __restrict__ u, const T* __restrict__ W,
                                                                      float* __restrict__ P, int nb, int nm, int D)
 {
+    using mma = ss::tile_mma<T>;
+    using ss::f32x4_t;
     __shared__ f32x4_t part[XP_WAVES - 1][64];
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int row0 = blockIdx.x * 16, col0 = blockIdx.y * 16;   // tile of P; its columns are rows of W
     const int urow = min(row0 + (lane & 15), nb - 1);           // rows past the end shadow the last one
     const int wrow = min(col0 + (lane & 15), nm - 1);
-    const int ksub = 8 * (lane >> 4);
-    const ss::bf16_t* up = u + (size_t)urow * D + ksub;
-    const ss::bf16_t* wp = W + (size_t)wrow * D + ksub;
+    const int ksub = mma::E * (lane >> 4);
+    const T* up = u + (size_t)urow * D;
+    const T* wp = W + (size_t)wrow * D;
     f32x4_t acc = {0.f, 0.f, 0.f, 0.f};
-    constexpr int STRIDE = 32 * XP_WAVES;
-    const int kpart = ((D + XP_NPARTS - 1) / XP_NPARTS + 31) / 32 * 32;   // contraction elements per part
+    constexpr int STRIDE = mma::K * XP_WAVES;
+    const int kpart = ((D + XP_NPARTS - 1) / XP_NPARTS + mma::K - 1) / mma::K * mma::K;   // contraction elements per part
     const int kend = min(D, (int)(blockIdx.z + 1) * kpart);
-    int k = blockIdx.z * kpart + 32 * wave;
-    for (; k + 3 * STRIDE < kend; k += 4 * STRIDE) {   // four k-steps' loads in flight together
-        bf16x8_t a[4], b[4];
+    auto load = [&](const T* row, int k) {
+        if constexpr (RAG) return mma::load(row, k + ksub, D);
+        else return *reinterpret_cast<const ss::u32x4*>(row + k + ksub);
+    };
+    auto step = [&](ss::u32x4 a, ss::u32x4 b, int k) {
+        if (RAG && k + mma::K > D) {   // uniform
+            a = mma::cut(a, k + ksub, D);
+            b = mma::cut(b, k + ksub, D);
+        }
+        acc = mma::step(a, b, acc);
+    };
+    int k = blockIdx.z * kpart + mma::K * wave;
+    for (; k + 3 * STRIDE < kend; k += 4 * STRIDE) {   // four steps' loads in flight together
+        ss::u32x4 a[4], b[4];
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-            a[i] = *reinterpret_cast<const bf16x8_t*>(up + k + i * STRIDE);
-            b[i] = *reinterpret_cast<const bf16x8_t*>(wp + k + i * STRIDE);
+            a[i] = load(up, k + i * STRIDE);
+            b[i] = load(wp, k + i * STRIDE);
         }
 #pragma unroll
-        for (int i = 0; i < 4; ++i) acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[i], b[i], acc, 0, 0, 0);
+        for (int i = 0; i < 4; ++i) step(a[i], b[i], k + i * STRIDE);
     }
-    for (; k < kend; k += STRIDE)
-        acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(*reinterpret_cast<const bf16x8_t*>(up + k),
-                                                     *reinterpret_cast<const bf16x8_t*>(wp + k), acc, 0, 0, 0);
+    for (; k < kend; k += STRIDE) step(load(up, k), load(wp, k), k);
     if (wave > 0) part[wave - 1][lane] = acc;
     __syncthreads();
     if (wave == 0) {
@@ -127,6 +135,15 @@ __global__ void __launch_bounds__(64 * XP_WAVES) xproj_decode_kernel(const ss::b
             if (row < nb && col < nm) P[((size_t)blockIdx.z * nb + row) * nm + col] = acc[r];
         }
     }
+}
+template <typename T>
+int launch_xproj_decode(const void* u, const void* W, float* P, int nb, int nm, int D, hipStream_t st)
+{
+    const dim3 grid((unsigned)((nb + 15) / 16), (unsigned)((nm + 15) / 16), (unsigned)XP_NPARTS), block(64 * XP_WAVES);
+    const T *up = static_cast<const T*>(u), *wp = static_cast<const T*>(W);
+    if (D % ss::tile_mma<T>::K == 0) hipLaunchKernelGGL((xproj_decode_kernel<T, false>), grid, block, 0, st, up, wp, P, nb, nm, D);
+    else hipLaunchKernelGGL((xproj_decode_kernel<T, true>), grid, block, 0, st, up, wp, P, nb, nm, D);
+    return hipGetLastError() == hipSuccess ? SS_OK : SS_ERR_LAUNCH;
 }
 
 // r (the first R rows of each batch entry of P, (B, Mx, L)) transposed and zero-padded to
@@ -509,17 +526,13 @@ int ss_layer_step(const ss_layer_step_params* p, void* stream)
     s.A = p->A; s.Dskip = p->Dskip; s.delta_bias = p->dt_bias;
     s.out_t = p->out_t;
 
-    // bf16 with friendly sizes: both projections on the matrix cores, delta_t = W_dt r_t inside the
-    // state-update kernel -- three launches, no library call, no atomics
-    auto aligned16 = [](const void* q) { return reinterpret_cast<uintptr_t>(q) % 16 == 0; };
-    if (bf16 && D % 32 == 0 && R % 8 == 0 && R <= 256 && N <= 16 && Mx % 4 == 0 && aligned16(p->W_x) && aligned16(p->W_dt) &&
-        aligned16(p->h)) {
+    // both projections on the matrix cores, delta_t = W_dt r_t inside the state-update kernel: three launches, no atomics
+    if (D >= 8 && R >= 8 && R <= 256 && N <= 16 && aligned_to(p->h, 16)) {
         int rc = ss_conv_step(&c, stream);
         if (rc != SS_OK) return rc;
-        const dim3 grid((unsigned)((B + 15) / 16), (unsigned)((Mx + 15) / 16), (unsigned)XP_NPARTS);
-        hipLaunchKernelGGL(xproj_decode_kernel, grid, dim3(64 * XP_WAVES), 0, st, reinterpret_cast<const ss::bf16_t*>(u_t),
-                           static_cast<const ss::bf16_t*>(p->W_x), P_acc, B, Mx, D);
-        if (hipGetLastError() != hipSuccess) return SS_ERR_LAUNCH;
+        rc = bf16 ? launch_xproj_decode<ss::bf16_t>(u_t, p->W_x, P_acc, B, Mx, D, st)
+                  : launch_xproj_decode<float>(u_t, p->W_x, P_acc, B, Mx, D, st);
+        if (rc != SS_OK) return rc;
         return ss::step_projected(&s, P_acc, p->W_dt, R, Mx, stream);
     }
 
