@@ -13,8 +13,8 @@
 // accumulator element i is row 4 * (l / 16) + i, column l % 16):
 //   gemm_nt_kernel    C = A B^T with both operands contiguous along the contraction index (the
 //                     weight gradients: contraction over L).  A workgroup takes 64 rows of the big
-//                     operand (a 16-row fragment per wave straight from global memory) against up to
-//                     192 rows of the small one, staged in 64-wide slabs through LDS.
+//                     operand, staged in 64-wide slabs through LDS, against up to 192 rows of the
+//                     small one, whose fragments each wave takes straight from the L2.
 //   gemm_rows_kernel  few output rows, long contraction over the ROWS of the (K, N) operand
 //                     ([r;B;C] = W_x u, dr = W_dt^T ddelta): that operand is contiguous along N, not
 //                     along the contraction index, so two rows at a time are interleaved into 32-bit
@@ -118,19 +118,15 @@ int launch_generic(const GemmArgs& g, hipStream_t stream)
 // place with zeros behind it; rows past the end re-read the last one and what comes of them is not stored.
 // Such sizes (sequences that are not a multiple of 64, widths that are not a multiple of 512 and so ranks that
 // are not a multiple of 16) used to take the general kernel: [r;B;C] and delta of 4 x 4096 x 1531 338 us each.
-typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
-union Frag8 { uint4 u; bf16x8_t v; };
-constexpr int MAXST = 12;          // 16-row tiles of the small operand in one launch (192 rows); kernels are built for 6, 10 or 12
+constexpr int SMAX = 192;          // rows of the small operand in one launch; kernels are built for 64, 128 and 192 of them
+using mma = tile_mma<bf16_t>;
 constexpr int KSLAB = 64;          // contraction indices per step
 constexpr int KP = KSLAB + 8;      // LDS pitch of a slab row (bf16): 144 bytes, 16-byte aligned, off the banks
 constexpr int XPITCH = 64 + 4;     // LDS pitch of a row of pairs (32-bit)
 
 __device__ __forceinline__ f32x4_t mfma_bf16(uint4 a, uint4 b, f32x4_t c)
 {
-    Frag8 fa, fb;
-    fa.u = a;
-    fb.u = b;
-    return __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa.v, fb.v, c, 0, 0, 0);
+    return mma::step(u32x4{a.x, a.y, a.z, a.w}, u32x4{b.x, b.y, b.z, b.w}, c);
 }
 
 // Eight consecutive elements from index k of a row of n; native vectors, not the uint4 struct: a copy of that
@@ -161,24 +157,19 @@ __device__ __forceinline__ uint4 cut(uint4 v, int k, int n)
 
 // 16-byte pieces of an (S rows) x (64 columns) slab of a row-major bf16 matrix: piece p -> row p / 8,
 // columns 8 * (p % 8) ..+7; thread t takes pieces t, t + 256, ... (NST / 2 of them cover 16 NST rows).  Pieces
-// past row S - 1 re-read the last row and land in LDS rows whose products are not stored: a load under a
-// per-lane condition would have to be waited for on the spot, to be merged with the register's old value.
-template <bool RAG, int NST>
-__device__ __forceinline__ void slab_load(u32x4 (&x)[NST / 2], const bf16_t* __restrict__ src, long ld, int S, int k0, int K, int tid)
+// past row S - 1 re-read the last row and land in LDS rows whose products are not stored.
+template <int NST>
+__device__ __forceinline__ void slab_load(u32x4 (&x)[NST / 2], const bf16_t* __restrict__ src, long ld, int S, int k0, int tid)
 {
 #pragma unroll
     for (int e = 0; e < NST / 2; ++e) {
         const int p = tid + 256 * e, row = min(p >> 3, S - 1);
-        x[e] = piece<RAG>(src + (long)row * ld, k0 + (p & 7) * 8, K);
+        x[e] = *reinterpret_cast<const u32x4*>(src + (long)row * ld + k0 + (p & 7) * 8);
     }
 }
-template <bool RAG, int NST>
-__device__ __forceinline__ void slab_store(u32x4 (&x)[NST / 2], bf16_t (*dst)[KP], int k0, int K, int tid)
+template <int NST>
+__device__ __forceinline__ void slab_store(const u32x4 (&x)[NST / 2], bf16_t (*dst)[KP], int tid)
 {
-    if (RAG && k0 + KSLAB > K) {   // uniform: the last slab
-#pragma unroll
-        for (int e = 0; e < NST / 2; ++e) x[e] = cut(x[e], k0 + ((tid + 256 * e) & 7) * 8, K);
-    }
 #pragma unroll
     for (int e = 0; e < NST / 2; ++e) {
         const int p = tid + 256 * e;
@@ -201,7 +192,7 @@ __device__ __forceinline__ void pair_rows(uint4 lo, uint4 hi, uint4& out0, uint4
     out1 = make_uint4(o[4], o[5], o[6], o[7]);
 }
 
-// Both kernels below walk the contraction index in 64-wide slabs and keep PD slabs in flight: the
+// The kernels below walk the contraction index in 64-wide slabs and keep PD slabs in flight: the
 // requests for slab s + PD go out at the start of step s into registers (slot s % PD, named at compile
 // time: the loop is unrolled PD times), step s multiplies out of LDS buffer s % 2, and slab s + 1
 // moves from its registers into the other LDS buffer before the step's one barrier.  The operand that
@@ -209,102 +200,249 @@ __device__ __forceinline__ void pair_rows(uint4 lo, uint4 hi, uint4& out0, uint4
 // of the L2.  Requests past the last slab re-read the last slab (never used) instead of branching, so
 // that the compiler's wait counts stay those of the steady state; the up to PD - 1 slabs left over are written
 // out behind the loop.
+// In gemm_nt_kernel and gemm_rows_kernel only the streamed operand goes through LDS, where all four waves read it.
+// The small operand's 16-row tiles are dealt out to the waves (tile w + 4 i), and a wave takes its fragments straight
+// from the L2: no two waves want the same ones.  Rows past S re-read the last one, and what comes of them is not
+// stored.  (With the small operand in LDS and a 16-row fragment of the big one per wave, every wave read the whole
+// slab, 100 KB of LDS traffic per step and workgroup against 40: dW_dt and dW_x of 8 x 4096 x 2048 55 and 58 us,
+// now 48 and 58; of 8 x 1536 x 2047 44 and 45, now 30 and 44; of 2 x 5120 x 4096 74 and 89, now 52 and 63.)
 constexpr int PD = 4;
 constexpr long ROWS_MIN_WGS = 512;   // two workgroups of gemm_rows_kernel fit on each of the 256 CUs
 constexpr int ROWS_MIN_SPLIT_K = 4096;   // shorter contractions lose more to the second launch than they gain (K = 1536: 21 -> 25 us)
 
+// A wave's fragments of the small operand for one slab: tiles w + 4 i, contraction halves ks.
+template <int NTW> struct small_frags { u32x4 f[NTW][2]; };
+template <bool RAG, int NTW, bool SKIP>
+__device__ __forceinline__ void load_frags(small_frags<NTW>& x, const bf16_t* __restrict__ src, long ld, int S, int w, int lane, int k0, int K)
+{
+#pragma unroll
+    for (int i = 0; i < NTW; ++i) {
+        if (SKIP && i == NTW - 1 && 16 * (w + 4 * i) >= S) continue;   // uniform: this wave has no such tile (gemm_rows_kernel: slower, 73 -> 97 us)
+        const bf16_t* row = src + (long)min(16 * (w + 4 * i) + (lane & 15), S - 1) * ld;
+#pragma unroll
+        for (int ks = 0; ks < 2; ++ks) x.f[i][ks] = piece<RAG>(row, k0 + 32 * ks + 8 * (lane >> 4), K);
+    }
+}
+template <int NTW>
+__device__ __forceinline__ void cut_frags(small_frags<NTW>& x, int lane, int k0, int K)
+{
+#pragma unroll
+    for (int i = 0; i < NTW; ++i)
+#pragma unroll
+        for (int ks = 0; ks < 2; ++ks) x.f[i][ks] = cut(x.f[i][ks], k0 + 32 * ks + 8 * (lane >> 4), K);
+}
+
 // C[big][small] (or, OUT_T, C[small][big]), float32, = sum_k Big[big][k] Small[small][k] per batch entry.
-// grid (M big rows / 64 rounded up, batch).  S <= 16 NST.  Plain: K % 64 == 0, M % 64 == 0, ldc and c_batch % 4 == 0.
-template <bool OUT_T, bool RAG, int NST>
+// grid (M big rows / 64 rounded up, batch).  S <= 64 NTW.  Plain: K % 64 == 0, M % 64 == 0, ldc and c_batch % 4 == 0.
+template <bool OUT_T, bool RAG, int NTW>
 __global__ void __launch_bounds__(256, 2) gemm_nt_kernel(const bf16_t* __restrict__ Big, long big_ld, long big_batch,
                                                        const bf16_t* __restrict__ Small, long small_ld, long small_batch,
-                                                       float* __restrict__ C, long ldc, long c_batch, int M, int S, int K)
+                                                       float* __restrict__ C, long ldc, long c_batch, int M, int S, int K, int vec_c)
 {
-    __shared__ __attribute__((aligned(16))) bf16_t Ss[2][NST * 16][KP];
-    const int tid = threadIdx.x, w = tid >> 6, lane = tid & 63, g = lane >> 4, j = lane & 15;
+    __shared__ __attribute__((aligned(16))) bf16_t Bs[2][64][KP];
+    const int tid = threadIdx.x, lane = tid & 63, g = lane >> 4, j = lane & 15;
+    const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int d0 = blockIdx.x * 64;
     const long b = blockIdx.y;
-    const bf16_t* __restrict__ arow = Big + b * big_batch + (long)(RAG ? min(d0 + 16 * w + j, M - 1) : d0 + 16 * w + j) * big_ld;
+    const int br = tid >> 3, bk = (tid & 7) * 8;   // this thread's pieces of the big operand's slab: rows br and br + 32
+    const bf16_t* __restrict__ brow0 = Big + b * big_batch + (long)(RAG ? min(d0 + br, M - 1) : d0 + br) * big_ld;
+    const bf16_t* __restrict__ brow1 = Big + b * big_batch + (long)(RAG ? min(d0 + br + 32, M - 1) : d0 + br + 32) * big_ld;
     const bf16_t* __restrict__ sm = Small + b * small_batch;
-    const int ST = (S + 15) >> 4;
     const int nsteps = (K + KSLAB - 1) / KSLAB;
-    f32x4_t acc[NST];
+    f32x4_t acc[4][NTW];
 #pragma unroll
-    for (int ct = 0; ct < NST; ++ct) acc[ct] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+    for (int rt = 0; rt < 4; ++rt)
+#pragma unroll
+        for (int i = 0; i < NTW; ++i) acc[rt][i] = f32x4_t{0.f, 0.f, 0.f, 0.f};
     // one named set of registers per slot, and the step written out per slot (a macro), so that every
     // register set is addressed statically
-    u32x4 sr0[NST / 2], sr1[NST / 2], sr2[NST / 2], sr3[NST / 2];
-    uint4 ar0[2], ar1[2], ar2[2], ar3[2];
-#define SS_NT_ISSUE(s_, SR, AR)                                          \
+    small_frags<NTW> sf0, sf1, sf2, sf3;
+    uint4 br0[2], br1[2], br2[2], br3[2];
+#define SS_NT_ISSUE(s_, SF, BR)                                          \
     {                                                                    \
         const int k0_ = min((s_), nsteps - 1) * KSLAB;                   \
-        AR[0] = piece_stream<RAG>(arow, k0_ + 8 * g, K);                 \
-        AR[1] = piece_stream<RAG>(arow, k0_ + 32 + 8 * g, K);            \
-        slab_load<RAG, NST>(SR, sm, small_ld, S, k0_, K, tid);           \
+        BR[0] = piece_stream<RAG>(brow0, k0_ + bk, K);                   \
+        BR[1] = piece_stream<RAG>(brow1, k0_ + bk, K);                   \
+        load_frags<RAG, NTW, true>(SF, sm, small_ld, S, w, lane, k0_, K);\
+    }
+#define SS_NT_FILL(s_, BUF, BR)                                          \
+    {                                                                    \
+        if (RAG && ((s_) + 1) * KSLAB > K) {                             \
+            BR[0] = cut(BR[0], (s_) * KSLAB + bk, K);                    \
+            BR[1] = cut(BR[1], (s_) * KSLAB + bk, K);                    \
+        }                                                                \
+        *reinterpret_cast<uint4*>(&Bs[BUF][br][bk]) = BR[0];             \
+        *reinterpret_cast<uint4*>(&Bs[BUF][br + 32][bk]) = BR[1];        \
     }
     // step s_ out of LDS buffer BUF; this slot's registers are free again (its slab went into LDS a
     // step ago, its fragments are copied out first), the next slot's slab moves into the other buffer
-#define SS_NT_STEP(s_, BUF, SR, AR, SRN)                                                                              \
+#define SS_NT_STEP(s_, BUF, SF, BR, BRN)                                                                              \
     {                                                                                                                 \
-        uint4 a_cur[2] = {AR[0], AR[1]};                                                                              \
-        if (RAG && ((s_) + 1) * KSLAB > K) {                                                                          \
-            a_cur[0] = cut(a_cur[0], (s_) * KSLAB + 8 * g, K);                                                        \
-            a_cur[1] = cut(a_cur[1], (s_) * KSLAB + 32 + 8 * g, K);                                                   \
-        }                                                                                                             \
-        SS_NT_ISSUE((s_) + PD, SR, AR)                                                                                \
+        small_frags<NTW> cur = SF;                                                                                    \
+        if (RAG && ((s_) + 1) * KSLAB > K) cut_frags<NTW>(cur, lane, (s_) * KSLAB, K);                                \
+        SS_NT_ISSUE((s_) + PD, SF, BR)                                                                                \
         _Pragma("unroll") for (int ks = 0; ks < 2; ++ks)                                                              \
-            _Pragma("unroll") for (int ct = 0; ct < NST; ++ct) if (ct < ST)                                           \
+            _Pragma("unroll") for (int rt = 0; rt < 4; ++rt)                                                          \
             {                                                                                                         \
-                const uint4 bf = *reinterpret_cast<const uint4*>(&Ss[BUF][16 * ct + j][32 * ks + 8 * g]);             \
-                acc[ct] = mfma_bf16(a_cur[ks], bf, acc[ct]);                                                          \
+                const u32x4 bf = *reinterpret_cast<const u32x4*>(&Bs[BUF][16 * rt + j][32 * ks + 8 * g]);             \
+                _Pragma("unroll") for (int i = 0; i < NTW; ++i) acc[rt][i] = mma::step(bf, cur.f[i][ks], acc[rt][i]); \
             }                                                                                                         \
-        if ((s_) + 1 < nsteps) slab_store<RAG, NST>(SRN, Ss[(BUF) ^ 1], ((s_) + 1) * KSLAB, K, tid);                  \
+        if ((s_) + 1 < nsteps) SS_NT_FILL((s_) + 1, (BUF) ^ 1, BRN)                                                   \
         __syncthreads();                                                                                              \
     }
-    SS_NT_ISSUE(0, sr0, ar0)
+    SS_NT_ISSUE(0, sf0, br0)
     __builtin_amdgcn_sched_barrier(0);
-    SS_NT_ISSUE(1, sr1, ar1)
+    SS_NT_ISSUE(1, sf1, br1)
     __builtin_amdgcn_sched_barrier(0);
-    SS_NT_ISSUE(2, sr2, ar2)
+    SS_NT_ISSUE(2, sf2, br2)
     __builtin_amdgcn_sched_barrier(0);
-    SS_NT_ISSUE(3, sr3, ar3)
+    SS_NT_ISSUE(3, sf3, br3)
     __builtin_amdgcn_sched_barrier(0);
-    slab_store<RAG, NST>(sr0, Ss[0], 0, K, tid);
+    SS_NT_FILL(0, 0, br0)
     __syncthreads();
     int s0 = 0;
     for (; s0 + PD <= nsteps; s0 += PD) {
-        SS_NT_STEP(s0, 0, sr0, ar0, sr1)
-        SS_NT_STEP(s0 + 1, 1, sr1, ar1, sr2)
-        SS_NT_STEP(s0 + 2, 0, sr2, ar2, sr3)
-        SS_NT_STEP(s0 + 3, 1, sr3, ar3, sr0)
+        SS_NT_STEP(s0, 0, sf0, br0, br1)
+        SS_NT_STEP(s0 + 1, 1, sf1, br1, br2)
+        SS_NT_STEP(s0 + 2, 0, sf2, br2, br3)
+        SS_NT_STEP(s0 + 3, 1, sf3, br3, br0)
     }
-    if (s0 < nsteps) SS_NT_STEP(s0, 0, sr0, ar0, sr1)
-    if (s0 + 1 < nsteps) SS_NT_STEP(s0 + 1, 1, sr1, ar1, sr2)
-    if (s0 + 2 < nsteps) SS_NT_STEP(s0 + 2, 0, sr2, ar2, sr3)
+    if (s0 < nsteps) SS_NT_STEP(s0, 0, sf0, br0, br1)
+    if (s0 + 1 < nsteps) SS_NT_STEP(s0 + 1, 1, sf1, br1, br2)
+    if (s0 + 2 < nsteps) SS_NT_STEP(s0 + 2, 0, sf2, br2, br3)
 #undef SS_NT_STEP
+#undef SS_NT_FILL
 #undef SS_NT_ISSUE
     float* __restrict__ c = C + b * c_batch;
 #pragma unroll
-    for (int ct = 0; ct < NST; ++ct) {
-        const int row = d0 + 16 * w + 4 * g, col = 16 * ct + j;
-        if (col >= S) continue;
-        if (OUT_T && !RAG) {
-            *reinterpret_cast<float4*>(c + (long)col * ldc + row) = make_float4(acc[ct][0], acc[ct][1], acc[ct][2], acc[ct][3]);
-        } else {
+    for (int rt = 0; rt < 4; ++rt)
 #pragma unroll
-            for (int i = 0; i < 4; ++i)
-                if (!RAG || row + i < M) c[OUT_T ? (long)col * ldc + row + i : (long)(row + i) * ldc + col] = acc[ct][i];
+        for (int t = 0; t < NTW; ++t) {
+            const int row = d0 + 16 * rt + 4 * g, col = 16 * (w + 4 * t) + j;
+            if (col >= S) continue;
+            if (OUT_T && vec_c) {
+                if (row < M) *reinterpret_cast<float4*>(c + (long)col * ldc + row) = make_float4(acc[rt][t][0], acc[rt][t][1], acc[rt][t][2], acc[rt][t][3]);
+            } else {
+#pragma unroll
+                for (int i = 0; i < 4; ++i)
+                    if (!RAG || row + i < M) c[OUT_T ? (long)col * ldc + row + i : (long)(row + i) * ldc + col] = acc[rt][t][i];
+            }
         }
-    }
 }
 
 // Out (S x N per batch entry, bf16) = W (S x K, contiguous along K) X (K x N, contiguous along N).
-// grid (N / 64 rounded up, batch, parts).  S <= 16 NST.  Plain: K % 64 == 0, N % 64 == 0.
+// grid (N / 64 rounded up, batch, parts).  S <= 64 NTW; any K and N >= 8, any pitch (RAG).
 // With parts > 1 workgroup (., ., z) contracts over the z-th part of K (none of them empty) and leaves its float32
 // share in Part[z][batch entry][S][N] for rows_reduce_kernel: a product with few columns would otherwise put a single
 // workgroup on a CU, with nothing to run while that one waits at its barrier.
-template <bool RAG, int NST>
+template <int NTW>
 __global__ void __launch_bounds__(256, 2) gemm_rows_kernel(const bf16_t* __restrict__ W, long w_ld, long w_batch,
+                                                         const bf16_t* __restrict__ X, long x_ld, long x_batch,
+                                                         bf16_t* __restrict__ Out, long o_ld, long o_batch, int S, int N, int K,
+                                                         float* __restrict__ Part)
+{
+    __shared__ __attribute__((aligned(16))) uint32_t Xp[2][KSLAB / 2][XPITCH];
+    const int tid = threadIdx.x, lane = tid & 63, g = lane >> 4, j = lane & 15;
+    const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int n0 = blockIdx.x * 64;
+    const long b = blockIdx.y;
+    const int slabs = (K + KSLAB - 1) / KSLAB, per_part = (slabs + (int)gridDim.z - 1) / (int)gridDim.z;
+    const int first = blockIdx.z * per_part, nsteps = min(slabs - first, per_part);   // this part's slabs
+    const bf16_t* __restrict__ wm = W + b * w_batch;
+    const int xp = tid >> 3, xo = tid & 7;   // pair of rows, group of eight columns
+    const bf16_t* __restrict__ xcol = X + b * x_batch;
+    f32x4_t acc[NTW][4];
+#pragma unroll
+    for (int i = 0; i < NTW; ++i)
+#pragma unroll
+        for (int ct = 0; ct < 4; ++ct) acc[i][ct] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+    small_frags<NTW> wf0, wf1, wf2, wf3;   // one named set of registers per slot, steps written out (see gemm_nt_kernel)
+    uint4 xr0[2], xr1[2], xr2[2], xr3[2];
+#define SS_ROWS_ISSUE(s_, WF, XR)                                                          \
+    {                                                                                      \
+        const int k0_ = (first + min((s_), nsteps - 1)) * KSLAB, x0_ = k0_ + 2 * xp;       \
+        XR[0] = piece_stream<true>(xcol + (long)min(x0_, K - 1) * x_ld, n0 + 8 * xo, N);         \
+        XR[1] = piece_stream<true>(xcol + (long)min(x0_ + 1, K - 1) * x_ld, n0 + 8 * xo, N); \
+        load_frags<true, NTW, false>(WF, wm, w_ld, S, w, lane, k0_, K);                            \
+    }
+#define SS_ROWS_FILL(s_, BUF, XR)                                                          \
+    {                                                                                      \
+        const int k0_ = (first + (s_)) * KSLAB;                                            \
+        if (n0 + 64 > N) {                                                          \
+            XR[0] = cut(XR[0], n0 + 8 * xo, N);                                            \
+            XR[1] = cut(XR[1], n0 + 8 * xo, N);                                            \
+        }                                                                                  \
+        if (k0_ + KSLAB > K) {                                                      \
+            if (k0_ + 2 * xp >= K) XR[0] = make_uint4(0u, 0u, 0u, 0u);                     \
+            if (k0_ + 2 * xp + 1 >= K) XR[1] = make_uint4(0u, 0u, 0u, 0u);                 \
+        }                                                                                  \
+        uint4 o0_, o1_;                                                                    \
+        pair_rows(XR[0], XR[1], o0_, o1_);                                                 \
+        *reinterpret_cast<uint4*>(&Xp[BUF][xp][8 * xo]) = o0_;                             \
+        *reinterpret_cast<uint4*>(&Xp[BUF][xp][8 * xo + 4]) = o1_;                         \
+    }
+#define SS_ROWS_STEP(s_, BUF, WF, XR, XRN)                                                                            \
+    {                                                                                                                 \
+        small_frags<NTW> cur = WF;                                                                                    \
+        if ((first + (s_) + 1) * KSLAB > K) cut_frags<NTW>(cur, lane, (first + (s_)) * KSLAB, K);              \
+        SS_ROWS_ISSUE((s_) + PD, WF, XR) /* this slot's slab went into LDS a step ago */                              \
+        _Pragma("unroll") for (int ks = 0; ks < 2; ++ks)                                                              \
+            _Pragma("unroll") for (int ct = 0; ct < 4; ++ct)                                                          \
+            {                                                                                                         \
+                const uint32_t* xq = &Xp[BUF][16 * ks + 4 * g][16 * ct + j];                                          \
+                const u32x4 bf = {xq[0], xq[XPITCH], xq[2 * XPITCH], xq[3 * XPITCH]};                                 \
+                _Pragma("unroll") for (int i = 0; i < NTW; ++i) acc[i][ct] = mma::step(cur.f[i][ks], bf, acc[i][ct]); \
+            }                                                                                                         \
+        if ((s_) + 1 < nsteps) SS_ROWS_FILL((s_) + 1, (BUF) ^ 1, XRN)                                                 \
+        __syncthreads();                                                                                              \
+    }
+    SS_ROWS_ISSUE(0, wf0, xr0)
+    __builtin_amdgcn_sched_barrier(0);
+    SS_ROWS_ISSUE(1, wf1, xr1)
+    __builtin_amdgcn_sched_barrier(0);
+    SS_ROWS_ISSUE(2, wf2, xr2)
+    __builtin_amdgcn_sched_barrier(0);
+    SS_ROWS_ISSUE(3, wf3, xr3)
+    __builtin_amdgcn_sched_barrier(0);
+    SS_ROWS_FILL(0, 0, xr0)
+    __syncthreads();
+    int s0 = 0;
+    for (; s0 + PD <= nsteps; s0 += PD) {
+        SS_ROWS_STEP(s0, 0, wf0, xr0, xr1)
+        SS_ROWS_STEP(s0 + 1, 1, wf1, xr1, xr2)
+        SS_ROWS_STEP(s0 + 2, 0, wf2, xr2, xr3)
+        SS_ROWS_STEP(s0 + 3, 1, wf3, xr3, xr0)
+    }
+    if (s0 < nsteps) SS_ROWS_STEP(s0, 0, wf0, xr0, xr1)
+    if (s0 + 1 < nsteps) SS_ROWS_STEP(s0 + 1, 1, wf1, xr1, xr2)
+    if (s0 + 2 < nsteps) SS_ROWS_STEP(s0 + 2, 0, wf2, xr2, xr3)
+#undef SS_ROWS_STEP
+#undef SS_ROWS_FILL
+#undef SS_ROWS_ISSUE
+    const bool split = gridDim.z > 1;
+    float* __restrict__ pp = Part + ((long)blockIdx.z * gridDim.y + b) * S * N;
+    bf16_t* __restrict__ o = Out + b * o_batch;
+#pragma unroll
+    for (int t = 0; t < NTW; ++t)
+#pragma unroll
+        for (int ct = 0; ct < 4; ++ct) {
+            const int row = 16 * (w + 4 * t) + 4 * g, col = n0 + 16 * ct + j;
+            if (col >= N) continue;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                if (row + i >= S) continue;
+                if (split) pp[(long)(row + i) * N + col] = acc[t][ct][i];
+                else o[(long)(row + i) * o_ld + col] = bf16_t(f32_to_bf16_bits(acc[t][ct][i]));
+            }
+        }
+}
+
+// The same product for operands of whole pieces (K % 64 == 0, N % 64 == 0, S <= 16 NST), the weights through LDS too:
+// 8 x 4096 x 2048, S = 160 and 128: 59 and 54 us against 73 and 60 with fragments from the L2, which is the faster
+// form at 8 x 1536 x 2047 (23 and 19 against 25 and 23 us) and at 4 x 4096 x 1531 (43 and 35 against 50 and 47).
+// grid (N / 64, batch, parts).
+template <int NST>
+__global__ void __launch_bounds__(256, 2) gemm_rows_lds_kernel(const bf16_t* __restrict__ W, long w_ld, long w_batch,
                                                          const bf16_t* __restrict__ X, long x_ld, long x_batch,
                                                          bf16_t* __restrict__ Out, long o_ld, long o_batch, int S, int N, int K,
                                                          float* __restrict__ Part)
@@ -322,8 +460,7 @@ __global__ void __launch_bounds__(256, 2) gemm_rows_kernel(const bf16_t* __restr
     const int ST = (S + 15) >> 4;
     // The four waves split the S x 64 tile two by two: wave (wv, wc) has half of the output's row tiles and
     // column tiles 2 wc, 2 wc + 1, so that every weight fragment read from LDS feeds two MFMAs (with a wave
-    // per column tile each wave read the whole weight slab and LDS was the limit: 78 -> 68 us).  The same
-    // split of gemm_nt_kernel doubles its global fragment loads and registers and measured slower (61 -> 88 us).
+    // per column tile each wave read the whole weight slab and LDS was the limit: 78 -> 68 us).
     const int wv = w >> 1, wc = w & 1;
     const int RH = (ST + 1) >> 1;
     constexpr int MAXRH = NST / 2;
@@ -335,22 +472,13 @@ __global__ void __launch_bounds__(256, 2) gemm_rows_kernel(const bf16_t* __restr
 #define SS_ROWS_ISSUE(s_, WR, XR)                                                          \
     {                                                                                      \
         const int k0_ = (first + min((s_), nsteps - 1)) * KSLAB, x0_ = k0_ + 2 * xp;       \
-        XR[0] = piece_stream<RAG>(xcol + (long)(RAG ? min(x0_, K - 1) : x0_) * x_ld, n0 + 8 * xo, N);         \
-        XR[1] = piece_stream<RAG>(xcol + (long)(RAG ? min(x0_ + 1, K - 1) : x0_ + 1) * x_ld, n0 + 8 * xo, N); \
-        slab_load<RAG, NST>(WR, wm, w_ld, S, k0_, K, tid);                                 \
+        XR[0] = piece_stream<false>(xcol + (long)x0_ * x_ld, n0 + 8 * xo, N);         \
+        XR[1] = piece_stream<false>(xcol + (long)(x0_ + 1) * x_ld, n0 + 8 * xo, N); \
+        slab_load<NST>(WR, wm, w_ld, S, k0_, tid);                                         \
     }
-#define SS_ROWS_FILL(s_, BUF, WR, XR)                                                      \
+#define SS_ROWS_FILL(BUF, WR, XR)                                                          \
     {                                                                                      \
-        const int k0_ = (first + (s_)) * KSLAB;                                            \
-        slab_store<RAG, NST>(WR, Ws[BUF], k0_, K, tid);                                    \
-        if (RAG && n0 + 64 > N) {                                                          \
-            XR[0] = cut(XR[0], n0 + 8 * xo, N);                                            \
-            XR[1] = cut(XR[1], n0 + 8 * xo, N);                                            \
-        }                                                                                  \
-        if (RAG && k0_ + KSLAB > K) {                                                      \
-            if (k0_ + 2 * xp >= K) XR[0] = make_uint4(0u, 0u, 0u, 0u);                     \
-            if (k0_ + 2 * xp + 1 >= K) XR[1] = make_uint4(0u, 0u, 0u, 0u);                 \
-        }                                                                                  \
+        slab_store<NST>(WR, Ws[BUF], tid);                                                 \
         uint4 o0_, o1_;                                                                    \
         pair_rows(XR[0], XR[1], o0_, o1_);                                                 \
         *reinterpret_cast<uint4*>(&Xp[BUF][xp][8 * xo]) = o0_;                             \
@@ -371,7 +499,7 @@ __global__ void __launch_bounds__(256, 2) gemm_rows_kernel(const bf16_t* __restr
                 acc[ri][1] = mfma_bf16(af, bf1, acc[ri][1]);                                                          \
             }                                                                                                         \
         }                                                                                                             \
-        if ((s_) + 1 < nsteps) SS_ROWS_FILL((s_) + 1, (BUF) ^ 1, WRN, XRN)                                            \
+        if ((s_) + 1 < nsteps) SS_ROWS_FILL((BUF) ^ 1, WRN, XRN)                                                      \
         __syncthreads();                                                                                              \
     }
     SS_ROWS_ISSUE(0, wr0, xr0)
@@ -382,7 +510,7 @@ __global__ void __launch_bounds__(256, 2) gemm_rows_kernel(const bf16_t* __restr
     __builtin_amdgcn_sched_barrier(0);
     SS_ROWS_ISSUE(3, wr3, xr3)
     __builtin_amdgcn_sched_barrier(0);
-    SS_ROWS_FILL(0, 0, wr0, xr0)
+    SS_ROWS_FILL(0, wr0, xr0)
     __syncthreads();
     int s0 = 0;
     for (; s0 + PD <= nsteps; s0 += PD) {
@@ -405,7 +533,7 @@ __global__ void __launch_bounds__(256, 2) gemm_rows_kernel(const bf16_t* __restr
 #pragma unroll
         for (int c2 = 0; c2 < 2; ++c2) {
             const int row = 16 * (wv * RH + ri) + 4 * g, col = n0 + 32 * wc + j + 16 * c2;
-            if (ri >= RH || (RAG && col >= N)) continue;
+            if (ri >= RH) continue;
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
                 if (row + i >= S) continue;
@@ -566,28 +694,31 @@ inline bool al16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15) =
 inline bool mult8(long x) { return x % 8 == 0; }
 inline unsigned tiles64(int n) { return (unsigned)((n + 63) / 64); }
 
-// One launch each (the small operand has at most 16 * MAXST rows); ST = its 16-row tiles.
+// One launch each (the small operand has at most SMAX rows).
 template <bool OUT_T, bool RAG>
 void launch_nt(const bf16_t* big, long big_ld, long big_batch, const bf16_t* small, long small_ld, long small_batch, float* C,
                long ldc, long c_batch, int M, int S, int K, int batch, hipStream_t stream)
 {
     const dim3 grid(tiles64(M), (unsigned)batch);
-    const int ST = (S + 15) / 16;
-#define SS_LAUNCH_NT(NST) hipLaunchKernelGGL((gemm_nt_kernel<OUT_T, RAG, NST>), grid, dim3(256), 0, stream, big, big_ld, big_batch, \
-                                             small, small_ld, small_batch, C, ldc, c_batch, M, S, K)
-    if (ST <= 6) SS_LAUNCH_NT(6); else if (ST <= 10) SS_LAUNCH_NT(10); else SS_LAUNCH_NT(12);
+    const int vec_c = M % 4 == 0 && ldc % 4 == 0 && c_batch % 4 == 0 && al16(C);   // four rows of the big operand are one aligned store (OUT_T)
+#define SS_LAUNCH_NT(NTW) hipLaunchKernelGGL((gemm_nt_kernel<OUT_T, RAG, NTW>), grid, dim3(256), 0, stream, big, big_ld, big_batch, \
+                                             small, small_ld, small_batch, C, ldc, c_batch, M, S, K, vec_c)
+    if (S <= 64) SS_LAUNCH_NT(1); else if (S <= 128) SS_LAUNCH_NT(2); else SS_LAUNCH_NT(3);
 #undef SS_LAUNCH_NT
 }
 template <bool RAG>
 void launch_rows(const GemmArgs& g, const bf16_t* A, bf16_t* C, int S, int parts, hipStream_t stream)
 {
     const dim3 grid(tiles64(g.N), (unsigned)g.batch, (unsigned)parts);
-    const int ST = (S + 15) / 16;
     const bf16_t* B = static_cast<const bf16_t*>(g.B);
     float* ws = static_cast<float*>(g.split_ws);
-#define SS_LAUNCH_ROWS(NST) hipLaunchKernelGGL((gemm_rows_kernel<RAG, NST>), grid, dim3(256), 0, stream, A, g.a_m, g.a_batch, B, \
-                                               g.b_k, g.b_batch, C, g.ldc, g.c_batch, S, g.N, g.K, ws)
-    if (ST <= 6) SS_LAUNCH_ROWS(6); else if (ST <= 10) SS_LAUNCH_ROWS(10); else SS_LAUNCH_ROWS(12);
+#define SS_LAUNCH_ROWS(KERN) hipLaunchKernelGGL(KERN, grid, dim3(256), 0, stream, A, g.a_m, g.a_batch, B, g.b_k, g.b_batch, C, \
+                                                g.ldc, g.c_batch, S, g.N, g.K, ws)
+    if constexpr (RAG) {
+        if (S <= 64) SS_LAUNCH_ROWS(gemm_rows_kernel<1>); else if (S <= 128) SS_LAUNCH_ROWS(gemm_rows_kernel<2>); else SS_LAUNCH_ROWS(gemm_rows_kernel<3>);
+    } else {
+        if (S <= 96) SS_LAUNCH_ROWS(gemm_rows_lds_kernel<6>); else if (S <= 160) SS_LAUNCH_ROWS(gemm_rows_lds_kernel<10>); else SS_LAUNCH_ROWS(gemm_rows_lds_kernel<12>);
+    }
 #undef SS_LAUNCH_ROWS
     if (parts > 1) {
         const bool whole = !RAG;
@@ -615,7 +746,6 @@ int launch_fast(const GemmArgs& g, hipStream_t stream)
     const bf16_t* A = static_cast<const bf16_t*>(g.A);
     const bf16_t* B = static_cast<const bf16_t*>(g.B);
     const bool whole = al16(g.A) && al16(g.B) && al16(g.C) && mult8(g.a_batch) && mult8(g.b_batch);   // operands made of aligned 16-byte pieces
-    constexpr int SMAX = MAXST * 16;
     if (g.a_k == 1 && g.b_k == 1 && g.c_float && !g.accumulate) {
         // C = A B^T: the operand with more rows is split over workgroups and waves, the other one, up to SMAX rows at a time,
         // goes through LDS
@@ -637,7 +767,7 @@ int launch_fast(const GemmArgs& g, hipStream_t stream)
     }
     if (g.a_k == 1 && g.b_n == 1 && !g.c_float && g.N >= 8) {
         const bool whole_c = whole && g.N % 64 == 0 && mult8(g.a_m) && mult8(g.b_k) && mult8(g.ldc) && mult8(g.c_batch);
-        if (g.K <= MAXST * 16 && g.a_batch == 0) {
+        if (g.K <= SMAX && g.a_batch == 0) {
             // as many 64-row tiles per workgroup as fit, up to 16, while the launch keeps >= 1024 workgroups
             int mtiles = 1;
             const long cols = (long)tiles64(g.N) * g.batch, mt = tiles64(g.M);
