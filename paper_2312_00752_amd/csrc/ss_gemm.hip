@@ -24,8 +24,8 @@
 //                     in registers as fragments; the product is formed transposed so that a lane
 //                     holds four consecutive columns, and leaves through an LDS tile as whole
 //                     128-byte row pieces.
-// gemm_generic_kernel takes every other stride and dtype (64 x 64 tiles through LDS, 4 x 4 outputs per
-// thread on the vector ALU): the float32 layer, sizes below 8 and the tiny per-token products.
+// gemm_generic_kernel takes every other stride and dtype (64 x 64 tiles through LDS, float MFMAs): the float32
+// layer, sizes below 8 and the per-token products of more than 256 ranks.
 #include <hip/hip_runtime.h>
 #include <type_traits>
 
@@ -44,61 +44,133 @@ template <> __device__ __forceinline__ void st<float>(float* p, float v) { *p = 
 template <> __device__ __forceinline__ void st<bf16_t>(bf16_t* p, float v) { *p = bf16_t(f32_to_bf16_bits(v)); }
 
 constexpr int GT = 64;   // tile edge
-constexpr int GK = 16;   // contraction indices per step
+constexpr int GK = 32;   // contraction indices per step
+constexpr int GP = GT + 4;   // LDS pitch (floats) of a contraction index's 64 rows or columns
 
+// One operand of the general kernel: element (r, k) at p + r * s_r + k * s_k, R rows (or columns), K contraction indices.
+// A thread moves two pieces of four consecutive elements per step, along whichever index is contiguous; a piece is
+// read whole from inside the matrix (clamped) and only the last tile or step, a uniform case, takes its elements
+// one by one.  Neither index contiguous, or fewer than four of it: always one by one.
+template <typename T>
+struct gemm_operand {
+    const T* p;
+    long s_r, s_k;
+    int R, K, r0, mode;   // mode 0: k contiguous, 1: r contiguous, 2: elements one by one
+    typedef uint32_t raw_t __attribute__((ext_vector_type(sizeof(T))));   // four elements
+    raw_t x[2];
+    __device__ __forceinline__ gemm_operand(const T* p_, long s_r_, long s_k_, int R_, int K_, int r0_)
+        : p(p_), s_r(s_r_), s_k(s_k_), R(R_), K(K_), r0(r0_),
+          mode(s_k_ == 1 && K_ >= 4 ? 0 : (s_r_ == 1 && R_ >= 4 ? 1 : 2)) {}
+    // piece e of this thread: first row and index within the tile
+    __device__ __forceinline__ void place(int e, int& r, int& k) const
+    {
+        const int i = (int)threadIdx.x + 256 * e;
+        if (mode == 1) { k = i >> 4; r = (i & 15) * 4; } else { r = i >> 3; k = (i & 7) * 4; }
+    }
+    __device__ __forceinline__ void load(int k0)
+    {
+#pragma unroll
+        for (int e = 0; e < 2; ++e) {
+            int r, k;
+            place(e, r, k);
+            const long rr = mode == 1 ? min(r0 + r, R - 4) : min(r0 + r, R - 1), kk = mode == 0 ? min(k0 + k, K - 4) : min(k0 + k, K - 1);
+            if (mode != 2) x[e] = load_any<raw_t>(p + rr * s_r + kk * s_k, 0u);
+        }
+    }
+    __device__ __forceinline__ void store(int k0, float (*dst)[GP])
+    {
+        const bool single = mode == 2 || k0 + GK > K || (mode == 1 && r0 + GT > R);   // uniform
+#pragma unroll
+        for (int e = 0; e < 2; ++e) {
+            int r, k;
+            place(e, r, k);
+            float v[4];
+            if (single) {
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const int ri = r0 + r + (mode == 1 ? i : 0), ki = k0 + k + (mode == 1 ? 0 : i);
+                    v[i] = ri < R && ki < K ? ld(p + ri * s_r + ki * s_k) : 0.0f;
+                }
+            } else if constexpr (sizeof(T) == 2) {
+                v[0] = bf16_lo(x[e][0]); v[1] = bf16_hi(x[e][0]); v[2] = bf16_lo(x[e][1]); v[3] = bf16_hi(x[e][1]);
+            } else {
+#pragma unroll
+                for (int i = 0; i < 4; ++i) v[i] = __uint_as_float(x[e][i]);
+            }
+            if (mode == 1) {
+                *reinterpret_cast<float4*>(&dst[k][r]) = make_float4(v[0], v[1], v[2], v[3]);
+            } else {
+#pragma unroll
+                for (int i = 0; i < 4; ++i) dst[k + i][r] = v[i];
+            }
+        }
+    }
+};
+
+// Any strides, either type: 64 x 64 tiles through LDS as floats, a step ahead in registers, 32 x 32 outputs per wave
+// on v_mfma_f32_16x16x4_f32 (lane l supplies row, resp. column, l % 16 at contraction index l / 16; float products
+// and sums, as on the vector ALU).
 template <typename T, typename TC>
 __global__ void __launch_bounds__(256) gemm_generic_kernel(const GemmArgs g)
 {
-    __shared__ float As[GK][GT + 4];
-    __shared__ float Bs[GK][GT + 4];
-    const int tid = threadIdx.x;
-    const int tx = tid & 15, ty = tid >> 4;
+    __shared__ __attribute__((aligned(16))) float As[2][GK][GP];
+    __shared__ __attribute__((aligned(16))) float Bs[2][GK][GP];
+    const int tid = threadIdx.x, lane = tid & 63, kg = lane >> 4, j = lane & 15;
+    const int wm = (tid >> 7) * 32, wn = ((tid >> 6) & 1) * 32;
     const int m0 = blockIdx.y * GT, n0 = blockIdx.x * GT;
     const long bi = blockIdx.z;
-    const T* __restrict__ A = static_cast<const T*>(g.A) + bi * g.a_batch;
-    const T* __restrict__ B = static_cast<const T*>(g.B) + bi * g.b_batch;
+    gemm_operand<T> A(static_cast<const T*>(g.A) + bi * g.a_batch, g.a_m, g.a_k, g.M, g.K, m0);
+    gemm_operand<T> B(static_cast<const T*>(g.B) + bi * g.b_batch, g.b_n, g.b_k, g.N, g.K, n0);
     TC* __restrict__ C = static_cast<TC*>(g.C) + bi * g.c_batch;
-    float acc[4][4] = {};
-    for (int k0 = 0; k0 < g.K; k0 += GK) {
-        // A tile (64 m x 16 k), B tile (16 k x 64 n): four elements each per thread, along whichever
-        // index is contiguous in memory
+    f32x4_t acc[2][2];
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            const int idx = tid + e * 256;
-            int am, ak;
-            if (g.a_k == 1) { ak = idx & (GK - 1); am = idx >> 4; } else { am = idx & (GT - 1); ak = idx >> 6; }
-            As[ak][am] = (m0 + am < g.M && k0 + ak < g.K) ? ld(A + (long)(m0 + am) * g.a_m + (long)(k0 + ak) * g.a_k) : 0.0f;
-            int bn, bk;
-            if (g.b_k == 1) { bk = idx & (GK - 1); bn = idx >> 4; } else { bn = idx & (GT - 1); bk = idx >> 6; }
-            Bs[bk][bn] = (n0 + bn < g.N && k0 + bk < g.K) ? ld(B + (long)(k0 + bk) * g.b_k + (long)(n0 + bn) * g.b_n) : 0.0f;
+    for (int i = 0; i < 2; ++i) acc[i][0] = acc[i][1] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+    if (g.K > 0) {
+        A.load(0);
+        B.load(0);
+        A.store(0, As[0]);
+        B.store(0, Bs[0]);
+    }
+    __syncthreads();
+    int buf = 0;
+    for (int k0 = 0; k0 < g.K; k0 += GK, buf ^= 1) {
+        const bool more = k0 + GK < g.K;   // uniform
+        if (more) {
+            A.load(k0 + GK);
+            B.load(k0 + GK);
         }
-        __syncthreads();
 #pragma unroll
-        for (int k = 0; k < GK; ++k) {
-            const float4 a4 = *reinterpret_cast<const float4*>(&As[k][ty * 4]);
-            const float4 b4 = *reinterpret_cast<const float4*>(&Bs[k][tx * 4]);
-            const float a[4] = {a4.x, a4.y, a4.z, a4.w}, b[4] = {b4.x, b4.y, b4.z, b4.w};
-#pragma unroll
-            for (int i = 0; i < 4; ++i)
-#pragma unroll
-                for (int j = 0; j < 4; ++j) acc[i][j] = fmaf(a[i], b[j], acc[i][j]);
+        for (int k = 0; k < GK; k += 4) {
+            const float* a = &As[buf][k + kg][wm + j];
+            const float* b = &Bs[buf][k + kg][wn + j];
+            const float a0 = a[0], a1 = a[16], b0 = b[0], b1 = b[16];
+            acc[0][0] = __builtin_amdgcn_mfma_f32_16x16x4f32(a0, b0, acc[0][0], 0, 0, 0);
+            acc[0][1] = __builtin_amdgcn_mfma_f32_16x16x4f32(a0, b1, acc[0][1], 0, 0, 0);
+            acc[1][0] = __builtin_amdgcn_mfma_f32_16x16x4f32(a1, b0, acc[1][0], 0, 0, 0);
+            acc[1][1] = __builtin_amdgcn_mfma_f32_16x16x4f32(a1, b1, acc[1][1], 0, 0, 0);
+        }
+        if (more) {
+            A.store(k0 + GK, As[buf ^ 1]);
+            B.store(k0 + GK, Bs[buf ^ 1]);
         }
         __syncthreads();
     }
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const int m = m0 + ty * 4 + i;
-        if (m >= g.M) continue;
+    for (int i = 0; i < 2; ++i)
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const int n = n0 + tx * 4 + j;
+        for (int c = 0; c < 2; ++c) {
+            const int n = n0 + wn + 16 * c + j;
             if (n >= g.N) continue;
-            TC* dst = C + (long)m * g.ldc + n;
-            float v = acc[i][j];
-            if (g.accumulate) v += ld(dst);
-            st(dst, v);
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const int m = m0 + wm + 16 * i + 4 * kg + r;
+                if (m >= g.M) continue;
+                TC* dst = C + (long)m * g.ldc + n;
+                float v = acc[i][c][r];
+                if (g.accumulate) v += ld(dst);
+                st(dst, v);
+            }
         }
-    }
 }
 
 template <typename T, typename TC>
