@@ -43,6 +43,26 @@ template <typename T> __device__ __forceinline__ void st(T* p, float v);
 template <> __device__ __forceinline__ void st<float>(float* p, float v) { *p = v; }
 template <> __device__ __forceinline__ void st<bf16_t>(bf16_t* p, float v) { *p = bf16_t(f32_to_bf16_bits(v)); }
 
+// Out[b][m][n] = sum over the parts of Part[part][b][m][n], in their order; one thread per element.
+template <typename TC>
+__global__ void __launch_bounds__(256) parts_reduce_kernel(const float* __restrict__ Part, int parts, TC* __restrict__ Out, long ldc,
+                                                           long c_batch, int M, int N, long items)
+{
+    const long idx = (long)blockIdx.x * 256 + threadIdx.x;   // over batch * M * N = the elements of a part
+    if (idx >= items) return;
+    float v = Part[idx];
+    for (int z = 1; z < parts; ++z) v += Part[z * items + idx];
+    const long bm = idx / N;
+    st(Out + bm / M * c_batch + bm % M * ldc + idx % N, v);
+}
+template <typename TC>
+void reduce_parts(const GemmArgs& g, int parts, TC* C, int M, int N, hipStream_t stream)
+{
+    const long items = (long)g.batch * M * N;
+    hipLaunchKernelGGL((parts_reduce_kernel<TC>), dim3((unsigned)((items + 255) / 256)), dim3(256), 0, stream,
+                       static_cast<const float*>(g.split_ws), parts, C, g.ldc, g.c_batch, M, N, items);
+}
+
 constexpr int GT = 64;   // tile edge
 constexpr int GK = 32;   // contraction indices per step
 constexpr int GP = GT + 4;   // LDS pitch (floats) of a contraction index's 64 rows or columns
@@ -118,23 +138,27 @@ __global__ void __launch_bounds__(256) gemm_generic_kernel(const GemmArgs g)
     const int tid = threadIdx.x, lane = tid & 63, kg = lane >> 4, j = lane & 15;
     const int wm = (tid >> 7) * 32, wn = ((tid >> 6) & 1) * 32;
     const int m0 = blockIdx.y * GT, n0 = blockIdx.x * GT;
-    const long bi = blockIdx.z;
+    const long bi = blockIdx.z % g.batch;
+    // parts > 1: this workgroup's part of the contraction, its float32 share left for parts_reduce_kernel
+    const int part = blockIdx.z / g.batch, parts = gridDim.z / g.batch;
+    const int per_part = ((g.K + GK - 1) / GK + parts - 1) / parts * GK;
+    const int k_begin = part * per_part, k_end = min(g.K, k_begin + per_part);
     gemm_operand<T> A(static_cast<const T*>(g.A) + bi * g.a_batch, g.a_m, g.a_k, g.M, g.K, m0);
     gemm_operand<T> B(static_cast<const T*>(g.B) + bi * g.b_batch, g.b_n, g.b_k, g.N, g.K, n0);
     TC* __restrict__ C = static_cast<TC*>(g.C) + bi * g.c_batch;
     f32x4_t acc[2][2];
 #pragma unroll
     for (int i = 0; i < 2; ++i) acc[i][0] = acc[i][1] = f32x4_t{0.f, 0.f, 0.f, 0.f};
-    if (g.K > 0) {
-        A.load(0);
-        B.load(0);
-        A.store(0, As[0]);
-        B.store(0, Bs[0]);
+    if (k_begin < k_end) {
+        A.load(k_begin);
+        B.load(k_begin);
+        A.store(k_begin, As[0]);
+        B.store(k_begin, Bs[0]);
     }
     __syncthreads();
     int buf = 0;
-    for (int k0 = 0; k0 < g.K; k0 += GK, buf ^= 1) {
-        const bool more = k0 + GK < g.K;   // uniform
+    for (int k0 = k_begin; k0 < k_end; k0 += GK, buf ^= 1) {
+        const bool more = k0 + GK < k_end;   // uniform
         if (more) {
             A.load(k0 + GK);
             B.load(k0 + GK);
@@ -165,22 +189,41 @@ __global__ void __launch_bounds__(256) gemm_generic_kernel(const GemmArgs g)
             for (int r = 0; r < 4; ++r) {
                 const int m = m0 + wm + 16 * i + 4 * kg + r;
                 if (m >= g.M) continue;
-                TC* dst = C + (long)m * g.ldc + n;
                 float v = acc[i][c][r];
+                if (parts > 1) {
+                    static_cast<float*>(g.split_ws)[(((long)part * g.batch + bi) * g.M + m) * g.N + n] = v;
+                    continue;
+                }
+                TC* dst = C + (long)m * g.ldc + n;
                 if (g.accumulate) v += ld(dst);
                 st(dst, v);
             }
         }
 }
 
+// Parts of a contraction of K that goes over `tiles` workgroups: one, unless that leaves half of the 256 compute units
+// or more idle; then as many, up to eight, as give each unit a workgroup and each workgroup 256 contraction
+// indices, if the workspace holds the shares.  Rounded so that none is empty when dealt out in steps of `step`.
+int parts_for(const GemmArgs& g, long tiles, int K, int step, size_t share)
+{
+    if (!g.split_ws || g.accumulate || tiles > 128) return 1;
+    int parts = 1;
+    while (parts < 8 && tiles * parts * 2 <= 256 && K / (parts * 2) >= 256 && (size_t)(parts * 2) * share <= g.split_ws_bytes) parts *= 2;
+    const int steps = (K + step - 1) / step, per = (steps + parts - 1) / parts;
+    return (steps + per - 1) / per;
+}
+
 template <typename T, typename TC>
 int launch_generic(const GemmArgs& g, hipStream_t stream)
 {
-    const dim3 grid((unsigned)((g.N + GT - 1) / GT), (unsigned)((g.M + GT - 1) / GT), (unsigned)g.batch);
+    const long tm = (g.M + GT - 1) / GT, tn = (g.N + GT - 1) / GT;
+    int parts = g.K > 0 ? parts_for(g, tm * tn * g.batch, g.K, GK, (size_t)g.batch * g.M * g.N * sizeof(float)) : 1;
+    if ((long)parts * g.batch > 65535) parts = 1;
+    const dim3 grid((unsigned)tn, (unsigned)tm, (unsigned)(g.batch * parts));
     hipLaunchKernelGGL((gemm_generic_kernel<T, TC>), grid, dim3(256), 0, stream, g);
+    if (parts > 1) reduce_parts<TC>(g, parts, static_cast<TC*>(g.C), g.M, g.N, stream);
     return hipGetLastError() == hipSuccess ? SS_OK : SS_ERR_LAUNCH;
 }
-
 
 // ---- matrix-core kernels (bf16) -------------------------------------------------------------------
 // Each exists twice.  The plain form takes operands made of whole 16-byte pieces (pitches and batch strides
@@ -305,11 +348,13 @@ __device__ __forceinline__ void cut_frags(small_frags<NTW>& x, int lane, int k0,
 }
 
 // C[big][small] (or, OUT_T, C[small][big]), float32, = sum_k Big[big][k] Small[small][k] per batch entry.
-// grid (M big rows / 64 rounded up, batch).  S <= 64 NTW.  Plain: K % 64 == 0, M % 64 == 0, ldc and c_batch % 4 == 0.
+// grid (M big rows / 64 rounded up, batch, parts).  S <= 64 NTW.  Plain: K % 64 == 0, M % 64 == 0, ldc and c_batch % 4 == 0.
+// With parts > 1 workgroup (., ., z) contracts over the z-th part of K and C is one share after another, part_stride apart.
 template <bool OUT_T, bool RAG, int NTW>
 __global__ void __launch_bounds__(256, 2) gemm_nt_kernel(const bf16_t* __restrict__ Big, long big_ld, long big_batch,
                                                        const bf16_t* __restrict__ Small, long small_ld, long small_batch,
-                                                       float* __restrict__ C, long ldc, long c_batch, int M, int S, int K, int vec_c)
+                                                       float* __restrict__ C, long ldc, long c_batch, long part_stride, int M, int S,
+                                                       int K, int vec_c)
 {
     __shared__ __attribute__((aligned(16))) bf16_t Bs[2][64][KP];
     const int tid = threadIdx.x, lane = tid & 63, g = lane >> 4, j = lane & 15;
@@ -317,10 +362,13 @@ __global__ void __launch_bounds__(256, 2) gemm_nt_kernel(const bf16_t* __restric
     const int d0 = blockIdx.x * 64;
     const long b = blockIdx.y;
     const int br = tid >> 3, bk = (tid & 7) * 8;   // this thread's pieces of the big operand's slab: rows br and br + 32
-    const bf16_t* __restrict__ brow0 = Big + b * big_batch + (long)(RAG ? min(d0 + br, M - 1) : d0 + br) * big_ld;
-    const bf16_t* __restrict__ brow1 = Big + b * big_batch + (long)(RAG ? min(d0 + br + 32, M - 1) : d0 + br + 32) * big_ld;
-    const bf16_t* __restrict__ sm = Small + b * small_batch;
-    const int nsteps = (K + KSLAB - 1) / KSLAB;
+    // this part's slabs: rows and contraction counted from its first one
+    const int slabs = (K + KSLAB - 1) / KSLAB, per_part = (slabs + (int)gridDim.z - 1) / (int)gridDim.z;
+    const int k_first = blockIdx.z * per_part * KSLAB, nsteps = min(slabs - (int)blockIdx.z * per_part, per_part);
+    K -= k_first;
+    const bf16_t* __restrict__ brow0 = Big + k_first + b * big_batch + (long)(RAG ? min(d0 + br, M - 1) : d0 + br) * big_ld;
+    const bf16_t* __restrict__ brow1 = Big + k_first + b * big_batch + (long)(RAG ? min(d0 + br + 32, M - 1) : d0 + br + 32) * big_ld;
+    const bf16_t* __restrict__ sm = Small + k_first + b * small_batch;
     f32x4_t acc[4][NTW];
 #pragma unroll
     for (int rt = 0; rt < 4; ++rt)
@@ -339,9 +387,9 @@ __global__ void __launch_bounds__(256, 2) gemm_nt_kernel(const bf16_t* __restric
     }
 #define SS_NT_FILL(s_, BUF, BR)                                          \
     {                                                                    \
-        if (RAG && ((s_) + 1) * KSLAB > K) {                             \
-            BR[0] = cut(BR[0], (s_) * KSLAB + bk, K);                    \
-            BR[1] = cut(BR[1], (s_) * KSLAB + bk, K);                    \
+        if (RAG && ((s_) + 1) * KSLAB > K) {                     \
+            BR[0] = cut(BR[0], (s_) * KSLAB + bk, K);          \
+            BR[1] = cut(BR[1], (s_) * KSLAB + bk, K);          \
         }                                                                \
         *reinterpret_cast<uint4*>(&Bs[BUF][br][bk]) = BR[0];             \
         *reinterpret_cast<uint4*>(&Bs[BUF][br + 32][bk]) = BR[1];        \
@@ -351,7 +399,7 @@ __global__ void __launch_bounds__(256, 2) gemm_nt_kernel(const bf16_t* __restric
 #define SS_NT_STEP(s_, BUF, SF, BR, BRN)                                                                              \
     {                                                                                                                 \
         small_frags<NTW> cur = SF;                                                                                    \
-        if (RAG && ((s_) + 1) * KSLAB > K) cut_frags<NTW>(cur, lane, (s_) * KSLAB, K);                                \
+        if (RAG && ((s_) + 1) * KSLAB > K) cut_frags<NTW>(cur, lane, (s_) * KSLAB, K);              \
         SS_NT_ISSUE((s_) + PD, SF, BR)                                                                                \
         _Pragma("unroll") for (int ks = 0; ks < 2; ++ks)                                                              \
             _Pragma("unroll") for (int rt = 0; rt < 4; ++rt)                                                          \
@@ -385,7 +433,7 @@ __global__ void __launch_bounds__(256, 2) gemm_nt_kernel(const bf16_t* __restric
 #undef SS_NT_STEP
 #undef SS_NT_FILL
 #undef SS_NT_ISSUE
-    float* __restrict__ c = C + b * c_batch;
+    float* __restrict__ c = C + blockIdx.z * part_stride + b * c_batch;
 #pragma unroll
     for (int rt = 0; rt < 4; ++rt)
 #pragma unroll
@@ -615,26 +663,18 @@ __global__ void __launch_bounds__(256, 2) gemm_rows_lds_kernel(const bf16_t* __r
         }
 }
 
-// Out[b][row][8 c ..+7] (bf16) = sum over the parts of Part[part][b][row][8 c ..+7]; one thread per eight columns
-// (RAG: per column).
-template <bool RAG>
+// Out[b][row][8 c ..+7] (bf16) = sum over the parts of Part[part][b][row][8 c ..+7]; one thread per eight columns.
 __global__ void __launch_bounds__(256) rows_reduce_kernel(const float* __restrict__ Part, int parts, long part_stride,
                                                            bf16_t* __restrict__ Out, long o_ld, long o_batch, int S, int ncols,
                                                            long items)
 {
     const long idx = (long)blockIdx.x * 256 + threadIdx.x;
     if (idx >= items) return;
-    const int per_row = RAG ? ncols : ncols >> 3;
+    const int per_row = ncols >> 3;
     const int c8 = (int)(idx % per_row);
     const long br = idx / per_row;
     const int row = (int)(br % S);
     const long b = br / S;
-    if constexpr (RAG) {
-        float v = Part[br * ncols + c8];
-        for (int z = 1; z < parts; ++z) v += Part[z * part_stride + br * ncols + c8];
-        Out[b * o_batch + (long)row * o_ld + c8] = bf16_t(f32_to_bf16_bits(v));
-        return;
-    }
     const float* __restrict__ src = Part + br * ncols + 8 * c8;
     float4 lo = *reinterpret_cast<const float4*>(src), hi = *reinterpret_cast<const float4*>(src + 4);
     for (int z = 1; z < parts; ++z) {
@@ -768,15 +808,20 @@ inline unsigned tiles64(int n) { return (unsigned)((n + 63) / 64); }
 
 // One launch each (the small operand has at most SMAX rows).
 template <bool OUT_T, bool RAG>
-void launch_nt(const bf16_t* big, long big_ld, long big_batch, const bf16_t* small, long small_ld, long small_batch, float* C,
-               long ldc, long c_batch, int M, int S, int K, int batch, hipStream_t stream)
+void launch_nt(const GemmArgs& g, const bf16_t* big, long big_ld, long big_batch, const bf16_t* small, long small_ld, long small_batch,
+               float* C, int M, int S, hipStream_t stream)
 {
-    const dim3 grid(tiles64(M), (unsigned)batch);
-    const int vec_c = M % 4 == 0 && ldc % 4 == 0 && c_batch % 4 == 0 && al16(C);   // four rows of the big operand are one aligned store (OUT_T)
+    // parts go to the workspace, each as a dense (batch, rows, columns) block, and are added up from there
+    const int parts = parts_for(g, (long)tiles64(M) * g.batch, g.K, KSLAB, (size_t)g.batch * M * S * sizeof(float));
+    float* const dst = parts > 1 ? static_cast<float*>(g.split_ws) : C;
+    const long ldc = parts > 1 ? (OUT_T ? M : S) : g.ldc, c_batch = parts > 1 ? (long)M * S : g.c_batch, part_stride = (long)g.batch * M * S;
+    const dim3 grid(tiles64(M), (unsigned)g.batch, (unsigned)parts);
+    const int vec_c = M % 4 == 0 && ldc % 4 == 0 && c_batch % 4 == 0 && al16(dst);   // four rows of the big operand are one aligned store (OUT_T)
 #define SS_LAUNCH_NT(NTW) hipLaunchKernelGGL((gemm_nt_kernel<OUT_T, RAG, NTW>), grid, dim3(256), 0, stream, big, big_ld, big_batch, \
-                                             small, small_ld, small_batch, C, ldc, c_batch, M, S, K, vec_c)
+                                             small, small_ld, small_batch, dst, ldc, c_batch, part_stride, M, S, g.K, vec_c)
     if (S <= 64) SS_LAUNCH_NT(1); else if (S <= 128) SS_LAUNCH_NT(2); else SS_LAUNCH_NT(3);
 #undef SS_LAUNCH_NT
+    if (parts > 1) reduce_parts<float>(g, parts, C, OUT_T ? S : M, OUT_T ? M : S, stream);
 }
 template <bool RAG>
 void launch_rows(const GemmArgs& g, const bf16_t* A, bf16_t* C, int S, int parts, hipStream_t stream)
@@ -793,10 +838,13 @@ void launch_rows(const GemmArgs& g, const bf16_t* A, bf16_t* C, int S, int parts
     }
 #undef SS_LAUNCH_ROWS
     if (parts > 1) {
-        const bool whole = !RAG;
-        const long items = (long)g.batch * S * (whole ? g.N / 8 : g.N);
-        hipLaunchKernelGGL((rows_reduce_kernel<RAG>), dim3((unsigned)((items + 255) / 256)), dim3(256), 0, stream, ws, parts,
-                           (long)g.batch * S * g.N, C, g.ldc, g.c_batch, S, g.N, items);
+        if constexpr (RAG) {
+            reduce_parts<bf16_t>(g, parts, C, S, g.N, stream);
+        } else {
+            const long items = (long)g.batch * S * (g.N / 8);
+            hipLaunchKernelGGL(rows_reduce_kernel, dim3((unsigned)((items + 255) / 256)), dim3(256), 0, stream, ws, parts,
+                               (long)g.batch * S * g.N, C, g.ldc, g.c_batch, S, g.N, items);
+        }
     }
 }
 template <bool RAG>
@@ -829,10 +877,10 @@ int launch_fast(const GemmArgs& g, hipStream_t stream)
             const int S = small - s0 < SMAX ? small - s0 : SMAX;
             if (out_t) {
                 auto f = rag ? launch_nt<true, true> : launch_nt<true, false>;
-                f(B, g.b_n, g.b_batch, A + (long)s0 * g.a_m, g.a_m, g.a_batch, C + (long)s0 * g.ldc, g.ldc, g.c_batch, big, S, g.K, g.batch, stream);
+                f(g, B, g.b_n, g.b_batch, A + (long)s0 * g.a_m, g.a_m, g.a_batch, C + (long)s0 * g.ldc, big, S, stream);
             } else {
                 auto f = rag ? launch_nt<false, true> : launch_nt<false, false>;
-                f(A, g.a_m, g.a_batch, B + (long)s0 * g.b_n, g.b_n, g.b_batch, C + s0, g.ldc, g.c_batch, big, S, g.K, g.batch, stream);
+                f(g, A, g.a_m, g.a_batch, B + (long)s0 * g.b_n, g.b_n, g.b_batch, C + s0, big, S, stream);
             }
         }
         return hipGetLastError() == hipSuccess ? SS_OK : SS_ERR_LAUNCH;
@@ -855,7 +903,8 @@ int launch_fast(const GemmArgs& g, hipStream_t stream)
             // fewer than two workgroups per CU: two parts if the workspace holds two float32 shares (headline shape: 66 -> 57 us both launches together; four parts measured slower)
             const long wgs = (long)tiles64(g.N) * g.batch;
             const size_t share = (size_t)g.batch * g.M * g.N * sizeof(float);
-            const int parts = (wgs < ROWS_MIN_WGS && g.K >= ROWS_MIN_SPLIT_K && g.split_ws && 2 * share <= g.split_ws_bytes) ? 2 : 1;
+            int parts = parts_for(g, wgs, g.K, KSLAB, share);
+            if (parts == 1 && wgs < ROWS_MIN_WGS && g.K >= ROWS_MIN_SPLIT_K && g.split_ws && 2 * share <= g.split_ws_bytes) parts = 2;
             for (int s0 = 0; s0 < g.M; s0 += SMAX) {   // in stream order: the shares of one launch are added up before the next overwrites them
                 const int S = g.M - s0 < SMAX ? g.M - s0 : SMAX;
                 const bf16_t* a = A + (long)s0 * g.a_m;

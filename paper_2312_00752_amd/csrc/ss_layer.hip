@@ -9,6 +9,8 @@
 // delta_raw = W_dt @ r lands in the (B, D, L) layout of the scan's step-size input.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
+
 #include "ss_device.h"
 #include "ss_kernels.h"
 #include "ss_layer.h"
@@ -268,7 +270,10 @@ ScratchLayout scratch_layout(const ss_layer_params* p, bool bwd)
         w.WdtT = take(s.R * s.D * s.esz);
         w.WxT = take(s.D * s.Mx * s.esz);
     }
-    w.gsplit_bytes = 2 * s.B * s.Mx * s.L * sizeof(float);
+    // two shares of [r;B;C], or the up to 256 64-wide tiles a small product of at most Mx rows is cut into (see parts_for)
+    const size_t two = 2 * s.B * s.Mx * s.L * sizeof(float);
+    const size_t columns = s.B * (bwd && s.D > s.L ? s.D : s.L), eight = 8 * columns * s.Mx * sizeof(float), most = (size_t)256 * 64 * s.Mx * sizeof(float);
+    w.gsplit_bytes = std::max(two, std::min(eight, most));
     w.gsplit = take(w.gsplit_bytes);
     w.total = off;
     return w;
@@ -391,7 +396,8 @@ int ss_layer_fwd(const ss_layer_params* p, void* stream)
         if (rc != SS_ERR_UNSUPPORTED) return rc;   // otherwise nothing was enqueued: take the general path
     }
     // delta_raw = W_dt @ r
-    if (!gemm_rm(st, false, false, D, L, R, p->W_dt, R, 0, P, L, (long)Mx * L, 0.0f, delta, L, (long)D * L, B, bf16))
+    if (!gemm_rm(st, false, false, D, L, R, p->W_dt, R, 0, P, L, (long)Mx * L, 0.0f, delta, L, (long)D * L, B, bf16, false,
+                 scratch + sc.gsplit, sc.gsplit_bytes))
         return SS_ERR_LAUNCH;
     return ss::scan_fwd_strided(&f, (long)Mx * L, stream);
 }
@@ -426,7 +432,8 @@ int ss_layer_bwd(const ss_layer_bwd_params* q, void* stream)
     // recompute the two cheap intermediates
     ss_conv_params c = conv_params(p, u);
     if ((rc = ss_conv_fwd(&c, stream)) != SS_OK) return rc;
-    if (!gemm_rm(st, false, false, D, L, R, p->W_dt, R, 0, P, L, (long)Mx * L, 0.0f, delta, L, (long)D * L, B, bf16))
+    if (!gemm_rm(st, false, false, D, L, R, p->W_dt, R, 0, P, L, (long)Mx * L, 0.0f, delta, L, (long)D * L, B, bf16, false,
+                 scratch + sc.gsplit, sc.gsplit_bytes))
         return SS_ERR_LAUNCH;
 
     // the scan
@@ -454,7 +461,8 @@ int ss_layer_bwd(const ss_layer_bwd_params* q, void* stream)
     if (!gemm_rm(st, false, false, R, L, D, WdtT, D, 0, ddelta, L, (long)D * L, 0.0f, dP, L, (long)Mx * L, B, bf16, false,
                  scratch + sc.gsplit, sc.gsplit_bytes))
         return SS_ERR_LAUNCH;
-    if (!gemm_rm(st, false, true, D, R, L, ddelta, L, (long)D * L, P, L, (long)Mx * L, 0.0f, part_dt, R, (long)D * R, B, bf16, true))
+    if (!gemm_rm(st, false, true, D, R, L, ddelta, L, (long)D * L, P, L, (long)Mx * L, 0.0f, part_dt, R, (long)D * R, B, bf16, true,
+                 scratch + sc.gsplit, sc.gsplit_bytes))
         return SS_ERR_LAUNCH;
     // rows R.. of dP from the scan's float32 dB, dC
     {
@@ -467,7 +475,8 @@ int ss_layer_bwd(const ss_layer_bwd_params* q, void* stream)
     // [r;B;C] = W_x @ u:  du += W_x^T @ dP,  dW_x = sum_b dP u^T
     if (!gemm_rm(st, false, false, D, L, Mx, WxT, Mx, 0, dP, L, (long)Mx * L, 1.0f, du, L, (long)D * L, B, bf16))
         return SS_ERR_LAUNCH;
-    if (!gemm_rm(st, false, true, Mx, D, L, dP, L, (long)Mx * L, u, L, (long)D * L, 0.0f, part_x, D, (long)Mx * D, B, bf16, true))
+    if (!gemm_rm(st, false, true, Mx, D, L, dP, L, (long)Mx * L, u, L, (long)D * L, 0.0f, part_x, D, (long)Mx * D, B, bf16, true,
+                 scratch + sc.gsplit, sc.gsplit_bytes))
         return SS_ERR_LAUNCH;
     {
         const long n_dt = (long)D * R, n_x = (long)Mx * D;

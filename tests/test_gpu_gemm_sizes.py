@@ -83,6 +83,18 @@ def test_whole_slabs_not_a_multiple_of_the_pipeline(slabs):
     _check(_rand(2, 40, n, 11), _rand(2, 192, n, 12), torch.float32, trans_b=True)
 
 
+@pytest.mark.parametrize("nb,D,L,R,Mx", [(1, 64, 2050, 16, 40), (1, 700, 1000, 8, 24), (2, 2050, 130, 33, 65), (1, 3001, 63, 190, 200)])
+@pytest.mark.parametrize("dtype", [BF, torch.float32])
+def test_few_tiles_split_the_contraction(nb, D, L, R, Mx, dtype):
+    """Products of few tiles and long contractions, with a workspace: up to eight shares per result, the last one ragged."""
+    u, P = _rand(nb, D, L, 21).to(dtype), _rand(nb, Mx, L, 22).to(dtype)
+    W_x = _rand(1, Mx, D, 23)[0].to(dtype)
+    ws = torch.full((8 * nb * max(Mx * L, Mx * D) * 4,), 0xFF, dtype=torch.uint8, device=DEV)
+    _check(W_x, u, dtype, workspace=ws)
+    _check(u, P[:, :R], torch.float32, trans_b=True, workspace=ws)
+    _check(P, u, torch.float32, trans_b=True, workspace=ws)
+
+
 def test_infinities_and_nan_stay_where_they_belong():
     """A last row or column of infinities reaches the results that contain it and no others."""
     nb, D, L, M = 1, 71, 77, 19
