@@ -198,7 +198,6 @@ ss::FwdArgs make_fwd_args(const ss_fwd_params* p, long bc_bstride)
     a.acc_y = 0;
     a.flags = p->flags;
     // 16-byte slices, addressed through per-workgroup buffer resources (64 rows, 31-bit offsets)
-    a.ld_ud = p->seqlen; a.ld_bc = p->seqlen;
     a.dpp_ok = p->seqlen >= 8 && (size_t)p->seqlen * 64 * sizeof(float) < ((size_t)1 << 31);
     a.vec_ok = a.dpp_ok && p->seqlen % 8 == 0;
     a.il = deals_states(a.dpp_ok, p->flags) && a.N < 16;

@@ -579,7 +579,7 @@ struct BwdSmemDpp {
 // like dt A / 2 and so magnifies phi's own rounding error by 2 / |dt A|: below |dt A| = 2^-4 (and for A = 0)
 // the term is g dt^2 (1/2 + x/3 + x^2/8) instead.  (8 x 1536 x 2048 bf16: 731 us with one workgroup per compute unit
 // and 361 registers, 553 us with two and 256.)
-// RAG: rows of any length >= 8 and any pitch (see scan_fwd_kernel).  Slices are read at element alignment from
+// RAG: rows of any length >= 8 (see scan_fwd_kernel).  Slices are read at element alignment from
 // inside the row and shifted into place, and rows past D cleared, in the blocks that need it only.
 template <typename T, int SPL, bool ZOH = false, bool RAG = false>
 __global__ void __launch_bounds__(THREADS, 2) scan_bwd_dpp_kernel(const BwdArgs a)
@@ -629,11 +629,10 @@ __global__ void __launch_bounds__(THREADS, 2) scan_bwd_dpp_kernel(const BwdArgs 
     // RAG: plain pointers to the workgroup's first row and offsets of this thread's row, clamped to a valid one
     const uint32_t esz = (uint32_t)sizeof(T);
     const int r_row = min(pr, rows_here - 1);
-    const uint32_t r_off = (uint32_t)r_row * (uint32_t)L * esz, r_off_ud = (uint32_t)r_row * (uint32_t)f.ld_ud * esz;
-    const uint32_t r_off_bc = (uint32_t)min(s_n, N - 1) * (uint32_t)f.ld_bc * esz;
-    const long wg_ud = ((long)b * f.D + d0) * f.ld_ud;
-    const T* const ru_p = static_cast<const T*>(f.u) + wg_ud;
-    const T* const rd_p = static_cast<const T*>(f.delta) + wg_ud;
+    const uint32_t r_off = (uint32_t)r_row * (uint32_t)L * esz;
+    const uint32_t r_off_bc = (uint32_t)min(s_n, N - 1) * (uint32_t)L * esz;
+    const T* const ru_p = static_cast<const T*>(f.u) + wg_first;
+    const T* const rd_p = static_cast<const T*>(f.delta) + wg_first;
     const T* const ro_p = static_cast<const T*>(a.dout) + wg_first;
     const T* const rz_p = has_z ? static_cast<const T*>(f.z) + wg_first : ro_p;
     const T* const ry_p = has_z ? static_cast<const T*>(f.ysave) + wg_first : ro_p;
@@ -685,8 +684,8 @@ __global__ void __launch_bounds__(THREADS, 2) scan_bwd_dpp_kernel(const BwdArgs 
             const int t0 = blk * BT + pq * BSL;
             if constexpr (RAG) {
                 const uint32_t t = (uint32_t)row_piece(t0, BSL, L) * esz;
-                ru[s] = io4<T>::load_elem(ru_p, r_off_ud + t);
-                rd[s] = io4<T>::load_elem(rd_p, r_off_ud + t);
+                ru[s] = io4<T>::load_elem(ru_p, r_off + t);
+                rd[s] = io4<T>::load_elem(rd_p, r_off + t);
                 ro[s] = io4<T>::load_elem(ro_p, r_off + t);
                 rz[s] = io4<T>::load_elem(rz_p, has_z ? r_off + t : 0u);
                 ry[s] = io4<T>::load_elem(ry_p, has_z ? r_off + t : 0u);
@@ -960,8 +959,8 @@ __global__ void __launch_bounds__(THREADS, 2) scan_bwd_dpp_kernel(const BwdArgs 
                 float pu[BSL], pl[BSL];
                 if constexpr (RAG) {
                     const int tp = row_piece(t0, BSL, L);
-                    typename io4<T>::raw xu = io4<T>::load_elem(static_cast<const T*>(a.du) + wg_ud, r_off_ud + (uint32_t)tp * esz);
-                    typename io4<T>::raw xl = io4<T>::load_elem(static_cast<const T*>(a.ddelta) + wg_ud, r_off_ud + (uint32_t)tp * esz);
+                    typename io4<T>::raw xu = io4<T>::load_elem(static_cast<const T*>(a.du) + wg_first, r_off + (uint32_t)tp * esz);
+                    typename io4<T>::raw xl = io4<T>::load_elem(static_cast<const T*>(a.ddelta) + wg_first, r_off + (uint32_t)tp * esz);
                     io4<T>::drop(xu, t0 - tp);
                     io4<T>::drop(xl, t0 - tp);
                     io4<T>::unpack(xu, pu);
@@ -974,9 +973,9 @@ __global__ void __launch_bounds__(THREADS, 2) scan_bwd_dpp_kernel(const BwdArgs 
                 for (int j = 0; j < BSL; ++j) { du4[j] += pu[j]; dl4[j] += pl[j]; }
             }
             if constexpr (RAG) {
-                const uint32_t off_ud = r_off_ud + (uint32_t)t0 * esz;
-                store_paired_rag(a.du, wg_ud, off_ud, t0, nv, io4<T>::pack(du4), keep_du, blk & 1);
-                store_paired_rag(a.ddelta, wg_ud, off_ud, t0, nv, io4<T>::pack(dl4), keep_dl, blk & 1);
+                const uint32_t off_t = r_off + (uint32_t)t0 * esz;
+                store_paired_rag(a.du, wg_first, off_t, t0, nv, io4<T>::pack(du4), keep_du, blk & 1);
+                store_paired_rag(a.ddelta, wg_first, off_t, t0, nv, io4<T>::pack(dl4), keep_dl, blk & 1);
                 if constexpr (LG == 2) keep_live = blk & 1;
             } else {
                 store_paired(bdu_, off, io4<T>::pack(du4), keep_du, blk & 1);
@@ -1131,7 +1130,7 @@ __global__ void __launch_bounds__(THREADS) adjoint_agg_kernel(const BwdArgs a)
 // The adjoint aggregate on the common path (real state, selective C, L % 8 == 0): as
 // adjoint_agg_kernel, with the chunk's C staged through an LDS tile and taken as a quad-broadcast
 // DPP operand (see scan_bwd_dpp_kernel), buffer-addressed inputs requested two chunks ahead into
-// compile-time slots, and no scalar loads.  RAG: rows of any length >= 8 and any pitch (see scan_fwd_kernel).
+// compile-time slots, and no scalar loads.  RAG: rows of any length >= 8 (see scan_fwd_kernel).
 template <typename T, int SPL, bool RAG = false>
 __global__ void __launch_bounds__(THREADS, 4) adjoint_agg_dpp_kernel(const BwdArgs a)
 {
@@ -1171,9 +1170,9 @@ __global__ void __launch_bounds__(THREADS, 4) adjoint_agg_dpp_kernel(const BwdAr
     const uint32_t c_row_off = s_n < N ? (uint32_t)s_n * (uint32_t)L * (uint32_t)sizeof(T) : BUF_OFF;
     const uint32_t esz = (uint32_t)sizeof(T);
     const int r_row = min(pr, rows_here - 1);
-    const uint32_t r_off = (uint32_t)r_row * (uint32_t)L * esz, r_off_ud = (uint32_t)r_row * (uint32_t)f.ld_ud * esz;
-    const uint32_t r_off_c = (uint32_t)min(s_n, N - 1) * (uint32_t)f.ld_bc * esz;
-    const T* const rd_p = static_cast<const T*>(f.delta) + ((long)b * f.D + d0) * f.ld_ud;
+    const uint32_t r_off = (uint32_t)r_row * (uint32_t)L * esz;
+    const uint32_t r_off_c = (uint32_t)min(s_n, N - 1) * (uint32_t)L * esz;
+    const T* const rd_p = static_cast<const T*>(f.delta) + wg_first;
     const T* const ro_p = static_cast<const T*>(a.dout) + wg_first;
     const T* const rz_p = has_z ? static_cast<const T*>(f.z) + wg_first : ro_p;
     const T* const rc_p = static_cast<const T*>(f.Cm) + (long)b * f.bc_bstride;
@@ -1199,7 +1198,7 @@ __global__ void __launch_bounds__(THREADS, 4) adjoint_agg_dpp_kernel(const BwdAr
         if constexpr (RAG) {   // before the segment's start: its first chunk again (never used)
             const int cc = max(c, c_begin) * CHUNK_T;
             const uint32_t t = (uint32_t)row_piece(cc + pq * SLICE, SLICE, L) * esz;
-            rd_[s] = io8<T>::load_elem(rd_p, r_off_ud + t);
+            rd_[s] = io8<T>::load_elem(rd_p, r_off + t);
             ro_[s] = io8<T>::load_elem(ro_p, r_off + t);
             rz_[s] = io8<T>::load_elem(rz_p, has_z ? r_off + t : 0u);
             rc_[s] = io4<T>::load_elem(rc_p, r_off_c + (uint32_t)row_piece(cc + s_tq * GROUP_T, GROUP_T, L) * esz);

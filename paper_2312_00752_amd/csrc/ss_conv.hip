@@ -22,7 +22,6 @@ constexpr int PIECE = WAVE * 8;          // steps one wave covers per pass
 
 struct ConvArgs {
     int B, D, L, W;
-    int ld_v;   // elements between rows of out (forward) / dout (backward); L, or a multiple of 8 beyond it: the rest of a row of out is written as zeros
     unsigned flags;
     const void *x, *state_in, *dout;
     const float *w, *bias;
@@ -201,15 +200,9 @@ __global__ __launch_bounds__(THREADS) void conv_fwd_kernel(const ConvArgs a)
         o[j] = SILU ? v * sigmoid_fast(v) : v;
     }
     const int nvalid = min(a.L - t0, 8);
-    T* const orow = static_cast<T*>(a.out) + (size_t)r * a.ld_v;
+    T* const orow = static_cast<T*>(a.out) + (size_t)r * a.L;
     if constexpr (KIND == ROWS_ANY) {
-        if (a.ld_v > a.L) {   // a padded pitch: the slice is whole, zeros past the end
-#pragma unroll
-            for (int j = 0; j < 8; ++j) o[j] = j < nvalid ? o[j] : 0.0f;
-            io8<T>::store_elem(orow, (uint32_t)t0 * (uint32_t)sizeof(T), io8<T>::pack(o), 8);
-        } else {
-            io8<T>::store_elem(orow, (uint32_t)t0 * (uint32_t)sizeof(T), io8<T>::pack(o), nvalid);
-        }
+        io8<T>::store_elem(orow, (uint32_t)t0 * (uint32_t)sizeof(T), io8<T>::pack(o), nvalid);
     } else {
         io8<T>::template store<KIND == ROWS_WHOLE>(orow + t0, o, nvalid);
     }
@@ -258,7 +251,7 @@ __global__ __launch_bounds__(THREADS) void conv_bwd_kernel(const ConvArgs a)
         const size_t r = (size_t)b * a.D + d;
         const int t0 = piece * PIECE + lane * 8;
         const T* row = static_cast<const T*>(a.x) + r * a.L;
-        const T* grow = static_cast<const T*>(a.dout) + r * a.ld_v;
+        const T* grow = static_cast<const T*>(a.dout) + r * a.L;
         const T* state_row = (a.flags & SS_CONV_HAS_STATE) ? static_cast<const T*>(a.state_in) + r * (a.W - 1) : nullptr;
         const int nvalid = min(max(a.L - t0, 0), 8);
 
@@ -480,7 +473,6 @@ ss::ConvArgs make_conv_args(const ss_conv_params* p)
 {
     ss::ConvArgs a{};
     a.B = p->batch; a.D = p->dim; a.L = p->seqlen; a.W = p->width;
-    a.ld_v = p->seqlen;
     a.flags = p->flags;
     if (p->width == 1) a.flags &= ~(unsigned)(SS_CONV_HAS_STATE | SS_CONV_WRITE_STATE);
     a.x = p->x; a.state_in = p->state_in; a.w = p->w; a.bias = p->bias;

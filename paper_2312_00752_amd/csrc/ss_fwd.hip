@@ -53,7 +53,7 @@ typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));   // MFMA operand a
 // (input_step_dpp, readout_step_dpp).  No scalar loads or their waits (which also drain LDS reads and
 // vice versa), no repacking pass, no touching of cache lines ahead, and no vector-memory wait that
 // has to cover the previous chunk's stores.
-// RAG (PAT): rows of any length >= 8 and any pitch.  Slices are read in one access at element alignment, the
+// RAG (PAT): rows of any length >= 8.  Slices are read in one access at element alignment, the
 // one that reaches past the end from inside the row (row_piece), and shifted into place in the last chunk
 // only; a partial slice is stored element by element.  Everything else is the aligned kernel's.  Such rows
 // used to take the scalar path with one access per element: 8 x 1536 x 2047 in bf16, main + aggregate pass
@@ -126,10 +126,10 @@ __global__ void __launch_bounds__(THREADS, PAT && AGG ? 4 : ((PAT && FUSED_KS <=
     // RAG: plain pointers to the workgroup's first row and offsets of this thread's row, clamped to a valid one
     const uint32_t esz = (uint32_t)sizeof(T);
     const int r_row = min(pr, rows_here - 1);
-    const uint32_t r_off = (uint32_t)r_row * (uint32_t)L * esz, r_off_ud = (uint32_t)r_row * (uint32_t)a.ld_ud * esz;
-    const uint32_t r_off_bc = (uint32_t)min(s_n, N - 1) * (uint32_t)a.ld_bc * esz;
-    const T* const ru_p = static_cast<const T*>(a.u) + ((long)b * a.D + d0) * a.ld_ud;
-    const T* const rd_p = static_cast<const T*>(a.delta) + ((long)b * a.D + d0) * a.ld_ud;
+    const uint32_t r_off = (uint32_t)r_row * (uint32_t)L * esz;
+    const uint32_t r_off_bc = (uint32_t)min(s_n, N - 1) * (uint32_t)L * esz;
+    const T* const ru_p = static_cast<const T*>(a.u) + wg_first;
+    const T* const rd_p = static_cast<const T*>(a.delta) + wg_first;
     const T* const rz_p = has_z ? static_cast<const T*>(a.z) + wg_first : ru_p;
     const T* const rp_p = acc_on ? static_cast<const T*>(has_z ? a.ysave : a.out) + wg_first : ru_p;
     const T* const rbc_p = static_cast<const T*>(s_which ? a.Cm : a.Bm) + (long)b * a.bc_bstride;
@@ -228,8 +228,8 @@ __global__ void __launch_bounds__(THREADS, PAT && AGG ? 4 : ((PAT && FUSED_KS <=
         if constexpr (RAG) {   // past the segment's end: its last chunk again (never used)
             const int cc = min(c, c_end - 1) * CHUNK_T;
             const uint32_t t = (uint32_t)row_piece(cc + pq * SLICE, SLICE, L) * esz;
-            ru_[s] = io8<T>::load_elem(ru_p, r_off_ud + t);
-            if constexpr (FUSED_KS == 0) rd_[s] = io8<T>::load_elem(rd_p, r_off_ud + t);
+            ru_[s] = io8<T>::load_elem(ru_p, r_off + t);
+            if constexpr (FUSED_KS == 0) rd_[s] = io8<T>::load_elem(rd_p, r_off + t);
             if constexpr (!AGG) {
                 rz_[s] = io8<T>::load_elem(rz_p, has_z ? r_off + t : 0u);
                 rp_[s] = io8<T>::load_elem(rp_p, acc_on ? r_off + t : 0u);
@@ -319,8 +319,8 @@ __global__ void __launch_bounds__(THREADS, PAT && AGG ? 4 : ((PAT && FUSED_KS <=
             t[s] = (uint32_t)row_piece(cc + pq * SLICE, SLICE, L) * esz;
             tb[s] = r_off_bc + (uint32_t)row_piece(cc + s_tq * GROUP_T, GROUP_T, L) * esz;
         }
-        ru_[0] = io8<T>::load_elem(ru_p, r_off_ud + t[0]); ru_[1] = io8<T>::load_elem(ru_p, r_off_ud + t[1]);
-        if constexpr (FUSED_KS == 0) { rd_[0] = io8<T>::load_elem(rd_p, r_off_ud + t[0]); rd_[1] = io8<T>::load_elem(rd_p, r_off_ud + t[1]); }
+        ru_[0] = io8<T>::load_elem(ru_p, r_off + t[0]); ru_[1] = io8<T>::load_elem(ru_p, r_off + t[1]);
+        if constexpr (FUSED_KS == 0) { rd_[0] = io8<T>::load_elem(rd_p, r_off + t[0]); rd_[1] = io8<T>::load_elem(rd_p, r_off + t[1]); }
         if constexpr (!AGG) {
             rz_[0] = io8<T>::load_elem(rz_p, has_z ? r_off + t[0] : 0u); rz_[1] = io8<T>::load_elem(rz_p, has_z ? r_off + t[1] : 0u);
             rp_[0] = io8<T>::load_elem(rp_p, acc_on ? r_off + t[0] : 0u); rp_[1] = io8<T>::load_elem(rp_p, acc_on ? r_off + t[1] : 0u);

@@ -33,13 +33,10 @@ struct FwdArgs {
     // the workspace (checkpoints, segment states and carries, dA partials) stay in slot order 4w + k.
     int il;
     uint32_t flags;
-    int vec_ok;  // L % 8 == 0 and pitches of L: every row starts 16-byte aligned and 8-step slices are whole or empty
+    int vec_ok;  // L % 8 == 0: every row starts 16-byte aligned and 8-step slices are whole or empty
     int dpp_ok;  // L >= 8 and 64 rows below 2^31 bytes: the kernels with B and C as quad-broadcast operands take the call
     const void *u, *delta, *z, *Bm, *Cm;
     long bc_bstride;  // elements between consecutive batch entries of Bm and Cm (N * L when dense)
-    // elements between consecutive rows of u and delta (and du, ddelta in the backward pass), and of Bm and Cm; L
-    // unless the layer keeps its intermediates at a padded pitch
-    int ld_ud, ld_bc;
     // Staged copy of the selective B and C for the forward kernels, or null.  In the io dtype,
     // packed per wave: [B][4 * ceil(NS / 16)][Lp / 4][B: 4 states x 4 steps | C: 4 states x 4 steps],
     // Lp = L rounded up to a whole chunk, zeros for states past NS and steps past L.  What one
