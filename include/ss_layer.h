@@ -98,10 +98,10 @@ size_t ss_layer_step_scratch_bytes(const ss_layer_step_params *p);
 
 /* One token of the layer in recurrent mode (Section 2): the conv window slides by one sample,
  * the projections become (B, D) x (D, R+2N) and (B, R) x (R, D) products, and Eq. 2a/2b are
- * applied once; constant time and memory per token.  bf16 calls with D % 32 == 0, R % 8 == 0,
- * R <= 256, N <= 16 and 16-byte aligned W_x, W_dt and h take three launches (both projections
- * on the matrix cores, delta_t formed inside the state update); other calls form the two
- * products with the general projection kernel first.  Deterministic either way. */
+ * applied once; constant time and memory per token.  Calls with D >= 8, 8 <= R <= 256, N <= 16
+ * and a 16-byte aligned h take three launches (both projections on the matrix cores, delta_t
+ * formed inside the state update); other calls form the two products with the general
+ * projection kernel first.  Deterministic either way. */
 int ss_layer_step(const ss_layer_step_params *p, void *stream);
 
 /* The products behind the layer's projections (Algorithm 2: the linear maps s_B, s_C of
@@ -113,14 +113,14 @@ int ss_layer_step(const ss_layer_step_params *p, void *stream);
  * operand may be stored transposed; a batch stride of 0 shares an operand); C is row-major with
  * row pitch ldc, float32 with SS_GEMM_C_FLOAT and in io_dtype otherwise.  A and B are io_dtype.
  * bf16 products of the layer's three shapes (few output rows with a long contraction over the rows
- * of B; many output rows with a contraction of at most 160; both operands contiguous along the
- * contraction index with a float32 result) run on matrix-core kernels when sizes are multiples of
- * 64 (rows / columns of the big side), 16 (the small side, at most 160) and pointers and strides
- * are multiples of 16 bytes; everything else, and every call with SS_GEMM_GENERAL, runs on a
- * general kernel.  `workspace` is optional device memory (256-byte aligned) that the call may
- * overwrite: with ss_proj_gemm_workspace_bytes(p) bytes of it, a product of the first shape with
- * fewer than 512 column tiles x batch entries and K >= 4096, a multiple of 512, splits its
- * contraction over two workgroups per tile (float32 shares, summed by a second kernel); the
+ * of B; many output rows with a contraction of at most 192; both operands contiguous along the
+ * contraction index with a float32 result) run on kernels of their own, at any size from 8 up and
+ * any pitch, fastest where sizes are multiples of 64 and pointers and strides of 16 bytes; everything
+ * else, and every call with SS_GEMM_GENERAL, runs on a general kernel.  `workspace` is optional device
+ * memory (256-byte aligned) that the call may overwrite: with it, a product of few tiles (of the first
+ * shape, with ss_proj_gemm_workspace_bytes(p) bytes, also one of fewer than 512 and K >= 4096) cuts its
+ * contraction into up to eight parts, as many as it holds float32 shares of the result for, and adds
+ * them in order with a second kernel; the
  * result may then differ from the unsplit one in the last bf16 digit.  Device pointers; C must not overlap A or B.  SS_OK, SS_ERR_NULL,
  * SS_ERR_SHAPE (negative size), SS_ERR_UNSUPPORTED (dtype, unknown flag, more than 65535 batch
  * entries or 64-row tiles) or SS_ERR_LAUNCH. */

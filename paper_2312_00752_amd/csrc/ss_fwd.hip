@@ -499,8 +499,10 @@ __global__ void __launch_bounds__(THREADS, PAT && AGG ? 4 : ((PAT && FUSED_KS <=
         };
         // The aggregate pass has little LDS and nothing but the recurrence, so it runs four waves per SIMD: a group
         // is read one ahead, and the barrier below keeps the scheduler from starting every later group early
-        // (which took all 256 or 512 registers, spills included, and one or two waves per SIMD).
-        constexpr bool LEAN = PAT && AGG;
+        // (which took all 256 or 512 registers, spills included, and one or two waves per SIMD).  The float main
+        // pass, whose inputs take twice the registers, spills up to 20 otherwise (4 x 1536 x 2047, forward +
+        // backward: 448 -> 422 us); the bf16 one does not, and gains nothing.
+        constexpr bool LEAN = PAT && (AGG || sizeof(T) == 4);
         if constexpr (LEAN) {
             read_group(0);
         } else {
@@ -582,7 +584,7 @@ __global__ void __launch_bounds__(THREADS, PAT && AGG ? 4 : ((PAT && FUSED_KS <=
             }
             if (!AGG)
                 *reinterpret_cast<float4*>(&s_yp[w][lane][tl]) = make_float4(yp[0], yp[1], yp[2], yp[3]);
-            if constexpr (LEAN)   // the group ends here: left alone, half of the chunk's arithmetic sinks below the barriers
+            if constexpr (PAT && AGG)   // the group ends here: left alone, half of the chunk's arithmetic sinks below the barriers
                 asm volatile("" : "+v"(h[0]), "+v"(h[1]), "+v"(h[2]), "+v"(h[3]));
         }
         // delta_raw of the next chunk, before the barrier: the next phase A rewrites s_rT after it
