@@ -578,7 +578,7 @@ struct BwdSmemDpp {
 // where g dphi/dA = (abar g dt - g phi)/A needs neither a division nor dphi itself.  That difference cancels
 // like dt A / 2 and so magnifies phi's own rounding error by 2 / |dt A|: below |dt A| = 2^-4 (and for A = 0)
 // the term is g dt^2 (1/2 + x/3 + x^2/8) instead.  (8 x 1536 x 2048 bf16: 731 us with one workgroup per compute unit
-// and 361 registers, 553 us with two and 256.)
+// and 361 registers, 533 us with two and 256.)
 // RAG: rows of any length >= 8 (see scan_fwd_kernel).  Slices are read at element alignment from
 // inside the row and shifted into place, and rows past D cleared, in the blocks that need it only.
 template <typename T, int SPL, bool ZOH = false, bool RAG = false>

@@ -1042,16 +1042,18 @@ __global__ void __launch_bounds__(SP_THREADS, SP_BT == 8 && sizeof(T) == 2 ? 4 :
 
     // Waves 0-3 form the tile (batch entries) x (channels d0 + 16 * wave ..+15) of r W_dt^T after
     // the staging below (fragments as tile_mma describes).  Their pieces of W_dt are requested now, with everything
-    // else (from a clamped, valid place; what lies past R meets zeros of r below).
+    // else (from a clamped, valid place; what lies past R meets zeros of r).
     const int dcol = 16 * (wave & 3) + (lane & 15);
     const int wrow = min(d0 + dcol, a.D - 1);
     const int ksub = mma::E * (lane >> 4);
     u32x4 wfrag[SP_MAX_KSTEPS];
     const float bias_raw = (has_bias ? a.bias : a.A)[has_bias ? wrow : 0];
     {
-        const T* wp = static_cast<const T*>(a.W_dt) + (long)wrow * R;
+        const T* wp = static_cast<const T*>(a.W_dt) + (long)d0 * R;   // the workgroup's first row
+        const int woff = (wrow - d0) * R;
 #pragma unroll
-        for (int i = 0; i < SP_MAX_KSTEPS; ++i) wfrag[i] = mma::load(wp, mma::K * i + ksub, R);
+        for (int i = 0; i < SP_MAX_KSTEPS; ++i)
+            wfrag[i] = load_any<u32x4>(wp, (uint32_t)(woff + row_piece(mma::K * i + ksub, mma::E, R)) * (uint32_t)sizeof(T));
     }
 
     {
@@ -1077,6 +1079,9 @@ __global__ void __launch_bounds__(SP_THREADS, SP_BT == 8 && sizeof(T) == 2 ? 4 :
             const int col = i % a.ldp;
             if (i < count) s_p[i / a.ldp][col < R ? col : SP_MAX_R + col - R] = as_stored(s);
         }
+        // r up to a whole step of the product
+        const int zcol = R + (tid & 31);
+        if ((tid >> 5) < SP_BT && zcol < (R + mma::K - 1) / mma::K * mma::K) s_p[tid >> 5][zcol] = 0.0f;
     }
     __syncthreads();
 
@@ -1095,11 +1100,7 @@ __global__ void __launch_bounds__(SP_THREADS, SP_BT == 8 && sizeof(T) == 2 ? 4 :
                     pv[e] = p4.x; pv[e + 1] = p4.y; pv[e + 2] = p4.z; pv[e + 3] = p4.w;
                 }
                 u32x4 av, wv = wfrag[i];
-                if (k + mma::K > R) {                         // uniform: the last step
-                    wv = mma::cut(wv, k + ksub, R);
-#pragma unroll
-                    for (int e = 0; e < mma::E; ++e) pv[e] = k + ksub + e < R ? pv[e] : 0.0f;
-                }
+                if (R % mma::E != 0 && k + mma::K > R) wv = mma::cut(wv, k + ksub, R);   // uniform
 #pragma unroll
                 for (int e = 0; e < 4; ++e) {
                     if constexpr (sizeof(T) == 2) av[e] = pack_bf16x2(pv[2 * e], pv[2 * e + 1]);   // exact: rounded above
