@@ -1142,6 +1142,10 @@ __global__ void __launch_bounds__(THREADS, 4) adjoint_agg_dpp_kernel(const BwdAr
     const int tid = threadIdx.x;
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int lane = tid & (WAVE - 1);
+    for (long i = ((long)blockIdx.y * gridDim.x + blockIdx.x) * THREADS + tid; i < a.zero_n; i += (long)gridDim.x * gridDim.y * THREADS) {
+        a.zeroB[i] = 0.0f;
+        a.zeroC[i] = 0.0f;
+    }
     const int groups = (f.D + ROWS - 1) / ROWS;
     const unsigned bx = xcd_contiguous(blockIdx.x, gridDim.x);
     const int b = bx / groups;
@@ -1545,10 +1549,18 @@ int launch_bwd(const BwdArgs& a, int io_dtype, hipStream_t stream)
     const long nbc = (long)f.B * f.NS * f.L;
     float* const zB = ((f.flags & F_B_FIXED) || a.acc) ? nullptr : a.dB;
     float* const zC = ((f.flags & F_C_FIXED) || a.acc) ? nullptr : a.dC;
-    if (zB || zC) zero_kernel<<<dim3((unsigned)((nbc + 255) / 256)), dim3(256), 0, stream>>>(zB, zC, nbc);
+    // a split sequence's aggregate kernel clears them on the way, where the call takes the kernels that have one
+    // (a launch of 4 us less in each such call)
+    BwdArgs b = a;
+    b.zero_n = 0;
+    if (zB && zC && f.nseg > 1 && f.dpp_ok && !(f.flags & F_COMPLEX)) {
+        b.zeroB = zB; b.zeroC = zC; b.zero_n = nbc;
+    } else if (zB || zC) {
+        zero_kernel<<<dim3((unsigned)((nbc + 255) / 256)), dim3(256), 0, stream>>>(zB, zC, nbc);
+    }
     const int groups = (f.D + ROWS - 1) / ROWS;
     const dim3 grid((unsigned)(f.B * groups));
-    const int rc = io_dtype == 0 ? launch_bwd_io<float>(a, grid, stream) : launch_bwd_io<bf16_t>(a, grid, stream);
+    const int rc = io_dtype == 0 ? launch_bwd_io<float>(b, grid, stream) : launch_bwd_io<bf16_t>(b, grid, stream);
     if (rc != 0) return rc;
     finalize_kernel<<<dim3(fin_blocks), dim3(64 * FIN_LANES), 0, stream>>>(a, 1);
     return hipGetLastError() == hipSuccess ? 0 : -1;

@@ -73,6 +73,8 @@ struct BwdArgs {
     float *dA_part;             // [nseg][B][D][16] partial sums per segment and batch entry
     float *dD_part, *db_part;   // [nseg][B][D]
     float* seg_g;               // [nseg][B][D][16]: adjoint carry of a segment (local, then incoming)
+    float *zeroB, *zeroC;       // what a split sequence's aggregate kernel clears for the scan kernel's atomics: dB and dC
+    long zero_n;                // (zero_n floats each), or 0
     float* dh0;
     float *dA, *dD, *dbias;     // final outputs of the reduction kernel
 };
