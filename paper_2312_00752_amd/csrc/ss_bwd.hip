@@ -174,9 +174,7 @@ __device__ __forceinline__ int lane_value(int lane)
 // dA instead of being reduced over the rows of the workgroup.
 // Exact ZOH with a time-invariant B or C needs more registers than two workgroups per compute unit leave; it is
 // built for one.  (Exact ZOH with selective B and C runs on scan_bwd_dpp_kernel but for the shortest rows.)
-// WGS: workgroups per compute unit the kernel is built for.  With a time-invariant B alone the registers of one
-// workgroup per unit are the faster choice for a grid that gives no more than that (8 x 2048 x 2048 bf16: 807 against
-// 876 us forward + backward; 8 x 4096 x 2048: 1467 against 1191).
+// WGS: workgroups per compute unit the kernel is built for (see ONE_WG_WINS for where both are built).
 template <typename T, bool VEC, bool FULLN, bool ZOH, int BCFIX = 0, bool CPLX = false, int WGS = ZOH ? 1 : 2>
 __global__ void __launch_bounds__(THREADS, WGS) scan_bwd_kernel(const BwdArgs a)
 {
@@ -1428,26 +1426,38 @@ static bool allow_backward_lds_once(K kern, std::atomic<bool> (&done)[MAX_DEVICE
 }
 
 constexpr unsigned COMPUTE_UNITS = 256;
-template <typename T, bool VEC, bool FULLN, bool ZOH, int BCFIX, int WGS = ZOH ? 1 : 2>
+// Time-invariant B and / or C (never split): a grid that gives each compute unit no more than one workgroup gains
+// nothing from a kernel that leaves room for two and pays for its 256 registers.  Variants for which that costs
+// something are built both ways; backward call, us, two per unit / one per unit:
+//   workgroups                                 256           512
+//   B, real, f32, 2048 steps                   563 / 563     1009 / 1134   (bf16 567 / 567, 835 / 1128)
+//   B, complex, f32, 2048 steps                772 / 672     1030 / 1349
+//   C, real, f32, 2047 steps                   1418 / 1327   1901 / 2589
+//   C, complex, f32, 2047 steps                1590 / 1403   2104 / 2768
+//   C, real, f32, 2048 steps                   597 / 602     1014 / 1016   (built for two only)
+//   B and C, real, bf16, 2047 steps            923 / 926     1300 / 1298   (built for two only)
+template <bool VEC, int BCFIX, bool CPLX>
+constexpr bool ONE_WG_WINS = BCFIX == 1 || (BCFIX == 2 && (CPLX || !VEC));
+template <typename T, bool VEC, bool FULLN, bool ZOH, int BCFIX, bool CPLX = false, int WGS = ZOH ? 1 : 2>
 static int launch_scan_bwd_fixed(const BwdArgs& a, dim3 grid, hipStream_t stream)
 {
-    if constexpr (BCFIX == 1 && WGS == 2)
-        if (grid.x <= COMPUTE_UNITS) return launch_scan_bwd_fixed<T, VEC, FULLN, ZOH, BCFIX, 1>(a, grid, stream);
-    auto kern = scan_bwd_kernel<T, VEC, FULLN, ZOH, BCFIX, false, WGS>;
+    if constexpr (WGS == 2 && ONE_WG_WINS<VEC, BCFIX, CPLX>)
+        if (grid.x <= COMPUTE_UNITS) return launch_scan_bwd_fixed<T, VEC, FULLN, ZOH, BCFIX, CPLX, 1>(a, grid, stream);
+    auto kern = scan_bwd_kernel<T, VEC, FULLN, ZOH, BCFIX, CPLX, WGS>;
     static std::atomic<bool> lds_ok[MAX_DEVICES];   // this launcher is instantiated once per kernel
     if (!allow_backward_lds_once(reinterpret_cast<const void*>(kern), lds_ok, sizeof(BwdSmem))) return -1;
     kern<<<dim3(grid.x, 1u), dim3(THREADS), sizeof(BwdSmem), stream>>>(a);
     return hipGetLastError() == hipSuccess ? 0 : -1;
 }
 
-// complex state: first-order B-bar only; selective or time-invariant B / C
-template <typename T, bool VEC, bool FULLN, int BCFIX>
+// complex state with selective B and C: first-order B-bar only
+template <typename T, bool VEC, bool FULLN>
 static int launch_scan_bwd_complex(const BwdArgs& a, dim3 grid, hipStream_t stream)
 {
-    auto kern = scan_bwd_kernel<T, VEC, FULLN, false, BCFIX, true>;
+    auto kern = scan_bwd_kernel<T, VEC, FULLN, false, 0, true>;
     static std::atomic<bool> lds_ok[MAX_DEVICES];   // this launcher is instantiated once per kernel
     if (!allow_backward_lds_once(reinterpret_cast<const void*>(kern), lds_ok, sizeof(BwdSmem))) return -1;
-    if (a.f.nseg > 1) {   // only with selective B and C (the planner does not split the others)
+    if (a.f.nseg > 1) {
         adjoint_agg_kernel<T, VEC, FULLN, true><<<dim3(grid.x, (unsigned)(a.f.nseg - 1)), dim3(THREADS), 0, stream>>>(a);
         const long n = (long)a.f.B * a.f.D * NPAD;
         carry_bwd_kernel<<<dim3((unsigned)((n + 255) / 256)), dim3(256), 0, stream>>>(a);
@@ -1504,10 +1514,10 @@ static int launch_bwd_variant(const BwdArgs& a, dim3 grid, hipStream_t stream)
     const int bcfix = ((a.f.flags & F_B_FIXED) ? 1 : 0) | ((a.f.flags & F_C_FIXED) ? 2 : 0);
     if constexpr (!ZOH) {
         if (a.f.flags & F_COMPLEX) {
-            if (bcfix == 0) return launch_scan_bwd_complex<T, VEC, FULLN, 0>(a, grid, stream);
-            if (bcfix == 1) return launch_scan_bwd_complex<T, VEC, FULLN, 1>(a, grid, stream);
-            if (bcfix == 2) return launch_scan_bwd_complex<T, VEC, FULLN, 2>(a, grid, stream);
-            return launch_scan_bwd_complex<T, VEC, FULLN, 3>(a, grid, stream);
+            if (bcfix == 0) return launch_scan_bwd_complex<T, VEC, FULLN>(a, grid, stream);
+            if (bcfix == 1) return launch_scan_bwd_fixed<T, VEC, FULLN, false, 1, true>(a, grid, stream);
+            if (bcfix == 2) return launch_scan_bwd_fixed<T, VEC, FULLN, false, 2, true>(a, grid, stream);
+            return launch_scan_bwd_fixed<T, VEC, FULLN, false, 3, true>(a, grid, stream);
         }
     }
     if (bcfix == 1) return launch_scan_bwd_fixed<T, VEC, FULLN, ZOH, 1>(a, grid, stream);
