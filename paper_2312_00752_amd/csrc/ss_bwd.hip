@@ -219,6 +219,13 @@ __global__ void __launch_bounds__(THREADS, WGS) scan_bwd_kernel(const BwdArgs a)
     const int sd = s_ok ? d0 + lane : f.D - 1;
     const long srow = (long)b * f.D + sd;
     constexpr bool BFIX = BCFIX & 1, CFIX = BCFIX & 2;
+    // Whether the sums that only the end of the loop reads (dA, dB, dC) are held to their place in the sweeps.  Left alone
+    // they sink below them, which takes registers: the builds that are short of those, and the ones whose loads do not
+    // already break the sweep up, are faster with the pin (exact ZOH, fixed B, 8 x 4096 x 2048 bf16: 8155 -> 2346 us
+    // backward; float32, fixed C, 2 x 4096 x 2048: 675 -> 565).  Off eight steps, where every load of a row is a branch,
+    // it costs instead wherever registers are left (one workgroup per unit, 4 x 4096 x 2047, fixed C, bf16: 2186 -> 2224 us;
+    // float32 1254 -> 1328; bf16, fixed B and C, 889 -> 923; complex, two per unit, 8 x 4096: 4369 -> 4408).
+    constexpr bool PINNED = VEC || ZOH || (BCFIX != 0 ? WGS == 2 : sizeof(T) == 4);
     float A2[STATES_PER_LANE], An[STATES_PER_LANE], invA[STATES_PER_LANE], ag[STATES_PER_LANE], dA[STATES_PER_LANE];
     float Bf[STATES_PER_LANE], Cf[STATES_PER_LANE], dBf[STATES_PER_LANE], dCf[STATES_PER_LANE];
     const T* __restrict__ gB[STATES_PER_LANE];
@@ -384,7 +391,7 @@ __global__ void __launch_bounds__(THREADS, WGS) scan_bwd_kernel(const BwdArgs a)
                     if (g > 0) reduce_take(red, dbc + STATES_PER_LANE * BT + tl - GROUP_T, lane);  // previous group
                     reduce_put(dCv, red, lane);
                 }
-                if (CFIX) asm volatile("" : "+v"(dCf[0]), "+v"(dCf[1]), "+v"(dCf[2]), "+v"(dCf[3]));
+                if constexpr (CFIX && PINNED) asm volatile("" : "+v"(dCf[0]), "+v"(dCf[1]), "+v"(dCf[2]), "+v"(dCf[3]));
             }
             if (!CFIX) reduce_take(red, dbc + STATES_PER_LANE * BT + (NG - 1) * GROUP_T, lane);
         }
@@ -462,8 +469,8 @@ __global__ void __launch_bounds__(THREADS, WGS) scan_bwd_kernel(const BwdArgs a)
                 reduce_put(dBv, red, lane);
             }
             // the sums that only the end of the loop reads are formed here, not below the sweep (see scan_bwd_dpp_kernel)
-            asm volatile("" : "+v"(dA[0]), "+v"(dA[1]), "+v"(dA[2]), "+v"(dA[3]));
-            if (BFIX) asm volatile("" : "+v"(dBf[0]), "+v"(dBf[1]), "+v"(dBf[2]), "+v"(dBf[3]));
+            if constexpr (PINNED) asm volatile("" : "+v"(dA[0]), "+v"(dA[1]), "+v"(dA[2]), "+v"(dA[3]));
+            if constexpr (BFIX && PINNED) asm volatile("" : "+v"(dBf[0]), "+v"(dBf[1]), "+v"(dBf[2]), "+v"(dBf[3]));
         }
         if (!BFIX) reduce_take(red, dbc, lane);
         // ---- flush this wave's dB/dC of the block to global memory -------------------------
@@ -1430,18 +1437,21 @@ constexpr unsigned COMPUTE_UNITS = 256;
 // nothing from a kernel that leaves room for two and pays for its 256 registers.  Variants for which that costs
 // something are built both ways; backward call, us, two per unit / one per unit:
 //   workgroups                                 256           512
-//   B, real, f32, 2048 steps                   563 / 563     1009 / 1134   (bf16 567 / 567, 835 / 1128)
-//   B, complex, f32, 2048 steps                772 / 672     1030 / 1349
-//   C, real, f32, 2047 steps                   1418 / 1327   1901 / 2589
-//   C, complex, f32, 2047 steps                1590 / 1403   2104 / 2768
-//   C, real, f32, 2048 steps                   597 / 602     1014 / 1016   (built for two only)
-//   B and C, real, bf16, 2047 steps            923 / 926     1300 / 1298   (built for two only)
-template <bool VEC, int BCFIX, bool CPLX>
-constexpr bool ONE_WG_WINS = BCFIX == 1 || (BCFIX == 2 && (CPLX || !VEC));
+//   B, real, bf16, 2048 steps                  645 / 568     828 / 1131
+//   B, complex, f32, 2048 steps                773 / 670     1006 / 1359
+//   C, real, f32, 2047 steps                   1425 / 1262   1926 / 2456
+//   C, complex, f32, 2047 steps                1602 / 1344   2083 / 2617
+//   B and C, real, bf16, 2047 steps            898 / 864     1324 / 1739
+//   C, real, f32, 2048 steps                   596 / 601     1007 / 1009   (built for two only)
+//   B and C, real, f32, 2047 steps             882 / 938     1478 / 1668   (built for two only)
+//   B and C, complex, bf16, 2047 steps         1008 / 1009   1494 / 2025   (built for two only)
+// (The one-workgroup builds off eight steps are without the pin described in scan_bwd_kernel.)
+template <typename T, bool VEC, int BCFIX, bool CPLX>
+constexpr bool ONE_WG_WINS = BCFIX == 1 || (BCFIX == 2 && (CPLX || !VEC)) || (BCFIX == 3 && !CPLX && !VEC && sizeof(T) == 2);
 template <typename T, bool VEC, bool FULLN, bool ZOH, int BCFIX, bool CPLX = false, int WGS = ZOH ? 1 : 2>
 static int launch_scan_bwd_fixed(const BwdArgs& a, dim3 grid, hipStream_t stream)
 {
-    if constexpr (WGS == 2 && ONE_WG_WINS<VEC, BCFIX, CPLX>)
+    if constexpr (WGS == 2 && ONE_WG_WINS<T, VEC, BCFIX, CPLX>)
         if (grid.x <= COMPUTE_UNITS) return launch_scan_bwd_fixed<T, VEC, FULLN, ZOH, BCFIX, CPLX, 1>(a, grid, stream);
     auto kern = scan_bwd_kernel<T, VEC, FULLN, ZOH, BCFIX, CPLX, WGS>;
     static std::atomic<bool> lds_ok[MAX_DEVICES];   // this launcher is instantiated once per kernel
