@@ -98,10 +98,11 @@ size_t ss_layer_step_scratch_bytes(const ss_layer_step_params *p);
 
 /* One token of the layer in recurrent mode (Section 2): the conv window slides by one sample,
  * the projections become (B, D) x (D, R+2N) and (B, R) x (R, D) products, and Eq. 2a/2b are
- * applied once; constant time and memory per token.  Calls with D >= 8, 8 <= R <= 256, N <= 16
- * and a 16-byte aligned h take three launches (both projections on the matrix cores, delta_t
- * formed inside the state update); other calls form the two products with the general
- * projection kernel first.  Deterministic either way. */
+ * applied once; constant time and memory per token.  Calls with D >= 8, 8 <= R <= 256 and N <= 16
+ * take three launches (both projections on the matrix cores, delta_t formed inside the state
+ * update); other calls form the two products with the general projection kernel first.
+ * Deterministic either way.  h, W_x and W_dt are 16-byte aligned; a call that is refused has
+ * touched neither h nor conv_state. */
 int ss_layer_step(const ss_layer_step_params *p, void *stream);
 
 /* The products behind the layer's projections (Algorithm 2: the linear maps s_B, s_C of

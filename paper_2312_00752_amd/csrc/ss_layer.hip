@@ -510,12 +510,15 @@ int ss_layer_step(const ss_layer_step_params* p, void* stream)
     if (!p->h || !p->x_t || !p->z_t || !p->conv_w || !p->conv_b || !p->W_x || !p->W_dt || !p->dt_bias || !p->A ||
         !p->Dskip || !p->out_t || (p->conv_width > 1 && !p->conv_state))
         return SS_ERR_NULL;
-    if (!aligned_to(p->W_x, 16) || !aligned_to(p->W_dt, 16)) return SS_ERR_ALIGN;
+    const bool bf16 = p->io_dtype == SS_BF16;
+    const size_t esz = bf16 ? 2 : 4;
+    // all that any of the launches would refuse: the first one already slides conv_state
+    if (!aligned_to(p->W_x, 16) || !aligned_to(p->W_dt, 16) || !aligned_to(p->h, 16)) return SS_ERR_ALIGN;
+    if (!aligned_to(p->z_t, esz) || !aligned_to(p->out_t, esz)) return SS_ERR_ALIGN;
+    if (!aligned_to(p->dt_bias, 4) || !aligned_to(p->A, 4) || !aligned_to(p->Dskip, 4)) return SS_ERR_ALIGN;
     if (!p->scratch || p->scratch_bytes < ss_layer_step_scratch_bytes(p)) return SS_ERR_WORKSPACE;
     if (!aligned_to(p->scratch, 256)) return SS_ERR_ALIGN;
     hipStream_t st = static_cast<hipStream_t>(stream);
-    const bool bf16 = p->io_dtype == SS_BF16;
-    const size_t esz = bf16 ? 2 : 4;
     const int B = p->batch, D = p->dim, N = p->dstate, R = p->dt_rank, Mx = R + 2 * N;
     char* scratch = static_cast<char*>(p->scratch);
     char* u_t = scratch;
@@ -536,7 +539,7 @@ int ss_layer_step(const ss_layer_step_params* p, void* stream)
     s.out_t = p->out_t;
 
     // both projections on the matrix cores, delta_t = W_dt r_t inside the state-update kernel: three launches, no atomics
-    if (D >= 8 && R >= 8 && R <= 256 && N <= 16 && aligned_to(p->h, 16)) {
+    if (D >= 8 && R >= 8 && R <= 256 && N <= 16) {
         int rc = ss_conv_step(&c, stream);
         if (rc != SS_OK) return rc;
         rc = bf16 ? launch_xproj_decode<ss::bf16_t>(u_t, p->W_x, P_acc, B, Mx, D, st)

@@ -268,6 +268,21 @@ def test_layer_struct_layout_sizes_and_rejections():
     assert B.ss_strerror(B.SS_ERR_BACKEND) not in ("", "unknown error code")
 
 
+@pytest.mark.parametrize("dim,rank", [(64, 8), (64, 6)])   # the three-launch path and the general products
+def test_layer_step_refuses_before_its_first_launch(dim, rank):
+    """The first launch slides conv_state, so a pointer that a later one refuses must be refused up front."""
+    def step(**bad):
+        p = B.LayerStepParams()
+        p.batch, p.dim, p.dstate, p.dt_rank, p.conv_width, p.io_dtype = 2, dim, 16, rank, 4, B.SS_BF16
+        for f in ("h", "conv_state", "x_t", "z_t", "conv_w", "conv_b", "W_x", "W_dt", "dt_bias", "A", "Dskip", "out_t", "scratch"):
+            setattr(p, f, FAKE + bad.get(f, 0))
+        p.scratch_bytes = B.lib().ss_layer_step_scratch_bytes(ctypes.byref(p))
+        return B.lib().ss_layer_step(ctypes.byref(p), None)
+    for f, off in (("h", 4), ("h", 8), ("z_t", 1), ("out_t", 1), ("A", 2), ("Dskip", 2), ("dt_bias", 2), ("conv_w", 2),
+                   ("x_t", 1), ("conv_state", 1), ("W_x", 8), ("W_dt", 8)):
+        assert step(**{f: off}) == B.SS_ERR_ALIGN, f
+
+
 def test_time_invariant_bc_flags():
     # partial sums for the (D,N) gradients are added to the workspace, and the sequence is never split
     base = B.ss_workspace_bytes(1, 256, 1 << 16, 16, True, B.SS_F32, True)

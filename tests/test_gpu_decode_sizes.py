@@ -18,3 +18,21 @@ pytestmark = pytest.mark.gpu
     ("f32", (2, 14, 40, 3, 7)), ("bf16", (2, 14, 7, 16, 12)), ("bf16", (2, 14, 20, 16, 264))])
 def test_decode_sizes(io, shape):
     layer.test_layer_prompt_then_token_by_token(io, shape)
+
+
+@pytest.mark.parametrize("rank", [8, 6])
+def test_refused_step_leaves_the_states_alone(rank):
+    import torch
+    from paper_2312_00752_amd import binding as B
+    nb, nd, nn, bf = 3, 64, 16, torch.bfloat16
+    r = lambda *s, dtype=torch.float32: torch.randn(s, device="cuda").to(dtype)
+    h = r(nb * nd * nn + 1)[1:].view(nb, nd, nn)   # four bytes off
+    conv_state = r(nb, nd, 3, dtype=bf)
+    keep_h, keep_conv = h.clone(), conv_state.clone()
+    scratch = torch.empty(B.ss_layer_step_scratch_bytes(nb, nd, nn, rank, B.SS_BF16), dtype=torch.uint8, device="cuda")
+    with pytest.raises(B.SsError) as e:
+        B.ss_layer_step(h, conv_state, r(nb, nd, dtype=bf), r(nb, nd, dtype=bf), r(nd, 4), r(nd), r(rank + 2 * nn, nd, dtype=bf),
+                        r(nd, rank, dtype=bf), r(nd), -r(nd, nn).abs(), r(nd), scratch)
+    torch.cuda.synchronize()
+    assert e.value.code == B.SS_ERR_ALIGN
+    assert torch.equal(h, keep_h) and torch.equal(conv_state, keep_conv)
