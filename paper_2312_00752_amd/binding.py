@@ -9,7 +9,19 @@ import ctypes
 import math
 import os
 
-import torch
+
+class _TorchOnFirstUse:
+    """Stands for torch until a call on tensors needs it: the library's size queries, its C structs and its error
+    strings are usable where torch is not installed, and importing this module does not wait for it.  The first
+    attribute puts the module itself in this name's place, so a call pays no import statement per function."""
+
+    def __getattr__(self, name):
+        global torch
+        import torch
+        return getattr(torch, name)
+
+
+torch = _TorchOnFirstUse()
 
 _PKG = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_PKG, "libss_scan.so")
@@ -221,16 +233,23 @@ def empty_channel_skewed(n, shape, dtype, device):
     return [pool.as_strided(shape, strides, i * pitch) for i in range(n)]
 
 
-# the current stream's handle without building a torch.cuda.Stream around it (2 us of every call)
-_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
-_device_index = getattr(torch._C, "_cuda_getDevice", None)
+# the current stream's handle without building a torch.cuda.Stream around it (2 us of every call); looked up on first use
+_raw_stream = _device_index = None
+
+
+def _find_raw_stream():
+    global _raw_stream, _device_index
+    _device_index = getattr(torch._C, "_cuda_getDevice", lambda: 0)
+    _raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None) if hasattr(torch._C, "_cuda_getDevice") else None
+    if _raw_stream is None:
+        _raw_stream = lambda _: torch.cuda.current_stream().cuda_stream
 
 
 def _stream(stream):
     if stream is None:
-        if _raw_stream is not None and _device_index is not None:
-            return _raw_stream(_device_index())
-        return torch.cuda.current_stream().cuda_stream
+        if _raw_stream is None:
+            _find_raw_stream()
+        return _raw_stream(_device_index())
     if isinstance(stream, int):
         return stream
     return stream.cuda_stream

@@ -3,6 +3,8 @@ and rejects bad arguments on the host before any device call."""
 import ctypes
 import os
 import re
+import subprocess
+import sys
 
 import pytest
 
@@ -29,6 +31,14 @@ def test_library_exports_every_declared_symbol():
     assert B.ss_strerror(0) == "success"
     for code in range(-7, 0):
         assert B.ss_strerror(code) not in ("", "success", "unknown error code")
+
+
+def test_binding_needs_no_torch_until_it_gets_tensors():
+    code = ("import sys; sys.modules['torch'] = None; from paper_2312_00752_amd import binding as B; "
+            "print(B.ss_version(), B.ss_workspace_bytes(2, 64, 128, 16), B.ss_strerror(B.SS_ERR_ALIGN))")
+    r = subprocess.run([sys.executable, "-c", code], cwd=ROOT, capture_output=True, text=True)
+    assert r.returncode == 0, r.stderr
+    assert r.stdout.split()[:2] == [str(B.ss_version()), str(B.ss_workspace_bytes(2, 64, 128, 16))]
 
 
 def test_struct_layout_matches_header():
