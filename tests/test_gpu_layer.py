@@ -89,9 +89,6 @@ def test_layer_full_size_bf16():
     _check(make_layer_inputs(8, 2048, 4096, 16, "bf16", seed=2))
 
 
-# bf16 shapes with D % 32 == 0 and R % 8 == 0 take the hand-written matrix-core decode path (ragged
-# batch tiles of 8 and of 16, ragged 64-channel groups, N below 16, R off and at the limits of the 32-wide
-# contraction steps); the others take the library GEMMs
 @pytest.mark.parametrize("dstate", [1, 4, 8, 9])
 def test_layer_few_states_on_an_unsplit_sequence(dstate):
     """Up to eight states run on kernels that read delta from memory: the layer must have written it."""
@@ -101,6 +98,19 @@ def test_layer_few_states_on_an_unsplit_sequence(dstate):
     assert_close(out, ref["out"], "bf16", "out", exact_inputs=False)
 
 
+# an unsplit sequence off eight steps: the scan forms delta itself, from more than 128 ranks in eight contraction steps
+@pytest.mark.parametrize("shape", [(5, 73, 320, 16, 160), (2, 127, 200, 12, 256), (3, 97, 130, 9, 136), (1, 9, 64, 16, 248)])
+def test_layer_many_ranks_on_an_unsplit_odd_length(shape):
+    batch, seqlen, dim, dstate, rank = shape
+    w = make_layer_inputs(batch, seqlen, dim, dstate, "bf16", seed=rank, rank=rank)
+    out, _ = _gpu(w, backward=False)
+    ref = inn.inner_fwd(rnd=_rnd("bf16"), nthreads=0, **{k: w[k] for k in PARAMS})
+    assert_close(out, ref["out"], "bf16", "out", exact_inputs=False)
+
+
+# D >= 8, 8 <= R <= 256 and N <= 16 take the decode path on the matrix cores, in either io type (ragged batch
+# tiles of 8 and of 16, ragged 64-channel groups, N below 16, R off and at the limits of the contraction steps);
+# the others form the two products with the general kernel
 @pytest.mark.parametrize("io,shape", [("bf16", (4, 96, 256, 16, 8)), ("f32", (2, 40, 72, 5, 3)), ("bf16", (1, 33, 128, 16, 6)),
                                       ("bf16", (21, 40, 96, 8, 40)), ("bf16", (1, 20, 64, 16, 256)),
                                       ("bf16", (17, 24, 160, 12, 24)), ("bf16", (3, 20, 32, 16, 16)),

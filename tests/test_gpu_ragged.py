@@ -68,6 +68,27 @@ def test_ragged_rows(io, batch, seqlen, dim, dstate, zoh):
         assert bool((pool[:PAD] == PATTERN).all()) and bool((pool[PAD + view.numel():] == PATTERN).all()), k
 
 
+def _segments(batch, seqlen, dim, dstate):
+    """How many segments a call is split into, from the size of its scratch: per segment 17 floats a row, and
+    B and C once in whole 32-step chunks (each block rounded up to 256 bytes)."""
+    from paper_2312_00752_amd import binding as B
+    up = lambda n: (n + 255) // 256 * 256
+    rows = batch * dim
+    bc = up(batch * ((dstate + 15) // 16 * 16) * ((seqlen + 31) // 32 * 32) * 2 * 4)
+    left = B.ss_workspace_bytes(batch, dim, seqlen, dstate, for_backward=False, io_dtype=B.SS_F32, has_z=False) - bc
+    return next(n for n in range(1, 4097) if left == (n > 1) * (up(n * rows * 64) + up(n * rows * 4)))
+
+
+@pytest.mark.parametrize("io", ["f32", "bf16"])
+@pytest.mark.parametrize("segments,batch,seqlen,dim,dstate,zoh", [
+    (2, 1, 193, 70, 16, False), (2, 1, 197, 40, 4, False), (3, 1, 257, 65, 16, True), (5, 1, 513, 40, 3, False),
+    (6, 2, 699, 33, 18, False), (9, 1, 1025, 70, 16, True), (16, 1, 1985, 70, 16, False), (16, 3, 1937, 130, 7, False)])
+def test_ragged_rows_in_few_segments(io, segments, batch, seqlen, dim, dstate, zoh):
+    """Up to sixteen segments every workgroup works its incoming state out itself: one, several and all fifteen aggregates."""
+    assert _segments(batch, seqlen, dim, dstate) == segments
+    test_ragged_rows(io, batch, seqlen, dim, dstate, zoh)
+
+
 @pytest.mark.parametrize("io", ["f32", "bf16"])
 @pytest.mark.parametrize("batch,dim,seqlen,width", [(2, 3, 9, 4), (1, 2, 11, 3), (3, 5, 15, 2), (1, 4, 509, 4), (2, 3, 517, 4),
                                                     (1, 2, 1021, 1)])
