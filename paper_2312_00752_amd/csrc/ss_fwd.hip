@@ -1263,8 +1263,8 @@ static void launch_fwd_dpp_t(const FwdArgs& a, hipStream_t stream)
     }
     if constexpr (sizeof(T) == 2 && !ZOH && SPL == STATES_PER_LANE) {
         if (a.W_dt) {   // the caller has checked: unsplit, R <= 256
-            if (a.Rp <= 128)
-                scan_fwd_kernel<T, true, false, false, ZOH, 0, false, false, 4, SPL, true, RAG><<<dim3((unsigned)(a.B * groups), 1u), block, 0, stream>>>(a);
+            if (!RAG && a.Rp <= 128)   // rows off whole slices come here for more than 192 ranks only
+                scan_fwd_kernel<T, true, false, false, ZOH, 0, false, false, 4, SPL, true, false><<<dim3((unsigned)(a.B * groups), 1u), block, 0, stream>>>(a);
             else
                 scan_fwd_kernel<T, true, false, false, ZOH, 0, false, false, 8, SPL, true, RAG><<<dim3((unsigned)(a.B * groups), 1u), block, 0, stream>>>(a);
             return;

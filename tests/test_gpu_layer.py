@@ -98,8 +98,8 @@ def test_layer_few_states_on_an_unsplit_sequence(dstate):
     assert_close(out, ref["out"], "bf16", "out", exact_inputs=False)
 
 
-# an unsplit sequence off eight steps: the scan forms delta itself, from more than 128 ranks in eight contraction steps
-@pytest.mark.parametrize("shape", [(5, 73, 320, 16, 160), (2, 127, 200, 12, 256), (3, 97, 130, 9, 136), (1, 9, 64, 16, 248)])
+# an unsplit sequence off eight steps: a product forms delta up to 192 ranks, the scan itself beyond
+@pytest.mark.parametrize("shape", [(5, 73, 320, 16, 160), (2, 127, 200, 12, 256), (3, 97, 130, 9, 192), (3, 97, 130, 9, 200), (1, 9, 64, 16, 248)])
 def test_layer_many_ranks_on_an_unsplit_odd_length(shape):
     batch, seqlen, dim, dstate, rank = shape
     w = make_layer_inputs(batch, seqlen, dim, dstate, "bf16", seed=rank, rank=rank)
