@@ -101,14 +101,16 @@ SegPlan plan_segments(int B, int D, int L, uint32_t flags)
 //                  [float dA partials nseg*B*D*16][float dD partials nseg*B*D][float dbias partials nseg*B*D]
 //                  [float dB partials B*D*16][float dC partials B*D*16]    (only for a time-invariant B / C)
 //   both end with: [io staged B and C, B * ceil16(slots) * Lp * 2]    (only for a real state with selective B and C)
-// where Lp is L rounded up to a whole 32-step chunk.
+// where Lp is L rounded up to a whole 32-step chunk.  The staged copy is written and read by the kernels for fewer than
+// 8 or at least 2^23 steps only (FwdArgs::dpp_ok false); the size of a workspace does not depend on that, so that a
+// caller's allocations do not change with the path.
 struct WsLayout {
     size_t ckpt_off, ckpt_group, y_off, segh_off, segdt_off, segg_off, dA_off, dD_off, db_off, dBf_off, dCf_off;
     size_t bcs_off, total;
     int Lp;
     SegPlan plan;
 };
-// The forward kernels read a real state's selective B and C from a repacked copy.
+// Whether the call has operands that can be repacked: a real state's selective B and C.
 inline bool stageable(const ss_fwd_params* p)
 {
     return !(p->flags & (SS_B_FIXED | SS_C_FIXED | SS_COMPLEX_STATE)) && p->seqlen > 0;

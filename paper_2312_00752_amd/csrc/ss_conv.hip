@@ -158,8 +158,9 @@ __device__ __forceinline__ float conv_at(const float (&k4)[TAPS], float bias, co
 
 // ---- forward --------------------------------------------------------------------------------
 // One wave per (row, piece); grid = ceil(B*D*pieces / NWAVES) workgroups.
-// Bound by HBM.  ROWS_ANY at 8 x 1536 x 2047 bf16: 60 -> 24 us (2048 steps: 21); its backward kernel, which has
-// five misaligned accesses to the forward's three, 105 -> 55 us (2048 steps: 34).
+// Bound by HBM.  ROWS_ANY at 8 x 1536 x 2047 bf16: 60 -> 24 us (2048 steps: 21); its backward kernel 105 -> 55 us
+// (2048 steps: 34): eight misaligned accesses per unit, three of them one-element reads of an initial state that most
+// calls do not have, and in bf16 part of the window goes through 6 KB of LDS, because window_raw is passed by value.
 template <typename T, int KIND, bool SILU>
 __global__ __launch_bounds__(THREADS) void conv_fwd_kernel(const ConvArgs a)
 {

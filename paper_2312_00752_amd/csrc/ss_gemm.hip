@@ -557,9 +557,13 @@ __global__ void __launch_bounds__(256, 2) gemm_rows_kernel(const bf16_t* __restr
         }
 }
 
-// The same product for operands of whole pieces (K % 64 == 0, N % 64 == 0, S <= 16 NST), the weights through LDS too:
-// 8 x 4096 x 2048, S = 160 and 128: 59 and 54 us against 73 and 60 with fragments from the L2, which is the faster
-// form at 8 x 1536 x 2047 (23 and 19 against 25 and 23 us) and at 4 x 4096 x 1531 (43 and 35 against 50 and 47).
+// The same product for operands of whole pieces (K % 64 == 0, N % 64 == 0, S <= 16 NST), the weights through LDS too.
+// Against fragments from the L2 that is the faster form for a large X, us, this kernel / gemm_rows_kernel:
+//   8 x 4096 x 2048, S = 160: 58 / 74, S = 128: 52 / 61      2 x 5120 x 16384, S = 192: 119 / 150, S = 160: 103 / 138
+//   32 x 2048 x 2048, S = 96: 77 / 89, S = 64: 69 / 71
+// and the slower one by 4 to 25 % for a smaller one (both forms would be needed for that line):
+//   8 x 1536 x 2048, S = 80: 18.9 / 18.0      8 x 3072 x 2048, S = 128: 48 / 36      4 x 2560 x 4096, S = 112: 38 / 29
+//   2 x 5120 x 4096, S = 192: 54 / 49         4 x 4096 x 1536, S = 128: 36 / 28      1 x 4096 x 2048, S = 160: 20.8 / 21.1
 // grid (N / 64, batch, parts).
 template <int NST>
 __global__ void __launch_bounds__(256, 2) gemm_rows_lds_kernel(const bf16_t* __restrict__ W, long w_ld, long w_batch,
@@ -868,7 +872,7 @@ int launch_fast(const GemmArgs& g, hipStream_t stream)
     const bool whole = al16(g.A) && al16(g.B) && al16(g.C) && mult8(g.a_batch) && mult8(g.b_batch);   // operands made of aligned 16-byte pieces
     if (g.a_k == 1 && g.b_k == 1 && g.c_float && !g.accumulate) {
         // C = A B^T: the operand with more rows is split over workgroups and waves, the other one, up to SMAX rows at a time,
-        // goes through LDS
+        // is read straight from the L2
         float* C = static_cast<float*>(g.C);
         const bool out_t = g.M < g.N;
         const int big = out_t ? g.N : g.M, small = out_t ? g.M : g.N;

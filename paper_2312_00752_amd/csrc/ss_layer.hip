@@ -78,7 +78,7 @@ __global__ void sum_partials_kernel(const T* __restrict__ part, int nb, long n, 
 // contraction index and spreads that part over its eight waves (four steps' loads in flight per wave); the waves'
 // accumulators are added through LDS in a fixed order and written to the z-th partial result, P + z * nb * nm.
 // The consumer adds the few partial results, again in a fixed order, so the outcome does not depend on timing
-// (atomics across workgroups would make it so).  RAG: D is not a whole number of steps or W's rows are not aligned.
+// (atomics across workgroups would make it so).  RAG: D is not a whole number of steps.
 constexpr int XP_WAVES = 8;
 constexpr int XP_NPARTS = ss::STEP_NPARTS;   // partial results (fixed, so that the consumer can unroll over them)
 
@@ -238,7 +238,8 @@ SavedLayout saved_layout(const ss_layer_params* p)
 //          backward [u][delta][du][ddelta][dP (B,Mx,L) io][dB, dC (B,N,L) f32]
 //                   [partials of dW_dt (B,D,R) f32][partials of dW_x (B,Mx,D) f32]
 //                   [W_dt transposed (R,D) io][W_x transposed (D,Mx) io]
-//          both     [float32 shares of a projection whose contraction is split across workgroups (B,Mx,L) x 2]
+//          both     [float32 shares of a projection whose contraction is split across workgroups: two of (B,Mx,L), or up to
+//                    eight of the largest small product]
 struct ScratchLayout { size_t u, delta, P, scan_ws, scan_ws_bytes, rT, du, ddelta, dP, dB, dC, part_dt, part_x, WdtT, WxT, gsplit, gsplit_bytes, total; };
 ScratchLayout scratch_layout(const ss_layer_params* p, bool bwd)
 {
