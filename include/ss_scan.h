@@ -116,17 +116,17 @@ typedef struct {
  * ss_scan_fwd, 1 for ss_scan_fwd with SS_SAVE_FOR_BWD and the ss_scan_bwd that follows
  * it.  Read: batch, dim, seqlen, dstate, io_dtype and the flags SS_HAS_Z, SS_B_FIXED,
  * SS_C_FIXED and SS_COMPLEX_STATE (they change the number of state slots, add partial-sum
- * blocks for a time-invariant operand's gradient, and decide whether B and C are repacked and
- * the sequence split), so pass the flags of the call the workspace is for.  The
+ * blocks for a time-invariant operand's gradient, and decide whether there is room for a
+ * repacked B and C and the sequence is split), so pass the flags of the call the workspace is for.  The
  * content is opaque (state checkpoints every SS_CHECKPOINT_STEPS steps, the pre-gate
  * output when there is a gate, per-segment carries when a long sequence with few rows is
  * split across workgroups, and partial sums of the backward pass); a forward call with
  * SS_SAVE_FOR_BWD fills it and the matching backward call must get the same, untouched
  * buffer.  256-byte alignment is required.  Returns 0 when none is needed.
  * A plain forward call (for_backward == 0) never requires a workspace: the size returned
- * for it is scratch that, if lent, lets the library read B and C from a repacked copy
- * (selective B and C, real state) and split a long sequence with few rows across
- * workgroups; without it the call is correct but slower and runs one workgroup per 64
+ * for it is scratch that, if lent, lets the library split a long sequence with few rows across
+ * workgroups and, below 8 or from 2^23 steps on, read B and C from a repacked copy (selective
+ * B and C, real state); without it the call is correct but slower and runs one workgroup per 64
  * rows.  (More than 16 states with a gate are the exception: the pre-gate output is
  * accumulated in the workspace, which is then required.) */
 size_t ss_workspace_bytes(const ss_fwd_params *p, int for_backward);

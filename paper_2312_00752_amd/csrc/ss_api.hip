@@ -40,7 +40,10 @@ struct SegPlan {
 // each runs at about 3/4 of the speed it has alone (measured: 256 workgroups of 2048 steps
 // take 1.01 ms, 512 take 1.35 ms), so the chip takes workgroups in rounds of 512.  A workgroup's
 // set-up, pipeline fill and final stores cost about as much as 32 more steps (fitted to sweeps of
-// the segment count at 160 x 16384, 192 x 2048 and 4 x 2^20 workgroups x steps).
+// the segment count at 160 x 16384, 192 x 2048 and 4 x 2^20 workgroups x steps).  The fits are of the main passes and of
+// aggregate passes that ran two workgroups per unit as well.  The aggregate kernels have since come to run four; what
+// they take per step is now 0.35 (4 x 2^20), 0.40 (160 x 16384) and 0.44 (192 x 2048) of a main pass, and neither the
+// rounds nor the 0.36 below have been fitted again.
 double launch_cost(long n, long len)
 {
     const double pair = 1.0 / 0.75, fixed = 32.0;

@@ -31,13 +31,14 @@ typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));   // MFMA operand a
 // Algorithm 1 instead of the selective (B,N,L) tensor: it then sits in registers like A.
 // CPLX: the lane's four state slots are two complex states (re, im) each (Section 3.6); only
 // the recurrence and the read-out differ, everything around them sees 2N real "states".
-// STAGED: B and C come from the wave-packed copy a.bcs that stage_bc_kernel made: one scalar
+// STAGED (rows of fewer than 8 or at least 2^23 steps, with a workspace): B and C come from the
+// wave-packed copy a.bcs that stage_bc_kernel made: one scalar
 // load per group instead of eight, one address per wave instead of eight clamped ones, so the
 // scalar registers suffice for a whole group of prefetch and the scalar unit does little but
 // widen bf16.  (Read in place, the eight loads of the next group compete with the current
 // group's operands for scalar registers, some are issued only right before their use, and the
 // wait for those drains the whole prefetch: the loads' latency shows once per group.)
-// FUSED_KS > 0 (bf16, VEC, STAGED, main pass of an unsplit sequence): delta_raw = W_dt r is not
+// FUSED_KS > 0 (bf16, PAT, main pass of an unsplit sequence): delta_raw = W_dt r is not
 // read but formed here, per chunk, as a 64 x 32 product over R <= 32 * FUSED_KS on the matrix
 // cores: wave w owns rows 16w..16w+15 (its pieces of W_dt stay in registers for the whole
 // kernel) and both 16-step halves of the chunk; the result goes through the dt tile in LDS to

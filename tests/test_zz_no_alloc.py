@@ -2,7 +2,8 @@
 fixed array in the library's device image.  Two calls in a row, the second on a smaller problem, each
 checked against ss_scan_fwd with a caller-lent workspace (same kernels, so bit-identical) and against
 the oracle.  Shapes are chosen so that the scratch is really used: few rows and a long sequence are
-split into segments (segment states and step-size sums in the scratch), and B / C are repacked there."""
+split into segments (segment states and step-size sums in the scratch), and below eight steps B / C are repacked
+there."""
 import numpy as np
 import pytest
 import torch
@@ -44,6 +45,8 @@ def test_static_scratch_forward_twice_second_smaller():
     _run((1, 4096, 128, 16), "bf16", 41)   # 2 row groups x 4096 steps: split into segments
     _run((1, 1024, 64, 16), "bf16", 42)    # smaller, right after: stale scratch contents must not matter
     _run((2, 2048, 72, 5), "f32", 43)      # float32 I/O, ragged rows and states
+    _run((3, 7, 72, 13), "bf16", 44)       # too short for the LDS tile: B and C repacked
+    _run((2, 5, 33, 16), "f32", 45)
 
 
 def test_static_scratch_rejects_what_it_cannot_hold():
