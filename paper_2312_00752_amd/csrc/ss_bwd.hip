@@ -85,43 +85,73 @@ __device__ __forceinline__ void reduce_take(float (*red)[RED_PITCH], float* acc,
 }
 // The same sums without LDS, for kernels whose values come out of DPP arithmetic anyway: a tree over the
 // lanes that halves the number of registers at each level.  Level i takes two registers to one: lanes whose
-// selecting bit is clear keep the first one's pair sums, the others the second one's, at two instructions per
-// result (a lane swap and an add, or two adds whose DPP masks write one half each): 2.0 vector instructions per
-// value against 1.3 through the LDS tile above, but no LDS traffic, which was half of this kernel's, no wait for
-// it and four spilled registers fewer: backward of 8 x 4096 x 2048 bf16 0.74 -> 0.66 ms, forward + backward of
-// 8 x 1536 x 2048 606 -> 571 us, with the exact zero-order hold 1250 -> 1177 us.
+// selecting bit is clear keep the first one's pair sums, the others the second one's.  Two adds whose DPP masks write one
+// part of the lanes each cost two issue slots per result; a lane swap, which takes two slots itself, and an add cost
+// three; a quad exchange with its selects three.  So the masked adds stand at the levels with the most results (2.2 slots
+// per value in all; with the swaps first 2.8), and they go four results to a block of instructions, since a DPP read must stay two wait
+// states behind the write of its operand.  Backward and forward of 8 x 4096 x 2048 bf16 955 -> 932 us by both.  (Through the LDS
+// tile above: 1.3 instructions per value, but half of the kernel's LDS traffic, waits for it and four spilled registers: 1045 us.)
 //   level:          0               1               2             3                  4              5
-//   partner:        lane ^ 32       lane ^ 16       lane ^ 8      lane ^ 7           lane ^ 1       lane ^ 2
-//   selecting bit:  5               4               3             2                  0              1
+//   partner:        lane ^ 8        lane ^ 7        lane ^ 32     lane ^ 16          lane ^ 1       lane ^ 2
+//   selecting bit:  3               2               5             4                  0              1
 template <int LEVEL>
 __device__ __forceinline__ float merge_lanes(float a, float b, int lane)
 {
     if constexpr (LEVEL == 0) {
-        const auto x = __builtin_amdgcn_permlane32_swap(__float_as_uint(a), __float_as_uint(b), false, false);
-        return __uint_as_float(x[0]) + __uint_as_float(x[1]);
-    } else if constexpr (LEVEL == 1) {
-        const auto x = __builtin_amdgcn_permlane16_swap(__float_as_uint(a), __float_as_uint(b), false, false);
-        return __uint_as_float(x[0]) + __uint_as_float(x[1]);
-    } else if constexpr (LEVEL == 2) {
         float r;   // the leading wait states cover operands written just before (a DPP read needs two)
         asm("s_nop 1\n\t"
             "v_add_f32_dpp %0, %1, %1 row_ror:8 row_mask:0xf bank_mask:0x3\n\t"
             "v_add_f32_dpp %0, %2, %2 row_ror:8 row_mask:0xf bank_mask:0xc"
             : "=&v"(r) : "v"(a), "v"(b));
         return r;
-    } else if constexpr (LEVEL == 3) {
+    } else if constexpr (LEVEL == 1) {
         float r;
         asm("s_nop 1\n\t"
             "v_add_f32_dpp %0, %1, %1 row_half_mirror row_mask:0xf bank_mask:0x5\n\t"
             "v_add_f32_dpp %0, %2, %2 row_half_mirror row_mask:0xf bank_mask:0xa"
             : "=&v"(r) : "v"(a), "v"(b));
         return r;
+    } else if constexpr (LEVEL == 2) {
+        const auto x = __builtin_amdgcn_permlane32_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+        return __uint_as_float(x[0]) + __uint_as_float(x[1]);
+    } else if constexpr (LEVEL == 3) {
+        const auto x = __builtin_amdgcn_permlane16_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+        return __uint_as_float(x[0]) + __uint_as_float(x[1]);
     } else {
         const bool odd = (lane >> (LEVEL - 4)) & 1;
         const float keep = odd ? b : a, give = odd ? a : b;
         constexpr int ctrl = LEVEL == 4 ? 0xb1 : 0x4e;   // quad_perm [1,0,3,2], [2,3,0,1]
         return keep + __uint_as_float(__builtin_amdgcn_update_dpp(0, __float_as_uint(give), ctrl, 0xf, 0xf, true));
     }
+}
+// Levels 0 and 1 of four pairs at once: one wait for all of them.
+template <int LEVEL>
+__device__ __forceinline__ void merge_four(float (&r)[4], const float (&v)[8])
+{
+    if constexpr (LEVEL == 0)
+        asm("s_nop 1\n\t"
+            "v_add_f32_dpp %0, %4, %4 row_ror:8 row_mask:0xf bank_mask:0x3\n\t"
+            "v_add_f32_dpp %1, %6, %6 row_ror:8 row_mask:0xf bank_mask:0x3\n\t"
+            "v_add_f32_dpp %2, %8, %8 row_ror:8 row_mask:0xf bank_mask:0x3\n\t"
+            "v_add_f32_dpp %3, %10, %10 row_ror:8 row_mask:0xf bank_mask:0x3\n\t"
+            "v_add_f32_dpp %0, %5, %5 row_ror:8 row_mask:0xf bank_mask:0xc\n\t"
+            "v_add_f32_dpp %1, %7, %7 row_ror:8 row_mask:0xf bank_mask:0xc\n\t"
+            "v_add_f32_dpp %2, %9, %9 row_ror:8 row_mask:0xf bank_mask:0xc\n\t"
+            "v_add_f32_dpp %3, %11, %11 row_ror:8 row_mask:0xf bank_mask:0xc"
+            : "=&v"(r[0]), "=&v"(r[1]), "=&v"(r[2]), "=&v"(r[3])
+            : "v"(v[0]), "v"(v[1]), "v"(v[2]), "v"(v[3]), "v"(v[4]), "v"(v[5]), "v"(v[6]), "v"(v[7]));
+    else
+        asm("s_nop 1\n\t"
+            "v_add_f32_dpp %0, %4, %4 row_half_mirror row_mask:0xf bank_mask:0x5\n\t"
+            "v_add_f32_dpp %1, %6, %6 row_half_mirror row_mask:0xf bank_mask:0x5\n\t"
+            "v_add_f32_dpp %2, %8, %8 row_half_mirror row_mask:0xf bank_mask:0x5\n\t"
+            "v_add_f32_dpp %3, %10, %10 row_half_mirror row_mask:0xf bank_mask:0x5\n\t"
+            "v_add_f32_dpp %0, %5, %5 row_half_mirror row_mask:0xf bank_mask:0xa\n\t"
+            "v_add_f32_dpp %1, %7, %7 row_half_mirror row_mask:0xf bank_mask:0xa\n\t"
+            "v_add_f32_dpp %2, %9, %9 row_half_mirror row_mask:0xf bank_mask:0xa\n\t"
+            "v_add_f32_dpp %3, %11, %11 row_half_mirror row_mask:0xf bank_mask:0xa"
+            : "=&v"(r[0]), "=&v"(r[1]), "=&v"(r[2]), "=&v"(r[3])
+            : "v"(v[0]), "v"(v[1]), "v"(v[2]), "v"(v[3]), "v"(v[4]), "v"(v[5]), "v"(v[6]), "v"(v[7]));
 }
 // Sums over the 64 rows of a wave of the 16 * SPL values (index e = step * SPL + slot) that a block's steps
 // yield for one of dB, dC.  A group of four steps is merged to one register as soon as it is complete
@@ -131,15 +161,24 @@ template <int SPL>
 __device__ __forceinline__ float merge_group(const float (&v)[RED_VALUES], int lane)
 {
     auto at = [&](int e) { return v[(e / SPL) * STATES_PER_LANE + e % SPL]; };   // slot k of step j sits at 4 j + k
-    float a[2 * SPL];
+    if constexpr (SPL == 4) {
+        float a[8], b[4], x[4], y[4];
+        const float v0[8] = {v[0], v[1], v[2], v[3], v[4], v[5], v[6], v[7]};
+        const float v1[8] = {v[8], v[9], v[10], v[11], v[12], v[13], v[14], v[15]};
+        merge_four<0>(x, v0);
+        merge_four<0>(y, v1);
+        const float v2[8] = {x[0], x[1], x[2], x[3], y[0], y[1], y[2], y[3]};
+        merge_four<1>(b, v2);
+        return merge_lanes<3>(merge_lanes<2>(b[0], b[1], lane), merge_lanes<2>(b[2], b[3], lane), lane);
+    } else {
+        float a[2 * SPL], b[SPL];
 #pragma unroll
-    for (int i = 0; i < 2 * SPL; ++i) a[i] = merge_lanes<0>(at(2 * i), at(2 * i + 1), lane);
-    float b[SPL];
+        for (int i = 0; i < 2 * SPL; ++i) a[i] = merge_lanes<0>(at(2 * i), at(2 * i + 1), lane);
 #pragma unroll
-    for (int i = 0; i < SPL; ++i) b[i] = merge_lanes<1>(a[2 * i], a[2 * i + 1], lane);
-    if constexpr (SPL == 1) return b[0];
-    else if constexpr (SPL == 2) return merge_lanes<2>(b[0], b[1], lane);
-    else return merge_lanes<3>(merge_lanes<2>(b[0], b[1], lane), merge_lanes<2>(b[2], b[3], lane), lane);
+        for (int i = 0; i < SPL; ++i) b[i] = merge_lanes<1>(a[2 * i], a[2 * i + 1], lane);
+        if constexpr (SPL == 1) return b[0];
+        else return merge_lanes<2>(b[0], b[1], lane);
+    }
 }
 template <int SPL>
 __device__ __forceinline__ float merge_block(const float (&s)[BT / GROUP_T], int lane)
@@ -152,7 +191,7 @@ __device__ __forceinline__ float merge_block(const float (&s)[BT / GROUP_T], int
 }
 __device__ __forceinline__ int lane_value(int lane)
 {
-    return ((lane >> 5) & 1) | ((lane >> 3) & 2) | ((lane >> 1) & 4) | ((lane << 1) & 8) | ((lane << 4) & 48);
+    return ((lane >> 3) & 1) | ((lane >> 1) & 2) | ((lane >> 3) & 4) | ((lane >> 1) & 8) | ((lane << 4) & 48);
 }
 
 // Same decomposition as the forward kernel (64 rows x 4 waves; wave w owns states
@@ -560,7 +599,9 @@ __global__ void __launch_bounds__(THREADS, WGS) scan_bwd_kernel(const BwdArgs a)
 // widening of bf16 by the scalar unit, and the scalar-register spills with their v_readlane /
 // v_writelane traffic on the vector ALU.  The compiler folds such a broadcast into a multiply only
 // now and then and never into a multiply-add with an accumulator, so these instructions are written
-// out (input_step_dpp, adjoint_step_dpp).
+// out (input_step_dpp, adjoint_step_dpp); the recompute sweep forms its B dt u on the idle matrix cores instead
+// (input_step_mfma: forward + backward of 8 x 4096 x 2048 932 -> 928 us, of 8 x 1536 x 2047 977 -> 972 with its layer; the
+// same for C dy in the adjoint sweep, where the matrix instruction stands in the dependent chain, 948 -> 982).
 // All (B,D,L) tensors are addressed through per-workgroup buffer resources with ONE per-thread
 // offset (they share the layout), B and C through one resource per batch entry: no 64-bit pointer
 // registers, and an out-of-range offset switches a load (zeros) or a store off without a branch.
@@ -846,7 +887,7 @@ __global__ void __launch_bounds__(THREADS, 2) scan_bwd_dpp_kernel(const BwdArgs 
                 for (int j = 0; j < GROUP_T; ++j) {
                     const float dt = f4_get(dt4, j), du = f4_get(du4, j), dy = f4_get(dy4, j);
                     float bu[STATES_PER_LANE];
-                    input_step_dpp<SPL>(bu, f4_get(Bp, j), du);
+                    input_step_mfma<SPL>(bu, f4_get(Bp, j), du);
                     f32x4_t ab = {1.f, 1.f, 1.f, 1.f};
                     if constexpr (ZOH) ab = f32x4_t{0.f, 0.f, 0.f, 0.f};
 #pragma unroll

@@ -760,6 +760,23 @@ __device__ __forceinline__ void input_step_dpp(float (&bu)[STATES_PER_LANE], flo
             : "=&v"(bu[0]) : "v"(Bq), "v"(du));
 }
 
+// The same for four slots as one matrix instruction.  v_mfma_f32_4x4x1 is sixteen independent outer products, one per
+// group of four lanes: D[i][j] = A[i] x B[j] with A[i] in lane i, B[j] in lane j and D[i][j] in register i of lane j.
+// With A = Bq (slot i's operand in lane i) and B = du that is bu[k] = B_k du for every row, exact products as before, in
+// one issue slot instead of four and without the wait states of a DPP read.  The compiler must see what reads the result (it
+// knows the wait a matrix instruction needs): not for a value that inline assembly takes next.
+template <int SPL>
+__device__ __forceinline__ void input_step_mfma(float (&bu)[STATES_PER_LANE], float Bq, float du)
+{
+    if constexpr (SPL == 4) {
+        const f32x4_t x = __builtin_amdgcn_mfma_f32_4x4x1f32(Bq, du, f32x4_t{0.f, 0.f, 0.f, 0.f}, 0, 0, 0);
+#pragma unroll
+        for (int k = 0; k < 4; ++k) bu[k] = x[k];
+    } else {
+        input_step_dpp<SPL>(bu, Bq, du);
+    }
+}
+
 // One step of the adjoint recurrence for a lane's SPL states.  On entry g[k] = abar+ g+ of slot k;
 // Cq / Bq hold C / B of the wave's states in every group of four lanes (slot k in lane k).
 //     g[k] += C_k dy            (the gradient reaching h_t)          sb = sum_k B_k g[k]
