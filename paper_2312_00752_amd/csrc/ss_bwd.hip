@@ -1122,8 +1122,8 @@ __global__ void __launch_bounds__(THREADS) adjoint_agg_kernel(const BwdArgs a)
             if (has_z) io8<T>::unpack(rz, z8);
 #pragma unroll
             for (int j = 0; j < SLICE; ++j) {
-                float x = v8[j] + bias, sp, sg;
-                if (softplus) softplus_sigmoid(x, sp, sg); else sp = x;
+                float sp = v8[j] + bias;
+                if (softplus) sp = ss::softplus(sp);
                 dt8[j] = (j < nv) ? sp : 0.0f;
                 if (has_z) o8[j] *= z8[j] * sigmoid_fast(z8[j]);
             }
@@ -1288,9 +1288,8 @@ __global__ void __launch_bounds__(THREADS, 4) adjoint_agg_dpp_kernel(const BwdAr
             const float bias_eff = live ? bias : (softplus ? -1e30f : 0.0f);   // an empty slice runs with dt = 0
 #pragma unroll
             for (int j = 0; j < SLICE; ++j) {
-                const float x = v8[j] + bias_eff;
-                float sp, sg;
-                if (softplus) softplus_sigmoid(x, sp, sg); else sp = x;
+                float sp = v8[j] + bias_eff;
+                if (softplus) sp = ss::softplus(sp);
                 if constexpr (RAG) sp = j < nv ? sp : 0.0f;
                 dt8[j] = sp;
                 if (has_z) o8[j] *= z8[j] * sigmoid_fast(z8[j]);

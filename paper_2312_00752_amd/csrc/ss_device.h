@@ -76,6 +76,17 @@ __device__ __forceinline__ void softplus_sigmoid(float r, float& sp, float& sg)
     sp = (r > 20.0f) ? r : lp;
     sg = e * inv;                                  // e^r / (1 + e^r)
 }
+// softplus alone, where no derivative is asked for: max(r, 0) + log(1 + e) with e = e^-|r| <= 1.  w lies between 1 and 2, so
+// 1 / w in the correction c / w (|c| <= 2^-24) may be 1 - e / 2, off by less than a tenth: no reciprocal, no overflow to
+// cap and no case split.  Eleven instructions, two of them transcendental, against twelve with three; its error is that of
+// the form above below r = 0 and half of it above.
+__device__ __forceinline__ float softplus(float r)
+{
+    const float e = exp2_fast(fabsf(r) * -LOG2E);
+    const float w = 1.0f + e;
+    const float c = e - (w - 1.0f);
+    return fmaf(c, fmaf(e, -0.5f, 1.0f), log2_fast(w) * LN2) + fmaxf(r, 0.0f);
+}
 // Exact zero-order hold (Eq. 4): phi(dt, A) = (exp(dt A) - 1) / A multiplies B u in the
 // state update (dt itself where A == 0), and d phi / d A = (x e^x - (e^x - 1)) / A^2 with
 // x = dt A (dt^2 / 2 where A == 0).  Both differences cancel for small x, where the Taylor
@@ -853,6 +864,32 @@ __device__ __forceinline__ void readout_step_dpp(float& y, float Cq, const float
         asm("s_nop 1\n\t"
             "v_mul_f32_dpp %0, %1, %2" SS_QP(0)
             : "=&v"(y) : "v"(Cq), "v"(h[0]));
+}
+// The read-outs of a group of four steps together: y[j] = sum_k C_k(j) h[j][k], Cq the group's four steps.  One wait for
+// all of them, and four sums side by side instead of one dependent chain after another.
+__device__ __forceinline__ void readout_group_dpp(float (&y)[4], const float4& Cq, const float (&h)[4][STATES_PER_LANE])
+{
+    asm("s_nop 1\n\t"
+        "v_mul_f32_dpp %0, %4, %8" SS_QP(0) "\n\t"
+        "v_mul_f32_dpp %1, %5, %12" SS_QP(0) "\n\t"
+        "v_mul_f32_dpp %2, %6, %16" SS_QP(0) "\n\t"
+        "v_mul_f32_dpp %3, %7, %20" SS_QP(0) "\n\t"
+        "v_fmac_f32_dpp %0, %4, %9" SS_QP(1) "\n\t"
+        "v_fmac_f32_dpp %1, %5, %13" SS_QP(1) "\n\t"
+        "v_fmac_f32_dpp %2, %6, %17" SS_QP(1) "\n\t"
+        "v_fmac_f32_dpp %3, %7, %21" SS_QP(1) "\n\t"
+        "v_fmac_f32_dpp %0, %4, %10" SS_QP(2) "\n\t"
+        "v_fmac_f32_dpp %1, %5, %14" SS_QP(2) "\n\t"
+        "v_fmac_f32_dpp %2, %6, %18" SS_QP(2) "\n\t"
+        "v_fmac_f32_dpp %3, %7, %22" SS_QP(2) "\n\t"
+        "v_fmac_f32_dpp %0, %4, %11" SS_QP(3) "\n\t"
+        "v_fmac_f32_dpp %1, %5, %15" SS_QP(3) "\n\t"
+        "v_fmac_f32_dpp %2, %6, %19" SS_QP(3) "\n\t"
+        "v_fmac_f32_dpp %3, %7, %23" SS_QP(3)
+        : "=&v"(y[0]), "=&v"(y[1]), "=&v"(y[2]), "=&v"(y[3])
+        : "v"(Cq.x), "v"(Cq.y), "v"(Cq.z), "v"(Cq.w), "v"(h[0][0]), "v"(h[0][1]), "v"(h[0][2]), "v"(h[0][3]), "v"(h[1][0]),
+          "v"(h[1][1]), "v"(h[1][2]), "v"(h[1][3]), "v"(h[2][0]), "v"(h[2][1]), "v"(h[2][2]), "v"(h[2][3]), "v"(h[3][0]),
+          "v"(h[3][1]), "v"(h[3][2]), "v"(h[3][3]));
 }
 #undef SS_QP
 

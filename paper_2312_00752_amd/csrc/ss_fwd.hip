@@ -413,8 +413,8 @@ __global__ void __launch_bounds__(THREADS, PAT && AGG ? 4 : ((PAT && FUSED_KS <=
             const float bias_e = !ZERO_BY_BIAS || nv == SLICE ? bias : (softplus ? -1e30f : 0.0f);
 #pragma unroll
             for (int j = 0; j < SLICE; ++j) {
-                float x = v8[j] + bias_e, sp, sg;
-                if (softplus) softplus_sigmoid(x, sp, sg); else sp = x;
+                float sp = v8[j] + bias_e;
+                if (softplus) sp = ss::softplus(sp);
                 if constexpr (!ZERO_BY_BIAS) sp = (j < nv) ? sp : 0.0f;
                 dt8[j] = sp;
                 du8[j] = ZOH ? u8[j] : sp * u8[j];
@@ -504,6 +504,10 @@ __global__ void __launch_bounds__(THREADS, PAT && AGG ? 4 : ((PAT && FUSED_KS <=
         // pass, whose inputs take twice the registers, spills up to 20 otherwise (4 x 1536 x 2047, forward +
         // backward: 448 -> 422 us); the bf16 one does not, and gains nothing.
         constexpr bool LEAN = PAT && (AGG || sizeof(T) == 4);
+        // The read-outs of a group of steps together (readout_group_dpp) and B dt u from the matrix cores (input_step_mfma):
+        // forward 357 -> 345 us at 8 x 4096 x 2048 bf16; layer prefill 4 x 4096 x 1531 281 -> 269.  The kernel that
+        // forms delta itself has no registers for either (layer training 8 x 4096 x 2048: 1515 -> 1560 us).
+        constexpr bool GROUP_OUT = PAT && !AGG && SPL == 4 && FUSED_KS == 0;
         if constexpr (LEAN) {
             read_group(0);
         } else {
@@ -529,7 +533,7 @@ __global__ void __launch_bounds__(THREADS, PAT && AGG ? 4 : ((PAT && FUSED_KS <=
             }
             const float4 dt4 = dtc[g], du4 = duc[g];
             if (g > 0 && tl % CKPT_T == 0) save_ckpt((tc + tl) / CKPT_T);
-            float yp[GROUP_T];
+            float yp[GROUP_T], hq[GROUP_T][STATES_PER_LANE];
 #pragma unroll
             for (int j = 0; j < GROUP_T; ++j) {
                 const float dt = f4_get(dt4, j), du = f4_get(du4, j);
@@ -551,7 +555,8 @@ __global__ void __launch_bounds__(THREADS, PAT && AGG ? 4 : ((PAT && FUSED_KS <=
                     }
                 } else if constexpr (PAT) {
                     float bu[STATES_PER_LANE];
-                    input_step_dpp<SPL>(bu, f4_get(Bpc[g], j), du);
+                    if constexpr (FUSED_KS == 0) input_step_mfma<SPL>(bu, f4_get(Bpc[g], j), du);
+                    else input_step_dpp<SPL>(bu, f4_get(Bpc[g], j), du);
 #pragma unroll
                     for (int k = 0; k < SPL; ++k) {
                         const float x2 = dt * A2[k];
@@ -559,7 +564,11 @@ __global__ void __launch_bounds__(THREADS, PAT && AGG ? 4 : ((PAT && FUSED_KS <=
                         if (ZOH) bu[k] *= zoh_phi_fast(dt, x2, abar, invA[k]);
                         h[k] = fmaf(abar, h[k], bu[k]);                              // Eq. 2a
                     }
-                    if (!AGG) readout_step_dpp<SPL>(y, f4_get(Cpc[g], j), h);        // Eq. 2b
+                    if constexpr (!AGG && !GROUP_OUT) readout_step_dpp<SPL>(y, f4_get(Cpc[g], j), h);        // Eq. 2b
+                    if constexpr (GROUP_OUT) {
+#pragma unroll
+                        for (int k = 0; k < SPL; ++k) hq[j][k] = h[k];
+                    }
                 } else {
 #pragma unroll
                     for (int k = 0; k < SPL; ++k) {
@@ -583,6 +592,7 @@ __global__ void __launch_bounds__(THREADS, PAT && AGG ? 4 : ((PAT && FUSED_KS <=
                     }
                 }
             }
+            if constexpr (GROUP_OUT) readout_group_dpp(yp, Cpc[g], hq);              // Eq. 2b
             if (!AGG)
                 *reinterpret_cast<float4*>(&s_yp[w][lane][tl]) = make_float4(yp[0], yp[1], yp[2], yp[3]);
             if constexpr (PAT && AGG)   // the group ends here: left alone, half of the chunk's arithmetic sinks below the barriers
