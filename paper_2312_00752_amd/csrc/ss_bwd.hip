@@ -667,6 +667,8 @@ __global__ void __launch_bounds__(THREADS, 2) scan_bwd_dpp_kernel(const BwdArgs 
     const rsrc_t bu_ = wg_rsrc(f.u, true), bd_ = wg_rsrc(f.delta, true), bo_ = wg_rsrc(a.dout, true);
     const rsrc_t bz_ = wg_rsrc(f.z, has_z), by_ = wg_rsrc(f.ysave, has_z);
     const rsrc_t bdu_ = wg_rsrc(a.du, true), bdd_ = wg_rsrc(a.ddelta, true), bdz_ = wg_rsrc(a.dz, has_z && a.dz);
+    const uint32_t bc_bytes4 = (uint32_t)N * (uint32_t)L * 4u;
+    const rsrc_t bdB_ = make_rsrc(a.dB + (long)b * a.dbc_bstride, bc_bytes4), bdC_ = make_rsrc(a.dC + (long)b * a.dbc_bstride, bc_bytes4);
     // staging view: waves 0, 1 stage B, waves 2, 3 stage C; thread -> (state s_n, pair of steps s_tp) of the block
     const int s_which = w >> 1, s_n = (tid >> 3) & (NPAD - 1), s_tp = tid & 7;
     const rsrc_t bbc_ = make_rsrc(static_cast<const T*>(s_which ? f.Cm : f.Bm) + (long)b * f.bc_bstride,
@@ -714,6 +716,7 @@ __global__ void __launch_bounds__(THREADS, 2) scan_bwd_dpp_kernel(const BwdArgs 
     // the value of the cross-row sums this lane ends up with: slot vk at step vt of a block
     const int ve = lane_value(lane) & (BT * SPL - 1), vt = ve / SPL, vn = slot_state(w, ve % SPL, f.il);
     const bool v_ok = vn < N && (lane_value(lane) < BT * SPL);
+    const uint32_t v_off = ((uint32_t)vn * (uint32_t)L + (uint32_t)vt) * 4u;
     const int pat = slot_state(w, lane & 3, f.il) * GROUP_T;   // in a group's [state][step] tile: the state of slot lane % 4
 
     const int nblocks = blk_end;
@@ -723,126 +726,128 @@ __global__ void __launch_bounds__(THREADS, 2) scan_bwd_dpp_kernel(const BwdArgs 
     typename io4<T>::raw ru[LG], rd[LG], rz[LG], ro[LG], ry[LG];
     typedef typename std::conditional<sizeof(T) == 2, uint32_t, uint2>::type bcpair_t;   // two steps of B or C
     bcpair_t rbc[LG];
-    auto issue_group = [&](int grp) {
-#pragma unroll
-        for (int s = 0; s < LG; ++s) {
-            const int blk = grp * LG + s;
-            const int t0 = blk * BT + pq * BSL;
-            if constexpr (RAG) {
-                const uint32_t t = (uint32_t)row_piece(t0, BSL, L) * esz;
-                ru[s] = io4<T>::load_elem(ru_p, r_off + t);
-                rd[s] = io4<T>::load_elem(rd_p, r_off + t);
-                ro[s] = io4<T>::load_elem(ro_p, r_off + t);
-                rz[s] = io4<T>::load_elem(rz_p, has_z ? r_off + t : 0u);
-                ry[s] = io4<T>::load_elem(ry_p, has_z ? r_off + t : 0u);
-                const uint32_t tb = r_off_bc + (uint32_t)row_piece(blk * BT + 2 * s_tp, 2, L) * esz;
-                if constexpr (sizeof(T) == 2) {
-                    rbc[s] = load_any<uint32_t>(rbc_p, tb);
-                } else {
-                    const u32x2 x = load_any<u32x2>(rbc_p, tb);
-                    rbc[s] = make_uint2(x[0], x[1]);
-                }
-                continue;
+    // One block's inputs into the slot given at compile time; a block before the segment's start reads nothing (RAG: its first block again)
+    auto issue_block = [&](int blk, auto slot_tag) {
+        constexpr int s = decltype(slot_tag)::value;
+        if constexpr (RAG) {
+            const int bl = max(blk, blk_begin);
+            const uint32_t t = (uint32_t)row_piece(bl * BT + pq * BSL, BSL, L) * esz;
+            ru[s] = io4<T>::load_elem(ru_p, r_off + t);
+            rd[s] = io4<T>::load_elem(rd_p, r_off + t);
+            ro[s] = io4<T>::load_elem(ro_p, r_off + t);
+            rz[s] = io4<T>::load_elem(rz_p, has_z ? r_off + t : 0u);
+            ry[s] = io4<T>::load_elem(ry_p, has_z ? r_off + t : 0u);
+            const uint32_t tb = r_off_bc + (uint32_t)row_piece(bl * BT + 2 * s_tp, 2, L) * esz;
+            if constexpr (sizeof(T) == 2) {
+                rbc[s] = load_any<uint32_t>(rbc_p, tb);
+            } else {
+                const u32x2 x = load_any<u32x2>(rbc_p, tb);
+                rbc[s] = make_uint2(x[0], x[1]);
             }
+        } else {
             // slices are whole or empty; rows past D lie beyond the resource
-            const uint32_t off = t0 < L ? row_off + (uint32_t)t0 * (uint32_t)sizeof(T) : BUF_OFF;
+            const int t0 = blk * BT + pq * BSL, ts = blk * BT + 2 * s_tp;
+            const uint32_t off = t0 < L && blk >= blk_begin ? row_off + (uint32_t)t0 * esz : BUF_OFF;
             ru[s] = io4<T>::load_buf(bu_, off);
             rd[s] = io4<T>::load_buf(bd_, off);
             ro[s] = io4<T>::load_buf(bo_, off);
             rz[s] = io4<T>::load_buf(bz_, off);
             ry[s] = io4<T>::load_buf(by_, off);
-            const int ts = blk * BT + 2 * s_tp;
-            const uint32_t boff = ts < L ? bc_row_off + (uint32_t)ts * (uint32_t)sizeof(T) : BUF_OFF;
+            const uint32_t boff = ts < L && blk >= blk_begin ? bc_row_off + (uint32_t)ts * esz : BUF_OFF;
             if constexpr (sizeof(T) == 2) rbc[s] = (uint32_t)__builtin_amdgcn_raw_buffer_load_b32(bbc_, (int)boff, 0, 0);
             else rbc[s] = buf_load8(bbc_, boff);
         }
     };
-    issue_group((nblocks - 1) / LG);
     // Stores likewise: with bf16 a block is 32 bytes of a row, so the results of an odd block wait in
     // registers for the even block below it (segments start at even blocks) and the two pieces of
     // the 64-byte neighbourhood are written back to back.
     typename io4<T>::packed keep_du{}, keep_dl{}, keep_dz{};
     uint32_t keep_off = BUF_OFF;
-    bool keep_live = false;   // RAG: something waits
-    auto store_paired = [&](rsrc_t rs, uint32_t off, typename io4<T>::packed now, typename io4<T>::packed& keep, bool odd) {
-        if constexpr (LG == 2) {
-            if (odd) { keep = now; return; }
-            io4<T>::store_packed(rs, keep_off, keep);   // switched off when nothing waits
+    // A block's results at byte offset off (of the thread's slice; BUF_OFF: not stored), an odd block's with the even block's
+    // below it.  TAIL: the nv leading elements only, at once.
+    auto store_block = [&](rsrc_t rs, void* base, uint32_t off, int nv, typename io4<T>::packed now, typename io4<T>::packed& keep,
+                           bool odd, auto tail_tag) {
+        if constexpr (decltype(tail_tag)::value) {
+            if (base && nv > 0) io4<T>::store_elem(static_cast<T*>(base) + wg_first, off, now, nv);
+            return;
         }
-        io4<T>::store_packed(rs, off, now);
-    };
-    // RAG: the same at element alignment; off of the present block's slice, nv of its steps inside the row (0 for rows past D)
-    auto store_paired_rag = [&](void* base, long first, uint32_t off, int t0, int nv, typename io4<T>::packed now,
-                                typename io4<T>::packed& keep, bool odd) {
-        T* const p = static_cast<T*>(base) + first;
         if constexpr (LG == 2) {
-            if (odd) { keep = now; return; }
-            if (keep_live) io4<T>::store_elem(p, off + BT * esz, keep, p_ok ? min(max(L - (t0 + BT), 0), BSL) : 0);
+            io4<T>::store_packed(rs, odd ? BUF_OFF : keep_off, keep);   // keep_off: switched off when nothing waits
+            io4<T>::store_packed(rs, odd ? BUF_OFF : off, now);
+            keep = now;
+        } else {
+            io4<T>::store_packed(rs, off, now);
         }
-        io4<T>::store_elem(p, off, now, nv);
     };
-
+    // The state entering a block, left by the forward pass: requested a block ahead.
     auto load_ckpt = [&](int blk) {
-        return *(reinterpret_cast<const float4*>(f.ckpt + (((long)blk * f.B + b) * f.D + sd) * NPAD) + w);
+        const rsrc_t r = make_rsrc(f.ckpt + (((long)max(blk, 0) * f.B + b) * f.D + d0) * NPAD,
+                                   blk >= blk_begin ? (uint32_t)rows_here * NPAD * (uint32_t)sizeof(float) : 0u);
+        const uint4 x = buf_load16(r, (uint32_t)(lane * NPAD + w * STATES_PER_LANE) * (uint32_t)sizeof(float));
+        return make_float4(__uint_as_float(x.x), __uint_as_float(x.y), __uint_as_float(x.z), __uint_as_float(x.w));
     };
-    float4 hck_next = load_ckpt(nblocks - 1);
-    for (int blk = nblocks - 1; blk >= blk_begin; --blk) {
+    float4 hck_next;
+
+    // One block.  TAIL (RAG): the row's last block, which its end may cut.
+    // Memory operations retire in order and are waited for by how many younger ones may stay in flight, which the
+    // compiler has to take from the path with the fewest.  With the stores of an odd block, the atomics of lanes without a
+    // value and the last block's state request behind branches, every block began by draining the stores and atomics of the
+    // one before; they are issued always now, switched off by an out-of-range offset.  Forward + backward, us: float32 1 x 256 x 2^20
+    // 8950 -> 8670, exact zero-order hold 8 x 1536 x 2048 bf16 843 -> 826, 8 x 4096 x 2048 bf16 919 -> 908.  (The loop unrolled over
+    // the two slots instead: 940, its 24 KB of instructions are fetched too slowly.)
+    auto do_block = [&](const int blk, auto tail_tag) {
+        const bool odd = LG == 2 && (blk & 1);   // uniform; the slot of its inputs
+        constexpr bool TAIL = decltype(tail_tag)::value;
         const int tc = blk * BT;
         const int t0 = tc + pq * BSL;
         const bool live = p_ok && t0 < L;
-        const uint32_t off = t0 < L ? row_off + (uint32_t)t0 * (uint32_t)sizeof(T) : BUF_OFF;
+        const uint32_t off = RAG ? (p_ok ? row_off + (uint32_t)t0 * esz : BUF_OFF) : (t0 < L ? row_off + (uint32_t)t0 * esz : BUF_OFF);
         const int nv = p_ok ? min(max(L - t0, 0), BSL) : 0;   // RAG: steps of the slice inside the row
-        // the state entering this block was requested a block ago (see scan_bwd_kernel)
         const float4 hck4 = hck_next;
-        if (blk > blk_begin) hck_next = load_ckpt(blk - 1);
+        hck_next = load_ckpt(blk - 1);
 
         // ---- A: pointwise pre-processing ---------------------------------------------------
         float u4[BSL], sg4[BSL];  // u and d softplus(x)/dx, needed again in C
         {
-            float v4[BSL], o4[BSL], dt4[BSL], du4[BSL], dy4[BSL];
-            float z4[BSL], y4[BSL];
+            float v4[BSL], o4[BSL], dt4[BSL], du4[BSL], dy4[BSL], z4[BSL], y4[BSL];
             bcpair_t bcw{};
-            const int slot = blk & (LG - 1);  // uniform
-            if constexpr (RAG) {
-                if (tc + BT > L || rows_here < ROWS) {   // uniform
-                    const int sh = p_ok ? t0 - row_piece(t0, BSL, L) : BSL, ts = tc + 2 * s_tp;
-                    const int shb = ts - row_piece(ts, 2, L);
 #pragma unroll
-                    for (int s = 0; s < LG; ++s)
-                        if (slot == s) {
-                            io4<T>::drop(ru[s], sh); io4<T>::drop(rd[s], sh); io4<T>::drop(ro[s], sh);
-                            io4<T>::drop(rz[s], sh); io4<T>::drop(ry[s], sh);
-                            if constexpr (sizeof(T) == 2) rbc[s] = shb == 0 ? rbc[s] : (shb == 1 ? rbc[s] >> 16 : 0u);
-                            else rbc[s] = shb == 0 ? rbc[s] : (shb == 1 ? make_uint2(rbc[s].y, 0u) : make_uint2(0u, 0u));
-                        }
+            for (int s = 0; s < LG; ++s) {   // unrolled so the register arrays stay statically indexed
+                if ((LG == 2 && odd) != (s == 1)) continue;
+                if constexpr (RAG) {
+                    if (TAIL || rows_here < ROWS) {   // uniform
+                        const int sh = p_ok ? t0 - row_piece(t0, BSL, L) : BSL, ts = tc + 2 * s_tp;
+                        const int shb = ts - row_piece(ts, 2, L);
+                        io4<T>::drop(ru[s], sh); io4<T>::drop(rd[s], sh); io4<T>::drop(ro[s], sh);
+                        io4<T>::drop(rz[s], sh); io4<T>::drop(ry[s], sh);
+                        if constexpr (sizeof(T) == 2) rbc[s] = shb == 0 ? rbc[s] : (shb == 1 ? rbc[s] >> 16 : 0u);
+                        else rbc[s] = shb == 0 ? rbc[s] : (shb == 1 ? make_uint2(rbc[s].y, 0u) : make_uint2(0u, 0u));
+                    }
                 }
-            }
-#pragma unroll
-            for (int s = 0; s < LG; ++s) {  // unrolled so the register arrays stay statically indexed
-                if (slot == s) {
-                    io4<T>::unpack(ru[s], u4); io4<T>::unpack(rd[s], v4); io4<T>::unpack(ro[s], o4);
-                    if (has_z) { io4<T>::unpack(rz[s], z4); io4<T>::unpack(ry[s], y4); }
-                    bcw = rbc[s];
-                }
+                io4<T>::unpack(ru[s], u4); io4<T>::unpack(rd[s], v4); io4<T>::unpack(ro[s], o4);
+                io4<T>::unpack(rz[s], z4); io4<T>::unpack(ry[s], y4);
+                bcw = rbc[s];
             }
             // An empty slice reads as zeros; its steps must run with dt = 0 (the identity of the
             // recurrence) and contribute nothing: a bias of -1e30 makes softplus and its derivative
             // exactly 0 there, without a select per element.
             const float bias_eff = live ? bias : (softplus ? -1e30f : 0.0f);
             const float sg_lin = live ? 1.0f : 0.0f;
+            if (softplus) {
+#pragma unroll
+                for (int j = 0; j < BSL; ++j) softplus_sigmoid(v4[j] + bias_eff, dt4[j], sg4[j]);
+            } else {
+#pragma unroll
+                for (int j = 0; j < BSL; ++j) { dt4[j] = v4[j] + bias_eff; sg4[j] = sg_lin; }
+            }
 #pragma unroll
             for (int j = 0; j < BSL; ++j) {
-                const float x = v4[j] + bias_eff;
-                float sp, sg;
-                if (softplus) softplus_sigmoid(x, sp, sg); else { sp = x; sg = sg_lin; }
-                if constexpr (RAG) { sp = j < nv ? sp : 0.0f; sg = j < nv ? sg : 0.0f; }   // a slice may be partly inside
-                dt4[j] = sp;
-                sg4[j] = sg;
-                du4[j] = ZOH ? u4[j] : sp * u4[j];
+                if constexpr (RAG && TAIL) { dt4[j] = j < nv ? dt4[j] : 0.0f; sg4[j] = j < nv ? sg4[j] : 0.0f; }   // a slice may be partly inside
+                du4[j] = ZOH ? u4[j] : dt4[j] * u4[j];
                 dy4[j] = o4[j];
             }
+            float dz4[BSL] = {0.f, 0.f, 0.f, 0.f};
             if (has_z) {
-                float dz4[BSL];
 #pragma unroll
                 for (int j = 0; j < BSL; ++j) {
                     const float s = sigmoid_fast(z4[j]);
@@ -850,12 +855,8 @@ __global__ void __launch_bounds__(THREADS, 2) scan_bwd_dpp_kernel(const BwdArgs 
                     dy4[j] = o4[j] * zs;
                     dz4[j] = (o4[j] * y4[j]) * fmaf(zs, 1.0f - s, s);   // dout y d[z sigmoid(z)]/dz
                 }
-                if constexpr (RAG) {
-                    if (a.dz) store_paired_rag(a.dz, wg_first, r_off + (uint32_t)t0 * esz, t0, nv, io4<T>::pack(dz4), keep_dz, blk & 1);
-                } else {
-                    store_paired(bdz_, off, io4<T>::pack(dz4), keep_dz, blk & 1);   // switched off for all but the first state group
-                }
             }
+            store_block(bdz_, a.dz, off, nv, io4<T>::pack(dz4), keep_dz, odd, tail_tag);   // switched off without a gate and for all but the first state group
             *reinterpret_cast<float4*>(&sm.dt[pr][pq * BSL]) = make_float4(dt4[0], dt4[1], dt4[2], dt4[3]);
             *reinterpret_cast<float4*>(&sm.du[pr][pq * BSL]) = make_float4(du4[0], du4[1], du4[2], du4[3]);
             *reinterpret_cast<float4*>(&sm.dy[pr][pq * BSL]) = make_float4(dy4[0], dy4[1], dy4[2], dy4[3]);
@@ -865,7 +866,10 @@ __global__ void __launch_bounds__(THREADS, 2) scan_bwd_dpp_kernel(const BwdArgs 
             if constexpr (RAG) bc2 = s_n < N ? bc2 : make_float2(0.0f, 0.0f);   // slots without a state
             *reinterpret_cast<float2*>(&sm.bcp[s_which][s_tp >> 1][s_n][(s_tp & 1) * 2]) = bc2;
         }
-        if ((blk & (LG - 1)) == 0 && blk > blk_begin) issue_group(blk / LG - 1);  // in flight during the sweeps below
+        if (!odd) {   // the pair (float: the block) below, in flight during the sweeps
+            if constexpr (LG == 2) issue_block(blk - 1, std::integral_constant<int, LG - 1>{});
+            issue_block(blk - LG, std::integral_constant<int, 0>{});
+        }
         __syncthreads();
 
         // ---- B1: recompute the states of the block -----------------------------------------
@@ -971,11 +975,9 @@ __global__ void __launch_bounds__(THREADS, 2) scan_bwd_dpp_kernel(const BwdArgs 
         }
         // ---- flush this wave's dB/dC of the block to global memory -------------------------
         const float dB_total = merge_block<SPL>(sB, lane);
-        if (v_ok && tc + vt < L) {
-            const long at = (long)b * a.dbc_bstride + (long)vn * L + tc + vt;
-            atomicAdd(a.dB + at, dB_total);
-            atomicAdd(a.dC + at, dC_total);
-        }
+        const uint32_t at = v_ok && tc + vt < L ? v_off + (uint32_t)tc * 4u : BUF_OFF;
+        __builtin_amdgcn_raw_ptr_buffer_atomic_fadd_f32(dB_total, bdB_, (int)at, 0, 0);
+        __builtin_amdgcn_raw_ptr_buffer_atomic_fadd_f32(dC_total, bdC_, (int)at, 0, 0);
         __syncthreads();
 
         // ---- C: pointwise post-processing ---------------------------------------------------
@@ -1018,18 +1020,24 @@ __global__ void __launch_bounds__(THREADS, 2) scan_bwd_dpp_kernel(const BwdArgs 
 #pragma unroll
                 for (int j = 0; j < BSL; ++j) { du4[j] += pu[j]; dl4[j] += pl[j]; }
             }
-            if constexpr (RAG) {
-                const uint32_t off_t = r_off + (uint32_t)t0 * esz;
-                store_paired_rag(a.du, wg_first, off_t, t0, nv, io4<T>::pack(du4), keep_du, blk & 1);
-                store_paired_rag(a.ddelta, wg_first, off_t, t0, nv, io4<T>::pack(dl4), keep_dl, blk & 1);
-                if constexpr (LG == 2) keep_live = blk & 1;
-            } else {
-                store_paired(bdu_, off, io4<T>::pack(du4), keep_du, blk & 1);
-                store_paired(bdd_, off, io4<T>::pack(dl4), keep_dl, blk & 1);
-                if constexpr (LG == 2) keep_off = (blk & 1) ? off : BUF_OFF;
-            }
+            store_block(bdu_, a.du, off, nv, io4<T>::pack(du4), keep_du, odd, tail_tag);
+            store_block(bdd_, a.ddelta, off, nv, io4<T>::pack(dl4), keep_dl, odd, tail_tag);
+            if constexpr (LG == 2 && !TAIL) keep_off = odd ? off : BUF_OFF;
         }
+    };
+    // The first block's state goes out before its inputs, as in the loop, so that the way in is not the path with the fewest
+    // younger accesses (see do_block) for it.
+    int blk = nblocks - 1;
+    hck_next = load_ckpt(blk);
+    __builtin_amdgcn_sched_barrier(0);
+    if constexpr (LG == 2) issue_block(blk | 1, std::integral_constant<int, LG - 1>{});
+    __builtin_amdgcn_sched_barrier(0);
+    issue_block(blk & ~(LG - 1), std::integral_constant<int, 0>{});
+    __builtin_amdgcn_sched_barrier(0);
+    if constexpr (RAG) {
+        if ((blk + 1) * BT > L) do_block(blk--, std::true_type{});   // the row's end cuts the block
     }
+    for (; blk >= blk_begin; --blk) do_block(blk, std::false_type{});
 
     // ---- per-row results --------------------------------------------------------------------
     if (s_ok) {
