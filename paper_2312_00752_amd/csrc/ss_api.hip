@@ -423,7 +423,8 @@ int scan_bwd_strided(const ss_bwd_params* p, long bc_bstride, void* stream)
 }
 
 
-static int step_impl(const ss_step_params* p, long bc_stride, const float* P, const void* W_dt, int R, int ldp, void* stream)
+static int step_impl(const ss_step_params* p, long bc_stride, const float* P, const void* W_dt, int R, int ldp, void* conv_state,
+                     const void* x_t, void* stream)
 {
     if (!p) return SS_ERR_NULL;
     if (p->batch < 1 || p->dim < 1 || p->dstate < 1) return SS_ERR_SHAPE;
@@ -451,7 +452,7 @@ static int step_impl(const ss_step_params* p, long bc_stride, const float* P, co
     a.B = p->batch; a.D = p->dim; a.N = slots(p); a.flags = p->flags;
     a.h = p->h; a.u_t = p->u_t; a.delta_t = p->delta_t; a.z_t = p->z_t;
     a.B_t = P ? nullptr : p->B_t; a.C_t = P ? nullptr : p->C_t; a.bc_stride = bc_stride;
-    a.P = P; a.W_dt = W_dt; a.R = R; a.ldp = ldp; a.A = p->A; a.Dskip = p->Dskip; a.bias = p->delta_bias;
+    a.P = P; a.W_dt = W_dt; a.R = R; a.ldp = ldp; a.conv_state = conv_state; a.x_t = x_t; a.A = p->A; a.Dskip = p->Dskip; a.bias = p->delta_bias;
     a.out_t = p->out_t;
     if (P) return ss::launch_step_projected(a, p->io_dtype, static_cast<hipStream_t>(stream)) == 0 ? SS_OK : SS_ERR_LAUNCH;
     return ss::launch_step(a, p->io_dtype, static_cast<hipStream_t>(stream)) == 0 ? SS_OK : SS_ERR_LAUNCH;
@@ -459,14 +460,15 @@ static int step_impl(const ss_step_params* p, long bc_stride, const float* P, co
 
 int step_strided(const ss_step_params* p, long bc_stride, void* stream)
 {
-    return step_impl(p, bc_stride, nullptr, nullptr, 0, 0, stream);
+    return step_impl(p, bc_stride, nullptr, nullptr, 0, 0, nullptr, nullptr, stream);
 }
 
-int step_projected(const ss_step_params* p, const float* P, const void* W_dt, int R, int ldp, void* stream)
+int step_projected(const ss_step_params* p, const float* P, const void* W_dt, int R, int ldp, void* conv_state, const void* x_t,
+                   void* stream)
 {
     if (!p || !P || !W_dt) return SS_ERR_NULL;
     if (R < 8 || R > 256 || p->dstate > 16 || ldp != R + 2 * p->dstate) return SS_ERR_UNSUPPORTED;
-    return step_impl(p, 0, P, W_dt, R, ldp, stream);
+    return step_impl(p, 0, P, W_dt, R, ldp, conv_state, x_t, stream);
 }
 
 }  // namespace ss

@@ -34,12 +34,6 @@ struct ConvArgs {
 // reaches past the end is read from inside the row and shifted into place, see row_piece).
 enum { ROWS_SHORT, ROWS_WHOLE, ROWS_ANY };
 
-template <typename T> __device__ __forceinline__ float io_to_f32(T v);
-template <> __device__ __forceinline__ float io_to_f32<float>(float v) { return v; }
-template <> __device__ __forceinline__ float io_to_f32<bf16_t>(bf16_t v) { return bf16_to_f32(v); }
-template <typename T> __device__ __forceinline__ T f32_to_io(float v);
-template <> __device__ __forceinline__ float f32_to_io<float>(float v) { return v; }
-template <> __device__ __forceinline__ bf16_t f32_to_io<bf16_t>(float v) { return bf16_t(f32_to_bf16_bits(v)); }
 
 __device__ __forceinline__ void load_taps(const float* __restrict__ w, int d, int W, float (&k4)[TAPS])
 {
@@ -149,11 +143,6 @@ __device__ __forceinline__ void unpack_window(const window_raw<T>& r, int t0, fl
 #pragma unroll
     for (int j = 0; j < HALO; ++j) xs[j] = t0 > 0 ? h[j + 1] : raw_to_f32<T>(r.st[j]);
     if (NEXT) io4<T>::unpack(r.next, xn);
-}
-
-__device__ __forceinline__ float conv_at(const float (&k4)[TAPS], float bias, const float* xs)
-{
-    return fmaf(k4[3], xs[3], fmaf(k4[2], xs[2], fmaf(k4[1], xs[1], fmaf(k4[0], xs[0], bias))));
 }
 
 // ---- forward --------------------------------------------------------------------------------

@@ -87,6 +87,19 @@ __device__ __forceinline__ float softplus(float r)
     const float c = e - (w - 1.0f);
     return fmaf(c, fmaf(e, -0.5f, 1.0f), log2_fast(w) * LN2) + fmaxf(r, 0.0f);
 }
+template <typename T> __device__ __forceinline__ float io_to_f32(T v);
+template <> __device__ __forceinline__ float io_to_f32<float>(float v) { return v; }
+template <> __device__ __forceinline__ float io_to_f32<bf16_t>(bf16_t v) { return bf16_to_f32(v); }
+template <typename T> __device__ __forceinline__ T f32_to_io(float v);
+template <> __device__ __forceinline__ float f32_to_io<float>(float v) { return v; }
+template <> __device__ __forceinline__ bf16_t f32_to_io<bf16_t>(float v) { return bf16_t(f32_to_bf16_bits(v)); }
+
+// The short convolution at one step: taps right-aligned in four slots, xs the four samples up to the step.
+__device__ __forceinline__ float conv_at(const float (&k4)[4], float bias, const float* xs)
+{
+    return fmaf(k4[3], xs[3], fmaf(k4[2], xs[2], fmaf(k4[1], xs[1], fmaf(k4[0], xs[0], bias))));
+}
+
 // Exact zero-order hold (Eq. 4): phi(dt, A) = (exp(dt A) - 1) / A multiplies B u in the
 // state update (dt itself where A == 0), and d phi / d A = (x e^x - (e^x - 1)) / A^2 with
 // x = dt A (dt^2 / 2 where A == 0).  Both differences cancel for small x, where the Taylor

@@ -995,7 +995,8 @@ constexpr int SP_MAX_R = 256;
 constexpr int STEP_MAX_LDP = SP_MAX_R + 2 * NPAD;   // R <= 256 and N <= 16 on this path
 constexpr int SP_LDP = STEP_MAX_LDP + 4;          // row stride of the staged P in floats: 16-byte rows, off the banks
 
-template <typename T, bool FULLN, int SP_BT>
+// WIN: the convolution's window slides here, the projection having formed u itself (see StepArgs).
+template <typename T, bool FULLN, int SP_BT, bool WIN = false>
 __global__ void __launch_bounds__(SP_THREADS, SP_BT == 8 && sizeof(T) == 2 ? 4 : 2) step_proj_kernel(const StepArgs a)
 {
     static_assert(SP_BT == 8 || SP_BT == SP_MFMA_ROWS, "batch tile");
@@ -1032,6 +1033,7 @@ __global__ void __launch_bounds__(SP_THREADS, SP_BT == 8 && sizeof(T) == 2 ? 4 :
     const T* zp = has_z ? z_t : u_t;
     float hv[SP_PER][STATES_PER_LANE];
     T ub_raw[SP_PER], zb_raw[SP_PER];
+    T slot_raw[SP_PER];   // WIN: quarter q < 3 moves slot q of its (b, d)
 #pragma unroll
     for (int i = 0; i < SP_PER; ++i) {
         const int b = min(b0 + half * SP_PER + i, a.B - 1);
@@ -1045,6 +1047,7 @@ __global__ void __launch_bounds__(SP_THREADS, SP_BT == 8 && sizeof(T) == 2 ? 4 :
         }
         ub_raw[i] = u_t[row];
         zb_raw[i] = zp[row];
+        if constexpr (WIN) slot_raw[i] = *(q < 2 ? static_cast<const T*>(a.conv_state) + row * 3 + q + 1 : static_cast<const T*>(a.x_t) + row);
     }
     float A_raw[STATES_PER_LANE];
 #pragma unroll
@@ -1187,6 +1190,9 @@ __global__ void __launch_bounds__(SP_THREADS, SP_BT == 8 && sizeof(T) == 2 ? 4 :
         if (d_ok && q == 0) {
             if constexpr (sizeof(T) == 2) static_cast<bf16_t*>(a.out_t)[row] = bf16_t(f32_to_bf16_bits(y));
             else static_cast<float*>(a.out_t)[row] = y;
+        }
+        if constexpr (WIN) {
+            if (d_ok && q < 3) static_cast<T*>(a.conv_state)[row * 3 + q] = slot_raw[i];
         }
     }
 }
@@ -1417,7 +1423,11 @@ static void launch_step_projected_t(const StepArgs& a, hipStream_t stream)
     const bool wide = n8 > 256 && n16 <= 256;
     const dim3 grid((unsigned)groups, (unsigned)(wide ? (a.B + SP_MFMA_ROWS - 1) / SP_MFMA_ROWS : (a.B + 7) / 8));
     const dim3 block(SP_THREADS);
-    if (a.N == NPAD) {
+    if (a.conv_state) {   // a few entries only: never wide
+        const dim3 g((unsigned)groups, (unsigned)((a.B + 7) / 8));
+        if (a.N == NPAD) step_proj_kernel<T, true, 8, true><<<g, block, 0, stream>>>(a);
+        else step_proj_kernel<T, false, 8, true><<<g, block, 0, stream>>>(a);
+    } else if (a.N == NPAD) {
         if (wide) step_proj_kernel<T, true, SP_MFMA_ROWS><<<grid, block, 0, stream>>>(a);
         else step_proj_kernel<T, true, 8><<<grid, block, 0, stream>>>(a);
     } else {

@@ -94,6 +94,10 @@ struct StepArgs {
     const float* P;
     const void* W_dt;
     int R, ldp;
+    // Layer decode with the convolution inside the projection (width 4): the step kernel, the last to run, slides the
+    // window conv_state (B, D, 3) by x_t (B, D).  Null: done elsewhere.
+    void* conv_state;
+    const void* x_t;
     const float *A, *Dskip, *bias;
     void* out_t;
 };
@@ -122,7 +126,9 @@ int step_strided(const ss_step_params* p, long bc_stride, void* stream);
 
 // ss_step for the layer's decode: delta_t, B_t, C_t come from the float32 projection output
 // P (B, ldp) = [r; B; C] and W_dt (D, R) (see StepArgs); p's delta_t, B_t, C_t are ignored.
-int step_projected(const ss_step_params* p, const float* P, const void* W_dt, int R, int ldp, void* stream);
+// conv_state, x_t: the window to slide (see StepArgs), or null.
+int step_projected(const ss_step_params* p, const float* P, const void* W_dt, int R, int ldp, void* conv_state, const void* x_t,
+                   void* stream);
 
 // C[i] (M x N, row pitch ldc) = op(A[i]) (M x K) op(B[i]) (K x N) [+ C[i]] for i < batch, float
 // accumulation.  Element (m, k) of op(A[i]) is A[i * a_batch + m * a_m + k * a_k], element (k, n) of

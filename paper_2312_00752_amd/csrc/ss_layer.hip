@@ -148,6 +148,138 @@ int launch_xproj_decode(const void* u, const void* W, float* P, int nb, int nm, 
     return hipGetLastError() == hipSuccess ? SS_OK : SS_ERR_LAUNCH;
 }
 
+// The same product with the convolution in front of it (width 4, whole pairs of channels): u = SiLU(conv(window, x)) of
+// the tile's entries and the part's channels is formed in LDS, two channels per thread and every entry of the tile, so that
+// taps are read once per workgroup; the workgroups of the first column tile also leave u in memory for the step
+// kernel.  The window is only read: other column tiles form the same u, so the step kernel, the next launch, slides it.  What
+// the column tiles repeat is a few multiply-adds and reads from the L2; what it saves is a launch that the product waits for.  That
+// pays for up to four entries, where a call is launches and latency: us per call, from Python, D 4096 bf16, batch 1,
+// 16.6 -> 15.3; replayed from a HIP graph, three launches / two, batch 1, 2, 4: D 4096 9.76 / 9.77, 11.3 / 10.6, 12.1 / 11.3;
+// D 1536, batch 1, 4: 8.2 / 7.5, 9.8 / 9.2; float32, D 4096, batch 1, 4: 13.2 / 12.5, 15.7 / 15.8; but batch 8: 12.6 / 13.6, 64: 18.3 / 18.7.
+// Values, and the order of every sum, are those of three launches.  ROWS: entries a thread's loads are issued for together.
+constexpr int CX_BATCH = 4;
+template <typename T> constexpr int CX_COLS = 3072 / (int)sizeof(T);   // channels staged at a time: 49 KB of LDS
+template <typename T, bool RAG, int ROWS>
+__global__ void __launch_bounds__(64 * XP_WAVES) conv_xproj_decode_kernel(const T* __restrict__ win, const T* __restrict__ x,
+                                                                          const float* __restrict__ cw, const float* __restrict__ cb,
+                                                                          T* __restrict__ u, const T* __restrict__ W,
+                                                                          float* __restrict__ P, int nb, int nm, int D)
+{
+    using mma = ss::tile_mma<T>;
+    using ss::f32x4_t;
+    using ss::u32x2;
+    using ss::u32x4;
+    constexpr int COLS = CX_COLS<T>, PAD = 16 / (int)sizeof(T), STEPS = COLS / mma::K / XP_WAVES;   // STEPS: of a wave
+    __shared__ __attribute__((aligned(16))) T s_u[16][COLS + PAD];
+    __shared__ f32x4_t part[XP_WAVES - 1][64];
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int row0 = blockIdx.x * 16, col0 = blockIdx.y * 16;
+    const int rows = min(16, nb - row0);
+    const int wrow = min(col0 + (lane & 15), nm - 1);
+    const int ksub = mma::E * (lane >> 4);
+    const T* wp = W + (size_t)wrow * D;
+    f32x4_t acc = {0.f, 0.f, 0.f, 0.f};
+    const int kpart = ((D + XP_NPARTS - 1) / XP_NPARTS + mma::K - 1) / mma::K * mma::K;
+    const int kend = min(D, (int)(blockIdx.z + 1) * kpart);
+    for (int c0 = blockIdx.z * kpart; c0 < kend; c0 += COLS) {
+        const int n = min(COLS, kend - c0), steps = (n + mma::K - 1) / mma::K;   // n is even
+        u32x4 wf[STEPS];   // requested before anything else; read at element alignment from inside the row
+#pragma unroll
+        for (int i = 0; i < STEPS; ++i)
+            if (wave + XP_WAVES * i < steps) wf[i] = mma::load(wp, c0 + mma::K * (wave + XP_WAVES * i) + ksub, D);   // uniform
+        for (int p = tid; p < n / 2; p += 64 * XP_WAVES) {
+            const int d = c0 + 2 * p;
+            const u32x4 k0 = ss::load_any<u32x4>(cw + (size_t)d * 4, 0u), k1 = ss::load_any<u32x4>(cw + (size_t)d * 4, 16u);
+            const u32x2 bb = ss::load_any<u32x2>(cb + d, 0u);
+            const float ka[4] = {__uint_as_float(k0[0]), __uint_as_float(k0[1]), __uint_as_float(k0[2]), __uint_as_float(k0[3])};
+            const float kb[4] = {__uint_as_float(k1[0]), __uint_as_float(k1[1]), __uint_as_float(k1[2]), __uint_as_float(k1[3])};
+            for (int r0 = 0; r0 < rows; r0 += ROWS) {
+                T s[ROWS][6], xn[ROWS][2];   // the two channels' windows, one after the other, and new samples
+#pragma unroll
+                for (int r = 0; r < ROWS; ++r) {
+                    const size_t at = (size_t)(row0 + min(r0 + r, rows - 1)) * D + d;
+                    const T* sp = win + at * 3;
+                    const u32x2 w01 = ss::load_any<u32x2>(sp, 0u);
+                    if constexpr (sizeof(T) == 2) {
+                        const uint32_t w2 = ss::load_any<uint32_t>(sp, 8u), w3 = ss::load_any<uint32_t>(x + at, 0u);
+                        s[r][0] = T(w01[0]); s[r][1] = T(w01[0] >> 16); s[r][2] = T(w01[1]); s[r][3] = T(w01[1] >> 16);
+                        s[r][4] = T(w2); s[r][5] = T(w2 >> 16);
+                        xn[r][0] = T(w3); xn[r][1] = T(w3 >> 16);
+                    } else {
+                        const u32x4 w2 = ss::load_any<u32x4>(sp, 8u);
+                        const u32x2 w3 = ss::load_any<u32x2>(x + at, 0u);
+                        s[r][0] = __uint_as_float(w01[0]); s[r][1] = __uint_as_float(w01[1]);
+#pragma unroll
+                        for (int i = 0; i < 4; ++i) s[r][2 + i] = __uint_as_float(w2[i]);
+                        xn[r][0] = __uint_as_float(w3[0]); xn[r][1] = __uint_as_float(w3[1]);
+                    }
+                }
+#pragma unroll
+                for (int r = 0; r < ROWS; ++r) {
+                    T o[2];
+#pragma unroll
+                    for (int i = 0; i < 2; ++i) {
+                        const float xs[4] = {ss::io_to_f32<T>(s[r][3 * i]), ss::io_to_f32<T>(s[r][3 * i + 1]),
+                                             ss::io_to_f32<T>(s[r][3 * i + 2]), ss::io_to_f32<T>(xn[r][i])};
+                        const float v = ss::conv_at(i ? kb : ka, __uint_as_float(bb[i]), xs);
+                        o[i] = ss::f32_to_io<T>(v * ss::sigmoid_fast(v));
+                    }
+                    const int rr = min(r0 + r, rows - 1);
+                    typedef T pair_t __attribute__((ext_vector_type(2)));
+                    *reinterpret_cast<pair_t*>(&s_u[rr][2 * p]) = pair_t{o[0], o[1]};
+                    if (blockIdx.y == 0) *reinterpret_cast<pair_t*>(u + (size_t)(row0 + rr) * D + d) = pair_t{o[0], o[1]};   // uniform
+                }
+            }
+        }
+        if (RAG && n % mma::K != 0)   // the product's last step: zeros past D
+            for (int i = tid; i < 16 * mma::K; i += 64 * XP_WAVES) {
+                const int c = steps * mma::K - 1 - i / 16;
+                if (c >= n) s_u[i % 16][c] = ss::f32_to_io<T>(0.0f);
+            }
+        __syncthreads();
+#pragma unroll
+        for (int i = 0; i < STEPS; ++i)
+            if (wave + XP_WAVES * i < steps) {   // uniform
+                const int k = mma::K * (wave + XP_WAVES * i);
+                u32x4 b = wf[i];
+                if (RAG && c0 + k + mma::K > D) b = mma::cut(b, c0 + k + ksub, D);   // uniform
+                acc = mma::step(*reinterpret_cast<const u32x4*>(&s_u[lane & 15][k + ksub]), b, acc);
+            }
+        if (c0 + COLS < kend) __syncthreads();   // s_u is rewritten
+    }
+    if (wave > 0) part[wave - 1][lane] = acc;
+    __syncthreads();
+    if (wave == 0) {
+#pragma unroll
+        for (int w = 0; w < XP_WAVES - 1; ++w) acc += part[w][lane];
+        const int col = col0 + (lane & 15);
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const int row = row0 + 4 * (lane >> 4) + r;
+            if (row < nb && col < nm) P[((size_t)blockIdx.z * nb + row) * nm + col] = acc[r];
+        }
+    }
+}
+template <typename T, int ROWS>
+int launch_conv_xproj_rows(const ss_layer_step_params* p, void* u, float* P, hipStream_t st)
+{
+    const int nb = p->batch, D = p->dim, nm = p->dt_rank + 2 * p->dstate;
+    const dim3 grid((unsigned)((nb + 15) / 16), (unsigned)((nm + 15) / 16), (unsigned)XP_NPARTS), block(64 * XP_WAVES);
+    const T *win = static_cast<const T*>(p->conv_state), *x = static_cast<const T*>(p->x_t), *W = static_cast<const T*>(p->W_x);
+    if (D % ss::tile_mma<T>::K == 0)
+        hipLaunchKernelGGL((conv_xproj_decode_kernel<T, false, ROWS>), grid, block, 0, st, win, x, p->conv_w, p->conv_b, static_cast<T*>(u), W, P, nb, nm, D);
+    else
+        hipLaunchKernelGGL((conv_xproj_decode_kernel<T, true, ROWS>), grid, block, 0, st, win, x, p->conv_w, p->conv_b, static_cast<T*>(u), W, P, nb, nm, D);
+    return hipGetLastError() == hipSuccess ? SS_OK : SS_ERR_LAUNCH;
+}
+template <typename T>
+int launch_conv_xproj(const ss_layer_step_params* p, void* u, float* P, hipStream_t st)
+{
+    if (p->batch == 1) return launch_conv_xproj_rows<T, 1>(p, u, P, st);
+    return launch_conv_xproj_rows<T, 4>(p, u, P, st);
+}
+
 // r (the first R rows of each batch entry of P, (B, Mx, L)) transposed and zero-padded to
 // (B, Lp, Rp), for the delta projection inside the scan kernel (see FwdArgs::rT).  32 x 32 tiles
 // through LDS; block (32, 8), grid (Lp / 32, Rp / 32, B).
@@ -519,6 +651,7 @@ int ss_layer_step(const ss_layer_step_params* p, void* stream)
     if (!aligned_to(p->dt_bias, 4) || !aligned_to(p->A, 4) || !aligned_to(p->Dskip, 4)) return SS_ERR_ALIGN;
     if (!p->scratch || p->scratch_bytes < ss_layer_step_scratch_bytes(p)) return SS_ERR_WORKSPACE;
     if (!aligned_to(p->scratch, 256)) return SS_ERR_ALIGN;
+    if (!aligned_to(p->x_t, esz) || !aligned_to(p->conv_state, esz) || !aligned_to(p->conv_w, 4) || !aligned_to(p->conv_b, 4)) return SS_ERR_ALIGN;
     hipStream_t st = static_cast<hipStream_t>(stream);
     const int B = p->batch, D = p->dim, N = p->dstate, R = p->dt_rank, Mx = R + 2 * N;
     char* scratch = static_cast<char*>(p->scratch);
@@ -539,14 +672,21 @@ int ss_layer_step(const ss_layer_step_params* p, void* stream)
     s.A = p->A; s.Dskip = p->Dskip; s.delta_bias = p->dt_bias;
     s.out_t = p->out_t;
 
-    // both projections on the matrix cores, delta_t = W_dt r_t inside the state-update kernel: three launches, no atomics
+    // both projections on the matrix cores, delta_t = W_dt r_t inside the state-update kernel, no atomics: two launches with the
+    // convolution inside the first projection (width 4, an even number of channels, up to CX_BATCH entries), three otherwise
     if (D >= 8 && R >= 8 && R <= 256 && N <= 16) {
+        if ((long)B * D >= 0x7fffffffL) return SS_ERR_UNSUPPORTED;
+        if (p->conv_width == 4 && D % 2 == 0 && B <= CX_BATCH) {
+            const int rc = bf16 ? launch_conv_xproj<ss::bf16_t>(p, u_t, P_acc, st) : launch_conv_xproj<float>(p, u_t, P_acc, st);
+            if (rc != SS_OK) return rc;
+            return ss::step_projected(&s, P_acc, p->W_dt, R, Mx, p->conv_state, p->x_t, stream);
+        }
         int rc = ss_conv_step(&c, stream);
         if (rc != SS_OK) return rc;
         rc = bf16 ? launch_xproj_decode<ss::bf16_t>(u_t, p->W_x, P_acc, B, Mx, D, st)
                   : launch_xproj_decode<float>(u_t, p->W_x, P_acc, B, Mx, D, st);
         if (rc != SS_OK) return rc;
-        return ss::step_projected(&s, P_acc, p->W_dt, R, Mx, stream);
+        return ss::step_projected(&s, P_acc, p->W_dt, R, Mx, nullptr, nullptr, stream);
     }
 
     int rc = ss_conv_step(&c, stream);
