@@ -19,14 +19,15 @@
 //                     ([r;B;C] = W_x u, dr = W_dt^T ddelta): that operand is contiguous along N, not
 //                     along the contraction index, so two rows at a time are interleaved into 32-bit
 //                     pairs on their way into LDS and a fragment is four such pairs.
-//   gemm_cols_kernel  many output rows, short contraction (delta = W_dt r, du += W_x^T d[r;B;C]): the
-//                     small (K, N) operand goes through the same pairing once per workgroup and stays
-//                     in registers as fragments; the product is formed transposed so that a lane
-//                     holds four consecutive columns, and leaves through an LDS tile as whole
-//                     128-byte row pieces.
+//   gemm_cols_kernel  many output rows, short contraction (delta = W_dt r, du += W_x^T d[r;B;C]): a
+//                     wave keeps its 64 columns of the small (K, N) operand in registers and walks
+//                     the rows of the other; the product is formed transposed, so that a lane holds
+//                     consecutive columns of the result.  With a result that is added to, gemm_cols_add_kernel: 64 x 64
+//                     tiles through LDS.
 // gemm_generic_kernel takes every other stride and dtype (64 x 64 tiles through LDS, float MFMAs): the float32
 // layer, sizes below 8 and the per-token products of more than 256 ranks.
 #include <hip/hip_runtime.h>
+#include <algorithm>
 #include <type_traits>
 
 #include "ss_device.h"
@@ -322,6 +323,7 @@ __device__ __forceinline__ void pair_rows(uint4 lo, uint4 hi, uint4& out0, uint4
 // slab, 100 KB of LDS traffic per step and workgroup against 40: dW_dt and dW_x of 8 x 4096 x 2048 55 and 58 us,
 // now 48 and 58; of 8 x 1536 x 2047 44 and 45, now 30 and 44; of 2 x 5120 x 4096 74 and 89, now 52 and 63.)
 constexpr int PD = 4;
+constexpr long COLS_WGS = 512;
 constexpr long ROWS_MIN_WGS = 512;   // two workgroups of gemm_rows_kernel fit on each of the 256 CUs
 constexpr int ROWS_MIN_SPLIT_K = 4096;   // shorter contractions lose more to the second launch than they gain (K = 1536: 21 -> 25 us)
 
@@ -695,13 +697,120 @@ __global__ void __launch_bounds__(256) rows_reduce_kernel(const float* __restric
     *reinterpret_cast<uint4*>(Out + b * o_batch + (long)row * o_ld + 8 * c8) = o;
 }
 
-// Out (M x N per batch entry, bf16) [+]= W (M x K, contiguous along K) Y (K x N, contiguous along N).
+// Out (M x N per batch entry, bf16) = W (M x K, contiguous along K) Y (K x N, contiguous along N).
+// grid (N / 256, M / (16 * mtiles), batch) rounded up, mtiles = 16-row tiles of the result per workgroup.  K <= 32 NKS.  Plain:
+// K % 32 == 0, N % 64 == 0, M % 16 == 0, whole 16-byte pieces.
+// Bound by writing Out once, if little else moves.  A wave owns 64 columns and walks the row tiles by itself, without LDS and
+// without a barrier; the four waves of a workgroup are neighbours along N, so that the weights, the same for all four, come
+// from the L2 once per 256 columns (with 64 columns per workgroup they were 256 MB at 8 x 4096 x 2048 against the 134 of Out).
+// The wave's part of Y stays in registers as first operands of the transposed product, whose row r is a column of Y and
+// may be any: a lane reads four columns at eight contraction indices, and a byte permute takes column c's pairs out of
+// them, so row r of product c is column strip_col(r) + c.  With strip_col as below a lane's results of all four products
+// are two runs of eight columns, and each of the two stores that write them covers 64 contiguous bytes of sixteen rows.
+// us, before (64 x 64 tiles through LDS, a column strip per workgroup) / now: 8 x 4096 x 2048, K = 128: 58 / 43; 2 x 5120 x 4096, K = 160:
+// 45 / 30; 4 x 2560 x 2048, K = 80: 19 / 15; 8 x 1536 x 2047, K = 48: 22 / 21; 4 x 4096 x 1531, K = 128: 36 / 33.
+__device__ __forceinline__ int strip_col(int r) { return 32 * ((r >> 1) & 1) + 8 * (r >> 2) + 4 * (r & 1); }
+template <bool RAG, int NKS>
+__global__ void __launch_bounds__(256, 2) gemm_cols_kernel(const bf16_t* __restrict__ W, long w_ld, const bf16_t* __restrict__ Y,
+                                                           long y_ld, long y_batch, bf16_t* __restrict__ Out, long o_ld, long o_batch,
+                                                           int M, int N, int K, int mtiles)
+{
+    const int lane = threadIdx.x & 63, g = lane >> 4, j = lane & 15;
+    const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int n0 = blockIdx.x * 256 + 64 * w;
+    if (n0 >= N) return;   // uniform; no barrier below
+    const long b = blockIdx.z;
+    const int KS = (K + 31) >> 5;   // 32-wide contraction steps (<= NKS)
+    const int t_begin = blockIdx.y * mtiles, t_end = min((M + 15) / 16, t_begin + mtiles);
+    auto load_w = [&](u32x4 (&f)[NKS], int t) {
+        const int m = 16 * min(t, t_end - 1) + j;
+        const bf16_t* __restrict__ wrow = W + (long)(RAG ? min(m, M - 1) : m) * w_ld;
+#pragma unroll
+        for (int ks = 0; ks < NKS; ++ks)
+            if (ks < KS) f[ks] = piece<RAG>(wrow, 32 * ks + 8 * g, K);
+    };
+    constexpr int AHEAD = 2;   // tiles requested ahead
+    u32x4 wf[AHEAD][NKS];
+#pragma unroll
+    for (int i = 0; i < AHEAD; ++i) load_w(wf[i], t_begin + i);
+    // the columns of Y: row r of the products, see above
+    u32x4 yf[NKS][4];
+    {
+        const int col = n0 + strip_col(j), ycol = RAG ? row_piece(col, 4, N) : col;
+        const bf16_t* __restrict__ y = Y + b * y_batch + ycol;
+        u32x2 raw[NKS][8];
+#pragma unroll
+        for (int ks = 0; ks < NKS; ++ks)
+            if (ks < KS)
+#pragma unroll
+                for (int r = 0; r < 8; ++r) {
+                    const int k = 32 * ks + 8 * g + r;
+                    raw[ks][r] = load_any<u32x2>(y + (long)(RAG ? min(k, K - 1) : k) * y_ld, 0u);
+                }
+#pragma unroll
+        for (int ks = 0; ks < NKS; ++ks)
+            if (ks < KS) {
+                if constexpr (RAG) {
+                    const int sh = 16 * min(col - ycol, 4);   // a piece that ended past the row; whole pieces past it are not stored
+#pragma unroll
+                    for (int r = 0; r < 8; ++r) {
+                        const uint64_t v = (uint64_t(raw[ks][r][1]) << 32) | raw[ks][r][0];
+                        const uint64_t x = sh >= 64 || 32 * ks + 8 * g + r >= K ? 0ull : v >> sh;
+                        raw[ks][r] = u32x2{(uint32_t)x, (uint32_t)(x >> 32)};
+                    }
+                }
+#pragma unroll
+                for (int c = 0; c < 4; ++c)
+#pragma unroll
+                    for (int q = 0; q < 4; ++q)
+                        yf[ks][c][q] = __builtin_amdgcn_perm(raw[ks][2 * q + 1][c >> 1], raw[ks][2 * q][c >> 1], c & 1 ? 0x07060302u : 0x05040100u);
+            }
+    }
+    // a lane's results: row 16 t + j, columns n0 + 32 h + 8 g ..+7 for h = 0, 1
+    bf16_t* __restrict__ o = Out + b * o_batch;
+    const int oc = n0 + 8 * g;
+    auto do_tile = [&](int t, auto slot_tag) {
+        constexpr int SLOT = decltype(slot_tag)::value;
+        f32x4_t acc[4];
+#pragma unroll
+        for (int c = 0; c < 4; ++c) acc[c] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int ks = 0; ks < NKS; ++ks)
+            if (ks < KS) {
+                u32x4 x = wf[SLOT][ks];
+                if (RAG && 32 * (ks + 1) > K) x = cut(x, 32 * ks + 8 * g, K);   // the last step
+#pragma unroll
+                for (int c = 0; c < 4; ++c) acc[c] = mma::step(yf[ks][c], x, acc[c]);
+            }
+        load_w(wf[SLOT], t + AHEAD);
+        const int m = 16 * t + j;
+        bf16_t* __restrict__ row = o + (long)m * o_ld;
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            float r[8];
+#pragma unroll
+            for (int i = 0; i < 8; ++i) r[i] = acc[i & 3][2 * h + (i >> 2)];
+            const uint4 x = io8<bf16_t>::pack(r);
+            if constexpr (!RAG) *reinterpret_cast<uint4*>(row + oc + 32 * h) = x;
+            else if (n0 + 64 <= N && 16 * t + 16 <= M) store_row16(row + oc + 32 * h, u32x4{x.x, x.y, x.z, x.w});   // uniform
+            else if (m < M && oc + 32 * h < N) io8<bf16_t>::store_elem(row + oc + 32 * h, 0u, x, N - (oc + 32 * h));
+        }
+    };
+    for (int t = t_begin; t < t_end; t += AHEAD) {
+        do_tile(t, std::integral_constant<int, 0>{});
+        if (t + 1 < t_end) do_tile(t + 1, std::integral_constant<int, 1>{});
+    }
+}
+
+// Out += W Y, of the same operands.  A result that is also read is the faster for leaving through LDS in whole rows of 128
+// bytes, 64 of them per workgroup: in the layer's backward pass, us, this kernel / the one above with the old values
+// requested two tiles ahead: 8 x 4096 x 2048, K = 160, 77 / 84, 8 x 1536 x 2047, K = 80, 42 / 47.
 // grid (N / 64, M / (64 * mtiles), batch) rounded up, mtiles = 64-row tiles of the result per workgroup (the small
 // operand is prepared once for all of them).  K <= 32 NKS.  Plain: K % 32 == 0, N % 64 == 0, M % (64 * mtiles) == 0.
 template <bool RAG, int NKS>
-__global__ void __launch_bounds__(256) gemm_cols_kernel(const bf16_t* __restrict__ W, long w_ld, const bf16_t* __restrict__ Y,
+__global__ void __launch_bounds__(256) gemm_cols_add_kernel(const bf16_t* __restrict__ W, long w_ld, const bf16_t* __restrict__ Y,
                                                          long y_ld, long y_batch, bf16_t* __restrict__ Out, long o_ld, long o_batch,
-                                                         int M, int N, int K, int accumulate, int mtiles)
+                                                         int M, int N, int K, int mtiles)
 {
     __shared__ __attribute__((aligned(16))) uint32_t Yp[NKS * 16][XPITCH];         // pairs of contraction indices x 64 columns
     __shared__ __attribute__((aligned(16))) float Os[64][64 + 4];                 // a tile of the result on its way out (two of them, one barrier per tile: slower, 71 -> 76 us)
@@ -761,14 +870,17 @@ __global__ void __launch_bounds__(256) gemm_cols_kernel(const bf16_t* __restrict
             if (RAG && ks < KS && 32 * (ks + 1) > K) wc[ks] = cut(wc[ks], 32 * ks + 8 * g, K);   // the last step
         }
         if (mt + 1 < mtiles) load_w(wf, m0 + 64);
-        // earlier values of this tile, for accumulation: requested before the arithmetic
-        uint4 prev[2];
+        // earlier values of this tile: requested before the arithmetic
+        u32x4 prev[2];
+        uint32_t last[2];   // RAG: see load_row16
+        auto prev_at = [&](int e) {
+            const int idx = tid + 256 * e, row = idx >> 3, pc = idx & 7;
+            return o + (long)(RAG ? min(m0 + row, M - 1) : m0 + row) * o_ld + (RAG ? row_piece(n0 + 8 * pc, 8, N) : n0 + 8 * pc);
+        };
 #pragma unroll
         for (int e = 0; e < 2; ++e) {
-            const int idx = tid + 256 * e, row = idx >> 3, pc = idx & 7;
-            u32x4 x = {0u, 0u, 0u, 0u};
-            if (accumulate) x = piece<RAG>(o + (long)(RAG ? min(m0 + row, M - 1) : m0 + row) * o_ld, n0 + 8 * pc, N);
-            prev[e] = make_uint4(x[0], x[1], x[2], x[3]);
+            if constexpr (RAG) load_row16(prev_at(e), prev[e], last[e]);
+            else prev[e] = *reinterpret_cast<const u32x4*>(prev_at(e));
         }
         f32x4_t acc[4];
 #pragma unroll
@@ -789,16 +901,20 @@ __global__ void __launch_bounds__(256) gemm_cols_kernel(const bf16_t* __restrict
             const float4 lo = *reinterpret_cast<const float4*>(&Os[row][8 * pc]);
             const float4 hi = *reinterpret_cast<const float4*>(&Os[row][8 * pc + 4]);
             float r[8] = {lo.x, lo.y, lo.z, lo.w, hi.x, hi.y, hi.z, hi.w};
-            if (RAG && n0 + 64 > N) prev[e] = cut(prev[e], n0 + 8 * pc, N);
-            const uint32_t c[4] = {prev[e].x, prev[e].y, prev[e].z, prev[e].w};   // zeros unless accumulating
+            if constexpr (RAG) {
+                prev[e] = shift_row16(prev_at(e), prev[e], last[e]);
+                if (n0 + 64 > N) prev[e] = cut(prev[e], n0 + 8 * pc, N);
+            }
 #pragma unroll
             for (int m = 0; m < 4; ++m) {
-                r[2 * m] += bf16_lo(c[m]);
-                r[2 * m + 1] += bf16_hi(c[m]);
+                r[2 * m] += bf16_lo(prev[e][m]);
+                r[2 * m + 1] += bf16_hi(prev[e][m]);
             }
             bf16_t* dst = o + (long)(m0 + row) * o_ld + n0 + 8 * pc;
             if constexpr (RAG) {
-                if (m0 + row < M) io8<bf16_t>::store_elem(dst, 0u, io8<bf16_t>::pack(r), N - (n0 + 8 * pc));
+                const uint4 x = io8<bf16_t>::pack(r);
+                if (n0 + 64 <= N && m0 + 64 <= M) store_row16(dst, u32x4{x.x, x.y, x.z, x.w});   // uniform
+                else if (m0 + row < M) io8<bf16_t>::store_elem(dst, 0u, x, N - (n0 + 8 * pc));
             } else {
                 *reinterpret_cast<uint4*>(dst) = io8<bf16_t>::pack(r);
             }
@@ -854,12 +970,18 @@ void launch_rows(const GemmArgs& g, const bf16_t* A, bf16_t* C, int S, int parts
 template <bool RAG>
 void launch_cols(const GemmArgs& g, int mtiles, hipStream_t stream)
 {
-    const dim3 grid(tiles64(g.N), (unsigned)((tiles64(g.M) + mtiles - 1) / mtiles), (unsigned)g.batch);
+    const dim3 grid((unsigned)((g.N + 255) / 256), (unsigned)(((g.M + 15) / 16 + mtiles - 1) / mtiles), (unsigned)g.batch);
+    const dim3 grid_add(tiles64(g.N), (unsigned)((tiles64(g.M) + mtiles - 1) / mtiles), (unsigned)g.batch);
     const int KS = (g.K + 31) / 32;
     const bf16_t *A = static_cast<const bf16_t*>(g.A), *B = static_cast<const bf16_t*>(g.B);
-#define SS_LAUNCH_COLS(NKS) hipLaunchKernelGGL((gemm_cols_kernel<RAG, NKS>), grid, dim3(256), 0, stream, A, g.a_m, B, g.b_k, g.b_batch, \
-                                               static_cast<bf16_t*>(g.C), g.ldc, g.c_batch, g.M, g.N, g.K, g.accumulate ? 1 : 0, mtiles)
-    if (KS <= 3) SS_LAUNCH_COLS(3); else if (KS <= 5) SS_LAUNCH_COLS(5); else SS_LAUNCH_COLS(6);
+#define SS_LAUNCH_COLS(NKS)                                                                                                                  \
+    if (g.accumulate)                                                                                                                        \
+        hipLaunchKernelGGL((gemm_cols_add_kernel<RAG, NKS>), grid_add, dim3(256), 0, stream, A, g.a_m, B, g.b_k, g.b_batch,                    \
+                           static_cast<bf16_t*>(g.C), g.ldc, g.c_batch, g.M, g.N, g.K, mtiles);                                               \
+    else                                                                                                                                     \
+        hipLaunchKernelGGL((gemm_cols_kernel<RAG, NKS>), grid, dim3(256), 0, stream, A, g.a_m, B, g.b_k, g.b_batch,                            \
+                           static_cast<bf16_t*>(g.C), g.ldc, g.c_batch, g.M, g.N, g.K, mtiles)
+    if (KS <= 3) { SS_LAUNCH_COLS(3); } else if (KS <= 5) { SS_LAUNCH_COLS(5); } else { SS_LAUNCH_COLS(6); }
 #undef SS_LAUNCH_COLS
 }
 
@@ -892,12 +1014,20 @@ int launch_fast(const GemmArgs& g, hipStream_t stream)
     if (g.a_k == 1 && g.b_n == 1 && !g.c_float && g.N >= 8) {
         const bool whole_c = whole && g.N % 64 == 0 && mult8(g.a_m) && mult8(g.b_k) && mult8(g.ldc) && mult8(g.c_batch);
         if (g.K <= SMAX && g.a_batch == 0) {
-            // as many 64-row tiles per workgroup as fit, up to 16, while the launch keeps >= 1024 workgroups
             int mtiles = 1;
-            const long cols = (long)tiles64(g.N) * g.batch, mt = tiles64(g.M);
-            for (int c = 16; c > 1; c >>= 1)
-                if (mt % c == 0 && cols * (mt / c) >= 1024) { mtiles = c; break; }
-            if (whole_c && g.K % 32 == 0 && g.M % 64 == 0) launch_cols<false>(g, mtiles, stream);
+            if (g.accumulate) {
+                // as many 64-row tiles per workgroup as fit, up to 16, while the launch keeps >= 1024 workgroups
+                const long cols = (long)tiles64(g.N) * g.batch, mt = tiles64(g.M);
+                for (int c = 16; c > 1; c >>= 1)
+                    if (mt % c == 0 && cols * (mt / c) >= 1024) { mtiles = c; break; }
+            } else {
+                // 512 workgroups, two per compute unit, in one round, each with its share of the 16-row tiles (256: 44 -> 68 us at the
+                // headline shape, 768: 46, 1024: 52)
+                const long cols = (long)((g.N + 255) / 256) * g.batch, mt = (g.M + 15) / 16;
+                mtiles = (int)std::min(64L, (cols * mt + COLS_WGS - 1) / COLS_WGS);
+            }
+            const int whole_rows = g.accumulate ? 64 : 16;
+            if (whole_c && g.K % 32 == 0 && g.M % whole_rows == 0) launch_cols<false>(g, mtiles, stream);
             else launch_cols<true>(g, mtiles, stream);
             return hipGetLastError() == hipSuccess ? SS_OK : SS_ERR_LAUNCH;
         }
