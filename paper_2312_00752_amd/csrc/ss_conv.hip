@@ -82,28 +82,62 @@ struct window_raw {
 };
 template <typename T>
 __device__ __forceinline__ uint32_t row_bytes(int L) { return (uint32_t)L * (uint32_t)sizeof(T); }   // rows below 2^31 bytes (checked by the host)
+// pieces of 512 steps a row is dealt out in; a row off a word starts one step before (see row_phase)
+template <typename T, int KIND>
+__host__ __device__ __forceinline__ int row_pieces(int L) { return (L + (KIND == ROWS_ANY && sizeof(T) == 2 ? 1 : 0) + PIECE - 1) / PIECE; }
 template <typename T, bool NEXT>
 __device__ __forceinline__ window_raw<T> issue_window_any(const T* row, const T* state_row, int t0, int L, int W)
 {
     window_raw<T> r;
     const uint32_t esz = (uint32_t)sizeof(T);
-    r.cur = io8<T>::load_elem(row, (uint32_t)row_piece(t0, 8, L) * esz);
+    r.cur = io8<T>::load_elem(row, (uint32_t)row_piece(max(t0, 0), 8, L) * esz);
     r.halo = io4<T>::load_elem(row, (uint32_t)row_piece(max(t0 - 4, 0), 4, L) * esz);
     if (NEXT) r.next = io4<T>::load_elem(row, (uint32_t)row_piece(t0 + 8, 4, L) * esz);
-    const T* const st = state_row ? state_row : row;   // W - 1 samples, or a row of at least 8
+    for (int j = 0; j < HALO; ++j) r.st[j] = 0u;
+    if (state_row && t0 <= 0) {   // W - 1 samples
 #pragma unroll
-    for (int j = 0; j < HALO; ++j) {
-        const T v = st[max(min(j - (TAPS - W), W - 2), 0)];
-        if constexpr (sizeof(T) == 2) r.st[j] = v; else r.st[j] = __float_as_uint(v);
+        for (int j = 0; j < HALO; ++j) {
+            const T v = state_row[max(min(j - (TAPS - W), W - 2), 0)];
+            if constexpr (sizeof(T) == 2) r.st[j] = v; else r.st[j] = __float_as_uint(v);
+        }
     }
     return r;
+}
+// ROWS_ANY, 16-bit elements: how many elements a row starts off a whole 32-bit word.  Slices start that many steps earlier, the
+// first one of such a row before the row, so that every access lies on words: off them the hardware takes wide accesses much
+// more slowly, and of an odd number of steps every other row is.  (Uniform: a wave works on one row.)
+template <typename T, int KIND>
+__device__ __forceinline__ int row_phase(const T* row)
+{
+    if constexpr (KIND == ROWS_ANY && sizeof(T) == 2) return (int)((reinterpret_cast<uintptr_t>(row) >> 1) & 1);
+    else return 0;
+}
+// One step earlier: what was read from the row's start moves up by one, behind v0.
+template <int N>
+__device__ __forceinline__ void shift_up(float (&v)[N], float v0)
+{
+#pragma unroll
+    for (int j = N - 1; j > 0; --j) v[j] = v[j - 1];
+    v[0] = v0;
+}
+// The slice from t0 of a row, of which t < 0 and t >= L are not stored.
+template <typename T>
+__device__ __forceinline__ void store_slice_any(T* row, int t0, const float (&o)[8], int nvalid)
+{
+    if (t0 < 0) {   // the first lane of a row off a word
+#pragma unroll
+        for (int j = 1; j < 8; ++j)
+            if (j < nvalid) row[j - 1] = f32_to_io<T>(o[j]);
+    } else {
+        io8<T>::store_elem(row + t0, 0u, io8<T>::pack(o), nvalid);
+    }
 }
 // after issue_window_any: shifts the pieces into place and clears what lies outside the row
 template <typename T, bool NEXT>
 __device__ __forceinline__ void settle_window(window_raw<T>& r, bool has_state, int t0, int L, int W)
 {
     if (t0 + 12 > L) {   // only the last lanes of a row
-        io8<T>::drop(r.cur, t0 - row_piece(t0, 8, L));
+        if (t0 >= 0) io8<T>::drop(r.cur, t0 - row_piece(t0, 8, L));
         if (t0 > 0) io4<T>::drop(r.halo, t0 - 4 - row_piece(t0 - 4, 4, L));
         if (NEXT) io4<T>::drop(r.next, t0 + 8 - row_piece(t0 + 8, 4, L));
     }
@@ -147,23 +181,23 @@ __device__ __forceinline__ void unpack_window(const window_raw<T>& r, int t0, fl
 
 // ---- forward --------------------------------------------------------------------------------
 // One wave per (row, piece); grid = ceil(B*D*pieces / NWAVES) workgroups.
-// Bound by HBM.  ROWS_ANY at 8 x 1536 x 2047 bf16: 60 -> 24 us (2048 steps: 21); its backward kernel 105 -> 55 us
-// (2048 steps: 34): eight misaligned accesses per unit, three of them one-element reads of an initial state that most
-// calls do not have, and in bf16 part of the window goes through 6 KB of LDS, because window_raw is passed by value.
+// Bound by HBM.  ROWS_ANY in the layer at 8 x 1536 x 2047 bf16, us, slices at multiples of eight / on words (see row_phase), with
+// an initial state read only where there is one: 26.0 / 24.8 (2048 steps: 21); its backward kernel 57.8 / 48.0 (2048 steps:
+// 34; part of its window still goes through 6 KB of LDS, because window_raw is passed by value).
 template <typename T, int KIND, bool SILU>
 __global__ __launch_bounds__(THREADS) void conv_fwd_kernel(const ConvArgs a)
 {
     const int lane = threadIdx.x & (WAVE - 1);
-    const int pieces = (a.L + PIECE - 1) / PIECE;
+    const int pieces = row_pieces<T, KIND>(a.L);
     const long unit = (long)blockIdx.x * NWAVES + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     if (unit >= (long)a.B * a.D * pieces) return;
     const long r = unit / pieces;                 // row b*D + d
     const int piece = int(unit - r * pieces);
     const int d = int(r % a.D);
-    const int t0 = piece * PIECE + lane * 8;
+    const T* row = static_cast<const T*>(a.x) + (size_t)r * a.L;
+    const int t0 = piece * PIECE + lane * 8 - row_phase<T, KIND>(row);
     if (t0 >= a.L) return;
 
-    const T* row = static_cast<const T*>(a.x) + (size_t)r * a.L;
     const T* state_row = (a.flags & SS_CONV_HAS_STATE) ? static_cast<const T*>(a.state_in) + (size_t)r * (a.W - 1) : nullptr;
     float k4[TAPS];
     load_taps(a.w, d, a.W, k4);
@@ -175,6 +209,7 @@ __global__ __launch_bounds__(THREADS) void conv_fwd_kernel(const ConvArgs a)
         window_raw<T> wr = issue_window_any<T, false>(row, state_row, t0, a.L, a.W);
         settle_window<T, false>(wr, state_row != nullptr, t0, a.L, a.W);
         unpack_window<T, false>(wr, t0, xs, unused);
+        if (t0 < 0) shift_up(xs, 0.0f);
     } else if constexpr (KIND == ROWS_WHOLE) {
         const rsrc_t brow = make_rsrc(row, row_bytes<T>(a.L));
         const rsrc_t bstate = make_rsrc(state_row ? state_row : row, state_row ? (uint32_t)(a.W - 1) * (uint32_t)sizeof(T) : 0u);
@@ -192,7 +227,7 @@ __global__ __launch_bounds__(THREADS) void conv_fwd_kernel(const ConvArgs a)
     const int nvalid = min(a.L - t0, 8);
     T* const orow = static_cast<T*>(a.out) + (size_t)r * a.L;
     if constexpr (KIND == ROWS_ANY) {
-        io8<T>::store_elem(orow, (uint32_t)t0 * (uint32_t)sizeof(T), io8<T>::pack(o), nvalid);
+        store_slice_any<T>(orow, t0, o, nvalid);
     } else {
         io8<T>::template store<KIND == ROWS_WHOLE>(orow + t0, o, nvalid);
     }
@@ -227,7 +262,7 @@ __global__ __launch_bounds__(THREADS) void conv_bwd_kernel(const ConvArgs a)
     const int lane = threadIdx.x & (WAVE - 1);
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int d = blockIdx.x;
-    const int pieces = (a.L + PIECE - 1) / PIECE;
+    const int pieces = row_pieces<T, KIND>(a.L);
     const int units = a.B * pieces;
     const int stride = gridDim.y * NWAVES;
 
@@ -239,8 +274,8 @@ __global__ __launch_bounds__(THREADS) void conv_bwd_kernel(const ConvArgs a)
     for (int unit = blockIdx.y * NWAVES + wave; unit < units; unit += stride) {
         const int b = unit / pieces, piece = unit - b * pieces;
         const size_t r = (size_t)b * a.D + d;
-        const int t0 = piece * PIECE + lane * 8;
         const T* row = static_cast<const T*>(a.x) + r * a.L;
+        const int t0 = piece * PIECE + lane * 8 - row_phase<T, KIND>(row);
         const T* grow = static_cast<const T*>(a.dout) + r * a.L;
         const T* state_row = (a.flags & SS_CONV_HAS_STATE) ? static_cast<const T*>(a.state_in) + r * (a.W - 1) : nullptr;
         const int nvalid = min(max(a.L - t0, 0), 8);
@@ -250,16 +285,17 @@ __global__ __launch_bounds__(THREADS) void conv_bwd_kernel(const ConvArgs a)
         if constexpr (KIND == ROWS_ANY) {
             const uint32_t esz = (uint32_t)sizeof(T);
             window_raw<T> wr = issue_window_any<T, true>(row, state_row, t0, a.L, a.W);
-            typename io8<T>::raw rg = io8<T>::load_elem(grow, (uint32_t)row_piece(t0, 8, a.L) * esz);
+            typename io8<T>::raw rg = io8<T>::load_elem(grow, (uint32_t)row_piece(max(t0, 0), 8, a.L) * esz);
             typename io4<T>::raw rgn = io4<T>::load_elem(grow, (uint32_t)row_piece(t0 + 8, 4, a.L) * esz);
             settle_window<T, true>(wr, state_row != nullptr, t0, a.L, a.W);
             if (t0 + 12 > a.L) {
-                io8<T>::drop(rg, t0 - row_piece(t0, 8, a.L));
+                if (t0 >= 0) io8<T>::drop(rg, t0 - row_piece(t0, 8, a.L));
                 io4<T>::drop(rgn, t0 + 8 - row_piece(t0 + 8, 4, a.L));
             }
             unpack_window<T, true>(wr, t0, xs, xn);
             io8<T>::unpack(rg, g);
             io4<T>::unpack(rgn, gn);
+            if (t0 < 0) { shift_up(xs, 0.0f); shift_up(g, 0.0f); }
         } else if constexpr (KIND == ROWS_WHOLE) {
             const rsrc_t brow = make_rsrc(row, row_bytes<T>(a.L));
             const rsrc_t bgrow = make_rsrc(grow, row_bytes<T>(a.L));
@@ -321,7 +357,7 @@ __global__ __launch_bounds__(THREADS) void conv_bwd_kernel(const ConvArgs a)
 #pragma unroll
             for (int i = 0; i < TAPS; ++i) gk[i] = fmaf(dv[j], xs[j + i], gk[i]);
         }
-        if constexpr (KIND == ROWS_ANY) io8<T>::store_elem(static_cast<T*>(a.dx) + r * a.L, (uint32_t)t0 * (uint32_t)sizeof(T), io8<T>::pack(o), nvalid);
+        if constexpr (KIND == ROWS_ANY) store_slice_any<T>(static_cast<T*>(a.dx) + r * a.L, t0, o, nvalid);
         else io8<T>::template store<KIND == ROWS_WHOLE>(static_cast<T*>(a.dx) + r * a.L + t0, o, nvalid);
     }
 
@@ -392,7 +428,7 @@ __global__ void conv_step_kernel(T* __restrict__ state, const T* __restrict__ x_
 template <typename T, int KIND>
 hipError_t launch_conv_fwd_t(const ConvArgs& a, hipStream_t st)
 {
-    const long pieces = (a.L + PIECE - 1) / PIECE;
+    const long pieces = row_pieces<T, KIND>(a.L);
     const long units = (long)a.B * a.D * pieces;
     const dim3 grid((unsigned)((units + NWAVES - 1) / NWAVES));
     if (a.flags & SS_CONV_SILU) hipLaunchKernelGGL((conv_fwd_kernel<T, KIND, true>), grid, dim3(THREADS), 0, st, a);
@@ -403,7 +439,7 @@ hipError_t launch_conv_fwd_t(const ConvArgs& a, hipStream_t st)
 template <typename T, int KIND>
 hipError_t launch_conv_bwd_t(const ConvArgs& a, hipStream_t st)
 {
-    const long pieces = (a.L + PIECE - 1) / PIECE;
+    const long pieces = row_pieces<T, KIND>(a.L);
     const long units = (long)a.B * pieces;
     // enough waves to keep every SIMD streaming, but no more splits than there are units
     long nsplit = (8192 + (long)a.D * NWAVES - 1) / ((long)a.D * NWAVES);
