@@ -10,6 +10,8 @@ import shutil
 import subprocess
 from concurrent.futures import ThreadPoolExecutor
 
+from . import isa_check
+
 PKG = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(PKG)
 CSRC = os.path.join(PKG, "csrc")
@@ -24,7 +26,6 @@ HIPCC_FLAGS = [
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",  # no packed-FP32 VALU ops
     "-Wno-unused-command-line-argument",
 ]
-PACKED_FP32_OPS = ("v_pk_fma_f32", "v_pk_mul_f32", "v_pk_add_f32")
 
 
 def sources():
@@ -44,14 +45,18 @@ def _run(cmd, cwd, verbose):
         raise RuntimeError("hipcc failed: " + " ".join(cmd))
 
 
-def _check_no_packed_fp32(directory):
-    """The device code must not contain packed-FP32 arithmetic."""
-    for asm in glob.glob(os.path.join(directory, "*gfx950*.s")):
+def device_assembly(directory=BUILD_DIR):
+    """The device assembly that the compiler left there."""
+    return sorted(glob.glob(os.path.join(directory, "*gfx950*.s")))
+
+
+def _check_device_code(directory):
+    """The device code must not contain what isa_check looks for."""
+    for asm in device_assembly(directory):
         with open(asm) as f:
-            text = f.read()
-        for op in PACKED_FP32_OPS:
-            if op in text:
-                raise RuntimeError("%s found in %s" % (op, asm))
+            found = isa_check.check(f.read())
+        if found:
+            raise RuntimeError("%s: %d findings, the first: %s" % (asm, len(found), found[0]))
 
 
 def build_library(verbose=False, jobs=None):
@@ -67,7 +72,7 @@ def build_library(verbose=False, jobs=None):
 
     with ThreadPoolExecutor(max_workers=jobs or min(8, os.cpu_count() or 1)) as pool:
         objs = list(pool.map(compile_one, sources()))
-    _check_no_packed_fp32(BUILD_DIR)
+    _check_device_code(BUILD_DIR)
     out = os.path.join(BUILD_DIR, "libss_scan.so")
     _run([_hipcc(), "--offload-arch=gfx950", "-shared", "-fPIC", "-o", out] + objs, BUILD_DIR, verbose)
     shutil.copy2(out, LIB)
@@ -81,7 +86,7 @@ def build_microbench(verbose=False):
     out = os.path.join(bdir, "ss_ceilings")
     flags = [f for f in HIPCC_FLAGS if f != "-fPIC"]
     _run([_hipcc()] + flags + ["-save-temps=obj", "-o", out, MICROBENCH_SRC], bdir, verbose)
-    _check_no_packed_fp32(bdir)
+    _check_device_code(bdir)
     shutil.copy2(out, MICROBENCH)
     return MICROBENCH
 

@@ -108,7 +108,8 @@ __device__ __forceinline__ float merge_lanes(float a, float b, int lane)
         float r;
         asm("s_nop 1\n\t"
             "v_add_f32_dpp %0, %1, %1 row_half_mirror row_mask:0xf bank_mask:0x5\n\t"
-            "v_add_f32_dpp %0, %2, %2 row_half_mirror row_mask:0xf bank_mask:0xa"
+            "v_add_f32_dpp %0, %2, %2 row_half_mirror row_mask:0xf bank_mask:0xa\n\t"
+            "s_nop 1"   // the next level's swap, see below
             : "=&v"(r) : "v"(a), "v"(b));
         return r;
     } else if constexpr (LEVEL == 2) {
@@ -124,34 +125,46 @@ __device__ __forceinline__ float merge_lanes(float a, float b, int lane)
         return keep + __uint_as_float(__builtin_amdgcn_update_dpp(0, __float_as_uint(give), ctrl, 0xf, 0xf, true));
     }
 }
-// Levels 0 and 1 of four pairs at once: one wait for all of them.
-template <int LEVEL>
+// Level 0 of four pairs at once: one wait for all of them.
 __device__ __forceinline__ void merge_four(float (&r)[4], const float (&v)[8])
 {
-    if constexpr (LEVEL == 0)
-        asm("s_nop 1\n\t"
-            "v_add_f32_dpp %0, %4, %4 row_ror:8 row_mask:0xf bank_mask:0x3\n\t"
-            "v_add_f32_dpp %1, %6, %6 row_ror:8 row_mask:0xf bank_mask:0x3\n\t"
-            "v_add_f32_dpp %2, %8, %8 row_ror:8 row_mask:0xf bank_mask:0x3\n\t"
-            "v_add_f32_dpp %3, %10, %10 row_ror:8 row_mask:0xf bank_mask:0x3\n\t"
-            "v_add_f32_dpp %0, %5, %5 row_ror:8 row_mask:0xf bank_mask:0xc\n\t"
-            "v_add_f32_dpp %1, %7, %7 row_ror:8 row_mask:0xf bank_mask:0xc\n\t"
-            "v_add_f32_dpp %2, %9, %9 row_ror:8 row_mask:0xf bank_mask:0xc\n\t"
-            "v_add_f32_dpp %3, %11, %11 row_ror:8 row_mask:0xf bank_mask:0xc"
-            : "=&v"(r[0]), "=&v"(r[1]), "=&v"(r[2]), "=&v"(r[3])
-            : "v"(v[0]), "v"(v[1]), "v"(v[2]), "v"(v[3]), "v"(v[4]), "v"(v[5]), "v"(v[6]), "v"(v[7]));
-    else
-        asm("s_nop 1\n\t"
-            "v_add_f32_dpp %0, %4, %4 row_half_mirror row_mask:0xf bank_mask:0x5\n\t"
-            "v_add_f32_dpp %1, %6, %6 row_half_mirror row_mask:0xf bank_mask:0x5\n\t"
-            "v_add_f32_dpp %2, %8, %8 row_half_mirror row_mask:0xf bank_mask:0x5\n\t"
-            "v_add_f32_dpp %3, %10, %10 row_half_mirror row_mask:0xf bank_mask:0x5\n\t"
-            "v_add_f32_dpp %0, %5, %5 row_half_mirror row_mask:0xf bank_mask:0xa\n\t"
-            "v_add_f32_dpp %1, %7, %7 row_half_mirror row_mask:0xf bank_mask:0xa\n\t"
-            "v_add_f32_dpp %2, %9, %9 row_half_mirror row_mask:0xf bank_mask:0xa\n\t"
-            "v_add_f32_dpp %3, %11, %11 row_half_mirror row_mask:0xf bank_mask:0xa"
-            : "=&v"(r[0]), "=&v"(r[1]), "=&v"(r[2]), "=&v"(r[3])
-            : "v"(v[0]), "v"(v[1]), "v"(v[2]), "v"(v[3]), "v"(v[4]), "v"(v[5]), "v"(v[6]), "v"(v[7]));
+    asm("s_nop 1\n\t"
+        "v_add_f32_dpp %0, %4, %4 row_ror:8 row_mask:0xf bank_mask:0x3\n\t"
+        "v_add_f32_dpp %1, %6, %6 row_ror:8 row_mask:0xf bank_mask:0x3\n\t"
+        "v_add_f32_dpp %2, %8, %8 row_ror:8 row_mask:0xf bank_mask:0x3\n\t"
+        "v_add_f32_dpp %3, %10, %10 row_ror:8 row_mask:0xf bank_mask:0x3\n\t"
+        "v_add_f32_dpp %0, %5, %5 row_ror:8 row_mask:0xf bank_mask:0xc\n\t"
+        "v_add_f32_dpp %1, %7, %7 row_ror:8 row_mask:0xf bank_mask:0xc\n\t"
+        "v_add_f32_dpp %2, %9, %9 row_ror:8 row_mask:0xf bank_mask:0xc\n\t"
+        "v_add_f32_dpp %3, %11, %11 row_ror:8 row_mask:0xf bank_mask:0xc"
+        : "=&v"(r[0]), "=&v"(r[1]), "=&v"(r[2]), "=&v"(r[3])
+        : "v"(v[0]), "v"(v[1]), "v"(v[2]), "v"(v[3]), "v"(v[4]), "v"(v[5]), "v"(v[6]), "v"(v[7]));
+}
+// Levels 1, 2 and 3 of its results, to one register.  A lane swap needs two wait states behind the write of either of its
+// registers, and the compiler, which keeps them for its own instructions, does not look into inline assembly: so the swaps
+// stand in the block that writes their operands, two instructions behind the later one.
+__device__ __forceinline__ float merge_eight(const float (&v)[8])
+{
+    float r, x, y, z;
+    asm("s_nop 1\n\t"
+        "v_add_f32_dpp %0, %4, %4 row_half_mirror row_mask:0xf bank_mask:0x5\n\t"
+        "v_add_f32_dpp %1, %6, %6 row_half_mirror row_mask:0xf bank_mask:0x5\n\t"
+        "v_add_f32_dpp %2, %8, %8 row_half_mirror row_mask:0xf bank_mask:0x5\n\t"
+        "v_add_f32_dpp %3, %10, %10 row_half_mirror row_mask:0xf bank_mask:0x5\n\t"
+        "v_add_f32_dpp %0, %5, %5 row_half_mirror row_mask:0xf bank_mask:0xa\n\t"
+        "v_add_f32_dpp %1, %7, %7 row_half_mirror row_mask:0xf bank_mask:0xa\n\t"
+        "v_add_f32_dpp %2, %9, %9 row_half_mirror row_mask:0xf bank_mask:0xa\n\t"
+        "v_add_f32_dpp %3, %11, %11 row_half_mirror row_mask:0xf bank_mask:0xa\n\t"
+        "v_permlane32_swap_b32 %0, %1\n\t"
+        "v_add_f32 %0, %0, %1\n\t"
+        "v_permlane32_swap_b32 %2, %3\n\t"
+        "v_add_f32 %2, %2, %3\n\t"
+        "s_nop 1\n\t"
+        "v_permlane16_swap_b32 %0, %2\n\t"
+        "v_add_f32 %0, %0, %2"
+        : "=&v"(r), "=&v"(x), "=&v"(y), "=&v"(z)
+        : "v"(v[0]), "v"(v[1]), "v"(v[2]), "v"(v[3]), "v"(v[4]), "v"(v[5]), "v"(v[6]), "v"(v[7]));
+    return r;
 }
 // Sums over the 64 rows of a wave of the 16 * SPL values (index e = step * SPL + slot) that a block's steps
 // yield for one of dB, dC.  A group of four steps is merged to one register as soon as it is complete
@@ -162,14 +175,13 @@ __device__ __forceinline__ float merge_group(const float (&v)[RED_VALUES], int l
 {
     auto at = [&](int e) { return v[(e / SPL) * STATES_PER_LANE + e % SPL]; };   // slot k of step j sits at 4 j + k
     if constexpr (SPL == 4) {
-        float a[8], b[4], x[4], y[4];
+        float x[4], y[4];
         const float v0[8] = {v[0], v[1], v[2], v[3], v[4], v[5], v[6], v[7]};
         const float v1[8] = {v[8], v[9], v[10], v[11], v[12], v[13], v[14], v[15]};
-        merge_four<0>(x, v0);
-        merge_four<0>(y, v1);
+        merge_four(x, v0);
+        merge_four(y, v1);
         const float v2[8] = {x[0], x[1], x[2], x[3], y[0], y[1], y[2], y[3]};
-        merge_four<1>(b, v2);
-        return merge_lanes<3>(merge_lanes<2>(b[0], b[1], lane), merge_lanes<2>(b[2], b[3], lane), lane);
+        return merge_eight(v2);
     } else {
         float a[2 * SPL], b[SPL];
 #pragma unroll
