@@ -65,10 +65,11 @@ __device__ __forceinline__ uint32_t f32_to_bf16_bits(float f) { return pack_bf16
 // log(1 + e) = log(w) + log(1 + c / w) = log(w) + c / w to float precision: accurate for every
 // e, however small, with no case split (w = 1 gives e itself).  Above r = 20 softplus(r) = r to
 // float precision (and e^r may overflow, which the select discards); the exponent is capped
-// so that the sigmoid comes out as 1 there instead of inf * 0.
+// so that the sigmoid comes out as 1 there instead of inf * 0.  The cap keeps a NaN (fminf would
+// not), so that a step size without a value is one in every kernel; it costs what fminf does.
 __device__ __forceinline__ void softplus_sigmoid(float r, float& sp, float& sg)
 {
-    const float e = exp2_fast(fminf(r * LOG2E, 64.0f));
+    const float e = exp2_fast(__builtin_elementwise_minimum(r * LOG2E, 64.0f));
     const float w = 1.0f + e;
     const float inv = rcp_fast(w);                 // 1 / (1 + e^r)
     const float c = e - (w - 1.0f);
