@@ -353,6 +353,7 @@ __global__ __launch_bounds__(THREADS) void conv_bwd_kernel(const ConvArgs a)
 #pragma unroll
         for (int j = 0; j < 8; ++j) {
             o[j] = fmaf(k4[0], dv[j + 3], fmaf(k4[1], dv[j + 2], fmaf(k4[2], dv[j + 1], k4[3] * dv[j])));
+            if (KIND == ROWS_ANY && j == 0 && t0 < 0) continue;   // no step of the row: dout is zero there, but the window need not be finite
             gb += dv[j];
 #pragma unroll
             for (int i = 0; i < TAPS; ++i) gk[i] = fmaf(dv[j], xs[j + i], gk[i]);
