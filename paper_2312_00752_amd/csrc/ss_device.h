@@ -268,18 +268,20 @@ __device__ __forceinline__ void store_row16(bf16_t* p, u32x4 v)
     }
 }
 // Eight elements from p, in two halves so that nothing waits between the request and the use: the four words from the one
-// that p lies in, and the eighth element (both inside the eight elements or the word before them, which holds p's
-// predecessor); shift_row16 puts them in place.
-__device__ __forceinline__ void load_row16(const bf16_t* p, u32x4& d, uint32_t& last)
+// that p lies in, and the eighth element; shift_row16 puts them in place.  The word holds p's predecessor, which must be
+// memory of the same tensor: at the tensor's first element the words are read from p itself, off a word.
+__host__ __device__ __forceinline__ uintptr_t row16_words(uintptr_t p, uintptr_t first) { return (p & ~uintptr_t(3)) > first ? (p & ~uintptr_t(3)) : first; }
+__device__ __forceinline__ void load_row16(const bf16_t* p, const bf16_t* first, u32x4& d, uint32_t& last)
 {
-    d = *reinterpret_cast<const elem_aligned<u32x4, 4>::type*>(reinterpret_cast<uintptr_t>(p) & ~uintptr_t(3));
+    d = *reinterpret_cast<const elem_aligned<u32x4, 2>::type*>(row16_words(reinterpret_cast<uintptr_t>(p), reinterpret_cast<uintptr_t>(first)));
     last = p[7];
 }
-__device__ __forceinline__ u32x4 shift_row16(const bf16_t* p, u32x4 d, uint32_t last)
+__device__ __forceinline__ u32x4 shift_row16(const bf16_t* p, const bf16_t* first, u32x4 d, uint32_t last)
 {
-    const uint32_t s = off_word(p) ? 16u : 0u;
+    const bool shifted = off_word(p) && p != first;
+    const uint32_t s = shifted ? 16u : 0u;
     return u32x4{__builtin_amdgcn_alignbit(d[1], d[0], s), __builtin_amdgcn_alignbit(d[2], d[1], s), __builtin_amdgcn_alignbit(d[3], d[2], s),
-                 off_word(p) ? __builtin_amdgcn_alignbit(last, d[3], 16) : d[3]};
+                 shifted ? __builtin_amdgcn_alignbit(last, d[3], 16) : d[3]};
 }
 // A piece of `len` steps starting at t of a row of L >= len steps: where to read it so that the access stays
 // inside the row.  A piece that ends past the row is read from L - len; dropping its first t - row_piece(t)

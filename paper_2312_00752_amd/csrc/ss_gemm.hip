@@ -879,7 +879,7 @@ __global__ void __launch_bounds__(256) gemm_cols_add_kernel(const bf16_t* __rest
         };
 #pragma unroll
         for (int e = 0; e < 2; ++e) {
-            if constexpr (RAG) load_row16(prev_at(e), prev[e], last[e]);
+            if constexpr (RAG) load_row16(prev_at(e), Out, prev[e], last[e]);
             else prev[e] = *reinterpret_cast<const u32x4*>(prev_at(e));
         }
         f32x4_t acc[4];
@@ -902,7 +902,7 @@ __global__ void __launch_bounds__(256) gemm_cols_add_kernel(const bf16_t* __rest
             const float4 hi = *reinterpret_cast<const float4*>(&Os[row][8 * pc + 4]);
             float r[8] = {lo.x, lo.y, lo.z, lo.w, hi.x, hi.y, hi.z, hi.w};
             if constexpr (RAG) {
-                prev[e] = shift_row16(prev_at(e), prev[e], last[e]);
+                prev[e] = shift_row16(prev_at(e), Out, prev[e], last[e]);
                 if (n0 + 64 > N) prev[e] = cut(prev[e], n0 + 8 * pc, N);
             }
 #pragma unroll
