@@ -323,7 +323,6 @@ __device__ __forceinline__ void pair_rows(uint4 lo, uint4 hi, uint4& out0, uint4
 // slab, 100 KB of LDS traffic per step and workgroup against 40: dW_dt and dW_x of 8 x 4096 x 2048 55 and 58 us,
 // now 48 and 58; of 8 x 1536 x 2047 44 and 45, now 30 and 44; of 2 x 5120 x 4096 74 and 89, now 52 and 63.)
 constexpr int PD = 4;
-constexpr long COLS_WGS = 512;
 constexpr long ROWS_MIN_WGS = 512;   // two workgroups of gemm_rows_kernel fit on each of the 256 CUs
 constexpr int ROWS_MIN_SPLIT_K = 4096;   // shorter contractions lose more to the second launch than they gain (K = 1536: 21 -> 25 us)
 
@@ -698,10 +697,11 @@ __global__ void __launch_bounds__(256) rows_reduce_kernel(const float* __restric
 }
 
 // Out (M x N per batch entry, bf16) = W (M x K, contiguous along K) Y (K x N, contiguous along N).
-// grid (N / 256, M / (16 * mtiles), batch) rounded up, mtiles = 16-row tiles of the result per workgroup.  K <= 32 NKS.  Plain:
-// K % 32 == 0, N % 64 == 0, M % 16 == 0, whole 16-byte pieces.
+// Workgroups of one or four waves, of 64 columns each; grid (columns / those of a workgroup, M / (16 * mtiles), batch) rounded up,
+// mtiles = 16-row tiles of the result per workgroup; every wave has columns.  K <= 32 NKS.  Plain: K % 32 == 0, N % 64 == 0,
+// M % 16 == 0, whole 16-byte pieces.
 // Bound by writing Out once, if little else moves.  A wave owns 64 columns and walks the row tiles by itself, without LDS and
-// without a barrier; the four waves of a workgroup are neighbours along N, so that the weights, the same for all four, come
+// without a barrier; four waves of a workgroup are neighbours along N, so that the weights, the same for all four, come
 // from the L2 once per 256 columns (with 64 columns per workgroup they were 256 MB at 8 x 4096 x 2048 against the 134 of Out).
 // The wave's part of Y stays in registers as first operands of the transposed product, whose row r is a column of Y and
 // may be any: a lane reads four columns at eight contraction indices, and a byte permute takes column c's pairs out of
@@ -717,7 +717,7 @@ __global__ void __launch_bounds__(256, 2) gemm_cols_kernel(const bf16_t* __restr
 {
     const int lane = threadIdx.x & 63, g = lane >> 4, j = lane & 15;
     const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int n0 = blockIdx.x * 256 + 64 * w;
+    const int n0 = blockIdx.x * blockDim.x + 64 * w;
     if (n0 >= N) return;   // uniform; no barrier below
     const long b = blockIdx.z;
     const int KS = (K + 31) >> 5;   // 32-wide contraction steps (<= NKS)
@@ -967,10 +967,35 @@ void launch_rows(const GemmArgs& g, const bf16_t* A, bf16_t* C, int S, int parts
         }
     }
 }
-template <bool RAG>
-void launch_cols(const GemmArgs& g, int mtiles, hipStream_t stream)
+// gemm_cols_kernel: 16-row tiles per workgroup, and waves of one.  All waves run at once, at most two per SIMD (2048), since a
+// round more costs what all before it do (4 x 4096 x 1531 in 528 workgroups of four, where 512 fit: 33.4 us, in 480: 28.3); and one per
+// SIMD, for the longest contractions one on every other, where that leaves a wave few tiles, since each wave lays out its columns of Y
+// first.  us, waves on half of the SIMDs / one / two per SIMD: K = 128, 1 x 4096 x 256 (2 tiles) 3.7 / 4.4 / -, 1 x 4096 x 1024 - / 6.9 / 8.4,
+// 64 x 4096 x 64 (one: 16 tiles) - / 15.8 / 16.5, off whole lines 64 x 4096 x 16 - / 17.8 / 15.1; K = 48, 4 x 1536 x 512 (one: 3 tiles)
+// - / 5.0 / 5.1, 64 x 1536 x 64 (6) - / 7.2 / 6.7.
+// One wave to a workgroup balances better (1 x 5120 x 256 5.0 / 4.4 us); four together, where the strips of 64 columns come in whole fours,
+// if the weights are read often or rows of the result share cache lines (8 x 4096 x 250 12.2 / 13.4).
+// (Counted in workgroups of four before, empty waves included, us, before / now: 64 x 1536 x 64 9.9 / 6.8, 1 x 5120 x 256 6.7 / 4.4,
+// 2 x 4096 x 1531 23.4 / 19.4; but 64 x 4096 x 128 23.6 / 24.2.)
+void cols_shares(const GemmArgs& g, int& mtiles, int& waves)
 {
-    const dim3 grid((unsigned)((g.N + 255) / 256), (unsigned)(((g.M + 15) / 16 + mtiles - 1) / mtiles), (unsigned)g.batch);
+    const long strips = tiles64(g.N), mt = (g.M + 15) / 16;
+    const bool whole_lines = g.N % 64 == 0 && g.ldc % 64 == 0;
+    auto share = [&](long most) {
+        const long parts = std::max(1L, most / (strips * g.batch));   // of the row tiles, per 64 columns
+        return (mt + parts - 1) / parts;
+    };
+    const long few = g.K <= 32 ? 1 : (g.K <= 96 ? 3 : (whole_lines ? 16 : 6));
+    long tiles = share(1024);
+    if (g.K > 96 && share(512) <= 4) tiles = share(512);
+    else if (tiles > few) tiles = share(2048);
+    mtiles = (int)std::min(64L, tiles);
+    waves = strips % 4 == 0 && (!whole_lines || mtiles > 8) ? 4 : 1;
+}
+template <bool RAG>
+void launch_cols(const GemmArgs& g, int mtiles, int waves, hipStream_t stream)
+{
+    const dim3 grid((unsigned)(tiles64(g.N) / waves), (unsigned)(((g.M + 15) / 16 + mtiles - 1) / mtiles), (unsigned)g.batch);
     const dim3 grid_add(tiles64(g.N), (unsigned)((tiles64(g.M) + mtiles - 1) / mtiles), (unsigned)g.batch);
     const int KS = (g.K + 31) / 32;
     const bf16_t *A = static_cast<const bf16_t*>(g.A), *B = static_cast<const bf16_t*>(g.B);
@@ -979,7 +1004,7 @@ void launch_cols(const GemmArgs& g, int mtiles, hipStream_t stream)
         hipLaunchKernelGGL((gemm_cols_add_kernel<RAG, NKS>), grid_add, dim3(256), 0, stream, A, g.a_m, B, g.b_k, g.b_batch,                    \
                            static_cast<bf16_t*>(g.C), g.ldc, g.c_batch, g.M, g.N, g.K, mtiles);                                               \
     else                                                                                                                                     \
-        hipLaunchKernelGGL((gemm_cols_kernel<RAG, NKS>), grid, dim3(256), 0, stream, A, g.a_m, B, g.b_k, g.b_batch,                            \
+        hipLaunchKernelGGL((gemm_cols_kernel<RAG, NKS>), grid, dim3(64 * waves), 0, stream, A, g.a_m, B, g.b_k, g.b_batch,                     \
                            static_cast<bf16_t*>(g.C), g.ldc, g.c_batch, g.M, g.N, g.K, mtiles)
     if (KS <= 3) { SS_LAUNCH_COLS(3); } else if (KS <= 5) { SS_LAUNCH_COLS(5); } else { SS_LAUNCH_COLS(6); }
 #undef SS_LAUNCH_COLS
@@ -1014,21 +1039,18 @@ int launch_fast(const GemmArgs& g, hipStream_t stream)
     if (g.a_k == 1 && g.b_n == 1 && !g.c_float && g.N >= 8) {
         const bool whole_c = whole && g.N % 64 == 0 && mult8(g.a_m) && mult8(g.b_k) && mult8(g.ldc) && mult8(g.c_batch);
         if (g.K <= SMAX && g.a_batch == 0) {
-            int mtiles = 1;
+            const bool plain = whole_c && g.K % 32 == 0 && g.M % (g.accumulate ? 64 : 16) == 0;
+            int mtiles = 1, waves = 1;
             if (g.accumulate) {
                 // as many 64-row tiles per workgroup as fit, up to 16, while the launch keeps >= 1024 workgroups
                 const long cols = (long)tiles64(g.N) * g.batch, mt = tiles64(g.M);
                 for (int c = 16; c > 1; c >>= 1)
                     if (mt % c == 0 && cols * (mt / c) >= 1024) { mtiles = c; break; }
             } else {
-                // 512 workgroups, two per compute unit, in one round, each with its share of the 16-row tiles (256: 44 -> 68 us at the
-                // headline shape, 768: 46, 1024: 52)
-                const long cols = (long)((g.N + 255) / 256) * g.batch, mt = (g.M + 15) / 16;
-                mtiles = (int)std::min(64L, (cols * mt + COLS_WGS - 1) / COLS_WGS);
+                cols_shares(g, mtiles, waves);
             }
-            const int whole_rows = g.accumulate ? 64 : 16;
-            if (whole_c && g.K % 32 == 0 && g.M % whole_rows == 0) launch_cols<false>(g, mtiles, stream);
-            else launch_cols<true>(g, mtiles, stream);
+            if (plain) launch_cols<false>(g, mtiles, waves, stream);
+            else launch_cols<true>(g, mtiles, waves, stream);
             return hipGetLastError() == hipSuccess ? SS_OK : SS_ERR_LAUNCH;
         }
         if (!g.accumulate) {
