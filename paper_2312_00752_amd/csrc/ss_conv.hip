@@ -31,8 +31,12 @@ struct ConvArgs {
 
 // How the rows of a call are read and written: one element at a time (fewer than 8 steps), in whole aligned
 // 16-byte pieces (L a multiple of 8), or in pieces at element alignment (any other length: the piece that
-// reaches past the end is read from inside the row and shifted into place, see row_piece).
-enum { ROWS_SHORT, ROWS_WHOLE, ROWS_ANY };
+// reaches past the end is read from inside the row and shifted into place, see row_piece), which for an odd number of
+// 16-bit elements can be laid on whole words (see row_phase).
+enum { ROWS_SHORT, ROWS_WHOLE, ROWS_ANY, ROWS_ODD };
+// Pieces of 512 steps that a row is dealt out in.  An odd number of steps leaves room in the last one for the step that
+// ROWS_ODD begins early.
+__host__ __device__ __forceinline__ int row_pieces(int L) { return (L + PIECE - 1) / PIECE; }
 
 
 __device__ __forceinline__ void load_taps(const float* __restrict__ w, int d, int W, float (&k4)[TAPS])
@@ -82,35 +86,35 @@ struct window_raw {
 };
 template <typename T>
 __device__ __forceinline__ uint32_t row_bytes(int L) { return (uint32_t)L * (uint32_t)sizeof(T); }   // rows below 2^31 bytes (checked by the host)
-// pieces of 512 steps a row is dealt out in; a row off a word starts one step before (see row_phase)
-template <typename T, int KIND>
-__host__ __device__ __forceinline__ int row_pieces(int L) { return (L + (KIND == ROWS_ANY && sizeof(T) == 2 ? 1 : 0) + PIECE - 1) / PIECE; }
-template <typename T, bool NEXT>
-__device__ __forceinline__ window_raw<T> issue_window_any(const T* row, const T* state_row, int t0, int L, int W)
-{
-    window_raw<T> r;
-    const uint32_t esz = (uint32_t)sizeof(T);
-    r.cur = io8<T>::load_elem(row, (uint32_t)row_piece(max(t0, 0), 8, L) * esz);
-    r.halo = io4<T>::load_elem(row, (uint32_t)row_piece(max(t0 - 4, 0), 4, L) * esz);
-    if (NEXT) r.next = io4<T>::load_elem(row, (uint32_t)row_piece(t0 + 8, 4, L) * esz);
-    for (int j = 0; j < HALO; ++j) r.st[j] = 0u;
-    if (state_row && t0 <= 0) {   // W - 1 samples
-#pragma unroll
-        for (int j = 0; j < HALO; ++j) {
-            const T v = state_row[max(min(j - (TAPS - W), W - 2), 0)];
-            if constexpr (sizeof(T) == 2) r.st[j] = v; else r.st[j] = __float_as_uint(v);
-        }
-    }
-    return r;
-}
-// ROWS_ANY, 16-bit elements: how many elements a row starts off a whole 32-bit word.  Slices start that many steps earlier, the
+// ROWS_ODD: how many elements a row starts off a whole 32-bit word.  Slices start that many steps earlier, the
 // first one of such a row before the row, so that every access lies on words: off them the hardware takes wide accesses much
 // more slowly, and of an odd number of steps every other row is.  (Uniform: a wave works on one row.)
 template <typename T, int KIND>
 __device__ __forceinline__ int row_phase(const T* row)
 {
-    if constexpr (KIND == ROWS_ANY && sizeof(T) == 2) return (int)((reinterpret_cast<uintptr_t>(row) >> 1) & 1);
+    if constexpr (KIND == ROWS_ODD) return (int)((reinterpret_cast<uintptr_t>(row) >> 1) & 1);
     else return 0;
+}
+template <int KIND>
+__device__ __forceinline__ bool before_row(int t0) { return KIND == ROWS_ODD && t0 < 0; }
+template <int KIND>
+__device__ __forceinline__ int slice_start(int t0) { return KIND == ROWS_ODD ? max(t0, 0) : t0; }
+template <typename T, int KIND, bool NEXT>
+__device__ __forceinline__ window_raw<T> issue_window_any(const T* row, const T* state_row, int t0, int L, int W)
+{
+    window_raw<T> r;
+    const uint32_t esz = (uint32_t)sizeof(T);
+    r.cur = io8<T>::load_elem(row, (uint32_t)row_piece(slice_start<KIND>(t0), 8, L) * esz);
+    r.halo = io4<T>::load_elem(row, (uint32_t)row_piece(max(t0 - 4, 0), 4, L) * esz);
+    if (NEXT) r.next = io4<T>::load_elem(row, (uint32_t)row_piece(t0 + 8, 4, L) * esz);
+    // Read by every lane and also without a state: behind a branch it is waited for by itself.
+    const T* const st = state_row ? state_row : row;   // W - 1 samples, or a row of at least 8
+#pragma unroll
+    for (int j = 0; j < HALO; ++j) {
+        const T v = st[max(min(j - (TAPS - W), W - 2), 0)];
+        if constexpr (sizeof(T) == 2) r.st[j] = v; else r.st[j] = __float_as_uint(v);
+    }
+    return r;
 }
 // One step earlier: what was read from the row's start moves up by one, behind v0.
 template <int N>
@@ -121,23 +125,23 @@ __device__ __forceinline__ void shift_up(float (&v)[N], float v0)
     v[0] = v0;
 }
 // The slice from t0 of a row, of which t < 0 and t >= L are not stored.
-template <typename T>
+template <typename T, int KIND>
 __device__ __forceinline__ void store_slice_any(T* row, int t0, const float (&o)[8], int nvalid)
 {
-    if (t0 < 0) {   // the first lane of a row off a word
+    if (before_row<KIND>(t0)) {   // the first lane of a row off a word
 #pragma unroll
         for (int j = 1; j < 8; ++j)
             if (j < nvalid) row[j - 1] = f32_to_io<T>(o[j]);
     } else {
-        io8<T>::store_elem(row + t0, 0u, io8<T>::pack(o), nvalid);
+        io8<T>::store_elem(row, (uint32_t)t0 * (uint32_t)sizeof(T), io8<T>::pack(o), nvalid);
     }
 }
 // after issue_window_any: shifts the pieces into place and clears what lies outside the row
-template <typename T, bool NEXT>
+template <typename T, int KIND, bool NEXT>
 __device__ __forceinline__ void settle_window(window_raw<T>& r, bool has_state, int t0, int L, int W)
 {
     if (t0 + 12 > L) {   // only the last lanes of a row
-        if (t0 >= 0) io8<T>::drop(r.cur, t0 - row_piece(t0, 8, L));
+        if (!before_row<KIND>(t0)) io8<T>::drop(r.cur, t0 - row_piece(t0, 8, L));
         if (t0 > 0) io4<T>::drop(r.halo, t0 - 4 - row_piece(t0 - 4, 4, L));
         if (NEXT) io4<T>::drop(r.next, t0 + 8 - row_piece(t0 + 8, 4, L));
     }
@@ -181,14 +185,13 @@ __device__ __forceinline__ void unpack_window(const window_raw<T>& r, int t0, fl
 
 // ---- forward --------------------------------------------------------------------------------
 // One wave per (row, piece); grid = ceil(B*D*pieces / NWAVES) workgroups.
-// Bound by HBM.  ROWS_ANY in the layer at 8 x 1536 x 2047 bf16, us, slices at multiples of eight / on words (see row_phase), with
-// an initial state read only where there is one: 26.0 / 24.8 (2048 steps: 21); its backward kernel 57.8 / 48.0 (2048 steps:
-// 34; part of its window still goes through 6 KB of LDS, because window_raw is passed by value).
+// Bound by HBM.  In the layer at 8 x 1536 x 2047 bf16, us, ROWS_ANY / ROWS_ODD: 26.0 / 24.8 (2048 steps: 21); its backward kernel
+// 57.8 / 48.0 (2048 steps: 34; part of its window still goes through 6 KB of LDS, because window_raw is passed by value).
 template <typename T, int KIND, bool SILU>
 __global__ __launch_bounds__(THREADS) void conv_fwd_kernel(const ConvArgs a)
 {
     const int lane = threadIdx.x & (WAVE - 1);
-    const int pieces = row_pieces<T, KIND>(a.L);
+    const int pieces = row_pieces(a.L);
     const long unit = (long)blockIdx.x * NWAVES + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     if (unit >= (long)a.B * a.D * pieces) return;
     const long r = unit / pieces;                 // row b*D + d
@@ -204,12 +207,12 @@ __global__ __launch_bounds__(THREADS) void conv_fwd_kernel(const ConvArgs a)
     const float bias = (a.flags & SS_CONV_HAS_BIAS) ? a.bias[d] : 0.0f;
 
     float xs[HALO + 8];
-    if constexpr (KIND == ROWS_ANY) {
+    if constexpr (KIND == ROWS_ANY || KIND == ROWS_ODD) {
         float unused[4];
-        window_raw<T> wr = issue_window_any<T, false>(row, state_row, t0, a.L, a.W);
-        settle_window<T, false>(wr, state_row != nullptr, t0, a.L, a.W);
+        window_raw<T> wr = issue_window_any<T, KIND, false>(row, state_row, t0, a.L, a.W);
+        settle_window<T, KIND, false>(wr, state_row != nullptr, t0, a.L, a.W);
         unpack_window<T, false>(wr, t0, xs, unused);
-        if (t0 < 0) shift_up(xs, 0.0f);
+        if (before_row<KIND>(t0)) shift_up(xs, 0.0f);
     } else if constexpr (KIND == ROWS_WHOLE) {
         const rsrc_t brow = make_rsrc(row, row_bytes<T>(a.L));
         const rsrc_t bstate = make_rsrc(state_row ? state_row : row, state_row ? (uint32_t)(a.W - 1) * (uint32_t)sizeof(T) : 0u);
@@ -226,8 +229,8 @@ __global__ __launch_bounds__(THREADS) void conv_fwd_kernel(const ConvArgs a)
     }
     const int nvalid = min(a.L - t0, 8);
     T* const orow = static_cast<T*>(a.out) + (size_t)r * a.L;
-    if constexpr (KIND == ROWS_ANY) {
-        store_slice_any<T>(orow, t0, o, nvalid);
+    if constexpr (KIND == ROWS_ANY || KIND == ROWS_ODD) {
+        store_slice_any<T, KIND>(orow, t0, o, nvalid);
     } else {
         io8<T>::template store<KIND == ROWS_WHOLE>(orow + t0, o, nvalid);
     }
@@ -262,7 +265,7 @@ __global__ __launch_bounds__(THREADS) void conv_bwd_kernel(const ConvArgs a)
     const int lane = threadIdx.x & (WAVE - 1);
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int d = blockIdx.x;
-    const int pieces = row_pieces<T, KIND>(a.L);
+    const int pieces = row_pieces(a.L);
     const int units = a.B * pieces;
     const int stride = gridDim.y * NWAVES;
 
@@ -282,20 +285,20 @@ __global__ __launch_bounds__(THREADS) void conv_bwd_kernel(const ConvArgs a)
 
         float xs[HALO + 8], g[8], dv[8 + HALO];
         float xn[4] = {0.f, 0.f, 0.f, 0.f}, gn[4] = {0.f, 0.f, 0.f, 0.f};   // x and dout of the 4 steps after the slice (8 steps and more)
-        if constexpr (KIND == ROWS_ANY) {
+        if constexpr (KIND == ROWS_ANY || KIND == ROWS_ODD) {
             const uint32_t esz = (uint32_t)sizeof(T);
-            window_raw<T> wr = issue_window_any<T, true>(row, state_row, t0, a.L, a.W);
-            typename io8<T>::raw rg = io8<T>::load_elem(grow, (uint32_t)row_piece(max(t0, 0), 8, a.L) * esz);
+            window_raw<T> wr = issue_window_any<T, KIND, true>(row, state_row, t0, a.L, a.W);
+            typename io8<T>::raw rg = io8<T>::load_elem(grow, (uint32_t)row_piece(slice_start<KIND>(t0), 8, a.L) * esz);
             typename io4<T>::raw rgn = io4<T>::load_elem(grow, (uint32_t)row_piece(t0 + 8, 4, a.L) * esz);
-            settle_window<T, true>(wr, state_row != nullptr, t0, a.L, a.W);
+            settle_window<T, KIND, true>(wr, state_row != nullptr, t0, a.L, a.W);
             if (t0 + 12 > a.L) {
-                if (t0 >= 0) io8<T>::drop(rg, t0 - row_piece(t0, 8, a.L));
+                if (!before_row<KIND>(t0)) io8<T>::drop(rg, t0 - row_piece(t0, 8, a.L));
                 io4<T>::drop(rgn, t0 + 8 - row_piece(t0 + 8, 4, a.L));
             }
             unpack_window<T, true>(wr, t0, xs, xn);
             io8<T>::unpack(rg, g);
             io4<T>::unpack(rgn, gn);
-            if (t0 < 0) { shift_up(xs, 0.0f); shift_up(g, 0.0f); }
+            if (before_row<KIND>(t0)) { shift_up(xs, 0.0f); shift_up(g, 0.0f); }
         } else if constexpr (KIND == ROWS_WHOLE) {
             const rsrc_t brow = make_rsrc(row, row_bytes<T>(a.L));
             const rsrc_t bgrow = make_rsrc(grow, row_bytes<T>(a.L));
@@ -353,12 +356,12 @@ __global__ __launch_bounds__(THREADS) void conv_bwd_kernel(const ConvArgs a)
 #pragma unroll
         for (int j = 0; j < 8; ++j) {
             o[j] = fmaf(k4[0], dv[j + 3], fmaf(k4[1], dv[j + 2], fmaf(k4[2], dv[j + 1], k4[3] * dv[j])));
-            if (KIND == ROWS_ANY && j == 0 && t0 < 0) continue;   // no step of the row: dout is zero there, but the window need not be finite
+            if (j == 0 && before_row<KIND>(t0)) continue;   // no step of the row: dout is zero there, but the window need not be finite
             gb += dv[j];
 #pragma unroll
             for (int i = 0; i < TAPS; ++i) gk[i] = fmaf(dv[j], xs[j + i], gk[i]);
         }
-        if constexpr (KIND == ROWS_ANY) store_slice_any<T>(static_cast<T*>(a.dx) + r * a.L, t0, o, nvalid);
+        if constexpr (KIND == ROWS_ANY || KIND == ROWS_ODD) store_slice_any<T, KIND>(static_cast<T*>(a.dx) + r * a.L, t0, o, nvalid);
         else io8<T>::template store<KIND == ROWS_WHOLE>(static_cast<T*>(a.dx) + r * a.L + t0, o, nvalid);
     }
 
@@ -429,7 +432,7 @@ __global__ void conv_step_kernel(T* __restrict__ state, const T* __restrict__ x_
 template <typename T, int KIND>
 hipError_t launch_conv_fwd_t(const ConvArgs& a, hipStream_t st)
 {
-    const long pieces = row_pieces<T, KIND>(a.L);
+    const long pieces = row_pieces(a.L);
     const long units = (long)a.B * a.D * pieces;
     const dim3 grid((unsigned)((units + NWAVES - 1) / NWAVES));
     if (a.flags & SS_CONV_SILU) hipLaunchKernelGGL((conv_fwd_kernel<T, KIND, true>), grid, dim3(THREADS), 0, st, a);
@@ -440,7 +443,7 @@ hipError_t launch_conv_fwd_t(const ConvArgs& a, hipStream_t st)
 template <typename T, int KIND>
 hipError_t launch_conv_bwd_t(const ConvArgs& a, hipStream_t st)
 {
-    const long pieces = row_pieces<T, KIND>(a.L);
+    const long pieces = row_pieces(a.L);
     const long units = (long)a.B * pieces;
     // enough waves to keep every SIMD streaming, but no more splits than there are units
     long nsplit = (8192 + (long)a.D * NWAVES - 1) / ((long)a.D * NWAVES);
@@ -456,7 +459,13 @@ hipError_t launch_conv_bwd_t(const ConvArgs& a, hipStream_t st)
 template <typename T>
 hipError_t launch_conv_t(const ConvArgs& a, bool bwd, hipStream_t st)
 {
-    const int kind = a.L % 8 == 0 ? ROWS_WHOLE : (a.L >= 8 ? ROWS_ANY : ROWS_SHORT);
+    // ROWS_ODD from two pieces a row: below, the lane that starts early costs more than the words give (us, ROWS_ANY / ROWS_ODD, buffers
+    // not in a cache, forward: 8 x 4096 x 101 14.5 / 15.3, 16 x 2048 x 515 28.5 / 29.1, 4 x 4096 x 1531 28.9 / 28.8, 8 x 1536 x 2047
+    // 27.1 / 23.8; backward: 8 x 4096 x 101 36.3 / 38.6, 4 x 4096 x 1531 48.6 / 44.0, 8 x 1536 x 2047 48.9 / 43.5).
+    const bool odd = sizeof(T) == 2 && a.L % 2 == 1 && a.L > 2 * PIECE;
+    const int kind = a.L % 8 == 0 ? ROWS_WHOLE : (a.L < 8 ? ROWS_SHORT : (odd ? ROWS_ODD : ROWS_ANY));
+    if constexpr (sizeof(T) == 2)
+        if (kind == ROWS_ODD) return bwd ? launch_conv_bwd_t<T, ROWS_ODD>(a, st) : launch_conv_fwd_t<T, ROWS_ODD>(a, st);
     if (kind == ROWS_WHOLE) return bwd ? launch_conv_bwd_t<T, ROWS_WHOLE>(a, st) : launch_conv_fwd_t<T, ROWS_WHOLE>(a, st);
     if (kind == ROWS_ANY) return bwd ? launch_conv_bwd_t<T, ROWS_ANY>(a, st) : launch_conv_fwd_t<T, ROWS_ANY>(a, st);
     return bwd ? launch_conv_bwd_t<T, ROWS_SHORT>(a, st) : launch_conv_fwd_t<T, ROWS_SHORT>(a, st);

@@ -13,7 +13,7 @@ pytestmark = pytest.mark.gpu
 
 @pytest.mark.parametrize("io", ["bf16", "f32"])
 @pytest.mark.parametrize("at", [0, 1, 2])
-@pytest.mark.parametrize("seqlen", [9, 513])
+@pytest.mark.parametrize("seqlen", [9, 513, 1025, 1039])
 def test_window_with_infinities(seqlen, at, io):
     w = make_conv_inputs(1, 4, seqlen, 4, io, seed=seqlen)
     w["state_in"][:, :, at] = np.inf
