@@ -100,7 +100,9 @@ size_t ss_layer_step_scratch_bytes(const ss_layer_step_params *p);
  * the projections become (B, D) x (D, R+2N) and (B, R) x (R, D) products, and Eq. 2a/2b are
  * applied once; constant time and memory per token.  Calls with D >= 8, 8 <= R <= 256 and N <= 16
  * take three launches (both projections on the matrix cores, delta_t formed inside the state
- * update); other calls form the two products with the general projection kernel first.
+ * update), or two with the same results (W = 4, D even, up to four entries, D not too large: the
+ * convolution inside the first projection, and the window slides in the last launch); other calls
+ * form the two products with the general projection kernel first.
  * Deterministic either way.  h, W_x and W_dt are 16-byte aligned; a call that is refused has
  * touched neither h nor conv_state. */
 int ss_layer_step(const ss_layer_step_params *p, void *stream);

@@ -153,9 +153,9 @@ int launch_xproj_decode(const void* u, const void* W, float* P, int nb, int nm, 
 // taps are read once per workgroup; the workgroups of the first column tile also leave u in memory for the step
 // kernel.  The window is only read: other column tiles form the same u, so the step kernel, the next launch, slides it.  What
 // the column tiles repeat is a few multiply-adds and reads from the L2; what it saves is a launch that the product waits for.  That
-// pays for up to four entries, where a call is launches and latency: us per call, from Python, D 4096 bf16, batch 1,
-// 16.6 -> 15.3; replayed from a HIP graph, three launches / two, batch 1, 2, 4: D 4096 9.76 / 9.77, 11.3 / 10.6, 12.1 / 11.3;
-// D 1536, batch 1, 4: 8.2 / 7.5, 9.8 / 9.2; float32, D 4096, batch 1, 4: 13.2 / 12.5, 15.7 / 15.8; but batch 8: 12.6 / 13.6, 64: 18.3 / 18.7.
+// pays where a call is launches and latency (conv_in_xproj).  us per call from Python, D 4096 bf16, batch 1, three launches / two:
+// 15.7 / 12.9; replayed from a HIP graph, batch 1, 2, 4: D 4096 bf16 9.8 / 8.7, 11.2 / 10.5, 12.2 / 11.3, D 1536 8.3 / 7.2, 8.7 / 7.9,
+// 9.8 / 9.0; but batch 8: 12.6 / 13.6, 64: 18.3 / 18.7.
 // Values, and the order of every sum, are those of three launches.  ROWS: entries a thread's loads are issued for together.
 constexpr int CX_BATCH = 4;
 template <typename T> constexpr int CX_COLS = 3072 / (int)sizeof(T);   // channels staged at a time: 49 KB of LDS
@@ -272,6 +272,17 @@ int launch_conv_xproj_rows(const ss_layer_step_params* p, void* u, float* P, hip
     else
         hipLaunchKernelGGL((conv_xproj_decode_kernel<T, true, ROWS>), grid, block, 0, st, win, x, p->conv_w, p->conv_b, static_cast<T*>(u), W, P, nb, nm, D);
     return hipGetLastError() == hipSuccess ? SS_OK : SS_ERR_LAUNCH;
+}
+// Whether it is taken: width 4, an even number of channels and up to CX_BATCH entries, as long as a part's channels are staged in one
+// round (float32 D <= 3072, 16-bit 6144); a second one waits for the first, which one entry alone bears up to 5 KB a part.  us, three
+// launches / two, from a HIP graph: float32, batch 2 and 4, D 3072 13.0 / 11.9, 15.2 / 14.5, D 5120 15.7 / 16.3, 16.7 / 17.1, D 8192
+// 18.2 / 21.7, 19.5 / 22.8; batch 1, D 5120 14.3 / 13.7, D 6400 13.8 / 14.8; bf16, batch 2 and 4, D 6144 12.2 / 11.8, 13.2 / 12.7, D 6400
+// 11.6 / 12.0, 12.5 / 13.0; batch 1, D 8192 12.3 / 11.9.
+template <typename T>
+bool conv_in_xproj(const ss_layer_step_params* p)
+{
+    const size_t part = ((size_t)p->dim + XP_NPARTS - 1) / XP_NPARTS * sizeof(T);
+    return p->conv_width == 4 && p->dim % 2 == 0 && p->batch <= CX_BATCH && part <= (p->batch == 1 ? 5120 : CX_COLS<T> * sizeof(T));
 }
 template <typename T>
 int launch_conv_xproj(const ss_layer_step_params* p, void* u, float* P, hipStream_t st)
@@ -645,7 +656,7 @@ int ss_layer_step(const ss_layer_step_params* p, void* stream)
         return SS_ERR_NULL;
     const bool bf16 = p->io_dtype == SS_BF16;
     const size_t esz = bf16 ? 2 : 4;
-    // all that any of the launches would refuse: the first one already slides conv_state
+    // all that any of the launches would refuse: a call that is refused has touched neither h nor conv_state
     if (!aligned_to(p->W_x, 16) || !aligned_to(p->W_dt, 16) || !aligned_to(p->h, 16)) return SS_ERR_ALIGN;
     if (!aligned_to(p->z_t, esz) || !aligned_to(p->out_t, esz)) return SS_ERR_ALIGN;
     if (!aligned_to(p->dt_bias, 4) || !aligned_to(p->A, 4) || !aligned_to(p->Dskip, 4)) return SS_ERR_ALIGN;
@@ -673,10 +684,10 @@ int ss_layer_step(const ss_layer_step_params* p, void* stream)
     s.out_t = p->out_t;
 
     // both projections on the matrix cores, delta_t = W_dt r_t inside the state-update kernel, no atomics: two launches with the
-    // convolution inside the first projection (width 4, an even number of channels, up to CX_BATCH entries), three otherwise
+    // convolution inside the first projection (conv_in_xproj), three otherwise
     if (D >= 8 && R >= 8 && R <= 256 && N <= 16) {
         if ((long)B * D >= 0x7fffffffL) return SS_ERR_UNSUPPORTED;
-        if (p->conv_width == 4 && D % 2 == 0 && B <= CX_BATCH) {
+        if (bf16 ? conv_in_xproj<ss::bf16_t>(p) : conv_in_xproj<float>(p)) {
             const int rc = bf16 ? launch_conv_xproj<ss::bf16_t>(p, u_t, P_acc, st) : launch_conv_xproj<float>(p, u_t, P_acc, st);
             if (rc != SS_OK) return rc;
             return ss::step_projected(&s, P_acc, p->W_dt, R, Mx, p->conv_state, p->x_t, stream);
