@@ -273,16 +273,18 @@ int launch_conv_xproj_rows(const ss_layer_step_params* p, void* u, float* P, hip
         hipLaunchKernelGGL((conv_xproj_decode_kernel<T, true, ROWS>), grid, block, 0, st, win, x, p->conv_w, p->conv_b, static_cast<T*>(u), W, P, nb, nm, D);
     return hipGetLastError() == hipSuccess ? SS_OK : SS_ERR_LAUNCH;
 }
-// Whether it is taken: width 4, an even number of channels and up to CX_BATCH entries, as long as a part's channels are staged in one
-// round (float32 D <= 3072, 16-bit 6144); a second one waits for the first, which one entry alone bears up to 5 KB a part.  us, three
-// launches / two, from a HIP graph: float32, batch 2 and 4, D 3072 13.0 / 11.9, 15.2 / 14.5, D 5120 15.7 / 16.3, 16.7 / 17.1, D 8192
-// 18.2 / 21.7, 19.5 / 22.8; batch 1, D 5120 14.3 / 13.7, D 6400 13.8 / 14.8; bf16, batch 2 and 4, D 6144 12.2 / 11.8, 13.2 / 12.7, D 6400
-// 11.6 / 12.0, 12.5 / 13.0; batch 1, D 8192 12.3 / 11.9.
+// Whether it is taken: width 4, an even number of channels and up to CX_BATCH entries, up to one and a half rounds of staging (3 KB of a
+// part's channels; the second waits for the first): float32 D <= 4608, 16-bit 9216, one entry alone 5120 and 10240.  Above, a launch
+// less no longer pays even for a caller that is bound by its launches.  us, three launches / two, called from Python (14.4 to 16
+// for three, from host to host): float32, batch 2, D 3584 14.4 / 13.4, D 4608 14.4 to 16.0 / 14.4, D 5120 16.0 / 16.6; bf16, batch 4,
+// D 6400 14.4 / 13.2, D 8192 14.5 to 16.3 / 14.8; from a HIP graph: float32, batch 2, D 3072 13.0 / 11.9, D 4096 14.8 / 15.1, D 8192
+// 18.2 / 21.7; bf16, batch 4, D 6144 13.2 / 12.7, D 8192 13.9 / 14.3; batch 1, float32 D 5120 14.3 / 13.7, D 6400 13.8 / 14.8, bf16 D 8192
+// 12.3 / 11.9.
 template <typename T>
 bool conv_in_xproj(const ss_layer_step_params* p)
 {
     const size_t part = ((size_t)p->dim + XP_NPARTS - 1) / XP_NPARTS * sizeof(T);
-    return p->conv_width == 4 && p->dim % 2 == 0 && p->batch <= CX_BATCH && part <= (p->batch == 1 ? 5120 : CX_COLS<T> * sizeof(T));
+    return p->conv_width == 4 && p->dim % 2 == 0 && p->batch <= CX_BATCH && part <= (p->batch == 1 ? 5120 : 4608);
 }
 template <typename T>
 int launch_conv_xproj(const ss_layer_step_params* p, void* u, float* P, hipStream_t st)
