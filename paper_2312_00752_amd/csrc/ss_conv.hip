@@ -107,12 +107,22 @@ __device__ __forceinline__ window_raw<T> issue_window_any(const T* row, const T*
     r.cur = io8<T>::load_elem(row, (uint32_t)row_piece(slice_start<KIND>(t0), 8, L) * esz);
     r.halo = io4<T>::load_elem(row, (uint32_t)row_piece(max(t0 - 4, 0), 4, L) * esz);
     if (NEXT) r.next = io4<T>::load_elem(row, (uint32_t)row_piece(t0 + 8, 4, L) * esz);
-    // Read by every lane and also without a state: behind a branch it is waited for by itself.
-    const T* const st = state_row ? state_row : row;   // W - 1 samples, or a row of at least 8
+    // The window of W - 1 samples: behind a branch it is waited for by itself, so every lane reads it, and without one the row's start (of
+    // at least 8).  The waves of ROWS_ODD are rarely a row's first and do without.
+    if constexpr (KIND == ROWS_ODD) {
 #pragma unroll
-    for (int j = 0; j < HALO; ++j) {
-        const T v = st[max(min(j - (TAPS - W), W - 2), 0)];
-        if constexpr (sizeof(T) == 2) r.st[j] = v; else r.st[j] = __float_as_uint(v);
+        for (int j = 0; j < HALO; ++j) r.st[j] = 0u;
+        if (state_row && t0 <= 0) {
+#pragma unroll
+            for (int j = 0; j < HALO; ++j) r.st[j] = state_row[max(min(j - (TAPS - W), W - 2), 0)];
+        }
+    } else {
+        const T* const st = state_row ? state_row : row;
+#pragma unroll
+        for (int j = 0; j < HALO; ++j) {
+            const T v = st[max(min(j - (TAPS - W), W - 2), 0)];
+            if constexpr (sizeof(T) == 2) r.st[j] = v; else r.st[j] = __float_as_uint(v);
+        }
     }
     return r;
 }
