@@ -89,7 +89,8 @@ __device__ __forceinline__ void reduce_take(float (*red)[RED_PITCH], float* acc,
 // part of the lanes each cost two issue slots per result; a lane swap, which takes two slots itself, and an add cost
 // three; a quad exchange with its selects three.  So the masked adds stand at the levels with the most results (2.2 slots
 // per value in all; with the swaps first 2.8), and they go four results to a block of instructions, since a DPP read must stay two wait
-// states behind the write of its operand.  Backward and forward of 8 x 4096 x 2048 bf16 955 -> 932 us by both.  (Through the LDS
+// states behind the write of its operand.  Backward and forward of 8 x 4096 x 2048 bf16 955 -> 932 us by both.  (One and two slots go pair
+// by pair: backward of 8 x 1536 x 2048 bf16, 4 and 8 states, 227 -> 220 and 246 -> 248 by the order; in blocks 225 -> 231 and 253 -> 255.  Through the LDS
 // tile above: 1.3 instructions per value, but half of the kernel's LDS traffic, waits for it and four spilled registers: 1045 us.)
 //   level:          0               1               2             3                  4              5
 //   partner:        lane ^ 8        lane ^ 7        lane ^ 32     lane ^ 16          lane ^ 1       lane ^ 2

@@ -80,7 +80,7 @@ __device__ __forceinline__ void softplus_sigmoid(float r, float& sp, float& sg)
 // softplus alone, where no derivative is asked for: max(r, 0) + log(1 + e) with e = e^-|r| <= 1.  w lies between 1 and 2, so
 // 1 / w in the correction c / w (|c| <= 2^-24) may be 1 - e / 2, off by less than a tenth: no reciprocal, no overflow to
 // cap and no case split.  Eleven instructions, two of them transcendental, against twelve with three; its error is that of
-// the form above below r = 0 and half of it above.
+// the form above below r = 0 and no larger above (float32 emulation over 0..20: worst 1.6e-7 / 1.8e-7, rms 2.3e-8 / 4.0e-8).
 __device__ __forceinline__ float softplus(float r)
 {
     const float e = exp2_fast(fabsf(r) * -LOG2E);
