@@ -24,8 +24,8 @@
 //                     the rows of the other; the product is formed transposed, so that a lane holds
 //                     consecutive columns of the result.  With a result that is added to, gemm_cols_add_kernel: 64 x 64
 //                     tiles through LDS.
-// gemm_generic_kernel takes every other stride and dtype (64 x 64 tiles through LDS, float MFMAs): the float32
-// layer, sizes below 8 and the per-token products of more than 256 ranks.
+// float32 products of these shapes go to gemm_f32_kernel; gemm_generic_kernel takes every other stride and dtype (64 x 64
+// tiles through LDS, float MFMAs): sizes below 8, and below 4 in float32.
 #include <hip/hip_runtime.h>
 #include <algorithm>
 #include <type_traits>
@@ -64,6 +64,7 @@ void reduce_parts(const GemmArgs& g, int parts, TC* C, int M, int N, hipStream_t
                        static_cast<const float*>(g.split_ws), parts, C, g.ldc, g.c_batch, M, N, items);
 }
 
+constexpr int SMAX = 192;   // rows of the small operand in one launch of a matrix-core kernel; they are built for 64, 128 and 192 of them
 constexpr int GT = 64;   // tile edge
 constexpr int GK = 32;   // contraction indices per step
 constexpr int GP = GT + 4;   // LDS pitch (floats) of a contraction index's 64 rows or columns
@@ -226,6 +227,232 @@ int launch_generic(const GemmArgs& g, hipStream_t stream)
     return hipGetLastError() == hipSuccess ? SS_OK : SS_ERR_LAUNCH;
 }
 
+// ---- float32 operands -------------------------------------------------------------------------------
+// C (M x N) = A B with A contiguous along the contraction index and B along either: the six products of the float32
+// layer.  Its floor is the float matrix rate (256 multiply-adds per clock and CU), so what matters is that every SIMD has a wave that
+// issues MFMAs back to back: a wave owns 16 MT rows x 64 columns of the result, whose operands it loads straight into the
+// fragments' registers, PD slabs of 16 contraction indices ahead, without LDS or barriers.  A lane's 16-byte piece of an
+// operand that is contiguous along the contraction index holds indices 4 g .. 4 g + 3 of the slab (g = lane / 16); the i-th
+// MFMA of a slab contracts over element i of the four groups, so with B contiguous along N the lane reads row 4 g + i, columns
+// 4 j .. 4 j + 3 (j = lane % 16), one for each of its four column tiles: rows of 256 bytes, and the lane's results are
+// four consecutive columns.
+// KW = 4: the workgroup's waves share a tile and deal out its slabs; their sums are added through LDS in the order of the
+// waves.  Long contractions, where tiles are few.  KW = 1: four tiles one below the other, for short contractions.
+// BK: B contiguous along the contraction index; out_t: the result is stored transposed (the operand with more rows is B then).
+// Through LDS, 64 x 64 per workgroup and one step ahead (gemm_generic_kernel), a launch had one wave per SIMD that
+// waited for LDS, barrier and memory in turn.  us per call, that kernel / this one: W_x u 2 x 4096 x 1024, R = 128 (18 at the peak
+// rate) 114 / 35, 1 x 2560 x 300, R = 80 26.0 / 13.9; W_dt r 1 x 5120 x 3001, R = 160 83 / 64; dW_x 8 x 768 x 4096, R = 24 121 / 47; with
+// shorter chains the error against 64 bits is the same or smaller (W_x u, D = 5120: 1.3e-6 / 4.6e-7).
+template <bool BK, int MT, int KW>
+__global__ void __launch_bounds__(256) gemm_f32_kernel(const GemmArgs g, const int out_t)
+{
+    constexpr int AHEAD = MT <= 2 ? 4 : 3;
+    __shared__ f32x4_t red[KW == 4 ? 3 * 4 * 4 * 64 : 1];
+    const int lane = threadIdx.x & 63, kg = lane >> 4, j = lane & 15;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int n0 = blockIdx.x * 64, m0 = (KW == 4 ? blockIdx.y : blockIdx.y * 4 + wave) * 16 * MT;
+    if (KW == 1 && m0 >= g.M) return;   // uniform; no barriers in this form
+    const long bi = blockIdx.z % g.batch;
+    const int part = blockIdx.z / g.batch, parts = gridDim.z / g.batch;
+    const int slabs = (g.K + 15) / 16, per_part = (slabs + parts - 1) / parts;
+    const int s_end = min(slabs, (part + 1) * per_part);
+    const int s_begin = part * per_part + (KW == 4 ? wave : 0);
+    const float* __restrict__ A = static_cast<const float*>(g.A) + bi * g.a_batch;
+    const float* __restrict__ B = static_cast<const float*>(g.B) + bi * g.b_batch;
+    const int M = g.M, N = g.N, K = g.K;
+    // byte offsets within a batch entry's operand (the launch checks that they fit)
+    uint32_t a_row[MT], b_row[BK ? 4 : 1];
+    const uint32_t b_step = BK ? 0u : (uint32_t)(g.b_k * 4);
+    const int n_at = BK ? n0 + 4 * j : min(n0 + 4 * j, N - 4);   // first of the lane's four columns
+#pragma unroll
+    for (int t = 0; t < MT; ++t) a_row[t] = (uint32_t)(min(m0 + 16 * t + j, M - 1) * g.a_m * 4);
+    if constexpr (BK) {
+#pragma unroll
+        for (int c = 0; c < 4; ++c) b_row[c] = (uint32_t)(min(n_at + c, N - 1) * g.b_n * 4);
+    } else {
+        b_row[0] = (uint32_t)n_at * 4u;
+    }
+    u32x4 a[AHEAD][MT], b[AHEAD][4];
+    f32x4_t acc[MT][4];
+#pragma unroll
+    for (int t = 0; t < MT; ++t)
+#pragma unroll
+        for (int c = 0; c < 4; ++c) acc[t][c] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+    auto load = [&](auto slot, int s) {   // past the last slab: that one again
+        constexpr int S = decltype(slot)::value;
+        const int k = 16 * min(s, s_end - 1) + 4 * kg;
+        const uint32_t ka = (uint32_t)row_piece(k, 4, K) * 4u;
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+            if constexpr (BK) b[S][c] = load_any<u32x4>(B, b_row[c] + ka);
+            else b[S][c] = load_any<u32x4>(B, b_row[0] + (uint32_t)min(k + c, K - 1) * b_step);
+        }
+#pragma unroll
+        for (int t = 0; t < MT; ++t) a[S][t] = load_any<u32x4>(A, a_row[t] + ka);
+    };
+    auto multiply = [&](auto slot, int s) {
+        constexpr int S = decltype(slot)::value;
+        if (16 * (s + 1) > K) {   // uniform: the last slab, zeros past K in both operands
+            const int k = 16 * s + 4 * kg;
+            using piece_f = tile_mma<float>;
+#pragma unroll
+            for (int c = 0; c < 4; ++c) {
+                if constexpr (BK) b[S][c] = piece_f::cut(b[S][c], k, K);
+                else if (k + c >= K) b[S][c] = u32x4{0u, 0u, 0u, 0u};
+            }
+#pragma unroll
+            for (int t = 0; t < MT; ++t) a[S][t] = piece_f::cut(a[S][t], k, K);
+        }
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+#pragma unroll
+            for (int t = 0; t < MT; ++t)
+#pragma unroll
+                for (int c = 0; c < 4; ++c)
+                    acc[t][c] = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(a[S][t][i]),
+                                                                     __uint_as_float(BK ? b[S][c][i] : b[S][i][c]), acc[t][c], 0, 0, 0);
+    };
+    if (s_begin < s_end) {   // uniform
+        load(std::integral_constant<int, 0>{}, s_begin);
+        load(std::integral_constant<int, 1>{}, s_begin + KW);
+        load(std::integral_constant<int, 2>{}, s_begin + 2 * KW);
+        if constexpr (AHEAD == 4) load(std::integral_constant<int, 3>{}, s_begin + 3 * KW);
+        for (int s = s_begin; s < s_end; s += AHEAD * KW) {
+            auto turn = [&](auto slot) {
+                constexpr int S = decltype(slot)::value;
+                if (s + S * KW < s_end) multiply(slot, s + S * KW);   // uniform
+                load(slot, s + (S + AHEAD) * KW);
+            };
+            turn(std::integral_constant<int, 0>{});
+            turn(std::integral_constant<int, 1>{});
+            turn(std::integral_constant<int, 2>{});
+            if constexpr (AHEAD == 4) turn(std::integral_constant<int, 3>{});
+        }
+    }
+    // a tile's results: element r of v[c] is row m_tile + 4 g + r, column n_at + c
+    const bool share = parts > 1;   // this part's share, left for parts_reduce_kernel
+    float* __restrict__ C = share ? static_cast<float*>(g.split_ws) + ((long)part * g.batch + bi) * M * N : static_cast<float*>(g.C) + bi * g.c_batch;
+    const long ldc = share ? (out_t ? M : N) : g.ldc;
+    auto store = [&](const f32x4_t (&v)[4], int m_tile) {
+        const int m = m_tile + 4 * kg;
+        if (out_t) {   // uniform; the launch never asks for it with a result that is added to
+#pragma unroll
+            for (int c = 0; c < 4; ++c) {
+                float* row = C + (long)(n_at + c) * ldc + m;
+                if (n_at + c < n0 + 4 * j || n_at + c >= N) continue;
+                if (m + 4 <= M) store_any(row, 0u, v[c]);
+                else
+#pragma unroll
+                    for (int r = 0; r < 4; ++r)
+                        if (m + r < M) row[r] = v[c][r];
+            }
+            return;
+        }
+        const bool whole = n_at == n0 + 4 * j && n_at + 4 <= N;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            if (m + r >= M) continue;
+            float* row = C + (long)(m + r) * ldc + n_at;
+            f32x4_t x = {v[0][r], v[1][r], v[2][r], v[3][r]};
+            if (whole) {
+                if (g.accumulate) x += load_any<f32x4_t>(row, 0u);
+                store_any(row, 0u, x);
+            } else {
+#pragma unroll
+                for (int c = 0; c < 4; ++c)
+                    if (n_at + c >= n0 + 4 * j && n_at + c < N) row[c] = g.accumulate ? x[c] + row[c] : x[c];
+            }
+        }
+    };
+    if constexpr (KW == 1) {
+#pragma unroll
+        for (int t = 0; t < MT; ++t) store(acc[t], m0 + 16 * t);
+    } else {
+        // four 16-row tiles at a time: wave w adds up the w-th, its own share in the place of its number
+#pragma unroll
+        for (int t0 = 0; t0 < MT; t0 += 4) {
+            if (t0 > 0) __syncthreads();   // the tiles before have been read
+#pragma unroll
+            for (int tt = 0; tt < 4; ++tt)
+                if (t0 + tt < MT && tt != wave) {
+                    const int slot = wave < tt ? wave : wave - 1;
+#pragma unroll
+                    for (int c = 0; c < 4; ++c) red[((slot * 4 + tt) * 4 + c) * 64 + lane] = acc[t0 + tt < MT ? t0 + tt : 0][c];
+                }
+            __syncthreads();
+            if (t0 + wave < MT) {   // uniform
+                f32x4_t v[4];
+#pragma unroll
+                for (int c = 0; c < 4; ++c) {
+                    f32x4_t own = acc[t0][c];
+#pragma unroll
+                    for (int tt = 1; tt < 4; ++tt)
+                        if (t0 + tt < MT && tt == wave) own = acc[t0 + tt < MT ? t0 + tt : 0][c];
+                    f32x4_t others[3];
+#pragma unroll
+                    for (int slot = 0; slot < 3; ++slot) others[slot] = red[((slot * 4 + wave) * 4 + c) * 64 + lane];
+                    v[c] = wave == 0 ? own : others[0];
+                    v[c] += wave == 1 ? own : (wave == 0 ? others[0] : others[1]);
+                    v[c] += wave == 2 ? own : (wave < 2 ? others[1] : others[2]);
+                    v[c] += wave == 3 ? own : others[2];
+                }
+                store(v, m0 + 16 * (t0 + wave));
+            }
+        }
+    }
+}
+
+// Fewer workgroups of four tiles leave half of the chip idle, and waves that share a tile are the faster (W_dt r, R = 80, 1 x 2560 x 300,
+// 50 of them: 12.6 against 8.6 us).
+constexpr long F32_ROWS_MIN_WGS = 128;
+// The float32 kernel for this product, if it is one of its forms; SS_ERR_UNSUPPORTED otherwise (nothing enqueued).
+int launch_f32(const GemmArgs& g0, hipStream_t stream)
+{
+    GemmArgs g = g0;
+    const bool bk = g.b_k == 1;
+    if (g.a_k != 1 || g.K < 4 || g.a_m < 0 || g.b_k < 0 || g.b_n < 0 || !(bk || (g.b_n == 1 && g.N >= 4))) return SS_ERR_UNSUPPORTED;
+    const int out_t = bk && g.M > g.N && !g.accumulate;
+    if (out_t) {
+        std::swap(g.M, g.N);
+        std::swap(g.A, g.B);
+        std::swap(g.a_m, g.b_n);
+        std::swap(g.a_batch, g.b_batch);
+    }
+    // 32-bit byte offsets within a batch entry
+    const double limit = 4294967296.0;
+    if (4.0 * ((double)g.M * g.a_m + g.K) >= limit || 4.0 * (bk ? (double)g.N * g.b_n + g.K : (double)g.K * g.b_k + g.N) >= limit) return SS_ERR_UNSUPPORTED;
+    const long strips = (g.N + 63) / 64;
+    const long my1 = (g.M + 255) / 256;
+    if (!bk && g.K <= SMAX && g.M > SMAX && strips * my1 * g.batch >= F32_ROWS_MIN_WGS) {   // many rows, short contraction
+        if (my1 > 65535) return SS_ERR_UNSUPPORTED;
+        hipLaunchKernelGGL((gemm_f32_kernel<false, 4, 1>), dim3((unsigned)strips, (unsigned)my1, (unsigned)g.batch), dim3(256), 0, stream, g, 0);
+        return hipGetLastError() == hipSuccess ? SS_OK : SS_ERR_LAUNCH;
+    }
+    const int tiles = (g.M + 79) / 80, mt = ((g.M + tiles - 1) / tiles + 15) / 16;   // row tiles of up to 80 (two waves per SIMD), of even height
+    const long my = (g.M + 16 * mt - 1) / (16 * mt);
+    if (my > 65535) return SS_ERR_UNSUPPORTED;
+    // parts of the contraction: two workgroups per CU, while each wave keeps four slabs
+    const size_t items = (size_t)g.batch * g.M * g.N;
+    int parts = 1;
+    if (g.split_ws && !g.accumulate)
+        while (parts < 8 && strips * my * g.batch * parts * 2 <= 512 && g.K / (parts * 2) >= 256 && parts * 2 * items * sizeof(float) <= g.split_ws_bytes) parts *= 2;
+    const int slabs = (g.K + 15) / 16, per = (slabs + parts - 1) / parts;
+    parts = (slabs + per - 1) / per;   // none empty
+    if ((long)parts * g.batch > 65535) parts = 1;
+    const dim3 grid((unsigned)strips, (unsigned)my, (unsigned)(g.batch * parts));
+#define SS_LAUNCH_F32(MT)                                                                                                  \
+    case MT:                                                                                                               \
+        if (bk) hipLaunchKernelGGL((gemm_f32_kernel<true, MT, 4>), grid, dim3(256), 0, stream, g, out_t);                   \
+        else hipLaunchKernelGGL((gemm_f32_kernel<false, MT, 4>), grid, dim3(256), 0, stream, g, 0);                         \
+        break
+    switch (mt) {
+        SS_LAUNCH_F32(1); SS_LAUNCH_F32(2); SS_LAUNCH_F32(3); SS_LAUNCH_F32(4); SS_LAUNCH_F32(5);
+    }
+#undef SS_LAUNCH_F32
+    if (parts > 1) reduce_parts<float>(g, parts, static_cast<float*>(g.C), out_t ? g.N : g.M, out_t ? g.M : g.N, stream);
+    return hipGetLastError() == hipSuccess ? SS_OK : SS_ERR_LAUNCH;
+}
+
 // ---- matrix-core kernels (bf16) -------------------------------------------------------------------
 // Each exists twice.  The plain form takes operands made of whole 16-byte pieces (pitches and batch strides
 // multiples of 8 elements, 16-byte aligned, contraction and columns whole slabs and tiles).  The RAG form takes
@@ -234,7 +461,6 @@ int launch_generic(const GemmArgs& g, hipStream_t stream)
 // place with zeros behind it; rows past the end re-read the last one and what comes of them is not stored.
 // Such sizes (sequences that are not a multiple of 64, widths that are not a multiple of 512 and so ranks that
 // are not a multiple of 16) used to take the general kernel: [r;B;C] and delta of 4 x 4096 x 1531 338 us each.
-constexpr int SMAX = 192;          // rows of the small operand in one launch; kernels are built for 64, 128 and 192 of them
 using mma = tile_mma<bf16_t>;
 constexpr int KSLAB = 64;          // contraction indices per step
 constexpr int KP = KSLAB + 8;      // LDS pitch of a slab row (bf16): 144 bytes, 16-byte aligned, off the banks
@@ -1013,7 +1239,8 @@ void launch_cols(const GemmArgs& g, int mtiles, int waves, hipStream_t stream)
 // The matrix-core kernel for this product, if there is one; SS_ERR_UNSUPPORTED otherwise (nothing enqueued).
 int launch_fast(const GemmArgs& g, hipStream_t stream)
 {
-    if (!g.bf16 || g.K < 8 || g.M / 64 > 65535 || g.N / 64 > 65535) return SS_ERR_UNSUPPORTED;
+    if (!g.bf16) return launch_f32(g, stream);
+    if (g.K < 8 || g.M / 64 > 65535 || g.N / 64 > 65535) return SS_ERR_UNSUPPORTED;
     const bf16_t* A = static_cast<const bf16_t*>(g.A);
     const bf16_t* B = static_cast<const bf16_t*>(g.B);
     const bool whole = al16(g.A) && al16(g.B) && al16(g.C) && mult8(g.a_batch) && mult8(g.b_batch);   // operands made of aligned 16-byte pieces

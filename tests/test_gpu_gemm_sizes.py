@@ -107,3 +107,44 @@ def test_infinities_and_nan_stay_where_they_belong():
     assert (C[0, :, 5] == float("inf")).all()
     C[0, :, 5] = 0
     assert torch.isfinite(C).all()
+
+
+# float32: (batch, D, L, R, Mx) at the edges of 16-row, 64-column and 16-index steps, of row tiles of 80, of four waves' slabs
+F32_SIZES = [(1, 4, 4, 4, 4), (2, 17, 5, 4, 7), (2, 63, 65, 15, 17), (1, 200, 67, 25, 57), (3, 81, 127, 33, 81), (2, 264, 131, 96, 161),
+             (1, 260, 321, 160, 192), (1, 1030, 71, 12, 44), (1, 300, 2050, 191, 223)]
+
+
+@pytest.mark.parametrize("pad", [0, 3])
+@pytest.mark.parametrize("nb,D,L,R,Mx", F32_SIZES)
+def test_float32_products_of_any_size(nb, D, L, R, Mx, pad):
+    f32 = torch.float32
+    draw = lambda *a: _inside(_rand(*a).float() * 1.2345678, pad)
+    u, P, W_x, W_dt, W_xT = draw(nb, D, L, 1), draw(nb, Mx, L, 2), draw(1, Mx, D, 3)[0], draw(1, D, R, 4)[0], draw(1, D, Mx, 5)[0]
+    r = P[:, :R]
+    ws = torch.full((8 * nb * max(Mx * L, Mx * D, D * R) * 4,), 0xFF, dtype=torch.uint8, device=DEV)
+    _check(W_x, u, f32, pad=pad)
+    _check(W_x, u, f32, workspace=ws, pad=pad)
+    _check(W_dt, r, f32, pad=pad)
+    _check(u, r, f32, trans_b=True, workspace=ws, pad=pad)
+    _check(P, u, f32, trans_b=True, workspace=ws, pad=pad)
+    # added to the old value: that sum rounds once more
+    C = _inside(_rand(nb, D, L, 6).float(), pad)
+    old, prod, size = C.cpu().double(), W_xT.cpu().double() @ P.cpu().double(), W_xT.cpu().double().abs() @ P.cpu().double().abs()
+    B.ss_proj_gemm(W_xT, P, C, accumulate=True)
+    torch.cuda.synchronize()
+    assert ((C.cpu().double() - old - prod).abs() <= Mx * 2.0 ** -23 * size + 2.0 ** -24 * (old.abs() + size)).all()
+
+
+def test_float32_infinities_stay_where_they_belong():
+    """The last contraction index, whose step is padded, the last row and the last column hold infinities."""
+    u, W = _rand(1, 71, 77, 13).float(), _rand(1, 19, 71, 14)[0].float()
+    u[0, 70, 5] = u[0, 3, 76] = float("inf")
+    W[:, 70] = W[:, 70].abs() + 0.1
+    W[:, 3] = W[:, 3].abs() + 0.1
+    for X, kw in ((u, {}), (u.transpose(1, 2).contiguous(), {"trans_b": True})):
+        C = torch.empty((1, 19, 77), dtype=torch.float32, device=DEV)
+        B.ss_proj_gemm(W, X, C, **kw)
+        torch.cuda.synchronize()
+        assert (C[0, :, 5] == float("inf")).all() and (C[0, :, 76] == float("inf")).all()
+        C[0, :, 5] = C[0, :, 76] = 0
+        assert torch.isfinite(C).all()
