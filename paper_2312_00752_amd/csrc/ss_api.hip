@@ -268,9 +268,14 @@ int static_scratch(void** out)
 namespace ss {
 
 // The fused projection exists for the plain bf16 kernel on an unsplit sequence of at least 8 steps,
-// with a workspace.  Off whole 8-step slices it is taken for the ranks only that the matrix-core product
-// does not reach: layer forward, us, fused / product and plain scan:
-//   16 x 2047 tokens, D = 4096, R = 128   1025 / 1000      4 x 101 tokens     57 / 55     (2048 tokens 787 / 846)
+// with a workspace.  It is taken up to a rank of 128 on whole 8-step slices, and for the ranks that the matrix-core product does
+// not reach (above 192).  Layer forward, us, fused / product and plain scan:
+//   8 x 2048 tokens, D = 4096, R = 128     419 / 429       16 x 2048 tokens, D = 2048, R = 64   387 / 397
+//   16 x 104 tokens, D = 3072, R = 96       87 / 92        8 x 2048 tokens, D = 3072, R = 96    383 / 377
+// Above 128 the pieces of W_dt take the registers that a second workgroup per CU needs:
+//   6 x 8192 tokens, D = 5120, R = 160    2474 / 1618      16 x 504 tokens    457 / 328      16 x 128 tokens    169 / 131
+// and off whole slices:
+//   16 x 2047 tokens, D = 4096, R = 128   1025 / 1000      4 x 101 tokens     57 / 55
 //   16 x 2047 tokens, D = 5120, R = 160   1701 / 1342      4 x 101 tokens     79 / 68
 //   16 x 701 tokens,  D = 6144, R = 192    856 / 698       4 x 127 tokens    101 / 91
 //   16 x 1001 tokens, D = 6400, R = 200   1297 / 1308      8 x 117 tokens    161 / 489
@@ -279,7 +284,7 @@ bool scan_fwd_fusable(const ss_fwd_params* p, int R)
     if (!p || p->seqlen < 1 || p->io_dtype != SS_BF16 || !stageable(p) || slots(p) > 16) return false;
     if (R < 8 || R % 8 != 0 || R > 256 || (p->flags & SS_EXACT_ZOH_B)) return false;
     if (p->seqlen < 8 || (size_t)p->seqlen * 64 * sizeof(float) >= ((size_t)1 << 31)) return false;
-    if (p->seqlen % 8 != 0 && R <= 192) return false;
+    if (R <= 192 && (R > 128 || p->seqlen % 8 != 0)) return false;
     // eight states or fewer are dealt out to kernels of one or two slots per lane, which are built without the projection
     if (slots(p) <= 8) return false;
     if (plan_segments(p->batch, p->dim, p->seqlen, p->flags).nseg != 1) return false;

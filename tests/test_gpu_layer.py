@@ -192,3 +192,9 @@ def test_layer_steps_replayed_from_a_hip_graph():
         graph.replay()
         torch.cuda.synchronize()
         assert torch.equal(outs, want_out) and torch.equal(h, want_h)
+
+
+@pytest.mark.parametrize("shape", [(3, 120, 200, 16, 128), (3, 120, 200, 16, 136), (2, 104, 330, 12, 192), (2, 104, 330, 16, 200)])
+def test_ranks_on_both_sides_of_the_projection_in_the_scan(shape):
+    batch, seqlen, dim, dstate, rank = shape
+    _check(make_layer_inputs(batch, seqlen, dim, dstate, "bf16", seed=rank + 1, rank=rank))
