@@ -1,4 +1,4 @@
-"""Thin ctypes binding of the C-ABI library declared in ``include/ss_scan.h``, ``include/ss_conv.h`` and ``include/ss_layer.h``.
+"""Thin binding (ctypes, and a compiled module for the hot calls) of the C-ABI library declared in ``include/ss_scan.h``, ``include/ss_conv.h`` and ``include/ss_layer.h``.
 
 Argument marshalling only: every step of the path runs in the library's HIP kernels.
 PyTorch appears here solely as the owner of device memory and streams.  The library must
@@ -167,6 +167,30 @@ def lib():
     return _lib
 
 
+_native = None
+
+
+def _marshal():
+    """The compiled marshalling of the calls that a step or a short sequence consists of (csrc/ss_marshal.cpp).  It serves plain
+    tensors; where it returns None the call goes through the code below it."""
+    global _native
+    if _native is None:
+        torch.Tensor   # its libraries are what the module is linked against
+        try:
+            from . import _marshal as native
+        except ImportError as e:
+            raise RuntimeError("%s cannot be loaded: build it with `python -m paper_2312_00752_amd.build`"
+                               % os.path.join(_PKG, "_marshal.so")) from e
+        _native = native
+    return _native
+
+
+def _result(r):
+    if r.__class__ is int:
+        raise SsError(r)
+    return r
+
+
 class SsError(RuntimeError):
     def __init__(self, code):
         self.code = code
@@ -322,6 +346,13 @@ def ss_scan_fwd(u, delta, A, Bmat, Cmat, Dskip=None, z=None, delta_bias=None, h0
     ``save_for_bwd`` (the default when a workspace is given) the call leaves what
     ``ss_scan_bwd`` needs in it; without, the workspace only serves as scratch that lets
     a long sequence with few rows be split across workgroups."""
+    if out is None and h_last is None and not complex_state and u.is_cuda:
+        flags = ((SS_DELTA_SOFTPLUS if delta_softplus else 0) | (SS_EXACT_ZOH_B if exact_zoh else 0)
+                 | (SS_SAVE_FOR_BWD if save_for_bwd else 0))
+        r = (_native or _marshal()).scan_fwd(u, delta, A, Bmat, Cmat, Dskip, z, delta_bias, h0, workspace, flags,
+                                             bool(return_last_state), _stream(stream))
+        if r is not None:
+            return _result(r)
     p = _fwd_params(u, delta, A, Bmat, Cmat, Dskip, z, delta_bias, h0, delta_softplus, exact_zoh, complex_state)
     state_shape = (p.batch, p.dim, p.dstate) + ((2,) if complex_state else ())
     if out is None:
@@ -368,6 +399,12 @@ def ss_scan_bwd(dout, u, delta, A, Bmat, Cmat, workspace, Dskip=None, z=None, de
     corresponding input was not given).  ``grads``: a dict an earlier call returned; its
     tensors are written again instead of allocating new ones.  Freshly allocated du, ddelta and dz
     are views into one allocation (``empty_channel_skewed``): it lives as long as any of them."""
+    if grads is None and not complex_state and u.is_cuda:
+        flags = (SS_DELTA_SOFTPLUS if delta_softplus else 0) | (SS_EXACT_ZOH_B if exact_zoh else 0)
+        r = (_native or _marshal()).scan_bwd(u, delta, A, Bmat, Cmat, Dskip, z, delta_bias, h0, workspace, dout, dh_last, flags,
+                                             bool(want_dh0), _stream(stream))
+        if r is not None:
+            return _result(r)
     f32 = torch.float32
     q = BwdParams()
     q.fwd = _fwd_params(u, delta, A, Bmat, Cmat, Dskip, z, delta_bias, h0, delta_softplus, exact_zoh, complex_state)
@@ -413,6 +450,12 @@ def ss_step(h, u_t, delta_t, A, B_t, C_t, Dskip=None, z_t=None, delta_bias=None,
             stream=None):
     """Enqueue one recurrent step; ``h`` (B,D,N) float32 is updated in place.  Returns out_t.
     With ``b_fixed`` / ``c_fixed`` B_t / C_t is the time-invariant (D,N) float32 parameter."""
+    if not complex_state and u_t.is_cuda:
+        flags = ((SS_DELTA_SOFTPLUS if delta_softplus else 0) | (SS_EXACT_ZOH_B if exact_zoh else 0)
+                 | (SS_B_FIXED if b_fixed else 0) | (SS_C_FIXED if c_fixed else 0))
+        r = (_native or _marshal()).step(h, u_t, delta_t, A, B_t, C_t, Dskip, z_t, delta_bias, out_t, flags, _stream(stream))
+        if r is not None:
+            return _result(r)
     f32 = torch.float32
     nb, nd, nn = h.shape[:3]
     c2 = (2,) if complex_state else ()
@@ -570,6 +613,11 @@ def ss_layer_fwd(x, z, conv_w, conv_b, W_x, W_dt, dt_bias, A, Dskip, scratch, sa
     """Enqueue the layer's forward pass; ``saved`` (if given) is filled for ``ss_layer_bwd``.
     Returns out, or (out, h_last, conv_state) with ``return_states`` (written into the caller's
     ``h_last`` (B,D,N) float32 and ``conv_state`` (B,D,W-1) tensors if given)."""
+    if out is None and h_last is None and conv_state is None and x.is_cuda:
+        r = (_native or _marshal()).layer_fwd(x, z, conv_w, conv_b, W_x, W_dt, dt_bias, A, Dskip, scratch, saved, bool(return_states),
+                                              _stream(stream))
+        if r is not None:
+            return _result(r)
     p = _layer_params(x, z, conv_w, conv_b, W_x, W_dt, dt_bias, A, Dskip, saved, scratch)
     if out is None:
         out = torch.empty_like(x)
@@ -596,6 +644,11 @@ def ss_layer_step_scratch_bytes(batch, dim, dstate, dt_rank, io_dtype=SS_BF16):
 def ss_layer_step(h, conv_state, x_t, z_t, conv_w, conv_b, W_x, W_dt, dt_bias, A, Dskip, scratch, out_t=None,
                   stream=None):
     """Enqueue one token of the layer; ``h`` (B,D,N) and ``conv_state`` (B,D,W-1) are updated in place."""
+    if x_t.is_cuda:
+        r = (_native or _marshal()).layer_step(h, conv_state, x_t, z_t, conv_w, conv_b, W_x, W_dt, dt_bias, A, Dskip, scratch, out_t,
+                                               _stream(stream))
+        if r is not None:
+            return _result(r)
     f32 = torch.float32
     nb, nd, nn = h.shape
     rank = W_dt.shape[1]
@@ -628,6 +681,10 @@ def ss_layer_step(h, conv_state, x_t, z_t, conv_w, conv_b, W_x, W_dt, dt_bias, A
 
 def ss_layer_bwd(dout, x, z, conv_w, conv_b, W_x, W_dt, dt_bias, A, Dskip, scratch, saved, stream=None):
     """Enqueue the layer's backward pass.  Returns a dict of gradients (weights in float32)."""
+    if x.is_cuda:
+        r = (_native or _marshal()).layer_bwd(x, z, conv_w, conv_b, W_x, W_dt, dt_bias, A, Dskip, scratch, saved, dout, _stream(stream))
+        if r is not None:
+            return _result(r)
     f32 = torch.float32
     q = LayerBwdParams()
     q.fwd = _layer_params(x, z, conv_w, conv_b, W_x, W_dt, dt_bias, A, Dskip, saved, scratch)

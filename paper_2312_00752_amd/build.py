@@ -1,4 +1,5 @@
-"""Build the C-ABI library ``libss_scan.so`` from ``csrc/`` with hipcc for gfx950.
+"""Build the C-ABI library ``libss_scan.so`` from ``csrc/`` with hipcc for gfx950, and ``_marshal.so``, through which
+the binding calls it, with the host compiler.
 
 The library is built in-tree (next to this file) so that it travels with the source
 tree; nothing is compiled at import time.  ``build_microbench`` builds the stand-alone
@@ -16,6 +17,8 @@ PKG = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(PKG)
 CSRC = os.path.join(PKG, "csrc")
 LIB = os.path.join(PKG, "libss_scan.so")
+MARSHAL_SRC = os.path.join(CSRC, "ss_marshal.cpp")
+MARSHAL = os.path.join(PKG, "_marshal.so")
 BUILD_DIR = os.path.join(PKG, "_build")
 MICROBENCH_SRC = os.path.join(PKG, "microbench", "ss_ceilings.hip")
 MICROBENCH = os.path.join(PKG, "microbench", "ss_ceilings")
@@ -42,7 +45,7 @@ def _run(cmd, cwd, verbose):
         print(res.stdout)
         print("\n".join(l for l in res.stderr.splitlines() if "packed-fp32-ops" not in l))
     if res.returncode != 0:
-        raise RuntimeError("hipcc failed: " + " ".join(cmd))
+        raise RuntimeError("compiler failed: " + " ".join(cmd))
 
 
 def device_assembly(directory=BUILD_DIR):
@@ -71,12 +74,33 @@ def build_library(verbose=False, jobs=None):
         return obj
 
     with ThreadPoolExecutor(max_workers=jobs or min(8, os.cpu_count() or 1)) as pool:
+        marshal_obj = pool.submit(_compile_marshal, verbose)
         objs = list(pool.map(compile_one, sources()))
+        marshal_obj = marshal_obj.result()
     _check_device_code(BUILD_DIR)
     out = os.path.join(BUILD_DIR, "libss_scan.so")
     _run([_hipcc(), "--offload-arch=gfx950", "-shared", "-fPIC", "-o", out] + objs, BUILD_DIR, verbose)
     shutil.copy2(out, LIB)
+    _link_marshal(marshal_obj, verbose)
     return LIB
+
+
+def _compile_marshal(verbose):
+    import sysconfig
+    from torch.utils import cpp_extension
+    obj = os.path.join(BUILD_DIR, "ss_marshal.o")
+    inc = [a for d in cpp_extension.include_paths() + [sysconfig.get_paths()["include"], os.path.join(ROOT, "include")] for a in ("-isystem", d)]
+    _run(["g++", "-O2", "-std=c++17", "-fPIC", "-c", "-o", obj, MARSHAL_SRC] + inc, BUILD_DIR, verbose)
+    return obj
+
+
+def _link_marshal(obj, verbose):
+    from torch.utils import cpp_extension
+    out = os.path.join(BUILD_DIR, "_marshal.so")
+    dirs = [a for d in cpp_extension.library_paths() for a in ("-L", d)]
+    _run(["g++", "-shared", "-o", out, obj, "-L", PKG, "-lss_scan"] + dirs + ["-ltorch_python", "-ltorch_cpu", "-lc10", "-Wl,-rpath,$ORIGIN"],
+         BUILD_DIR, verbose)
+    shutil.copy2(out, MARSHAL)
 
 
 def build_microbench(verbose=False):
