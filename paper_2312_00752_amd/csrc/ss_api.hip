@@ -65,12 +65,11 @@ long segment_length(int L, long nseg)
     return len;
 }
 
-SegPlan plan_segments(int B, int D, int L, uint32_t flags)
+SegPlan plan_segments(int B, int D, int L)
 {
     const long wgs = (long)B * ((D + 63) / 64);
     SegPlan s{1, (L + 31) / 32 * 32};
     if (s.seg_len == 0) s.seg_len = 32;
-    if (flags & (SS_B_FIXED | SS_C_FIXED)) return s;   // the time-invariant variants are not split
     if (L < 128) return s;
     // Pick the number of segments that the model says finishes first: the main pass over
     // wgs * nseg workgroups plus the aggregate pass over wgs * (nseg - 1) of them, which costs
@@ -102,7 +101,7 @@ SegPlan plan_segments(int B, int D, int L, uint32_t flags)
 //   with backward: [float checkpoints groups*nck*B*D*16][io pre-gate y B*D*L, only with a gate]
 //                  [seg_h][seg_sumdt][float seg_g nseg*B*D*16]                 (only when split)
 //                  [float dA partials nseg*B*D*16][float dD partials nseg*B*D][float dbias partials nseg*B*D]
-//                  [float dB partials B*D*16][float dC partials B*D*16]    (only for a time-invariant B / C)
+//                  [float dB partials nseg*B*D*16][float dC partials nseg*B*D*16]    (only for a time-invariant B / C)
 //   both end with: [io staged B and C, B * ceil16(slots) * Lp * 2]    (only for a real state with selective B and C)
 // where Lp is L rounded up to a whole 32-step chunk.  The staged copy is written and read by the kernels for fewer than
 // 8 or at least 2^23 steps only (FwdArgs::dpp_ok false); the size of a workspace does not depend on that, so that a
@@ -124,7 +123,9 @@ WsLayout ws_layout(const ss_fwd_params* p, bool for_bwd)
     const size_t rows = (size_t)p->batch * p->dim;
     const size_t esz = p->io_dtype == SS_BF16 ? 2 : 4;
     WsLayout w{};
-    w.plan = plan_segments(p->batch, p->dim, p->seqlen, p->flags);
+    // a forward call with a time-invariant B or C that keeps nothing asks for no scratch, and is not split
+    const bool split_ok = for_bwd || !(p->flags & (SS_B_FIXED | SS_C_FIXED));
+    w.plan = plan_segments(p->batch, p->dim, split_ok ? p->seqlen : 0);
     const size_t ns = (size_t)w.plan.nseg, split = ns > 1 ? 1 : 0;
     size_t off = 0;
     auto take = [&](size_t bytes) { const size_t at = off; off += round_up(bytes, 256); return at; };
@@ -139,9 +140,9 @@ WsLayout ws_layout(const ss_fwd_params* p, bool for_bwd)
     w.dA_off = take(for_bwd ? ns * rows * 16 * sizeof(float) : 0);
     w.dD_off = take(for_bwd ? ns * rows * sizeof(float) : 0);
     w.db_off = take(for_bwd ? ns * rows * sizeof(float) : 0);
-    // per-batch partial sums of the gradient of a time-invariant B / C
-    w.dBf_off = take(for_bwd && (p->flags & SS_B_FIXED) ? rows * 16 * sizeof(float) : 0);
-    w.dCf_off = take(for_bwd && (p->flags & SS_C_FIXED) ? rows * 16 * sizeof(float) : 0);
+    // partial sums of the gradient of a time-invariant B / C, per batch entry and segment
+    w.dBf_off = take(for_bwd && (p->flags & SS_B_FIXED) ? ns * rows * 16 * sizeof(float) : 0);
+    w.dCf_off = take(for_bwd && (p->flags & SS_C_FIXED) ? ns * rows * 16 * sizeof(float) : 0);
     w.Lp = (p->seqlen + 31) / 32 * 32;
     w.bcs_off = take(stageable(p) ? (size_t)p->batch * (((size_t)slots(p) + 15) / 16 * 16) * w.Lp * 2 * esz : 0);
     w.total = off;
@@ -287,7 +288,7 @@ bool scan_fwd_fusable(const ss_fwd_params* p, int R)
     if (R <= 192 && (R > 128 || p->seqlen % 8 != 0)) return false;
     // eight states or fewer are dealt out to kernels of one or two slots per lane, which are built without the projection
     if (slots(p) <= 8) return false;
-    if (plan_segments(p->batch, p->dim, p->seqlen, p->flags).nseg != 1) return false;
+    if (plan_segments(p->batch, p->dim, p->seqlen).nseg != 1) return false;
     return p->workspace && aligned(p->workspace, 256) &&
            p->workspace_bytes >= ws_layout(p, (p->flags & SS_SAVE_FOR_BWD) != 0).total;
 }

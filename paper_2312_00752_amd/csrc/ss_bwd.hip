@@ -581,8 +581,8 @@ __global__ void __launch_bounds__(THREADS, WGS) scan_bwd_kernel(const BwdArgs a)
     if (s_ok) {
         float4* pa = reinterpret_cast<float4*>(a.dA_part + (seg_rows + srow) * NPAD) + w;
         *pa = make_float4(dA[0], dA[1], dA[2], dA[3]);
-        if (BFIX) *(reinterpret_cast<float4*>(a.dBf_part + srow * NPAD) + w) = make_float4(dBf[0], dBf[1], dBf[2], dBf[3]);
-        if (CFIX) *(reinterpret_cast<float4*>(a.dCf_part + srow * NPAD) + w) = make_float4(dCf[0], dCf[1], dCf[2], dCf[3]);
+        if (BFIX) *(reinterpret_cast<float4*>(a.dBf_part + (seg_rows + srow) * NPAD) + w) = make_float4(dBf[0], dBf[1], dBf[2], dBf[3]);
+        if (CFIX) *(reinterpret_cast<float4*>(a.dCf_part + (seg_rows + srow) * NPAD) + w) = make_float4(dCf[0], dCf[1], dCf[2], dCf[3]);
         if (a.dh0 && seg == 0) {
 #pragma unroll
             for (int k = 0; k < STATES_PER_LANE; ++k)
@@ -1076,8 +1076,8 @@ __global__ void __launch_bounds__(THREADS, 2) scan_bwd_dpp_kernel(const BwdArgs 
 // adjoint recurrence g = C dy + abar+ g+ over the segment, from a zero carry (last segment:
 // from dh_last), and leaves the carry abar g at the segment's first step in seg_g.  Needs
 // no states, so it is the forward kernel's loop structure walked backwards: 32-step chunks,
-// dt and dy staged through LDS, C on the scalar path.
-template <typename T, bool VEC, bool FULLN, bool CPLX = false, int SPL = STATES_PER_LANE>
+// dt and dy staged through LDS, C on the scalar path (CFIX: the time-invariant (D,N) parameter, in registers).
+template <typename T, bool VEC, bool FULLN, bool CPLX = false, bool CFIX = false>
 __global__ void __launch_bounds__(THREADS) adjoint_agg_kernel(const BwdArgs a)
 {
     __shared__ __attribute__((aligned(16))) float s_dt[ROWS][TPAD];
@@ -1109,17 +1109,19 @@ __global__ void __launch_bounds__(THREADS) adjoint_agg_kernel(const BwdArgs a)
     const int sd = s_ok ? d0 + lane : f.D - 1;
     const long srow = (long)b * f.D + sd;
     float A2[STATES_PER_LANE], An[STATES_PER_LANE], ag[STATES_PER_LANE];
+    float Cf[STATES_PER_LANE];
     const T* __restrict__ gC[STATES_PER_LANE];
     bool n_ok[STATES_PER_LANE];
 #pragma unroll
     for (int k = 0; k < STATES_PER_LANE; ++k) {
         const int n = slot_state(w, k, f.il);
-        n_ok[k] = n < N && k < SPL;
+        n_ok[k] = n < N;
         const int nc = n_ok[k] ? n : 0;
         An[k] = n_ok[k] ? f.A[(long)sd * NS + nc] : 0.0f;
         A2[k] = An[k] * LOG2E;
         ag[k] = (seg == f.nseg - 1 && n_ok[k] && a.dh_last) ? a.dh_last[srow * NS + nc] : 0.0f;
-        gC[k] = static_cast<const T*>(f.Cm) + (long)b * f.bc_bstride + (long)nc * L;
+        gC[k] = CFIX ? nullptr : static_cast<const T*>(f.Cm) + (long)b * f.bc_bstride + (long)nc * L;
+        Cf[k] = (CFIX && n_ok[k]) ? static_cast<const float*>(f.Cm)[(long)sd * NS + nc] : 0.0f;
     }
     typename io8<T>::raw rd, rz, ro;
     auto issue_loads = [&](int c) {
@@ -1130,11 +1132,12 @@ __global__ void __launch_bounds__(THREADS) adjoint_agg_kernel(const BwdArgs a)
         if (has_z) rz = io8<T>::template load<VEC>(gz + t0, nv);
     };
     issue_loads(c_end - 1);
-    uint32_t touched = touch_bc<T>(f.Cm, f.Cm, b, f.bc_bstride, N, L, w, lane, (c_end - 1) * CHUNK_T);
+    uint32_t touched = 0u;
+    if (!CFIX) touched = touch_bc<T>(f.Cm, f.Cm, b, f.bc_bstride, N, L, w, lane, (c_end - 1) * CHUNK_T);
     for (int c = c_end - 1; c >= c_begin; --c) {
         const int tc = c * CHUNK_T;
         consume_touch(touched);
-        touched = touch_bc<T>(f.Cm, f.Cm, b, f.bc_bstride, N, L, w, lane, (c - 1) * CHUNK_T);
+        if (!CFIX) touched = touch_bc<T>(f.Cm, f.Cm, b, f.bc_bstride, N, L, w, lane, (c - 1) * CHUNK_T);
         const int nv = p_ok ? min(max(L - (tc + pq * SLICE), 0), SLICE) : 0;
         {
             float v8[SLICE], o8[SLICE], z8[SLICE], dt8[SLICE];
@@ -1164,7 +1167,8 @@ __global__ void __launch_bounds__(THREADS) adjoint_agg_kernel(const BwdArgs a)
             bc_group<T> Cg[STATES_PER_LANE];
 #pragma unroll
             for (int k = 0; k < STATES_PER_LANE; ++k)
-                Cg[k] = load_bc<T, VEC, !FULLN>(gC[k], tc + g * GROUP_T, L, n_ok[k]);
+                if (!CFIX) Cg[k] = load_bc<T, VEC, !FULLN>(gC[k], tc + g * GROUP_T, L, n_ok[k]);
+            auto Cval = [&](int k, int j) -> float { return CFIX ? Cf[k] : Cg[k].get(j); };
             const float4 dt4 = *reinterpret_cast<const float4*>(&s_dt[lane][g * GROUP_T]);
             const float4 dy4 = *reinterpret_cast<const float4*>(&s_dy[lane][g * GROUP_T]);
 #pragma unroll
@@ -1174,14 +1178,14 @@ __global__ void __launch_bounds__(THREADS) adjoint_agg_kernel(const BwdArgs a)
 #pragma unroll
                     for (int k = 0; k < STATES_PER_LANE; k += 2) {
                         const cplx ab = complex_decay(dt, A2[k], An[k + 1]);
-                        const float gr = fmaf(Cg[k].get(j), dy, ag[k]), gi = fmaf(-Cg[k + 1].get(j), dy, ag[k + 1]);
+                        const float gr = fmaf(Cval(k, j), dy, ag[k]), gi = fmaf(-Cval(k + 1, j), dy, ag[k + 1]);
                         ag[k] = fmaf(ab.re, gr, ab.im * gi);
                         ag[k + 1] = fmaf(ab.re, gi, -ab.im * gr);
                     }
                 } else {
 #pragma unroll
-                    for (int k = 0; k < SPL; ++k)
-                        ag[k] = exp2_fast(dt * A2[k]) * fmaf(Cg[k].get(j), dy, ag[k]);
+                    for (int k = 0; k < STATES_PER_LANE; ++k)
+                        ag[k] = exp2_fast(dt * A2[k]) * fmaf(Cval(k, j), dy, ag[k]);
                 }
             }
         }
@@ -1444,7 +1448,7 @@ __global__ void __launch_bounds__(64 * FIN_LANES) finalize_kernel(const BwdArgs 
         for (int b = part; b < a.f.B * a.f.nseg; b += FIN_LANES) {  // per segment and batch entry
             const long row = (long)b * a.f.D + dc;
             sA += a.dA_part[row * NPAD + n];
-            if (bfix) sB += a.dBf_part[row * NPAD + n];   // time-invariant B / C are never split: nseg == 1
+            if (bfix) sB += a.dBf_part[row * NPAD + n];
             if (cfix) sC += a.dCf_part[row * NPAD + n];
             if (n < 2) sDb += extra[row];
         }
@@ -1494,7 +1498,7 @@ static bool allow_backward_lds_once(K kern, std::atomic<bool> (&done)[MAX_DEVICE
 }
 
 constexpr unsigned COMPUTE_UNITS = 256;
-// Time-invariant B and / or C (never split): a grid that gives each compute unit no more than one workgroup gains
+// Time-invariant B and / or C: a grid that gives each compute unit no more than one workgroup gains
 // nothing from a kernel that leaves room for two and pays for its 256 registers.  Variants for which that costs
 // something are built both ways; backward call, us, two per unit / one per unit:
 //   workgroups                                 256           512
@@ -1513,11 +1517,21 @@ template <typename T, bool VEC, bool FULLN, bool ZOH, int BCFIX, bool CPLX = fal
 static int launch_scan_bwd_fixed(const BwdArgs& a, dim3 grid, hipStream_t stream)
 {
     if constexpr (WGS == 2 && ONE_WG_WINS<T, VEC, BCFIX, CPLX>)
-        if (grid.x <= COMPUTE_UNITS) return launch_scan_bwd_fixed<T, VEC, FULLN, ZOH, BCFIX, CPLX, 1>(a, grid, stream);
+        if (grid.x * (unsigned)a.f.nseg <= COMPUTE_UNITS) return launch_scan_bwd_fixed<T, VEC, FULLN, ZOH, BCFIX, CPLX, 1>(a, grid, stream);
     auto kern = scan_bwd_kernel<T, VEC, FULLN, ZOH, BCFIX, CPLX, WGS>;
     static std::atomic<bool> lds_ok[MAX_DEVICES];   // this launcher is instantiated once per kernel
     if (!allow_backward_lds_once(reinterpret_cast<const void*>(kern), lds_ok, sizeof(BwdSmem))) return -1;
-    kern<<<dim3(grid.x, 1u), dim3(THREADS), sizeof(BwdSmem), stream>>>(a);
+    if (a.f.nseg > 1) {
+        const dim3 agg((unsigned)grid.x, (unsigned)(a.f.nseg - 1)), block(THREADS);
+        if constexpr (BCFIX & 2) adjoint_agg_kernel<T, VEC, FULLN, CPLX, true><<<agg, block, 0, stream>>>(a);
+        else if constexpr (CPLX) adjoint_agg_kernel<T, VEC, FULLN, true><<<agg, block, 0, stream>>>(a);
+        else if (a.f.vec_ok) adjoint_agg_dpp_kernel<T, STATES_PER_LANE, false><<<agg, block, 0, stream>>>(a);
+        else if (a.f.dpp_ok) adjoint_agg_dpp_kernel<T, STATES_PER_LANE, true><<<agg, block, 0, stream>>>(a);
+        else adjoint_agg_kernel<T, false, false><<<agg, block, 0, stream>>>(a);
+        const long n = (long)a.f.B * a.f.D * NPAD;
+        carry_bwd_kernel<<<dim3((unsigned)((n + 255) / 256)), dim3(256), 0, stream>>>(a);
+    }
+    kern<<<dim3(grid.x, (unsigned)a.f.nseg), dim3(THREADS), sizeof(BwdSmem), stream>>>(a);
     return hipGetLastError() == hipSuccess ? 0 : -1;
 }
 

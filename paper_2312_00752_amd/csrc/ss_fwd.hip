@@ -1246,11 +1246,33 @@ int launch_stage_bc(const FwdArgs& a, void* bcs, int io_dtype, hipStream_t strea
     return hipGetLastError() == hipSuccess ? 0 : -1;
 }
 
+// The aggregate pass of a real state with time-invariant B and / or C.  It has no use for C: with a selective B it is the
+// common path's (or the scalar path's) and with a time-invariant one the kernel that reads neither along the sequence, each
+// given B in the place of C.
+template <typename T, bool VEC, bool FULLN, bool ZOH, int BCFIX>
+static void launch_agg_fixed(const FwdArgs& a, hipStream_t stream)
+{
+    const int groups = (a.D + ROWS - 1) / ROWS;
+    const dim3 grid((unsigned)(a.B * groups), (unsigned)(a.nseg - 1)), block(THREADS);
+    FwdArgs b = a;
+    b.Cm = a.Bm;
+    if constexpr (BCFIX & 1) {
+        scan_fwd_kernel<T, VEC, FULLN, true, ZOH, 3><<<grid, block, 0, stream>>>(b);
+    } else {
+        if (a.vec_ok) scan_fwd_kernel<T, true, false, true, ZOH, 0, false, false, 0, STATES_PER_LANE, true, false><<<grid, block, 0, stream>>>(b);
+        else if (a.dpp_ok) scan_fwd_kernel<T, true, false, true, ZOH, 0, false, false, 0, STATES_PER_LANE, true, true><<<grid, block, 0, stream>>>(b);
+        else scan_fwd_kernel<T, false, false, true, ZOH><<<grid, block, 0, stream>>>(b);
+    }
+    const long n = (long)a.B * a.D * NPAD;
+    carry_fwd_kernel<<<dim3((unsigned)((n + 255) / 256)), dim3(256), 0, stream>>>(a);
+}
+
 template <typename T, bool VEC, bool FULLN, bool ZOH, int BCFIX>
 static void launch_fwd_fixed(const FwdArgs& a, hipStream_t stream)
 {
     const int groups = (a.D + ROWS - 1) / ROWS;
-    scan_fwd_kernel<T, VEC, FULLN, false, ZOH, BCFIX><<<dim3((unsigned)(a.B * groups), 1u), dim3(THREADS), 0, stream>>>(a);
+    if (a.nseg > 1) launch_agg_fixed<T, VEC, FULLN, ZOH, BCFIX>(a, stream);
+    scan_fwd_kernel<T, VEC, FULLN, false, ZOH, BCFIX><<<dim3((unsigned)(a.B * groups), (unsigned)a.nseg), dim3(THREADS), 0, stream>>>(a);
 }
 
 // complex state: first-order B-bar only; selective or time-invariant B / C
@@ -1319,7 +1341,7 @@ static void launch_fwd_scalar(const FwdArgs& a, hipStream_t stream)
     else scan_fwd_kernel<T, false, false, false, ZOH><<<main_grid, block, 0, stream>>>(a);
 }
 
-// complex state and time-invariant B and / or C (the latter never split: the planner keeps nseg == 1 for them)
+// complex state and time-invariant B and / or C
 template <typename T, bool VEC, bool FULLN, bool ZOH>
 static void launch_fwd_variant(const FwdArgs& a, hipStream_t stream)
 {
