@@ -117,7 +117,7 @@ inline bool stageable(const ss_fwd_params* p)
 {
     return !(p->flags & (SS_B_FIXED | SS_C_FIXED | SS_COMPLEX_STATE)) && p->seqlen > 0;
 }
-WsLayout ws_layout(const ss_fwd_params* p, bool for_bwd)
+WsLayout ws_layout(const ss_fwd_params* p, bool for_bwd, int pitch)
 {
     const size_t nck = ((size_t)p->seqlen + SS_CHECKPOINT_STEPS - 1) / SS_CHECKPOINT_STEPS;
     const size_t rows = (size_t)p->batch * p->dim;
@@ -133,7 +133,7 @@ WsLayout ws_layout(const ss_fwd_params* p, bool for_bwd)
     w.ckpt_group = nck * rows * 16 * sizeof(float);
     w.ckpt_off = take(for_bwd ? groups * w.ckpt_group : 0);
     // the pre-gate y: for the backward pass, and as the accumulator across state groups
-    w.y_off = take((for_bwd || groups > 1) && (p->flags & SS_HAS_Z) ? rows * (size_t)p->seqlen * esz : 0);
+    w.y_off = take((for_bwd || groups > 1) && (p->flags & SS_HAS_Z) ? rows * (size_t)pitch * esz : 0);
     w.segh_off = take(split * ns * rows * 16 * sizeof(float));
     w.segdt_off = take(split * ns * rows * sizeof(float));
     w.segg_off = take(for_bwd ? split * ns * rows * 16 * sizeof(float) : 0);
@@ -149,7 +149,7 @@ WsLayout ws_layout(const ss_fwd_params* p, bool for_bwd)
     return w;
 }
 
-int check_fwd(const ss_fwd_params* p, bool for_bwd, bool bc_dense = true)
+int check_fwd(const ss_fwd_params* p, bool for_bwd, int pitch, bool bc_dense = true)
 {
     if (!p) return SS_ERR_NULL;
     if (p->batch < 1 || p->dim < 1 || p->dstate < 1 || p->seqlen < 0) return SS_ERR_SHAPE;
@@ -179,11 +179,11 @@ int check_fwd(const ss_fwd_params* p, bool for_bwd, bool bc_dense = true)
         if (q && !aligned(q, 4)) return SS_ERR_ALIGN;
     if (!for_bwd && !(p->flags & SS_SAVE_FOR_BWD) && slots(p) > 16 && (p->flags & SS_HAS_Z) && p->seqlen > 0) {
         // the pre-gate output is accumulated over the groups of 16 states in the workspace
-        if (!p->workspace || p->workspace_bytes < ws_layout(p, false).total) return SS_ERR_WORKSPACE;
+        if (!p->workspace || p->workspace_bytes < ws_layout(p, false, pitch).total) return SS_ERR_WORKSPACE;
         if (!aligned(p->workspace, 256)) return SS_ERR_ALIGN;
     }
     if (for_bwd || (p->flags & SS_SAVE_FOR_BWD)) {
-        const size_t need = ws_layout(p, true).total;
+        const size_t need = ws_layout(p, true, pitch).total;
         if (!p->workspace || p->workspace_bytes < need) return SS_ERR_WORKSPACE;
         if (!aligned(p->workspace, 256)) return SS_ERR_ALIGN;
     }
@@ -197,7 +197,7 @@ inline bool deals_states(int dpp_ok, uint32_t flags)
     return dpp_ok && !(flags & (SS_EXACT_ZOH_B | SS_B_FIXED | SS_C_FIXED | SS_COMPLEX_STATE));
 }
 
-ss::FwdArgs make_fwd_args(const ss_fwd_params* p, long bc_bstride)
+ss::FwdArgs make_fwd_args(const ss_fwd_params* p, long bc_bstride, int pitch)
 {
     ss::FwdArgs a{};
     a.B = p->batch; a.D = p->dim; a.L = p->seqlen; a.N = slots(p); a.NS = slots(p);
@@ -206,6 +206,7 @@ ss::FwdArgs make_fwd_args(const ss_fwd_params* p, long bc_bstride)
     // 16-byte slices, addressed through per-workgroup buffer resources (64 rows, 31-bit offsets)
     a.dpp_ok = p->seqlen >= 8 && (size_t)p->seqlen * 64 * sizeof(float) < ((size_t)1 << 31);
     a.vec_ok = a.dpp_ok && p->seqlen % 8 == 0;
+    a.Li = pitch;
     a.il = deals_states(a.dpp_ok, p->flags) && a.N < 16;
     a.u = p->u; a.delta = p->delta; a.z = (p->flags & SS_HAS_Z) ? p->z : nullptr;
     a.Bm = p->Bmat; a.Cm = p->Cmat; a.A = p->A;
@@ -280,7 +281,7 @@ namespace ss {
 //   16 x 2047 tokens, D = 5120, R = 160   1701 / 1342      4 x 101 tokens     79 / 68
 //   16 x 701 tokens,  D = 6144, R = 192    856 / 698       4 x 127 tokens    101 / 91
 //   16 x 1001 tokens, D = 6400, R = 200   1297 / 1308      8 x 117 tokens    161 / 489
-bool scan_fwd_fusable(const ss_fwd_params* p, int R)
+bool scan_fwd_fusable(const ss_fwd_params* p, int pitch, int R)
 {
     if (!p || p->seqlen < 1 || p->io_dtype != SS_BF16 || !stageable(p) || slots(p) > 16) return false;
     if (R < 8 || R % 8 != 0 || R > 256 || (p->flags & SS_EXACT_ZOH_B)) return false;
@@ -290,16 +291,23 @@ bool scan_fwd_fusable(const ss_fwd_params* p, int R)
     if (slots(p) <= 8) return false;
     if (plan_segments(p->batch, p->dim, p->seqlen).nseg != 1) return false;
     return p->workspace && aligned(p->workspace, 256) &&
-           p->workspace_bytes >= ws_layout(p, (p->flags & SS_SAVE_FOR_BWD) != 0).total;
+           p->workspace_bytes >= ws_layout(p, (p->flags & SS_SAVE_FOR_BWD) != 0, pitch).total;
 }
 
-static int scan_fwd_impl(const ss_fwd_params* p, long bc_bstride, const void* W_dt, int R, const void* rT, void* stream)
+// Whether rows of delta, ddelta and the saved y may be that far apart: the kernels for any row length take it.
+static bool pitch_ok(const ss_fwd_params* p, int pitch)
 {
-    const int rc = check_fwd(p, false, p && bc_bstride == (long)slots(p) * p->seqlen);
+    return pitch == p->seqlen || (pitch > p->seqlen && p->seqlen >= 8 && p->seqlen % 8 != 0 && stageable(p) && (size_t)pitch * 64 * sizeof(float) < ((size_t)1 << 31));
+}
+
+static int scan_fwd_impl(const ss_fwd_params* p, long bc_bstride, int pitch, const void* W_dt, int R, const void* rT, void* stream)
+{
+    if (p && !pitch_ok(p, pitch)) return SS_ERR_UNSUPPORTED;
+    const int rc = check_fwd(p, false, pitch, p && bc_bstride == (long)slots(p) * p->seqlen);
     if (rc != SS_OK) return rc;
-    ss::FwdArgs a = make_fwd_args(p, bc_bstride);
+    ss::FwdArgs a = make_fwd_args(p, bc_bstride, pitch);
     if (W_dt) {
-        if (!scan_fwd_fusable(p, R) || !aligned(W_dt, 16) || !aligned(rT, 16)) return SS_ERR_UNSUPPORTED;
+        if (!scan_fwd_fusable(p, pitch, R) || !aligned(W_dt, 16) || !aligned(rT, 16)) return SS_ERR_UNSUPPORTED;
         a.W_dt = W_dt; a.rT = rT; a.R = R; a.Rp = (R + 31) / 32 * 32;
     }
     char* ws = static_cast<char*>(p->workspace);
@@ -314,7 +322,7 @@ static int scan_fwd_impl(const ss_fwd_params* p, long bc_bstride, const void* W_
         return true;
     };
     if (p->flags & SS_SAVE_FOR_BWD) {
-        const WsLayout w = ws_layout(p, true);
+        const WsLayout w = ws_layout(p, true, pitch);
         if (stageable(p) && !stage(w)) return SS_ERR_LAUNCH;
         ckpt_group = w.ckpt_group;
         a.ckpt = reinterpret_cast<float*>(ws + w.ckpt_off);
@@ -326,7 +334,7 @@ static int scan_fwd_impl(const ss_fwd_params* p, long bc_bstride, const void* W_
         }
     } else {
         // a plain forward call splits the sequence only if the caller lent the scratch for it
-        const WsLayout w = ws_layout(p, false);
+        const WsLayout w = ws_layout(p, false, pitch);
         const bool lent = ws && p->workspace_bytes >= w.total && aligned(ws, 256);
         if (stageable(p) && lent && !stage(w)) return SS_ERR_LAUNCH;
         if (groups > 1 && (p->flags & SS_HAS_Z)) a.ysave = ws + w.y_off;   // checked to be there
@@ -347,21 +355,28 @@ static int scan_fwd_impl(const ss_fwd_params* p, long bc_bstride, const void* W_
 }
 
 
-int scan_fwd_strided(const ss_fwd_params* p, long bc_bstride, void* stream)
+int scan_fwd_strided(const ss_fwd_params* p, long bc_bstride, int pitch, void* stream)
 {
-    return scan_fwd_impl(p, bc_bstride, nullptr, 0, nullptr, stream);
+    return scan_fwd_impl(p, bc_bstride, pitch, nullptr, 0, nullptr, stream);
 }
 
-int scan_fwd_fused(const ss_fwd_params* p, long bc_bstride, const void* W_dt, int R, const void* rT, void* stream)
+size_t scan_workspace_bytes(const ss_fwd_params* p, int for_backward, int pitch)
+{
+    if (!p || p->batch < 1 || p->dim < 1 || p->seqlen < 0) return 0;
+    return ws_layout(p, for_backward != 0, pitch).total;
+}
+
+int scan_fwd_fused(const ss_fwd_params* p, long bc_bstride, int pitch, const void* W_dt, int R, const void* rT, void* stream)
 {
     if (!W_dt || !rT) return SS_ERR_NULL;
-    return scan_fwd_impl(p, bc_bstride, W_dt, R, rT, stream);
+    return scan_fwd_impl(p, bc_bstride, pitch, W_dt, R, rT, stream);
 }
 
-int scan_bwd_strided(const ss_bwd_params* p, long bc_bstride, void* stream)
+int scan_bwd_strided(const ss_bwd_params* p, long bc_bstride, int pitch, void* stream)
 {
     if (!p) return SS_ERR_NULL;
-    const int rc = check_fwd(&p->fwd, true, bc_bstride == (long)slots(&p->fwd) * p->fwd.seqlen);
+    if (!pitch_ok(&p->fwd, pitch)) return SS_ERR_UNSUPPORTED;
+    const int rc = check_fwd(&p->fwd, true, pitch, bc_bstride == (long)slots(&p->fwd) * p->fwd.seqlen);
     if (rc != SS_OK) return rc;
     const ss_fwd_params* f = &p->fwd;
     const bool empty = f->seqlen == 0;
@@ -378,10 +393,10 @@ int scan_bwd_strided(const ss_bwd_params* p, long bc_bstride, void* stream)
     for (const void* q : f32)
         if (q && !aligned(q, 4)) return SS_ERR_ALIGN;
 
-    const WsLayout w = ws_layout(f, true);
+    const WsLayout w = ws_layout(f, true, pitch);
     char* ws = static_cast<char*>(f->workspace);
     ss::BwdArgs a{};
-    a.f = make_fwd_args(f, bc_bstride);
+    a.f = make_fwd_args(f, bc_bstride, pitch);
     a.f.out = nullptr;
     a.f.h_last = nullptr;
     a.f.ckpt = reinterpret_cast<float*>(ws + w.ckpt_off);
@@ -483,14 +498,13 @@ extern "C" {
 
 size_t ss_workspace_bytes(const ss_fwd_params* p, int for_backward)
 {
-    if (!p || p->batch < 1 || p->dim < 1 || p->seqlen < 0) return 0;
-    return ws_layout(p, for_backward != 0).total;
+    return p ? ss::scan_workspace_bytes(p, for_backward, p->seqlen) : 0;
 }
 
 int ss_scan_fwd(const ss_fwd_params* p, void* stream)
 {
     if (!p) return SS_ERR_NULL;
-    return ss::scan_fwd_strided(p, (long)slots(p) * p->seqlen, stream);
+    return ss::scan_fwd_strided(p, (long)slots(p) * p->seqlen, p->seqlen, stream);
 }
 
 int ss_scan_fwd_static(const ss_fwd_params* p, void* stream)
@@ -501,21 +515,21 @@ int ss_scan_fwd_static(const ss_fwd_params* p, void* stream)
     q.workspace = nullptr;
     q.workspace_bytes = 0;
     // everything else is checked first, so that an invalid call reports its own error
-    const int rc = check_fwd(&q, false);
+    const int rc = check_fwd(&q, false, q.seqlen);
     if (rc != SS_OK && rc != SS_ERR_WORKSPACE) return rc;
-    if (ws_layout(&q, false).total > (size_t)SS_STATIC_SCRATCH_BYTES) return SS_ERR_WORKSPACE;
+    if (ws_layout(&q, false, q.seqlen).total > (size_t)SS_STATIC_SCRATCH_BYTES) return SS_ERR_WORKSPACE;
     void* ptr = nullptr;
     const int rs = static_scratch(&ptr);
     if (rs != SS_OK) return rs;
     q.workspace = ptr;
     q.workspace_bytes = SS_STATIC_SCRATCH_BYTES;
-    return ss::scan_fwd_strided(&q, (long)slots(&q) * q.seqlen, stream);
+    return ss::scan_fwd_strided(&q, (long)slots(&q) * q.seqlen, q.seqlen, stream);
 }
 
 int ss_scan_bwd(const ss_bwd_params* p, void* stream)
 {
     if (!p) return SS_ERR_NULL;
-    return ss::scan_bwd_strided(p, (long)slots(&p->fwd) * p->fwd.seqlen, stream);
+    return ss::scan_bwd_strided(p, (long)slots(&p->fwd) * p->fwd.seqlen, p->fwd.seqlen, stream);
 }
 
 int ss_step(const ss_step_params* p, void* stream)

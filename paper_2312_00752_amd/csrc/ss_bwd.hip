@@ -679,7 +679,7 @@ __global__ void __launch_bounds__(THREADS, 2) scan_bwd_dpp_kernel(const BwdArgs 
     };
     const rsrc_t bu_ = wg_rsrc(f.u, true), bd_ = wg_rsrc(f.delta, true), bo_ = wg_rsrc(a.dout, true);
     const rsrc_t bz_ = wg_rsrc(f.z, has_z), by_ = wg_rsrc(f.ysave, has_z);
-    const rsrc_t bdu_ = wg_rsrc(a.du, true), bdd_ = wg_rsrc(a.ddelta, true), bdz_ = wg_rsrc(a.dz, has_z && a.dz);
+    const rsrc_t bdu_ = wg_rsrc(a.du, true), bdz_ = wg_rsrc(a.dz, has_z && a.dz);
     const uint32_t bc_bytes4 = (uint32_t)N * (uint32_t)L * 4u;
     const rsrc_t bdB_ = make_rsrc(a.dB + (long)b * a.dbc_bstride, bc_bytes4), bdC_ = make_rsrc(a.dC + (long)b * a.dbc_bstride, bc_bytes4);
     // staging view: waves 0, 1 stage B, waves 2, 3 stage C; thread -> (state s_n, pair of steps s_tp) of the block
@@ -693,11 +693,16 @@ __global__ void __launch_bounds__(THREADS, 2) scan_bwd_dpp_kernel(const BwdArgs 
     const uint32_t r_off = (uint32_t)r_row * (uint32_t)L * esz;
     const uint32_t r_off_bc = (uint32_t)min(s_n, N - 1) * (uint32_t)L * esz;
     const T* const ru_p = static_cast<const T*>(f.u) + wg_first;
-    const T* const rd_p = static_cast<const T*>(f.delta) + wg_first;
+    // ... delta, ysave and ddelta have rows of their own (FwdArgs::Li); i_off: what that adds to an offset of this thread's row
+    const long wg_first_i = RAG ? ((long)b * f.D + d0) * f.Li : wg_first;
+    const uint32_t i_off = RAG ? (uint32_t)pr * (uint32_t)(f.Li - L) * esz : 0u, r_off_i = (uint32_t)r_row * (uint32_t)f.Li * esz;
+    const T* const rd_p = static_cast<const T*>(f.delta) + wg_first_i;
     const T* const ro_p = static_cast<const T*>(a.dout) + wg_first;
     const T* const rz_p = has_z ? static_cast<const T*>(f.z) + wg_first : ro_p;
-    const T* const ry_p = has_z ? static_cast<const T*>(f.ysave) + wg_first : ro_p;
+    const T* const ry_p = has_z ? static_cast<const T*>(f.ysave) + wg_first_i : ro_p;
     const T* const rbc_p = static_cast<const T*>(s_which ? f.Cm : f.Bm) + (long)b * f.bc_bstride;
+
+    const rsrc_t bdd_ = RAG ? make_rsrc(static_cast<const T*>(a.ddelta) + wg_first_i, (uint32_t)rows_here * (uint32_t)f.Li * esz) : wg_rsrc(a.ddelta, true);
 
     // ---- state view: lane -> row, wave -> states 4w..4w+3 --------------------------------
     const bool s_ok = d0 + lane < f.D;
@@ -746,10 +751,10 @@ __global__ void __launch_bounds__(THREADS, 2) scan_bwd_dpp_kernel(const BwdArgs 
             const int bl = max(blk, blk_begin);
             const uint32_t t = (uint32_t)row_piece(bl * BT + pq * BSL, BSL, L) * esz;
             ru[s] = io4<T>::load_elem(ru_p, r_off + t);
-            rd[s] = io4<T>::load_elem(rd_p, r_off + t);
+            rd[s] = io4<T>::load_elem(rd_p, r_off_i + t);
             ro[s] = io4<T>::load_elem(ro_p, r_off + t);
             rz[s] = io4<T>::load_elem(rz_p, has_z ? r_off + t : 0u);
-            ry[s] = io4<T>::load_elem(ry_p, has_z ? r_off + t : 0u);
+            ry[s] = io4<T>::load_elem(ry_p, has_z ? r_off_i + t : 0u);
             const uint32_t tb = r_off_bc + (uint32_t)row_piece(bl * BT + 2 * s_tp, 2, L) * esz;
             if constexpr (sizeof(T) == 2) {
                 rbc[s] = load_any<uint32_t>(rbc_p, tb);
@@ -778,18 +783,19 @@ __global__ void __launch_bounds__(THREADS, 2) scan_bwd_dpp_kernel(const BwdArgs 
     uint32_t keep_off = BUF_OFF;
     // A block's results at byte offset off (of the thread's slice; BUF_OFF: not stored), an odd block's with the even block's
     // below it.  TAIL: the nv leading elements only, at once.
-    auto store_block = [&](rsrc_t rs, void* base, uint32_t off, int nv, typename io4<T>::packed now, typename io4<T>::packed& keep,
-                           bool odd, auto tail_tag) {
+    // more: added to the offsets (an offset that is off stays off: resources end below 2^31).
+    auto store_block = [&](rsrc_t rs, void* base, uint32_t off, uint32_t more, int nv, typename io4<T>::packed now,
+                           typename io4<T>::packed& keep, bool odd, auto tail_tag) {
         if constexpr (decltype(tail_tag)::value) {
-            if (base && nv > 0) io4<T>::store_elem(static_cast<T*>(base) + wg_first, off, now, nv);
+            if (base && nv > 0) io4<T>::store_elem(static_cast<T*>(base), off + more, now, nv);
             return;
         }
         if constexpr (LG == 2) {
-            io4<T>::store_packed(rs, odd ? BUF_OFF : keep_off, keep);   // keep_off: switched off when nothing waits
-            io4<T>::store_packed(rs, odd ? BUF_OFF : off, now);
+            io4<T>::store_packed(rs, (odd ? BUF_OFF : keep_off) + more, keep);   // keep_off: switched off when nothing waits
+            io4<T>::store_packed(rs, (odd ? BUF_OFF : off) + more, now);
             keep = now;
         } else {
-            io4<T>::store_packed(rs, off, now);
+            io4<T>::store_packed(rs, off + more, now);
         }
     };
     // The state entering a block, left by the forward pass: requested a block ahead.
@@ -869,7 +875,7 @@ __global__ void __launch_bounds__(THREADS, 2) scan_bwd_dpp_kernel(const BwdArgs 
                     dz4[j] = (o4[j] * y4[j]) * fmaf(zs, 1.0f - s, s);   // dout y d[z sigmoid(z)]/dz
                 }
             }
-            store_block(bdz_, a.dz, off, nv, io4<T>::pack(dz4), keep_dz, odd, tail_tag);   // switched off without a gate and for all but the first state group
+            store_block(bdz_, a.dz ? static_cast<T*>(a.dz) + wg_first : nullptr, off, 0u, nv, io4<T>::pack(dz4), keep_dz, odd, tail_tag);   // switched off without a gate and for all but the first state group
             *reinterpret_cast<float4*>(&sm.dt[pr][pq * BSL]) = make_float4(dt4[0], dt4[1], dt4[2], dt4[3]);
             *reinterpret_cast<float4*>(&sm.du[pr][pq * BSL]) = make_float4(du4[0], du4[1], du4[2], du4[3]);
             *reinterpret_cast<float4*>(&sm.dy[pr][pq * BSL]) = make_float4(dy4[0], dy4[1], dy4[2], dy4[3]);
@@ -1021,7 +1027,7 @@ __global__ void __launch_bounds__(THREADS, 2) scan_bwd_dpp_kernel(const BwdArgs 
                 if constexpr (RAG) {
                     const int tp = row_piece(t0, BSL, L);
                     typename io4<T>::raw xu = io4<T>::load_elem(static_cast<const T*>(a.du) + wg_first, r_off + (uint32_t)tp * esz);
-                    typename io4<T>::raw xl = io4<T>::load_elem(static_cast<const T*>(a.ddelta) + wg_first, r_off + (uint32_t)tp * esz);
+                    typename io4<T>::raw xl = io4<T>::load_elem(static_cast<const T*>(a.ddelta) + wg_first_i, r_off_i + (uint32_t)tp * esz);
                     io4<T>::drop(xu, t0 - tp);
                     io4<T>::drop(xl, t0 - tp);
                     io4<T>::unpack(xu, pu);
@@ -1033,8 +1039,8 @@ __global__ void __launch_bounds__(THREADS, 2) scan_bwd_dpp_kernel(const BwdArgs 
 #pragma unroll
                 for (int j = 0; j < BSL; ++j) { du4[j] += pu[j]; dl4[j] += pl[j]; }
             }
-            store_block(bdu_, a.du, off, nv, io4<T>::pack(du4), keep_du, odd, tail_tag);
-            store_block(bdd_, a.ddelta, off, nv, io4<T>::pack(dl4), keep_dl, odd, tail_tag);
+            store_block(bdu_, static_cast<T*>(a.du) + wg_first, off, 0u, nv, io4<T>::pack(du4), keep_du, odd, tail_tag);
+            store_block(bdd_, static_cast<T*>(a.ddelta) + wg_first_i, off, i_off, nv, io4<T>::pack(dl4), keep_dl, odd, tail_tag);
             if constexpr (LG == 2 && !TAIL) keep_off = odd ? off : BUF_OFF;
         }
     };
@@ -1247,7 +1253,8 @@ __global__ void __launch_bounds__(THREADS, 4) adjoint_agg_dpp_kernel(const BwdAr
     const int r_row = min(pr, rows_here - 1);
     const uint32_t r_off = (uint32_t)r_row * (uint32_t)L * esz;
     const uint32_t r_off_c = (uint32_t)min(s_n, N - 1) * (uint32_t)L * esz;
-    const T* const rd_p = static_cast<const T*>(f.delta) + wg_first;
+    const uint32_t r_off_i = (uint32_t)r_row * (uint32_t)f.Li * esz;   // delta has rows of its own (FwdArgs::Li)
+    const T* const rd_p = static_cast<const T*>(f.delta) + ((long)b * f.D + d0) * f.Li;
     const T* const ro_p = static_cast<const T*>(a.dout) + wg_first;
     const T* const rz_p = has_z ? static_cast<const T*>(f.z) + wg_first : ro_p;
     const T* const rc_p = static_cast<const T*>(f.Cm) + (long)b * f.bc_bstride;
@@ -1273,7 +1280,7 @@ __global__ void __launch_bounds__(THREADS, 4) adjoint_agg_dpp_kernel(const BwdAr
         if constexpr (RAG) {   // before the segment's start: its first chunk again (never used)
             const int cc = max(c, c_begin) * CHUNK_T;
             const uint32_t t = (uint32_t)row_piece(cc + pq * SLICE, SLICE, L) * esz;
-            rd_[s] = io8<T>::load_elem(rd_p, r_off + t);
+            rd_[s] = io8<T>::load_elem(rd_p, r_off_i + t);
             ro_[s] = io8<T>::load_elem(ro_p, r_off + t);
             rz_[s] = io8<T>::load_elem(rz_p, has_z ? r_off + t : 0u);
             rc_[s] = io4<T>::load_elem(rc_p, r_off_c + (uint32_t)row_piece(cc + s_tq * GROUP_T, GROUP_T, L) * esz);

@@ -130,9 +130,12 @@ __global__ void __launch_bounds__(THREADS, PAT && AGG ? 4 : ((PAT && FUSED_KS <=
     const uint32_t r_off = (uint32_t)r_row * (uint32_t)L * esz;
     const uint32_t r_off_bc = (uint32_t)min(s_n, N - 1) * (uint32_t)L * esz;
     const T* const ru_p = static_cast<const T*>(a.u) + wg_first;
-    const T* const rd_p = static_cast<const T*>(a.delta) + wg_first;
+    // ... delta and ysave have rows of their own (FwdArgs::Li)
+    const long wg_first_i = ((long)b * a.D + d0) * a.Li;
+    const uint32_t r_off_i = (uint32_t)r_row * (uint32_t)a.Li * esz, r_off_p = has_z ? r_off_i : r_off;
+    const T* const rd_p = static_cast<const T*>(a.delta) + wg_first_i;
     const T* const rz_p = has_z ? static_cast<const T*>(a.z) + wg_first : ru_p;
-    const T* const rp_p = acc_on ? static_cast<const T*>(has_z ? a.ysave : a.out) + wg_first : ru_p;
+    const T* const rp_p = !acc_on ? ru_p : (has_z ? static_cast<const T*>(a.ysave) + wg_first_i : static_cast<const T*>(a.out) + wg_first);
     const T* const rbc_p = static_cast<const T*>(s_which ? a.Cm : a.Bm) + (long)b * a.bc_bstride;
 
     // ---- state view: lane -> row, wave -> states 4w..4w+3 -------------------------------
@@ -230,10 +233,10 @@ __global__ void __launch_bounds__(THREADS, PAT && AGG ? 4 : ((PAT && FUSED_KS <=
             const int cc = min(c, c_end - 1) * CHUNK_T;
             const uint32_t t = (uint32_t)row_piece(cc + pq * SLICE, SLICE, L) * esz;
             ru_[s] = io8<T>::load_elem(ru_p, r_off + t);
-            if constexpr (FUSED_KS == 0) rd_[s] = io8<T>::load_elem(rd_p, r_off + t);
+            if constexpr (FUSED_KS == 0) rd_[s] = io8<T>::load_elem(rd_p, r_off_i + t);
             if constexpr (!AGG) {
                 rz_[s] = io8<T>::load_elem(rz_p, has_z ? r_off + t : 0u);
-                rp_[s] = io8<T>::load_elem(rp_p, acc_on ? r_off + t : 0u);
+                rp_[s] = io8<T>::load_elem(rp_p, acc_on ? r_off_p + t : 0u);
             }
             rbc_[s] = io4<T>::load_elem(rbc_p, r_off_bc + (uint32_t)row_piece(cc + s_tq * GROUP_T, GROUP_T, L) * esz);
         } else if constexpr (VEC) {   // slices are whole or empty
@@ -321,10 +324,10 @@ __global__ void __launch_bounds__(THREADS, PAT && AGG ? 4 : ((PAT && FUSED_KS <=
             tb[s] = r_off_bc + (uint32_t)row_piece(cc + s_tq * GROUP_T, GROUP_T, L) * esz;
         }
         ru_[0] = io8<T>::load_elem(ru_p, r_off + t[0]); ru_[1] = io8<T>::load_elem(ru_p, r_off + t[1]);
-        if constexpr (FUSED_KS == 0) { rd_[0] = io8<T>::load_elem(rd_p, r_off + t[0]); rd_[1] = io8<T>::load_elem(rd_p, r_off + t[1]); }
+        if constexpr (FUSED_KS == 0) { rd_[0] = io8<T>::load_elem(rd_p, r_off_i + t[0]); rd_[1] = io8<T>::load_elem(rd_p, r_off_i + t[1]); }
         if constexpr (!AGG) {
             rz_[0] = io8<T>::load_elem(rz_p, has_z ? r_off + t[0] : 0u); rz_[1] = io8<T>::load_elem(rz_p, has_z ? r_off + t[1] : 0u);
-            rp_[0] = io8<T>::load_elem(rp_p, acc_on ? r_off + t[0] : 0u); rp_[1] = io8<T>::load_elem(rp_p, acc_on ? r_off + t[1] : 0u);
+            rp_[0] = io8<T>::load_elem(rp_p, acc_on ? r_off_p + t[0] : 0u); rp_[1] = io8<T>::load_elem(rp_p, acc_on ? r_off_p + t[1] : 0u);
         }
         rbc_[0] = io4<T>::load_elem(rbc_p, tb[0]); rbc_[1] = io4<T>::load_elem(rbc_p, tb[1]);
       } else if constexpr (PAIR) {
@@ -640,14 +643,14 @@ __global__ void __launch_bounds__(THREADS, PAT && AGG ? 4 : ((PAT && FUSED_KS <=
                 } else if constexpr (RAG) {
                     const uint32_t off_t = (uint32_t)t0 * esz;
                     if (p_ok) {
-                        T* const yp = static_cast<T*>(a.ysave) + wg_first;
+                        T* const yp = static_cast<T*>(a.ysave) + wg_first_i;
                         T* const op = static_cast<T*>(a.out) + wg_first;
                         if (SLOT == 1) {   // the even chunk before an odd one is whole
-                            if (keep_y) io8<T>::store_elem(yp, r_off + off_t - CHUNK_T * esz, held_y, SLICE);
-                            if (keep_y) io8<T>::store_elem(yp, r_off + off_t, py, nv);
+                            if (keep_y) io8<T>::store_elem(yp, r_off_i + off_t - CHUNK_T * esz, held_y, SLICE);
+                            if (keep_y) io8<T>::store_elem(yp, r_off_i + off_t, py, nv);
                             io8<T>::store_elem(op, r_off + off_t - CHUNK_T * esz, held_o, SLICE);
                         } else if (keep_y) {
-                            io8<T>::store_elem(yp, r_off + off_t, py, nv);
+                            io8<T>::store_elem(yp, r_off_i + off_t, py, nv);
                         }
                         io8<T>::store_elem(op, r_off + off_t, po, nv);
                     }
@@ -660,7 +663,7 @@ __global__ void __launch_bounds__(THREADS, PAT && AGG ? 4 : ((PAT && FUSED_KS <=
                     io8<T>::store_packed(bo, off, po);
                 }
             } else if constexpr (RAG) {
-                if (keep_y && p_ok) io8<T>::store_elem(static_cast<T*>(a.ysave) + wg_first, r_off + (uint32_t)t0 * esz, io8<T>::pack(y8), nv);
+                if (keep_y && p_ok) io8<T>::store_elem(static_cast<T*>(a.ysave) + wg_first_i, r_off_i + (uint32_t)t0 * esz, io8<T>::pack(y8), nv);
                 if (has_z) {
 #pragma unroll
                     for (int j = 0; j < SLICE; ++j) y8[j] *= z8[j] * sigmoid_fast(z8[j]);

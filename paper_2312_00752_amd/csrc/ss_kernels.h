@@ -35,6 +35,9 @@ struct FwdArgs {
     uint32_t flags;
     int vec_ok;  // L % 8 == 0: every row starts 16-byte aligned and 8-step slices are whole or empty
     int dpp_ok;  // L >= 8 and 64 rows below 2^31 bytes: the kernels with B and C as quad-broadcast operands take the call
+    // Elements between the rows of delta, of ysave and (backward) of ddelta.  L, but where the caller owns all three and rows of L
+    // elements would start off a 32-bit word (the layer, see delta_pitch there); other than L in the kernels for any row length only.
+    int Li;
     const void *u, *delta, *z, *Bm, *Cm;
     long bc_bstride;  // elements between consecutive batch entries of Bm and Cm (N * L when dense)
     // Staged copy of the selective B and C for the forward kernels, or null.  In the io dtype,
@@ -113,14 +116,17 @@ int launch_step_projected(const StepArgs& a, int io_dtype, hipStream_t stream);
 // The public scan entry points with one extra degree of freedom: B and C of batch entry b
 // start b * bc_bstride elements after Bmat / Cmat (the public calls pass dstate * seqlen).
 // Validation and return codes are those of ss_scan_fwd / ss_scan_bwd.
-int scan_fwd_strided(const ss_fwd_params* p, long bc_bstride, void* stream);
+// pitch: elements between the rows of delta and ddelta and of the saved y (see FwdArgs::Li); at least L, and L unless L >= 8 is odd.
+// scan_workspace_bytes is ss_workspace_bytes for it.
+int scan_fwd_strided(const ss_fwd_params* p, long bc_bstride, int pitch, void* stream);
+size_t scan_workspace_bytes(const ss_fwd_params* p, int for_backward, int pitch);
 // The same with delta_raw = W_dt r formed inside the scan kernel (bf16): W_dt (D, R) row-major,
 // rT (B, Lp, Rp) = r transposed and zero-padded, Lp = L rounded up to 32, Rp = R rounded up to 32;
 // p->delta is not read.  Returns SS_ERR_UNSUPPORTED, before anything is enqueued, when the call
 // does not qualify (then use scan_fwd_strided with delta in memory).
-int scan_fwd_fused(const ss_fwd_params* p, long bc_bstride, const void* W_dt, int R, const void* rT, void* stream);
-bool scan_fwd_fusable(const ss_fwd_params* p, int R);   // whether scan_fwd_fused would take the call
-int scan_bwd_strided(const ss_bwd_params* p, long bc_bstride, void* stream);
+int scan_fwd_fused(const ss_fwd_params* p, long bc_bstride, int pitch, const void* W_dt, int R, const void* rT, void* stream);
+bool scan_fwd_fusable(const ss_fwd_params* p, int pitch, int R);   // whether scan_fwd_fused would take the call
+int scan_bwd_strided(const ss_bwd_params* p, long bc_bstride, int pitch, void* stream);
 // ss_step with B_t / C_t rows bc_stride elements apart (the public call passes dstate).
 int step_strided(const ss_step_params* p, long bc_stride, void* stream);
 

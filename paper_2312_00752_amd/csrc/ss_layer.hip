@@ -365,6 +365,14 @@ ss_fwd_params scan_params(const ss_layer_params* p)
     return f;
 }
 
+// Elements between the rows of the layer's own delta and ddelta and of the saved y.  Every other row of an odd number of 16-bit elements
+// starts off a 32-bit word, where wide accesses are much slower; rows of these three are a whole number of 16-byte pieces apart.
+// us, L / this: training 8 x 1536 x 2047 954 / 907, 2 x 2560 x 4095 896 / 855, prefill 4 x 4096 x 1531 266 / 258.
+int delta_pitch(const ss_layer_params* p)
+{
+    return p->io_dtype == SS_BF16 && p->seqlen % 2 != 0 && p->seqlen >= 8 && p->seqlen < (1 << 22) ? (p->seqlen + 7) / 8 * 8 : p->seqlen;
+}
+
 // saved:   [P = [r;B;C] (B, Mx, L) io][workspace of the scan]
 struct SavedLayout { size_t P_off, scan_off, scan_bytes, total; };
 SavedLayout saved_layout(const ss_layer_params* p)
@@ -374,7 +382,7 @@ SavedLayout saved_layout(const ss_layer_params* p)
     SavedLayout w{};
     w.P_off = 0;
     w.scan_off = round_up(s.B * s.Mx * s.L * s.esz, 256);
-    w.scan_bytes = ss_workspace_bytes(&f, 1);
+    w.scan_bytes = ss::scan_workspace_bytes(&f, 1, delta_pitch(p));
     w.total = w.scan_off + round_up(w.scan_bytes, 256);
     return w;
 }
@@ -396,18 +404,18 @@ ScratchLayout scratch_layout(const ss_layer_params* p, bool bwd)
     // touches all of them at the same row and step, and with rows a large power of two of bytes apart equal
     // starting offsets into the memory channels' interleave would put all of that on one channel.
     constexpr size_t SKEW = 66560;
-    const size_t T = s.B * s.D * s.L * s.esz + SKEW;
+    const size_t T = s.B * s.D * s.L * s.esz + SKEW, Td = s.B * s.D * delta_pitch(p) * s.esz + SKEW;
     w.u = take(T);
-    w.delta = take(T);
+    w.delta = take(Td);
     if (!bwd) {
         w.P = take(s.B * s.Mx * s.L * s.esz);
         const ss_fwd_params f = scan_params(p);
-        w.scan_ws_bytes = ss_workspace_bytes(&f, 0);
+        w.scan_ws_bytes = ss::scan_workspace_bytes(&f, 0, delta_pitch(p));
         w.scan_ws = take(w.scan_ws_bytes);
         w.rT = take(s.B * round_up(s.L, 32) * round_up(s.R, 32) * s.esz);
     } else {
         w.du = take(T);
-        w.ddelta = take(T);
+        w.ddelta = take(Td);
         w.dP = take(s.B * s.Mx * s.L * s.esz);
         w.dB = take(s.B * s.N * s.L * sizeof(float));
         w.dC = take(s.B * s.N * s.L * sizeof(float));
@@ -501,7 +509,7 @@ int ss_layer_fwd(const ss_layer_params* p, void* stream)
     char* u = scratch + sc.u;
     char* delta = scratch + sc.delta;
     char* P = saved ? saved + sv.P_off : scratch + sc.P;
-    const int B = p->batch, D = p->dim, L = p->seqlen, N = p->dstate, R = p->dt_rank, Mx = R + 2 * N;
+    const int B = p->batch, D = p->dim, L = p->seqlen, N = p->dstate, R = p->dt_rank, Mx = R + 2 * N, Ld = delta_pitch(p);
 
     ss_conv_params c = conv_params(p, u);
     if (p->conv_state && p->conv_width > 1) {
@@ -532,20 +540,20 @@ int ss_layer_fwd(const ss_layer_params* p, void* stream)
         f.workspace_bytes = sc.scan_ws_bytes;
     }
     // bf16: delta_raw = W_dt r is formed inside the scan kernel where that variant applies
-    if (ss::scan_fwd_fusable(&f, R)) {
+    if (ss::scan_fwd_fusable(&f, Ld, R)) {
         ss::bf16_t* rT = reinterpret_cast<ss::bf16_t*>(scratch + sc.rT);
         const int Lp = (L + 31) / 32 * 32, Rp = (R + 31) / 32 * 32;
         hipLaunchKernelGGL(transpose_r_kernel, dim3((unsigned)(Lp / 32), (unsigned)(Rp / 32), (unsigned)B), dim3(32, 8), 0, st,
                            reinterpret_cast<const ss::bf16_t*>(P), (long)Mx * L, rT, R, L, Lp, Rp);
         if (hipGetLastError() != hipSuccess) return SS_ERR_LAUNCH;
-        rc = ss::scan_fwd_fused(&f, (long)Mx * L, p->W_dt, R, rT, stream);
+        rc = ss::scan_fwd_fused(&f, (long)Mx * L, Ld, p->W_dt, R, rT, stream);
         if (rc != SS_ERR_UNSUPPORTED) return rc;   // otherwise nothing was enqueued: take the general path
     }
     // delta_raw = W_dt @ r
-    if (!gemm_rm(st, false, false, D, L, R, p->W_dt, R, 0, P, L, (long)Mx * L, 0.0f, delta, L, (long)D * L, B, bf16, false,
+    if (!gemm_rm(st, false, false, D, L, R, p->W_dt, R, 0, P, L, (long)Mx * L, 0.0f, delta, Ld, (long)D * Ld, B, bf16, false,
                  scratch + sc.gsplit, sc.gsplit_bytes))
         return SS_ERR_LAUNCH;
-    return ss::scan_fwd_strided(&f, (long)Mx * L, stream);
+    return ss::scan_fwd_strided(&f, (long)Mx * L, Ld, stream);
 }
 
 int ss_layer_bwd(const ss_layer_bwd_params* q, void* stream)
@@ -573,12 +581,12 @@ int ss_layer_bwd(const ss_layer_bwd_params* q, void* stream)
     float* dB = reinterpret_cast<float*>(scratch + sc.dB);
     float* dC = reinterpret_cast<float*>(scratch + sc.dC);
     char* P = saved + sv.P_off;
-    const int B = p->batch, D = p->dim, L = p->seqlen, N = p->dstate, R = p->dt_rank, Mx = R + 2 * N;
+    const int B = p->batch, D = p->dim, L = p->seqlen, N = p->dstate, R = p->dt_rank, Mx = R + 2 * N, Ld = delta_pitch(p);
 
     // recompute the two cheap intermediates
     ss_conv_params c = conv_params(p, u);
     if ((rc = ss_conv_fwd(&c, stream)) != SS_OK) return rc;
-    if (!gemm_rm(st, false, false, D, L, R, p->W_dt, R, 0, P, L, (long)Mx * L, 0.0f, delta, L, (long)D * L, B, bf16, false,
+    if (!gemm_rm(st, false, false, D, L, R, p->W_dt, R, 0, P, L, (long)Mx * L, 0.0f, delta, Ld, (long)D * Ld, B, bf16, false,
                  scratch + sc.gsplit, sc.gsplit_bytes))
         return SS_ERR_LAUNCH;
 
@@ -595,7 +603,7 @@ int ss_layer_bwd(const ss_layer_bwd_params* q, void* stream)
     b.du = du; b.ddelta = ddelta; b.dz = q->dz;
     b.dB = dB; b.dC = dC;
     b.dA = q->dA; b.dD = q->dD; b.ddelta_bias = q->ddt_bias;
-    if ((rc = ss::scan_bwd_strided(&b, (long)Mx * L, stream)) != SS_OK) return rc;
+    if ((rc = ss::scan_bwd_strided(&b, (long)Mx * L, Ld, stream)) != SS_OK) return rc;
 
     // The two products with a transposed weight take it from a transposed copy (a megabyte each), so
     // that their first operand is contiguous along the contraction index like everywhere else.
@@ -604,10 +612,10 @@ int ss_layer_bwd(const ss_layer_bwd_params* q, void* stream)
         !(bf16 ? transpose_weight<ss::bf16_t>(p->W_x, WxT, Mx, D, st) : transpose_weight<float>(p->W_x, WxT, Mx, D, st)))
         return SS_ERR_LAUNCH;
     // delta_raw = W_dt @ r:  dr = W_dt^T @ ddelta  (rows 0..R-1 of dP),  dW_dt = sum_b ddelta r^T
-    if (!gemm_rm(st, false, false, R, L, D, WdtT, D, 0, ddelta, L, (long)D * L, 0.0f, dP, L, (long)Mx * L, B, bf16, false,
+    if (!gemm_rm(st, false, false, R, L, D, WdtT, D, 0, ddelta, Ld, (long)D * Ld, 0.0f, dP, L, (long)Mx * L, B, bf16, false,
                  scratch + sc.gsplit, sc.gsplit_bytes))
         return SS_ERR_LAUNCH;
-    if (!gemm_rm(st, false, true, D, R, L, ddelta, L, (long)D * L, P, L, (long)Mx * L, 0.0f, part_dt, R, (long)D * R, B, bf16, true,
+    if (!gemm_rm(st, false, true, D, R, L, ddelta, Ld, (long)D * Ld, P, L, (long)Mx * L, 0.0f, part_dt, R, (long)D * R, B, bf16, true,
                  scratch + sc.gsplit, sc.gsplit_bytes))
         return SS_ERR_LAUNCH;
     // rows R.. of dP from the scan's float32 dB, dC
