@@ -679,7 +679,7 @@ __global__ void __launch_bounds__(THREADS, 2) scan_bwd_dpp_kernel(const BwdArgs 
     };
     const rsrc_t bu_ = wg_rsrc(f.u, true), bd_ = wg_rsrc(f.delta, true), bo_ = wg_rsrc(a.dout, true);
     const rsrc_t bz_ = wg_rsrc(f.z, has_z), by_ = wg_rsrc(f.ysave, has_z);
-    const rsrc_t bdu_ = wg_rsrc(a.du, true), bdz_ = wg_rsrc(a.dz, has_z && a.dz);
+    const rsrc_t bdz_ = wg_rsrc(a.dz, has_z && a.dz);
     const uint32_t bc_bytes4 = (uint32_t)N * (uint32_t)L * 4u;
     const rsrc_t bdB_ = make_rsrc(a.dB + (long)b * a.dbc_bstride, bc_bytes4), bdC_ = make_rsrc(a.dC + (long)b * a.dbc_bstride, bc_bytes4);
     // staging view: waves 0, 1 stage B, waves 2, 3 stage C; thread -> (state s_n, pair of steps s_tp) of the block
@@ -692,17 +692,20 @@ __global__ void __launch_bounds__(THREADS, 2) scan_bwd_dpp_kernel(const BwdArgs 
     const int r_row = min(pr, rows_here - 1);
     const uint32_t r_off = (uint32_t)r_row * (uint32_t)L * esz;
     const uint32_t r_off_bc = (uint32_t)min(s_n, N - 1) * (uint32_t)L * esz;
-    const T* const ru_p = static_cast<const T*>(f.u) + wg_first;
-    // ... delta, ysave and ddelta have rows of their own (FwdArgs::Li); i_off: what that adds to an offset of this thread's row
+    // ... u, delta, ysave, du and ddelta have rows of their own (FwdArgs::Li); i_off: what that adds to an offset of this thread's row
     const long wg_first_i = RAG ? ((long)b * f.D + d0) * f.Li : wg_first;
     const uint32_t i_off = RAG ? (uint32_t)pr * (uint32_t)(f.Li - L) * esz : 0u, r_off_i = (uint32_t)r_row * (uint32_t)f.Li * esz;
+    const T* const ru_p = static_cast<const T*>(f.u) + wg_first_i;
     const T* const rd_p = static_cast<const T*>(f.delta) + wg_first_i;
     const T* const ro_p = static_cast<const T*>(a.dout) + wg_first;
     const T* const rz_p = has_z ? static_cast<const T*>(f.z) + wg_first : ro_p;
     const T* const ry_p = has_z ? static_cast<const T*>(f.ysave) + wg_first_i : ro_p;
     const T* const rbc_p = static_cast<const T*>(s_which ? f.Cm : f.Bm) + (long)b * f.bc_bstride;
 
-    const rsrc_t bdd_ = RAG ? make_rsrc(static_cast<const T*>(a.ddelta) + wg_first_i, (uint32_t)rows_here * (uint32_t)f.Li * esz) : wg_rsrc(a.ddelta, true);
+    auto own_rsrc = [&](void* base) {
+        return RAG ? make_rsrc(static_cast<T*>(base) + wg_first_i, (uint32_t)rows_here * (uint32_t)f.Li * esz) : wg_rsrc(base, true);
+    };
+    const rsrc_t bdu_ = own_rsrc(a.du), bdd_ = own_rsrc(a.ddelta);
 
     // ---- state view: lane -> row, wave -> states 4w..4w+3 --------------------------------
     const bool s_ok = d0 + lane < f.D;
@@ -750,7 +753,7 @@ __global__ void __launch_bounds__(THREADS, 2) scan_bwd_dpp_kernel(const BwdArgs 
         if constexpr (RAG) {
             const int bl = max(blk, blk_begin);
             const uint32_t t = (uint32_t)row_piece(bl * BT + pq * BSL, BSL, L) * esz;
-            ru[s] = io4<T>::load_elem(ru_p, r_off + t);
+            ru[s] = io4<T>::load_elem(ru_p, r_off_i + t);
             rd[s] = io4<T>::load_elem(rd_p, r_off_i + t);
             ro[s] = io4<T>::load_elem(ro_p, r_off + t);
             rz[s] = io4<T>::load_elem(rz_p, has_z ? r_off + t : 0u);
@@ -1026,7 +1029,7 @@ __global__ void __launch_bounds__(THREADS, 2) scan_bwd_dpp_kernel(const BwdArgs 
                 float pu[BSL], pl[BSL];
                 if constexpr (RAG) {
                     const int tp = row_piece(t0, BSL, L);
-                    typename io4<T>::raw xu = io4<T>::load_elem(static_cast<const T*>(a.du) + wg_first, r_off + (uint32_t)tp * esz);
+                    typename io4<T>::raw xu = io4<T>::load_elem(static_cast<const T*>(a.du) + wg_first_i, r_off_i + (uint32_t)tp * esz);
                     typename io4<T>::raw xl = io4<T>::load_elem(static_cast<const T*>(a.ddelta) + wg_first_i, r_off_i + (uint32_t)tp * esz);
                     io4<T>::drop(xu, t0 - tp);
                     io4<T>::drop(xl, t0 - tp);
@@ -1039,7 +1042,7 @@ __global__ void __launch_bounds__(THREADS, 2) scan_bwd_dpp_kernel(const BwdArgs 
 #pragma unroll
                 for (int j = 0; j < BSL; ++j) { du4[j] += pu[j]; dl4[j] += pl[j]; }
             }
-            store_block(bdu_, static_cast<T*>(a.du) + wg_first, off, 0u, nv, io4<T>::pack(du4), keep_du, odd, tail_tag);
+            store_block(bdu_, static_cast<T*>(a.du) + wg_first_i, off, i_off, nv, io4<T>::pack(du4), keep_du, odd, tail_tag);
             store_block(bdd_, static_cast<T*>(a.ddelta) + wg_first_i, off, i_off, nv, io4<T>::pack(dl4), keep_dl, odd, tail_tag);
             if constexpr (LG == 2 && !TAIL) keep_off = odd ? off : BUF_OFF;
         }

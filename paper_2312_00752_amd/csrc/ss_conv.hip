@@ -22,6 +22,7 @@ constexpr int PIECE = WAVE * 8;          // steps one wave covers per pass
 
 struct ConvArgs {
     int B, D, L, W;
+    int Lo;   // elements between the rows of out (forward) or dout (backward): L, or in 16-bit at an odd L a multiple of 8
     unsigned flags;
     const void *x, *state_in, *dout;
     const float *w, *bias;
@@ -32,8 +33,11 @@ struct ConvArgs {
 // How the rows of a call are read and written: one element at a time (fewer than 8 steps), in whole aligned
 // 16-byte pieces (L a multiple of 8), or in pieces at element alignment (any other length: the piece that
 // reaches past the end is read from inside the row and shifted into place, see row_piece), which for an odd number of
-// 16-bit elements can be laid on whole words (see row_phase).
-enum { ROWS_SHORT, ROWS_WHOLE, ROWS_ANY, ROWS_ODD };
+// 16-bit elements can be laid on whole words (see row_phase).  The last two are for an odd number of 16-bit elements whose out
+// (ROWS_SHIFT, forward) or dout (ROWS_ODD_ONE, backward) has rows of whole 16-byte pieces, as in the layer: the other tensor's rows are read
+// from the word a slice lies on and put in place in registers, so that nothing is accessed off a word.
+enum { ROWS_SHORT, ROWS_WHOLE, ROWS_ANY, ROWS_ODD, ROWS_SHIFT, ROWS_ODD_ONE };
+__host__ __device__ constexpr bool starts_early(int kind) { return kind == ROWS_ODD || kind == ROWS_ODD_ONE; }
 // Pieces of 512 steps that a row is dealt out in.  An odd number of steps leaves room in the last one for the step that
 // ROWS_ODD begins early.
 __host__ __device__ __forceinline__ int row_pieces(int L) { return (L + PIECE - 1) / PIECE; }
@@ -92,13 +96,13 @@ __device__ __forceinline__ uint32_t row_bytes(int L) { return (uint32_t)L * (uin
 template <typename T, int KIND>
 __device__ __forceinline__ int row_phase(const T* row)
 {
-    if constexpr (KIND == ROWS_ODD) return (int)((reinterpret_cast<uintptr_t>(row) >> 1) & 1);
+    if constexpr (starts_early(KIND)) return (int)((reinterpret_cast<uintptr_t>(row) >> 1) & 1);
     else return 0;
 }
 template <int KIND>
-__device__ __forceinline__ bool before_row(int t0) { return KIND == ROWS_ODD && t0 < 0; }
+__device__ __forceinline__ bool before_row(int t0) { return starts_early(KIND) && t0 < 0; }
 template <int KIND>
-__device__ __forceinline__ int slice_start(int t0) { return KIND == ROWS_ODD ? max(t0, 0) : t0; }
+__device__ __forceinline__ int slice_start(int t0) { return starts_early(KIND) ? max(t0, 0) : t0; }
 template <typename T, int KIND, bool NEXT>
 __device__ __forceinline__ window_raw<T> issue_window_any(const T* row, const T* state_row, int t0, int L, int W)
 {
@@ -109,7 +113,7 @@ __device__ __forceinline__ window_raw<T> issue_window_any(const T* row, const T*
     if (NEXT) r.next = io4<T>::load_elem(row, (uint32_t)row_piece(t0 + 8, 4, L) * esz);
     // The window of W - 1 samples: behind a branch it is waited for by itself, so every lane reads it, and without one the row's start (of
     // at least 8).  The waves of ROWS_ODD are rarely a row's first and do without.
-    if constexpr (KIND == ROWS_ODD) {
+    if constexpr (starts_early(KIND)) {
 #pragma unroll
         for (int j = 0; j < HALO; ++j) r.st[j] = 0u;
         if (state_row && t0 <= 0) {
@@ -193,6 +197,37 @@ __device__ __forceinline__ void unpack_window(const window_raw<T>& r, int t0, fl
     if (NEXT) io4<T>::unpack(r.next, xn);
 }
 
+// ROWS_SHIFT: xs[0 .. 10] = x[t0 - 3 .. t0 + 7] of a row that may start off a word (uniform), t0 a multiple of eight: the 16 elements
+// from the word of t0 - 4 on, of which the row's own phase picks eleven.  A row off a word is not the tensor's first, so
+// the element in front of it is memory of the tensor (and is not used).
+template <typename T>
+__device__ __forceinline__ void load_shifted(const T* row, const T* state_row, int t0, int L, int W, float (&xs)[HALO + 8])
+{
+    const int s = (int)((reinterpret_cast<uintptr_t>(row) >> 1) & 1), tb = t0 - s;
+    const int at_cur = row_piece(tb, 8, L), at_halo = t0 > 0 ? row_piece(tb - 4, 4, L) : 0, at_next = row_piece(tb + 8, 4, L);
+    typename io8<T>::raw cur = io8<T>::load_elem(row + at_cur, 0u);
+    typename io4<T>::raw halo = io4<T>::load_elem(row + at_halo, 0u), next = io4<T>::load_elem(row + at_next, 0u);
+    float st[HALO] = {0.f, 0.f, 0.f};
+    if (t0 == 0) {   // the window handed over from before the sequence
+#pragma unroll
+        for (int j = 0; j < HALO; ++j) st[j] = before_start<T>(state_row, j - HALO, W);
+    }
+    if (t0 + 12 > L) {   // only the last lanes of a row
+        io8<T>::drop(cur, tb - at_cur);
+        if (t0 > 0) io4<T>::drop(halo, tb - 4 - at_halo);
+        io4<T>::drop(next, tb + 8 - at_next);
+    }
+    float h[4], c[8], n[4];
+    io4<T>::unpack(halo, h);
+    io8<T>::unpack(cur, c);
+    io4<T>::unpack(next, n);
+    auto elem = [&](int i) { return i < 4 ? h[i < 4 ? i : 0] : (i < 12 ? c[i >= 4 && i < 12 ? i - 4 : 0] : n[i >= 12 ? i - 12 : 0]); };
+#pragma unroll
+    for (int j = 0; j < HALO + 8; ++j) xs[j] = s ? elem(j + 2) : elem(j + 1);
+#pragma unroll
+    for (int j = 0; j < HALO; ++j) xs[j] = t0 > 0 ? xs[j] : st[j];
+}
+
 // ---- forward --------------------------------------------------------------------------------
 // One wave per (row, piece); grid = ceil(B*D*pieces / NWAVES) workgroups.
 // Bound by HBM.  In the layer at 8 x 1536 x 2047 bf16, us, ROWS_ANY / ROWS_ODD: 26.0 / 24.8 (2048 steps: 21); its backward kernel
@@ -217,7 +252,9 @@ __global__ __launch_bounds__(THREADS) void conv_fwd_kernel(const ConvArgs a)
     const float bias = (a.flags & SS_CONV_HAS_BIAS) ? a.bias[d] : 0.0f;
 
     float xs[HALO + 8];
-    if constexpr (KIND == ROWS_ANY || KIND == ROWS_ODD) {
+    if constexpr (KIND == ROWS_SHIFT) {
+        load_shifted<T>(row, state_row, t0, a.L, a.W, xs);
+    } else if constexpr (KIND == ROWS_ANY || KIND == ROWS_ODD) {
         float unused[4];
         window_raw<T> wr = issue_window_any<T, KIND, false>(row, state_row, t0, a.L, a.W);
         settle_window<T, KIND, false>(wr, state_row != nullptr, t0, a.L, a.W);
@@ -238,8 +275,10 @@ __global__ __launch_bounds__(THREADS) void conv_fwd_kernel(const ConvArgs a)
         o[j] = SILU ? v * sigmoid_fast(v) : v;
     }
     const int nvalid = min(a.L - t0, 8);
-    T* const orow = static_cast<T*>(a.out) + (size_t)r * a.L;
-    if constexpr (KIND == ROWS_ANY || KIND == ROWS_ODD) {
+    T* const orow = static_cast<T*>(a.out) + (size_t)r * a.Lo;
+    if constexpr (KIND == ROWS_SHIFT) {   // whole: what lies past the end is the space between the rows
+        io8<T>::store_elem(orow + t0, 0u, io8<T>::pack(o), 8);
+    } else if constexpr (KIND == ROWS_ANY || KIND == ROWS_ODD) {
         store_slice_any<T, KIND>(orow, t0, o, nvalid);
     } else {
         io8<T>::template store<KIND == ROWS_WHOLE>(orow + t0, o, nvalid);
@@ -289,13 +328,38 @@ __global__ __launch_bounds__(THREADS) void conv_bwd_kernel(const ConvArgs a)
         const size_t r = (size_t)b * a.D + d;
         const T* row = static_cast<const T*>(a.x) + r * a.L;
         const int t0 = piece * PIECE + lane * 8 - row_phase<T, KIND>(row);
-        const T* grow = static_cast<const T*>(a.dout) + r * a.L;
+        const T* grow = static_cast<const T*>(a.dout) + r * a.Lo;
         const T* state_row = (a.flags & SS_CONV_HAS_STATE) ? static_cast<const T*>(a.state_in) + r * (a.W - 1) : nullptr;
         const int nvalid = min(max(a.L - t0, 0), 8);
 
         float xs[HALO + 8], g[8], dv[8 + HALO];
         float xn[4] = {0.f, 0.f, 0.f, 0.f}, gn[4] = {0.f, 0.f, 0.f, 0.f};   // x and dout of the 4 steps after the slice (8 steps and more)
-        if constexpr (KIND == ROWS_ANY || KIND == ROWS_ODD) {
+        if constexpr (KIND == ROWS_ODD_ONE) {
+            // dout's rows are on words, so a slice that starts early in x starts off one in them: from the element in front of it (of a first
+            // slice, in the space behind the previous row: a row off a word is not the first), and one element on in registers
+            window_raw<T> wr = issue_window_any<T, KIND, true>(row, state_row, t0, a.L, a.W);
+            const int s = row_phase<T, KIND>(row), tg = t0 - s, at_g = row_piece(tg, 8, a.L), at_n = row_piece(tg + 8, 4, a.L);
+            typename io8<T>::raw rg = io8<T>::load_elem(grow + at_g, 0u);
+            typename io4<T>::raw rgn = io4<T>::load_elem(grow + at_n, 0u);
+            settle_window<T, KIND, true>(wr, state_row != nullptr, t0, a.L, a.W);
+            if (t0 + 12 > a.L) {
+                io8<T>::drop(rg, tg - at_g);
+                io4<T>::drop(rgn, tg + 8 - at_n);
+            }
+            unpack_window<T, true>(wr, t0, xs, xn);
+            float c[8], n[4];
+            io8<T>::unpack(rg, c);
+            io4<T>::unpack(rgn, n);
+            auto elem = [&](int i) { return i < 8 ? c[i < 8 ? i : 0] : n[i >= 8 ? i - 8 : 0]; };
+#pragma unroll
+            for (int j = 0; j < 8; ++j) g[j] = s ? elem(j + 1) : elem(j);
+#pragma unroll
+            for (int j = 0; j < HALO; ++j) gn[j] = s ? elem(j + 9) : elem(j + 8);
+            if (before_row<KIND>(t0)) {
+                shift_up(xs, 0.0f);
+                g[0] = 0.0f;
+            }
+        } else if constexpr (KIND == ROWS_ANY || KIND == ROWS_ODD) {
             const uint32_t esz = (uint32_t)sizeof(T);
             window_raw<T> wr = issue_window_any<T, KIND, true>(row, state_row, t0, a.L, a.W);
             typename io8<T>::raw rg = io8<T>::load_elem(grow, (uint32_t)row_piece(slice_start<KIND>(t0), 8, a.L) * esz);
@@ -371,7 +435,7 @@ __global__ __launch_bounds__(THREADS) void conv_bwd_kernel(const ConvArgs a)
 #pragma unroll
             for (int i = 0; i < TAPS; ++i) gk[i] = fmaf(dv[j], xs[j + i], gk[i]);
         }
-        if constexpr (KIND == ROWS_ANY || KIND == ROWS_ODD) store_slice_any<T, KIND>(static_cast<T*>(a.dx) + r * a.L, t0, o, nvalid);
+        if constexpr (KIND == ROWS_ANY || starts_early(KIND)) store_slice_any<T, KIND>(static_cast<T*>(a.dx) + r * a.L, t0, o, nvalid);
         else io8<T>::template store<KIND == ROWS_WHOLE>(static_cast<T*>(a.dx) + r * a.L + t0, o, nvalid);
     }
 
@@ -474,8 +538,10 @@ hipError_t launch_conv_t(const ConvArgs& a, bool bwd, hipStream_t st)
     // 27.1 / 23.8; backward: 8 x 4096 x 101 36.3 / 38.6, 4 x 4096 x 1531 48.6 / 44.0, 8 x 1536 x 2047 48.9 / 43.5).
     const bool odd = sizeof(T) == 2 && a.L % 2 == 1 && a.L > 2 * PIECE;
     const int kind = a.L % 8 == 0 ? ROWS_WHOLE : (a.L < 8 ? ROWS_SHORT : (odd ? ROWS_ODD : ROWS_ANY));
-    if constexpr (sizeof(T) == 2)
+    if constexpr (sizeof(T) == 2) {
+        if (a.Lo != a.L) return !bwd ? launch_conv_fwd_t<T, ROWS_SHIFT>(a, st) : (odd ? launch_conv_bwd_t<T, ROWS_ODD_ONE>(a, st) : launch_conv_bwd_t<T, ROWS_ANY>(a, st));
         if (kind == ROWS_ODD) return bwd ? launch_conv_bwd_t<T, ROWS_ODD>(a, st) : launch_conv_fwd_t<T, ROWS_ODD>(a, st);
+    }
     if (kind == ROWS_WHOLE) return bwd ? launch_conv_bwd_t<T, ROWS_WHOLE>(a, st) : launch_conv_fwd_t<T, ROWS_WHOLE>(a, st);
     if (kind == ROWS_ANY) return bwd ? launch_conv_bwd_t<T, ROWS_ANY>(a, st) : launch_conv_fwd_t<T, ROWS_ANY>(a, st);
     return bwd ? launch_conv_bwd_t<T, ROWS_SHORT>(a, st) : launch_conv_fwd_t<T, ROWS_SHORT>(a, st);
@@ -523,19 +589,26 @@ ss::ConvArgs make_conv_args(const ss_conv_params* p)
     if (p->width == 1) a.flags &= ~(unsigned)(SS_CONV_HAS_STATE | SS_CONV_WRITE_STATE);
     a.x = p->x; a.state_in = p->state_in; a.w = p->w; a.bias = p->bias;
     a.out = p->out; a.state_out = p->state_out;
+    a.Lo = p->seqlen;
     return a;
+}
+bool pitch_ok(const ss_conv_params* p, int pitch)
+{
+    return pitch == p->seqlen || (p->io_dtype == SS_BF16 && p->seqlen >= 8 && p->seqlen % 2 == 1 && pitch % 8 == 0 && pitch > p->seqlen);
 }
 
 }  // namespace
 
-extern "C" {
+namespace ss {
 
-int ss_conv_fwd(const ss_conv_params* p, void* stream)
+int conv_fwd_pitched(const ss_conv_params* p, int pitch, void* stream)
 {
     const int rc = check_conv(p, false);
     if (rc != SS_OK) return rc;
+    if (!pitch_ok(p, pitch)) return SS_ERR_UNSUPPORTED;
     hipStream_t st = static_cast<hipStream_t>(stream);
-    const ss::ConvArgs a = make_conv_args(p);
+    ss::ConvArgs a = make_conv_args(p);
+    a.Lo = pitch;
     hipError_t e = hipSuccess;
     if (a.L == 0) {
         if (a.flags & SS_CONV_WRITE_STATE) {
@@ -556,11 +629,12 @@ int ss_conv_fwd(const ss_conv_params* p, void* stream)
     return e == hipSuccess ? SS_OK : SS_ERR_LAUNCH;
 }
 
-int ss_conv_bwd(const ss_conv_bwd_params* p, void* stream)
+int conv_bwd_pitched(const ss_conv_bwd_params* p, int pitch, void* stream)
 {
     if (!p) return SS_ERR_NULL;
     const int rc = check_conv(&p->fwd, true);
     if (rc != SS_OK) return rc;
+    if (!pitch_ok(&p->fwd, pitch)) return SS_ERR_UNSUPPORTED;
     const bool empty = p->fwd.seqlen == 0;
     if (!p->dw) return SS_ERR_NULL;
     if ((p->fwd.flags & SS_CONV_HAS_BIAS) && !p->dbias) return SS_ERR_NULL;
@@ -570,6 +644,7 @@ int ss_conv_bwd(const ss_conv_bwd_params* p, void* stream)
     hipStream_t st = static_cast<hipStream_t>(stream);
     ss::ConvArgs a = make_conv_args(&p->fwd);
     a.dout = p->dout; a.dx = p->dx; a.dw = p->dw;
+    a.Lo = pitch;
     a.dbias = (a.flags & SS_CONV_HAS_BIAS) ? p->dbias : nullptr;
     const size_t nw = (size_t)a.D * a.W, nb = a.dbias ? (size_t)a.D : 0;
     hipLaunchKernelGGL(ss::conv_zero_kernel, dim3((unsigned)((nw + 255) / 256)), dim3(256), 0, st, a.dw, nw, a.dbias, nb);
@@ -578,6 +653,14 @@ int ss_conv_bwd(const ss_conv_bwd_params* p, void* stream)
         e = p->fwd.io_dtype == SS_BF16 ? ss::launch_conv_t<ss::bf16_t>(a, true, st) : ss::launch_conv_t<float>(a, true, st);
     return e == hipSuccess ? SS_OK : SS_ERR_LAUNCH;
 }
+
+}  // namespace ss
+
+extern "C" {
+
+int ss_conv_fwd(const ss_conv_params* p, void* stream) { return ss::conv_fwd_pitched(p, p ? p->seqlen : 0, stream); }
+
+int ss_conv_bwd(const ss_conv_bwd_params* p, void* stream) { return ss::conv_bwd_pitched(p, p ? p->fwd.seqlen : 0, stream); }
 
 int ss_conv_step(const ss_conv_step_params* p, void* stream)
 {

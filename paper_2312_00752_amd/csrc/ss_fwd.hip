@@ -129,10 +129,10 @@ __global__ void __launch_bounds__(THREADS, PAT && AGG ? 4 : ((PAT && FUSED_KS <=
     const int r_row = min(pr, rows_here - 1);
     const uint32_t r_off = (uint32_t)r_row * (uint32_t)L * esz;
     const uint32_t r_off_bc = (uint32_t)min(s_n, N - 1) * (uint32_t)L * esz;
-    const T* const ru_p = static_cast<const T*>(a.u) + wg_first;
-    // ... delta and ysave have rows of their own (FwdArgs::Li)
+    // ... u, delta and ysave have rows of their own (FwdArgs::Li)
     const long wg_first_i = ((long)b * a.D + d0) * a.Li;
     const uint32_t r_off_i = (uint32_t)r_row * (uint32_t)a.Li * esz, r_off_p = has_z ? r_off_i : r_off;
+    const T* const ru_p = static_cast<const T*>(a.u) + wg_first_i;
     const T* const rd_p = static_cast<const T*>(a.delta) + wg_first_i;
     const T* const rz_p = has_z ? static_cast<const T*>(a.z) + wg_first : ru_p;
     const T* const rp_p = !acc_on ? ru_p : (has_z ? static_cast<const T*>(a.ysave) + wg_first_i : static_cast<const T*>(a.out) + wg_first);
@@ -232,7 +232,7 @@ __global__ void __launch_bounds__(THREADS, PAT && AGG ? 4 : ((PAT && FUSED_KS <=
         if constexpr (RAG) {   // past the segment's end: its last chunk again (never used)
             const int cc = min(c, c_end - 1) * CHUNK_T;
             const uint32_t t = (uint32_t)row_piece(cc + pq * SLICE, SLICE, L) * esz;
-            ru_[s] = io8<T>::load_elem(ru_p, r_off + t);
+            ru_[s] = io8<T>::load_elem(ru_p, r_off_i + t);
             if constexpr (FUSED_KS == 0) rd_[s] = io8<T>::load_elem(rd_p, r_off_i + t);
             if constexpr (!AGG) {
                 rz_[s] = io8<T>::load_elem(rz_p, has_z ? r_off + t : 0u);
@@ -323,7 +323,7 @@ __global__ void __launch_bounds__(THREADS, PAT && AGG ? 4 : ((PAT && FUSED_KS <=
             t[s] = (uint32_t)row_piece(cc + pq * SLICE, SLICE, L) * esz;
             tb[s] = r_off_bc + (uint32_t)row_piece(cc + s_tq * GROUP_T, GROUP_T, L) * esz;
         }
-        ru_[0] = io8<T>::load_elem(ru_p, r_off + t[0]); ru_[1] = io8<T>::load_elem(ru_p, r_off + t[1]);
+        ru_[0] = io8<T>::load_elem(ru_p, r_off_i + t[0]); ru_[1] = io8<T>::load_elem(ru_p, r_off_i + t[1]);
         if constexpr (FUSED_KS == 0) { rd_[0] = io8<T>::load_elem(rd_p, r_off_i + t[0]); rd_[1] = io8<T>::load_elem(rd_p, r_off_i + t[1]); }
         if constexpr (!AGG) {
             rz_[0] = io8<T>::load_elem(rz_p, has_z ? r_off + t[0] : 0u); rz_[1] = io8<T>::load_elem(rz_p, has_z ? r_off + t[1] : 0u);

@@ -3,6 +3,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "ss_conv.h"
 #include "ss_scan.h"
 
 namespace ss {
@@ -35,8 +36,8 @@ struct FwdArgs {
     uint32_t flags;
     int vec_ok;  // L % 8 == 0: every row starts 16-byte aligned and 8-step slices are whole or empty
     int dpp_ok;  // L >= 8 and 64 rows below 2^31 bytes: the kernels with B and C as quad-broadcast operands take the call
-    // Elements between the rows of delta, of ysave and (backward) of ddelta.  L, but where the caller owns all three and rows of L
-    // elements would start off a 32-bit word (the layer, see delta_pitch there); other than L in the kernels for any row length only.
+    // Elements between the rows of u, delta, ysave and (backward) of du and ddelta.  L, but where the caller owns all of them and rows of L
+    // elements would start off a 32-bit word (the layer, see own_pitch there); other than L in the kernels for any row length only.
     int Li;
     const void *u, *delta, *z, *Bm, *Cm;
     long bc_bstride;  // elements between consecutive batch entries of Bm and Cm (N * L when dense)
@@ -116,7 +117,7 @@ int launch_step_projected(const StepArgs& a, int io_dtype, hipStream_t stream);
 // The public scan entry points with one extra degree of freedom: B and C of batch entry b
 // start b * bc_bstride elements after Bmat / Cmat (the public calls pass dstate * seqlen).
 // Validation and return codes are those of ss_scan_fwd / ss_scan_bwd.
-// pitch: elements between the rows of delta and ddelta and of the saved y (see FwdArgs::Li); at least L, and L unless L >= 8 is odd.
+// pitch: elements between the rows of u, delta, du, ddelta and the saved y (see FwdArgs::Li); at least L, and L unless L >= 8 is odd.
 // scan_workspace_bytes is ss_workspace_bytes for it.
 int scan_fwd_strided(const ss_fwd_params* p, long bc_bstride, int pitch, void* stream);
 size_t scan_workspace_bytes(const ss_fwd_params* p, int for_backward, int pitch);
@@ -135,6 +136,11 @@ int step_strided(const ss_step_params* p, long bc_stride, void* stream);
 // conv_state, x_t: the window to slide (see StepArgs), or null.
 int step_projected(const ss_step_params* p, const float* P, const void* W_dt, int R, int ldp, void* conv_state, const void* x_t,
                    void* stream);
+
+// ss_conv_fwd / ss_conv_bwd with the rows of out / dout pitch elements apart: seqlen, or at an odd number of at least 8 16-bit elements
+// a larger multiple of 8, whose space between the rows the forward call writes too.
+int conv_fwd_pitched(const ss_conv_params* p, int pitch, void* stream);
+int conv_bwd_pitched(const ss_conv_bwd_params* p, int pitch, void* stream);
 
 // C[i] (M x N, row pitch ldc) = op(A[i]) (M x K) op(B[i]) (K x N) [+ C[i]] for i < batch, float
 // accumulation.  Element (m, k) of op(A[i]) is A[i * a_batch + m * a_m + k * a_k], element (k, n) of

@@ -365,10 +365,10 @@ ss_fwd_params scan_params(const ss_layer_params* p)
     return f;
 }
 
-// Elements between the rows of the layer's own delta and ddelta and of the saved y.  Every other row of an odd number of 16-bit elements
-// starts off a 32-bit word, where wide accesses are much slower; rows of these three are a whole number of 16-byte pieces apart.
-// us, L / this: training 8 x 1536 x 2047 954 / 907, 2 x 2560 x 4095 896 / 855, prefill 4 x 4096 x 1531 266 / 258.
-int delta_pitch(const ss_layer_params* p)
+// Elements between the rows of the layer's own tensors: u, delta, du, ddelta and the saved y.  Every other row of an odd number of 16-bit elements
+// starts off a 32-bit word, where wide accesses are much slower; rows of these are a whole number of 16-byte pieces apart.
+// us, rows of L / this: training 8 x 1536 x 2047 951 / 866, 2 x 2560 x 4095 896 / 827, prefill 4 x 4096 x 1531 266 / 249.
+int own_pitch(const ss_layer_params* p)
 {
     return p->io_dtype == SS_BF16 && p->seqlen % 2 != 0 && p->seqlen >= 8 && p->seqlen < (1 << 22) ? (p->seqlen + 7) / 8 * 8 : p->seqlen;
 }
@@ -382,7 +382,7 @@ SavedLayout saved_layout(const ss_layer_params* p)
     SavedLayout w{};
     w.P_off = 0;
     w.scan_off = round_up(s.B * s.Mx * s.L * s.esz, 256);
-    w.scan_bytes = ss::scan_workspace_bytes(&f, 1, delta_pitch(p));
+    w.scan_bytes = ss::scan_workspace_bytes(&f, 1, own_pitch(p));
     w.total = w.scan_off + round_up(w.scan_bytes, 256);
     return w;
 }
@@ -404,18 +404,18 @@ ScratchLayout scratch_layout(const ss_layer_params* p, bool bwd)
     // touches all of them at the same row and step, and with rows a large power of two of bytes apart equal
     // starting offsets into the memory channels' interleave would put all of that on one channel.
     constexpr size_t SKEW = 66560;
-    const size_t T = s.B * s.D * s.L * s.esz + SKEW, Td = s.B * s.D * delta_pitch(p) * s.esz + SKEW;
+    const size_t T = s.B * s.D * own_pitch(p) * s.esz + SKEW;
     w.u = take(T);
-    w.delta = take(Td);
+    w.delta = take(T);
     if (!bwd) {
         w.P = take(s.B * s.Mx * s.L * s.esz);
         const ss_fwd_params f = scan_params(p);
-        w.scan_ws_bytes = ss::scan_workspace_bytes(&f, 0, delta_pitch(p));
+        w.scan_ws_bytes = ss::scan_workspace_bytes(&f, 0, own_pitch(p));
         w.scan_ws = take(w.scan_ws_bytes);
         w.rT = take(s.B * round_up(s.L, 32) * round_up(s.R, 32) * s.esz);
     } else {
         w.du = take(T);
-        w.ddelta = take(Td);
+        w.ddelta = take(T);
         w.dP = take(s.B * s.Mx * s.L * s.esz);
         w.dB = take(s.B * s.N * s.L * sizeof(float));
         w.dC = take(s.B * s.N * s.L * sizeof(float));
@@ -509,16 +509,16 @@ int ss_layer_fwd(const ss_layer_params* p, void* stream)
     char* u = scratch + sc.u;
     char* delta = scratch + sc.delta;
     char* P = saved ? saved + sv.P_off : scratch + sc.P;
-    const int B = p->batch, D = p->dim, L = p->seqlen, N = p->dstate, R = p->dt_rank, Mx = R + 2 * N, Ld = delta_pitch(p);
+    const int B = p->batch, D = p->dim, L = p->seqlen, N = p->dstate, R = p->dt_rank, Mx = R + 2 * N, Ld = own_pitch(p);
 
     ss_conv_params c = conv_params(p, u);
     if (p->conv_state && p->conv_width > 1) {
         c.flags |= SS_CONV_WRITE_STATE;
         c.state_out = p->conv_state;
     }
-    if ((rc = ss_conv_fwd(&c, stream)) != SS_OK) return rc;
+    if ((rc = ss::conv_fwd_pitched(&c, Ld, stream)) != SS_OK) return rc;
     // [r;B;C] = W_x @ u
-    if (!gemm_rm(st, false, false, Mx, L, D, p->W_x, D, 0, u, L, (long)D * L, 0.0f, P, L, (long)Mx * L, B, bf16, false,
+    if (!gemm_rm(st, false, false, Mx, L, D, p->W_x, D, 0, u, Ld, (long)D * Ld, 0.0f, P, L, (long)Mx * L, B, bf16, false,
                  scratch + sc.gsplit, sc.gsplit_bytes))
         return SS_ERR_LAUNCH;
     ss_fwd_params f = scan_params(p);
@@ -581,11 +581,11 @@ int ss_layer_bwd(const ss_layer_bwd_params* q, void* stream)
     float* dB = reinterpret_cast<float*>(scratch + sc.dB);
     float* dC = reinterpret_cast<float*>(scratch + sc.dC);
     char* P = saved + sv.P_off;
-    const int B = p->batch, D = p->dim, L = p->seqlen, N = p->dstate, R = p->dt_rank, Mx = R + 2 * N, Ld = delta_pitch(p);
+    const int B = p->batch, D = p->dim, L = p->seqlen, N = p->dstate, R = p->dt_rank, Mx = R + 2 * N, Ld = own_pitch(p);
 
     // recompute the two cheap intermediates
     ss_conv_params c = conv_params(p, u);
-    if ((rc = ss_conv_fwd(&c, stream)) != SS_OK) return rc;
+    if ((rc = ss::conv_fwd_pitched(&c, Ld, stream)) != SS_OK) return rc;
     if (!gemm_rm(st, false, false, D, L, R, p->W_dt, R, 0, P, L, (long)Mx * L, 0.0f, delta, Ld, (long)D * Ld, B, bf16, false,
                  scratch + sc.gsplit, sc.gsplit_bytes))
         return SS_ERR_LAUNCH;
@@ -627,9 +627,9 @@ int ss_layer_bwd(const ss_layer_bwd_params* q, void* stream)
         if (hipGetLastError() != hipSuccess) return SS_ERR_LAUNCH;
     }
     // [r;B;C] = W_x @ u:  du += W_x^T @ dP,  dW_x = sum_b dP u^T
-    if (!gemm_rm(st, false, false, D, L, Mx, WxT, Mx, 0, dP, L, (long)Mx * L, 1.0f, du, L, (long)D * L, B, bf16))
+    if (!gemm_rm(st, false, false, D, L, Mx, WxT, Mx, 0, dP, L, (long)Mx * L, 1.0f, du, Ld, (long)D * Ld, B, bf16))
         return SS_ERR_LAUNCH;
-    if (!gemm_rm(st, false, true, Mx, D, L, dP, L, (long)Mx * L, u, L, (long)D * L, 0.0f, part_x, D, (long)Mx * D, B, bf16, true,
+    if (!gemm_rm(st, false, true, Mx, D, L, dP, L, (long)Mx * L, u, Ld, (long)D * Ld, 0.0f, part_x, D, (long)Mx * D, B, bf16, true,
                  scratch + sc.gsplit, sc.gsplit_bytes))
         return SS_ERR_LAUNCH;
     {
@@ -642,7 +642,7 @@ int ss_layer_bwd(const ss_layer_bwd_params* q, void* stream)
     ss_conv_bwd_params cb{};
     cb.fwd = conv_params(p, nullptr);
     cb.dout = du; cb.dx = q->dx; cb.dw = q->dconv_w; cb.dbias = q->dconv_b;
-    return ss_conv_bwd(&cb, stream);
+    return ss::conv_bwd_pitched(&cb, Ld, stream);
 }
 
 size_t ss_layer_step_scratch_bytes(const ss_layer_step_params* p)
