@@ -206,7 +206,7 @@ ss::FwdArgs make_fwd_args(const ss_fwd_params* p, long bc_bstride, int pitch)
     // 16-byte slices, addressed through per-workgroup buffer resources (64 rows, 31-bit offsets)
     a.dpp_ok = p->seqlen >= 8 && (size_t)p->seqlen * 64 * sizeof(float) < ((size_t)1 << 31);
     a.vec_ok = a.dpp_ok && p->seqlen % 8 == 0;
-    a.Li = pitch;
+    a.Li = a.Lb = pitch;
     a.il = deals_states(a.dpp_ok, p->flags) && a.N < 16;
     a.u = p->u; a.delta = p->delta; a.z = (p->flags & SS_HAS_Z) ? p->z : nullptr;
     a.Bm = p->Bmat; a.Cm = p->Cmat; a.A = p->A;
@@ -239,8 +239,8 @@ void narrow_to_group(ss::FwdArgs& a, const ss_fwd_params* p, int g, size_t ckpt_
     a.A = at(a.A, n0);
     a.h0 = at(a.h0, n0);
     a.h_last = at(a.h_last, n0);
-    a.Bm = (p->flags & SS_B_FIXED) ? at_bytes(a.Bm, (size_t)n0 * 4) : at_bytes(a.Bm, (size_t)n0 * p->seqlen * esz);
-    a.Cm = (p->flags & SS_C_FIXED) ? at_bytes(a.Cm, (size_t)n0 * 4) : at_bytes(a.Cm, (size_t)n0 * p->seqlen * esz);
+    a.Bm = (p->flags & SS_B_FIXED) ? at_bytes(a.Bm, (size_t)n0 * 4) : at_bytes(a.Bm, (size_t)n0 * a.Lb * esz);
+    a.Cm = (p->flags & SS_C_FIXED) ? at_bytes(a.Cm, (size_t)n0 * 4) : at_bytes(a.Cm, (size_t)n0 * a.Lb * esz);
     a.bcs = at_bytes(a.bcs, (size_t)(n0 / 4) * (a.Lp / 4) * 32 * esz);   // the group's first packed piece
     if (a.ckpt) a.ckpt = reinterpret_cast<float*>(reinterpret_cast<char*>(a.ckpt) + (size_t)g * ckpt_group_bytes);
     if (g > 0) {

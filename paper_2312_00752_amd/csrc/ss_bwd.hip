@@ -691,7 +691,7 @@ __global__ void __launch_bounds__(THREADS, 2) scan_bwd_dpp_kernel(const BwdArgs 
     const uint32_t esz = (uint32_t)sizeof(T);
     const int r_row = min(pr, rows_here - 1);
     const uint32_t r_off = (uint32_t)r_row * (uint32_t)L * esz;
-    const uint32_t r_off_bc = (uint32_t)min(s_n, N - 1) * (uint32_t)L * esz;
+    const uint32_t r_off_bc = (uint32_t)min(s_n, N - 1) * (uint32_t)f.Lb * esz;
     // ... u, delta, ysave, du and ddelta have rows of their own (FwdArgs::Li); i_off: what that adds to an offset of this thread's row
     const long wg_first_i = RAG ? ((long)b * f.D + d0) * f.Li : wg_first;
     const uint32_t i_off = RAG ? (uint32_t)pr * (uint32_t)(f.Li - L) * esz : 0u, r_off_i = (uint32_t)r_row * (uint32_t)f.Li * esz;
@@ -1255,7 +1255,7 @@ __global__ void __launch_bounds__(THREADS, 4) adjoint_agg_dpp_kernel(const BwdAr
     const uint32_t esz = (uint32_t)sizeof(T);
     const int r_row = min(pr, rows_here - 1);
     const uint32_t r_off = (uint32_t)r_row * (uint32_t)L * esz;
-    const uint32_t r_off_c = (uint32_t)min(s_n, N - 1) * (uint32_t)L * esz;
+    const uint32_t r_off_c = (uint32_t)min(s_n, N - 1) * (uint32_t)f.Lb * esz;
     const uint32_t r_off_i = (uint32_t)r_row * (uint32_t)f.Li * esz;   // delta has rows of its own (FwdArgs::Li)
     const T* const rd_p = static_cast<const T*>(f.delta) + ((long)b * f.D + d0) * f.Li;
     const T* const ro_p = static_cast<const T*>(a.dout) + wg_first;

@@ -39,6 +39,7 @@ struct FwdArgs {
     // Elements between the rows of u, delta, ysave and (backward) of du and ddelta.  L, but where the caller owns all of them and rows of L
     // elements would start off a 32-bit word (the layer, see own_pitch there); other than L in the kernels for any row length only.
     int Li;
+    int Lb;   // ... and between those of selective B and C
     const void *u, *delta, *z, *Bm, *Cm;
     long bc_bstride;  // elements between consecutive batch entries of Bm and Cm (N * L when dense)
     // Staged copy of the selective B and C for the forward kernels, or null.  In the io dtype,
@@ -117,7 +118,7 @@ int launch_step_projected(const StepArgs& a, int io_dtype, hipStream_t stream);
 // The public scan entry points with one extra degree of freedom: B and C of batch entry b
 // start b * bc_bstride elements after Bmat / Cmat (the public calls pass dstate * seqlen).
 // Validation and return codes are those of ss_scan_fwd / ss_scan_bwd.
-// pitch: elements between the rows of u, delta, du, ddelta and the saved y (see FwdArgs::Li); at least L, and L unless L >= 8 is odd.
+// pitch: elements between the rows of u, delta, B, C, du, ddelta and the saved y (see FwdArgs::Li; of dB and dC: L); at least L, and L unless L >= 8 is odd.
 // scan_workspace_bytes is ss_workspace_bytes for it.
 int scan_fwd_strided(const ss_fwd_params* p, long bc_bstride, int pitch, void* stream);
 size_t scan_workspace_bytes(const ss_fwd_params* p, int for_backward, int pitch);

@@ -38,10 +38,10 @@ bool gemm_rm(hipStream_t st, bool tA, bool tB, int M, int N, int K, const void* 
 }
 
 // ---- small kernels around the GEMMs -----------------------------------------------------------
-// dB, dC (B,N,L) float32 -> rows R.. of d[r;B;C] (B, R+2N, L) in the io dtype.
+// dB, dC (B,N,L) float32 -> rows R.. of d[r;B;C] (B, R+2N, rows ld apart) in the io dtype.
 template <typename T>
 __global__ void pack_dbc_kernel(const float* __restrict__ dB, const float* __restrict__ dC, T* __restrict__ dP,
-                                int N, int R, long L, long total)
+                                int N, int R, long L, long ld, long total)
 {
     const long i = (long)blockIdx.x * blockDim.x + threadIdx.x;   // over B * 2N * L
     if (i >= total) return;
@@ -50,7 +50,7 @@ __global__ void pack_dbc_kernel(const float* __restrict__ dB, const float* __res
     const long b = row / (2 * N);
     const int j = int(row - b * 2 * N);   // 0..N-1: B, N..2N-1: C
     const float v = j < N ? dB[(b * N + j) * L + l] : dC[(b * N + (j - N)) * L + l];
-    T* dst = dP + (b * (R + 2 * N) + R + j) * L + l;
+    T* dst = dP + (b * (R + 2 * N) + R + j) * ld + l;
     if constexpr (sizeof(T) == 2) *dst = T(ss::f32_to_bf16_bits(v));
     else *dst = v;
 }
@@ -293,10 +293,10 @@ int launch_conv_xproj(const ss_layer_step_params* p, void* u, float* P, hipStrea
     return launch_conv_xproj_rows<T, 4>(p, u, P, st);
 }
 
-// r (the first R rows of each batch entry of P, (B, Mx, L)) transposed and zero-padded to
+// r (the first R rows of each batch entry of P, (B, Mx, L), rows ld apart) transposed and zero-padded to
 // (B, Lp, Rp), for the delta projection inside the scan kernel (see FwdArgs::rT).  32 x 32 tiles
 // through LDS; block (32, 8), grid (Lp / 32, Rp / 32, B).
-__global__ void transpose_r_kernel(const ss::bf16_t* __restrict__ P, long bstride, ss::bf16_t* __restrict__ rT, int R, int L,
+__global__ void transpose_r_kernel(const ss::bf16_t* __restrict__ P, long bstride, int ld, ss::bf16_t* __restrict__ rT, int R, int L,
                                    int Lp, int Rp)
 {
     __shared__ ss::bf16_t tile[32][33];
@@ -305,7 +305,7 @@ __global__ void transpose_r_kernel(const ss::bf16_t* __restrict__ P, long bstrid
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
         const int r = r0 + ty + 8 * i, t = t0 + tx;
-        tile[ty + 8 * i][tx] = (r < R && t < L) ? P[(size_t)b * bstride + (size_t)r * L + t] : ss::bf16_t(0);
+        tile[ty + 8 * i][tx] = (r < R && t < L) ? P[(size_t)b * bstride + (size_t)r * ld + t] : ss::bf16_t(0);
     }
     __syncthreads();
 #pragma unroll
@@ -365,9 +365,10 @@ ss_fwd_params scan_params(const ss_layer_params* p)
     return f;
 }
 
-// Elements between the rows of the layer's own tensors: u, delta, du, ddelta and the saved y.  Every other row of an odd number of 16-bit elements
+// Elements between the rows of the layer's own tensors: u, [r;B;C], delta, their gradients and the saved y.  Every other row of an odd number of 16-bit elements
 // starts off a 32-bit word, where wide accesses are much slower; rows of these are a whole number of 16-byte pieces apart.
-// us, rows of L / this: training 8 x 1536 x 2047 951 / 866, 2 x 2560 x 4095 896 / 827, prefill 4 x 4096 x 1531 266 / 249.
+// us, rows of L / this: training 8 x 1536 x 2047 951 / 835, 2 x 2560 x 4095 896 / 771, prefill 4 x 4096 x 1531 266 / 247 (the nt products of
+// the first 46 and 31 / 23 and 20, since a wave reads its fragments of [r;B;C] straight from memory).
 int own_pitch(const ss_layer_params* p)
 {
     return p->io_dtype == SS_BF16 && p->seqlen % 2 != 0 && p->seqlen >= 8 && p->seqlen < (1 << 22) ? (p->seqlen + 7) / 8 * 8 : p->seqlen;
@@ -381,7 +382,7 @@ SavedLayout saved_layout(const ss_layer_params* p)
     const ss_fwd_params f = scan_params(p);
     SavedLayout w{};
     w.P_off = 0;
-    w.scan_off = round_up(s.B * s.Mx * s.L * s.esz, 256);
+    w.scan_off = round_up(s.B * s.Mx * own_pitch(p) * s.esz, 256);
     w.scan_bytes = ss::scan_workspace_bytes(&f, 1, own_pitch(p));
     w.total = w.scan_off + round_up(w.scan_bytes, 256);
     return w;
@@ -408,7 +409,7 @@ ScratchLayout scratch_layout(const ss_layer_params* p, bool bwd)
     w.u = take(T);
     w.delta = take(T);
     if (!bwd) {
-        w.P = take(s.B * s.Mx * s.L * s.esz);
+        w.P = take(s.B * s.Mx * own_pitch(p) * s.esz);
         const ss_fwd_params f = scan_params(p);
         w.scan_ws_bytes = ss::scan_workspace_bytes(&f, 0, own_pitch(p));
         w.scan_ws = take(w.scan_ws_bytes);
@@ -416,7 +417,7 @@ ScratchLayout scratch_layout(const ss_layer_params* p, bool bwd)
     } else {
         w.du = take(T);
         w.ddelta = take(T);
-        w.dP = take(s.B * s.Mx * s.L * s.esz);
+        w.dP = take(s.B * s.Mx * own_pitch(p) * s.esz);
         w.dB = take(s.B * s.N * s.L * sizeof(float));
         w.dC = take(s.B * s.N * s.L * sizeof(float));
         w.part_dt = take(s.B * s.D * s.R * sizeof(float));
@@ -518,13 +519,13 @@ int ss_layer_fwd(const ss_layer_params* p, void* stream)
     }
     if ((rc = ss::conv_fwd_pitched(&c, Ld, stream)) != SS_OK) return rc;
     // [r;B;C] = W_x @ u
-    if (!gemm_rm(st, false, false, Mx, L, D, p->W_x, D, 0, u, Ld, (long)D * Ld, 0.0f, P, L, (long)Mx * L, B, bf16, false,
+    if (!gemm_rm(st, false, false, Mx, L, D, p->W_x, D, 0, u, Ld, (long)D * Ld, 0.0f, P, Ld, (long)Mx * Ld, B, bf16, false,
                  scratch + sc.gsplit, sc.gsplit_bytes))
         return SS_ERR_LAUNCH;
     ss_fwd_params f = scan_params(p);
     f.u = u; f.delta = delta; f.z = p->z;
-    f.Bmat = P + (size_t)R * L * s.esz;
-    f.Cmat = P + (size_t)(R + N) * L * s.esz;
+    f.Bmat = P + (size_t)R * Ld * s.esz;
+    f.Cmat = P + (size_t)(R + N) * Ld * s.esz;
     f.A = p->A; f.Dskip = p->Dskip; f.delta_bias = p->dt_bias;
     f.out = p->out;
     if (p->h_last) {
@@ -544,16 +545,16 @@ int ss_layer_fwd(const ss_layer_params* p, void* stream)
         ss::bf16_t* rT = reinterpret_cast<ss::bf16_t*>(scratch + sc.rT);
         const int Lp = (L + 31) / 32 * 32, Rp = (R + 31) / 32 * 32;
         hipLaunchKernelGGL(transpose_r_kernel, dim3((unsigned)(Lp / 32), (unsigned)(Rp / 32), (unsigned)B), dim3(32, 8), 0, st,
-                           reinterpret_cast<const ss::bf16_t*>(P), (long)Mx * L, rT, R, L, Lp, Rp);
+                           reinterpret_cast<const ss::bf16_t*>(P), (long)Mx * Ld, Ld, rT, R, L, Lp, Rp);
         if (hipGetLastError() != hipSuccess) return SS_ERR_LAUNCH;
-        rc = ss::scan_fwd_fused(&f, (long)Mx * L, Ld, p->W_dt, R, rT, stream);
+        rc = ss::scan_fwd_fused(&f, (long)Mx * Ld, Ld, p->W_dt, R, rT, stream);
         if (rc != SS_ERR_UNSUPPORTED) return rc;   // otherwise nothing was enqueued: take the general path
     }
     // delta_raw = W_dt @ r
-    if (!gemm_rm(st, false, false, D, L, R, p->W_dt, R, 0, P, L, (long)Mx * L, 0.0f, delta, Ld, (long)D * Ld, B, bf16, false,
+    if (!gemm_rm(st, false, false, D, L, R, p->W_dt, R, 0, P, Ld, (long)Mx * Ld, 0.0f, delta, Ld, (long)D * Ld, B, bf16, false,
                  scratch + sc.gsplit, sc.gsplit_bytes))
         return SS_ERR_LAUNCH;
-    return ss::scan_fwd_strided(&f, (long)Mx * L, Ld, stream);
+    return ss::scan_fwd_strided(&f, (long)Mx * Ld, Ld, stream);
 }
 
 int ss_layer_bwd(const ss_layer_bwd_params* q, void* stream)
@@ -586,7 +587,7 @@ int ss_layer_bwd(const ss_layer_bwd_params* q, void* stream)
     // recompute the two cheap intermediates
     ss_conv_params c = conv_params(p, u);
     if ((rc = ss::conv_fwd_pitched(&c, Ld, stream)) != SS_OK) return rc;
-    if (!gemm_rm(st, false, false, D, L, R, p->W_dt, R, 0, P, L, (long)Mx * L, 0.0f, delta, Ld, (long)D * Ld, B, bf16, false,
+    if (!gemm_rm(st, false, false, D, L, R, p->W_dt, R, 0, P, Ld, (long)Mx * Ld, 0.0f, delta, Ld, (long)D * Ld, B, bf16, false,
                  scratch + sc.gsplit, sc.gsplit_bytes))
         return SS_ERR_LAUNCH;
 
@@ -594,8 +595,8 @@ int ss_layer_bwd(const ss_layer_bwd_params* q, void* stream)
     ss_bwd_params b{};
     b.fwd = scan_params(p);
     b.fwd.u = u; b.fwd.delta = delta; b.fwd.z = p->z;
-    b.fwd.Bmat = P + (size_t)R * L * s.esz;
-    b.fwd.Cmat = P + (size_t)(R + N) * L * s.esz;
+    b.fwd.Bmat = P + (size_t)R * Ld * s.esz;
+    b.fwd.Cmat = P + (size_t)(R + N) * Ld * s.esz;
     b.fwd.A = p->A; b.fwd.Dskip = p->Dskip; b.fwd.delta_bias = p->dt_bias;
     b.fwd.workspace = saved + sv.scan_off;
     b.fwd.workspace_bytes = sv.scan_bytes;
@@ -603,7 +604,7 @@ int ss_layer_bwd(const ss_layer_bwd_params* q, void* stream)
     b.du = du; b.ddelta = ddelta; b.dz = q->dz;
     b.dB = dB; b.dC = dC;
     b.dA = q->dA; b.dD = q->dD; b.ddelta_bias = q->ddt_bias;
-    if ((rc = ss::scan_bwd_strided(&b, (long)Mx * L, Ld, stream)) != SS_OK) return rc;
+    if ((rc = ss::scan_bwd_strided(&b, (long)Mx * Ld, Ld, stream)) != SS_OK) return rc;
 
     // The two products with a transposed weight take it from a transposed copy (a megabyte each), so
     // that their first operand is contiguous along the contraction index like everywhere else.
@@ -612,24 +613,24 @@ int ss_layer_bwd(const ss_layer_bwd_params* q, void* stream)
         !(bf16 ? transpose_weight<ss::bf16_t>(p->W_x, WxT, Mx, D, st) : transpose_weight<float>(p->W_x, WxT, Mx, D, st)))
         return SS_ERR_LAUNCH;
     // delta_raw = W_dt @ r:  dr = W_dt^T @ ddelta  (rows 0..R-1 of dP),  dW_dt = sum_b ddelta r^T
-    if (!gemm_rm(st, false, false, R, L, D, WdtT, D, 0, ddelta, Ld, (long)D * Ld, 0.0f, dP, L, (long)Mx * L, B, bf16, false,
+    if (!gemm_rm(st, false, false, R, L, D, WdtT, D, 0, ddelta, Ld, (long)D * Ld, 0.0f, dP, Ld, (long)Mx * Ld, B, bf16, false,
                  scratch + sc.gsplit, sc.gsplit_bytes))
         return SS_ERR_LAUNCH;
-    if (!gemm_rm(st, false, true, D, R, L, ddelta, Ld, (long)D * Ld, P, L, (long)Mx * L, 0.0f, part_dt, R, (long)D * R, B, bf16, true,
+    if (!gemm_rm(st, false, true, D, R, L, ddelta, Ld, (long)D * Ld, P, Ld, (long)Mx * Ld, 0.0f, part_dt, R, (long)D * R, B, bf16, true,
                  scratch + sc.gsplit, sc.gsplit_bytes))
         return SS_ERR_LAUNCH;
     // rows R.. of dP from the scan's float32 dB, dC
     {
         const long total = (long)B * 2 * N * L;
         const dim3 grid((unsigned)((total + 255) / 256));
-        if (bf16) hipLaunchKernelGGL(pack_dbc_kernel<ss::bf16_t>, grid, dim3(256), 0, st, dB, dC, reinterpret_cast<ss::bf16_t*>(dP), N, R, (long)L, total);
-        else hipLaunchKernelGGL(pack_dbc_kernel<float>, grid, dim3(256), 0, st, dB, dC, reinterpret_cast<float*>(dP), N, R, (long)L, total);
+        if (bf16) hipLaunchKernelGGL(pack_dbc_kernel<ss::bf16_t>, grid, dim3(256), 0, st, dB, dC, reinterpret_cast<ss::bf16_t*>(dP), N, R, (long)L, (long)Ld, total);
+        else hipLaunchKernelGGL(pack_dbc_kernel<float>, grid, dim3(256), 0, st, dB, dC, reinterpret_cast<float*>(dP), N, R, (long)L, (long)Ld, total);
         if (hipGetLastError() != hipSuccess) return SS_ERR_LAUNCH;
     }
     // [r;B;C] = W_x @ u:  du += W_x^T @ dP,  dW_x = sum_b dP u^T
-    if (!gemm_rm(st, false, false, D, L, Mx, WxT, Mx, 0, dP, L, (long)Mx * L, 1.0f, du, Ld, (long)D * Ld, B, bf16))
+    if (!gemm_rm(st, false, false, D, L, Mx, WxT, Mx, 0, dP, Ld, (long)Mx * Ld, 1.0f, du, Ld, (long)D * Ld, B, bf16))
         return SS_ERR_LAUNCH;
-    if (!gemm_rm(st, false, true, Mx, D, L, dP, L, (long)Mx * L, u, Ld, (long)D * Ld, 0.0f, part_x, D, (long)Mx * D, B, bf16, true,
+    if (!gemm_rm(st, false, true, Mx, D, L, dP, Ld, (long)Mx * Ld, u, Ld, (long)D * Ld, 0.0f, part_x, D, (long)Mx * D, B, bf16, true,
                  scratch + sc.gsplit, sc.gsplit_bytes))
         return SS_ERR_LAUNCH;
     {
