@@ -372,7 +372,7 @@ int scan_fwd_fused(const ss_fwd_params* p, long bc_bstride, int pitch, const voi
     return scan_fwd_impl(p, bc_bstride, pitch, W_dt, R, rT, stream);
 }
 
-int scan_bwd_strided(const ss_bwd_params* p, long bc_bstride, int pitch, void* stream)
+int scan_bwd_strided(const ss_bwd_params* p, long bc_bstride, int pitch, const BwdSide* side, void* stream)
 {
     if (!p) return SS_ERR_NULL;
     if (!pitch_ok(&p->fwd, pitch)) return SS_ERR_UNSUPPORTED;
@@ -421,6 +421,7 @@ int scan_bwd_strided(const ss_bwd_params* p, long bc_bstride, int pitch, void* s
     a.dbias = (f->flags & SS_HAS_DELTA_BIAS) ? p->ddelta_bias : nullptr;
     a.acc = 0;
     a.dbc_bstride = (long)slots(f) * f->seqlen;
+    if (side) a.bc_cleared = side->bc_cleared;
     // one pass per group of 16 states, in stream order: each adds its share of du, ddelta and
     // dbias to the earlier ones' and writes its own slices of dA, dB, dC and dh0
     const int groups = (slots(f) + 15) / 16;
@@ -437,6 +438,10 @@ int scan_bwd_strided(const ss_bwd_params* p, long bc_bstride, int pitch, void* s
             ag.dB = at(ag.dB, (f->flags & SS_B_FIXED) ? (long)n0 : (long)n0 * f->seqlen);
             ag.dC = at(ag.dC, (f->flags & SS_C_FIXED) ? (long)n0 : (long)n0 * f->seqlen);
             if (g > 0) { ag.dz = nullptr; ag.dD = nullptr; }
+        }
+        if (side && g == groups - 1) {   // all of dB and dC are there
+            ag.pack = side->pack; ag.pack_ld = side->pack_ld; ag.pack_bstride = side->pack_bstride;
+            ag.pack_dB = p->dB; ag.pack_dC = p->dC;
         }
         if (ss::launch_bwd(ag, f->io_dtype, static_cast<hipStream_t>(stream)) != 0) return SS_ERR_LAUNCH;
     }
@@ -529,7 +534,7 @@ int ss_scan_fwd_static(const ss_fwd_params* p, void* stream)
 int ss_scan_bwd(const ss_bwd_params* p, void* stream)
 {
     if (!p) return SS_ERR_NULL;
-    return ss::scan_bwd_strided(p, (long)slots(&p->fwd) * p->fwd.seqlen, p->fwd.seqlen, stream);
+    return ss::scan_bwd_strided(p, (long)slots(&p->fwd) * p->fwd.seqlen, p->fwd.seqlen, nullptr, stream);
 }
 
 int ss_step(const ss_step_params* p, void* stream)

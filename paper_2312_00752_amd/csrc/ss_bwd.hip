@@ -1442,9 +1442,21 @@ __global__ void zero_kernel(float* __restrict__ p0, float* __restrict__ p1, long
 // (4 channels x 16 slots) and its FIN_LANES waves share the partials, so that a split sequence's
 // B * nseg of them (64 at 8 x 1536 x 2048) are not one thread's serial chain of 27 us: forward + backward
 // 623 -> 602 us there, 9544 -> 9454 us with 124 segments.  The waves' shares are added in a fixed order.
+// Workgroups from fin_blocks on pack dB and dC for the layer's products instead (a launch of 5 us less).
 constexpr int FIN_LANES = 8;
-__global__ void __launch_bounds__(64 * FIN_LANES) finalize_kernel(const BwdArgs a, int have_partials)
+template <typename T>
+__global__ void __launch_bounds__(64 * FIN_LANES) finalize_kernel(const BwdArgs a, int have_partials, int fin_blocks)
 {
+    if ((int)blockIdx.x >= fin_blocks) {   // uniform
+        const long i = (long)(blockIdx.x - fin_blocks) * (64 * FIN_LANES) + threadIdx.x, L = a.f.L;   // over B * 2N * L
+        const int NS = a.f.NS;
+        if (i >= (long)a.f.B * 2 * NS * L) return;
+        const long row = i / L, l = i - row * L, b = row / (2 * NS);
+        const int j = int(row - b * 2 * NS);   // 0..N-1: dB, N..2N-1: dC
+        const float v = j < NS ? a.pack_dB[(b * NS + j) * L + l] : a.pack_dC[(b * NS + (j - NS)) * L + l];
+        static_cast<T*>(a.pack)[b * a.pack_bstride + j * a.pack_ld + l] = f32_to_io<T>(v);
+        return;
+    }
     __shared__ float share[4][FIN_LANES][64];
     const int col = threadIdx.x & 63, part = threadIdx.x >> 6;
     const int d = blockIdx.x * (64 / NPAD) + col / NPAD;
@@ -1643,7 +1655,7 @@ int launch_bwd(const BwdArgs& a, int io_dtype, hipStream_t stream)
     const FwdArgs& f = a.f;
     const int fin_blocks = (f.D * NPAD + 63) / 64;
     if (f.L == 0) {
-        finalize_kernel<<<dim3(fin_blocks), dim3(64 * FIN_LANES), 0, stream>>>(a, 0);
+        finalize_kernel<float><<<dim3(fin_blocks), dim3(64 * FIN_LANES), 0, stream>>>(a, 0, fin_blocks);
         if (a.dh0 && !a.acc) {
             const long n = (long)f.B * f.D * f.NS;
             copy_dh_kernel<<<dim3((unsigned)((n + 255) / 256)), dim3(256), 0, stream>>>(a.dh_last, a.dh0, n);
@@ -1658,7 +1670,8 @@ int launch_bwd(const BwdArgs& a, int io_dtype, hipStream_t stream)
     // (a launch of 4 us less in each such call)
     BwdArgs b = a;
     b.zero_n = 0;
-    if (zB && zC && f.nseg > 1 && f.dpp_ok && !(f.flags & F_COMPLEX)) {
+    if (a.bc_cleared) {
+    } else if (zB && zC && f.nseg > 1 && f.dpp_ok && !(f.flags & F_COMPLEX)) {
         b.zeroB = zB; b.zeroC = zC; b.zero_n = nbc;
     } else if (zB || zC) {
         zero_kernel<<<dim3((unsigned)((nbc + 255) / 256)), dim3(256), 0, stream>>>(zB, zC, nbc);
@@ -1667,7 +1680,10 @@ int launch_bwd(const BwdArgs& a, int io_dtype, hipStream_t stream)
     const dim3 grid((unsigned)(f.B * groups));
     const int rc = io_dtype == 0 ? launch_bwd_io<float>(b, grid, stream) : launch_bwd_io<bf16_t>(b, grid, stream);
     if (rc != 0) return rc;
-    finalize_kernel<<<dim3(fin_blocks), dim3(64 * FIN_LANES), 0, stream>>>(a, 1);
+    const long packed = a.pack ? 2 * nbc : 0;
+    const dim3 fin((unsigned)(fin_blocks + (packed + 64 * FIN_LANES - 1) / (64 * FIN_LANES)));
+    if (io_dtype == 0) finalize_kernel<float><<<fin, dim3(64 * FIN_LANES), 0, stream>>>(a, 1, fin_blocks);
+    else finalize_kernel<bf16_t><<<fin, dim3(64 * FIN_LANES), 0, stream>>>(a, 1, fin_blocks);
     return hipGetLastError() == hipSuccess ? 0 : -1;
 }
 

@@ -629,7 +629,7 @@ int conv_fwd_pitched(const ss_conv_params* p, int pitch, void* stream)
     return e == hipSuccess ? SS_OK : SS_ERR_LAUNCH;
 }
 
-int conv_bwd_pitched(const ss_conv_bwd_params* p, int pitch, void* stream)
+int conv_bwd_pitched(const ss_conv_bwd_params* p, int pitch, bool cleared, void* stream)
 {
     if (!p) return SS_ERR_NULL;
     const int rc = check_conv(&p->fwd, true);
@@ -647,7 +647,7 @@ int conv_bwd_pitched(const ss_conv_bwd_params* p, int pitch, void* stream)
     a.Lo = pitch;
     a.dbias = (a.flags & SS_CONV_HAS_BIAS) ? p->dbias : nullptr;
     const size_t nw = (size_t)a.D * a.W, nb = a.dbias ? (size_t)a.D : 0;
-    hipLaunchKernelGGL(ss::conv_zero_kernel, dim3((unsigned)((nw + 255) / 256)), dim3(256), 0, st, a.dw, nw, a.dbias, nb);
+    if (!cleared) hipLaunchKernelGGL(ss::conv_zero_kernel, dim3((unsigned)((nw + 255) / 256)), dim3(256), 0, st, a.dw, nw, a.dbias, nb);
     hipError_t e = hipGetLastError();
     if (e == hipSuccess && !empty)
         e = p->fwd.io_dtype == SS_BF16 ? ss::launch_conv_t<ss::bf16_t>(a, true, st) : ss::launch_conv_t<float>(a, true, st);
@@ -660,7 +660,7 @@ extern "C" {
 
 int ss_conv_fwd(const ss_conv_params* p, void* stream) { return ss::conv_fwd_pitched(p, p ? p->seqlen : 0, stream); }
 
-int ss_conv_bwd(const ss_conv_bwd_params* p, void* stream) { return ss::conv_bwd_pitched(p, p ? p->fwd.seqlen : 0, stream); }
+int ss_conv_bwd(const ss_conv_bwd_params* p, void* stream) { return ss::conv_bwd_pitched(p, p ? p->fwd.seqlen : 0, false, stream); }
 
 int ss_conv_step(const ss_conv_step_params* p, void* stream)
 {

@@ -82,6 +82,11 @@ struct BwdArgs {
     long zero_n;                // (zero_n floats each), or 0
     float* dh0;
     float *dA, *dD, *dbias;     // final outputs of the reduction kernel
+    // what the reduction kernel copies on the side: all of dB and dC, 2 * NS rows a batch entry, in the io dtype (null: nothing)
+    const float *pack_dB, *pack_dC;
+    void* pack;
+    long pack_ld, pack_bstride;
+    int bc_cleared;             // dB and dC are zeros already
 };
 
 constexpr int STEP_NPARTS = 4;   // partial results the layer's decode projection leaves for the step kernel
@@ -128,7 +133,14 @@ size_t scan_workspace_bytes(const ss_fwd_params* p, int for_backward, int pitch)
 // does not qualify (then use scan_fwd_strided with delta in memory).
 int scan_fwd_fused(const ss_fwd_params* p, long bc_bstride, int pitch, const void* W_dt, int R, const void* rT, void* stream);
 bool scan_fwd_fusable(const ss_fwd_params* p, int pitch, int R);   // whether scan_fwd_fused would take the call
-int scan_bwd_strided(const ss_bwd_params* p, long bc_bstride, int pitch, void* stream);
+// What the layer has the backward scan's launches do on the side, instead of launches of its own: dB and dC are zeros already; the
+// float32 sums dB and dC also go to the rows of pack, in the io dtype (batch entries pack_bstride, rows pack_ld elements apart).
+struct BwdSide {
+    bool bc_cleared;
+    void* pack;
+    long pack_ld, pack_bstride;
+};
+int scan_bwd_strided(const ss_bwd_params* p, long bc_bstride, int pitch, const BwdSide* side, void* stream);
 // ss_step with B_t / C_t rows bc_stride elements apart (the public call passes dstate).
 int step_strided(const ss_step_params* p, long bc_stride, void* stream);
 
@@ -141,7 +153,8 @@ int step_projected(const ss_step_params* p, const float* P, const void* W_dt, in
 // ss_conv_fwd / ss_conv_bwd with the rows of out / dout pitch elements apart: seqlen, or at an odd number of at least 8 16-bit elements
 // a larger multiple of 8, whose space between the rows the forward call writes too.
 int conv_fwd_pitched(const ss_conv_params* p, int pitch, void* stream);
-int conv_bwd_pitched(const ss_conv_bwd_params* p, int pitch, void* stream);
+// cleared: dw and dbias are zeros already.
+int conv_bwd_pitched(const ss_conv_bwd_params* p, int pitch, bool cleared, void* stream);
 
 // C[i] (M x N, row pitch ldc) = op(A[i]) (M x K) op(B[i]) (K x N) [+ C[i]] for i < batch, float
 // accumulation.  Element (m, k) of op(A[i]) is A[i * a_batch + m * a_m + k * a_k], element (k, n) of

@@ -38,35 +38,19 @@ bool gemm_rm(hipStream_t st, bool tA, bool tB, int M, int N, int K, const void* 
 }
 
 // ---- small kernels around the GEMMs -----------------------------------------------------------
-// dB, dC (B,N,L) float32 -> rows R.. of d[r;B;C] (B, R+2N, rows ld apart) in the io dtype.
-template <typename T>
-__global__ void pack_dbc_kernel(const float* __restrict__ dB, const float* __restrict__ dC, T* __restrict__ dP,
-                                int N, int R, long L, long ld, long total)
+// out[i] = sum_b part[b][i], accumulation in batch order, for the partial results of two weight gradients.
+__global__ void sum_partials_kernel(const float* __restrict__ part0, long n0, float* __restrict__ out0, const float* __restrict__ part1,
+                                    long n1, float* __restrict__ out1, int nb)
 {
-    const long i = (long)blockIdx.x * blockDim.x + threadIdx.x;   // over B * 2N * L
-    if (i >= total) return;
-    const long l = i % L;
-    const long row = i / L;               // b * 2N + j
-    const long b = row / (2 * N);
-    const int j = int(row - b * 2 * N);   // 0..N-1: B, N..2N-1: C
-    const float v = j < N ? dB[(b * N + j) * L + l] : dC[(b * N + (j - N)) * L + l];
-    T* dst = dP + (b * (R + 2 * N) + R + j) * ld + l;
-    if constexpr (sizeof(T) == 2) *dst = T(ss::f32_to_bf16_bits(v));
-    else *dst = v;
-}
-
-// out[i] = sum_b part[b][i], float32 accumulation in batch order.
-template <typename T>
-__global__ void sum_partials_kernel(const T* __restrict__ part, int nb, long n, float* __restrict__ out)
-{
-    const long i = (long)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n) return;
+    long i = (long)blockIdx.x * blockDim.x + threadIdx.x;
+    if (i >= n0 + n1) return;
+    const bool second = i >= n0;
+    const float* __restrict__ part = second ? part1 : part0;
+    const long n = second ? n1 : n0;
+    if (second) i -= n0;
     float acc = 0.0f;
-    for (int b = 0; b < nb; ++b) {
-        if constexpr (sizeof(T) == 2) acc += ss::bf16_to_f32(part[b * n + i]);
-        else acc += part[b * n + i];
-    }
-    out[i] = acc;
+    for (int b = 0; b < nb; ++b) acc += part[b * n + i];
+    (second ? out1 : out0)[i] = acc;
 }
 
 // ---- decode: [r;B;C]_t = u_t @ W_x^T on the matrix cores --------------------------------------------
@@ -315,13 +299,36 @@ __global__ void transpose_r_kernel(const ss::bf16_t* __restrict__ P, long bstrid
     }
 }
 
-// dst (cols, rows) = src (rows, cols)^T for a weight matrix, 32 x 32 tiles through LDS; block (32, 8),
-// grid (cols / 32 rounded up, rows / 32 rounded up).
+// What the backward pass needs before its first kernel, in one launch (as launches of their own these four were 5 us each, one
+// after the other): the weights W_dt and W_x transposed, (rows, cols) -> (cols, rows), a 32 x 32 tile through LDS per workgroup of
+// (32, 8) threads, and zeros where the scan's and the convolution's kernels add up dB and dC, and the tap and bias gradients.
+struct BeginArgs {
+    const void* src[2];
+    void* dst[2];
+    int rows[2], cols[2], tiles[2];
+    float* zero[4];
+    long n[4];
+    int zero_blocks;
+};
 template <typename T>
-__global__ void transpose_weight_kernel(const T* __restrict__ src, T* __restrict__ dst, int rows, int cols)
+__global__ void __launch_bounds__(256) bwd_begin_kernel(const BeginArgs a)
 {
     __shared__ T tile[32][33];
-    const int c0 = blockIdx.x * 32, r0 = blockIdx.y * 32;
+    int blk = blockIdx.x;
+    if (blk >= a.tiles[0] + a.tiles[1]) {   // uniform
+        blk -= a.tiles[0] + a.tiles[1];
+        const long first = (long)blk * 256 + threadIdx.y * 32 + threadIdx.x, step = (long)a.zero_blocks * 256;
+#pragma unroll
+        for (int k = 0; k < 4; ++k)
+            for (long i = first; i < a.n[k]; i += step) a.zero[k][i] = 0.0f;
+        return;
+    }
+    const int m = blk >= a.tiles[0];
+    if (m) blk -= a.tiles[0];
+    const T* __restrict__ src = static_cast<const T*>(a.src[m]);
+    T* __restrict__ dst = static_cast<T*>(a.dst[m]);
+    const int rows = a.rows[m], cols = a.cols[m], across = (cols + 31) / 32;
+    const int c0 = blk % across * 32, r0 = blk / across * 32;
     const int tx = threadIdx.x, ty = threadIdx.y;
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
@@ -334,13 +341,6 @@ __global__ void transpose_weight_kernel(const T* __restrict__ src, T* __restrict
         const int c = c0 + ty + 8 * i, r = r0 + tx;
         if (r < rows && c < cols) dst[(size_t)c * rows + r] = tile[tx][ty + 8 * i];
     }
-}
-template <typename T>
-bool transpose_weight(const void* src, void* dst, int rows, int cols, hipStream_t st)
-{
-    hipLaunchKernelGGL(transpose_weight_kernel<T>, dim3((unsigned)((cols + 31) / 32), (unsigned)((rows + 31) / 32)), dim3(32, 8), 0, st,
-                       static_cast<const T*>(src), static_cast<T*>(dst), rows, cols);
-    return hipGetLastError() == hipSuccess;
 }
 
 // ---- buffers -------------------------------------------------------------------------------------
@@ -578,18 +578,45 @@ int ss_layer_bwd(const ss_layer_bwd_params* q, void* stream)
     char* scratch = static_cast<char*>(p->scratch);
     char* saved = static_cast<char*>(p->saved);
     char *u = scratch + sc.u, *delta = scratch + sc.delta, *du = scratch + sc.du, *ddelta = scratch + sc.ddelta;
-    char *dP = scratch + sc.dP, *part_dt = scratch + sc.part_dt, *part_x = scratch + sc.part_x;
+    char* dP = scratch + sc.dP;
     float* dB = reinterpret_cast<float*>(scratch + sc.dB);
     float* dC = reinterpret_cast<float*>(scratch + sc.dC);
     char* P = saved + sv.P_off;
     const int B = p->batch, D = p->dim, L = p->seqlen, N = p->dstate, R = p->dt_rank, Mx = R + 2 * N, Ld = own_pitch(p);
 
+    // The two products with a transposed weight take it from a transposed copy (a megabyte each), so
+    // that their first operand is contiguous along the contraction index like everywhere else.
+    char *WdtT = scratch + sc.WdtT, *WxT = scratch + sc.WxT;
+    {
+        BeginArgs g{};
+        auto weight = [&](int m, const void* src, void* dst, int rows, int cols) {
+            g.src[m] = src; g.dst[m] = dst; g.rows[m] = rows; g.cols[m] = cols;
+            g.tiles[m] = (rows + 31) / 32 * ((cols + 31) / 32);   // below 2^31: dim * rows of W_x is (check_layer)
+        };
+        weight(0, p->W_dt, WdtT, D, R);
+        weight(1, p->W_x, WxT, Mx, D);
+        auto zeros = [&](int k, float* dst, long n) { g.zero[k] = dst; g.n[k] = n; };
+        const long nbc = (long)B * N * L;
+        zeros(0, dB, nbc);
+        zeros(1, dC, nbc);
+        zeros(2, q->dconv_w, (long)D * p->conv_width);
+        zeros(3, q->dconv_b, D);
+        g.zero_blocks = (int)std::min(1024L, (std::max(nbc, (long)D * p->conv_width) + 255) / 256);
+        const dim3 grid((unsigned)(g.tiles[0] + g.tiles[1] + g.zero_blocks)), block(32, 8);
+        if (bf16) hipLaunchKernelGGL(bwd_begin_kernel<ss::bf16_t>, grid, block, 0, st, g);
+        else hipLaunchKernelGGL(bwd_begin_kernel<float>, grid, block, 0, st, g);
+        if (hipGetLastError() != hipSuccess) return SS_ERR_LAUNCH;
+    }
     // recompute the two cheap intermediates
     ss_conv_params c = conv_params(p, u);
     if ((rc = ss::conv_fwd_pitched(&c, Ld, stream)) != SS_OK) return rc;
     if (!gemm_rm(st, false, false, D, L, R, p->W_dt, R, 0, P, Ld, (long)Mx * Ld, 0.0f, delta, Ld, (long)D * Ld, B, bf16, false,
                  scratch + sc.gsplit, sc.gsplit_bytes))
         return SS_ERR_LAUNCH;
+
+    // the weight gradients of each batch entry; of a single one they are the result
+    float* part_dt = B == 1 ? q->dW_dt : reinterpret_cast<float*>(scratch + sc.part_dt);
+    float* part_x = B == 1 ? q->dW_x : reinterpret_cast<float*>(scratch + sc.part_x);
 
     // the scan
     ss_bwd_params b{};
@@ -604,14 +631,10 @@ int ss_layer_bwd(const ss_layer_bwd_params* q, void* stream)
     b.du = du; b.ddelta = ddelta; b.dz = q->dz;
     b.dB = dB; b.dC = dC;
     b.dA = q->dA; b.dD = q->dD; b.ddelta_bias = q->ddt_bias;
-    if ((rc = ss::scan_bwd_strided(&b, (long)Mx * Ld, Ld, stream)) != SS_OK) return rc;
+    // ... which leaves dB and dC next to where dr will be as well: rows R.. of dP
+    const ss::BwdSide side = {true, dP + (size_t)R * Ld * s.esz, Ld, (long)Mx * Ld};
+    if ((rc = ss::scan_bwd_strided(&b, (long)Mx * Ld, Ld, &side, stream)) != SS_OK) return rc;
 
-    // The two products with a transposed weight take it from a transposed copy (a megabyte each), so
-    // that their first operand is contiguous along the contraction index like everywhere else.
-    char *WdtT = scratch + sc.WdtT, *WxT = scratch + sc.WxT;
-    if (!(bf16 ? transpose_weight<ss::bf16_t>(p->W_dt, WdtT, D, R, st) : transpose_weight<float>(p->W_dt, WdtT, D, R, st)) ||
-        !(bf16 ? transpose_weight<ss::bf16_t>(p->W_x, WxT, Mx, D, st) : transpose_weight<float>(p->W_x, WxT, Mx, D, st)))
-        return SS_ERR_LAUNCH;
     // delta_raw = W_dt @ r:  dr = W_dt^T @ ddelta  (rows 0..R-1 of dP),  dW_dt = sum_b ddelta r^T
     if (!gemm_rm(st, false, false, R, L, D, WdtT, D, 0, ddelta, Ld, (long)D * Ld, 0.0f, dP, Ld, (long)Mx * Ld, B, bf16, false,
                  scratch + sc.gsplit, sc.gsplit_bytes))
@@ -619,31 +642,23 @@ int ss_layer_bwd(const ss_layer_bwd_params* q, void* stream)
     if (!gemm_rm(st, false, true, D, R, L, ddelta, Ld, (long)D * Ld, P, Ld, (long)Mx * Ld, 0.0f, part_dt, R, (long)D * R, B, bf16, true,
                  scratch + sc.gsplit, sc.gsplit_bytes))
         return SS_ERR_LAUNCH;
-    // rows R.. of dP from the scan's float32 dB, dC
-    {
-        const long total = (long)B * 2 * N * L;
-        const dim3 grid((unsigned)((total + 255) / 256));
-        if (bf16) hipLaunchKernelGGL(pack_dbc_kernel<ss::bf16_t>, grid, dim3(256), 0, st, dB, dC, reinterpret_cast<ss::bf16_t*>(dP), N, R, (long)L, (long)Ld, total);
-        else hipLaunchKernelGGL(pack_dbc_kernel<float>, grid, dim3(256), 0, st, dB, dC, reinterpret_cast<float*>(dP), N, R, (long)L, (long)Ld, total);
-        if (hipGetLastError() != hipSuccess) return SS_ERR_LAUNCH;
-    }
     // [r;B;C] = W_x @ u:  du += W_x^T @ dP,  dW_x = sum_b dP u^T
     if (!gemm_rm(st, false, false, D, L, Mx, WxT, Mx, 0, dP, Ld, (long)Mx * Ld, 1.0f, du, Ld, (long)D * Ld, B, bf16))
         return SS_ERR_LAUNCH;
     if (!gemm_rm(st, false, true, Mx, D, L, dP, Ld, (long)Mx * Ld, u, Ld, (long)D * Ld, 0.0f, part_x, D, (long)Mx * D, B, bf16, true,
                  scratch + sc.gsplit, sc.gsplit_bytes))
         return SS_ERR_LAUNCH;
-    {
+    if (B > 1) {
         const long n_dt = (long)D * R, n_x = (long)Mx * D;
-        hipLaunchKernelGGL(sum_partials_kernel<float>, dim3((unsigned)((n_dt + 255) / 256)), dim3(256), 0, st, reinterpret_cast<const float*>(part_dt), B, n_dt, q->dW_dt);
-        hipLaunchKernelGGL(sum_partials_kernel<float>, dim3((unsigned)((n_x + 255) / 256)), dim3(256), 0, st, reinterpret_cast<const float*>(part_x), B, n_x, q->dW_x);
+        hipLaunchKernelGGL(sum_partials_kernel, dim3((unsigned)((n_dt + n_x + 255) / 256)), dim3(256), 0, st,
+                           part_dt, n_dt, q->dW_dt, part_x, n_x, q->dW_x, B);
         if (hipGetLastError() != hipSuccess) return SS_ERR_LAUNCH;
     }
     // u = SiLU(conv(x))
     ss_conv_bwd_params cb{};
     cb.fwd = conv_params(p, nullptr);
     cb.dout = du; cb.dx = q->dx; cb.dw = q->dconv_w; cb.dbias = q->dconv_b;
-    return ss::conv_bwd_pitched(&cb, Ld, stream);
+    return ss::conv_bwd_pitched(&cb, Ld, true, stream);
 }
 
 size_t ss_layer_step_scratch_bytes(const ss_layer_step_params* p)
