@@ -271,13 +271,10 @@ __global__ void __launch_bounds__(THREADS, WGS) scan_bwd_kernel(const BwdArgs a)
     const int sd = s_ok ? d0 + lane : f.D - 1;
     const long srow = (long)b * f.D + sd;
     constexpr bool BFIX = BCFIX & 1, CFIX = BCFIX & 2;
-    // Whether the sums that only the end of the loop reads (dA, dB, dC) are held to their place in the sweeps.  Left alone
-    // they sink below them, which takes registers: the builds that are short of those, and the ones whose loads do not
-    // already break the sweep up, are faster with the pin (exact ZOH, fixed B, 8 x 4096 x 2048 bf16: 8155 -> 2346 us
-    // backward; float32, fixed C, 2 x 4096 x 2048: 675 -> 565).  Off eight steps, where every load of a row is a branch,
-    // it costs instead wherever registers are left (one workgroup per unit, 4 x 4096 x 2047, fixed C, bf16: 2186 -> 2224 us;
-    // float32 1254 -> 1328; bf16, fixed B and C, 889 -> 923; complex, two per unit, 8 x 4096: 4369 -> 4408).
-    constexpr bool PINNED = VEC || ZOH || (BCFIX != 0 ? WGS == 2 : sizeof(T) == 4);
+    // The sums that only the end of the loop reads (dA, dB, dC) are held to their place in the sweeps (the empty asm statements).  Left alone
+    // they sink below them, which takes registers: exact ZOH, fixed B, 8 x 4096 x 2048 bf16: 8155 -> 2346 us backward; float32, fixed C,
+    // 2 x 4096 x 2048: 675 -> 565.  Off eight steps, forward + backward, without / with: complex 8 x 4096 x 2047 bf16 3646 / 3607,
+    // fixed B and C 4 x 4096 x 103 131 / 125, no difference in others.
     float A2[STATES_PER_LANE], An[STATES_PER_LANE], invA[STATES_PER_LANE], ag[STATES_PER_LANE], dA[STATES_PER_LANE];
     float Bf[STATES_PER_LANE], Cf[STATES_PER_LANE], dBf[STATES_PER_LANE], dCf[STATES_PER_LANE];
     const T* __restrict__ gB[STATES_PER_LANE];
@@ -316,14 +313,13 @@ __global__ void __launch_bounds__(THREADS, WGS) scan_bwd_kernel(const BwdArgs a)
 #pragma unroll
         for (int s = 0; s < LG; ++s) {
             const int blk = grp * LG + s;
-            const int t0 = blk * BT + pq * BSL;
-            const int nv = p_ok ? min(max(L - t0, 0), BSL) : 0;  // rows past D contribute nothing
-            ru[s] = io4<T>::template load<VEC>(gu + t0, nv);
-            rd[s] = io4<T>::template load<VEC>(gdl + t0, nv);
-            ro[s] = io4<T>::template load<VEC>(gdo + t0, nv);
+            const int t0 = blk * BT + pq * BSL;   // rows past D contribute nothing
+            ru[s] = load_slice4<T, VEC>(gu, t0, L, p_ok);
+            rd[s] = load_slice4<T, VEC>(gdl, t0, L, p_ok);
+            ro[s] = load_slice4<T, VEC>(gdo, t0, L, p_ok);
             if (has_z) {
-                rz[s] = io4<T>::template load<VEC>(gz + t0, nv);
-                ry[s] = io4<T>::template load<VEC>(gy + t0, nv);
+                rz[s] = load_slice4<T, VEC>(gz, t0, L, p_ok);
+                ry[s] = load_slice4<T, VEC>(gy, t0, L, p_ok);
             }
         }
     };
@@ -378,7 +374,7 @@ __global__ void __launch_bounds__(THREADS, WGS) scan_bwd_kernel(const BwdArgs a)
                     dz4[j] = o4[j] * y4[j] * s * fmaf(z4[j], 1.0f - s, 1.0f);  // dout y d[z sigmoid(z)]/dz
                     dy4[j] = o4[j] * z4[j] * s;
                 }
-                if (a.dz) io4<T>::template store<VEC>(gdz + t0, dz4, nv);   // null for all but the first state group
+                if (a.dz) store_slice<T, VEC, io4, BSL>(gdz + t0, dz4, nv);   // null for all but the first state group
             }
             *reinterpret_cast<float4*>(&sm.dt[pr][pq * BSL]) = make_float4(dt4[0], dt4[1], dt4[2], dt4[3]);
             *reinterpret_cast<float4*>(&sm.du[pr][pq * BSL]) = make_float4(du4[0], du4[1], du4[2], du4[3]);
@@ -443,7 +439,7 @@ __global__ void __launch_bounds__(THREADS, WGS) scan_bwd_kernel(const BwdArgs a)
                     if (g > 0) reduce_take(red, dbc + STATES_PER_LANE * BT + tl - GROUP_T, lane);  // previous group
                     reduce_put(dCv, red, lane);
                 }
-                if constexpr (CFIX && PINNED) asm volatile("" : "+v"(dCf[0]), "+v"(dCf[1]), "+v"(dCf[2]), "+v"(dCf[3]));
+                if constexpr (CFIX) asm volatile("" : "+v"(dCf[0]), "+v"(dCf[1]), "+v"(dCf[2]), "+v"(dCf[3]));
             }
             if (!CFIX) reduce_take(red, dbc + STATES_PER_LANE * BT + (NG - 1) * GROUP_T, lane);
         }
@@ -521,8 +517,8 @@ __global__ void __launch_bounds__(THREADS, WGS) scan_bwd_kernel(const BwdArgs a)
                 reduce_put(dBv, red, lane);
             }
             // the sums that only the end of the loop reads are formed here, not below the sweep (see scan_bwd_dpp_kernel)
-            if constexpr (PINNED) asm volatile("" : "+v"(dA[0]), "+v"(dA[1]), "+v"(dA[2]), "+v"(dA[3]));
-            if constexpr (BFIX && PINNED) asm volatile("" : "+v"(dBf[0]), "+v"(dBf[1]), "+v"(dBf[2]), "+v"(dBf[3]));
+            asm volatile("" : "+v"(dA[0]), "+v"(dA[1]), "+v"(dA[2]), "+v"(dA[3]));
+            if constexpr (BFIX) asm volatile("" : "+v"(dBf[0]), "+v"(dBf[1]), "+v"(dBf[2]), "+v"(dBf[3]));
         }
         if (!BFIX) reduce_take(red, dbc, lane);
         // ---- flush this wave's dB/dC of the block to global memory -------------------------
@@ -565,13 +561,13 @@ __global__ void __launch_bounds__(THREADS, WGS) scan_bwd_kernel(const BwdArgs a)
             }
             if (a.acc) {  // states beyond the first 16: add to the earlier groups' du and ddelta
                 float pu[BSL], pl[BSL];
-                io4<T>::unpack(io4<T>::template load<VEC>(gdu + t0, nv), pu);
-                io4<T>::unpack(io4<T>::template load<VEC>(gdd + t0, nv), pl);
+                io4<T>::unpack(load_slice4<T, VEC>(gdu, t0, L, p_ok), pu);
+                io4<T>::unpack(load_slice4<T, VEC>(gdd, t0, L, p_ok), pl);
 #pragma unroll
                 for (int j = 0; j < BSL; ++j) { du4[j] += pu[j]; dl4[j] += pl[j]; }
             }
-            io4<T>::template store<VEC>(gdu + t0, du4, nv);
-            io4<T>::template store<VEC>(gdd + t0, dl4, nv);
+            store_slice<T, VEC, io4, BSL>(gdu + t0, du4, nv);
+            store_slice<T, VEC, io4, BSL>(gdd + t0, dl4, nv);
         }
         // the next phase A rewrites only this thread's own slices of dt/du/dy; the share
         // tiles are rewritten only after the next barrier
@@ -1135,10 +1131,9 @@ __global__ void __launch_bounds__(THREADS) adjoint_agg_kernel(const BwdArgs a)
     typename io8<T>::raw rd, rz, ro;
     auto issue_loads = [&](int c) {
         const int t0 = c * CHUNK_T + pq * SLICE;
-        const int nv = p_ok ? min(max(L - t0, 0), SLICE) : 0;
-        rd = io8<T>::template load<VEC>(gdl + t0, nv);
-        ro = io8<T>::template load<VEC>(gdo + t0, nv);
-        if (has_z) rz = io8<T>::template load<VEC>(gz + t0, nv);
+        rd = load_slice8<T, VEC>(gdl, t0, L, p_ok);
+        ro = load_slice8<T, VEC>(gdo, t0, L, p_ok);
+        if (has_z) rz = load_slice8<T, VEC>(gz, t0, L, p_ok);
     };
     issue_loads(c_end - 1);
     uint32_t touched = 0u;
@@ -1526,13 +1521,8 @@ constexpr unsigned COMPUTE_UNITS = 256;
 //   workgroups                                 256           512
 //   B, real, bf16, 2048 steps                  645 / 568     828 / 1131
 //   B, complex, f32, 2048 steps                773 / 670     1006 / 1359
-//   C, real, f32, 2047 steps                   1425 / 1262   1926 / 2456
-//   C, complex, f32, 2047 steps                1602 / 1344   2083 / 2617
-//   B and C, real, bf16, 2047 steps            898 / 864     1324 / 1739
 //   C, real, f32, 2048 steps                   596 / 601     1007 / 1009   (built for two only)
-//   B and C, real, f32, 2047 steps             882 / 938     1478 / 1668   (built for two only)
-//   B and C, complex, bf16, 2047 steps         1008 / 1009   1494 / 2025   (built for two only)
-// (The one-workgroup builds off eight steps are without the pin described in scan_bwd_kernel.)
+// Off eight steps, 4 x 4096 x 103 (256 workgroups, unsplit), forward + backward: C, complex, f32 123 / 112; real ones within 3 %.
 template <typename T, bool VEC, int BCFIX, bool CPLX>
 constexpr bool ONE_WG_WINS = BCFIX == 1 || (BCFIX == 2 && (CPLX || !VEC)) || (BCFIX == 3 && !CPLX && !VEC && sizeof(T) == 2);
 template <typename T, bool VEC, bool FULLN, bool ZOH, int BCFIX, bool CPLX = false, int WGS = ZOH ? 1 : 2>

@@ -252,9 +252,9 @@ __global__ void __launch_bounds__(THREADS, PAT && AGG ? 4 : ((PAT && FUSED_KS <=
                 rbc_[s] = io4<T>::load_buf(bbc, (ts < L && c < c_end) ? bc_row_off + (uint32_t)ts * (uint32_t)sizeof(T) : BUF_OFF);
             }
         } else {
-            ru_[s] = io8<T>::template load<VEC>(gu + t0, nv);
-            rd_[s] = io8<T>::template load<VEC>(gdl + t0, nv);
-            if (has_z) rz_[s] = io8<T>::template load<VEC>(gz + t0, nv);
+            ru_[s] = load_slice8<T, VEC>(gu, t0, L, true);
+            rd_[s] = load_slice8<T, VEC>(gdl, t0, L, true);
+            if (has_z) rz_[s] = load_slice8<T, VEC>(gz, t0, L, true);
         }
     };
     // FUSED: delta_raw of a chunk from the fragments in registers: two 16 x 16 tiles per wave,
@@ -624,8 +624,8 @@ __global__ void __launch_bounds__(THREADS, PAT && AGG ? 4 : ((PAT && FUSED_KS <=
                     for (int j = 0; j < SLICE; ++j) y8[j] += p8[j];
                 }
             } else if (a.acc_y) {
-                const T* prev = (has_z ? static_cast<const T*>(a.ysave) : static_cast<const T*>(a.out)) + prow * L + t0;
-                io8<T>::unpack(io8<T>::template load<VEC>(prev, nvs), p8);
+                const T* prev = (has_z ? static_cast<const T*>(a.ysave) : static_cast<const T*>(a.out)) + prow * L;
+                io8<T>::unpack(load_slice8<T, VEC>(prev, t0, L, p_ok), p8);
 #pragma unroll
                 for (int j = 0; j < SLICE; ++j) y8[j] += p8[j];
             }
@@ -679,11 +679,11 @@ __global__ void __launch_bounds__(THREADS, PAT && AGG ? 4 : ((PAT && FUSED_KS <=
             } else {
                 if (has_z) {
                     if (a.ysave)  // y before the gate, for the backward pass's dz
-                        io8<T>::template store<VEC>(static_cast<T*>(a.ysave) + prow * L + t0, y8, nvs);
+                        store_slice<T, VEC, io8, SLICE>(static_cast<T*>(a.ysave) + prow * L + t0, y8, nvs);
 #pragma unroll
                     for (int j = 0; j < SLICE; ++j) y8[j] *= z8[j] * sigmoid_fast(z8[j]);
                 }
-                io8<T>::template store<VEC>(gout + t0, y8, nvs);
+                store_slice<T, VEC, io8, SLICE>(gout + t0, y8, nvs);
             }
         }
         // no barrier needed here: the next phase A writes s_dt/s_du, which every wave has
