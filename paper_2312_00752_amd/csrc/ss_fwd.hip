@@ -1000,14 +1000,19 @@ constexpr int SP_LDP = STEP_MAX_LDP + 4;          // row stride of the staged P 
 
 // WIN: the convolution's window slides here, the projection having formed u itself (see StepArgs).
 template <typename T, bool FULLN, int SP_BT, bool WIN = false>
-__global__ void __launch_bounds__(SP_THREADS, SP_BT == 8 && sizeof(T) == 2 ? 4 : 2) step_proj_kernel(const StepArgs a)
+__global__ void __launch_bounds__(SP_THREADS, SP_BT == 8 ? 4 : 2) step_proj_kernel(const StepArgs a)
 {
     static_assert(SP_BT == 8 || SP_BT == SP_MFMA_ROWS, "batch tile");
     constexpr int SP_PER = SP_BT / 2;                // batch entries per thread
     using mma = tile_mma<T>;
-    constexpr int SP_MAX_KSTEPS = SP_MAX_R / mma::K;  // contraction steps of the delta projection
+    // Contraction steps of the delta projection a wave takes.  In float, where they are twice as many and four dependent MFMAs each, all eight
+    // waves share them, the second four every other step: half the registers for W_dt, so that two workgroups of the 8-entry tile fit a CU
+    // (float32, D 5120, kernel: batch 64 28.4 -> 18.8 us, 256 86 -> 50; D 1536, batch 128, the 16-entry tile 10.8 -> 9.8).
+    constexpr bool HALVES = sizeof(T) == 4;
+    constexpr int SP_MAX_KSTEPS = SP_MAX_R / mma::K / (HALVES ? 2 : 1), KSTRIDE = HALVES ? 2 * mma::K : mma::K;
     __shared__ __attribute__((aligned(16))) float s_p[SP_BT][SP_LDP];   // r, and from SP_MAX_R on B and C
     __shared__ float s_dt[SP_MFMA_ROWS][64];
+    __shared__ f32x4_t s_half[HALVES ? 4 : 1][HALVES ? 64 : 1];
     const int tid = threadIdx.x;
     const int lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -1063,6 +1068,7 @@ __global__ void __launch_bounds__(SP_THREADS, SP_BT == 8 && sizeof(T) == 2 ? 4 :
     const int dcol = 16 * (wave & 3) + (lane & 15);
     const int wrow = min(d0 + dcol, a.D - 1);
     const int ksub = mma::E * (lane >> 4);
+    const int kfirst = HALVES ? mma::K * (wave >> 2) : 0;   // this wave's first step
     u32x4 wfrag[SP_MAX_KSTEPS];
     const float bias_raw = (has_bias ? a.bias : a.A)[has_bias ? wrow : 0];
     {
@@ -1070,7 +1076,7 @@ __global__ void __launch_bounds__(SP_THREADS, SP_BT == 8 && sizeof(T) == 2 ? 4 :
         const int woff = (wrow - d0) * R;
 #pragma unroll
         for (int i = 0; i < SP_MAX_KSTEPS; ++i)
-            wfrag[i] = load_any<u32x4>(wp, (uint32_t)(woff + row_piece(mma::K * i + ksub, mma::E, R)) * (uint32_t)sizeof(T));
+            wfrag[i] = load_any<u32x4>(wp, (uint32_t)(woff + row_piece(kfirst + KSTRIDE * i + ksub, mma::E, R)) * (uint32_t)sizeof(T));
     }
 
     {
@@ -1102,13 +1108,13 @@ __global__ void __launch_bounds__(SP_THREADS, SP_BT == 8 && sizeof(T) == 2 ? 4 :
     }
     __syncthreads();
 
-    if (wave < 4) {
+    f32x4_t acc = {0.f, 0.f, 0.f, 0.f};
+    if (HALVES || wave < 4) {
         const int arow = min(lane & 15, nbt - 1);             // rows past the end shadow the last one
         const float* pp = &s_p[arow][ksub];
-        f32x4_t acc = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
         for (int i = 0; i < SP_MAX_KSTEPS; ++i) {
-            const int k = mma::K * i;
+            const int k = kfirst + KSTRIDE * i;
             if (k < R) {                                      // uniform
                 float pv[mma::E];
 #pragma unroll
@@ -1126,6 +1132,13 @@ __global__ void __launch_bounds__(SP_THREADS, SP_BT == 8 && sizeof(T) == 2 ? 4 :
                 acc = mma::step(av, wv, acc);
             }
         }
+    }
+    if constexpr (HALVES) {
+        if (wave >= 4) s_half[wave & 3][lane] = acc;
+        __syncthreads();
+        if (wave < 4) acc += s_half[wave][lane];
+    }
+    if (wave < 4) {
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
             float x = as_stored(acc[i]) + (has_bias ? bias_raw : 0.0f), dt = x, sg;
