@@ -37,16 +37,17 @@ struct SegPlan {
 };
 // Modelled duration (in steps of one unsplit workgroup running alone on its compute unit) of a
 // launch of n equal workgroups of len steps each.  Two workgroups fit a compute unit and then
-// each runs at about 3/4 of the speed it has alone (measured: 256 workgroups of 2048 steps
+// take `pair` times what one takes alone (selective B and C 4/3: 256 workgroups of 2048 steps
 // take 1.01 ms, 512 take 1.35 ms), so the chip takes workgroups in rounds of 512.  A workgroup's
 // set-up, pipeline fill and final stores cost about as much as 32 more steps (fitted to sweeps of
 // the segment count at 160 x 16384, 192 x 2048 and 4 x 2^20 workgroups x steps).  The fits are of the main passes and of
 // aggregate passes that ran two workgroups per unit as well.  The aggregate kernels have since come to run four; what
 // they take per step is now 0.35 (4 x 2^20), 0.40 (160 x 16384) and 0.44 (192 x 2048) of a main pass, and neither the
-// rounds nor the 0.36 below have been fitted again.
-double launch_cost(long n, long len)
+// rounds nor AGG_COST have been fitted again.
+constexpr double AGG_COST = 0.36;   // an aggregate pass, per step of a main pass (over forward + backward)
+double launch_cost(long n, long len, double pair = 1.0 / 0.75)
 {
-    const double pair = 1.0 / 0.75, fixed = 32.0;
+    const double fixed = 32.0;
     const long full = n / 512, rest = n % 512;
     return ((double)len + fixed) * ((double)full * pair + (rest == 0 ? 0.0 : (rest <= 256 ? 1.0 : pair)));
 }
@@ -72,8 +73,7 @@ SegPlan plan_segments(int B, int D, int L)
     if (s.seg_len == 0) s.seg_len = 32;
     if (L < 128) return s;
     // Pick the number of segments that the model says finishes first: the main pass over
-    // wgs * nseg workgroups plus the aggregate pass over wgs * (nseg - 1) of them, which costs
-    // about 0.36 of a main pass per step (measured over forward + backward).  Segments stay
+    // wgs * nseg workgroups plus the aggregate pass over wgs * (nseg - 1) of them.  Segments stay
     // at least 64 steps long (two forward chunks), and a launch within 8192 workgroups, which
     // bounds the aggregates' workspace.
     double best = launch_cost(wgs, s.seg_len);
@@ -85,7 +85,7 @@ SegPlan plan_segments(int B, int D, int L)
         const long len = segment_length(L, want);
         const long n = (L + len - 1) / len;   // what that length really gives
         if (n < 2) continue;
-        const double c = launch_cost(wgs * n, len) + 0.36 * launch_cost(wgs * (n - 1), len);
+        const double c = launch_cost(wgs * n, len) + AGG_COST * launch_cost(wgs * (n - 1), len);
         if (c < best * 0.97) { best = c; best_n = want; }   // more segments only for a clear gain
     }
     if (best_n > 1) {
@@ -93,6 +93,49 @@ SegPlan plan_segments(int B, int D, int L)
         s.nseg = (L + s.seg_len - 1) / s.seg_len;
     }
     return s;
+}
+
+// Whether that plan pays with a time-invariant B and / or C, whose kernels are others: forward + backward of 72 grids of 64 to 2112 row
+// groups x 128 to 8192 steps in the 18 forms of B and C, state, rule and dtype, whole and in this plan, by the model above with what two
+// workgroups of a unit take (pair) and what the launches of a split call cost beside (launches, in steps) fitted for each form.  Where it
+// keeps a split that does not pay, that costs 6 % at most (256 x 2048 float32 C 840 / 891).  us, whole / split, refused: exact zero-order hold, whose backward
+// kernels have a unit to themselves, 256 x 2048 bf16 B and C 1339 / 1539; B and C in registers, float32 256 x 2048 665 / 889, bf16
+// 256 x 512 175 / 192; grids that share units as they are, 320 x 2048 float32 C 1 / 1.04.  Kept: 64 x 2048 bf16 B 777 / 230, with the
+// exact hold 1576 / 512, 320 x 2048 1 / 0.84; 256 x 2048 bf16 B 790 / 689.
+bool fixed_split_pays(const ss_fwd_params* p, const SegPlan& s)
+{
+    const bool both = (p->flags & SS_B_FIXED) && (p->flags & SS_C_FIXED), zoh = p->flags & SS_EXACT_ZOH_B;
+    const bool f32 = p->io_dtype != SS_BF16, cplx = p->flags & SS_COMPLEX_STATE, whole_slices = p->seqlen % 8 == 0;
+    const long wgs = (long)p->batch * ((p->dim + 63) / 64);
+    if (!zoh && wgs > 256 && wgs <= 512) return false;
+    double pair = 1.3, launches = 30.0;
+    if (zoh) {
+        pair = both ? 1.35 : 1.25;
+        launches = 0.0;
+    } else if (both) {
+        pair = whole_slices ? (f32 ? 1.95 : 1.55) : (f32 ? 1.8 : 1.4);
+        if (!whole_slices) launches = f32 ? 0.0 : 40.0;
+    } else if (f32 && whole_slices) {
+        if (cplx || (p->flags & SS_B_FIXED)) pair = cplx ? 1.5 : 1.55;
+    } else if (f32 && (p->flags & SS_B_FIXED)) {
+        pair = cplx ? 1.65 : 1.4;
+        launches = cplx ? 0.0 : 40.0;
+    }
+    auto main_pass = [&](long n, long len) {
+        const double shared = launch_cost(n, len, pair);
+        return zoh ? 0.4 * shared + 0.6 * (double)(len + 32) * (double)((n + 255) / 256) : shared;   // forward + backward
+    };
+    return main_pass(wgs * s.nseg, s.seg_len) + AGG_COST * launch_cost(wgs * (s.nseg - 1), s.seg_len, pair) + launches <
+           main_pass(wgs, (p->seqlen + 31) / 32 * 32);
+}
+
+inline bool fixed_bc(const ss_fwd_params* p) { return p->flags & (SS_B_FIXED | SS_C_FIXED); }
+// a forward call with a time-invariant B or C that keeps nothing asks for no scratch, and is not split
+inline int split_steps(const ss_fwd_params* p, bool for_bwd) { return for_bwd || !fixed_bc(p) ? p->seqlen : 0; }
+SegPlan plan_of(const ss_fwd_params* p, bool for_bwd)
+{
+    const SegPlan s = plan_segments(p->batch, p->dim, split_steps(p, for_bwd));
+    return s.nseg > 1 && fixed_bc(p) && !fixed_split_pays(p, s) ? plan_segments(p->batch, p->dim, 0) : s;
 }
 
 // Workspace layouts, each block 256-byte aligned.
@@ -117,15 +160,13 @@ inline bool stageable(const ss_fwd_params* p)
 {
     return !(p->flags & (SS_B_FIXED | SS_C_FIXED | SS_COMPLEX_STATE)) && p->seqlen > 0;
 }
-WsLayout ws_layout(const ss_fwd_params* p, bool for_bwd, int pitch)
+WsLayout ws_layout(const ss_fwd_params* p, bool for_bwd, int pitch, const SegPlan& plan)
 {
     const size_t nck = ((size_t)p->seqlen + SS_CHECKPOINT_STEPS - 1) / SS_CHECKPOINT_STEPS;
     const size_t rows = (size_t)p->batch * p->dim;
     const size_t esz = p->io_dtype == SS_BF16 ? 2 : 4;
     WsLayout w{};
-    // a forward call with a time-invariant B or C that keeps nothing asks for no scratch, and is not split
-    const bool split_ok = for_bwd || !(p->flags & (SS_B_FIXED | SS_C_FIXED));
-    w.plan = plan_segments(p->batch, p->dim, split_ok ? p->seqlen : 0);
+    w.plan = plan;
     const size_t ns = (size_t)w.plan.nseg, split = ns > 1 ? 1 : 0;
     size_t off = 0;
     auto take = [&](size_t bytes) { const size_t at = off; off += round_up(bytes, 256); return at; };
@@ -148,6 +189,7 @@ WsLayout ws_layout(const ss_fwd_params* p, bool for_bwd, int pitch)
     w.total = off;
     return w;
 }
+WsLayout ws_layout(const ss_fwd_params* p, bool for_bwd, int pitch) { return ws_layout(p, for_bwd, pitch, plan_of(p, for_bwd)); }
 
 int check_fwd(const ss_fwd_params* p, bool for_bwd, int pitch, bool bc_dense = true)
 {
@@ -289,7 +331,7 @@ bool scan_fwd_fusable(const ss_fwd_params* p, int pitch, int R)
     if (R <= 192 && (R > 128 || p->seqlen % 8 != 0)) return false;
     // eight states or fewer are dealt out to kernels of one or two slots per lane, which are built without the projection
     if (slots(p) <= 8) return false;
-    if (plan_segments(p->batch, p->dim, p->seqlen).nseg != 1) return false;
+    if (plan_of(p, true).nseg != 1) return false;   // stageable: B and C selective
     return p->workspace && aligned(p->workspace, 256) &&
            p->workspace_bytes >= ws_layout(p, (p->flags & SS_SAVE_FOR_BWD) != 0, pitch).total;
 }
@@ -363,7 +405,8 @@ int scan_fwd_strided(const ss_fwd_params* p, long bc_bstride, int pitch, void* s
 size_t scan_workspace_bytes(const ss_fwd_params* p, int for_backward, int pitch)
 {
     if (!p || p->batch < 1 || p->dim < 1 || p->seqlen < 0) return 0;
-    return ws_layout(p, for_backward != 0, pitch).total;
+    // of the split plan, whether or not it pays: that depends on what a query need not give (SS_EXACT_ZOH_B)
+    return ws_layout(p, for_backward != 0, pitch, plan_segments(p->batch, p->dim, split_steps(p, for_backward != 0))).total;
 }
 
 int scan_fwd_fused(const ss_fwd_params* p, long bc_bstride, int pitch, const void* W_dt, int R, const void* rT, void* stream)
