@@ -336,10 +336,12 @@ bool scan_fwd_fusable(const ss_fwd_params* p, int pitch, int R)
            p->workspace_bytes >= ws_layout(p, (p->flags & SS_SAVE_FOR_BWD) != 0, pitch).total;
 }
 
-// Whether rows of delta, ddelta and the saved y may be that far apart: the kernels for any row length take it.
+// Whether rows of the caller's own tensors may be that far apart: the kernels that own_rows() names take it.
 static bool pitch_ok(const ss_fwd_params* p, int pitch)
 {
-    return pitch == p->seqlen || (pitch > p->seqlen && p->seqlen >= 8 && p->seqlen % 8 != 0 && stageable(p) && (size_t)pitch * 64 * sizeof(float) < ((size_t)1 << 31));
+    if (pitch == p->seqlen) return true;
+    return pitch > p->seqlen && p->seqlen >= 8 && p->seqlen % 8 != 0 && p->io_dtype == SS_BF16 && !(p->flags & SS_EXACT_ZOH_B) && stageable(p) &&
+           (size_t)pitch * 64 * sizeof(float) < ((size_t)1 << 31);
 }
 
 static int scan_fwd_impl(const ss_fwd_params* p, long bc_bstride, int pitch, const void* W_dt, int R, const void* rT, void* stream)

@@ -687,10 +687,12 @@ __global__ void __launch_bounds__(THREADS, 2) scan_bwd_dpp_kernel(const BwdArgs 
     const uint32_t esz = (uint32_t)sizeof(T);
     const int r_row = min(pr, rows_here - 1);
     const uint32_t r_off = (uint32_t)r_row * (uint32_t)L * esz;
-    const uint32_t r_off_bc = (uint32_t)min(s_n, N - 1) * (uint32_t)f.Lb * esz;
-    // ... u, delta, ysave, du and ddelta have rows of their own (FwdArgs::Li); i_off: what that adds to an offset of this thread's row
-    const long wg_first_i = RAG ? ((long)b * f.D + d0) * f.Li : wg_first;
-    const uint32_t i_off = RAG ? (uint32_t)pr * (uint32_t)(f.Li - L) * esz : 0u, r_off_i = (uint32_t)r_row * (uint32_t)f.Li * esz;
+    // ... u, delta, ysave, du and ddelta, and B, C, have rows of their own (FwdArgs::Li); i_off: what that adds to an offset of this thread's row
+    constexpr bool OWN = own_rows<T, RAG, ZOH>();
+    const int Li = OWN ? f.Li : L;
+    const uint32_t r_off_bc = (uint32_t)min(s_n, N - 1) * (uint32_t)(OWN ? f.Lb : L) * esz;
+    const long wg_first_i = OWN ? ((long)b * f.D + d0) * Li : wg_first;
+    const uint32_t i_off = OWN ? (uint32_t)pr * (uint32_t)(Li - L) * esz : 0u, r_off_i = (uint32_t)r_row * (uint32_t)Li * esz;
     const T* const ru_p = static_cast<const T*>(f.u) + wg_first_i;
     const T* const rd_p = static_cast<const T*>(f.delta) + wg_first_i;
     const T* const ro_p = static_cast<const T*>(a.dout) + wg_first;
@@ -699,7 +701,7 @@ __global__ void __launch_bounds__(THREADS, 2) scan_bwd_dpp_kernel(const BwdArgs 
     const T* const rbc_p = static_cast<const T*>(s_which ? f.Cm : f.Bm) + (long)b * f.bc_bstride;
 
     auto own_rsrc = [&](void* base) {
-        return RAG ? make_rsrc(static_cast<T*>(base) + wg_first_i, (uint32_t)rows_here * (uint32_t)f.Li * esz) : wg_rsrc(base, true);
+        return OWN ? make_rsrc(static_cast<T*>(base) + wg_first_i, (uint32_t)rows_here * (uint32_t)Li * esz) : wg_rsrc(base, true);
     };
     const rsrc_t bdu_ = own_rsrc(a.du), bdd_ = own_rsrc(a.ddelta);
 
@@ -1250,9 +1252,12 @@ __global__ void __launch_bounds__(THREADS, 4) adjoint_agg_dpp_kernel(const BwdAr
     const uint32_t esz = (uint32_t)sizeof(T);
     const int r_row = min(pr, rows_here - 1);
     const uint32_t r_off = (uint32_t)r_row * (uint32_t)L * esz;
-    const uint32_t r_off_c = (uint32_t)min(s_n, N - 1) * (uint32_t)f.Lb * esz;
-    const uint32_t r_off_i = (uint32_t)r_row * (uint32_t)f.Li * esz;   // delta has rows of its own (FwdArgs::Li)
-    const T* const rd_p = static_cast<const T*>(f.delta) + ((long)b * f.D + d0) * f.Li;
+    // delta and C have rows of their own (FwdArgs::Li)
+    constexpr bool OWN = own_rows<T, RAG, false>();
+    const int Li = OWN ? f.Li : L;
+    const uint32_t r_off_c = (uint32_t)min(s_n, N - 1) * (uint32_t)(OWN ? f.Lb : L) * esz;
+    const uint32_t r_off_i = (uint32_t)r_row * (uint32_t)Li * esz;
+    const T* const rd_p = static_cast<const T*>(f.delta) + ((long)b * f.D + d0) * Li;
     const T* const ro_p = static_cast<const T*>(a.dout) + wg_first;
     const T* const rz_p = has_z ? static_cast<const T*>(f.z) + wg_first : ro_p;
     const T* const rc_p = static_cast<const T*>(f.Cm) + (long)b * f.bc_bstride;

@@ -676,6 +676,11 @@ template <> struct bc_group<bf16_t> {
     __device__ __forceinline__ float get(int j) const { return (j & 1) ? bf16_hi(w[j >> 1]) : bf16_lo(w[j >> 1]); }
 };
 
+// Whether a kernel takes rows FwdArgs::Li and Lb apart: those the layer has for an odd number of 16-bit steps.  The kernels that the layer
+// does not launch so are built without (exact zero-order hold, bf16, us: 8 x 1536 x 2047 874 / 862, 16 x 768 x 333 211 / 207).
+template <typename T, bool RAG, bool ZOH>
+constexpr bool own_rows() { return RAG && !ZOH && sizeof(T) == 2; }
+
 // Slices of 8 and of 4 steps of a row for the kernels that take rows of any length (VEC: of whole slices): those from t, in one access where
 // the row holds a slice.  Element by element, each behind a branch, complex state 2 x 1536 x 2047 bf16 took 1056 us forward + backward, now 598
 // (2048 steps: 300), fixed B 4 x 1536 x 2047 970, now 590.  on: false reads as zeros.

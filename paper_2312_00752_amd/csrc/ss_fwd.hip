@@ -128,10 +128,12 @@ __global__ void __launch_bounds__(THREADS, PAT && AGG ? 4 : ((PAT && FUSED_KS <=
     const uint32_t esz = (uint32_t)sizeof(T);
     const int r_row = min(pr, rows_here - 1);
     const uint32_t r_off = (uint32_t)r_row * (uint32_t)L * esz;
-    const uint32_t r_off_bc = (uint32_t)min(s_n, N - 1) * (uint32_t)a.Lb * esz;
-    // ... u, delta and ysave have rows of their own (FwdArgs::Li)
-    const long wg_first_i = ((long)b * a.D + d0) * a.Li;
-    const uint32_t r_off_i = (uint32_t)r_row * (uint32_t)a.Li * esz, r_off_p = has_z ? r_off_i : r_off;
+    // ... u, delta, ysave and B, C have rows of their own (FwdArgs::Li)
+    constexpr bool OWN = own_rows<T, RAG, ZOH>();
+    const int Li = OWN ? a.Li : L;
+    const uint32_t r_off_bc = (uint32_t)min(s_n, N - 1) * (uint32_t)(OWN ? a.Lb : L) * esz;
+    const long wg_first_i = ((long)b * a.D + d0) * Li;
+    const uint32_t r_off_i = (uint32_t)r_row * (uint32_t)Li * esz, r_off_p = has_z ? r_off_i : r_off;
     const T* const ru_p = static_cast<const T*>(a.u) + wg_first_i;
     const T* const rd_p = static_cast<const T*>(a.delta) + wg_first_i;
     const T* const rz_p = has_z ? static_cast<const T*>(a.z) + wg_first : ru_p;

@@ -37,7 +37,7 @@ struct FwdArgs {
     int vec_ok;  // L % 8 == 0: every row starts 16-byte aligned and 8-step slices are whole or empty
     int dpp_ok;  // L >= 8 and 64 rows below 2^31 bytes: the kernels with B and C as quad-broadcast operands take the call
     // Elements between the rows of u, delta, ysave and (backward) of du and ddelta.  L, but where the caller owns all of them and rows of L
-    // elements would start off a 32-bit word (the layer, see own_pitch there); other than L in the kernels for any row length only.
+    // elements would start off a 32-bit word (the layer, see own_pitch there); other than L in the kernels own_rows() names only.
     int Li;
     int Lb;   // ... and between those of selective B and C
     const void *u, *delta, *z, *Bm, *Cm;
