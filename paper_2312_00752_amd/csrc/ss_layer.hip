@@ -368,10 +368,11 @@ ss_fwd_params scan_params(const ss_layer_params* p)
 // Elements between the rows of the layer's own tensors: u, [r;B;C], delta, their gradients and the saved y.  Every other row of an odd number of 16-bit elements
 // starts off a 32-bit word, where wide accesses are much slower; rows of these are a whole number of 16-byte pieces apart.
 // us, rows of L / this: training 8 x 1536 x 2047 951 / 835, 2 x 2560 x 4095 896 / 771, prefill 4 x 4096 x 1531 266 / 247 (the nt products of
-// the first 46 and 31 / 23 and 20, since a wave reads its fragments of [r;B;C] straight from memory).
+// the first 46 and 31 / 23 and 20, since a wave reads its fragments of [r;B;C] straight from memory).  From 32 steps on: prefill 64 x 1536 x 63
+// 114.9 / 112.9, x 33 104.9 / 106.0 (training 370 / 362), x 25 91.8 / 93.7 (334 / 340), x 9 89.5 / 91.2.
 int own_pitch(const ss_layer_params* p)
 {
-    return p->io_dtype == SS_BF16 && p->seqlen % 2 != 0 && p->seqlen >= 8 && p->seqlen < (1 << 22) ? (p->seqlen + 7) / 8 * 8 : p->seqlen;
+    return p->io_dtype == SS_BF16 && p->seqlen % 2 != 0 && p->seqlen >= 32 && p->seqlen < (1 << 22) ? (p->seqlen + 7) / 8 * 8 : p->seqlen;
 }
 
 // saved:   [P = [r;B;C] (B, Mx, L) io][workspace of the scan]

@@ -293,6 +293,15 @@ def test_layer_step_refuses_before_its_first_launch(dim, rank):
         assert step(**{f: off}) == B.SS_ERR_ALIGN, f
 
 
+@pytest.mark.parametrize("seqlen,pitch", [(9, 9), (31, 31), (33, 40), (34, 34), (2047, 2048)])
+def test_rows_of_the_layers_own_tensors(seqlen, pitch):
+    # [r;B;C] and the scan's saved y in rows of whole 16-byte pieces for an odd number of bf16 steps, from 32 on
+    nb, nd, nn, rank = 3, 64, 16, 8
+    up = lambda n: -(-n // 256) * 256
+    scan = B.ss_workspace_bytes(nb, nd, seqlen, nn, True, B.SS_BF16, True) - up(nb * nd * seqlen * 2) + up(nb * nd * pitch * 2)
+    assert B.ss_layer_saved_bytes(nb, nd, seqlen, nn, rank) == up(nb * (rank + 2 * nn) * pitch * 2) + up(scan)
+
+
 def test_time_invariant_bc_flags():
     # partial sums for the (D,N) gradients are added to the workspace, and the sequence is never split
     base = B.ss_workspace_bytes(1, 256, 1 << 16, 16, True, B.SS_F32, True)

@@ -201,9 +201,9 @@ def test_ranks_on_both_sides_of_the_projection_in_the_scan(shape):
 
 
 # bf16 at an odd number of steps: the layer's own tensors in rows of whole pieces; split, more than 16 states (the passes add
-# to them), the projection in the scan (rank 200), one row of a workgroup, the shortest row, convolution rows of two pieces and more
+# to them), the projection in the scan (rank 200), one row of a workgroup, the shortest such row (33 steps) and shorter ones, convolution rows of two pieces and more
 @pytest.mark.parametrize("shape", [(2, 9, 70, 16, 8), (1, 15, 1, 4, 1), (2, 333, 66, 16, 24), (1, 259, 80, 20, 9), (2, 101, 64, 40, 12), (3, 33, 130, 16, 200),
-                                   (1, 1025, 9, 16, 8), (2, 1537, 70, 12, 8)])
+                                   (1, 1025, 9, 16, 8), (2, 1537, 70, 12, 8), (2, 31, 70, 16, 8), (2, 33, 70, 16, 8)])
 def test_odd_lengths_in_bf16(shape):
     batch, seqlen, dim, dstate, rank = shape
     _check(make_layer_inputs(batch, seqlen, dim, dstate, "bf16", seed=seqlen + 3, rank=rank))
