@@ -8,6 +8,7 @@ has not been.
 import ctypes
 import math
 import os
+import warnings
 
 
 class _TorchOnFirstUse:
@@ -170,17 +171,27 @@ def lib():
 _native = None
 
 
+class _NoMarshal:
+    """In the place of a module that is not built: serves no call."""
+    def _none(*args):
+        return None
+
+    step = layer_step = scan_fwd = scan_bwd = layer_fwd = layer_bwd = staticmethod(_none)
+
+
 def _marshal():
     """The compiled marshalling of the calls that a step or a short sequence consists of (csrc/ss_marshal.cpp).  It serves plain
-    tensors; where it returns None the call goes through the code below it."""
+    tensors; where it returns None, or is not built, the call goes through the code below it."""
     global _native
     if _native is None:
         torch.Tensor   # its libraries are what the module is linked against
+        lib()          # a library that is missing is reported as such
         try:
             from . import _marshal as native
         except ImportError as e:
-            raise RuntimeError("%s cannot be loaded: build it with `python -m paper_2312_00752_amd.build`"
-                               % os.path.join(_PKG, "_marshal.so")) from e
+            warnings.warn("%s cannot be loaded (%s): calls are marshalled in Python, which takes a few microseconds more each; build it "
+                          "with `python -m paper_2312_00752_amd.build`" % (os.path.join(_PKG, "_marshal.so"), e), RuntimeWarning, stacklevel=3)
+            native = _NoMarshal
         _native = native
     return _native
 

@@ -1,5 +1,6 @@
-"""Build the C-ABI library ``libss_scan.so`` from ``csrc/`` with hipcc for gfx950, and ``_marshal.so``, through which
-the binding calls it, with the host compiler.
+"""Build the C-ABI library ``libss_scan.so`` from ``csrc/`` with hipcc for gfx950, and then ``_marshal.so``, through which
+the binding makes its hot calls, with the host compiler.  The library needs hipcc alone and is complete before the module is
+begun, which is left out, with a note, where torch, the Python headers or g++ are missing.
 
 The library is built in-tree (next to this file) so that it travels with the source
 tree; nothing is compiled at import time.  ``build_microbench`` builds the stand-alone
@@ -9,6 +10,7 @@ import glob
 import os
 import shutil
 import subprocess
+import sysconfig
 from concurrent.futures import ThreadPoolExecutor
 
 from . import isa_check
@@ -63,7 +65,7 @@ def _check_device_code(directory):
 
 
 def build_library(verbose=False, jobs=None):
-    """Compile every .hip source (in parallel) and link libss_scan.so; returns its path."""
+    """Compile every .hip source (in parallel) and link libss_scan.so, then _marshal.so; returns the library's path."""
     os.makedirs(BUILD_DIR, exist_ok=True)
     inc = ["-I", os.path.join(ROOT, "include"), "-I", CSRC]
     objs = []
@@ -74,33 +76,38 @@ def build_library(verbose=False, jobs=None):
         return obj
 
     with ThreadPoolExecutor(max_workers=jobs or min(8, os.cpu_count() or 1)) as pool:
-        marshal_obj = pool.submit(_compile_marshal, verbose)
         objs = list(pool.map(compile_one, sources()))
-        marshal_obj = marshal_obj.result()
     _check_device_code(BUILD_DIR)
     out = os.path.join(BUILD_DIR, "libss_scan.so")
     _run([_hipcc(), "--offload-arch=gfx950", "-shared", "-fPIC", "-o", out] + objs, BUILD_DIR, verbose)
     shutil.copy2(out, LIB)
-    _link_marshal(marshal_obj, verbose)
+    missing = build_marshal(verbose)
+    if missing:
+        print("%s is built; %s is not, for want of %s: the binding marshals all calls in Python" % (LIB, MARSHAL, missing))
     return LIB
 
 
-def _compile_marshal(verbose):
-    import sysconfig
-    from torch.utils import cpp_extension
-    obj = os.path.join(BUILD_DIR, "ss_marshal.o")
-    inc = [a for d in cpp_extension.include_paths() + [sysconfig.get_paths()["include"], os.path.join(ROOT, "include")] for a in ("-isystem", d)]
+def build_marshal(verbose=False):
+    """Compile _marshal.so against the built library.  Returns what is missing for it, or None."""
+    if os.path.exists(MARSHAL):
+        os.remove(MARSHAL)   # one that is left behind must not call another library than it was built for
+    try:
+        from torch.utils import cpp_extension
+    except ImportError:
+        return "torch"
+    python_inc = sysconfig.get_paths()["include"]
+    if not os.path.exists(os.path.join(python_inc, "Python.h")):
+        return "the Python headers"
+    if not shutil.which("g++"):
+        return "g++"
+    obj, out = os.path.join(BUILD_DIR, "ss_marshal.o"), os.path.join(BUILD_DIR, "_marshal.so")
+    inc = [a for d in cpp_extension.include_paths() + [python_inc, os.path.join(ROOT, "include")] for a in ("-isystem", d)]
     _run(["g++", "-O2", "-std=c++17", "-fPIC", "-c", "-o", obj, MARSHAL_SRC] + inc, BUILD_DIR, verbose)
-    return obj
-
-
-def _link_marshal(obj, verbose):
-    from torch.utils import cpp_extension
-    out = os.path.join(BUILD_DIR, "_marshal.so")
     dirs = [a for d in cpp_extension.library_paths() for a in ("-L", d)]
-    _run(["g++", "-shared", "-o", out, obj, "-L", PKG, "-lss_scan"] + dirs + ["-ltorch_python", "-ltorch_cpu", "-lc10", "-Wl,-rpath,$ORIGIN"],
-         BUILD_DIR, verbose)
+    _run(["g++", "-shared", "-o", out, obj, "-L", os.path.dirname(LIB), "-lss_scan"] + dirs +
+         ["-ltorch_python", "-ltorch_cpu", "-lc10", "-Wl,-rpath,$ORIGIN"], BUILD_DIR, verbose)
     shutil.copy2(out, MARSHAL)
+    return None
 
 
 def build_microbench(verbose=False):
