@@ -1522,18 +1522,21 @@ static bool allow_backward_lds_once(K kern, std::atomic<bool> (&done)[MAX_DEVICE
 constexpr unsigned COMPUTE_UNITS = 256;
 // Time-invariant B and / or C: a grid that gives each compute unit no more than one workgroup gains
 // nothing from a kernel that leaves room for two and pays for its 256 registers.  Variants for which that costs
-// something are built both ways; backward call, us, two per unit / one per unit:
-//   workgroups                                 256           512
-//   B, real, bf16, 2048 steps                  645 / 568     828 / 1131
-//   B, complex, f32, 2048 steps                773 / 670     1006 / 1359
-//   C, real, f32, 2048 steps                   596 / 601     1007 / 1009   (built for two only)
-// Off eight steps, 4 x 4096 x 103 (256 workgroups, unsplit), forward + backward: C, complex, f32 123 / 112; real ones within 3 %.
-template <typename T, bool VEC, int BCFIX, bool CPLX>
-constexpr bool ONE_WG_WINS = BCFIX == 1 || (BCFIX == 2 && (CPLX || !VEC)) || (BCFIX == 3 && !CPLX && !VEC && sizeof(T) == 2);
+// something are built both ways.  256 workgroups in one segment (4 x 4096), forward + backward, us, two per unit / one per unit:
+//   steps                 104           103          256          255          511
+//   B, real, bf16         62.0 / 59.6   100 / 91     115 / 112    203 / 187    split
+//   B, real, f32          63.1 / 62.4   92 / 83      114 / 113    180 / 160    377 / 310
+//   B, complex, f32       79.2 / 72.5   98 / 92      144 / 134    192 / 179    403 / 345
+//   C, complex, f32       73.9 / 73.0   121 / 109    139 / 136    245 / 217    split
+//   C, real, f32                        112 / 100                 226 / 198    split
+// 512 workgroups of 2048 steps, backward call: B, real, bf16 828 / 1131.  With both, and C of a real state on whole slices, there is no
+// difference (B and C, real, bf16, 103 steps 58.6 / 59.0): built for two only.
+template <bool VEC, int BCFIX, bool CPLX>
+constexpr bool ONE_WG_WINS = BCFIX == 1 || (BCFIX == 2 && (CPLX || !VEC));
 template <typename T, bool VEC, bool FULLN, bool ZOH, int BCFIX, bool CPLX = false, int WGS = ZOH ? 1 : 2>
 static int launch_scan_bwd_fixed(const BwdArgs& a, dim3 grid, hipStream_t stream)
 {
-    if constexpr (WGS == 2 && ONE_WG_WINS<T, VEC, BCFIX, CPLX>)
+    if constexpr (WGS == 2 && ONE_WG_WINS<VEC, BCFIX, CPLX>)
         if (grid.x * (unsigned)a.f.nseg <= COMPUTE_UNITS) return launch_scan_bwd_fixed<T, VEC, FULLN, ZOH, BCFIX, CPLX, 1>(a, grid, stream);
     auto kern = scan_bwd_kernel<T, VEC, FULLN, ZOH, BCFIX, CPLX, WGS>;
     static std::atomic<bool> lds_ok[MAX_DEVICES];   // this launcher is instantiated once per kernel
