@@ -24,16 +24,27 @@ def _refusal(p, nbytes):
     return B.lib().ss_scan_fwd(ctypes.byref(p), None)
 
 
-def _uncut_bytes(p):
+def _bytes(p, nseg):
+    """What a call cut into nseg segments needs (without a gate)."""
     up = lambda n: -(-n // 256) * 256
     rows, slots = p.batch * p.dim, p.dstate * (2 if p.flags & B.SS_COMPLEX_STATE else 1)
-    assert slots <= 16
     fixed = bool(p.flags & B.SS_B_FIXED) + bool(p.flags & B.SS_C_FIXED)
-    return up(-(-p.seqlen // B.SS_CHECKPOINT_STEPS) * rows * 64) + (1 + fixed) * up(rows * 64) + 2 * up(rows * 4)
+    state, scalar = up(nseg * rows * 64), up(nseg * rows * 4)
+    return up(-(-slots // 16) * -(-p.seqlen // B.SS_CHECKPOINT_STEPS) * rows * 64) + (1 + fixed) * state + 2 * scalar + (2 * state + scalar if nseg > 1 else 0)
 
 
 def _is_cut(p):
-    return {B.SS_ERR_ALIGN: False, B.SS_ERR_WORKSPACE: True}[_refusal(p, _uncut_bytes(p))]
+    return {B.SS_ERR_ALIGN: False, B.SS_ERR_WORKSPACE: True}[_refusal(p, _bytes(p, 1))]
+
+
+def segments(batch, seqlen, dim, io, flags, dstate=16):
+    """Into how many segments a call with a time-invariant B or C that keeps what its backward pass needs is cut."""
+    p = _params(batch, seqlen, dim, io, flags, dstate)
+    for n in range(1, max(2, seqlen // 64 + 2)):
+        if _refusal(p, _bytes(p, n)) == B.SS_ERR_ALIGN:
+            assert _refusal(p, _bytes(p, n) - 256) == B.SS_ERR_WORKSPACE
+            return n
+    raise AssertionError("no number of segments fits")
 
 
 BOTH, ZOH, CPLX = B.SS_B_FIXED | B.SS_C_FIXED, B.SS_EXACT_ZOH_B, B.SS_COMPLEX_STATE
