@@ -9,6 +9,7 @@ import sys
 import pytest
 
 from paper_2312_00752_amd import binding as B
+from tests.test_split_plan_cpu import segments
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 FAKE = 0x7F0000001000  # a non-null, 4096-byte aligned address that is never dereferenced
@@ -303,10 +304,13 @@ def test_rows_of_the_layers_own_tensors(seqlen, pitch):
 
 
 def test_time_invariant_bc_flags():
-    # partial sums for the (D,N) gradients are added to the workspace, and the sequence is never split
+    # partial sums for the (D,N) gradients are added to the workspace, for each segment; in place of the repacked copy of B and C
     base = B.ss_workspace_bytes(1, 256, 1 << 16, 16, True, B.SS_F32, True)
+    one = B.ss_workspace_bytes(1, 256, 1 << 16, 16, True, B.SS_F32, True, b_fixed=True)
     fixed = B.ss_workspace_bytes(1, 256, 1 << 16, 16, True, B.SS_F32, True, b_fixed=True, c_fixed=True)
-    assert fixed != base
+    nseg = segments(1, 1 << 16, 256, B.SS_F32, B.SS_B_FIXED | B.SS_C_FIXED)
+    assert nseg > 1 and one - base == nseg * 256 * 16 * 4 - 2 * 16 * (1 << 16) * 4 and fixed - one == nseg * 256 * 16 * 4
+    # a forward call that keeps nothing asks for no scratch
     assert B.ss_workspace_bytes(1, 256, 1 << 16, 16, False, B.SS_F32, True) > 0
     assert B.ss_workspace_bytes(1, 256, 1 << 16, 16, False, B.SS_F32, True, b_fixed=True) == 0
     small = B.ss_workspace_bytes(2, 64, 96, 16, True, B.SS_BF16, True)

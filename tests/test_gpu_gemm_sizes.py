@@ -135,6 +135,28 @@ def test_float32_products_of_any_size(nb, D, L, R, Mx, pad):
     assert ((C.cpu().double() - old - prod).abs() <= Mx * 2.0 ** -23 * size + 2.0 ** -24 * (old.abs() + size)).all()
 
 
+# float32: (batch, M, N, K) of more than 192 rows and at most 192 contraction indices in 128 tiles of 256 x 64 or more, where every wave has
+# 64 rows of its own (the last waves of a tile none or few), from the smallest N and K on; the last in 120 tiles, where four waves share them
+F32_MANY_ROWS = [(8, 1030, 259, 25), (4, 777, 511, 191), (8, 1930, 129, 96), (32, 193, 256, 192), (128, 193, 4, 4), (2, 1601, 639, 17), (4, 300, 1024, 40),
+                 (4, 300, 960, 40)]
+
+
+@pytest.mark.parametrize("pad", [0, 3])
+@pytest.mark.parametrize("nb,M,N,K", F32_MANY_ROWS)
+def test_float32_products_of_many_rows(nb, M, N, K, pad):
+    W = _inside(_rand(1, M, K, 21).float() * 1.2345678, pad)[0]
+    X = _inside(_rand(nb, K, N, 22).float() * 1.2345678, pad)
+    _check(W, X, torch.float32, pad=pad)
+    C = _inside(_rand(nb, M, N, 23).float(), pad)
+    old, prod, size = C.cpu().double(), W.cpu().double() @ X.cpu().double(), W.cpu().double().abs() @ X.cpu().double().abs()
+    B.ss_proj_gemm(W, X, C, accumulate=True)
+    torch.cuda.synchronize()
+    # as above; the old value's sum rounds once more
+    assert ((C.cpu().double() - old - prod).abs() <= K * 2.0 ** -23 * size + 2.0 ** -24 * (old.abs() + size)).all()
+    if pad:
+        assert torch.isnan(C.as_strided((nb, M, N + pad), C.stride())[:, :, N:]).all()
+
+
 def test_float32_infinities_stay_where_they_belong():
     """The last contraction index, whose step is padded, the last row and the last column hold infinities."""
     u, W = _rand(1, 71, 77, 13).float(), _rand(1, 19, 71, 14)[0].float()
