@@ -118,13 +118,16 @@ int ss_layer_step(const ss_layer_step_params *p, void *stream);
  * bf16 products of the layer's three shapes (few output rows with a long contraction over the rows
  * of B; many output rows with a contraction of at most 192; both operands contiguous along the
  * contraction index with a float32 result) run on kernels of their own, at any size from 8 up and
- * any pitch, fastest where sizes are multiples of 64 and pointers and strides of 16 bytes; everything
+ * any pitch, fastest where sizes are multiples of 64 and pointers and strides of 16 bytes.  float32 products
+ * of any shape with A contiguous along the contraction index and B along either axis run on one of their own
+ * from 4 contraction indices (and, with B contiguous along its columns, 4 columns) up.  Everything
  * else, and every call with SS_GEMM_GENERAL, runs on a general kernel.  `workspace` is optional device
  * memory (256-byte aligned) that the call may overwrite: with it, a product of few tiles (of the first
  * shape, with ss_proj_gemm_workspace_bytes(p) bytes, also one of fewer than 512 and K >= 4096) cuts its
- * contraction into up to eight parts, as many as it holds float32 shares of the result for, and adds
- * them in order with a second kernel; the
- * result may then differ from the unsplit one in the last bf16 digit.  Device pointers; C must not overlap A or B.  SS_OK, SS_ERR_NULL,
+ * contraction into up to eight parts, as many as it holds float32 shares of the result for (in float32
+ * too, while each keeps 256 indices and there are no more than 512 workgroups), and adds
+ * them in order with a second kernel; the result may then differ from the unsplit one in the rounding of
+ * float32 sums and so in the last bf16 digit.  Device pointers; C must not overlap A or B.  SS_OK, SS_ERR_NULL,
  * SS_ERR_SHAPE (negative size), SS_ERR_UNSUPPORTED (dtype, unknown flag, more than 65535 batch
  * entries or 64-row tiles) or SS_ERR_LAUNCH. */
 #define SS_GEMM_C_FLOAT    1u
@@ -144,8 +147,9 @@ typedef struct {
     size_t workspace_bytes;
 } ss_gemm_params;
 int ss_proj_gemm(const ss_gemm_params *p, void *stream);
-/* Bytes of workspace with which ss_proj_gemm may split the contraction of *p (reads M, N, batch;
- * 0 for a NULL or negative-size argument).  Smaller or absent workspaces are valid: no split. */
+/* Bytes of workspace with which ss_proj_gemm may split the contraction of *p in two (reads M, N, batch;
+ * 0 for a NULL or negative-size argument).  Smaller or absent workspaces are valid: no split.  Larger ones, up
+ * to four times as large, allow more parts (see above). */
 size_t ss_proj_gemm_workspace_bytes(const ss_gemm_params *p);
 
 #ifdef __cplusplus

@@ -986,8 +986,8 @@ __global__ void __launch_bounds__(256) step_multi_kernel(const StepArgs a)
 // from the float32 output P = [r; B; C] of the projection (the sum of STEP_NPARTS partial results,
 // rounded to the io type as the layer stores it) and delta_t = W_dt r_t + bias is formed here.  A workgroup
 // owns 64 channels and a tile of BT = 16 or 8 batch entries.  It stages the tile's rows of P in LDS;
-// four of its eight waves then form the 16 x 64 block of W_dt r_t on the matrix cores (one 16 x 16
-// tile per wave, rows past the tile shadowing its last one, W_dt rows straight from global memory)
+// four of its eight waves (in float32 all eight, two to a tile, every other contraction step each) then form the 16 x 64 block of
+// W_dt r_t on the matrix cores (16 x 16 tiles, rows past the tile shadowing its last one, W_dt rows straight from global memory)
 // and leave softplus(. + bias) in LDS, once per (b, d) instead of once per quarter; after that a
 // thread is (channel d, quarter q, half of the batch tile) as in step_kernel and walks its BT / 2
 // batch entries.  The 8-entry tile needs fewer registers (two workgroups per CU instead of one) and
@@ -1456,8 +1456,9 @@ static void launch_step_projected_t(const StepArgs& a, hipStream_t stream)
 {
     // One workgroup per CU is the fastest arrangement (the state streams while the projection's
     // dependent steps run), so: 8-entry batch tiles while they fit the chip's 256 CUs once, 16-entry
-    // tiles while those still do, and 8-entry tiles again beyond that, where two of them share a CU
-    // (measured at D = 2048, 4096, 5120 and batch 32 ... 256: the better tile by 5-15 % in every case).
+    // tiles while those still do, and 8-entry tiles again beyond that, where two of them share a CU.  A token, us, 16 / 8 entries in between:
+    // 64 x 4096 bf16 17.5 / 18.4, float32 20.6 / 21.7, 48 x 5120 17.4 / 17.5, 22.3 / 23.4, 128 x 2048 16.1 / 17.2, 18.0 / 19.2, but
+    // 128 x 1536 13.9 / 13.7 (float32 15.6 / 16.0), 256 x 768 13.5 / 13.3.
     const long groups = (a.D + 63) / 64;
     const long n16 = groups * ((a.B + SP_MFMA_ROWS - 1) / SP_MFMA_ROWS), n8 = groups * ((a.B + 7) / 8);
     const bool wide = n8 > 256 && n16 <= 256;

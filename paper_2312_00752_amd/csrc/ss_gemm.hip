@@ -229,9 +229,9 @@ int launch_generic(const GemmArgs& g, hipStream_t stream)
 
 // ---- float32 operands -------------------------------------------------------------------------------
 // C (M x N) = A B with A contiguous along the contraction index and B along either: the six products of the float32
-// layer.  Its floor is the float matrix rate (256 multiply-adds per clock and CU), so what matters is that every SIMD has a wave that
+// layer.  Its floor is the float matrix rate (128 multiply-adds per clock and CU), so what matters is that every SIMD has a wave that
 // issues MFMAs back to back: a wave owns 16 MT rows x 64 columns of the result, whose operands it loads straight into the
-// fragments' registers, PD slabs of 16 contraction indices ahead, without LDS or barriers.  A lane's 16-byte piece of an
+// fragments' registers, AHEAD (three, four for up to 32 rows) slabs of 16 contraction indices ahead, without LDS or barriers.  A lane's 16-byte piece of an
 // operand that is contiguous along the contraction index holds indices 4 g .. 4 g + 3 of the slab (g = lane / 16); the i-th
 // MFMA of a slab contracts over element i of the four groups, so with B contiguous along N the lane reads row 4 g + i, columns
 // 4 j .. 4 j + 3 (j = lane % 16), one for each of its four column tiles: rows of 256 bytes, and the lane's results are

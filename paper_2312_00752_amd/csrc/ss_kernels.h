@@ -74,7 +74,7 @@ struct BwdArgs {
     void *du, *ddelta, *dz;
     float *dB, *dC;             // (B,N,L), zeroed before the scan kernel, atomically accumulated;
                                 // (D,N), written by the reduction kernel, for a time-invariant B / C
-    float *dBf_part, *dCf_part; // [B][D][16] per-batch partial sums of a time-invariant B's / C's gradient
+    float *dBf_part, *dCf_part; // [nseg][B][D][16] partial sums of a time-invariant B's / C's gradient
     float *dA_part;             // [nseg][B][D][16] partial sums per segment and batch entry
     float *dD_part, *db_part;   // [nseg][B][D]
     float* seg_g;               // [nseg][B][D][16]: adjoint carry of a segment (local, then incoming)
@@ -167,7 +167,7 @@ struct GemmArgs {
     void* C; long ldc, c_batch;
     bool bf16, c_float, accumulate;
     bool general;   // take the general kernel even where a matrix-core kernel fits (for verification)
-    // optional device memory for float32 shares of the result (up to 4 * batch * M * N floats are used): lets a
+    // optional device memory for float32 shares of the result (up to 8 * batch * M * N floats are used): lets a
     // product with few output rows and few columns split its contraction across workgroups
     void* split_ws;
     size_t split_ws_bytes;

@@ -277,7 +277,7 @@ int launch_conv_xproj(const ss_layer_step_params* p, void* u, float* P, hipStrea
     return launch_conv_xproj_rows<T, 4>(p, u, P, st);
 }
 
-// r (the first R rows of each batch entry of P, (B, Mx, L), rows ld apart) transposed and zero-padded to
+// r (the first R rows of each batch entry of P, (B, Mx, L) in rows ld apart) transposed and zero-padded to
 // (B, Lp, Rp), for the delta projection inside the scan kernel (see FwdArgs::rT).  32 x 32 tiles
 // through LDS; block (32, 8), grid (Lp / 32, Rp / 32, B).
 __global__ void transpose_r_kernel(const ss::bf16_t* __restrict__ P, long bstride, int ld, ss::bf16_t* __restrict__ rT, int R, int L,
@@ -375,7 +375,7 @@ int own_pitch(const ss_layer_params* p)
     return p->io_dtype == SS_BF16 && p->seqlen % 2 != 0 && p->seqlen >= 32 && p->seqlen < (1 << 22) ? (p->seqlen + 7) / 8 * 8 : p->seqlen;
 }
 
-// saved:   [P = [r;B;C] (B, Mx, L) io][workspace of the scan]
+// saved:   [P = [r;B;C] (B, Mx, own_pitch) io][workspace of the scan]
 struct SavedLayout { size_t P_off, scan_off, scan_bytes, total; };
 SavedLayout saved_layout(const ss_layer_params* p)
 {
@@ -390,7 +390,7 @@ SavedLayout saved_layout(const ss_layer_params* p)
 }
 
 // scratch: forward  [u][delta][P and the scan's split scratch, used if nothing is saved][r transposed and padded, bf16]
-//          backward [u][delta][du][ddelta][dP (B,Mx,L) io][dB, dC (B,N,L) f32]
+//          backward [u][delta][du][ddelta][dP (B, Mx, own_pitch) io][dB, dC (B,N,L) f32]
 //                   [partials of dW_dt (B,D,R) f32][partials of dW_x (B,Mx,D) f32]
 //                   [W_dt transposed (R,D) io][W_x transposed (D,Mx) io]
 //          both     [float32 shares of a projection whose contraction is split across workgroups: two of (B,Mx,L), or up to
