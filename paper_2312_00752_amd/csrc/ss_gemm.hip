@@ -237,7 +237,7 @@ int launch_generic(const GemmArgs& g, hipStream_t stream)
 // 4 j .. 4 j + 3 (j = lane % 16), one for each of its four column tiles: rows of 256 bytes, and the lane's results are
 // four consecutive columns.
 // KW = 4: the workgroup's waves share a tile and deal out its slabs; their sums are added through LDS in the order of the
-// waves.  Long contractions, where tiles are few.  KW = 1: four tiles one below the other, for short contractions.
+// waves.  Long contractions, where tiles are few.  KW = 1: four tiles one below the other, for short contractions (see f32_form).
 // BK: B contiguous along the contraction index; out_t: the result is stored transposed (the operand with more rows is B then).
 // Through LDS, 64 x 64 per workgroup and one step ahead (gemm_generic_kernel), a launch had one wave per SIMD that
 // waited for LDS, barrier and memory in turn.  us per call, that kernel / this one: W_x u 2 x 4096 x 1024, R = 128 (18 at the peak
@@ -349,19 +349,31 @@ __global__ void __launch_bounds__(256) gemm_f32_kernel(const GemmArgs g, const i
             return;
         }
         const bool whole = n_at == n0 + 4 * j && n_at + 4 <= N;
+        f32x4_t x[4];
+#pragma unroll
+        for (int r = 0; r < 4; ++r) x[r] = f32x4_t{v[0][r], v[1][r], v[2][r], v[3][r]};
+        if (g.accumulate) {   // uniform; all requested before one is waited for, past the end the last row and column (not used)
+            f32x4_t old[4];
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const float* row = C + (long)min(m + r, M - 1) * ldc;
+                if (whole) old[r] = load_any<f32x4_t>(row + n_at, 0u);
+                else
+#pragma unroll
+                    for (int c = 0; c < 4; ++c) old[r][c] = row[min(n_at + c, N - 1)];
+            }
+#pragma unroll
+            for (int r = 0; r < 4; ++r) x[r] += old[r];
+        }
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
             if (m + r >= M) continue;
             float* row = C + (long)(m + r) * ldc + n_at;
-            f32x4_t x = {v[0][r], v[1][r], v[2][r], v[3][r]};
-            if (whole) {
-                if (g.accumulate) x += load_any<f32x4_t>(row, 0u);
-                store_any(row, 0u, x);
-            } else {
+            if (whole) store_any(row, 0u, x[r]);
+            else
 #pragma unroll
                 for (int c = 0; c < 4; ++c)
-                    if (n_at + c >= n0 + 4 * j && n_at + c < N) row[c] = g.accumulate ? x[c] + row[c] : x[c];
-            }
+                    if (n_at + c >= n0 + 4 * j && n_at + c < N) row[c] = x[r][c];
         }
     };
     if constexpr (KW == 1) {
@@ -402,9 +414,39 @@ __global__ void __launch_bounds__(256) gemm_f32_kernel(const GemmArgs g, const i
     }
 }
 
-// Fewer workgroups of four tiles leave half of the chip idle, and waves that share a tile are the faster (W_dt r, R = 80, 1 x 2560 x 300,
-// 50 of them: 12.6 against 8.6 us).
-constexpr long F32_ROWS_MIN_WGS = 128;
+// Row tiles of a wave that has them to itself (KW = 1): of one to five (two waves a SIMD), the number with the least rounds of 256
+// workgroups times what a slab of the tile loads and multiplies (the four pieces of B cost a row tile if they are rows, two along K).
+// us, 1 / 2 / 3 / 4 / 5: W_dt r 16 x 1536 x 64, K = 96 9.5 / 9.3 / 10.5 / 12.5 / 14.4, 1 x 4096 x 1024, K = 128 17.8 / 16.9 / 20.8 / 16.8 / 19.1,
+// 4 x 1536 x 1024, K = 128 23.7 / 22.5 / 21.5 / 25.1 / 29.4; dW_x 4 x 288 x 4096, K = 64 25.5 / 22.4 / 19.3 / 22.2 / 15.6.
+int f32_row_tiles(const GemmArgs& g, long strips, bool bk)
+{
+    int best = 1;
+    double least = 0.0;
+    for (int mt = 1; mt <= 5; ++mt) {
+        const long wgs = strips * g.batch * ((g.M + 64L * mt - 1) / (64L * mt));
+        const double rows = mt == 5 ? 5.8 : mt;   // its registers leave less to overlap: 4 x 1195 x 2799, K = 64 48.6 / 42.5 with four
+        const double cost = (wgs <= 512 ? (double)((wgs + 255) / 256) : (double)wgs / 256) * (rows + (bk ? 2 : 1));
+        if (mt == 1 || cost <= least) { least = cost; best = mt; }
+    }
+    return best;
+}
+// Which kernel, by measurement.  With B contiguous along N a wave has tiles of its own for up to 320 contraction indices if that gives 160
+// workgroups (W_dt r 1 x 1536 x 700, K = 160, 132 of them: 11.4, four waves to a tile 11.3).  With B along K four waves that share a tile have a slab each up to 64
+// indices, and only a long contraction pays for adding up their sums: own tiles up to 88 indices, of four and more row tiles up to 512.  us, own
+// tiles / shared / general kernel: dW_dt 16 x 4096 x 256, K = 64 40.8 / 79.6 / 41.7, 200 70 / 96 / 109, 512 142 / 173 / 211; 1 x 1536 x 96, K = 64
+// 7.3 / 8.1 / 7.6, 81 7.1 / 7.2 / 9.9, 96 9.5 / 8.1 / 8.9.  In between, results of few rows and many tiles are best left to the general
+// kernel where its steps are whole: dW_x 16 x 128 x 1536, K = 64 14.9 / 19.8 / 12.8, 96 20.0 / 20.0 / 15.1, 160 25.4 / 24.8 / 20.7.
+enum class F32Form { OWN, SHARED, GENERAL };
+F32Form f32_form(const GemmArgs& g, long strips, bool bk, int mt)
+{
+    if (!bk) {
+        const long wgs = strips * g.batch * ((g.M + 64L * mt - 1) / (64L * mt));
+        return g.K <= 48 || (g.K <= 320 && g.M > SMAX && wgs >= 160) ? F32Form::OWN : F32Form::SHARED;
+    }
+    const long tiles = strips * g.batch * ((g.M + 63) / 64);
+    if (g.M <= SMAX && tiles >= 512 && g.K <= 160 && g.K % 32 == 0) return F32Form::GENERAL;
+    return mt >= 4 ? (g.K <= 512 ? F32Form::OWN : F32Form::SHARED) : (g.K > 16 && g.K <= 88 ? F32Form::OWN : F32Form::SHARED);
+}
 // The float32 kernel for this product, if it is one of its forms; SS_ERR_UNSUPPORTED otherwise (nothing enqueued).
 int launch_f32(const GemmArgs& g0, hipStream_t stream)
 {
@@ -422,10 +464,22 @@ int launch_f32(const GemmArgs& g0, hipStream_t stream)
     const double limit = 4294967296.0;
     if (4.0 * ((double)g.M * g.a_m + g.K) >= limit || 4.0 * (bk ? (double)g.N * g.b_n + g.K : (double)g.K * g.b_k + g.N) >= limit) return SS_ERR_UNSUPPORTED;
     const long strips = (g.N + 63) / 64;
-    const long my1 = (g.M + 255) / 256;
-    if (!bk && g.K <= SMAX && g.M > SMAX && strips * my1 * g.batch >= F32_ROWS_MIN_WGS) {   // many rows, short contraction
-        if (my1 > 65535) return SS_ERR_UNSUPPORTED;
-        hipLaunchKernelGGL((gemm_f32_kernel<false, 4, 1>), dim3((unsigned)strips, (unsigned)my1, (unsigned)g.batch), dim3(256), 0, stream, g, 0);
+    const int own = f32_row_tiles(g, strips, bk);
+    const F32Form form = f32_form(g, strips, bk, own);
+    if (form == F32Form::GENERAL) return SS_ERR_UNSUPPORTED;
+    if (form == F32Form::OWN) {
+        const long rows = (g.M + 64L * own - 1) / (64L * own);
+        if (rows > 65535) return SS_ERR_UNSUPPORTED;
+        const dim3 grid((unsigned)strips, (unsigned)rows, (unsigned)g.batch);
+#define SS_LAUNCH_F32(MT)                                                                                                  \
+    case MT:                                                                                                               \
+        if (bk) hipLaunchKernelGGL((gemm_f32_kernel<true, MT, 1>), grid, dim3(256), 0, stream, g, out_t);                   \
+        else hipLaunchKernelGGL((gemm_f32_kernel<false, MT, 1>), grid, dim3(256), 0, stream, g, 0);                         \
+        break
+        switch (own) {
+            SS_LAUNCH_F32(1); SS_LAUNCH_F32(2); SS_LAUNCH_F32(3); SS_LAUNCH_F32(4); SS_LAUNCH_F32(5);
+        }
+#undef SS_LAUNCH_F32
         return hipGetLastError() == hipSuccess ? SS_OK : SS_ERR_LAUNCH;
     }
     const int tiles = (g.M + 79) / 80, mt = ((g.M + tiles - 1) / tiles + 15) / 16;   // row tiles of up to 80 (two waves per SIMD), of even height

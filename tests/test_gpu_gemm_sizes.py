@@ -135,26 +135,36 @@ def test_float32_products_of_any_size(nb, D, L, R, Mx, pad):
     assert ((C.cpu().double() - old - prod).abs() <= Mx * 2.0 ** -23 * size + 2.0 ** -24 * (old.abs() + size)).all()
 
 
-# float32: (batch, M, N, K) of more than 192 rows and at most 192 contraction indices in 128 tiles of 256 x 64 or more, where every wave has
-# 64 rows of its own (the last waves of a tile none or few), from the smallest N and K on; the last in 120 tiles, where four waves share them
-F32_MANY_ROWS = [(8, 1030, 259, 25), (4, 777, 511, 191), (8, 1930, 129, 96), (32, 193, 256, 192), (128, 193, 4, 4), (2, 1601, 639, 17), (4, 300, 1024, 40),
-                 (4, 300, 960, 40)]
+# float32: (batch, M, N, K) of contractions short enough that a wave has row tiles of its own: one to five of them (200 and 130 strips of
+# columns are a round of workgroups), the last waves with few rows or none, from the smallest N and K on, and lengths on both sides of the lines
+# at which four waves share a tile (48 and 320 indices, along K 16, 88 and 512, few rows along K in whole steps: the general kernel)
+F32_SHORT = [(8, 1030, 259, 25), (4, 777, 511, 191), (8, 1930, 129, 96), (32, 193, 256, 192), (128, 193, 4, 4), (2, 1601, 639, 17),
+             (200, 300, 64, 40), (200, 256, 61, 17), (200, 190, 64, 33), (130, 128, 63, 48), (130, 128, 62, 49), (3, 100, 70, 16), (3, 100, 70, 88),
+             (3, 100, 70, 89), (1, 70, 300, 12), (2, 300, 7, 30), (4, 700, 640, 320), (4, 700, 640, 321), (40, 260, 250, 19), (260, 300, 66, 8)]
 
 
 @pytest.mark.parametrize("pad", [0, 3])
-@pytest.mark.parametrize("nb,M,N,K", F32_MANY_ROWS)
-def test_float32_products_of_many_rows(nb, M, N, K, pad):
-    W = _inside(_rand(1, M, K, 21).float() * 1.2345678, pad)[0]
-    X = _inside(_rand(nb, K, N, 22).float() * 1.2345678, pad)
-    _check(W, X, torch.float32, pad=pad)
-    C = _inside(_rand(nb, M, N, 23).float(), pad)
-    old, prod, size = C.cpu().double(), W.cpu().double() @ X.cpu().double(), W.cpu().double().abs() @ X.cpu().double().abs()
-    B.ss_proj_gemm(W, X, C, accumulate=True)
-    torch.cuda.synchronize()
-    # as above; the old value's sum rounds once more
-    assert ((C.cpu().double() - old - prod).abs() <= K * 2.0 ** -23 * size + 2.0 ** -24 * (old.abs() + size)).all()
-    if pad:
-        assert torch.isnan(C.as_strided((nb, M, N + pad), C.stride())[:, :, N:]).all()
+@pytest.mark.parametrize("nb,M,N,K", F32_SHORT)
+def test_float32_products_of_short_contractions(nb, M, N, K, pad):
+    draw = lambda *a: _inside(_rand(*a).float() * 1.2345678, pad)
+    W, A, X, XT = draw(1, M, K, 21)[0], draw(nb, M, K, 24), draw(nb, K, N, 22), draw(nb, N, K, 25)
+    for a, x, trans_b in ((W, X, False), (A, XT, True), (XT, A, True)):
+        _check(a, x, torch.float32, trans_b=trans_b, pad=pad)
+        b = (x.transpose(1, 2) if trans_b else x).cpu().double()
+        C = _inside(_rand(nb, a.shape[-2], b.shape[-1], 23).float(), pad)
+        old, prod, size = C.cpu().double(), a.cpu().double() @ b, a.cpu().double().abs() @ b.abs()
+        B.ss_proj_gemm(a, x, C, trans_b=trans_b, accumulate=True)
+        torch.cuda.synchronize()
+        # as above; the old value's sum rounds once more
+        assert ((C.cpu().double() - old - prod).abs() <= K * 2.0 ** -23 * size + 2.0 ** -24 * (old.abs() + size)).all()
+        if pad:
+            assert torch.isnan(C.as_strided((nb, C.shape[1], C.shape[2] + pad), C.stride())[:, :, C.shape[2]:]).all()
+
+
+@pytest.mark.parametrize("K", [64, 160, 161, 512, 513])
+def test_float32_weight_gradients_on_both_sides_of_the_lines(K):
+    for nb, M, N in ((32, 128, 512), (16, 512, 200), (9, 300, 1030)):
+        _check(_rand(nb, M, K, 31).float() * 1.2345678, _rand(nb, N, K, 32).float(), torch.float32, trans_b=True)
 
 
 def test_float32_infinities_stay_where_they_belong():
