@@ -430,10 +430,10 @@ int f32_row_tiles(const GemmArgs& g, long strips, bool bk)
     }
     return best;
 }
-// Which kernel, by measurement.  With B contiguous along N a wave has tiles of its own for up to 320 contraction indices if that gives 160
-// workgroups (W_dt r 1 x 1536 x 700, K = 160, 132 of them: 11.4, four waves to a tile 11.3).  With B along K four waves that share a tile have a slab each up to 64
-// indices, and only a long contraction pays for adding up their sums: own tiles up to 88 indices, of four and more row tiles up to 512.  us, own
-// tiles / shared / general kernel: dW_dt 16 x 4096 x 256, K = 64 40.8 / 79.6 / 41.7, 200 70 / 96 / 109, 512 142 / 173 / 211; 1 x 1536 x 96, K = 64
+// Which kernel, by measurement.  With B contiguous along N a wave has tiles of its own for up to 48 contraction indices (1 x 200 x 4, K = 24 4.9 us,
+// four waves to a tile 7.2), and up to 320 if that gives 160 workgroups (1 x 1536 x 700, K = 160, 132 of them: 11.4 / 11.3).  With B along K four
+// waves that share a tile have a slab each up to 64 indices, and only a long contraction pays for adding up their sums: own tiles up to 88 indices
+// (but not a single slab of few row tiles, 1 x 1536 x 96, K = 16 6.5 / 5.1), of four and more row tiles up to 512.  us, own tiles / shared / general kernel: dW_dt 16 x 4096 x 256, K = 64 40.8 / 79.6 / 41.7, 200 70 / 96 / 109, 512 142 / 173 / 211; 1 x 1536 x 96, K = 64
 // 7.3 / 8.1 / 7.6, 81 7.1 / 7.2 / 9.9, 96 9.5 / 8.1 / 8.9.  In between, results of few rows and many tiles are best left to the general
 // kernel where its steps are whole: dW_x 16 x 128 x 1536, K = 64 14.9 / 19.8 / 12.8, 96 20.0 / 20.0 / 15.1, 160 25.4 / 24.8 / 20.7.
 enum class F32Form { OWN, SHARED, GENERAL };
