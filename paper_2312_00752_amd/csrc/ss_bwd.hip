@@ -227,7 +227,7 @@ __device__ __forceinline__ int lane_value(int lane)
 // Exact ZOH with a time-invariant B or C needs more registers than two workgroups per compute unit leave; it is
 // built for one.  (Exact ZOH with selective B and C runs on scan_bwd_dpp_kernel but for the shortest rows.)
 // WGS: workgroups per compute unit the kernel is built for (see ONE_WG_WINS for where both are built).
-template <typename T, bool VEC, bool FULLN, bool ZOH, int BCFIX = 0, bool CPLX = false, int WGS = ZOH ? 1 : 2>
+template <typename T, bool VEC, bool FULLN, bool ZOH, int BCFIX = 0, bool CPLX = false, int WGS = ZOH ? 1 : 2, bool SHORT = false>
 __global__ void __launch_bounds__(THREADS, WGS) scan_bwd_kernel(const BwdArgs a)
 {
     extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
@@ -314,12 +314,12 @@ __global__ void __launch_bounds__(THREADS, WGS) scan_bwd_kernel(const BwdArgs a)
         for (int s = 0; s < LG; ++s) {
             const int blk = grp * LG + s;
             const int t0 = blk * BT + pq * BSL;   // rows past D contribute nothing
-            ru[s] = load_slice4<T, VEC>(gu, t0, L, p_ok);
-            rd[s] = load_slice4<T, VEC>(gdl, t0, L, p_ok);
-            ro[s] = load_slice4<T, VEC>(gdo, t0, L, p_ok);
+            ru[s] = load_slice4<T, VEC, SHORT>(gu, t0, L, p_ok);
+            rd[s] = load_slice4<T, VEC, SHORT>(gdl, t0, L, p_ok);
+            ro[s] = load_slice4<T, VEC, SHORT>(gdo, t0, L, p_ok);
             if (has_z) {
-                rz[s] = load_slice4<T, VEC>(gz, t0, L, p_ok);
-                ry[s] = load_slice4<T, VEC>(gy, t0, L, p_ok);
+                rz[s] = load_slice4<T, VEC, SHORT>(gz, t0, L, p_ok);
+                ry[s] = load_slice4<T, VEC, SHORT>(gy, t0, L, p_ok);
             }
         }
     };
@@ -374,7 +374,7 @@ __global__ void __launch_bounds__(THREADS, WGS) scan_bwd_kernel(const BwdArgs a)
                     dz4[j] = o4[j] * y4[j] * s * fmaf(z4[j], 1.0f - s, 1.0f);  // dout y d[z sigmoid(z)]/dz
                     dy4[j] = o4[j] * z4[j] * s;
                 }
-                if (a.dz) store_slice<T, VEC, io4, BSL>(gdz + t0, dz4, nv);   // null for all but the first state group
+                if (a.dz) store_slice<T, VEC, SHORT, io4, BSL>(gdz + t0, dz4, nv);   // null for all but the first state group
             }
             *reinterpret_cast<float4*>(&sm.dt[pr][pq * BSL]) = make_float4(dt4[0], dt4[1], dt4[2], dt4[3]);
             *reinterpret_cast<float4*>(&sm.du[pr][pq * BSL]) = make_float4(du4[0], du4[1], du4[2], du4[3]);
@@ -398,7 +398,7 @@ __global__ void __launch_bounds__(THREADS, WGS) scan_bwd_kernel(const BwdArgs a)
                 bc_group<T> Bg[STATES_PER_LANE];
 #pragma unroll
                 for (int k = 0; k < STATES_PER_LANE; ++k)
-                    if (!BFIX) Bg[k] = load_bc<T, VEC, !FULLN>(gB[k], tc + g * GROUP_T, L, n_ok[k]);
+                    if (!BFIX) Bg[k] = load_bc<T, VEC, !FULLN, SHORT>(gB[k], tc + g * GROUP_T, L, n_ok[k]);
                 const int tl = g * GROUP_T;
                 const float4 dt4 = *reinterpret_cast<const float4*>(&sm.dt[lane][tl]);
                 const float4 du4 = *reinterpret_cast<const float4*>(&sm.du[lane][tl]);
@@ -450,8 +450,8 @@ __global__ void __launch_bounds__(THREADS, WGS) scan_bwd_kernel(const BwdArgs a)
             bc_group<T> Bg[STATES_PER_LANE], Cg[STATES_PER_LANE];
 #pragma unroll
             for (int k = 0; k < STATES_PER_LANE; ++k) {
-                if (!BFIX) Bg[k] = load_bc<T, VEC, !FULLN>(gB[k], tc + g * GROUP_T, L, n_ok[k]);
-                if (!CFIX) Cg[k] = load_bc<T, VEC, !FULLN>(gC[k], tc + g * GROUP_T, L, n_ok[k]);
+                if (!BFIX) Bg[k] = load_bc<T, VEC, !FULLN, SHORT>(gB[k], tc + g * GROUP_T, L, n_ok[k]);
+                if (!CFIX) Cg[k] = load_bc<T, VEC, !FULLN, SHORT>(gC[k], tc + g * GROUP_T, L, n_ok[k]);
             }
             const int tl = g * GROUP_T;
             const float4 dt4 = *reinterpret_cast<const float4*>(&sm.dt[lane][tl]);
@@ -561,13 +561,13 @@ __global__ void __launch_bounds__(THREADS, WGS) scan_bwd_kernel(const BwdArgs a)
             }
             if (a.acc) {  // states beyond the first 16: add to the earlier groups' du and ddelta
                 float pu[BSL], pl[BSL];
-                io4<T>::unpack(load_slice4<T, VEC>(gdu, t0, L, p_ok), pu);
-                io4<T>::unpack(load_slice4<T, VEC>(gdd, t0, L, p_ok), pl);
+                io4<T>::unpack(load_slice4<T, VEC, SHORT>(gdu, t0, L, p_ok), pu);
+                io4<T>::unpack(load_slice4<T, VEC, SHORT>(gdd, t0, L, p_ok), pl);
 #pragma unroll
                 for (int j = 0; j < BSL; ++j) { du4[j] += pu[j]; dl4[j] += pl[j]; }
             }
-            store_slice<T, VEC, io4, BSL>(gdu + t0, du4, nv);
-            store_slice<T, VEC, io4, BSL>(gdd + t0, dl4, nv);
+            store_slice<T, VEC, SHORT, io4, BSL>(gdu + t0, du4, nv);
+            store_slice<T, VEC, SHORT, io4, BSL>(gdd + t0, dl4, nv);
         }
         // the next phase A rewrites only this thread's own slices of dt/du/dy; the share
         // tiles are rewritten only after the next barrier
@@ -1133,9 +1133,9 @@ __global__ void __launch_bounds__(THREADS) adjoint_agg_kernel(const BwdArgs a)
     typename io8<T>::raw rd, rz, ro;
     auto issue_loads = [&](int c) {
         const int t0 = c * CHUNK_T + pq * SLICE;
-        rd = load_slice8<T, VEC>(gdl, t0, L, p_ok);
-        ro = load_slice8<T, VEC>(gdo, t0, L, p_ok);
-        if (has_z) rz = load_slice8<T, VEC>(gz, t0, L, p_ok);
+        rd = load_slice8<T, VEC, false>(gdl, t0, L, p_ok);
+        ro = load_slice8<T, VEC, false>(gdo, t0, L, p_ok);
+        if (has_z) rz = load_slice8<T, VEC, false>(gz, t0, L, p_ok);
     };
     issue_loads(c_end - 1);
     uint32_t touched = 0u;
@@ -1173,7 +1173,7 @@ __global__ void __launch_bounds__(THREADS) adjoint_agg_kernel(const BwdArgs a)
             bc_group<T> Cg[STATES_PER_LANE];
 #pragma unroll
             for (int k = 0; k < STATES_PER_LANE; ++k)
-                if (!CFIX) Cg[k] = load_bc<T, VEC, !FULLN>(gC[k], tc + g * GROUP_T, L, n_ok[k]);
+                if (!CFIX) Cg[k] = load_bc<T, VEC, !FULLN, false>(gC[k], tc + g * GROUP_T, L, n_ok[k]);
             auto Cval = [&](int k, int j) -> float { return CFIX ? Cf[k] : Cg[k].get(j); };
             const float4 dt4 = *reinterpret_cast<const float4*>(&s_dt[lane][g * GROUP_T]);
             const float4 dy4 = *reinterpret_cast<const float4*>(&s_dy[lane][g * GROUP_T]);
@@ -1519,6 +1519,19 @@ static bool allow_backward_lds_once(K kern, std::atomic<bool> (&done)[MAX_DEVICE
     return true;
 }
 
+// The main pass off the quad-broadcast kernel; rows that are not whole slices by elements if they are short (never split).
+template <typename T, bool VEC, bool FULLN, bool ZOH, int BCFIX, bool CPLX, int WGS, bool SHORT = false>
+static int launch_bwd_rows(const BwdArgs& a, dim3 grid, hipStream_t stream)
+{
+    if constexpr (!VEC && !SHORT)
+        if (short_rows<T>(a.f.L, BSL)) return launch_bwd_rows<T, VEC, FULLN, ZOH, BCFIX, CPLX, WGS, true>(a, grid, stream);
+    auto kern = scan_bwd_kernel<T, VEC, FULLN, ZOH, BCFIX, CPLX, WGS, SHORT>;
+    static std::atomic<bool> lds_ok[MAX_DEVICES];   // this launcher is instantiated once per kernel
+    if (!allow_backward_lds_once(reinterpret_cast<const void*>(kern), lds_ok, sizeof(BwdSmem))) return -1;
+    kern<<<dim3(grid.x, (unsigned)a.f.nseg), dim3(THREADS), sizeof(BwdSmem), stream>>>(a);
+    return hipGetLastError() == hipSuccess ? 0 : -1;
+}
+
 constexpr unsigned COMPUTE_UNITS = 256;
 // Time-invariant B and / or C: a grid that gives each compute unit no more than one workgroup gains
 // nothing from a kernel that leaves room for two and pays for its 256 registers.  Variants for which that costs
@@ -1538,9 +1551,6 @@ static int launch_scan_bwd_fixed(const BwdArgs& a, dim3 grid, hipStream_t stream
 {
     if constexpr (WGS == 2 && ONE_WG_WINS<VEC, BCFIX, CPLX>)
         if (grid.x * (unsigned)a.f.nseg <= COMPUTE_UNITS) return launch_scan_bwd_fixed<T, VEC, FULLN, ZOH, BCFIX, CPLX, 1>(a, grid, stream);
-    auto kern = scan_bwd_kernel<T, VEC, FULLN, ZOH, BCFIX, CPLX, WGS>;
-    static std::atomic<bool> lds_ok[MAX_DEVICES];   // this launcher is instantiated once per kernel
-    if (!allow_backward_lds_once(reinterpret_cast<const void*>(kern), lds_ok, sizeof(BwdSmem))) return -1;
     if (a.f.nseg > 1) {
         const dim3 agg((unsigned)grid.x, (unsigned)(a.f.nseg - 1)), block(THREADS);
         if constexpr (BCFIX & 2) adjoint_agg_kernel<T, VEC, FULLN, CPLX, true><<<agg, block, 0, stream>>>(a);
@@ -1551,24 +1561,19 @@ static int launch_scan_bwd_fixed(const BwdArgs& a, dim3 grid, hipStream_t stream
         const long n = (long)a.f.B * a.f.D * NPAD;
         carry_bwd_kernel<<<dim3((unsigned)((n + 255) / 256)), dim3(256), 0, stream>>>(a);
     }
-    kern<<<dim3(grid.x, (unsigned)a.f.nseg), dim3(THREADS), sizeof(BwdSmem), stream>>>(a);
-    return hipGetLastError() == hipSuccess ? 0 : -1;
+    return launch_bwd_rows<T, VEC, FULLN, ZOH, BCFIX, CPLX, WGS>(a, grid, stream);
 }
 
 // complex state with selective B and C: first-order B-bar only
 template <typename T, bool VEC, bool FULLN>
 static int launch_scan_bwd_complex(const BwdArgs& a, dim3 grid, hipStream_t stream)
 {
-    auto kern = scan_bwd_kernel<T, VEC, FULLN, false, 0, true>;
-    static std::atomic<bool> lds_ok[MAX_DEVICES];   // this launcher is instantiated once per kernel
-    if (!allow_backward_lds_once(reinterpret_cast<const void*>(kern), lds_ok, sizeof(BwdSmem))) return -1;
     if (a.f.nseg > 1) {
         adjoint_agg_kernel<T, VEC, FULLN, true><<<dim3(grid.x, (unsigned)(a.f.nseg - 1)), dim3(THREADS), 0, stream>>>(a);
         const long n = (long)a.f.B * a.f.D * NPAD;
         carry_bwd_kernel<<<dim3((unsigned)((n + 255) / 256)), dim3(256), 0, stream>>>(a);
     }
-    kern<<<dim3(grid.x, (unsigned)a.f.nseg), dim3(THREADS), sizeof(BwdSmem), stream>>>(a);
-    return hipGetLastError() == hipSuccess ? 0 : -1;
+    return launch_bwd_rows<T, VEC, FULLN, false, 0, true, 2>(a, grid, stream);
 }
 
 // the common case (scan_bwd_dpp_kernel), with the adjoint aggregates of a split sequence first
@@ -1605,11 +1610,7 @@ static int launch_bwd_scalar(const BwdArgs& a, dim3 grid, hipStream_t stream)
         const long n = (long)a.f.B * a.f.D * NPAD;
         carry_bwd_kernel<<<dim3((unsigned)((n + 255) / 256)), dim3(256), 0, stream>>>(a);
     }
-    auto kern = scan_bwd_kernel<T, false, false, ZOH>;
-    static std::atomic<bool> lds_ok[MAX_DEVICES];   // this launcher is instantiated once per kernel
-    if (!allow_backward_lds_once(reinterpret_cast<const void*>(kern), lds_ok, sizeof(BwdSmem))) return -1;
-    kern<<<dim3(grid.x, (unsigned)a.f.nseg), dim3(THREADS), sizeof(BwdSmem), stream>>>(a);
-    return hipGetLastError() == hipSuccess ? 0 : -1;
+    return launch_bwd_rows<T, false, false, ZOH, 0, false, ZOH ? 1 : 2>(a, grid, stream);
 }
 
 // complex state and time-invariant B and / or C

@@ -681,35 +681,41 @@ template <> struct bc_group<bf16_t> {
 template <typename T, bool RAG, bool ZOH>
 constexpr bool own_rows() { return RAG && !ZOH && sizeof(T) == 2; }
 
-// Slices of 8 and of 4 steps of a row for the kernels that take rows of any length (VEC: of whole slices): those from t, in one access where
-// the row holds a slice.  Element by element, each behind a branch, complex state 2 x 1536 x 2047 bf16 took 1056 us forward + backward, now 598
-// (2048 steps: 300), fixed B 4 x 1536 x 2047 970, now 590.  on: false reads as zeros.
-template <typename T, bool VEC, template <typename> class IO, int E>
+// Rows that the kernels off the quad-broadcast ones read element by element (SHORT): those that do not hold a slice (8 steps forward, 4 backward),
+// and float32 ones of little more, where there is too little to gain for what shifting the last slice into place costs.  Forward + backward, us, by
+// elements / slices: 64 x 768, fixed B, bf16 x 2 52.5 / 59.3, x 7 61.7 / 58.2 (4 in the backward pass), float32 x 9 51.1 / 54.8, x 15 54.2 / 57.5,
+// complex x 17 98.2 / 101.6, 8 x 4096 x 21 63.8 / 64.4.
+template <typename T>
+constexpr bool short_rows(int L, int slice) { return L < (sizeof(T) == 4 ? 20 : slice); }
+
+// Slices of 8 and of 4 steps of a row for the kernels that take rows of any length (VEC: of whole slices; SHORT: see above; otherwise of at least
+// E steps): those from t, in one access.  Element by element, each behind a branch, complex state 2 x 1536 x 2047 bf16 took 1056 us forward +
+// backward, now 598 (2048 steps: 300), fixed B 4 x 1536 x 2047 970, now 590.  on: false reads as zeros.
+template <typename T, bool VEC, bool SHORT, template <typename> class IO, int E>
 __device__ __forceinline__ typename IO<T>::raw load_slice(const T* __restrict__ row, int t, int L, bool on)
 {
     const int n = on ? min(max(L - t, 0), E) : 0;
-    if constexpr (VEC) {
-        return IO<T>::template load<true>(row + t, n);
+    if constexpr (VEC || SHORT) {
+        return IO<T>::template load<VEC>(row + t, n);
     } else {
-        if (L < E) return IO<T>::template load<false>(row + t, n);   // uniform
         const int tp = row_piece(t, E, L);
         typename IO<T>::raw r = IO<T>::load_elem(row + tp, 0u);
         if (n < E) IO<T>::drop(r, on ? t - tp : E);
         return r;
     }
 }
-template <typename T, bool VEC> __device__ __forceinline__ typename io8<T>::raw load_slice8(const T* row, int t, int L, bool on) { return load_slice<T, VEC, io8, 8>(row, t, L, on); }
-template <typename T, bool VEC> __device__ __forceinline__ typename io4<T>::raw load_slice4(const T* row, int t, int L, bool on) { return load_slice<T, VEC, io4, 4>(row, t, L, on); }
-template <typename T, bool VEC, template <typename> class IO, int E>
+template <typename T, bool VEC, bool SHORT> __device__ __forceinline__ typename io8<T>::raw load_slice8(const T* row, int t, int L, bool on) { return load_slice<T, VEC, SHORT, io8, 8>(row, t, L, on); }
+template <typename T, bool VEC, bool SHORT> __device__ __forceinline__ typename io4<T>::raw load_slice4(const T* row, int t, int L, bool on) { return load_slice<T, VEC, SHORT, io4, 4>(row, t, L, on); }
+template <typename T, bool VEC, bool SHORT, template <typename> class IO, int E>
 __device__ __forceinline__ void store_slice(T* p, const float (&v)[E], int n)   // the first n elements
 {
-    if constexpr (VEC) IO<T>::template store<true>(p, v, n);
+    if constexpr (VEC || SHORT) IO<T>::template store<VEC>(p, v, n);
     else IO<T>::store_elem(p, 0u, IO<T>::pack(v), n);
 }
 
 // p: start of the (b,n) row; t: first step of the group; L: row length.
 // MASKED: `state_ok` false (padding state) reads as zero.
-template <typename T, bool VEC, bool MASKED>
+template <typename T, bool VEC, bool MASKED, bool SHORT>
 __device__ __forceinline__ bc_group<T> load_bc(const T* __restrict__ p, int t, int L, bool state_ok)
 {
     bc_group<T> g;
@@ -731,7 +737,7 @@ __device__ __forceinline__ bc_group<T> load_bc(const T* __restrict__ p, int t, i
 #pragma unroll
             for (int i = 0; i < int(sizeof(g.w) / 4); ++i) g.w[i] = state_ok ? g.w[i] : 0u;
         }
-    } else if (sizeof(T) == 2 && L >= GROUP_T) {   // uniform; a row of any length: in one access, from inside the row, and shifted into place at its
+    } else if (sizeof(T) == 2 && !SHORT) {   // a row of any length: in one access, from inside the row, and shifted into place at its
         // end.  (Float elements are words, which the scalar path reads one by one: complex state 2 x 1536 x 2047 603 us, in one access 665.)
         const int tp = row_piece(t, GROUP_T, L), n = t - tp;
         const u32x2 v = load_any<u32x2>(p + tp, 0u);

@@ -61,7 +61,7 @@ typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));   // MFMA operand a
 // 309 + 139 -> 158 + 90 us (2048 steps: 137 + 86), backward 1632 + 385 -> 445 + 93 us (320 + 84); float32,
 // 4 x 1536 x 2047, all passes: 865 -> 512 us.
 template <typename T, bool VEC, bool FULLN, bool AGG, bool ZOH, int BCFIX = 0, bool CPLX = false, bool STAGED = false,
-          int FUSED_KS = 0, int SPL = STATES_PER_LANE, bool PAT = false, bool RAG = false>
+          int FUSED_KS = 0, int SPL = STATES_PER_LANE, bool PAT = false, bool RAG = false, bool SHORT = false>
 __global__ void __launch_bounds__(THREADS, PAT && AGG ? 4 : ((PAT && FUSED_KS <= 4) ? 2 : 1)) scan_fwd_kernel(const FwdArgs a)
 {
     static_assert(!PAT || (VEC && BCFIX == 0 && !CPLX && !STAGED), "PAT: vector path, real state, selective B and C");
@@ -254,9 +254,9 @@ __global__ void __launch_bounds__(THREADS, PAT && AGG ? 4 : ((PAT && FUSED_KS <=
                 rbc_[s] = io4<T>::load_buf(bbc, (ts < L && c < c_end) ? bc_row_off + (uint32_t)ts * (uint32_t)sizeof(T) : BUF_OFF);
             }
         } else {
-            ru_[s] = load_slice8<T, VEC>(gu, t0, L, true);
-            rd_[s] = load_slice8<T, VEC>(gdl, t0, L, true);
-            if (has_z) rz_[s] = load_slice8<T, VEC>(gz, t0, L, true);
+            ru_[s] = load_slice8<T, VEC, SHORT>(gu, t0, L, true);
+            rd_[s] = load_slice8<T, VEC, SHORT>(gdl, t0, L, true);
+            if (has_z) rz_[s] = load_slice8<T, VEC, SHORT>(gz, t0, L, true);
         }
     };
     // FUSED: delta_raw of a chunk from the fragments in registers: two 16 x 16 tiles per wave,
@@ -479,8 +479,8 @@ __global__ void __launch_bounds__(THREADS, PAT && AGG ? 4 : ((PAT && FUSED_KS <=
             } else {
 #pragma unroll
                 for (int k = 0; k < STATES_PER_LANE; ++k) {
-                    if (!BFIX) Bg[slot][k] = load_bc<T, VEC, !FULLN>(gB[k], tc + g * GROUP_T, L, n_ok[k]);
-                    if (!CFIX && !AGG) Cg[slot][k] = load_bc<T, VEC, !FULLN>(gC[k], tc + g * GROUP_T, L, n_ok[k]);
+                    if (!BFIX) Bg[slot][k] = load_bc<T, VEC, !FULLN, SHORT>(gB[k], tc + g * GROUP_T, L, n_ok[k]);
+                    if (!CFIX && !AGG) Cg[slot][k] = load_bc<T, VEC, !FULLN, SHORT>(gC[k], tc + g * GROUP_T, L, n_ok[k]);
                 }
             }
         };
@@ -627,7 +627,7 @@ __global__ void __launch_bounds__(THREADS, PAT && AGG ? 4 : ((PAT && FUSED_KS <=
                 }
             } else if (a.acc_y) {
                 const T* prev = (has_z ? static_cast<const T*>(a.ysave) : static_cast<const T*>(a.out)) + prow * L;
-                io8<T>::unpack(load_slice8<T, VEC>(prev, t0, L, p_ok), p8);
+                io8<T>::unpack(load_slice8<T, VEC, SHORT>(prev, t0, L, p_ok), p8);
 #pragma unroll
                 for (int j = 0; j < SLICE; ++j) y8[j] += p8[j];
             }
@@ -681,11 +681,11 @@ __global__ void __launch_bounds__(THREADS, PAT && AGG ? 4 : ((PAT && FUSED_KS <=
             } else {
                 if (has_z) {
                     if (a.ysave)  // y before the gate, for the backward pass's dz
-                        store_slice<T, VEC, io8, SLICE>(static_cast<T*>(a.ysave) + prow * L + t0, y8, nvs);
+                        store_slice<T, VEC, SHORT, io8, SLICE>(static_cast<T*>(a.ysave) + prow * L + t0, y8, nvs);
 #pragma unroll
                     for (int j = 0; j < SLICE; ++j) y8[j] *= z8[j] * sigmoid_fast(z8[j]);
                 }
-                store_slice<T, VEC, io8, SLICE>(gout + t0, y8, nvs);
+                store_slice<T, VEC, SHORT, io8, SLICE>(gout + t0, y8, nvs);
             }
         }
         // no barrier needed here: the next phase A writes s_dt/s_du, which every wave has
@@ -1264,6 +1264,19 @@ int launch_stage_bc(const FwdArgs& a, void* bcs, int io_dtype, hipStream_t strea
     return hipGetLastError() == hipSuccess ? 0 : -1;
 }
 
+// The main pass off the quad-broadcast kernels; rows that are not whole slices by elements if they are short (never split).
+template <typename T, bool VEC, bool FULLN, bool ZOH, int BCFIX, bool CPLX = false, bool STAGED = false>
+static void launch_fwd_rows(const FwdArgs& a, dim3 grid, hipStream_t stream)
+{
+    if constexpr (!VEC) {
+        if (short_rows<T>(a.L, SLICE)) {
+            scan_fwd_kernel<T, false, FULLN, false, ZOH, BCFIX, CPLX, STAGED, 0, STATES_PER_LANE, false, false, true><<<grid, dim3(THREADS), 0, stream>>>(a);
+            return;
+        }
+    }
+    scan_fwd_kernel<T, VEC, FULLN, false, ZOH, BCFIX, CPLX, STAGED><<<grid, dim3(THREADS), 0, stream>>>(a);
+}
+
 // The aggregate pass of a real state with time-invariant B and / or C.  It has no use for C: with a selective B it is the
 // common path's (or the scalar path's) and with a time-invariant one the kernel that reads neither along the sequence, each
 // given B in the place of C.
@@ -1290,7 +1303,7 @@ static void launch_fwd_fixed(const FwdArgs& a, hipStream_t stream)
 {
     const int groups = (a.D + ROWS - 1) / ROWS;
     if (a.nseg > 1) launch_agg_fixed<T, VEC, FULLN, ZOH, BCFIX>(a, stream);
-    scan_fwd_kernel<T, VEC, FULLN, false, ZOH, BCFIX><<<dim3((unsigned)(a.B * groups), (unsigned)a.nseg), dim3(THREADS), 0, stream>>>(a);
+    launch_fwd_rows<T, VEC, FULLN, ZOH, BCFIX>(a, dim3((unsigned)(a.B * groups), (unsigned)a.nseg), stream);
 }
 
 // complex state: first-order B-bar only; selective or time-invariant B / C
@@ -1304,7 +1317,7 @@ static void launch_fwd_complex(const FwdArgs& a, hipStream_t stream)
         const long n = (long)a.B * a.D * NPAD;
         carry_fwd_kernel<<<dim3((unsigned)((n + 255) / 256)), dim3(256), 0, stream>>>(a);
     }
-    scan_fwd_kernel<T, VEC, FULLN, false, false, BCFIX, true><<<dim3((unsigned)(a.B * groups), (unsigned)a.nseg), block, 0, stream>>>(a);
+    launch_fwd_rows<T, VEC, FULLN, false, BCFIX, true>(a, dim3((unsigned)(a.B * groups), (unsigned)a.nseg), stream);
 }
 
 // Real state, selective B and C, rows of at least 8 steps: B and C as quad-broadcast operands.
@@ -1355,8 +1368,8 @@ static void launch_fwd_scalar(const FwdArgs& a, hipStream_t stream)
         const long n = (long)a.B * a.D * NPAD;
         carry_fwd_kernel<<<dim3((unsigned)((n + 255) / 256)), dim3(256), 0, stream>>>(a);
     }
-    if (a.bcs) scan_fwd_kernel<T, false, false, false, ZOH, 0, false, true><<<main_grid, block, 0, stream>>>(a);
-    else scan_fwd_kernel<T, false, false, false, ZOH><<<main_grid, block, 0, stream>>>(a);
+    if (a.bcs) launch_fwd_rows<T, false, false, ZOH, 0, false, true>(a, main_grid, stream);
+    else launch_fwd_rows<T, false, false, ZOH, 0>(a, main_grid, stream);
 }
 
 // complex state and time-invariant B and / or C
