@@ -8,7 +8,7 @@ from tests import test_gpu_fixed_bc_grids as grids
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("seqlen", [1, 3, 4, 5, 7, 9, 15, 31, 33, 65])
+@pytest.mark.parametrize("seqlen", [1, 2, 3, 4, 5, 7, 9, 15, 19, 20, 21, 31, 33, 65])
 @pytest.mark.parametrize("io", ["f32", "bf16"])
 def test_every_remainder(io, seqlen):
     for bfix, cfix in gf.MODES:

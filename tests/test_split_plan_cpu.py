@@ -55,7 +55,7 @@ BOTH, ZOH, CPLX = B.SS_B_FIXED | B.SS_C_FIXED, B.SS_EXACT_ZOH_B, B.SS_COMPLEX_ST
 @pytest.mark.parametrize("batch,seqlen,dim,io,flags", [
     (4, 2048, 4096, B.SS_BF16, BOTH | ZOH), (4, 2048, 4096, B.SS_F32, B.SS_B_FIXED | ZOH), (4, 512, 4096, B.SS_BF16, B.SS_C_FIXED | ZOH),
     (4, 2048, 4096, B.SS_F32, BOTH), (3, 2048, 4096, B.SS_F32, BOTH), (4, 512, 4096, B.SS_F32, BOTH), (4, 256, 4096, B.SS_BF16, BOTH),
-    (4, 256, 4096, B.SS_BF16, B.SS_B_FIXED), (5, 2048, 4096, B.SS_BF16, BOTH), (6, 2048, 4096, B.SS_F32, B.SS_C_FIXED), (1, 96, 64, B.SS_F32, BOTH)])
+    (4, 256, 4096, B.SS_BF16, B.SS_B_FIXED), (5, 2048, 4096, B.SS_BF16, BOTH), (6, 2048, 4096, B.SS_F32, B.SS_C_FIXED), (1, 96, 64, B.SS_F32, BOTH), (1, 200, 4096, B.SS_F32, BOTH)])
 def test_stays_whole(batch, seqlen, dim, io, flags):
     assert not _is_cut(_params(batch, seqlen, dim, io, flags))
 
