@@ -108,7 +108,7 @@ bool fixed_split_pays(const ss_fwd_params* p, const SegPlan& s)
     const bool f32 = p->io_dtype != SS_BF16, cplx = p->flags & SS_COMPLEX_STATE, whole_slices = p->seqlen % 8 == 0;
     const long wgs = (long)p->batch * ((p->dim + 63) / 64);
     if (!zoh && ((wgs > 256 && wgs <= 512) || (both && p->seqlen < 256))) return false;   // 64 x 200 B and C, float32: 77.7 / 84.1
-    double pair = 1.3, launches = 30.0;
+    double pair = 1.3, launches = wgs <= 64 ? 28.0 : 30.0;   // 128 steps, C, bf16, whole / split: 1 x 4096 60.4 / 58.4, 2 x 4096 1 / 1.05
     if (zoh) {
         pair = both ? 1.35 : 1.25;
         launches = 0.0;
