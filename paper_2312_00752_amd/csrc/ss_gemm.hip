@@ -231,22 +231,25 @@ int launch_generic(const GemmArgs& g, hipStream_t stream)
 // C (M x N) = A B with A contiguous along the contraction index and B along either: the six products of the float32
 // layer.  Its floor is the float matrix rate (128 multiply-adds per clock and CU), so what matters is that every SIMD has a wave that
 // issues MFMAs back to back: a wave owns 16 MT rows x 64 columns of the result, whose operands it loads straight into the
-// fragments' registers, AHEAD (three, four for up to 32 rows) slabs of 16 contraction indices ahead, without LDS or barriers.  A lane's 16-byte piece of an
+// fragments' registers, AHEAD (two to four) slabs of 16 contraction indices ahead, without LDS or barriers.  A lane's 16-byte piece of an
 // operand that is contiguous along the contraction index holds indices 4 g .. 4 g + 3 of the slab (g = lane / 16); the i-th
 // MFMA of a slab contracts over element i of the four groups, so with B contiguous along N the lane reads row 4 g + i, columns
 // 4 j .. 4 j + 3 (j = lane % 16), one for each of its four column tiles: rows of 256 bytes, and the lane's results are
 // four consecutive columns.
 // KW = 4: the workgroup's waves share a tile and deal out its slabs; their sums are added through LDS in the order of the
-// waves.  Long contractions, where tiles are few.  KW = 1: four tiles one below the other, for short contractions (see f32_form).
+// waves.  Long contractions, where tiles are few.  KW = 1: four tiles one below the other, for short contractions (see f32_own_tiles).
+// CHAIN: one chain of multiply-adds through the contraction.  Otherwise every slab is summed by itself and then added, so that the error is
+// no larger than with the shorter chains of four waves: 4 x 4096 x 256 over 64 / 512 indices, relative to 64 bits, in one chain 1.44e-7 / 4.06e-7,
+// shared 0.84e-7 / 2.07e-7, by slabs 0.84e-7 / 1.29e-7.
 // BK: B contiguous along the contraction index; out_t: the result is stored transposed (the operand with more rows is B then).
 // Through LDS, 64 x 64 per workgroup and one step ahead (gemm_generic_kernel), a launch had one wave per SIMD that
 // waited for LDS, barrier and memory in turn.  us per call, that kernel / this one: W_x u 2 x 4096 x 1024, R = 128 (18 at the peak
 // rate) 114 / 35, 1 x 2560 x 300, R = 80 26.0 / 13.9; W_dt r 1 x 5120 x 3001, R = 160 83 / 64; dW_x 8 x 768 x 4096, R = 24 121 / 47; with
 // shorter chains the error against 64 bits is the same or smaller (W_x u, D = 5120: 1.3e-6 / 4.6e-7).
-template <bool BK, int MT, int KW>
-__global__ void __launch_bounds__(256) gemm_f32_kernel(const GemmArgs g, const int out_t)
+template <bool BK, int MT, int KW, bool CHAIN = KW == 4>
+__global__ void __launch_bounds__(256, KW == 1 ? 2 : 1) gemm_f32_kernel(const GemmArgs g, const int out_t)
 {
-    constexpr int AHEAD = MT <= 2 ? 4 : 3;
+    constexpr int AHEAD = MT <= 2 ? 4 : (KW == 1 && MT == 5 ? 2 : 3);   // two waves of five row tiles of their own fit a SIMD with two
     __shared__ f32x4_t red[KW == 4 ? 3 * 4 * 4 * 64 : 1];
     const int lane = threadIdx.x & 63, kg = lane >> 4, j = lane & 15;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -290,6 +293,7 @@ __global__ void __launch_bounds__(256) gemm_f32_kernel(const GemmArgs g, const i
 #pragma unroll
         for (int t = 0; t < MT; ++t) a[S][t] = load_any<u32x4>(A, a_row[t] + ka);
     };
+    f32x4_t wait[4] = {};   // without CHAIN: the last row tile's sum of the slab before
     auto multiply = [&](auto slot, int s) {
         constexpr int S = decltype(slot)::value;
         if (16 * (s + 1) > K) {   // uniform: the last slab, zeros past K in both operands
@@ -303,19 +307,37 @@ __global__ void __launch_bounds__(256) gemm_f32_kernel(const GemmArgs g, const i
 #pragma unroll
             for (int t = 0; t < MT; ++t) a[S][t] = piece_f::cut(a[S][t], k, K);
         }
+        auto mfma = [&](int t, int c, int i, f32x4_t sum) {
+            return __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(a[S][t][i]), __uint_as_float(BK ? b[S][c][i] : b[S][i][c]), sum, 0, 0, 0);
+        };
+        if constexpr (CHAIN) {
 #pragma unroll
-        for (int i = 0; i < 4; ++i)
+            for (int i = 0; i < 4; ++i)
 #pragma unroll
-            for (int t = 0; t < MT; ++t)
+                for (int t = 0; t < MT; ++t)
 #pragma unroll
-                for (int c = 0; c < 4; ++c)
-                    acc[t][c] = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(a[S][t][i]),
-                                                                     __uint_as_float(BK ? b[S][c][i] : b[S][i][c]), acc[t][c], 0, 0, 0);
+                    for (int c = 0; c < 4; ++c) acc[t][c] = mfma(t, c, i, acc[t][c]);
+        } else {
+            // a row tile's sum is added up between the instructions of the next one's (all sixteen behind their own: a sixth more time)
+#pragma unroll
+            for (int t = 0; t < MT; ++t) {
+                f32x4_t sum[4];
+#pragma unroll
+                for (int i = 0; i < 4; ++i)
+#pragma unroll
+                    for (int c = 0; c < 4; ++c) {
+                        sum[c] = mfma(t, c, i, i == 0 ? f32x4_t{0.f, 0.f, 0.f, 0.f} : sum[c]);
+                        acc[(t + MT - 1) % MT][c][i] += wait[c][i];
+                    }
+#pragma unroll
+                for (int c = 0; c < 4; ++c) wait[c] = sum[c];
+            }
+        }
     };
     if (s_begin < s_end) {   // uniform
         load(std::integral_constant<int, 0>{}, s_begin);
         load(std::integral_constant<int, 1>{}, s_begin + KW);
-        load(std::integral_constant<int, 2>{}, s_begin + 2 * KW);
+        if constexpr (AHEAD >= 3) load(std::integral_constant<int, 2>{}, s_begin + 2 * KW);
         if constexpr (AHEAD == 4) load(std::integral_constant<int, 3>{}, s_begin + 3 * KW);
         for (int s = s_begin; s < s_end; s += AHEAD * KW) {
             auto turn = [&](auto slot) {
@@ -325,7 +347,7 @@ __global__ void __launch_bounds__(256) gemm_f32_kernel(const GemmArgs g, const i
             };
             turn(std::integral_constant<int, 0>{});
             turn(std::integral_constant<int, 1>{});
-            turn(std::integral_constant<int, 2>{});
+            if constexpr (AHEAD >= 3) turn(std::integral_constant<int, 2>{});
             if constexpr (AHEAD == 4) turn(std::integral_constant<int, 3>{});
         }
     }
@@ -377,6 +399,10 @@ __global__ void __launch_bounds__(256) gemm_f32_kernel(const GemmArgs g, const i
         }
     };
     if constexpr (KW == 1) {
+        if constexpr (!CHAIN) {
+#pragma unroll
+            for (int c = 0; c < 4; ++c) acc[MT - 1][c] += wait[c];
+        }
 #pragma unroll
         for (int t = 0; t < MT; ++t) store(acc[t], m0 + 16 * t);
     } else {
@@ -416,36 +442,28 @@ __global__ void __launch_bounds__(256) gemm_f32_kernel(const GemmArgs g, const i
 
 // Row tiles of a wave that has them to itself (KW = 1): of one to five (two waves a SIMD), the number with the least rounds of 256
 // workgroups times what a slab of the tile loads and multiplies (the four pieces of B cost a row tile if they are rows, two along K).
-// us, 1 / 2 / 3 / 4 / 5: W_dt r 16 x 1536 x 64, K = 96 9.5 / 9.3 / 10.5 / 12.5 / 14.4, 1 x 4096 x 1024, K = 128 17.8 / 16.9 / 20.8 / 16.8 / 19.1,
-// 4 x 1536 x 1024, K = 128 23.7 / 22.5 / 21.5 / 25.1 / 29.4; dW_x 4 x 288 x 4096, K = 64 25.5 / 22.4 / 19.3 / 22.2 / 15.6.
+// us, 1 / 2 / 3 / 4 / 5: W_dt r 16 x 1536 x 64, K = 96 9.5 / 9.6 / 11.1 / 13.2 / 15.0, 16 x 4096 x 64, K = 96 16.6 / 15.3 / 17.6 / 14.5 / 18.1,
+// 16 x 1536 x 1024, K = 96 69 / 64 / 55.1 / 55.8 / 56.2; dW_x 4 x 288 x 4096, K = 64 24.7 / 20.3 / 19.0 / 21.4 / 14.0.
 int f32_row_tiles(const GemmArgs& g, long strips, bool bk)
 {
     int best = 1;
     double least = 0.0;
     for (int mt = 1; mt <= 5; ++mt) {
         const long wgs = strips * g.batch * ((g.M + 64L * mt - 1) / (64L * mt));
-        const double rows = mt == 5 ? 5.8 : mt;   // its registers leave less to overlap: 4 x 1195 x 2799, K = 64 48.6 / 42.5 with four
-        const double cost = (wgs <= 512 ? (double)((wgs + 255) / 256) : (double)wgs / 256) * (rows + (bk ? 2 : 1));
+        const double cost = (wgs <= 512 ? (double)((wgs + 255) / 256) : (double)wgs / 256) * (mt + (bk ? 2 : 1));
         if (mt == 1 || cost <= least) { least = cost; best = mt; }
     }
     return best;
 }
-// Which kernel, by measurement.  With B contiguous along N a wave has tiles of its own for up to 48 contraction indices (1 x 200 x 4, K = 24 4.9 us,
-// four waves to a tile 7.2), and up to 320 if that gives 160 workgroups (1 x 1536 x 700, K = 160, 132 of them: 11.4 / 11.3).  With B along K four
-// waves that share a tile have a slab each up to 64 indices, and only a long contraction pays for adding up their sums: own tiles up to 88 indices
-// (but not a single slab of few row tiles, 1 x 1536 x 96, K = 16 6.5 / 5.1), of four and more row tiles up to 512.  us, own tiles / shared / general kernel: dW_dt 16 x 4096 x 256, K = 64 40.8 / 79.6 / 41.7, 200 70 / 96 / 109, 512 142 / 173 / 211; 1 x 1536 x 96, K = 64
-// 7.3 / 8.1 / 7.6, 81 7.1 / 7.2 / 9.9, 96 9.5 / 8.1 / 8.9.  In between, results of few rows and many tiles are best left to the general
-// kernel where its steps are whole: dW_x 16 x 128 x 1536, K = 64 14.9 / 19.8 / 12.8, 96 20.0 / 20.0 / 15.1, 160 25.4 / 24.8 / 20.7.
-enum class F32Form { OWN, SHARED, GENERAL };
-F32Form f32_form(const GemmArgs& g, long strips, bool bk, int mt)
+// Whether a wave has row tiles of its own, by measurement, us, own / shared by four waves.  With B contiguous along N for up to 48 contraction
+// indices (1 x 200 x 4, K = 24 4.9 / 7.2), and up to 320 if that gives 160 workgroups (1 x 1536 x 700, K = 192, 132 of them: 12.9 / 11.5).  With B
+// along K four waves that share a tile have a slab each up to 64 indices, and only a long contraction pays for adding up their sums: own tiles up to
+// 88 indices (but not a single slab of few row tiles, 1 x 1536 x 96, K = 16 6.5 / 5.6), of four and more row tiles up to 512.  dW_dt 16 x 4096 x 256,
+// K = 64 41.0 / 79.9, 200 73.8 / 95.9, 512 148 / 174; 1 x 1536 x 96, K = 64 7.3 / 8.1, 96 9.4 / 8.1.
+bool f32_own_tiles(const GemmArgs& g, long strips, bool bk, int mt)
 {
-    if (!bk) {
-        const long wgs = strips * g.batch * ((g.M + 64L * mt - 1) / (64L * mt));
-        return g.K <= 48 || (g.K <= 320 && g.M > SMAX && wgs >= 160) ? F32Form::OWN : F32Form::SHARED;
-    }
-    const long tiles = strips * g.batch * ((g.M + 63) / 64);
-    if (g.M <= SMAX && tiles >= 512 && g.K <= 160 && g.K % 32 == 0) return F32Form::GENERAL;
-    return mt >= 4 ? (g.K <= 512 ? F32Form::OWN : F32Form::SHARED) : (g.K > 16 && g.K <= 88 ? F32Form::OWN : F32Form::SHARED);
+    if (bk) return mt >= 4 ? g.K <= 512 : g.K > 16 && g.K <= 88;
+    return g.K <= 48 || (g.K <= 320 && g.M > SMAX && strips * g.batch * ((g.M + 64L * mt - 1) / (64L * mt)) >= 160);
 }
 // The float32 kernel for this product, if it is one of its forms; SS_ERR_UNSUPPORTED otherwise (nothing enqueued).
 int launch_f32(const GemmArgs& g0, hipStream_t stream)
@@ -465,15 +483,16 @@ int launch_f32(const GemmArgs& g0, hipStream_t stream)
     if (4.0 * ((double)g.M * g.a_m + g.K) >= limit || 4.0 * (bk ? (double)g.N * g.b_n + g.K : (double)g.K * g.b_k + g.N) >= limit) return SS_ERR_UNSUPPORTED;
     const long strips = (g.N + 63) / 64;
     const int own = f32_row_tiles(g, strips, bk);
-    const F32Form form = f32_form(g, strips, bk, own);
-    if (form == F32Form::GENERAL) return SS_ERR_UNSUPPORTED;
-    if (form == F32Form::OWN) {
+    if (f32_own_tiles(g, strips, bk, own)) {
         const long rows = (g.M + 64L * own - 1) / (64L * own);
         if (rows > 65535) return SS_ERR_UNSUPPORTED;
         const dim3 grid((unsigned)strips, (unsigned)rows, (unsigned)g.batch);
+        // many tiles of many rows over up to 192 indices in one chain, which takes 6 to 8 % less (16 x 4096 x 64, K = 192 19.3 / 21.2)
+        const bool chain = !bk && g.K <= SMAX && g.M > SMAX && strips * g.batch * ((g.M + 255) / 256) >= 128;
 #define SS_LAUNCH_F32(MT)                                                                                                  \
     case MT:                                                                                                               \
         if (bk) hipLaunchKernelGGL((gemm_f32_kernel<true, MT, 1>), grid, dim3(256), 0, stream, g, out_t);                   \
+        else if (chain) hipLaunchKernelGGL((gemm_f32_kernel<false, MT, 1, true>), grid, dim3(256), 0, stream, g, 0);        \
         else hipLaunchKernelGGL((gemm_f32_kernel<false, MT, 1>), grid, dim3(256), 0, stream, g, 0);                         \
         break
         switch (own) {

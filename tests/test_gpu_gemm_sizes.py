@@ -137,7 +137,7 @@ def test_float32_products_of_any_size(nb, D, L, R, Mx, pad):
 
 # float32: (batch, M, N, K) of contractions short enough that a wave has row tiles of its own: one to five of them (200 and 130 strips of
 # columns are a round of workgroups), the last waves with few rows or none, from the smallest N and K on, and lengths on both sides of the lines
-# at which four waves share a tile (48 and 320 indices, along K 16, 88 and 512, few rows along K in whole steps: the general kernel)
+# at which four waves share a tile (48 and 320 indices, along K 16, 88 and 512)
 F32_SHORT = [(8, 1030, 259, 25), (4, 777, 511, 191), (8, 1930, 129, 96), (32, 193, 256, 192), (128, 193, 4, 4), (2, 1601, 639, 17),
              (200, 300, 64, 40), (200, 256, 61, 17), (200, 190, 64, 33), (130, 128, 63, 48), (130, 128, 62, 49), (3, 100, 70, 16), (3, 100, 70, 88),
              (3, 100, 70, 89), (1, 70, 300, 12), (2, 300, 7, 30), (4, 700, 640, 320), (4, 700, 640, 321), (40, 260, 250, 19), (260, 300, 66, 8)]
@@ -165,6 +165,18 @@ def test_float32_products_of_short_contractions(nb, M, N, K, pad):
 def test_float32_weight_gradients_on_both_sides_of_the_lines(K):
     for nb, M, N in ((32, 128, 512), (16, 512, 200), (9, 300, 1030)):
         _check(_rand(nb, M, K, 31).float() * 1.2345678, _rand(nb, N, K, 32).float(), torch.float32, trans_b=True)
+
+
+@pytest.mark.parametrize("K,shared", [(64, 0.842e-7), (200, 1.345e-7), (512, 2.072e-7)])
+def test_float32_row_tiles_of_a_wave_round_no_more_than_shared_ones(K, shared):
+    """Errors against 64 bits, over the whole result.  `shared`: measured where four waves share a tile, whose chains are a quarter of the
+    contraction; one chain through it has 1.44e-7, 2.54e-7 and 4.06e-7.  3 % for the draw."""
+    for nb, M, N in ((4, 4096, 256), (4, 288, 4096), (1, 1536, 96)):
+        A, X = _rand(nb, M, K, 61).float() * 1.2345678, _rand(nb, N, K, 62).float() * 1.1234567
+        C = torch.empty((nb, M, N), dtype=torch.float32, device=DEV)
+        B.ss_proj_gemm(A, X, C, trans_b=True)
+        ref = torch.matmul(A.double(), X.double().transpose(1, 2).contiguous())
+        assert (C.double() - ref).norm() <= 1.03 * shared * ref.norm()
 
 
 def test_float32_infinities_stay_where_they_belong():
