@@ -249,7 +249,7 @@ int launch_generic(const GemmArgs& g, hipStream_t stream)
 template <bool BK, int MT, int KW, bool CHAIN = KW == 4>
 __global__ void __launch_bounds__(256, KW == 1 ? 2 : 1) gemm_f32_kernel(const GemmArgs g, const int out_t)
 {
-    constexpr int AHEAD = MT <= 2 ? 4 : (KW == 1 && MT == 5 ? 2 : 3);   // two waves of five row tiles of their own fit a SIMD with two
+    constexpr int AHEAD = MT <= 2 ? 4 : (KW == 1 && MT == 5 ? 2 : 3);   // with two, two waves of five row tiles of their own fit a SIMD (up to 20 bytes a lane wait in scratch, outside the loop)
     __shared__ f32x4_t red[KW == 4 ? 3 * 4 * 4 * 64 : 1];
     const int lane = threadIdx.x & 63, kg = lane >> 4, j = lane & 15;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
