@@ -622,7 +622,12 @@ struct BwdSmemDpp {
     float psb[NWAVES][ROWS][BPAD];
     float bcp[2][BT / GROUP_T][NPAD][GROUP_T];   // B (0) and C (1) of the block
 };
-
+// What an odd block leaves of du, ddelta and dz, each thread its own 16 bytes, in the kernels that have no registers for it
+struct BwdSmemDppKept : BwdSmemDpp {
+    float4 kept[3][THREADS];
+};
+template <typename T, bool ZOH, bool RAG> constexpr bool kept_in_lds() { return sizeof(T) == 4 && (ZOH || RAG); }
+template <typename T, bool ZOH, bool RAG> using bwd_smem_dpp = typename std::conditional<kept_in_lds<T, ZOH, RAG>(), BwdSmemDppKept, BwdSmemDpp>::type;
 
 // SPL: slots per lane the state phases are built for (see scan_fwd_kernel).
 // ZOH: the exact zero-order-hold B-bar of Eq. 4, b = phi B u with phi = (abar - 1)/A.  The LDS tile that
@@ -640,7 +645,7 @@ template <typename T, int SPL, bool ZOH = false, bool RAG = false>
 __global__ void __launch_bounds__(THREADS, 2) scan_bwd_dpp_kernel(const BwdArgs a)
 {
     extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
-    BwdSmemDpp& sm = *reinterpret_cast<BwdSmemDpp*>(smem_raw);
+    bwd_smem_dpp<T, ZOH, RAG>& sm = *reinterpret_cast<bwd_smem_dpp<T, ZOH, RAG>*>(smem_raw);
 
     const FwdArgs& f = a.f;
     const int tid = threadIdx.x;
@@ -777,26 +782,31 @@ __global__ void __launch_bounds__(THREADS, 2) scan_bwd_dpp_kernel(const BwdArgs 
             else rbc[s] = buf_load8(bbc_, boff);
         }
     };
-    // Stores likewise: with bf16 a block is 32 bytes of a row, so the results of an odd block wait in
-    // registers for the even block below it (segments start at even blocks) and the two pieces of
-    // the 64-byte neighbourhood are written back to back.
+    // Stores likewise: a block is 32 bytes of a bf16 row, 64 of a float one, so the results of an odd block wait for the even block below
+    // it (segments start at even blocks) and the two pieces of the 64 or 128 bytes are written back to back, from registers or
+    // (kept_in_lds) LDS.  float32, forward + backward, us, the pairs alone: 8 x 4096 x 2048 1075 -> 1012, with 4 states
+    // 1078 -> 926, 1 x 256 x 2^20 7830 -> 7480, 2 x 5120 x 16383 4758 -> 4427 (in registers 4485).
     typename io4<T>::packed keep_du{}, keep_dl{}, keep_dz{};
     uint32_t keep_off = BUF_OFF;
     // A block's results at byte offset off (of the thread's slice; BUF_OFF: not stored), an odd block's with the even block's
     // below it.  TAIL: the nv leading elements only, at once.
     // more: added to the offsets (an offset that is off stays off: resources end below 2^31).
     auto store_block = [&](rsrc_t rs, void* base, uint32_t off, uint32_t more, int nv, typename io4<T>::packed now,
-                           typename io4<T>::packed& keep, bool odd, auto tail_tag) {
+                           typename io4<T>::packed& keep, auto which_tag, bool odd, auto tail_tag) {
         if constexpr (decltype(tail_tag)::value) {
             if (base && nv > 0) io4<T>::store_elem(static_cast<T*>(base), off + more, now, nv);
             return;
         }
-        if constexpr (LG == 2) {
+        if constexpr (kept_in_lds<T, ZOH, RAG>()) {
+            u32x4* const at = reinterpret_cast<u32x4*>(&sm.kept[decltype(which_tag)::value][tid]);
+            const u32x4 x = *at;
+            io4<T>::store_packed(rs, (odd ? BUF_OFF : keep_off) + more, make_uint4(x[0], x[1], x[2], x[3]));
+            io4<T>::store_packed(rs, (odd ? BUF_OFF : off) + more, now);
+            *at = u32x4{now.x, now.y, now.z, now.w};
+        } else {
             io4<T>::store_packed(rs, (odd ? BUF_OFF : keep_off) + more, keep);   // keep_off: switched off when nothing waits
             io4<T>::store_packed(rs, (odd ? BUF_OFF : off) + more, now);
             keep = now;
-        } else {
-            io4<T>::store_packed(rs, off + more, now);
         }
     };
     // The state entering a block, left by the forward pass: requested a block ahead.
@@ -816,7 +826,7 @@ __global__ void __launch_bounds__(THREADS, 2) scan_bwd_dpp_kernel(const BwdArgs 
     // 8950 -> 8670, exact zero-order hold 8 x 1536 x 2048 bf16 843 -> 826, 8 x 4096 x 2048 bf16 919 -> 908.  (The loop unrolled over
     // the two slots instead: 940, its 24 KB of instructions are fetched too slowly.)
     auto do_block = [&](const int blk, auto tail_tag) {
-        const bool odd = LG == 2 && (blk & 1);   // uniform; the slot of its inputs
+        const bool odd = blk & 1, second = LG == 2 && odd;   // uniform; second: the slot of its inputs
         constexpr bool TAIL = decltype(tail_tag)::value;
         const int tc = blk * BT;
         const int t0 = tc + pq * BSL;
@@ -833,7 +843,7 @@ __global__ void __launch_bounds__(THREADS, 2) scan_bwd_dpp_kernel(const BwdArgs 
             bcpair_t bcw{};
 #pragma unroll
             for (int s = 0; s < LG; ++s) {   // unrolled so the register arrays stay statically indexed
-                if ((LG == 2 && odd) != (s == 1)) continue;
+                if (second != (s == 1)) continue;
                 if constexpr (RAG) {
                     if (TAIL || rows_here < ROWS) {   // uniform
                         const int sh = p_ok ? t0 - row_piece(t0, BSL, L) : BSL, ts = tc + 2 * s_tp;
@@ -876,7 +886,7 @@ __global__ void __launch_bounds__(THREADS, 2) scan_bwd_dpp_kernel(const BwdArgs 
                     dz4[j] = (o4[j] * y4[j]) * fmaf(zs, 1.0f - s, s);   // dout y d[z sigmoid(z)]/dz
                 }
             }
-            store_block(bdz_, a.dz ? static_cast<T*>(a.dz) + wg_first : nullptr, off, 0u, nv, io4<T>::pack(dz4), keep_dz, odd, tail_tag);   // switched off without a gate and for all but the first state group
+            store_block(bdz_, a.dz ? static_cast<T*>(a.dz) + wg_first : nullptr, off, 0u, nv, io4<T>::pack(dz4), keep_dz, std::integral_constant<int, 2>{}, odd, tail_tag);   // switched off without a gate and for all but the first state group
             *reinterpret_cast<float4*>(&sm.dt[pr][pq * BSL]) = make_float4(dt4[0], dt4[1], dt4[2], dt4[3]);
             *reinterpret_cast<float4*>(&sm.du[pr][pq * BSL]) = make_float4(du4[0], du4[1], du4[2], du4[3]);
             *reinterpret_cast<float4*>(&sm.dy[pr][pq * BSL]) = make_float4(dy4[0], dy4[1], dy4[2], dy4[3]);
@@ -886,7 +896,7 @@ __global__ void __launch_bounds__(THREADS, 2) scan_bwd_dpp_kernel(const BwdArgs 
             if constexpr (RAG) bc2 = s_n < N ? bc2 : make_float2(0.0f, 0.0f);   // slots without a state
             *reinterpret_cast<float2*>(&sm.bcp[s_which][s_tp >> 1][s_n][(s_tp & 1) * 2]) = bc2;
         }
-        if (!odd) {   // the pair (float: the block) below, in flight during the sweeps
+        if (!second) {   // the pair (float: the block) below, in flight during the sweeps
             if constexpr (LG == 2) issue_block(blk - 1, std::integral_constant<int, LG - 1>{});
             issue_block(blk - LG, std::integral_constant<int, 0>{});
         }
@@ -1040,9 +1050,9 @@ __global__ void __launch_bounds__(THREADS, 2) scan_bwd_dpp_kernel(const BwdArgs 
 #pragma unroll
                 for (int j = 0; j < BSL; ++j) { du4[j] += pu[j]; dl4[j] += pl[j]; }
             }
-            store_block(bdu_, static_cast<T*>(a.du) + wg_first_i, off, i_off, nv, io4<T>::pack(du4), keep_du, odd, tail_tag);
-            store_block(bdd_, static_cast<T*>(a.ddelta) + wg_first_i, off, i_off, nv, io4<T>::pack(dl4), keep_dl, odd, tail_tag);
-            if constexpr (LG == 2 && !TAIL) keep_off = odd ? off : BUF_OFF;
+            store_block(bdu_, static_cast<T*>(a.du) + wg_first_i, off, i_off, nv, io4<T>::pack(du4), keep_du, std::integral_constant<int, 0>{}, odd, tail_tag);
+            store_block(bdd_, static_cast<T*>(a.ddelta) + wg_first_i, off, i_off, nv, io4<T>::pack(dl4), keep_dl, std::integral_constant<int, 1>{}, odd, tail_tag);
+            if constexpr (!TAIL) keep_off = odd ? off : BUF_OFF;
         }
     };
     // The first block's state goes out before its inputs, as in the loop, so that the way in is not the path with the fewest
@@ -1233,7 +1243,10 @@ __global__ void __launch_bounds__(THREADS, 4) adjoint_agg_dpp_kernel(const BwdAr
     const int c_begin = seg * (f.seg_len / CHUNK_T);
     const int c_end = min((L + CHUNK_T - 1) / CHUNK_T, (seg + 1) * (f.seg_len / CHUNK_T));
 
-    const int pr = pointwise_row_pitch9(tid), pq = tid & 3;   // TPAD = 36 floats
+    constexpr int PC = slice_pieces<T>(), PE = SLICE / PC, PSTEP = CHUNK_T / PC;   // see scan_fwd_kernel
+    constexpr int HALF4 = PC == 2 ? PSTEP / 4 : 1;
+    typedef slice_io<T, PC> pio;
+    const int pr = PC == 2 ? pointwise_row_pitch5(tid) : pointwise_row_pitch9(tid), pq = tid & 3;   // TPAD = 36 floats
     const bool p_ok = d0 + pr < f.D;
     const int pd = p_ok ? d0 + pr : f.D - 1;
     const float bias = (f.flags & F_HAS_DELTA_BIAS) ? f.bias[pd] : 0.0f;
@@ -1276,72 +1289,100 @@ __global__ void __launch_bounds__(THREADS, 4) adjoint_agg_dpp_kernel(const BwdAr
     const int pat = slot_state(w, lane & 3, f.il);
 
     constexpr int PF = 2;
-    typename io8<T>::raw rd_[PF], rz_[PF], ro_[PF];
+    typename pio::raw rd_[PF][PC], rz_[PF][PC], ro_[PF][PC];
     typename io4<T>::raw rc_[PF];
-    auto issue_loads = [&](int c, auto slot_tag) {   // chunk c (walking down from c_end - 1) into a compile-time slot
-        constexpr int s = decltype(slot_tag)::value;
-        if constexpr (RAG) {   // before the segment's start: its first chunk again (never used)
-            const int cc = max(c, c_begin) * CHUNK_T;
-            const uint32_t t = (uint32_t)row_piece(cc + pq * SLICE, SLICE, L) * esz;
-            rd_[s] = io8<T>::load_elem(rd_p, r_off_i + t);
-            ro_[s] = io8<T>::load_elem(ro_p, r_off + t);
-            rz_[s] = io8<T>::load_elem(rz_p, has_z ? r_off + t : 0u);
-            rc_[s] = io4<T>::load_elem(rc_p, r_off_c + (uint32_t)row_piece(cc + s_tq * GROUP_T, GROUP_T, L) * esz);
-            return;
+    // bf16, whole slices: chunks 2i (slot 0) and 2i + 1 (slot 1) are requested together, tensor by tensor, the 128 bytes of a line (see
+    // scan_fwd_kernel; rows of any length lose 1 %).  A float chunk is a whole line (1 x 5001 x 4096, forward + backward, one by one 585 us, in pairs 596).
+    constexpr bool PAIR = sizeof(T) == 2 && !RAG;
+    auto issue = [&](int c0, auto from_tag, auto to_tag) {   // slots from .. to - 1 of the pair c0, c0 + 1
+        constexpr int S0 = decltype(from_tag)::value, S1 = decltype(to_tag)::value;
+        uint32_t off[PF][PC], offc[PF];
+#pragma unroll
+        for (int s = S0; s < S1; ++s) {
+            // RAG: before the segment's start or past its end: its first or last chunk again (never used)
+            const int c = RAG ? min(max(c0 + s, c_begin), c_end - 1) : c0 + s, ts = c * CHUNK_T + s_tq * GROUP_T;
+#pragma unroll
+            for (int p = 0; p < PC; ++p) {   // pieces are whole or empty
+                const int t = c * CHUNK_T + p * PSTEP + pq * PE;
+                if constexpr (RAG) off[s][p] = (uint32_t)row_piece(t, PE, L) * esz;
+                else off[s][p] = (t < L && c >= c_begin) ? row_off + (uint32_t)t * esz : BUF_OFF;
+            }
+            if constexpr (RAG) offc[s] = r_off_c + (uint32_t)row_piece(ts, GROUP_T, L) * esz;
+            else offc[s] = (ts < L && c >= c_begin) ? c_row_off + (uint32_t)ts * esz : BUF_OFF;
         }
-        const int t0 = c * CHUNK_T + pq * SLICE;
-        const uint32_t off = (t0 < L && c >= c_begin) ? row_off + (uint32_t)t0 * (uint32_t)sizeof(T) : BUF_OFF;   // slices are whole or empty
-        rd_[s] = io8<T>::load_buf(bd_, off);
-        ro_[s] = io8<T>::load_buf(bo_, off);
-        rz_[s] = io8<T>::load_buf(bz_, off);
-        const int ts = c * CHUNK_T + s_tq * GROUP_T;
-        rc_[s] = io4<T>::load_buf(bc_, (ts < L && c >= c_begin) ? c_row_off + (uint32_t)ts * (uint32_t)sizeof(T) : BUF_OFF);
+        auto both = [&](typename pio::raw (&r)[PF][PC], const rsrc_t& rs, const T* base, uint32_t row, bool on) {
+#pragma unroll
+            for (int s = S0; s < S1; ++s)
+#pragma unroll
+                for (int p = 0; p < PC; ++p) {
+                    if constexpr (RAG) r[s][p] = pio::load_elem(base, on ? row + off[s][p] : 0u);
+                    else r[s][p] = pio::load_buf(rs, off[s][p]);
+                }
+        };
+        both(rd_, bd_, rd_p, r_off_i, true);
+        both(ro_, bo_, ro_p, r_off, true);
+        both(rz_, bz_, rz_p, r_off, has_z);
+#pragma unroll
+        for (int s = S0; s < S1; ++s) {
+            if constexpr (RAG) rc_[s] = io4<T>::load_elem(rc_p, offc[s]);
+            else rc_[s] = io4<T>::load_buf(bc_, offc[s]);
+        }
     };
-    issue_loads(c_end - 1, std::integral_constant<int, 0>{});
-    issue_loads(c_end - 2, std::integral_constant<int, 1>{});
+    {
+        const int top = (c_end - 1) & ~1;   // where it is the segment's last chunk, slot 1 is next used below it
+        if constexpr (PAIR) {
+            issue(top, std::integral_constant<int, 0>{}, std::integral_constant<int, PF>{});
+        } else {
+            issue(top, std::integral_constant<int, 0>{}, std::integral_constant<int, 1>{});
+            issue(top + 1 < c_end ? top : top - PF, std::integral_constant<int, 1>{}, std::integral_constant<int, PF>{});
+        }
+    }
 
     auto do_chunk = [&](const int c, auto slot_tag) {
         constexpr int SLOT = decltype(slot_tag)::value;
-        const int t0 = c * CHUNK_T + pq * SLICE;
-        const bool live = p_ok && t0 < L;
+        const int t0 = c * CHUNK_T + pq * PE;
         {
             float v8[SLICE], o8[SLICE], z8[SLICE], dt8[SLICE], c4[GROUP_T];
-            const int nv = min(max(L - t0, 0), SLICE);
             if constexpr (RAG) {
                 if ((c + 1) * CHUNK_T > L) {   // uniform
-                    const int sh = t0 - row_piece(t0, SLICE, L), ts = c * CHUNK_T + s_tq * GROUP_T;
-                    io8<T>::drop(rd_[SLOT], sh);
-                    io8<T>::drop(ro_[SLOT], sh);
-                    io8<T>::drop(rz_[SLOT], sh);
+                    const int ts = c * CHUNK_T + s_tq * GROUP_T;
+#pragma unroll
+                    for (int p = 0; p < PC; ++p) {
+                        const int t = t0 + p * PSTEP, sh = t - row_piece(t, PE, L);
+                        pio::drop(rd_[SLOT][p], sh);
+                        pio::drop(ro_[SLOT][p], sh);
+                        pio::drop(rz_[SLOT][p], sh);
+                    }
                     io4<T>::drop(rc_[SLOT], ts - row_piece(ts, GROUP_T, L));
                 }
             }
-            io8<T>::unpack(rd_[SLOT], v8);
-            io8<T>::unpack(ro_[SLOT], o8);
-            if (has_z) io8<T>::unpack(rz_[SLOT], z8);
+            unpack_slice<pio, PC>(rd_[SLOT], v8);
+            unpack_slice<pio, PC>(ro_[SLOT], o8);
+            if (has_z) unpack_slice<pio, PC>(rz_[SLOT], z8);
             io4<T>::unpack(rc_[SLOT], c4);
-            const float bias_eff = live ? bias : (softplus ? -1e30f : 0.0f);   // an empty slice runs with dt = 0
 #pragma unroll
             for (int j = 0; j < SLICE; ++j) {
-                float sp = v8[j] + bias_eff;
+                const int tp = t0 + j / PE * PSTEP;   // an empty piece runs with dt = 0
+                float sp = v8[j] + (p_ok && tp < L ? bias : (softplus ? -1e30f : 0.0f));
                 if (softplus) sp = ss::softplus(sp);
-                if constexpr (RAG) sp = j < nv ? sp : 0.0f;
+                if constexpr (RAG) sp = tp + j % PE < L ? sp : 0.0f;
                 dt8[j] = sp;
                 if (has_z) o8[j] *= z8[j] * sigmoid_fast(z8[j]);
             }
-            float4* pd4 = reinterpret_cast<float4*>(&s_dt[pr][pq * SLICE]);
-            float4* py4 = reinterpret_cast<float4*>(&s_dy[pr][pq * SLICE]);
+            float4* pd4 = reinterpret_cast<float4*>(&s_dt[pr][pq * PE]);
+            float4* py4 = reinterpret_cast<float4*>(&s_dy[pr][pq * PE]);
             pd4[0] = make_float4(dt8[0], dt8[1], dt8[2], dt8[3]);
-            pd4[1] = make_float4(dt8[4], dt8[5], dt8[6], dt8[7]);
+            pd4[HALF4] = make_float4(dt8[4], dt8[5], dt8[6], dt8[7]);
             py4[0] = make_float4(o8[0], o8[1], o8[2], o8[3]);
-            py4[1] = make_float4(o8[4], o8[5], o8[6], o8[7]);
+            py4[HALF4] = make_float4(o8[4], o8[5], o8[6], o8[7]);
             if constexpr (RAG) {   // slots without a state
 #pragma unroll
                 for (int j = 0; j < GROUP_T; ++j) c4[j] = s_n < N ? c4[j] : 0.0f;
             }
             if (w < 2) *reinterpret_cast<float4*>(&s_c[s_tq][s_n][0]) = make_float4(c4[0], c4[1], c4[2], c4[3]);
         }
-        issue_loads(c - PF, slot_tag);
+        if constexpr (!PAIR) issue((c & ~1) - PF, slot_tag, std::integral_constant<int, SLOT + 1>{});
+        else if constexpr (SLOT == 0) issue(c - PF, slot_tag, std::integral_constant<int, PF>{});
         __syncthreads();
         __builtin_amdgcn_s_setprio(2);   // as in scan_bwd_kernel: the recurrence at a raised wave priority
         float4 dtc[NGC], dyc[NGC], Cpc[NGC];
@@ -1367,9 +1408,9 @@ __global__ void __launch_bounds__(THREADS, 4) adjoint_agg_dpp_kernel(const BwdAr
         __builtin_amdgcn_s_setprio(0);
         __syncthreads();
     };
-    for (int c = c_end - 1; c >= c_begin; c -= PF) {
+    for (int c = (c_end - 1) & ~1; c >= c_begin; c -= PF) {   // segments start at even chunks
+        if (c + 1 < c_end) do_chunk(c + 1, std::integral_constant<int, 1>{});
         do_chunk(c, std::integral_constant<int, 0>{});
-        if (c - 1 >= c_begin) do_chunk(c - 1, std::integral_constant<int, 1>{});
     }
     if (s_ok) {
         float4* dst = reinterpret_cast<float4*>(a.seg_g + ((long)seg * f.B * f.D + srow) * NPAD) + w;
@@ -1587,8 +1628,9 @@ static int launch_bwd_dpp_t(const BwdArgs& a, dim3 grid, hipStream_t stream)
     }
     auto kern = scan_bwd_dpp_kernel<T, SPL, ZOH, RAG>;
     static std::atomic<bool> lds_ok[MAX_DEVICES];   // this launcher is instantiated once per kernel
-    if (!allow_backward_lds_once(reinterpret_cast<const void*>(kern), lds_ok, sizeof(BwdSmemDpp))) return -1;
-    kern<<<dim3(grid.x, (unsigned)a.f.nseg), dim3(THREADS), sizeof(BwdSmemDpp), stream>>>(a);
+    constexpr size_t lds = sizeof(bwd_smem_dpp<T, ZOH, RAG>);
+    if (!allow_backward_lds_once(reinterpret_cast<const void*>(kern), lds_ok, lds)) return -1;
+    kern<<<dim3(grid.x, (unsigned)a.f.nseg), dim3(THREADS), lds, stream>>>(a);
     return hipGetLastError() == hipSuccess ? 0 : -1;
 }
 template <typename T, bool RAG>

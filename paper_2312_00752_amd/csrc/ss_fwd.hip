@@ -92,7 +92,11 @@ __global__ void __launch_bounds__(THREADS, PAT && AGG ? 4 : ((PAT && FUSED_KS <=
     const int c_end = min((L + CHUNK_T - 1) / CHUNK_T, (seg + 1) * (a.seg_len / CHUNK_T));
 
     // ---- pointwise view: thread -> (row pr, slice pq) -----------------------------------
-    const int pr = pointwise_row_pitch9(tid), pq = tid & 3;   // TPAD = 36 floats
+    // A slice is PC pieces of PE consecutive steps, one 16-byte access each (float off the quad-broadcast kernels: two)
+    constexpr int PC = PAT ? slice_pieces<T>() : 1, PE = SLICE / PC, PSTEP = CHUNK_T / PC;
+    constexpr int HALF4 = PC == 2 ? PSTEP / 4 : 1;   // float4s from a slice's first four steps to its last four
+    typedef slice_io<T, PC> pio;
+    const int pr = PC == 2 ? pointwise_row_pitch5(tid) : pointwise_row_pitch9(tid), pq = tid & 3;   // TPAD = 36 floats
     const bool p_ok = d0 + pr < a.D;
     const int pd = p_ok ? d0 + pr : a.D - 1;  // out-of-range rows shadow the last row; stores masked
     const long prow = (long)b * a.D + pd;
@@ -224,39 +228,45 @@ __global__ void __launch_bounds__(THREADS, PAT && AGG ? 4 : ((PAT && FUSED_KS <=
     // enough to cover a memory round trip under load, and with one chunk in flight per workgroup
     // the kernel ran at the pace of that latency whatever the state size.
     constexpr int PF = VEC ? 2 : 1;
-    typename io8<T>::raw ru_[PF], rd_[PF], rz_[PF];
+    typename pio::raw ru_[PF][PC], rd_[PF][PC], rz_[PF][PC];
     typename io4<T>::raw rbc_[PF];   // PAT: the thread's four steps of B or C
-    typename io8<T>::raw rp_[PF];    // VEC: the pre-gate y of the earlier state groups (zeros if there are none)
+    typename pio::raw rp_[PF][PC];   // VEC: the pre-gate y of the earlier state groups (zeros if there are none)
     auto issue_loads = [&](int c, auto slot_tag) {   // chunk c into the slot given at compile time
         constexpr int s = decltype(slot_tag)::value;
-        const int t0 = c * CHUNK_T + pq * SLICE;
-        const int nv = min(max(L - t0, 0), SLICE);
         if constexpr (RAG) {   // past the segment's end: its last chunk again (never used)
             const int cc = min(c, c_end - 1) * CHUNK_T;
-            const uint32_t t = (uint32_t)row_piece(cc + pq * SLICE, SLICE, L) * esz;
-            ru_[s] = io8<T>::load_elem(ru_p, r_off_i + t);
-            if constexpr (FUSED_KS == 0) rd_[s] = io8<T>::load_elem(rd_p, r_off_i + t);
-            if constexpr (!AGG) {
-                rz_[s] = io8<T>::load_elem(rz_p, has_z ? r_off + t : 0u);
-                rp_[s] = io8<T>::load_elem(rp_p, acc_on ? r_off_p + t : 0u);
+#pragma unroll
+            for (int p = 0; p < PC; ++p) {
+                const uint32_t t = (uint32_t)row_piece(cc + p * PSTEP + pq * PE, PE, L) * esz;
+                ru_[s][p] = pio::load_elem(ru_p, r_off_i + t);
+                if constexpr (FUSED_KS == 0) rd_[s][p] = pio::load_elem(rd_p, r_off_i + t);
+                if constexpr (!AGG) {
+                    rz_[s][p] = pio::load_elem(rz_p, has_z ? r_off + t : 0u);
+                    rp_[s][p] = pio::load_elem(rp_p, acc_on ? r_off_p + t : 0u);
+                }
             }
             rbc_[s] = io4<T>::load_elem(rbc_p, r_off_bc + (uint32_t)row_piece(cc + s_tq * GROUP_T, GROUP_T, L) * esz);
-        } else if constexpr (VEC) {   // slices are whole or empty
-            const uint32_t off = (nv == SLICE && c < c_end) ? row_off + (uint32_t)t0 * (uint32_t)sizeof(T) : BUF_OFF;
-            ru_[s] = io8<T>::load_buf(bu, off);
-            if constexpr (FUSED_KS == 0) rd_[s] = io8<T>::load_buf(bd, off);
-            if constexpr (!AGG) {
-                rz_[s] = io8<T>::load_buf(bz, off);
-                rp_[s] = io8<T>::load_buf(bp, off);
+        } else if constexpr (VEC) {   // pieces are whole or empty
+#pragma unroll
+            for (int p = 0; p < PC; ++p) {
+                const int t = c * CHUNK_T + p * PSTEP + pq * PE;
+                const uint32_t off = (t < L && c < c_end) ? row_off + (uint32_t)t * (uint32_t)sizeof(T) : BUF_OFF;
+                ru_[s][p] = pio::load_buf(bu, off);
+                if constexpr (FUSED_KS == 0) rd_[s][p] = pio::load_buf(bd, off);
+                if constexpr (!AGG) {
+                    rz_[s][p] = pio::load_buf(bz, off);
+                    rp_[s][p] = pio::load_buf(bp, off);
+                }
             }
             if constexpr (PAT) {   // L % 8 == 0: a group of four steps is whole or past the end
                 const int ts = c * CHUNK_T + s_tq * GROUP_T;
                 rbc_[s] = io4<T>::load_buf(bbc, (ts < L && c < c_end) ? bc_row_off + (uint32_t)ts * (uint32_t)sizeof(T) : BUF_OFF);
             }
         } else {
-            ru_[s] = load_slice8<T, VEC, SHORT>(gu, t0, L, true);
-            rd_[s] = load_slice8<T, VEC, SHORT>(gdl, t0, L, true);
-            if (has_z) rz_[s] = load_slice8<T, VEC, SHORT>(gz, t0, L, true);
+            const int t0 = c * CHUNK_T + pq * SLICE;
+            ru_[s][0] = load_slice8<T, VEC, SHORT>(gu, t0, L, true);
+            rd_[s][0] = load_slice8<T, VEC, SHORT>(gdl, t0, L, true);
+            if (has_z) rz_[s][0] = load_slice8<T, VEC, SHORT>(gz, t0, L, true);
         }
     };
     // FUSED: delta_raw of a chunk from the fragments in registers: two 16 x 16 tiles per wave,
@@ -314,8 +324,11 @@ __global__ void __launch_bounds__(THREADS, PAT && AGG ? 4 : ((PAT && FUSED_KS <=
     // half lines reach about half the throughput of whole lines (and reads somewhat less than whole
     // ones), so the traffic of an even chunk and the odd one after it (segments start at even
     // chunks) is issued together: both chunks' inputs are requested in the odd chunk's phase A, tensor
-    // by tensor, and the even chunk's results wait in registers for the odd chunk's.
-    constexpr bool PAIR = PAT && sizeof(T) == 2 && PF == 2;
+    // by tensor, and the even chunk's results wait in registers for the odd chunk's.  A float chunk is a whole
+    // line: its inputs are better requested one by one (8 x 2048 x 4096 forward 293 us, in pairs 306), its results
+    // wait all the same, for rows a large power of two apart (256 x 2^20, forward + backward 7800 -> 7670 us, the
+    // shorter rows within 0.5 %).
+    constexpr bool PAIR = PAT && sizeof(T) == 2;
     auto issue_pair = [&](int c0) {   // chunks c0 (slot 0) and c0 + 1 (slot 1)
       if constexpr (PAIR && RAG) {
         uint32_t t[2], tb[2];
@@ -325,11 +338,11 @@ __global__ void __launch_bounds__(THREADS, PAT && AGG ? 4 : ((PAT && FUSED_KS <=
             t[s] = (uint32_t)row_piece(cc + pq * SLICE, SLICE, L) * esz;
             tb[s] = r_off_bc + (uint32_t)row_piece(cc + s_tq * GROUP_T, GROUP_T, L) * esz;
         }
-        ru_[0] = io8<T>::load_elem(ru_p, r_off_i + t[0]); ru_[1] = io8<T>::load_elem(ru_p, r_off_i + t[1]);
-        if constexpr (FUSED_KS == 0) { rd_[0] = io8<T>::load_elem(rd_p, r_off_i + t[0]); rd_[1] = io8<T>::load_elem(rd_p, r_off_i + t[1]); }
+        ru_[0][0] = io8<T>::load_elem(ru_p, r_off_i + t[0]); ru_[1][0] = io8<T>::load_elem(ru_p, r_off_i + t[1]);
+        if constexpr (FUSED_KS == 0) { rd_[0][0] = io8<T>::load_elem(rd_p, r_off_i + t[0]); rd_[1][0] = io8<T>::load_elem(rd_p, r_off_i + t[1]); }
         if constexpr (!AGG) {
-            rz_[0] = io8<T>::load_elem(rz_p, has_z ? r_off + t[0] : 0u); rz_[1] = io8<T>::load_elem(rz_p, has_z ? r_off + t[1] : 0u);
-            rp_[0] = io8<T>::load_elem(rp_p, acc_on ? r_off_p + t[0] : 0u); rp_[1] = io8<T>::load_elem(rp_p, acc_on ? r_off_p + t[1] : 0u);
+            rz_[0][0] = io8<T>::load_elem(rz_p, has_z ? r_off + t[0] : 0u); rz_[1][0] = io8<T>::load_elem(rz_p, has_z ? r_off + t[1] : 0u);
+            rp_[0][0] = io8<T>::load_elem(rp_p, acc_on ? r_off_p + t[0] : 0u); rp_[1][0] = io8<T>::load_elem(rp_p, acc_on ? r_off_p + t[1] : 0u);
         }
         rbc_[0] = io4<T>::load_elem(rbc_p, tb[0]); rbc_[1] = io4<T>::load_elem(rbc_p, tb[1]);
       } else if constexpr (PAIR) {
@@ -342,16 +355,16 @@ __global__ void __launch_bounds__(THREADS, PAT && AGG ? 4 : ((PAT && FUSED_KS <=
             const int ts = c * CHUNK_T + s_tq * GROUP_T;
             boff[s] = (ts < L && c < c_end) ? bc_row_off + (uint32_t)ts * (uint32_t)sizeof(T) : BUF_OFF;
         }
-        ru_[0] = io8<T>::load_buf(bu, off[0]); ru_[1] = io8<T>::load_buf(bu, off[1]);
-        if constexpr (FUSED_KS == 0) { rd_[0] = io8<T>::load_buf(bd, off[0]); rd_[1] = io8<T>::load_buf(bd, off[1]); }
+        ru_[0][0] = io8<T>::load_buf(bu, off[0]); ru_[1][0] = io8<T>::load_buf(bu, off[1]);
+        if constexpr (FUSED_KS == 0) { rd_[0][0] = io8<T>::load_buf(bd, off[0]); rd_[1][0] = io8<T>::load_buf(bd, off[1]); }
         if constexpr (!AGG) {
-            rz_[0] = io8<T>::load_buf(bz, off[0]); rz_[1] = io8<T>::load_buf(bz, off[1]);
-            rp_[0] = io8<T>::load_buf(bp, off[0]); rp_[1] = io8<T>::load_buf(bp, off[1]);
+            rz_[0][0] = io8<T>::load_buf(bz, off[0]); rz_[1][0] = io8<T>::load_buf(bz, off[1]);
+            rp_[0][0] = io8<T>::load_buf(bp, off[0]); rp_[1][0] = io8<T>::load_buf(bp, off[1]);
         }
         rbc_[0] = io4<T>::load_buf(bbc, boff[0]); rbc_[1] = io4<T>::load_buf(bbc, boff[1]);
       }
     };
-    typename io8<T>::packed held_y{}, held_o{};
+    typename pio::packed held_y[PC]{}, held_o[PC]{};
     if constexpr (FUSED_KS > 0) {
         issue_r(c_begin);
         stage_r();
@@ -370,24 +383,32 @@ __global__ void __launch_bounds__(THREADS, PAT && AGG ? 4 : ((PAT && FUSED_KS <=
         constexpr int SLOT = decltype(slot_tag)::value;
         float u8[SLICE], z8[SLICE], v8[SLICE];
         const int tc = c * CHUNK_T;
-        const int t0 = tc + pq * SLICE;
-        const int nv = min(max(L - t0, 0), SLICE);
+        const int t0 = tc + pq * PE;
+        int nv[PC];   // steps of each piece inside the row
+#pragma unroll
+        for (int p = 0; p < PC; ++p) nv[p] = min(max(L - t0 - p * PSTEP, 0), PE);
         // ---- A: pointwise pre-processing --------------------------------------------
-        typename io8<T>::raw ru = ru_[SLOT], rd = rd_[SLOT], rz = rz_[SLOT];
+        typename pio::raw ru[PC], rd[PC], rz[PC];
+#pragma unroll
+        for (int p = 0; p < PC; ++p) { ru[p] = ru_[SLOT][p]; rd[p] = rd_[SLOT][p]; rz[p] = rz_[SLOT][p]; }
         typename io4<T>::raw rbc = rbc_[SLOT];
         if constexpr (RAG) {
             if (tc + CHUNK_T > L) {   // uniform: the last chunk of a row that does not fill it
-                const int sh = t0 - row_piece(t0, SLICE, L), ts = tc + s_tq * GROUP_T;
-                io8<T>::drop(ru, sh);
-                if constexpr (FUSED_KS == 0) io8<T>::drop(rd, sh);
-                if constexpr (!AGG) io8<T>::drop(rz, sh);
-                if (acc_on) io8<T>::drop(rp_[SLOT], sh);
+                const int ts = tc + s_tq * GROUP_T;
+#pragma unroll
+                for (int p = 0; p < PC; ++p) {
+                    const int t = t0 + p * PSTEP, sh = t - row_piece(t, PE, L);
+                    pio::drop(ru[p], sh);
+                    if constexpr (FUSED_KS == 0) pio::drop(rd[p], sh);
+                    if constexpr (!AGG) pio::drop(rz[p], sh);
+                    if (acc_on) pio::drop(rp_[SLOT][p], sh);
+                }
                 io4<T>::drop(rbc, ts - row_piece(ts, GROUP_T, L));
             }
         }
         float p8[SLICE];
         if constexpr (VEC) {
-            if (acc_on) io8<T>::unpack(rp_[SLOT], p8);   // uniform: only with more than 16 states
+            if (acc_on) unpack_slice<pio, PC>(rp_[SLOT], p8);   // uniform: only with more than 16 states
         }
         if constexpr (PAT) {
             float bc4[GROUP_T];
@@ -398,7 +419,7 @@ __global__ void __launch_bounds__(THREADS, PAT && AGG ? 4 : ((PAT && FUSED_KS <=
             }
             *reinterpret_cast<float4*>(&s_bc[s_which][s_tq][s_n][0]) = make_float4(bc4[0], bc4[1], bc4[2], bc4[3]);
         }
-        io8<T>::unpack(ru, u8);
+        unpack_slice<pio, PC>(ru, u8);
         if constexpr (FUSED_KS > 0) {   // delta_raw of this chunk: left in s_raw by this same wave (project)
             const float4 d0v = *reinterpret_cast<const float4*>(&s_raw[pr][pq * SLICE]);
             const float4 d1v = *reinterpret_cast<const float4*>(&s_raw[pr][pq * SLICE + 4]);
@@ -406,31 +427,31 @@ __global__ void __launch_bounds__(THREADS, PAT && AGG ? 4 : ((PAT && FUSED_KS <=
 #pragma unroll
             for (int j = 0; j < SLICE; ++j) v8[j] = bf16_to_f32(bf16_t(f32_to_bf16_bits(raw[j])));   // as the stored delta would be
         } else {
-            io8<T>::unpack(rd, v8);
+            unpack_slice<pio, PC>(rd, v8);
         }
-        if (has_z) io8<T>::unpack(rz, z8);
+        if (has_z) unpack_slice<pio, PC>(rz, z8);
         {
             float dt8[SLICE], du8[SLICE];
-            // PAT without the in-kernel projection: a slice is whole or empty, and an empty one was read as
+            // PAT without the in-kernel projection: a piece is whole or empty, and an empty one was read as
             // zeros; a bias of -1e30 (0 without softplus) then makes its step sizes exactly 0, the identity of
             // the recurrence, without a select per element
             constexpr bool ZERO_BY_BIAS = PAT && FUSED_KS == 0 && !RAG;
-            const float bias_e = !ZERO_BY_BIAS || nv == SLICE ? bias : (softplus ? -1e30f : 0.0f);
 #pragma unroll
             for (int j = 0; j < SLICE; ++j) {
+                const float bias_e = !ZERO_BY_BIAS || nv[j / PE] == PE ? bias : (softplus ? -1e30f : 0.0f);
                 float sp = v8[j] + bias_e;
                 if (softplus) sp = ss::softplus(sp);
-                if constexpr (!ZERO_BY_BIAS) sp = (j < nv) ? sp : 0.0f;
+                if constexpr (!ZERO_BY_BIAS) sp = (j % PE < nv[j / PE]) ? sp : 0.0f;
                 dt8[j] = sp;
                 du8[j] = ZOH ? u8[j] : sp * u8[j];
                 if (AGG) sum_dt += sp;
             }
-            float4* pd4 = reinterpret_cast<float4*>(&s_dt[pr][pq * SLICE]);
-            float4* pu4 = reinterpret_cast<float4*>(&s_du[pr][pq * SLICE]);
+            float4* const pd4 = reinterpret_cast<float4*>(&s_dt[pr][pq * PE]);   // four steps each
+            float4* const pu4 = reinterpret_cast<float4*>(&s_du[pr][pq * PE]);
             pd4[0] = make_float4(dt8[0], dt8[1], dt8[2], dt8[3]);
-            pd4[1] = make_float4(dt8[4], dt8[5], dt8[6], dt8[7]);
+            pd4[HALF4] = make_float4(dt8[4], dt8[5], dt8[6], dt8[7]);
             pu4[0] = make_float4(du8[0], du8[1], du8[2], du8[3]);
-            pu4[1] = make_float4(du8[4], du8[5], du8[6], du8[7]);
+            pu4[HALF4] = make_float4(du8[4], du8[5], du8[6], du8[7]);
         }
         // The touch of the next chunk's B and C goes here, after the wait for this chunk's u,
         // delta and z: the value touched a chunk ago is older than those and costs no wait of
@@ -614,12 +635,11 @@ __global__ void __launch_bounds__(THREADS, PAT && AGG ? 4 : ((PAT && FUSED_KS <=
             for (int j = 0; j < SLICE; ++j) y8[j] = has_D ? Dsk * u8[j] : 0.0f;
 #pragma unroll
             for (int ww = 0; ww < NWAVES; ++ww) {
-                const float4 p0 = *reinterpret_cast<const float4*>(&s_yp[ww][pr][pq * SLICE]);
-                const float4 p1 = *reinterpret_cast<const float4*>(&s_yp[ww][pr][pq * SLICE + 4]);
+                const float4* const p4 = reinterpret_cast<const float4*>(&s_yp[ww][pr][pq * PE]);
+                const float4 p0 = p4[0], p1 = p4[HALF4];
                 y8[0] += p0.x; y8[1] += p0.y; y8[2] += p0.z; y8[3] += p0.w;
                 y8[4] += p1.x; y8[5] += p1.y; y8[6] += p1.z; y8[7] += p1.w;
             }
-            const int nvs = p_ok ? nv : 0;
             if constexpr (VEC) {   // states beyond the first 16: add to what the earlier groups left
                 if (acc_on) {
 #pragma unroll
@@ -631,47 +651,56 @@ __global__ void __launch_bounds__(THREADS, PAT && AGG ? 4 : ((PAT && FUSED_KS <=
 #pragma unroll
                 for (int j = 0; j < SLICE; ++j) y8[j] += p8[j];
             }
-            const uint32_t off = nv == SLICE ? row_off + (uint32_t)t0 * (uint32_t)sizeof(T) : BUF_OFF;
-            if constexpr (PAIR) {
-                const typename io8<T>::packed py = io8<T>::pack(y8);   // y before the gate, for the backward pass's dz (if kept)
+            if constexpr (PAT) {
+                uint32_t off[PC], off_e[PC];   // a piece, and the same piece of the even chunk (whole before an odd one; a lone even chunk has nothing waiting)
+                typename pio::packed py[PC], po[PC];
+#pragma unroll
+                for (int p = 0; p < PC; ++p) {
+                    const uint32_t at = row_off + (uint32_t)(t0 + p * PSTEP) * esz;
+                    off[p] = nv[p] == PE ? at : BUF_OFF;
+                    off_e[p] = SLOT == 1 ? at - CHUNK_T * esz : BUF_OFF;
+                }
+                pack_slice<pio, PC>(y8, py);   // y before the gate, for the backward pass's dz (if kept)
                 if (has_z) {
 #pragma unroll
                     for (int j = 0; j < SLICE; ++j) y8[j] *= z8[j] * sigmoid_fast(z8[j]);
                 }
-                const typename io8<T>::packed po = io8<T>::pack(y8);
+                pack_slice<pio, PC>(y8, po);
                 if (SLOT == 0 && c + 1 < c_end) {   // wait for the odd chunk
-                    held_y = py;
-                    held_o = po;
+#pragma unroll
+                    for (int p = 0; p < PC; ++p) { held_y[p] = py[p]; held_o[p] = po[p]; }
                 } else if constexpr (RAG) {
-                    const uint32_t off_t = (uint32_t)t0 * esz;
                     if (p_ok) {
                         T* const yp = static_cast<T*>(a.ysave) + wg_first_i;
                         T* const op = static_cast<T*>(a.out) + wg_first;
-                        if (SLOT == 1) {   // the even chunk before an odd one is whole
-                            if (keep_y) io8<T>::store_elem(yp, r_off_i + off_t - CHUNK_T * esz, held_y, SLICE);
-                            if (keep_y) io8<T>::store_elem(yp, r_off_i + off_t, py, nv);
-                            io8<T>::store_elem(op, r_off + off_t - CHUNK_T * esz, held_o, SLICE);
-                        } else if (keep_y) {
-                            io8<T>::store_elem(yp, r_off_i + off_t, py, nv);
+                        const uint32_t yt = r_off_i + (uint32_t)t0 * esz, ot = r_off + (uint32_t)t0 * esz;
+                        if (SLOT == 1) {
+#pragma unroll
+                            for (int p = 0; p < PC; ++p)
+                                if (keep_y) pio::store_elem(yp, yt + (uint32_t)(p * PSTEP - CHUNK_T) * esz, held_y[p], PE);
                         }
-                        io8<T>::store_elem(op, r_off + off_t, po, nv);
+#pragma unroll
+                        for (int p = 0; p < PC; ++p)
+                            if (keep_y) pio::store_elem(yp, yt + (uint32_t)(p * PSTEP) * esz, py[p], nv[p]);
+                        if (SLOT == 1) {
+#pragma unroll
+                            for (int p = 0; p < PC; ++p) pio::store_elem(op, ot + (uint32_t)(p * PSTEP - CHUNK_T) * esz, held_o[p], PE);
+                        }
+#pragma unroll
+                        for (int p = 0; p < PC; ++p) pio::store_elem(op, ot + (uint32_t)(p * PSTEP) * esz, po[p], nv[p]);
                     }
                 } else {
-                    // the even chunk before an odd one is whole; a lone even chunk has nothing waiting
-                    const uint32_t off_e = SLOT == 1 ? row_off + (uint32_t)(t0 - CHUNK_T) * (uint32_t)sizeof(T) : BUF_OFF;
-                    io8<T>::store_packed(by, off_e, held_y);
-                    io8<T>::store_packed(by, off, py);
-                    io8<T>::store_packed(bo, off_e, held_o);
-                    io8<T>::store_packed(bo, off, po);
-                }
-            } else if constexpr (RAG) {
-                if (keep_y && p_ok) io8<T>::store_elem(static_cast<T*>(a.ysave) + wg_first_i, r_off_i + (uint32_t)t0 * esz, io8<T>::pack(y8), nv);
-                if (has_z) {
 #pragma unroll
-                    for (int j = 0; j < SLICE; ++j) y8[j] *= z8[j] * sigmoid_fast(z8[j]);
+                    for (int p = 0; p < PC; ++p) pio::store_packed(by, off_e[p], held_y[p]);
+#pragma unroll
+                    for (int p = 0; p < PC; ++p) pio::store_packed(by, off[p], py[p]);
+#pragma unroll
+                    for (int p = 0; p < PC; ++p) pio::store_packed(bo, off_e[p], held_o[p]);
+#pragma unroll
+                    for (int p = 0; p < PC; ++p) pio::store_packed(bo, off[p], po[p]);
                 }
-                if (p_ok) io8<T>::store_elem(static_cast<T*>(a.out) + wg_first, r_off + (uint32_t)t0 * esz, io8<T>::pack(y8), nv);
             } else if constexpr (VEC) {
+                const uint32_t off = nv[0] == SLICE ? row_off + (uint32_t)t0 * (uint32_t)sizeof(T) : BUF_OFF;
                 io8<T>::store_buf(by, off, y8);   // y before the gate, for the backward pass's dz (if kept)
                 if (has_z) {
 #pragma unroll
@@ -679,6 +708,7 @@ __global__ void __launch_bounds__(THREADS, PAT && AGG ? 4 : ((PAT && FUSED_KS <=
                 }
                 io8<T>::store_buf(bo, off, y8);
             } else {
+                const int nvs = p_ok ? nv[0] : 0;
                 if (has_z) {
                     if (a.ysave)  // y before the gate, for the backward pass's dz
                         store_slice<T, VEC, SHORT, io8, SLICE>(static_cast<T*>(a.ysave) + prow * L + t0, y8, nvs);

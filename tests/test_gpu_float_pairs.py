@@ -1,0 +1,18 @@
+"""Float32 rows of whole slices: a thread's slice is four steps from each half of a 32-step chunk, and the results of an odd
+chunk (forward) or of an even block (backward) take the waiting ones of its neighbour along.  Lengths that end in the first and
+in the second half of an even and of an odd chunk, in an even and in an odd block; whole and in segments; the patterns around
+every output, NaN around every input (as for rows of any length)."""
+import pytest
+
+from tests.test_gpu_ragged import test_ragged_rows
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("batch,seqlen,dim,dstate,zoh", [
+    (1, 8, 64, 16, False), (2, 16, 65, 4, False), (1, 24, 3, 16, True), (1, 40, 70, 16, False), (2, 56, 66, 1, False), (1, 64, 130, 16, False),
+    (1, 72, 64, 20, False), (1, 88, 40, 7, True), (3, 104, 33, 16, False),
+    # split: the last segment ends in either half of an even and of an odd chunk
+    (1, 520, 64, 16, False), (1, 536, 100, 16, True), (2, 560, 70, 5, False), (1, 2072, 64, 16, False), (1, 2096, 30, 18, False)])
+def test_float_rows_of_whole_slices(batch, seqlen, dim, dstate, zoh):
+    test_ragged_rows("f32", batch, seqlen, dim, dstate, zoh)
