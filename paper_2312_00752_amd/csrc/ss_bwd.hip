@@ -1338,6 +1338,7 @@ __global__ void __launch_bounds__(THREADS, 4) adjoint_agg_dpp_kernel(const BwdAr
         }
     }
 
+    float sum_dt = 0.0f;   // this thread's share of the segment's sum of step sizes
     auto do_chunk = [&](const int c, auto slot_tag) {
         constexpr int SLOT = decltype(slot_tag)::value;
         const int t0 = c * CHUNK_T + pq * PE;
@@ -1367,6 +1368,7 @@ __global__ void __launch_bounds__(THREADS, 4) adjoint_agg_dpp_kernel(const BwdAr
                 if (softplus) sp = ss::softplus(sp);
                 if constexpr (RAG) sp = tp + j % PE < L ? sp : 0.0f;
                 dt8[j] = sp;
+                sum_dt += sp;
                 if (has_z) o8[j] *= z8[j] * sigmoid_fast(z8[j]);
             }
             float4* pd4 = reinterpret_cast<float4*>(&s_dt[pr][pq * PE]);
@@ -1416,6 +1418,10 @@ __global__ void __launch_bounds__(THREADS, 4) adjoint_agg_dpp_kernel(const BwdAr
         float4* dst = reinterpret_cast<float4*>(a.seg_g + ((long)seg * f.B * f.D + srow) * NPAD) + w;
         *dst = make_float4(ag[0], ag[1], ag[2], ag[3]);
     }
+    // what the chain over the segments takes beside (a forward pass over whole rows has not left it)
+    sum_dt += __shfl_xor(sum_dt, 1);
+    sum_dt += __shfl_xor(sum_dt, 2);
+    if (p_ok && pq == 0) f.seg_sumdt[(long)seg * f.B * f.D + (long)b * f.D + pd] = sum_dt;
 }
 
 // Turns the segments' local adjoint carries into incoming ones, in place, walking the

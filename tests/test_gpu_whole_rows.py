@@ -1,0 +1,40 @@
+"""Forward passes over whole rows in workgroups of eight waves (at most 256 row groups): numbers of 32-step chunks around the
+four slots of their inputs, lengths of whole slices and others, the edges of a chunk, fewer states, the exact hold; what the backward
+pass takes from them, whole and in segments (whose sums of step sizes it then forms itself); the last grid that they take and the
+first that they do not."""
+import numpy as np
+import pytest
+
+from paper_2312_00752_amd import workloads as wl
+from tests import util
+from tests.test_gpu_ragged import test_ragged_rows
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("io", ["f32", "bf16"])
+@pytest.mark.parametrize("batch,seqlen,dim,dstate,zoh", [
+    (1, 8, 64, 16, False), (2, 32, 70, 16, False), (1, 33, 64, 7, False), (1, 64, 3, 16, True), (1, 72, 66, 2, False), (2, 96, 64, 16, False),
+    (1, 97, 40, 16, True), (1, 104, 130, 12, False), (1, 119, 64, 1, False), (3, 120, 65, 16, True), (1, 127, 64, 16, False),
+    (48, 257, 250, 16, False), (40, 520, 256, 9, False), (64, 136, 193, 16, True), (56, 295, 256, 16, False)])
+def test_whole_rows(io, batch, seqlen, dim, dstate, zoh):
+    test_ragged_rows(io, batch, seqlen, dim, dstate, zoh)
+
+
+@pytest.mark.parametrize("groups", [256, 257])
+@pytest.mark.parametrize("io,seqlen", [("f32", 136), ("bf16", 131)])
+def test_last_grid(io, seqlen, groups):
+    """Bare calls (no gate, no softplus, no skip, nothing lent) on both sides of the line."""
+    import torch
+    from oracle import ss_oracle as orc
+    from paper_2312_00752_amd import binding as B
+    w = wl.make_scan_inputs(groups, seqlen, 20, 16, io=io, seed=groups)
+    w["delta"] = np.abs(w["delta"]) * 0.1
+    if io == "bf16":
+        w["delta"] = torch.from_numpy(w["delta"]).to(torch.bfloat16).float().numpy()
+    g = util.upload(w)
+    out, h_last = B.ss_scan_fwd(g["u"], g["delta"], g["A"], g["B"], g["C"], return_last_state=True)
+    torch.cuda.synchronize()
+    ref = orc.scan_fwd(w["u"], w["delta"], w["A"], w["B"], w["C"])
+    util.assert_close(out, ref["out"], io, "out")
+    util.assert_close(h_last, ref["h_last"], io, "h_last")
