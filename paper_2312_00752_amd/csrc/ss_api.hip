@@ -345,19 +345,20 @@ static bool pitch_ok(const ss_fwd_params* p, int pitch)
 }
 
 // Whether the forward pass goes over whole rows in workgroups of eight waves (launch_fwd_whole), whatever the plan of the backward
-// pass: where every row group has a compute unit of its own and that is less than what the pass in s.nseg segments is modelled to
-// take.  A step of such a workgroup is 0.60 (float: 0.65, its rows are twice the traffic of few units) of one of a workgroup of four waves alone,
-// fitted to 26 lengths x 64 to 256 row groups, forward alone and with the backward pass, of which it misses the faster side by 6 % at most.
-// Forward, us, in segments / whole, bf16: 256 x 2048 201 / 144, 160 x 2048 159 / 141, 128 x 2048 123 / 141, 96 x 512 35.2 / 33.9, unsplit
-// 256 x 64 10.5 / 8.4; with the backward pass: 192 x 2048 523 / 476, exact hold 823 / 757, 160 x 16384 3155 / 3205, float 192 x 2048
-// 559 / 524, 160 x 8192 1844 / 1885.
+// pass: where every row group has a compute unit of its own and that is less than what the pass in nseg segments is modelled to
+// take.  A step of such a workgroup is 0.565 (float, whose other pass is the slower one: 0.53) of one of a workgroup of four waves alone, and
+// it has one set-up, not two (26 lengths x 64 to 256 row groups, forward alone and with the backward pass; of these the line misses the
+// faster side by 3 % at most).  us, in segments / whole, forward alone, bf16: 136 x 4736 292 / 314, 136 x 6000 397 / 411, 136 x 3000 213 / 212, 256 x 2048
+// 201 / 137, 160 x 2048 158 / 135, 128 x 2048 123 / 133, 128 x 512 38.4 / 36.3, unsplit
+// 256 x 64 10.5 / 8.4; with the backward pass: 192 x 2048 522 / 468, exact hold 822 / 754, 160 x 16384 3270 / 3220, 128 x 2047 407 / 412,
+// 128 x 4096 660 / 678, float 192 x 2048 600 / 492, 160 x 8192 1785 / 1660, 128 x 1024 194 / 196.
 static bool runs_whole(const ss_fwd_params* p, int dpp_ok, int nseg, int seg_len)
 {
     const long wgs = (long)p->batch * ((p->dim + 63) / 64), L = p->seqlen;
     if (!dpp_ok || !stageable(p) || slots(p) > 16 || wgs > 256) return false;
     const double split = nseg > 1 ? launch_cost(wgs * nseg, seg_len) + AGG_COST * launch_cost(wgs * (nseg - 1), seg_len)
                                   : launch_cost(wgs, (L + 31) / 32 * 32);
-    return (p->io_dtype == SS_BF16 ? 0.60 : 0.65) * (double)(L + 32) <= split;
+    return (p->io_dtype == SS_BF16 ? 0.565 : 0.53) * (double)L <= split;
 }
 
 static int scan_fwd_impl(const ss_fwd_params* p, long bc_bstride, int pitch, const void* W_dt, int R, const void* rT, void* stream)
@@ -405,7 +406,7 @@ static int scan_fwd_impl(const ss_fwd_params* p, long bc_bstride, int pitch, con
         }
     }
     if (!W_dt && runs_whole(p, a.dpp_ok, a.nseg, a.seg_len)) {
-        a.nseg = 1;
+        if (!(p->flags & SS_SAVE_FOR_BWD)) a.seg_sumdt = nullptr;
         return ss::launch_fwd_whole(a, p->io_dtype, static_cast<hipStream_t>(stream)) == 0 ? SS_OK : SS_ERR_LAUNCH;
     }
     // one pass per group of 16 states; the passes run in stream order and share the segment

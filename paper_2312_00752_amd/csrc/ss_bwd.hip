@@ -1291,54 +1291,34 @@ __global__ void __launch_bounds__(THREADS, 4) adjoint_agg_dpp_kernel(const BwdAr
     constexpr int PF = 2;
     typename pio::raw rd_[PF][PC], rz_[PF][PC], ro_[PF][PC];
     typename io4<T>::raw rc_[PF];
-    // bf16, whole slices: chunks 2i (slot 0) and 2i + 1 (slot 1) are requested together, tensor by tensor, the 128 bytes of a line (see
-    // scan_fwd_kernel; rows of any length lose 1 %).  A float chunk is a whole line (1 x 5001 x 4096, forward + backward, one by one 585 us, in pairs 596).
-    constexpr bool PAIR = sizeof(T) == 2 && !RAG;
-    auto issue = [&](int c0, auto from_tag, auto to_tag) {   // slots from .. to - 1 of the pair c0, c0 + 1
-        constexpr int S0 = decltype(from_tag)::value, S1 = decltype(to_tag)::value;
-        uint32_t off[PF][PC], offc[PF];
+    auto issue_loads = [&](int c, auto slot_tag) {   // chunk c (walking down from c_end - 1) into a compile-time slot
+        constexpr int s = decltype(slot_tag)::value;
+        if constexpr (RAG) {   // before the segment's start: its first chunk again (never used)
+            const int cc = max(c, c_begin) * CHUNK_T;
 #pragma unroll
-        for (int s = S0; s < S1; ++s) {
-            // RAG: before the segment's start or past its end: its first or last chunk again (never used)
-            const int c = RAG ? min(max(c0 + s, c_begin), c_end - 1) : c0 + s, ts = c * CHUNK_T + s_tq * GROUP_T;
-#pragma unroll
-            for (int p = 0; p < PC; ++p) {   // pieces are whole or empty
-                const int t = c * CHUNK_T + p * PSTEP + pq * PE;
-                if constexpr (RAG) off[s][p] = (uint32_t)row_piece(t, PE, L) * esz;
-                else off[s][p] = (t < L && c >= c_begin) ? row_off + (uint32_t)t * esz : BUF_OFF;
+            for (int p = 0; p < PC; ++p) {
+                const uint32_t t = (uint32_t)row_piece(cc + p * PSTEP + pq * PE, PE, L) * esz;
+                rd_[s][p] = pio::load_elem(rd_p, r_off_i + t);
+                ro_[s][p] = pio::load_elem(ro_p, r_off + t);
+                rz_[s][p] = pio::load_elem(rz_p, has_z ? r_off + t : 0u);
             }
-            if constexpr (RAG) offc[s] = r_off_c + (uint32_t)row_piece(ts, GROUP_T, L) * esz;
-            else offc[s] = (ts < L && c >= c_begin) ? c_row_off + (uint32_t)ts * esz : BUF_OFF;
+            rc_[s] = io4<T>::load_elem(rc_p, r_off_c + (uint32_t)row_piece(cc + s_tq * GROUP_T, GROUP_T, L) * esz);
+            return;
         }
-        auto both = [&](typename pio::raw (&r)[PF][PC], const rsrc_t& rs, const T* base, uint32_t row, bool on) {
 #pragma unroll
-            for (int s = S0; s < S1; ++s)
-#pragma unroll
-                for (int p = 0; p < PC; ++p) {
-                    if constexpr (RAG) r[s][p] = pio::load_elem(base, on ? row + off[s][p] : 0u);
-                    else r[s][p] = pio::load_buf(rs, off[s][p]);
-                }
-        };
-        both(rd_, bd_, rd_p, r_off_i, true);
-        both(ro_, bo_, ro_p, r_off, true);
-        both(rz_, bz_, rz_p, r_off, has_z);
-#pragma unroll
-        for (int s = S0; s < S1; ++s) {
-            if constexpr (RAG) rc_[s] = io4<T>::load_elem(rc_p, offc[s]);
-            else rc_[s] = io4<T>::load_buf(bc_, offc[s]);
+        for (int p = 0; p < PC; ++p) {   // pieces are whole or empty
+            const int t = c * CHUNK_T + p * PSTEP + pq * PE;
+            const uint32_t off = (t < L && c >= c_begin) ? row_off + (uint32_t)t * esz : BUF_OFF;
+            rd_[s][p] = pio::load_buf(bd_, off);
+            ro_[s][p] = pio::load_buf(bo_, off);
+            rz_[s][p] = pio::load_buf(bz_, off);
         }
+        const int ts = c * CHUNK_T + s_tq * GROUP_T;
+        rc_[s] = io4<T>::load_buf(bc_, (ts < L && c >= c_begin) ? c_row_off + (uint32_t)ts * esz : BUF_OFF);
     };
-    {
-        const int top = (c_end - 1) & ~1;   // where it is the segment's last chunk, slot 1 is next used below it
-        if constexpr (PAIR) {
-            issue(top, std::integral_constant<int, 0>{}, std::integral_constant<int, PF>{});
-        } else {
-            issue(top, std::integral_constant<int, 0>{}, std::integral_constant<int, 1>{});
-            issue(top + 1 < c_end ? top : top - PF, std::integral_constant<int, 1>{}, std::integral_constant<int, PF>{});
-        }
-    }
+    issue_loads(c_end - 1, std::integral_constant<int, 0>{});
+    issue_loads(c_end - 2, std::integral_constant<int, 1>{});
 
-    float sum_dt = 0.0f;   // this thread's share of the segment's sum of step sizes
     auto do_chunk = [&](const int c, auto slot_tag) {
         constexpr int SLOT = decltype(slot_tag)::value;
         const int t0 = c * CHUNK_T + pq * PE;
@@ -1368,7 +1348,6 @@ __global__ void __launch_bounds__(THREADS, 4) adjoint_agg_dpp_kernel(const BwdAr
                 if (softplus) sp = ss::softplus(sp);
                 if constexpr (RAG) sp = tp + j % PE < L ? sp : 0.0f;
                 dt8[j] = sp;
-                sum_dt += sp;
                 if (has_z) o8[j] *= z8[j] * sigmoid_fast(z8[j]);
             }
             float4* pd4 = reinterpret_cast<float4*>(&s_dt[pr][pq * PE]);
@@ -1383,8 +1362,7 @@ __global__ void __launch_bounds__(THREADS, 4) adjoint_agg_dpp_kernel(const BwdAr
             }
             if (w < 2) *reinterpret_cast<float4*>(&s_c[s_tq][s_n][0]) = make_float4(c4[0], c4[1], c4[2], c4[3]);
         }
-        if constexpr (!PAIR) issue((c & ~1) - PF, slot_tag, std::integral_constant<int, SLOT + 1>{});
-        else if constexpr (SLOT == 0) issue(c - PF, slot_tag, std::integral_constant<int, PF>{});
+        issue_loads(c - PF, slot_tag);
         __syncthreads();
         __builtin_amdgcn_s_setprio(2);   // as in scan_bwd_kernel: the recurrence at a raised wave priority
         float4 dtc[NGC], dyc[NGC], Cpc[NGC];
@@ -1410,18 +1388,14 @@ __global__ void __launch_bounds__(THREADS, 4) adjoint_agg_dpp_kernel(const BwdAr
         __builtin_amdgcn_s_setprio(0);
         __syncthreads();
     };
-    for (int c = (c_end - 1) & ~1; c >= c_begin; c -= PF) {   // segments start at even chunks
-        if (c + 1 < c_end) do_chunk(c + 1, std::integral_constant<int, 1>{});
+    for (int c = c_end - 1; c >= c_begin; c -= PF) {
         do_chunk(c, std::integral_constant<int, 0>{});
+        if (c - 1 >= c_begin) do_chunk(c - 1, std::integral_constant<int, 1>{});
     }
     if (s_ok) {
         float4* dst = reinterpret_cast<float4*>(a.seg_g + ((long)seg * f.B * f.D + srow) * NPAD) + w;
         *dst = make_float4(ag[0], ag[1], ag[2], ag[3]);
     }
-    // what the chain over the segments takes beside (a forward pass over whole rows has not left it)
-    sum_dt += __shfl_xor(sum_dt, 1);
-    sum_dt += __shfl_xor(sum_dt, 2);
-    if (p_ok && pq == 0) f.seg_sumdt[(long)seg * f.B * f.D + (long)b * f.D + pd] = sum_dt;
 }
 
 // Turns the segments' local adjoint carries into incoming ones, in place, walking the

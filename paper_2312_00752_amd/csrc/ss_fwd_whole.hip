@@ -81,9 +81,12 @@ __global__ void __launch_bounds__(WHOLE_THREADS, 2) scan_fwd_whole_kernel(const 
         const T* const rz_p = has_z ? static_cast<const T*>(a.z) + wg_first : ru_p;
         const T* const rbc_p = static_cast<const T*>(s_which ? a.Cm : a.Bm) + (long)b * a.bc_bstride;
 
-        // inputs of chunk c in slot c % 4; what the second half of a chunk's work needs of them again in slot c % 2
+        // inputs of chunk c in slot c % 4; what the second half of a chunk's work takes two chunks later in slot c % 2: u and z as they
+        // came, or, in the kernel that would spill then (float rows of any length, 4 x 3072 x 2047 749 -> 717 us), the skip term and the gate
+        constexpr bool RAW = !(RAG && sizeof(T) == 4);
         constexpr int RING = 4;
         typename pio::raw ru_[RING][PC], rd_[RING][PC], rz_[RING][PC], hu_[2][PC], hz_[2][PC];
+        float skip_[2][SLICE], gate_[2][SLICE];
         typename io4<T>::raw rbc_[RING];
         // chunks c (into slot S) to c + COUNT - 1, tensor by tensor: bf16 by twos, the 128 bytes of a line; past the end the last
         // chunk again (rows of any length) or nothing
@@ -129,6 +132,19 @@ __global__ void __launch_bounds__(WHOLE_THREADS, 2) scan_fwd_whole_kernel(const 
                 else rbc_[S + k] = io4<T>::load_buf(bbc, boff[k]);
             }
         };
+        // this thread's share of the step sizes of a segment: what a backward pass in segments chains them by
+        float sum_dt = 0.0f;
+        float* sum_to = a.seg_sumdt + (long)b * a.D + pd;
+        int sum_end = a.seg_sumdt ? min(a.seg_len, L) : 0x7fffffff;
+        auto leave_sum = [&](int end) {   // the chunk that ends here is prepared
+            if (end < sum_end) return;    // uniform
+            sum_dt += __shfl_xor(sum_dt, 1);
+            sum_dt += __shfl_xor(sum_dt, 2);
+            if (p_ok && pq == 0) *sum_to = sum_dt;
+            sum_dt = 0.0f;
+            sum_to += (long)a.B * a.D;
+            sum_end = sum_end >= L ? 0x7fffffff : min(sum_end + a.seg_len, L);
+        };
         // what the recurrence over chunk c takes, into the tiles of parity S % 2
         auto prepare = [&](const int c, auto slot_tag) {
             constexpr int S = decltype(slot_tag)::value, H = S % 2;
@@ -146,7 +162,7 @@ __global__ void __launch_bounds__(WHOLE_THREADS, 2) scan_fwd_whole_kernel(const 
                     io4<T>::drop(rbc_[S], ts - row_piece(ts, GROUP_T, L));
                 }
             }
-            float bc4[GROUP_T], u8[SLICE], v8[SLICE];
+            float bc4[GROUP_T], u8[SLICE], v8[SLICE], z8[SLICE];
             io4<T>::unpack(rbc_[S], bc4);
             if constexpr (RAG) {   // slots without a state
 #pragma unroll
@@ -155,8 +171,17 @@ __global__ void __launch_bounds__(WHOLE_THREADS, 2) scan_fwd_whole_kernel(const 
             *reinterpret_cast<float4*>(&s_bc[H][s_which][s_tq][s_n][0]) = make_float4(bc4[0], bc4[1], bc4[2], bc4[3]);
             unpack_slice<pio, PC>(ru_[S], u8);
             unpack_slice<pio, PC>(rd_[S], v8);
+            if constexpr (RAW) {
 #pragma unroll
-            for (int p = 0; p < PC; ++p) { hu_[H][p] = ru_[S][p]; hz_[H][p] = rz_[S][p]; }
+                for (int p = 0; p < PC; ++p) { hu_[H][p] = ru_[S][p]; hz_[H][p] = rz_[S][p]; }
+            } else {
+                if (has_z) unpack_slice<pio, PC>(rz_[S], z8);
+#pragma unroll
+                for (int j = 0; j < SLICE; ++j) {
+                    skip_[H][j] = has_D ? Dsk * u8[j] : 0.0f;
+                    gate_[H][j] = has_z ? z8[j] * sigmoid_fast(z8[j]) : 1.0f;
+                }
+            }
             float dt8[SLICE], du8[SLICE];
 #pragma unroll
             for (int j = 0; j < SLICE; ++j) {
@@ -166,6 +191,7 @@ __global__ void __launch_bounds__(WHOLE_THREADS, 2) scan_fwd_whole_kernel(const 
                 if constexpr (RAG) sp = tp + j % PE < L ? sp : 0.0f;
                 dt8[j] = sp;
                 du8[j] = ZOH ? u8[j] : sp * u8[j];
+                sum_dt += sp;
             }
             float4* const pd4 = reinterpret_cast<float4*>(&s_dt[H][pr][pq * PE]);   // four steps each
             float4* const pu4 = reinterpret_cast<float4*>(&s_du[H][pr][pq * PE]);
@@ -180,10 +206,12 @@ __global__ void __launch_bounds__(WHOLE_THREADS, 2) scan_fwd_whole_kernel(const 
             constexpr int H = decltype(parity_tag)::value;
             const int t0 = c * CHUNK_T + pq * PE;
             float u8[SLICE], z8[SLICE], y8[SLICE];
-            unpack_slice<pio, PC>(hu_[H], u8);
-            if (has_z) unpack_slice<pio, PC>(hz_[H], z8);
+            if constexpr (RAW) {
+                unpack_slice<pio, PC>(hu_[H], u8);
+                if (has_z) unpack_slice<pio, PC>(hz_[H], z8);
+            }
 #pragma unroll
-            for (int j = 0; j < SLICE; ++j) y8[j] = has_D ? Dsk * u8[j] : 0.0f;
+            for (int j = 0; j < SLICE; ++j) y8[j] = RAW ? (has_D ? Dsk * u8[j] : 0.0f) : skip_[H][j];
 #pragma unroll
             for (int ww = 0; ww < NWAVES; ++ww) {
                 const float4* const p4 = reinterpret_cast<const float4*>(&s_yp[H][ww][pr][pq * PE]);
@@ -204,7 +232,7 @@ __global__ void __launch_bounds__(WHOLE_THREADS, 2) scan_fwd_whole_kernel(const 
             pack_slice<pio, PC>(y8, py);   // y before the gate, for the backward pass's dz (if kept)
             if (has_z) {
 #pragma unroll
-                for (int j = 0; j < SLICE; ++j) y8[j] *= z8[j] * sigmoid_fast(z8[j]);
+                for (int j = 0; j < SLICE; ++j) y8[j] *= RAW ? z8[j] * sigmoid_fast(z8[j]) : gate_[H][j];
             }
             pack_slice<pio, PC>(y8, po);
             if (H == 0 && c + 1 < chunks) {
@@ -244,23 +272,31 @@ __global__ void __launch_bounds__(WHOLE_THREADS, 2) scan_fwd_whole_kernel(const 
         __builtin_amdgcn_sched_barrier(0);
         prepare(0, std::integral_constant<int, 0>{});
         if constexpr (LOADS == 1) issue(4, std::integral_constant<int, 0>{}, std::integral_constant<int, 1>{});
+        leave_sum(CHUNK_T);
         __syncthreads();
-        // beside the recurrence over chunk i (i % 4 = K)
-        auto beside = [&](const int i, auto k_tag) {
-            constexpr int K = decltype(k_tag)::value, S = (K + 1) % RING;
-            if (i > 0) finish(i - 1, std::integral_constant<int, (K + 1) % 2>{});
-            if (i + 1 < chunks) {
-                prepare(i + 1, std::integral_constant<int, S>{});
-                if constexpr (LOADS == 1) issue(i + 1 + RING, std::integral_constant<int, S>{}, std::integral_constant<int, 1>{});
-                else if constexpr (S % 2 == 1) issue(i + RING, std::integral_constant<int, S - 1>{}, std::integral_constant<int, 2>{});
-            }
+        // Beside the recurrence over chunk i (i % 4 = K).  Nothing of it is conditional, also where chunk i + 1 is past the end (its tiles
+        // are not read): where requests stand behind a branch, their registers are copied at its end, and waited for there.
+        auto next = [&](const int i, auto k_tag) {
+            constexpr int S = (decltype(k_tag)::value + 1) % RING;
+            prepare(i + 1, std::integral_constant<int, S>{});
+            if constexpr (LOADS == 1) issue(i + 1 + RING, std::integral_constant<int, S>{}, std::integral_constant<int, 1>{});
+            else if constexpr (S % 2 == 1) issue(i + RING, std::integral_constant<int, S - 1>{}, std::integral_constant<int, 2>{});
+            leave_sum((i + 2) * CHUNK_T);
             __syncthreads();
         };
-        for (int i = 0; i < chunks; i += RING) {
-            beside(i, std::integral_constant<int, 0>{});
-            if (i + 1 < chunks) beside(i + 1, std::integral_constant<int, 1>{});
-            if (i + 2 < chunks) beside(i + 2, std::integral_constant<int, 2>{});
-            if (i + 3 < chunks) beside(i + 3, std::integral_constant<int, 3>{});
+        auto beside = [&](const int i, auto k_tag) {
+            finish(i - 1, std::integral_constant<int, (decltype(k_tag)::value + 1) % 2>{});
+            next(i, k_tag);
+        };
+        next(0, std::integral_constant<int, 0>{});
+        for (int i = 1; i < chunks; i += RING) {
+            beside(i, std::integral_constant<int, 1>{});
+            if (i + 1 >= chunks) break;
+            beside(i + 1, std::integral_constant<int, 2>{});
+            if (i + 2 >= chunks) break;
+            beside(i + 2, std::integral_constant<int, 3>{});
+            if (i + 3 >= chunks) break;
+            beside(i + 3, std::integral_constant<int, 0>{});
         }
         if (chunks & 1) finish(chunks - 1, std::integral_constant<int, 0>{});
         else finish(chunks - 1, std::integral_constant<int, 1>{});
@@ -379,7 +415,7 @@ static void launch_whole(const FwdArgs& a, hipStream_t stream)
 
 int launch_fwd_whole(const FwdArgs& a, int io_dtype, hipStream_t stream)
 {
-    if (a.L <= 0 || !a.dpp_ok || a.nseg != 1 || a.acc_y) return -1;
+    if (a.L <= 0 || !a.dpp_ok || a.acc_y) return -1;
     if (io_dtype == 0) a.vec_ok ? launch_whole<float, false>(a, stream) : launch_whole<float, true>(a, stream);
     else a.vec_ok ? launch_whole<bf16_t, false>(a, stream) : launch_whole<bf16_t, true>(a, stream);
     return hipGetLastError() == hipSuccess ? 0 : -1;

@@ -114,7 +114,8 @@ struct StepArgs {
 
 // Each returns 0, or -1 if the runtime refused a launch.  io_dtype: 0 = float, 1 = bf16.
 int launch_fwd(const FwdArgs& a, int io_dtype, hipStream_t stream);
-// whole rows in workgroups of eight waves: the common path (dpp_ok, real state, selective B and C), at most 16 states, nseg == 1, steps > 0
+// whole rows in workgroups of eight waves: the common path (dpp_ok, real state, selective B and C), at most 16 states, steps > 0.  Not in
+// segments, but with seg_sumdt the sums of the step sizes of segments of seg_len steps are left there for a backward pass that is.
 int launch_fwd_whole(const FwdArgs& a, int io_dtype, hipStream_t stream);
 // fills the staged copy `bcs` (all NS states) from a.Bm and a.Cm
 int launch_stage_bc(const FwdArgs& a, void* bcs, int io_dtype, hipStream_t stream);

@@ -4,7 +4,7 @@ in the second half of an even and of an odd chunk, in an even and in an odd bloc
 every output, NaN around every input (as for rows of any length)."""
 import pytest
 
-from tests.test_gpu_ragged import test_ragged_rows
+from tests import test_gpu_ragged
 
 pytestmark = pytest.mark.gpu
 
@@ -15,4 +15,4 @@ pytestmark = pytest.mark.gpu
     # split: the last segment ends in either half of an even and of an odd chunk
     (1, 520, 64, 16, False), (1, 536, 100, 16, True), (2, 560, 70, 5, False), (1, 2072, 64, 16, False), (1, 2096, 30, 18, False)])
 def test_float_rows_of_whole_slices(batch, seqlen, dim, dstate, zoh):
-    test_ragged_rows("f32", batch, seqlen, dim, dstate, zoh)
+    test_gpu_ragged.test_ragged_rows("f32", batch, seqlen, dim, dstate, zoh)

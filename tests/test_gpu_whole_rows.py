@@ -7,7 +7,7 @@ import pytest
 
 from paper_2312_00752_amd import workloads as wl
 from tests import util
-from tests.test_gpu_ragged import test_ragged_rows
+from tests import test_gpu_ragged
 
 pytestmark = pytest.mark.gpu
 
@@ -18,7 +18,7 @@ pytestmark = pytest.mark.gpu
     (1, 97, 40, 16, True), (1, 104, 130, 12, False), (1, 119, 64, 1, False), (3, 120, 65, 16, True), (1, 127, 64, 16, False),
     (48, 257, 250, 16, False), (40, 520, 256, 9, False), (64, 136, 193, 16, True), (56, 295, 256, 16, False)])
 def test_whole_rows(io, batch, seqlen, dim, dstate, zoh):
-    test_ragged_rows(io, batch, seqlen, dim, dstate, zoh)
+    test_gpu_ragged.test_ragged_rows(io, batch, seqlen, dim, dstate, zoh)
 
 
 @pytest.mark.parametrize("groups", [256, 257])
