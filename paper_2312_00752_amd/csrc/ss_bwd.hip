@@ -1243,7 +1243,7 @@ __global__ void __launch_bounds__(THREADS, 4) adjoint_agg_dpp_kernel(const BwdAr
     const int c_begin = seg * (f.seg_len / CHUNK_T);
     const int c_end = min((L + CHUNK_T - 1) / CHUNK_T, (seg + 1) * (f.seg_len / CHUNK_T));
 
-    constexpr int PC = slice_pieces<T>(), PE = SLICE / PC, PSTEP = CHUNK_T / PC;   // see scan_fwd_kernel
+    constexpr int PC = slice_pieces<T, RAG>(), PE = SLICE / PC, PSTEP = CHUNK_T / PC;   // see scan_fwd_kernel
     constexpr int HALF4 = PC == 2 ? PSTEP / 4 : 1;
     typedef slice_io<T, PC> pio;
     const int pr = PC == 2 ? pointwise_row_pitch5(tid) : pointwise_row_pitch9(tid), pq = tid & 3;   // TPAD = 36 floats

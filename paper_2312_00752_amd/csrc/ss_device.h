@@ -653,9 +653,10 @@ template <> struct io4<bf16_t> {
 
 // A thread's slice of eight steps of a chunk in the quad-broadcast kernels.  bf16: eight consecutive steps, 16 bytes.  float:
 // four steps from each half of the chunk, so that every access of the four threads of a row covers 64 bytes of it without gaps.
+// Rows of any length gain nothing from it and keep eight steps (layer prefill 1 x 3936 x 4649 342 us, by fours 347).
 // (Eight consecutive steps are two accesses of 16 bytes, 32 apart, to the same lines, and half-filled writes: float32
 // forward + backward 8 x 4096 x 2048 1110 -> 1075 us, 2 x 5120 x 16384 3730 -> 3680, 1 x 256 x 2^20 8670 -> 7830.)
-template <typename T> __host__ __device__ constexpr int slice_pieces() { return sizeof(T) == 4 ? 2 : 1; }
+template <typename T, bool RAG> __host__ __device__ constexpr int slice_pieces() { return sizeof(T) == 4 && !RAG ? 2 : 1; }
 template <typename T, int PC> struct slice_io : io8<T> {};
 template <> struct slice_io<float, 2> : io4<float> {};
 template <typename IO, int PC>

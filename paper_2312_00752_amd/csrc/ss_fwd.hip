@@ -93,7 +93,7 @@ __global__ void __launch_bounds__(THREADS, PAT && AGG ? 4 : ((PAT && FUSED_KS <=
 
     // ---- pointwise view: thread -> (row pr, slice pq) -----------------------------------
     // A slice is PC pieces of PE consecutive steps, one 16-byte access each (float off the quad-broadcast kernels: two)
-    constexpr int PC = PAT ? slice_pieces<T>() : 1, PE = SLICE / PC, PSTEP = CHUNK_T / PC;
+    constexpr int PC = PAT ? slice_pieces<T, RAG>() : 1, PE = SLICE / PC, PSTEP = CHUNK_T / PC;
     constexpr int HALF4 = PC == 2 ? PSTEP / 4 : 1;   // float4s from a slice's first four steps to its last four
     typedef slice_io<T, PC> pio;
     const int pr = PC == 2 ? pointwise_row_pitch5(tid) : pointwise_row_pitch9(tid), pq = tid & 3;   // TPAD = 36 floats

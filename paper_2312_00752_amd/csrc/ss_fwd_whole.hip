@@ -48,7 +48,8 @@ __global__ void __launch_bounds__(WHOLE_THREADS, 2) scan_fwd_whole_kernel(const 
     if (pointwise) {
         const bool has_z = a.flags & F_HAS_Z, has_D = a.flags & F_HAS_D, softplus = a.flags & F_DELTA_SOFTPLUS;
         const bool keep_y = has_z && a.ysave;
-        constexpr int PC = slice_pieces<T>(), PE = SLICE / PC, PSTEP = CHUNK_T / PC, HALF4 = PC == 2 ? PSTEP / 4 : 1;
+        // by fours in rows of any length as well: 8 x 1536 x 2047 forward + backward 742 us, by eights 795 (spills)
+        constexpr int PC = slice_pieces<T, false>(), PE = SLICE / PC, PSTEP = CHUNK_T / PC, HALF4 = PC == 2 ? PSTEP / 4 : 1;
         typedef slice_io<T, PC> pio;
         const uint32_t esz = (uint32_t)sizeof(T);
         const int pr = PC == 2 ? pointwise_row_pitch5(tid) : pointwise_row_pitch9(tid), pq = tid & 3;
