@@ -3,6 +3,7 @@
 
 #include <atomic>
 
+#include "ss_device.h"
 #include "ss_kernels.h"
 #include "ss_layer.h"
 #include "ss_scan.h"
@@ -346,19 +347,32 @@ static bool pitch_ok(const ss_fwd_params* p, int pitch)
 
 // Whether the forward pass goes over whole rows in workgroups of eight waves (launch_fwd_whole), whatever the plan of the backward
 // pass: where every row group has a compute unit of its own and that is less than what the pass in nseg segments is modelled to
-// take.  A step of such a workgroup is 0.565 (float, whose other pass is the slower one: 0.53) of one of a workgroup of four waves alone, and
-// it has one set-up, not two (26 lengths x 64 to 256 row groups, forward alone and with the backward pass; of these the line misses the
-// faster side by 3 % at most).  us, in segments / whole, forward alone, bf16: 136 x 4736 292 / 314, 136 x 6000 397 / 411, 136 x 3000 213 / 212, 256 x 2048
-// 201 / 137, 160 x 2048 158 / 135, 128 x 2048 123 / 133, 128 x 512 38.4 / 36.3, unsplit
-// 256 x 64 10.5 / 8.4; with the backward pass: 192 x 2048 522 / 468, exact hold 822 / 754, 160 x 16384 3270 / 3220, 128 x 2047 407 / 412,
-// 128 x 4096 660 / 678, float 192 x 2048 600 / 492, 160 x 8192 1785 / 1660, 128 x 1024 194 / 196.
-static bool runs_whole(const ss_fwd_params* p, int dpp_ok, int nseg, int seg_len)
+// take.  In steps of a workgroup of four waves alone, a whole row is `step` per step and `fixed` more, fitted for what differs
+// between the kernels: the rule, the dtype and, in bf16, the slots per lane (with fewer the four waves are done sooner, the
+// pointwise waves here are not).  Measured: 1 to 256 row groups x 32 to 16384 steps, on and off eight steps, N = 1, 4, 8, 16 and the
+// exact hold, forward alone and with the backward pass; profiles/whole_rows_line.txt has both sides of every point.  Where the line
+// sends a call whole that is faster in segments, that costs 2.5 % at most, float rows of up to four states 6 % (136 x 3072).
+// us, in segments / whole, forward alone.  Sent whole: 192 x 2048 N = 16 bf16 182 / 135, float 189 / 135, exact hold 304 / 234, N = 4 bf16
+// 112 / 95; 160 x 16384 bf16 1106 / 1029; float 160 x 8192 621 / 512.  Kept in segments: 128 x 2048 bf16 126 / 134, N = 4 160 x 16384
+// 664 / 729, 136 x 3072 134 / 147, N = 8 157 / 162; exact hold, float 80 x 320 34.3 / 40.6, bf16 1 x 192 23.4 / 24.9.  With the backward pass:
+// 192 x 2048 520 / 465, exact hold 819 / 751, 160 x 16384 3199 / 3076, N = 4 2170 / 2232, 128 x 2048 352 / 354, float 192 x 2048 560 / 491.
+static bool runs_whole(const ss_fwd_params* p, const ss::FwdArgs& a)
 {
     const long wgs = (long)p->batch * ((p->dim + 63) / 64), L = p->seqlen;
-    if (!dpp_ok || !stageable(p) || slots(p) > 16 || wgs > 256) return false;
-    const double split = nseg > 1 ? launch_cost(wgs * nseg, seg_len) + AGG_COST * launch_cost(wgs * (nseg - 1), seg_len)
-                                  : launch_cost(wgs, (L + 31) / 32 * 32);
-    return (p->io_dtype == SS_BF16 ? 0.565 : 0.53) * (double)L <= split;
+    if (!a.dpp_ok || !stageable(p) || slots(p) > 16 || wgs > 256) return false;
+    const int spl = ss::slots_for(a.N, a.il);
+    // not split: beside a second chunk always (256 x 64 9.3 / 7.9 us); a single one has nothing to run beside, which shows with one slot
+    // per lane (192 x 32 bf16 4.74 / 4.87, float 5.19 / 5.41; two slots bf16 5.27 / 5.14)
+    if (a.nseg == 1) return spl > 1 || L > 32;
+    double step = 0.48, fixed = 32.0;   // float
+    if (p->flags & SS_EXACT_ZOH_B) {
+        step = 0.535;
+        fixed = 48.0;
+    } else if (p->io_dtype == SS_BF16) {
+        step = spl == 1 ? 0.605 : (spl == 2 ? 0.59 : 0.55);
+        fixed = spl == 2 ? -12.0 : 0.0;
+    }
+    return step * (double)L + fixed <= launch_cost(wgs * a.nseg, a.seg_len) + AGG_COST * launch_cost(wgs * (a.nseg - 1), a.seg_len);
 }
 
 static int scan_fwd_impl(const ss_fwd_params* p, long bc_bstride, int pitch, const void* W_dt, int R, const void* rT, void* stream)
@@ -405,7 +419,7 @@ static int scan_fwd_impl(const ss_fwd_params* p, long bc_bstride, int pitch, con
             a.seg_sumdt = reinterpret_cast<float*>(ws + w.segdt_off);
         }
     }
-    if (!W_dt && runs_whole(p, a.dpp_ok, a.nseg, a.seg_len)) {
+    if (!W_dt && runs_whole(p, a)) {
         if (!(p->flags & SS_SAVE_FOR_BWD)) a.seg_sumdt = nullptr;
         return ss::launch_fwd_whole(a, p->io_dtype, static_cast<hipStream_t>(stream)) == 0 ? SS_OK : SS_ERR_LAUNCH;
     }

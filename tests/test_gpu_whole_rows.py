@@ -38,3 +38,18 @@ def test_last_grid(io, seqlen, groups):
     ref = orc.scan_fwd(w["u"], w["delta"], w["A"], w["B"], w["C"])
     util.assert_close(out, ref["out"], io, "out")
     util.assert_close(h_last, ref["h_last"], io, "h_last")
+
+
+# with few states the four-wave kernels are done sooner, and short segments of the exact hold cost less than they are modelled to
+@pytest.mark.parametrize("io,groups,seqlen,dstate,zoh", [
+    ("bf16", 136, 3072, 4, False), ("bf16", 136, 3072, 8, False), ("f32", 1, 192, 16, True), ("bf16", 8, 192, 3, True), ("f32", 80, 320, 16, True),
+    ("f32", 80, 320, 4, False), ("bf16", 1, 2048, 16, False)])
+def test_faster_in_segments(io, groups, seqlen, dstate, zoh):
+    assert util.in_segments(io, 1, seqlen, 64 * groups, dstate, zoh)
+
+
+@pytest.mark.parametrize("io,groups,seqlen,dstate,zoh", [
+    ("bf16", 136, 3072, 16, False), ("bf16", 160, 1536, 4, False), ("bf16", 160, 1536, 8, False), ("f32", 1, 192, 16, False), ("f32", 144, 320, 16, True),
+    ("f32", 104, 320, 4, False)])
+def test_faster_whole(io, groups, seqlen, dstate, zoh):
+    assert not util.in_segments(io, 1, seqlen, 64 * groups, dstate, zoh)

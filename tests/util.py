@@ -95,3 +95,16 @@ def assert_close(got, ref, io, name, exact_inputs=True, elem_floor=None):
     ee = elem_err(got, ref, floor)
     assert ee <= tol, "%s: element-wise error %.3e (of |ref| + %.2f max|ref|) exceeds %.1e" % (name, ee, floor, tol)
     return e
+
+
+def in_segments(io, batch, seqlen, dim, dstate, zoh=False):
+    """Whether a forward call that is lent scratch goes over segments: those leave their states there, whole rows nothing."""
+    import torch
+    from paper_2312_00752_amd import binding as B
+    tio, code = (torch.bfloat16, B.SS_BF16) if io == "bf16" else (torch.float32, B.SS_F32)
+    u = torch.zeros(batch, dim, seqlen, dtype=tio, device="cuda")
+    bc = torch.zeros(batch, dstate, seqlen, dtype=tio, device="cuda")
+    A = torch.full((dim, dstate), -1.0, device="cuda")
+    ws = torch.full((B.ss_workspace_bytes(batch, dim, seqlen, dstate, False, code, False),), 0x5a, dtype=torch.uint8, device="cuda")
+    B.ss_scan_fwd(u, u, A, bc, bc, delta_softplus=True, workspace=ws, save_for_bwd=False, exact_zoh=zoh)
+    return bool((ws != 0x5a).any())
