@@ -60,7 +60,8 @@ typedef struct {
 } ss_layer_params;
 
 /* Sizes of the two buffers; only the shape fields and io_dtype are read.  for_backward
- * selects the scratch size of ss_layer_bwd (larger) or of ss_layer_fwd. */
+ * selects the scratch size of ss_layer_bwd (the larger one but for widths of a few tens at most)
+ * or of ss_layer_fwd; one buffer for both takes the larger. */
 size_t ss_layer_saved_bytes(const ss_layer_params *p);
 size_t ss_layer_scratch_bytes(const ss_layer_params *p, int for_backward);
 
