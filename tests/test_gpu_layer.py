@@ -211,3 +211,12 @@ def test_ranks_on_both_sides_of_the_projection_in_the_scan(shape):
 def test_odd_lengths_in_bf16(shape):
     batch, seqlen, dim, dstate, rank = shape
     _check(make_layer_inputs(batch, seqlen, dim, dstate, "bf16", seed=seqlen + 3, rank=rank), fill=0xff)   # NaN in the space between the rows
+
+
+@pytest.mark.parametrize("shape", [(96, 583, 65, 16, 8), (192, 1283, 40, 9, 3), (144, 779, 33, 4, 2)])
+def test_odd_lengths_in_bf16_whole_forward_backward_in_segments(shape):
+    """Rows of the layer's own pitch over whole rows, which leave the sums of the step sizes of the backward pass's five or seven segments."""
+    from tests import util
+    batch, seqlen, dim, dstate, rank = shape
+    assert not util.in_segments("bf16", batch, seqlen, dim, dstate)
+    _check(make_layer_inputs(batch, seqlen, dim, dstate, "bf16", seed=seqlen + 3, rank=rank), fill=0xff)

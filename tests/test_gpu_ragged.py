@@ -84,8 +84,29 @@ def _segments(batch, seqlen, dim, dstate):
     (2, 1, 193, 70, 16, False), (2, 1, 197, 40, 4, False), (3, 1, 257, 65, 16, True), (5, 1, 513, 40, 3, False),
     (6, 2, 699, 33, 18, False), (9, 1, 1025, 70, 16, True), (16, 1, 1985, 70, 16, False), (16, 3, 1937, 130, 7, False)])
 def test_ragged_rows_in_few_segments(io, segments, batch, seqlen, dim, dstate, zoh):
-    """Up to sixteen segments every workgroup works its incoming state out itself: one, several and all fifteen aggregates."""
+    """Up to sixteen segments every workgroup works its incoming state out itself: one, several and all fifteen aggregates.  (The
+    forward pass of the shapes in two or three segments goes over whole rows; those below are its own.)"""
     assert _segments(batch, seqlen, dim, dstate) == segments
+    test_ragged_rows(io, batch, seqlen, dim, dstate, zoh)
+
+
+@pytest.mark.parametrize("io", ["f32", "bf16"])
+@pytest.mark.parametrize("segments,batch,seqlen,dim,dstate,zoh", [
+    # more than 16 states, the exact hold in short segments, more than 256 row groups
+    (2, 1, 193, 70, 18, False), (2, 1, 200, 40, 20, False), (3, 1, 192, 66, 16, True), (3, 1, 192, 40, 5, True),
+    (3, 320, 904, 2, 16, False), (3, 320, 907, 1, 7, False), (3, 320, 905, 2, 3, True)])
+def test_few_segments_of_the_forward_pass(io, segments, batch, seqlen, dim, dstate, zoh):
+    assert _segments(batch, seqlen, dim, dstate) == segments and util.in_segments(io, batch, seqlen, dim, dstate, zoh)
+    test_ragged_rows(io, batch, seqlen, dim, dstate, zoh)
+
+
+@pytest.mark.parametrize("io", ["f32", "bf16"])
+@pytest.mark.parametrize("batch,seqlen,dim,dstate,zoh", [
+    (257, 8, 2, 16, False), (257, 9, 2, 3, False), (130, 33, 65, 16, False), (257, 40, 3, 4, False), (257, 47, 1, 7, True), (257, 63, 2, 16, False),
+    (257, 88, 2, 6, True), (257, 95, 3, 2, False), (257, 97, 1, 8, False), (260, 104, 2, 16, True), (129, 123, 66, 13, False)])
+def test_rows_of_more_groups_than_units(io, batch, seqlen, dim, dstate, zoh):
+    """More than 256 row groups, unsplit: the four-wave forward kernel with one, two and four slots per lane and the exact hold, on and
+    off eight steps, ending in an even and in an odd chunk."""
     test_ragged_rows(io, batch, seqlen, dim, dstate, zoh)
 
 

@@ -1,7 +1,7 @@
 """Forward passes over whole rows in workgroups of eight waves (at most 256 row groups): numbers of 32-step chunks around the
 four slots of their inputs, lengths of whole slices and others, the edges of a chunk, fewer states, the exact hold; what the backward
-pass takes from them, whole and in segments (whose sums of step sizes it then forms itself); the last grid that they take and the
-first that they do not."""
+pass takes from them, whole and in segments (the sums of whose step sizes they leave); the last grid that they take and the
+first that they do not; calls on both sides of the line."""
 import numpy as np
 import pytest
 
@@ -18,6 +18,16 @@ pytestmark = pytest.mark.gpu
     (1, 97, 40, 16, True), (1, 104, 130, 12, False), (1, 119, 64, 1, False), (3, 120, 65, 16, True), (1, 127, 64, 16, False),
     (48, 257, 250, 16, False), (40, 520, 256, 9, False), (64, 136, 193, 16, True), (56, 295, 256, 16, False)])
 def test_whole_rows(io, batch, seqlen, dim, dstate, zoh):
+    test_gpu_ragged.test_ragged_rows(io, batch, seqlen, dim, dstate, zoh)
+
+
+@pytest.mark.parametrize("io", ["f32", "bf16"])
+@pytest.mark.parametrize("segments,batch,seqlen,dim,dstate,zoh", [
+    (5, 96, 583, 65, 16, False), (5, 192, 584, 2, 7, False), (7, 192, 1283, 1, 16, True), (7, 144, 779, 3, 16, False), (7, 192, 1344, 2, 16, False),
+    (5, 176, 777, 1, 4, False), (3, 160, 777, 2, 12, True)])
+def test_sums_of_segments(io, segments, batch, seqlen, dim, dstate, zoh):
+    """Whole forward, backward in several segments, the last of them shorter or as long: each reads the sums of the others' step sizes."""
+    assert test_gpu_ragged._segments(batch, seqlen, dim, dstate) == segments and not util.in_segments(io, batch, seqlen, dim, dstate, zoh)
     test_gpu_ragged.test_ragged_rows(io, batch, seqlen, dim, dstate, zoh)
 
 
