@@ -1246,6 +1246,7 @@ __global__ void __launch_bounds__(THREADS, 4) adjoint_agg_dpp_kernel(const BwdAr
     constexpr int PC = slice_pieces<T, RAG>(), PE = SLICE / PC, PSTEP = CHUNK_T / PC;   // see scan_fwd_kernel
     constexpr int HALF4 = PC == 2 ? PSTEP / 4 : 1;
     typedef slice_io<T, PC> pio;
+    static_assert(!RAG || PC == 1, "rows of any length: a slice is one piece");
     const int pr = PC == 2 ? pointwise_row_pitch5(tid) : pointwise_row_pitch9(tid), pq = tid & 3;   // TPAD = 36 floats
     const bool p_ok = d0 + pr < f.D;
     const int pd = p_ok ? d0 + pr : f.D - 1;
@@ -1295,13 +1296,10 @@ __global__ void __launch_bounds__(THREADS, 4) adjoint_agg_dpp_kernel(const BwdAr
         constexpr int s = decltype(slot_tag)::value;
         if constexpr (RAG) {   // before the segment's start: its first chunk again (never used)
             const int cc = max(c, c_begin) * CHUNK_T;
-#pragma unroll
-            for (int p = 0; p < PC; ++p) {
-                const uint32_t t = (uint32_t)row_piece(cc + p * PSTEP + pq * PE, PE, L) * esz;
-                rd_[s][p] = pio::load_elem(rd_p, r_off_i + t);
-                ro_[s][p] = pio::load_elem(ro_p, r_off + t);
-                rz_[s][p] = pio::load_elem(rz_p, has_z ? r_off + t : 0u);
-            }
+            const uint32_t t = (uint32_t)row_piece(cc + pq * SLICE, SLICE, L) * esz;
+            rd_[s][0] = pio::load_elem(rd_p, r_off_i + t);
+            ro_[s][0] = pio::load_elem(ro_p, r_off + t);
+            rz_[s][0] = pio::load_elem(rz_p, has_z ? r_off + t : 0u);
             rc_[s] = io4<T>::load_elem(rc_p, r_off_c + (uint32_t)row_piece(cc + s_tq * GROUP_T, GROUP_T, L) * esz);
             return;
         }
@@ -1326,14 +1324,10 @@ __global__ void __launch_bounds__(THREADS, 4) adjoint_agg_dpp_kernel(const BwdAr
             float v8[SLICE], o8[SLICE], z8[SLICE], dt8[SLICE], c4[GROUP_T];
             if constexpr (RAG) {
                 if ((c + 1) * CHUNK_T > L) {   // uniform
-                    const int ts = c * CHUNK_T + s_tq * GROUP_T;
-#pragma unroll
-                    for (int p = 0; p < PC; ++p) {
-                        const int t = t0 + p * PSTEP, sh = t - row_piece(t, PE, L);
-                        pio::drop(rd_[SLOT][p], sh);
-                        pio::drop(ro_[SLOT][p], sh);
-                        pio::drop(rz_[SLOT][p], sh);
-                    }
+                    const int sh = t0 - row_piece(t0, SLICE, L), ts = c * CHUNK_T + s_tq * GROUP_T;
+                    pio::drop(rd_[SLOT][0], sh);
+                    pio::drop(ro_[SLOT][0], sh);
+                    pio::drop(rz_[SLOT][0], sh);
                     io4<T>::drop(rc_[SLOT], ts - row_piece(ts, GROUP_T, L));
                 }
             }

@@ -92,10 +92,11 @@ __global__ void __launch_bounds__(THREADS, PAT && AGG ? 4 : ((PAT && FUSED_KS <=
     const int c_end = min((L + CHUNK_T - 1) / CHUNK_T, (seg + 1) * (a.seg_len / CHUNK_T));
 
     // ---- pointwise view: thread -> (row pr, slice pq) -----------------------------------
-    // A slice is PC pieces of PE consecutive steps, one 16-byte access each (float off the quad-broadcast kernels: two)
+    // A slice is PC pieces of PE consecutive steps, one 16-byte access each (float with PC = 1, rows of any length and off the quad-broadcast kernels: two)
     constexpr int PC = PAT ? slice_pieces<T, RAG>() : 1, PE = SLICE / PC, PSTEP = CHUNK_T / PC;
     constexpr int HALF4 = PC == 2 ? PSTEP / 4 : 1;   // float4s from a slice's first four steps to its last four
     typedef slice_io<T, PC> pio;
+    static_assert(!RAG || PC == 1, "rows of any length: a slice is one piece");
     const int pr = PC == 2 ? pointwise_row_pitch5(tid) : pointwise_row_pitch9(tid), pq = tid & 3;   // TPAD = 36 floats
     const bool p_ok = d0 + pr < a.D;
     const int pd = p_ok ? d0 + pr : a.D - 1;  // out-of-range rows shadow the last row; stores masked
@@ -235,15 +236,12 @@ __global__ void __launch_bounds__(THREADS, PAT && AGG ? 4 : ((PAT && FUSED_KS <=
         constexpr int s = decltype(slot_tag)::value;
         if constexpr (RAG) {   // past the segment's end: its last chunk again (never used)
             const int cc = min(c, c_end - 1) * CHUNK_T;
-#pragma unroll
-            for (int p = 0; p < PC; ++p) {
-                const uint32_t t = (uint32_t)row_piece(cc + p * PSTEP + pq * PE, PE, L) * esz;
-                ru_[s][p] = pio::load_elem(ru_p, r_off_i + t);
-                if constexpr (FUSED_KS == 0) rd_[s][p] = pio::load_elem(rd_p, r_off_i + t);
-                if constexpr (!AGG) {
-                    rz_[s][p] = pio::load_elem(rz_p, has_z ? r_off + t : 0u);
-                    rp_[s][p] = pio::load_elem(rp_p, acc_on ? r_off_p + t : 0u);
-                }
+            const uint32_t t = (uint32_t)row_piece(cc + pq * SLICE, SLICE, L) * esz;
+            ru_[s][0] = pio::load_elem(ru_p, r_off_i + t);
+            if constexpr (FUSED_KS == 0) rd_[s][0] = pio::load_elem(rd_p, r_off_i + t);
+            if constexpr (!AGG) {
+                rz_[s][0] = pio::load_elem(rz_p, has_z ? r_off + t : 0u);
+                rp_[s][0] = pio::load_elem(rp_p, acc_on ? r_off_p + t : 0u);
             }
             rbc_[s] = io4<T>::load_elem(rbc_p, r_off_bc + (uint32_t)row_piece(cc + s_tq * GROUP_T, GROUP_T, L) * esz);
         } else if constexpr (VEC) {   // pieces are whole or empty
@@ -394,15 +392,11 @@ __global__ void __launch_bounds__(THREADS, PAT && AGG ? 4 : ((PAT && FUSED_KS <=
         typename io4<T>::raw rbc = rbc_[SLOT];
         if constexpr (RAG) {
             if (tc + CHUNK_T > L) {   // uniform: the last chunk of a row that does not fill it
-                const int ts = tc + s_tq * GROUP_T;
-#pragma unroll
-                for (int p = 0; p < PC; ++p) {
-                    const int t = t0 + p * PSTEP, sh = t - row_piece(t, PE, L);
-                    pio::drop(ru[p], sh);
-                    if constexpr (FUSED_KS == 0) pio::drop(rd[p], sh);
-                    if constexpr (!AGG) pio::drop(rz[p], sh);
-                    if (acc_on) pio::drop(rp_[SLOT][p], sh);
-                }
+                const int sh = t0 - row_piece(t0, SLICE, L), ts = tc + s_tq * GROUP_T;
+                pio::drop(ru[0], sh);
+                if constexpr (FUSED_KS == 0) pio::drop(rd[0], sh);
+                if constexpr (!AGG) pio::drop(rz[0], sh);
+                if (acc_on) pio::drop(rp_[SLOT][0], sh);
                 io4<T>::drop(rbc, ts - row_piece(ts, GROUP_T, L));
             }
         }
@@ -674,20 +668,10 @@ __global__ void __launch_bounds__(THREADS, PAT && AGG ? 4 : ((PAT && FUSED_KS <=
                         T* const yp = static_cast<T*>(a.ysave) + wg_first_i;
                         T* const op = static_cast<T*>(a.out) + wg_first;
                         const uint32_t yt = r_off_i + (uint32_t)t0 * esz, ot = r_off + (uint32_t)t0 * esz;
-                        if (SLOT == 1) {
-#pragma unroll
-                            for (int p = 0; p < PC; ++p)
-                                if (keep_y) pio::store_elem(yp, yt + (uint32_t)(p * PSTEP - CHUNK_T) * esz, held_y[p], PE);
-                        }
-#pragma unroll
-                        for (int p = 0; p < PC; ++p)
-                            if (keep_y) pio::store_elem(yp, yt + (uint32_t)(p * PSTEP) * esz, py[p], nv[p]);
-                        if (SLOT == 1) {
-#pragma unroll
-                            for (int p = 0; p < PC; ++p) pio::store_elem(op, ot + (uint32_t)(p * PSTEP - CHUNK_T) * esz, held_o[p], PE);
-                        }
-#pragma unroll
-                        for (int p = 0; p < PC; ++p) pio::store_elem(op, ot + (uint32_t)(p * PSTEP) * esz, po[p], nv[p]);
+                        if (SLOT == 1 && keep_y) pio::store_elem(yp, yt - CHUNK_T * esz, held_y[0], SLICE);
+                        if (keep_y) pio::store_elem(yp, yt, py[0], nv[0]);
+                        if (SLOT == 1) pio::store_elem(op, ot - CHUNK_T * esz, held_o[0], SLICE);
+                        pio::store_elem(op, ot, po[0], nv[0]);
                     }
                 } else {
 #pragma unroll
