@@ -1335,12 +1335,15 @@ __global__ void __launch_bounds__(THREADS, 4) adjoint_agg_dpp_kernel(const BwdAr
             unpack_slice<pio, PC>(ro_[SLOT], o8);
             if (has_z) unpack_slice<pio, PC>(rz_[SLOT], z8);
             io4<T>::unpack(rc_[SLOT], c4);
+            float bias_e[PC];   // an empty piece runs with dt = 0
+#pragma unroll
+            for (int p = 0; p < PC; ++p) bias_e[p] = p_ok && t0 + p * PSTEP < L ? bias : (softplus ? -1e30f : 0.0f);
+            const int nv = min(max(L - t0, 0), SLICE);
 #pragma unroll
             for (int j = 0; j < SLICE; ++j) {
-                const int tp = t0 + j / PE * PSTEP;   // an empty piece runs with dt = 0
-                float sp = v8[j] + (p_ok && tp < L ? bias : (softplus ? -1e30f : 0.0f));
+                float sp = v8[j] + bias_e[j / PE];
                 if (softplus) sp = ss::softplus(sp);
-                if constexpr (RAG) sp = tp + j % PE < L ? sp : 0.0f;
+                if constexpr (RAG) sp = j < nv ? sp : 0.0f;
                 dt8[j] = sp;
                 if (has_z) o8[j] *= z8[j] * sigmoid_fast(z8[j]);
             }

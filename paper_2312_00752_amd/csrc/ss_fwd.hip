@@ -430,10 +430,12 @@ __global__ void __launch_bounds__(THREADS, PAT && AGG ? 4 : ((PAT && FUSED_KS <=
             // zeros; a bias of -1e30 (0 without softplus) then makes its step sizes exactly 0, the identity of
             // the recurrence, without a select per element
             constexpr bool ZERO_BY_BIAS = PAT && FUSED_KS == 0 && !RAG;
+            float bias_e[PC];   // selected here: inside the loop the select is made again in front of every softplus
+#pragma unroll
+            for (int p = 0; p < PC; ++p) bias_e[p] = !ZERO_BY_BIAS || nv[p] == PE ? bias : (softplus ? -1e30f : 0.0f);
 #pragma unroll
             for (int j = 0; j < SLICE; ++j) {
-                const float bias_e = !ZERO_BY_BIAS || nv[j / PE] == PE ? bias : (softplus ? -1e30f : 0.0f);
-                float sp = v8[j] + bias_e;
+                float sp = v8[j] + bias_e[j / PE];
                 if (softplus) sp = ss::softplus(sp);
                 if constexpr (!ZERO_BY_BIAS) sp = (j % PE < nv[j / PE]) ? sp : 0.0f;
                 dt8[j] = sp;

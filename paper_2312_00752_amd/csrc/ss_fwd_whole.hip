@@ -183,13 +183,14 @@ __global__ void __launch_bounds__(WHOLE_THREADS, 2) scan_fwd_whole_kernel(const 
                     gate_[H][j] = has_z ? z8[j] * sigmoid_fast(z8[j]) : 1.0f;
                 }
             }
-            float dt8[SLICE], du8[SLICE];
+            float dt8[SLICE], du8[SLICE], bias_e[PC];   // an empty piece runs with dt = 0
+#pragma unroll
+            for (int p = 0; p < PC; ++p) bias_e[p] = RAG || t0 + p * PSTEP < L ? bias : (softplus ? -1e30f : 0.0f);
 #pragma unroll
             for (int j = 0; j < SLICE; ++j) {
-                const int tp = t0 + j / PE * PSTEP;   // an empty piece runs with dt = 0
-                float sp = v8[j] + (RAG || tp < L ? bias : (softplus ? -1e30f : 0.0f));
+                float sp = v8[j] + bias_e[j / PE];
                 if (softplus) sp = ss::softplus(sp);
-                if constexpr (RAG) sp = tp + j % PE < L ? sp : 0.0f;
+                if constexpr (RAG) sp = t0 + j / PE * PSTEP + j % PE < L ? sp : 0.0f;
                 dt8[j] = sp;
                 du8[j] = ZOH ? u8[j] : sp * u8[j];
                 sum_dt += sp;
