@@ -626,8 +626,8 @@ struct BwdSmemDpp {
 struct BwdSmemDppKept : BwdSmemDpp {
     float4 kept[3][THREADS];
 };
-template <typename T, bool ZOH, bool RAG> constexpr bool kept_in_lds() { return sizeof(T) == 4 && (ZOH || RAG); }
-template <typename T, bool ZOH, bool RAG> using bwd_smem_dpp = typename std::conditional<kept_in_lds<T, ZOH, RAG>(), BwdSmemDppKept, BwdSmemDpp>::type;
+template <typename T, bool ZOH, bool RAG, bool WAIT> constexpr bool kept_in_lds() { return WAIT && sizeof(T) == 4 && (ZOH || RAG); }
+template <typename T, bool ZOH, bool RAG, bool WAIT> using bwd_smem_dpp = typename std::conditional<kept_in_lds<T, ZOH, RAG, WAIT>(), BwdSmemDppKept, BwdSmemDpp>::type;
 
 // SPL: slots per lane the state phases are built for (see scan_fwd_kernel).
 // ZOH: the exact zero-order-hold B-bar of Eq. 4, b = phi B u with phi = (abar - 1)/A.  The LDS tile that
@@ -641,11 +641,11 @@ template <typename T, bool ZOH, bool RAG> using bwd_smem_dpp = typename std::con
 // and 361 registers, 533 us with two and 256.)
 // RAG: rows of any length >= 8 (see scan_fwd_kernel).  Slices are read at element alignment from
 // inside the row and shifted into place, and rows past D cleared, in the blocks that need it only.
-template <typename T, int SPL, bool ZOH = false, bool RAG = false>
+template <typename T, int SPL, bool ZOH = false, bool RAG = false, bool WAIT = true>
 __global__ void __launch_bounds__(THREADS, 2) scan_bwd_dpp_kernel(const BwdArgs a)
 {
     extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
-    bwd_smem_dpp<T, ZOH, RAG>& sm = *reinterpret_cast<bwd_smem_dpp<T, ZOH, RAG>*>(smem_raw);
+    bwd_smem_dpp<T, ZOH, RAG, WAIT>& sm = *reinterpret_cast<bwd_smem_dpp<T, ZOH, RAG, WAIT>*>(smem_raw);
 
     const FwdArgs& f = a.f;
     const int tid = threadIdx.x;
@@ -784,7 +784,7 @@ __global__ void __launch_bounds__(THREADS, 2) scan_bwd_dpp_kernel(const BwdArgs 
     };
     // Stores likewise: a block is 32 bytes of a bf16 row, 64 of a float one, so the results of an odd block wait for the even block below
     // it (segments start at even blocks) and the two pieces of the 64 or 128 bytes are written back to back, from registers or
-    // (kept_in_lds) LDS.  float32, forward + backward, us, the pairs alone: 8 x 4096 x 2048 1075 -> 1012, with 4 states
+    // (kept_in_lds) LDS; float results where that pays (WAIT, see choose_waits).  float32, forward + backward, us, the pairs alone: 8 x 4096 x 2048 1075 -> 1012, with 4 states
     // 1078 -> 926, 1 x 256 x 2^20 7830 -> 7480, 2 x 5120 x 16383 4758 -> 4427 (in registers 4485).
     typename io4<T>::packed keep_du{}, keep_dl{}, keep_dz{};
     uint32_t keep_off = BUF_OFF;
@@ -797,7 +797,9 @@ __global__ void __launch_bounds__(THREADS, 2) scan_bwd_dpp_kernel(const BwdArgs 
             if (base && nv > 0) io4<T>::store_elem(static_cast<T*>(base), off + more, now, nv);
             return;
         }
-        if constexpr (kept_in_lds<T, ZOH, RAG>()) {
+        if constexpr (!WAIT) {
+            io4<T>::store_packed(rs, off + more, now);
+        } else if constexpr (kept_in_lds<T, ZOH, RAG, WAIT>()) {
             u32x4* const at = reinterpret_cast<u32x4*>(&sm.kept[decltype(which_tag)::value][tid]);
             const u32x4 x = *at;
             io4<T>::store_packed(rs, (odd ? BUF_OFF : keep_off) + more, make_uint4(x[0], x[1], x[2], x[3]));
@@ -1052,7 +1054,7 @@ __global__ void __launch_bounds__(THREADS, 2) scan_bwd_dpp_kernel(const BwdArgs 
             }
             store_block(bdu_, static_cast<T*>(a.du) + wg_first_i, off, i_off, nv, io4<T>::pack(du4), keep_du, std::integral_constant<int, 0>{}, odd, tail_tag);
             store_block(bdd_, static_cast<T*>(a.ddelta) + wg_first_i, off, i_off, nv, io4<T>::pack(dl4), keep_dl, std::integral_constant<int, 1>{}, odd, tail_tag);
-            if constexpr (!TAIL) keep_off = odd ? off : BUF_OFF;
+            if constexpr (!TAIL && WAIT) keep_off = odd ? off : BUF_OFF;
         }
     };
     // The first block's state goes out before its inputs, as in the loop, so that the way in is not the path with the fewest
@@ -1594,6 +1596,17 @@ static int launch_scan_bwd_complex(const BwdArgs& a, dim3 grid, hipStream_t stre
     return launch_bwd_rows<T, VEC, FULLN, false, 0, true, 2>(a, grid, stream);
 }
 
+template <typename T, int SPL, bool ZOH, bool RAG, bool WAIT>
+static int launch_bwd_dpp_main(const BwdArgs& a, dim3 grid, hipStream_t stream)
+{
+    auto kern = scan_bwd_dpp_kernel<T, SPL, ZOH, RAG, WAIT>;
+    static std::atomic<bool> lds_ok[MAX_DEVICES];   // this launcher is instantiated once per kernel
+    constexpr size_t lds = sizeof(bwd_smem_dpp<T, ZOH, RAG, WAIT>);
+    if (!allow_backward_lds_once(reinterpret_cast<const void*>(kern), lds_ok, lds)) return -1;
+    kern<<<dim3(grid.x, (unsigned)a.f.nseg), dim3(THREADS), lds, stream>>>(a);
+    return hipGetLastError() == hipSuccess ? 0 : -1;
+}
+
 // the common case (scan_bwd_dpp_kernel), with the adjoint aggregates of a split sequence first
 template <typename T, int SPL, bool ZOH, bool RAG>
 static int launch_bwd_dpp_t(const BwdArgs& a, dim3 grid, hipStream_t stream)
@@ -1603,12 +1616,8 @@ static int launch_bwd_dpp_t(const BwdArgs& a, dim3 grid, hipStream_t stream)
         const long n = (long)a.f.B * a.f.D * NPAD;
         if (a.f.nseg > CARRY_INLINE) carry_bwd_kernel<<<dim3((unsigned)((n + 255) / 256)), dim3(256), 0, stream>>>(a);
     }
-    auto kern = scan_bwd_dpp_kernel<T, SPL, ZOH, RAG>;
-    static std::atomic<bool> lds_ok[MAX_DEVICES];   // this launcher is instantiated once per kernel
-    constexpr size_t lds = sizeof(bwd_smem_dpp<T, ZOH, RAG>);
-    if (!allow_backward_lds_once(reinterpret_cast<const void*>(kern), lds_ok, lds)) return -1;
-    kern<<<dim3(grid.x, (unsigned)a.f.nseg), dim3(THREADS), lds, stream>>>(a);
-    return hipGetLastError() == hipSuccess ? 0 : -1;
+    if (sizeof(T) == 2 || a.f.wait_bwd) return launch_bwd_dpp_main<T, SPL, ZOH, RAG, true>(a, grid, stream);
+    return launch_bwd_dpp_main<T, SPL, ZOH, RAG, sizeof(T) == 2>(a, grid, stream);
 }
 template <typename T, bool RAG>
 static int launch_bwd_dpp(const BwdArgs& a, dim3 grid, hipStream_t stream)

@@ -61,7 +61,7 @@ typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));   // MFMA operand a
 // 309 + 139 -> 158 + 90 us (2048 steps: 137 + 86), backward 1632 + 385 -> 445 + 93 us (320 + 84); float32,
 // 4 x 1536 x 2047, all passes: 865 -> 512 us.
 template <typename T, bool VEC, bool FULLN, bool AGG, bool ZOH, int BCFIX = 0, bool CPLX = false, bool STAGED = false,
-          int FUSED_KS = 0, int SPL = STATES_PER_LANE, bool PAT = false, bool RAG = false, bool SHORT = false>
+          int FUSED_KS = 0, int SPL = STATES_PER_LANE, bool PAT = false, bool RAG = false, bool SHORT = false, bool WAIT = true>
 __global__ void __launch_bounds__(THREADS, PAT && AGG ? 4 : ((PAT && FUSED_KS <= 4) ? 2 : 1)) scan_fwd_kernel(const FwdArgs a)
 {
     static_assert(!PAT || (VEC && BCFIX == 0 && !CPLX && !STAGED), "PAT: vector path, real state, selective B and C");
@@ -324,8 +324,7 @@ __global__ void __launch_bounds__(THREADS, PAT && AGG ? 4 : ((PAT && FUSED_KS <=
     // chunks) is issued together: both chunks' inputs are requested in the odd chunk's phase A, tensor
     // by tensor, and the even chunk's results wait in registers for the odd chunk's.  A float chunk is a whole
     // line: its inputs are better requested one by one (8 x 2048 x 4096 forward 293 us, in pairs 306), its results
-    // wait all the same, for rows a large power of two apart (256 x 2^20, forward + backward 7800 -> 7670 us, the
-    // shorter rows within 0.5 %).
+    // wait where that pays (WAIT, see choose_waits).
     constexpr bool PAIR = PAT && sizeof(T) == 2;
     auto issue_pair = [&](int c0) {   // chunks c0 (slot 0) and c0 + 1 (slot 1)
       if constexpr (PAIR && RAG) {
@@ -662,7 +661,7 @@ __global__ void __launch_bounds__(THREADS, PAT && AGG ? 4 : ((PAT && FUSED_KS <=
                     for (int j = 0; j < SLICE; ++j) y8[j] *= z8[j] * sigmoid_fast(z8[j]);
                 }
                 pack_slice<pio, PC>(y8, po);
-                if (SLOT == 0 && c + 1 < c_end) {   // wait for the odd chunk
+                if (WAIT && SLOT == 0 && c + 1 < c_end) {   // for the odd chunk
 #pragma unroll
                     for (int p = 0; p < PC; ++p) { held_y[p] = py[p]; held_o[p] = po[p]; }
                 } else if constexpr (RAG) {
@@ -670,11 +669,16 @@ __global__ void __launch_bounds__(THREADS, PAT && AGG ? 4 : ((PAT && FUSED_KS <=
                         T* const yp = static_cast<T*>(a.ysave) + wg_first_i;
                         T* const op = static_cast<T*>(a.out) + wg_first;
                         const uint32_t yt = r_off_i + (uint32_t)t0 * esz, ot = r_off + (uint32_t)t0 * esz;
-                        if (SLOT == 1 && keep_y) pio::store_elem(yp, yt - CHUNK_T * esz, held_y[0], SLICE);
+                        if (WAIT && SLOT == 1 && keep_y) pio::store_elem(yp, yt - CHUNK_T * esz, held_y[0], SLICE);
                         if (keep_y) pio::store_elem(yp, yt, py[0], nv[0]);
-                        if (SLOT == 1) pio::store_elem(op, ot - CHUNK_T * esz, held_o[0], SLICE);
+                        if (WAIT && SLOT == 1) pio::store_elem(op, ot - CHUNK_T * esz, held_o[0], SLICE);
                         pio::store_elem(op, ot, po[0], nv[0]);
                     }
+                } else if constexpr (!WAIT) {
+#pragma unroll
+                    for (int p = 0; p < PC; ++p) pio::store_packed(by, off[p], py[p]);
+#pragma unroll
+                    for (int p = 0; p < PC; ++p) pio::store_packed(bo, off[p], po[p]);
                 } else {
 #pragma unroll
                     for (int p = 0; p < PC; ++p) pio::store_packed(by, off_e[p], held_y[p]);
@@ -1356,7 +1360,10 @@ static void launch_fwd_dpp_t(const FwdArgs& a, hipStream_t stream)
             return;
         }
     }
-    scan_fwd_kernel<T, true, false, false, ZOH, 0, false, false, 0, SPL, true, RAG><<<dim3((unsigned)(a.B * groups), (unsigned)a.nseg), block, 0, stream>>>(a);
+    if (sizeof(T) == 2 || a.wait_fwd)
+        scan_fwd_kernel<T, true, false, false, ZOH, 0, false, false, 0, SPL, true, RAG><<<dim3((unsigned)(a.B * groups), (unsigned)a.nseg), block, 0, stream>>>(a);
+    else
+        scan_fwd_kernel<T, true, false, false, ZOH, 0, false, false, 0, SPL, true, RAG, false, sizeof(T) == 2><<<dim3((unsigned)(a.B * groups), (unsigned)a.nseg), block, 0, stream>>>(a);
 }
 // Rows of whole 16-byte pieces take the kernel with buffer-addressed accesses, all others the one for any row length.
 // Fewer than 16 states dealt out to the waves: kernels built for 1 or 2 slots per lane.

@@ -61,6 +61,9 @@ struct FwdArgs {
     // Split of the sequence across workgroups (few rows, long L).  Segment s covers steps
     // [s*seg_len, min(L, (s+1)*seg_len)); seg_len is a multiple of 32.  nseg == 1: no split.
     int seg_len, nseg;
+    // float: whether the results of an even (forward) or odd (backward) chunk wait for its neighbour's so that
+    // both are written together (choose_waits); bf16 results always do
+    int wait_fwd, wait_bwd;
     float* seg_h;      // [nseg][B][D][16]: local end state of a segment, then its incoming state
     float* seg_sumdt;  // [nseg][B][D]: sum of the step sizes of a segment
 };
