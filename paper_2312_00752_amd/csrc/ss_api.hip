@@ -369,18 +369,18 @@ static bool pitch_ok(const ss_fwd_params* p, int pitch)
 // between the kernels: the rule, the dtype and, in bf16, the slots per lane (with fewer the four waves are done sooner, the
 // pointwise waves here are not).  Measured: 1 to 256 row groups x 32 to 16384 steps, on and off eight steps, N = 1, 4, 8, 16 and the
 // exact hold, forward alone and with the backward pass; profiles/whole_rows_line.txt has both sides of every point.  Where the line
-// sends a call whole that is faster in segments, that costs 2.5 % at most, float rows of up to four states 6 % (136 x 3072).
-// us, in segments / whole, forward alone.  Sent whole: 192 x 2048 N = 16 bf16 182 / 135, float 189 / 135, exact hold 304 / 234, N = 4 bf16
-// 112 / 95; 160 x 16384 bf16 1106 / 1029; float 160 x 8192 621 / 512.  Kept in segments: 128 x 2048 bf16 126 / 134, N = 4 160 x 16384
-// 664 / 729, 136 x 3072 134 / 147, N = 8 157 / 162; exact hold, float 80 x 320 34.3 / 40.6, bf16 1 x 192 23.4 / 24.9.  With the backward pass:
-// 192 x 2048 520 / 465, exact hold 819 / 751, 160 x 16384 3199 / 3076, N = 4 2170 / 2232, 128 x 2048 352 / 354, float 192 x 2048 560 / 491.
+// sends a call whole that is faster in segments, that costs 3 % at most, float rows of up to four states 4 % (136 x 3072).
+// us, in segments / whole, forward alone.  Sent whole: 192 x 2048 N = 16 bf16 181 / 133, float 186 / 130, exact hold 305 / 235, N = 4 bf16
+// 110 / 93; 160 x 16384 bf16 1110 / 1006; float 160 x 8192 598 / 497.  Kept in segments: 128 x 2048 bf16 127 / 132, N = 4 160 x 16384
+// 647 / 708, 136 x 3072 129 / 143, N = 8 155 / 158; exact hold, float 80 x 320 34.0 / 40.8, bf16 1 x 192 23.1 / 24.9.  With the backward pass:
+// 192 x 2048 518 / 464, exact hold 821 / 749, 160 x 16384 3171 / 3044, N = 4 2182 / 2215, 128 x 2048 350 / 350, float 192 x 2048 560 / 490.
 static bool runs_whole(const ss_fwd_params* p, const ss::FwdArgs& a)
 {
     const long wgs = (long)p->batch * ((p->dim + 63) / 64), L = p->seqlen;
     if (!a.dpp_ok || !stageable(p) || slots(p) > 16 || wgs > 256) return false;
     const int spl = ss::slots_for(a.N, a.il);
-    // not split: beside a second chunk always (256 x 64 9.3 / 7.9 us); a single one has nothing to run beside, which shows with one slot
-    // per lane (192 x 32 bf16 4.74 / 4.87, float 5.19 / 5.41; two slots bf16 5.27 / 5.14)
+    // not split: always (256 x 64 9.3 / 7.9 us), but for a single chunk, which has nothing to run beside, with one slot per lane
+    // (192 x 32 float 5.04 / 5.24, bf16 4.69 / 4.76; two slots bf16 5.26 / 5.12)
     if (a.nseg == 1) return spl > 1 || L > 32;
     double step = 0.48, fixed = 32.0;   // float
     if (p->flags & SS_EXACT_ZOH_B) {
